@@ -27,10 +27,20 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// wavefront-scope ordering of LDS traffic: one wavefront's LDS operations execute in order, so
+// this only keeps the compiler from moving accesses across the phases of a stage
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ uint32_t umax3(uint32_t a, uint32_t b, uint32_t c) {
     uint32_t m = a > b ? a : b;
     return m > c ? m : c;
 }
+
+__device__ __forceinline__ uint32_t umax2(uint32_t a, uint32_t b) { return a > b ? a : b; }
 
 // A value every lane of the wave holds, moved to a scalar register.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }

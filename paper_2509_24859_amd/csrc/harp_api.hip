@@ -167,9 +167,10 @@ size_t plan_bytes_on_path(const harp_tables *t, const harp_candidates *cd, bool 
     return prepass + size_t(units) * plan_generic_ws_per_group(t->dev.L, cd->S_max) + 256;
 }
 
-// Workgroups of the submesh planner: resident ones, fewer when their slices would pass 16 GiB.
-int n_mesh_groups(const harp_ctx *ctx, int C, size_t per_group, int threads) {
-    long long n = (long long)ctx->n_cu * (2048 / threads);         // as many wavefronts as a CU holds
+// Workgroups of the submesh planner: as many of 256 threads as are resident, fewer when their slices
+// would pass 16 GiB.
+int n_mesh_groups(const harp_ctx *ctx, int C, size_t per_group) {
+    long long n = (long long)ctx->n_cu * 8;
     const long long fit = (long long)((size_t(16) << 30) / (per_group ? per_group : 1));
     if (n > fit) n = fit;
     if (n > C) n = C;
@@ -537,8 +538,7 @@ int harp_plan_h1f1b_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *
 size_t harp_plan_mesh_workspace_bytes(harp_ctx *ctx, harp_tables *t, const harp_orderings *od) {
     if (check_orderings(ctx, t, od) != HARP_OK) return 0;
     const size_t per_group = plan_mesh_ws_per_group(t->dev.L, od->S_max, t->total_devices);
-    return 256 + size_t(n_mesh_groups(ctx, od->C, per_group,
-                                      plan_mesh_threads(t->dev.L, t->total_devices, od->C, ctx->n_cu))) * per_group;
+    return plan_mesh_ws_fixed(t->dev, od->S_max, od->C) + size_t(n_mesh_groups(ctx, od->C, per_group)) * per_group;
 }
 
 size_t harp_plan_mesh_sweep_workspace_bytes(harp_ctx *ctx, harp_tables *t, const harp_orderings *od) {
@@ -565,8 +565,8 @@ int plan_mesh_common(harp_ctx *ctx, harp_tables *t, const harp_orderings *od, co
     if (!mesh_index_fits(t)) return fail(ctx, HARP_ERR_SHAPE, "(devices + 1) x (L + 1) must stay below 2^31 for the kernels with a device index");
     const size_t per_group = plan_mesh_ws_per_group(t->dev.L, od->S_max, t->total_devices);
     const int threads = plan_mesh_threads(t->dev.L, t->total_devices, od->C, ctx->n_cu);
-    const int groups = n_mesh_groups(ctx, od->C, per_group, threads);
-    const size_t need = 256 + size_t(groups) * per_group;
+    const int groups = n_mesh_groups(ctx, od->C, per_group);
+    const size_t need = plan_mesh_ws_fixed(t->dev, od->S_max, od->C) + size_t(groups) * per_group;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return fail(ctx, HARP_ERR_WORKSPACE, "workspace must be a 256-byte aligned device pointer");
     if (workspace_bytes < need)
@@ -576,7 +576,7 @@ int plan_mesh_common(harp_ctx *ctx, harp_tables *t, const harp_orderings *od, co
     const OrdDev o = { od->C, od->G_max, od->S_max, od->ord_S, od->ord_G, od->ord_group };
     const PlansDev pl = { out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
     launch_plan_mesh(t->dev, o, pl, stage_group, stage_tp, n_passes, exact, use_fast_rows(ctx, t), workspace, groups,
-                     threads, t->total_devices,
+                     threads, t->total_devices, ctx->n_cu,
                      static_cast<hipStream_t>(hip_stream));
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the submesh planner kernel");
@@ -609,8 +609,8 @@ int harp_plan_mesh_h1f1b_batch(harp_ctx *ctx, harp_tables *t, const harp_orderin
     if (!mesh_index_fits(t)) return fail(ctx, HARP_ERR_SHAPE, "(devices + 1) x (L + 1) must stay below 2^31 for the kernels with a device index");
     const size_t per_group = plan_mesh_ws_per_group(t->dev.L, od->S_max, t->total_devices);
     const int threads = plan_mesh_threads(t->dev.L, t->total_devices, od->C, ctx->n_cu);
-    const int groups = n_mesh_groups(ctx, od->C, per_group, threads);
-    const size_t need = 256 + size_t(groups) * per_group;
+    const int groups = n_mesh_groups(ctx, od->C, per_group);
+    const size_t need = plan_mesh_ws_fixed(t->dev, od->S_max, od->C) + size_t(groups) * per_group;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return fail(ctx, HARP_ERR_WORKSPACE, "workspace must be a 256-byte aligned device pointer");
     if (workspace_bytes < need)
@@ -620,7 +620,7 @@ int harp_plan_mesh_h1f1b_batch(harp_ctx *ctx, harp_tables *t, const harp_orderin
     const OrdDev o = { od->C, od->G_max, od->S_max, od->ord_S, od->ord_G, od->ord_group };
     const PlansDev pl = { out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
     launch_plan_mesh_h1f1b(t->dev, o, t_max, pl, stage_group, stage_tp, warmup, use_fast_rows(ctx, t), workspace, groups,
-                           threads, t->total_devices, static_cast<hipStream_t>(hip_stream));
+                           threads, t->total_devices, ctx->n_cu, static_cast<hipStream_t>(hip_stream));
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the submesh H-1F1B kernel");
     return HARP_OK;

@@ -87,6 +87,7 @@ void launch_plan_generic_exact(const TablesDev &tb, const CandDev &cd, const Pla
 size_t plan_generic_ws_per_group(int L, int S_max);
 void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &out, void *ws,
                       int n_slices, int n_cu, unsigned long long *work, hipStream_t st);
+void launch_plan_index(const TablesDev &tb, int S_max, uint16_t *index, hipStream_t st);
 void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n_groups, hipStream_t st);
 void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_max, const PlansDev &out,
                        int32_t *warmup, void *ws, int n_groups, int n_slices, int n_cu, hipStream_t st);
@@ -103,10 +104,10 @@ struct OrdDev {
 constexpr int kMaxOrderGroups = 1024;   // groups one ordering may list (their offsets sit in LDS)
 void launch_plan_mesh(const TablesDev &tb, const OrdDev &od, const PlansDev &out, int32_t *stage_group,
                       int32_t *stage_tp, int32_t *n_passes, bool exact, bool fast32, void *ws, int n_groups,
-                      int threads, int64_t total_devices, hipStream_t st);
+                      int threads, int64_t total_devices, int n_cu, hipStream_t st);
 void launch_plan_mesh_h1f1b(const TablesDev &tb, const OrdDev &od, const int64_t *t_max, const PlansDev &out,
                             int32_t *stage_group, int32_t *stage_tp, int32_t *warmup, bool fast32, void *ws,
-                            int n_groups, int threads, int64_t total_devices, hipStream_t st);
+                            int n_groups, int threads, int64_t total_devices, int n_cu, hipStream_t st);
 void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const int32_t *cand_group,
                                   const int32_t *cand_tp, int max_caps, const PlansDev &out,
                                   int32_t *stage_group, int32_t *stage_tp, int32_t *warmup, int64_t *t_max_out,
@@ -114,6 +115,7 @@ void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const i
                                   int W, int64_t total_devices, hipStream_t st);
 size_t plan_mesh_sweep_slot_bytes(int S_max);
 size_t plan_mesh_ws_per_group(int L, int S_max, int64_t total_devices);
+size_t plan_mesh_ws_fixed(const TablesDev &tb, int S_max, int C);
 int plan_mesh_threads(int L, int64_t total_devices, int C, int n_cu);
 size_t plan_fast_ws_bytes(const TablesDev &tb, int S_max, int C, int n_slices);
 void launch_clear_work(unsigned long long *work, hipStream_t st);

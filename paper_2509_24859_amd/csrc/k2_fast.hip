@@ -269,14 +269,6 @@ constexpr int kArgEscape = 255;         // one-byte back-pointer: distance too l
 constexpr uint32_t kArgBias = 1u << 16;     // keeps (stage offset - lowest cut of the row) positive
 constexpr uint32_t kArgInLds = 1u << 31;    // flag on that word: the stage's back-pointers are in the LDS arena
 
-// wavefront-scope ordering of LDS traffic: one wavefront's LDS operations execute in order, so
-// this only keeps the compiler from moving accesses across the phases of a stage
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ uint32_t umin2(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
 struct FastArgs {
@@ -752,6 +744,14 @@ int plan_fast_groups(int L, int S_max, int n_cu) {
     return per_cu * n_cu;
 }
 
+// The feasibility index for stages of at most S_max-stage pipelines: lower limits, then upper limits.
+void launch_plan_index(const TablesDev &tb, int S_max, uint16_t *index, hipStream_t st) {
+    const long long rows = (long long)lo_n_max(tb.L, S_max, tb.M) * tb.T * tb.n_tp;
+    const int pitch = int(lo_pitch(tb.L));
+    hipLaunchKernelGGL(k2_index, dim3(unsigned(rows < 65536 ? rows : 65536)), dim3(256), size_t(tb.L + 1) * 8, st, tb,
+                       index, index + rows * pitch, pitch, int(rows));
+}
+
 // Pre-pass shared by every 32-bit planner entry point: clears the counters, checks the slot lists,
 // computes the reachability bands, compacts the live and dead lists, and writes the feasibility
 // index.
@@ -760,9 +760,7 @@ void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n
     hipLaunchKernelGGL(k2_clear_count, dim3(1), dim3(64), 0, st, w.counts);
     const long long idx_rows = (long long)lo_n_max(tb.L, cd.S_max, tb.M) * tb.T * tb.n_tp;
     const int idx_pitch = int(lo_pitch(tb.L));
-    hipLaunchKernelGGL(k2_index, dim3(unsigned(idx_rows < 65536 ? idx_rows : 65536)), dim3(256),
-                       size_t(tb.L + 1) * 8, st, tb, w.lo_tab, w.lo_tab + idx_rows * idx_pitch, idx_pitch,
-                       int(idx_rows));
+    launch_plan_index(tb, cd.S_max, w.lo_tab, st);
     const int types_in_lds = tb.G <= kBandTypeTable ? 1 : 0;
     const int bt = band_threads(cd.S_max);
     const size_t band_lds = size_t(cd.S_max + 1) * (bt + 2) * 2 * 2 + (types_in_lds ? size_t(tb.G) * 8 : 0);

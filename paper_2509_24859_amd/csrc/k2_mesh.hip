@@ -10,34 +10,44 @@
 //   D[s+1][i][d + tp] = min over (j, tp) of max(D[s][j][d], time, comm),
 // ties resolved by the lowest previous cut j, then the smallest degree.
 //
-// Mapping: one workgroup per ordering at a time (drawn from a shared counter); within a stage one
-// lane per target cell (i, d'), the cells of a wave on consecutive i of one d' so that reads of the
-// previous row and of the table rows are contiguous.  For every degree the lane scans the previous
-// cuts downwards and stops once the stage time alone exceeds the best value found (the stage time
-// never decreases as j moves down) or the stage no longer fits in memory (monotone as well); the
-// stop is strict and the update accepts equal values at a lower j, which keeps the lowest j.  The
-// three-index table does not fit in LDS (L x devices entries per stage): the two live rows and the
-// back-pointers sit in a per-workgroup slice of the caller's workspace, L2-resident at the sizes
-// of interest.  Two forms of every pass: one on the int64 rows (any degrees, any time width, values
-// int64), and one on the fused 32-bit rows and the cut table for tables that have them
-// (mesh_pass_fast, mesh_h1_pass_fast in mesh_passes.h), chosen per launch.
+// Two forms.  k2_mesh_band and k2_mesh_band_h1f1b run on the fused 32-bit rows, on the ranges of cuts
+// that some plan under the bottleneck (or cap) in question can have (mesh_band.h); k2_mesh and
+// k2_mesh_h1f1b fill the whole table in int64 (any degrees, any time width), one lane per target
+// cell (i, d'), rows and back-pointers in the workspace.  The int64 form serves tables without 32-bit
+// rows, more than 1,024 operators or 2,048 devices, and the orderings the band form hands over because
+// their sets of time rows do not fit its LDS or their sums could reach 2^31.
+#include "mesh_band.h"
 #include "mesh_passes.h"
 
 namespace harp {
 
 using namespace meshdp;
+using meshband::Band;
+using meshband::BandShape;
 
 namespace {
+
+// Orderings a kernel works on: all of the batch, or those a band kernel handed over.
+struct MeshItems {
+    int *ticket;
+    const int *list;         // null: all
+    const int *n_list;
+};
+__device__ __forceinline__ int next_item(const MeshItems &it, int C) {
+    const int n = atomicAdd(it.ticket, 1);
+    if (!it.list) return n < C ? n : -1;
+    return n < *it.n_list ? it.list[n] : -1;
+}
 
 // kExact = false: the min-max plan of every ordering.  kExact = true: the optimum of the
 // iteration-time model (section 5.2.2) over every slicing and partition: the capped least-sum
 // table is walked over the caps exactly as the exact search of the hot path walks them (first at
 // t_S, then down from ceil(T / B), skipping caps that the sums rule out; equal totals keep the lower
 // cap), which returns what the increasing sweep over every distinct stage cost returns.
-template <bool kExact, bool kFast>
+template <bool kExact>
 __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od, const PlansDev &out,
                                           int32_t *stage_group, int32_t *stage_tp, int32_t *n_passes,
-                                          unsigned char *ws, size_t per_group, int64_t n_dev, int *ticket) {
+                                          unsigned char *ws, size_t per_group, int64_t n_dev, const MeshItems &items) {
     __shared__ int32_t offs[kMaxOrderGroups + 1];     // O_0 .. O_K
     __shared__ uint16_t order[kMaxOrderGroups];      // group ids are below 4096
     __shared__ uint16_t group_at[kMeshGroupTable];    // group index (in the order) of every device offset
@@ -54,7 +64,7 @@ __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od,
 
     // all threads: thread 0 backtracks into cuts/slot_*, the first wave scores them
     auto backtrack_and_score = [&](int K, int S, int64_t &bott, int64_t &total) {
-        if (tid == 0) mesh_backtrack<kFast>(tb, m, offs, order, K, S, n_dev, cuts, slot_g, slot_k, slot_first);
+        if (tid == 0) mesh_backtrack<false>(tb, m, offs, order, K, S, n_dev, cuts, slot_g, slot_k, slot_first);
         __syncthreads();
         if (wave == 0) {
             int64_t b, t;
@@ -65,13 +75,8 @@ __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od,
         bott = scored[0];
         total = scored[1];
     };
-    // one pass over the stages, in the form the launch chose (the fast form keeps a row of memory sums in LDS)
-    extern __shared__ __align__(16) unsigned char mesh_lds[];
-    int64_t *Q = reinterpret_cast<int64_t *>(mesh_lds);
     auto run_pass = [&](auto capped, int K, int S, int64_t cap) -> int64_t {
-        constexpr bool kCapped = decltype(capped)::value;
-        if constexpr (kFast) return mesh_pass_fast<kCapped>(tb, m, offs, order, group_at, Q, K, S, n_dev, cap);
-        else return mesh_pass<kCapped>(tb, m, offs, order, group_at, K, S, n_dev, cap);
+        return mesh_pass<decltype(capped)::value>(tb, m, offs, order, group_at, K, S, n_dev, cap);
     };
     auto keep = [&](int S) {
         for (int s = tid; s <= S; s += nthreads) kept_cuts[s] = cuts[s];
@@ -82,10 +87,10 @@ __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od,
 
     for (;;) {
         __syncthreads();
-        if (tid == 0) shared_int[0] = atomicAdd(ticket, 1);
+        if (tid == 0) shared_int[0] = next_item(items, od.C);
         __syncthreads();
         const int c = shared_int[0];
-        if (c >= od.C) break;
+        if (c < 0) break;
         const int S = od.ord_S[c], K = od.ord_G[c];
         const int32_t *og = od.ord_group + int64_t(c) * od.G_max;
         int32_t *sg = stage_group + int64_t(c) * S_max, *stp = stage_tp + int64_t(c) * S_max;
@@ -170,24 +175,21 @@ __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od,
     }
 }
 
-template <bool kExact, bool kFast>
+template <bool kExact>
 __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh(TablesDev tb, OrdDev od, PlansDev out,
                                                            int32_t *stage_group, int32_t *stage_tp,
                                                            int32_t *n_passes, unsigned char *ws,
-                                                           size_t per_group, int64_t n_dev, int *ticket) {
-    mesh_body<kExact, kFast>(tb, od, out, stage_group, stage_tp, n_passes, ws, per_group, n_dev, ticket);
+                                                           size_t per_group, int64_t n_dev, MeshItems items) {
+    mesh_body<kExact>(tb, od, out, stage_group, stage_tp, n_passes, ws, per_group, n_dev, items);
 }
 
-template <bool kFast>
 __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &od, const int64_t *t_max,
                                              const PlansDev &out, int32_t *stage_group, int32_t *stage_tp,
                                              int32_t *warmup, unsigned char *ws, size_t per_group, int64_t n_dev,
-                                             int *ticket) {
+                                             const MeshItems &items) {
     __shared__ int32_t offs[kMaxOrderGroups + 1];
     __shared__ uint16_t order[kMaxOrderGroups];
     __shared__ uint16_t group_at[kMeshGroupTable];
-    extern __shared__ __align__(16) unsigned char mesh_lds[];      // fast form: PP and PS, L + 1 entries each
-    int64_t *sums_lds = reinterpret_cast<int64_t *>(mesh_lds);
     __shared__ int32_t cuts[kMaxStages + 1], count[kMaxStages];
     __shared__ uint16_t slot_g[kMaxStages];
     __shared__ uint8_t slot_k[kMaxStages];
@@ -200,10 +202,10 @@ __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &
 
     for (;;) {
         __syncthreads();
-        if (tid == 0) shared_int[0] = atomicAdd(ticket, 1);
+        if (tid == 0) shared_int[0] = next_item(items, od.C);
         __syncthreads();
         const int c = shared_int[0];
-        if (c >= od.C) break;
+        if (c < 0) break;
         const int S = od.ord_S[c], K = od.ord_G[c];
         const int64_t cap = t_max[c];
         const int32_t *og = od.ord_group + int64_t(c) * od.G_max;
@@ -236,11 +238,9 @@ __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &
             for (int k = 0; k < K; ++k)
                 for (int d = offs[k] + tid; d < offs[k + 1]; d += nthreads) group_at[d] = uint16_t(k);
         }
-        int64_t sum;
-        if constexpr (kFast) sum = mesh_h1_pass_fast(tb, m, offs, order, group_at, sums_lds, K, S, n_dev, cap);
-        else sum = mesh_h1_pass(tb, m, offs, order, group_at, K, S, n_dev, cap);
+        const int64_t sum = mesh_h1_pass(tb, m, offs, order, group_at, K, S, n_dev, cap);
         if (sum == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
-        if (tid == 0) mesh_h1_backtrack<kFast>(tb, m, offs, order, K, S, n_dev, cap, cuts, slot_g, slot_k, slot_first, count);
+        if (tid == 0) mesh_h1_backtrack<false>(tb, m, offs, order, K, S, n_dev, cap, cuts, slot_g, slot_k, slot_first, count);
         __syncthreads();
         int32_t *sp = out.splits + int64_t(c) * (S_max + 1);
         int32_t *df = out.dev_first + int64_t(c) * S_max;
@@ -263,23 +263,277 @@ __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &
     }
 }
 
-template <bool kFast>
 __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh_h1f1b(TablesDev tb, OrdDev od, const int64_t *t_max,
                                                                  PlansDev out, int32_t *stage_group,
                                                                  int32_t *stage_tp, int32_t *warmup,
                                                                  unsigned char *ws, size_t per_group,
-                                                                 int64_t n_dev, int *ticket) {
-    mesh_h1_body<kFast>(tb, od, t_max, out, stage_group, stage_tp, warmup, ws, per_group, n_dev, ticket);
+                                                                 int64_t n_dev, MeshItems items) {
+    mesh_h1_body(tb, od, t_max, out, stage_group, stage_tp, warmup, ws, per_group, n_dev, items);
 }
 
-__global__ void k2_mesh_clear(int *ticket) {
-    if (threadIdx.x < 4) ticket[threadIdx.x] = 0;
+// ------------------------------------------------------------------------------------ band form
+
+// What the band kernels share: the launch's LDS shape, the feasibility index, slices, and counters
+// [0] ticket, [1] orderings handed over, [2] ticket of the int64 kernel that takes those.
+struct BandArgs {
+    BandShape sh;
+    const uint16_t *lo_tab, *hi_tab;
+    unsigned char *slices;
+    size_t per_group;
+    int *counters;
+    int *redo;
+};
+
+// Outputs of an ordering whose plan is in the band's cuts / slot_*.
+__device__ __forceinline__ void write_slots(const TablesDev &tb, const PlansDev &out, const Band &b, int c, int S_max,
+                                            int32_t *sg, int32_t *stp) {
+    int32_t *sp = out.splits + int64_t(c) * (S_max + 1), *df = out.dev_first + int64_t(c) * S_max;
+    const int tid = Band::thread_id();
+    for (int s = tid; s <= S_max; s += b.nthreads) sp[s] = s <= b.S ? b.cuts[s] : -1;
+    for (int s = tid; s < S_max; s += b.nthreads) {
+        sg[s] = s < b.S ? int32_t(b.slot_g[s]) : -1;
+        stp[s] = s < b.S ? tb.tp[b.slot_k[s]] : -1;
+        df[s] = s < b.S ? b.slot_first[s] : -1;
+    }
+}
+
+// Bound by vector issue and by the latency of its serial parts (chains, plan recovery: one wavefront of a
+// workgroup).  Measured against the whole-table form on 32-bit rows it replaces: 4,096 orderings of 82
+// operators and 64 devices 3.57 -> 0.95 ms; exact form, 256 orderings of 160 operators and 128 devices,
+// 15-19 -> 3.4 ms (of an ordering's time there: finding t_S 4%, ranges of the caps 14%, value passes 68%).
+// The exact form walks the caps as k2_mesh does: first at t_S, then down from ceil(T / B).  A plan that
+// is not kept costs nothing but its score: the outputs are written whenever a better one is found.
+template <bool kExact>
+__global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, PlansDev out, int32_t *stage_group,
+                                                    int32_t *stage_tp, int32_t *n_passes, BandArgs ba) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ int64_t scored[2];
+    __shared__ int item;
+    Band b(tb, ba.sh, lds_raw, ba.lo_tab, ba.hi_tab,
+           meshband::band_slice(ba.slices + size_t(blockIdx.x) * ba.per_group, ba.sh));
+    const int S_max = od.S_max, tid = threadIdx.x;
+    const int64_t m_cap = tb.M;
+    b.find_least_cut();
+    auto score = [&](int64_t &bott, int64_t &total) {
+        if (b.wave == 0) {
+            int64_t x, y;
+            wave_score_partition(tb, b.S, b.slot_g, b.slot_k, b.cuts, tid & 63, x, y);
+            if ((tid & 63) == 0) { scored[0] = x; scored[1] = y; }
+        }
+        __syncthreads();
+        bott = scored[0];
+        total = scored[1];
+    };
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) item = atomicAdd(&ba.counters[0], 1);
+        __syncthreads();
+        const int c = item;
+        if (c >= od.C) break;
+        int32_t *sg = stage_group + int64_t(c) * S_max, *stp = stage_tp + int64_t(c) * S_max;
+        auto fail = [&](int status) {
+            write_failed(out, c, S_max, status);
+            for (int s = tid; s < S_max; s += b.nthreads) { sg[s] = -1; stp[s] = -1; }
+            if (tid == 0 && n_passes) n_passes[c] = 0;
+        };
+        const int verdict = b.load(od.ord_S[c], od.ord_G[c], od.ord_group + int64_t(c) * od.G_max, S_max, od.G_max);
+        if (verdict == 1) { fail(HARP_CAND_INVALID); continue; }
+        if (verdict == 2) { fail(HARP_CAND_INFEASIBLE); continue; }
+        auto hand_over = [&]() { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c; };
+        if (verdict == 3) { hand_over(); continue; }
+        if (b.min_max() == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
+        int64_t t_S, best_T;
+        score(t_S, best_T);
+        if (kExact && b.S >= 2 && !b.sums_fit((best_T + m_cap - 1) / m_cap)) { hand_over(); continue; }
+        write_slots(tb, out, b, c, S_max, sg, stp);
+        int64_t best_b = t_S;
+        int passes = 0;
+        if (kExact) {
+            int64_t cap = t_S;
+            while (b.S >= 2) {
+                if (!b.prepare(uint32_t(cap))) break;             // cannot happen at or above t_S
+                const int64_t sum = b.template value_pass<true>(uint32_t(cap));
+                if (sum == kInf) break;
+                b.template find_plan<true>(uint32_t(sum), uint32_t(cap));
+                int64_t bn, T;
+                score(bn, T);
+                ++passes;
+                if (T < best_T || (T == best_T && bn <= best_b)) {   // equal totals: the lower cap; equal caps: the capped plan
+                    best_T = T;
+                    best_b = bn;
+                    write_slots(tb, out, b, c, S_max, sg, stp);
+                }
+                if (passes >= (1 << 20) || bn > cap) break;          // cannot happen: the cap falls with every pass
+                int64_t next_cap;
+                if (passes == 1) {
+                    next_cap = (best_T + m_cap - 1) / m_cap;
+                } else {
+                    next_cap = bn - 1;
+                    if (m_cap > 1) {
+                        const int64_t bound = (best_T - sum) / (m_cap - 1);
+                        next_cap = next_cap < bound ? next_cap : bound;
+                    }
+                }
+                if (next_cap <= t_S) break;
+                cap = next_cap;
+            }
+        }
+        if (tid == 0) {
+            out.bottleneck[c] = best_b;
+            out.iter_time[c] = best_T;
+            out.status[c] = HARP_CAND_OK;
+            if (n_passes) n_passes[c] = passes;
+        }
+    }
+}
+
+__global__ __launch_bounds__(1024) void k2_mesh_band_h1f1b(TablesDev tb, OrdDev od, const int64_t *t_max, PlansDev out,
+                                                          int32_t *stage_group, int32_t *stage_tp, int32_t *warmup,
+                                                          BandArgs ba) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ int item;
+    Band b(tb, ba.sh, lds_raw, ba.lo_tab, ba.hi_tab,
+           meshband::band_slice(ba.slices + size_t(blockIdx.x) * ba.per_group, ba.sh));
+    const int S_max = od.S_max, tid = threadIdx.x;
+    b.load_memory_sums();
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) item = atomicAdd(&ba.counters[0], 1);
+        __syncthreads();
+        const int c = item;
+        if (c >= od.C) break;
+        const int64_t cap = t_max[c];
+        int32_t *sg = stage_group + int64_t(c) * S_max, *stp = stage_tp + int64_t(c) * S_max;
+        int32_t *wu = warmup + int64_t(c) * S_max;
+        auto fail = [&](int status) {
+            write_failed(out, c, S_max, status);
+            for (int s = tid; s < S_max; s += b.nthreads) { sg[s] = -1; stp[s] = -1; wu[s] = -1; }
+        };
+        const int verdict = b.load(od.ord_S[c], od.ord_G[c], od.ord_group + int64_t(c) * od.G_max, S_max, od.G_max);
+        if (verdict == 1 || cap_out_of_range(tb, cap)) { fail(HARP_CAND_INVALID); continue; }
+        if (verdict == 2 || cap < 0) { fail(HARP_CAND_INFEASIBLE); continue; }
+        if (verdict == 3 || !b.sums_fit(cap)) {
+            if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c;
+            continue;
+        }
+        const int64_t sum = b.prepare(uint32_t(cap)) ? b.h1_pass(uint32_t(cap)) : kInf;
+        if (sum == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
+        b.find_h1_plan(uint32_t(cap));
+        write_slots(tb, out, b, c, S_max, sg, stp);
+        for (int s = tid; s < S_max; s += b.nthreads) wu[s] = s < b.S ? b.warmup[s] : -1;
+        if (b.wave == 0) {
+            int64_t bott, iter;
+            wave_score_partition(tb, b.S, b.slot_g, b.slot_k, b.cuts, tid & 63, bott, iter);   // the plan's own bottleneck
+            if ((tid & 63) == 0) {
+                out.bottleneck[c] = bott;
+                out.iter_time[c] = sum + (int64_t(tb.M) - 1) * cap;
+                out.status[c] = HARP_CAND_OK;
+            }
+        }
+    }
+}
+
+__global__ void k2_mesh_clear(int *counters) {
+    if (threadIdx.x < 8) counters[threadIdx.x] = 0;
+}
+
+// Workspace: counters | orderings handed over [C] | feasibility index | slices.
+struct MeshWorkspace {
+    int *counters, *redo;
+    uint16_t *index;
+    unsigned char *slices;
+    size_t before_slices;
+};
+MeshWorkspace mesh_carve(void *ws, int C, size_t index_bytes) {
+    auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
+    unsigned char *p = static_cast<unsigned char *>(ws);
+    MeshWorkspace w;
+    size_t off = 0;
+    w.counters = reinterpret_cast<int *>(p); off += 256;
+    w.redo = reinterpret_cast<int *>(p + off); off += up(size_t(C) * sizeof(int));
+    w.index = reinterpret_cast<uint16_t *>(p + off); off += up(index_bytes);
+    w.slices = p + off;
+    w.before_slices = off;
+    return w;
+}
+
+size_t mesh_index_bytes(const TablesDev &tb, int S_max) {
+    if (tb.L > kFastRowsMaxL) return 0;
+    const size_t n = fastdp::lo_table_bytes(tb.L, S_max, tb.M, tb.T, tb.n_tp);
+    return n <= kFastIndexLimit ? n : 0;
 }
 
 }  // namespace
 
-// A stage has up to L x devices target cells: small tables get many small workgroups (more
-// orderings in flight), large ones few large workgroups (more lanes per ordering).
+// LDS of a band workgroup: `budget` bytes, more when the time rows need it; false when they do not fit
+// the CU.
+bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t total_devices, int threads, int form,
+                          size_t budget, BandShape &sh) {
+    if (total_devices > kMaxDevices) return false;
+    sh.W = tb.L + 1;
+    sh.NW = (sh.W + 63) / 64;
+    sh.cols = int(total_devices) + 1;
+    sh.K_cap = G_max < tb.G ? G_max : tb.G;
+    sh.teams = threads > 64 ? 2 : 1;
+    sh.S_cap = S_max < tb.L ? S_max : tb.L;
+    sh.idx_pitch = int(fastdp::lo_pitch(tb.L));
+    size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t at = off; off = (off + bytes + 15) & ~size_t(15); return uint32_t(at); };
+    sh.o_offs = take(size_t(sh.K_cap + 1) * 4);
+    sh.o_order = take(size_t(sh.K_cap) * 2);
+    sh.o_type = take(size_t(sh.K_cap) * 2);
+    sh.o_row_at = take(size_t(sh.K_cap) * 16);
+    sh.o_cut_at = take(size_t(sh.cols) * 4);
+    sh.o_group_at = take(size_t(sh.cols) * 2);
+    sh.o_mem = take(form == kFormH1 ? size_t(sh.W) * 16 : 0);
+    sh.o_chain = take(size_t(sh.teams) * sh.cols * 2);
+    sh.o_ok = take(size_t(sh.teams) * 2 * sh.K_cap * sh.NW * 8);
+    sh.o_col = take(size_t(sh.cols) * 24);
+    sh.o_small = take(32 + size_t(sh.S_cap + 1) * 12 + size_t(sh.S_cap) * 11);
+    // time rows: of every group when they fit half the budget, else of as many sets as do, at least one per type
+    // (a set: its time rows and its two reach tables)
+    const size_t per_set = size_t(tb.n_tp) * sh.W * 8;
+    size_t sets = budget / 2 / per_set;
+    const size_t least = size_t(tb.T < sh.K_cap ? tb.T : sh.K_cap);
+    sets = sets < least ? least : sets;
+    sh.set_cap = int(sets < size_t(sh.K_cap) ? sets : size_t(sh.K_cap));
+    sh.o_prow = take(size_t(sh.set_cap) * per_set / 2 + 16);
+    sh.o_reach = take(size_t(sh.set_cap) * per_set / 2);
+    // bytes per cell: two value rows; or one and the key rows; or two rows of sums and counts; and the map
+    const size_t value_rows = form == kFormSum && tb.n_tp > 1 ? 1 + size_t(tb.n_tp) : 2;
+    const size_t per_cell = value_rows * 4 + (form == kFormH1 ? 4 : 0) + 2, lds_cu = size_t(160) << 10;
+    size_t room = budget > off ? budget - off : 0;
+    const size_t want = size_t(sh.K_cap) > 1024 ? size_t(sh.K_cap) : 1024;        // the map also numbers the sets
+    if (room < want * per_cell + 128) room = want * per_cell + 128;
+    if (off + room > lds_cu) return false;
+    size_t cells = (room - 128) / per_cell;
+    const size_t all = size_t(sh.cols) * sh.W;
+    cells = cells > all && all >= want ? all : cells;
+    sh.row_cap = int(cells & ~size_t(7));
+    const size_t row = size_t(sh.row_cap) + kRowPad;
+    sh.o_rows = take((value_rows > 2 ? value_rows : 2) * row * 4);
+    sh.o_count = take(form == kFormH1 ? 2 * row * 2 : 0);
+    sh.o_map = take(size_t(sh.row_cap) * 2);
+    sh.total = uint32_t(off);
+    return off <= lds_cu;
+}
+
+namespace {
+
+// Workgroups of the band kernels: a batch of at most one ordering per CU gets the whole CU's LDS and
+// 1,024 threads each; beyond that two workgroups of 512 threads share a CU (the key rows of the exact form
+// and the rows of the H-1F1B form want the room), or four of 256 in the min-max form.
+bool band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int &threads,
+                 BandShape &sh) {
+    threads = od.C <= n_cu ? 1024 : (form != meshband::kFormMinMax || od.C <= 2 * n_cu) ? 512 : 256;
+    const size_t budget = threads == 1024 ? (size_t(156) << 10) : threads == 512 ? (size_t(79) << 10) : (size_t(39) << 10);
+    return meshband::band_shape(tb, od.S_max, od.G_max, total_devices, threads, form, budget, sh);
+}
+
+}  // namespace
+
+// Threads of an int64 workgroup: a stage has up to L x devices target cells, so small tables get many
+// small workgroups (more orderings in flight), large ones few large workgroups (more lanes per ordering).
 int plan_mesh_threads(int L, int64_t total_devices, int C, int n_cu) {
     if (int64_t(L + 1) * (total_devices + 1) >= 16384) return kMeshMaxThreads;
     // a batch too small to fill the chip with 256-thread workgroups gets more lanes per ordering
@@ -288,50 +542,84 @@ int plan_mesh_threads(int L, int64_t total_devices, int C, int n_cu) {
     return 256;
 }
 
-// Per-workgroup slice: two rows of the table, the back-pointers, and (first slice only) the ticket.
+// Per-workgroup slice: two rows of the table, the back-pointers; or the ranges and value rows of the band form.
 size_t plan_mesh_ws_per_group(int L, int S_max, int64_t total_devices) {
     const size_t row = size_t(total_devices + 1) * size_t(L + 1);
     size_t b = 2 * row * sizeof(int64_t) + 2 * row * sizeof(int32_t) + size_t(S_max) * row * sizeof(uint32_t);
+    const size_t band = meshband::band_slice_bytes(L, S_max, total_devices);
+    b = b > band ? b : band;
     return (b + 255) & ~size_t(255);
 }
 
+size_t plan_mesh_ws_fixed(const TablesDev &tb, int S_max, int C) {
+    return mesh_carve(nullptr, C, mesh_index_bytes(tb, S_max)).before_slices;
+}
+
+namespace {
+
+// The band launch of a batch and, behind it, the int64 launch over what it handed over.  band(sh, ...)
+// and wide(items, ...) launch the two kernels.
+template <typename BandFn, typename WideFn>
+void mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int form, void *ws, int n_groups, int threads,
+                 int64_t total_devices, int n_cu, hipStream_t st, BandFn band, WideFn wide) {
+    const size_t index_bytes = mesh_index_bytes(tb, od.S_max);
+    const MeshWorkspace w = mesh_carve(ws, od.C, index_bytes);
+    const size_t per_group = plan_mesh_ws_per_group(tb.L, od.S_max, total_devices);
+    hipLaunchKernelGGL(k2_mesh_clear, dim3(1), dim3(64), 0, st, w.counters);
+    BandArgs ba;
+    int band_threads = 0;
+    if (fast32 && index_bytes != 0 && band_launch(tb, od, total_devices, form, n_cu, band_threads, ba.sh)) {
+        launch_plan_index(tb, od.S_max, w.index, st);
+        ba.lo_tab = w.index;
+        ba.hi_tab = w.index + index_bytes / 4;
+        ba.slices = w.slices;
+        ba.per_group = per_group;
+        ba.counters = w.counters;
+        ba.redo = w.redo;
+        band(dim3(n_groups), dim3(band_threads), size_t(ba.sh.total), ba);
+        wide(dim3(n_groups < n_cu ? n_groups : n_cu), dim3(threads), MeshItems{w.counters + 2, w.redo, w.counters + 1},
+             w.slices, per_group);
+    } else {
+        wide(dim3(n_groups), dim3(threads), MeshItems{w.counters, nullptr, nullptr}, w.slices, per_group);
+    }
+}
+
+}  // namespace
+
 void launch_plan_mesh(const TablesDev &tb, const OrdDev &od, const PlansDev &out, int32_t *stage_group,
                       int32_t *stage_tp, int32_t *n_passes, bool exact, bool fast32, void *ws, int n_groups,
-                      int threads, int64_t total_devices, hipStream_t st) {
-    // layout: 256 bytes for the ticket, then the slices
-    int *ticket = static_cast<int *>(ws);
-    unsigned char *slices = static_cast<unsigned char *>(ws) + 256;
-    const size_t per_group = plan_mesh_ws_per_group(tb.L, od.S_max, total_devices);
-    const dim3 grid(n_groups), block(threads);
-    fast32 = fast32 && tb.L <= kMeshFastMaxL;      // the fast form keeps L + 1 memory sums in LDS
-    const size_t lds = fast32 ? size_t(tb.L + 1) * sizeof(int64_t) : 0;
-    hipLaunchKernelGGL(k2_mesh_clear, dim3(1), dim3(64), 0, st, ticket);
-#define HARP_MESH_LAUNCH(E, F)                                                                            \
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_mesh<E, F>), grid, block, lds, st, tb, od, out, stage_group, stage_tp, \
-                       n_passes, slices, per_group, total_devices, ticket)
-    if (exact && fast32) HARP_MESH_LAUNCH(true, true);
-    else if (exact) HARP_MESH_LAUNCH(true, false);
-    else if (fast32) HARP_MESH_LAUNCH(false, true);
-    else HARP_MESH_LAUNCH(false, false);
-#undef HARP_MESH_LAUNCH
+                      int threads, int64_t total_devices, int n_cu, hipStream_t st) {
+    mesh_launch(tb, od, fast32, exact ? meshband::kFormSum : meshband::kFormMinMax, ws, n_groups, threads, total_devices, n_cu, st,
+                [&](dim3 grid, dim3 block, size_t lds, const BandArgs &ba) {
+                    if (exact)
+                        hipLaunchKernelGGL(k2_mesh_band<true>, grid, block, lds, st, tb, od, out, stage_group, stage_tp,
+                                           n_passes, ba);
+                    else
+                        hipLaunchKernelGGL(k2_mesh_band<false>, grid, block, lds, st, tb, od, out, stage_group, stage_tp,
+                                           n_passes, ba);
+                },
+                [&](dim3 grid, dim3 block, const MeshItems &items, unsigned char *slices, size_t per_group) {
+                    if (exact)
+                        hipLaunchKernelGGL(k2_mesh<true>, grid, block, 0, st, tb, od, out, stage_group, stage_tp,
+                                           n_passes, slices, per_group, total_devices, items);
+                    else
+                        hipLaunchKernelGGL(k2_mesh<false>, grid, block, 0, st, tb, od, out, stage_group, stage_tp,
+                                           n_passes, slices, per_group, total_devices, items);
+                });
 }
 
 void launch_plan_mesh_h1f1b(const TablesDev &tb, const OrdDev &od, const int64_t *t_max, const PlansDev &out,
                             int32_t *stage_group, int32_t *stage_tp, int32_t *warmup, bool fast32, void *ws,
-                            int n_groups, int threads, int64_t total_devices, hipStream_t st) {
-    int *ticket = static_cast<int *>(ws);
-    unsigned char *slices = static_cast<unsigned char *>(ws) + 256;
-    const size_t per_group = plan_mesh_ws_per_group(tb.L, od.S_max, total_devices);
-    const dim3 grid(n_groups), block(threads);
-    fast32 = fast32 && tb.L <= kMeshFastMaxL;      // the fast form keeps 2 (L + 1) running sums in LDS
-    const size_t lds = fast32 ? 2 * size_t(tb.L + 1) * sizeof(int64_t) : 0;
-    hipLaunchKernelGGL(k2_mesh_clear, dim3(1), dim3(64), 0, st, ticket);
-    if (fast32)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_mesh_h1f1b<true>), grid, block, lds, st, tb, od, t_max, out, stage_group,
-                           stage_tp, warmup, slices, per_group, total_devices, ticket);
-    else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_mesh_h1f1b<false>), grid, block, 0, st, tb, od, t_max, out,
-                           stage_group, stage_tp, warmup, slices, per_group, total_devices, ticket);
+                            int n_groups, int threads, int64_t total_devices, int n_cu, hipStream_t st) {
+    mesh_launch(tb, od, fast32, meshband::kFormH1, ws, n_groups, threads, total_devices, n_cu, st,
+                [&](dim3 grid, dim3 block, size_t lds, const BandArgs &ba) {
+                    hipLaunchKernelGGL(k2_mesh_band_h1f1b, grid, block, lds, st, tb, od, t_max, out, stage_group,
+                                       stage_tp, warmup, ba);
+                },
+                [&](dim3 grid, dim3 block, const MeshItems &items, unsigned char *slices, size_t per_group) {
+                    hipLaunchKernelGGL(k2_mesh_h1f1b, grid, block, 0, st, tb, od, t_max, out, stage_group, stage_tp,
+                                       warmup, slices, per_group, total_devices, items);
+                });
 }
 
 }  // namespace harp

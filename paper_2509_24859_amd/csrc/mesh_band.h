@@ -1,0 +1,1015 @@
+// Band-limited passes of the submesh planner on the 32-bit rows (paper section 5.2.3, eq. dp_general
+// with its device index).  Device functions called by all threads of a workgroup, one ordering of
+// device groups at a time; k2_mesh.hip drives them.
+//
+// The state is (s, i, d): s stages hold the first i operators and use exactly the first d devices of
+// the ordering.  Under a cap t on every stage and transfer time, and the memory constraint, the cuts
+// i that matter for a given (s, d) form a narrow range [B, F]:
+//   F[s+1][d'] = max over degrees q, d = d' - tp_q inside the group of d', of
+//                the highest cut that a stage started at F[s][d] reaches with time <= t, in memory,
+//                lowered to a cut whose transfer time is at most t;
+//   B[s][d]    = the same from the end: the lowest cut from which stage s reaches B[s+1][d + tp_q].
+// Both reaches never decrease with the cut they start from, so F bounds every cut some plan under t
+// can have after s stages on d devices, and B every cut from which one can be completed; cells
+// outside the range are on no plan under t.  Leaving them out changes no cell on such a plan: its
+// value, and the lowest previous cut that attains it, come from cells on plans under t as well.
+// For the capped (least-sum) and H-1F1B passes t is the cap (H-1F1B's counts are never below the
+// classic ones the ranges are worked out with).  For the min-max pass any t >= the optimum will do:
+// the smallest t at which F reaches (S, L, all devices) is found by a search over chains first (it
+// is the optimum itself on all problems looked at; when the pass finds no plan under it, t is
+// raised and the pass repeated).  On orderings of 82 operators and 64 devices the ranges hold between
+// 0.1% and 25% of the (i, d) cells, the wide ones where a slow link decides the bottleneck.
+//
+// A chain is worked by one wavefront, lanes over the columns d, so several values of t are tried at
+// once by the wavefronts of a workgroup.  A pass keeps two value rows in LDS (cells of a row packed
+// one column after the other), writes every row to the workgroup's slice of the workspace, and keeps
+// no back-pointers: the plan is found from the value rows, per stage one step for all degrees and
+// cuts at once.  That leaves a minimum per transition (a subtraction, a shift, a three-way maximum)
+// where back-pointers cost a 64-bit key.  Rows of the fused stage times sit in LDS, one set per
+// distinct (GPU type, own link) of the ordering; memory limits come from the feasibility index
+// (k2_index), one 16-bit load per cell and degree.
+#pragma once
+
+#include "fast_common.h"
+#include "harp_internal.h"
+#include "plan_common.h"
+
+namespace harp {
+namespace meshband {
+
+using fastdp::uniform;
+using fastdp::wave_sync;
+
+constexpr uint32_t kNoCut = 0xFFFFu;
+constexpr uint32_t kInfSum = 0x80000000u;        // least sums stay below this (sums_fit)
+constexpr uint32_t kTopCap = 0x7FFFFFFFu;        // no time on these tables is larger
+constexpr int kRowPad = 4;                       // a window of four entries may overrun a row
+
+// LDS layout of a launch (byte offsets into dynamic LDS) and its capacities.
+struct BandShape {
+    int W, NW;                   // cuts (L + 1), 64-bit words of a mask of cuts
+    int cols;                    // columns: devices + 1
+    int K_cap, set_cap, row_cap; // groups of an ordering, sets of time rows, cells of a value row in LDS
+    int teams;                   // chains worked at once, by one wavefront each: 2, or 1 in a one-wavefront workgroup
+    int S_cap;                   // min(S_max, L)
+    int idx_pitch;               // feasibility index
+    uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_prow, o_reach, o_mem, o_chain, o_ok, o_col, o_small, o_rows,
+        o_count, o_map, total;
+};
+
+constexpr int kMaxDevices = 2048;                // columns sit in LDS, 24 bytes each
+// forms of a launch: what the value rows hold
+constexpr int kFormMinMax = 0, kFormSum = 1, kFormH1 = 2;
+bool band_shape(const TablesDev &tb, int S_max, int G_max, int64_t total_devices, int threads, int form, size_t budget,
+                BandShape &sh);
+
+// Per workgroup, in the workspace slice: F, B [S_cap + 1][cols] uint16, first cell index less lowest
+// cut [S_cap + 1][cols] int32, value rows (uint32) or, H-1F1B, back-pointers (uint16).
+struct BandSlice {
+    uint16_t *F, *B;
+    int32_t *off;
+    uint32_t *hist;
+    uint32_t *spare_h;           // two rows of sums and two of counts, for H-1F1B rows that do not fit in LDS
+    uint16_t *spare_n;
+    int64_t row;                 // cells of a spare row
+};
+__device__ __forceinline__ BandSlice band_slice(unsigned char *mine, const BandShape &sh) {
+    BandSlice b;
+    const size_t n = size_t(sh.S_cap + 1) * sh.cols;
+    b.off = reinterpret_cast<int32_t *>(mine);
+    b.F = reinterpret_cast<uint16_t *>(b.off + n);
+    b.B = b.F + n;
+    b.row = int64_t(sh.cols) * sh.W + kRowPad;
+    b.spare_h = reinterpret_cast<uint32_t *>(mine + ((n * 8 + 255) & ~size_t(255)));
+    b.spare_n = reinterpret_cast<uint16_t *>(b.spare_h + 2 * b.row);
+    b.hist = b.spare_h + 3 * b.row;
+    return b;
+}
+inline size_t band_slice_bytes(int L, int S_max, int64_t total_devices) {
+    const size_t S_cap = size_t(S_max < L ? S_max : L), cols = size_t(total_devices + 1);
+    const size_t row = cols * size_t(L + 1) + kRowPad;
+    return (((S_cap + 1) * cols * 8 + 255) & ~size_t(255)) + (((S_cap + 4) * row * 4 + 255) & ~size_t(255));
+}
+
+struct Band {
+    const TablesDev &tb;
+    const BandShape &sh;
+    const uint16_t *lo_tab, *hi_tab;
+    BandSlice sl;
+    // LDS
+    int32_t *offs;               // [K + 1] first device offset of every group
+    uint16_t *order, *type, *group_at;
+    uint32_t *prow_at, *index_at;   // [K] first entry of a group's time rows (and reach rows), of its type's index rows
+    uint32_t *link_at;           // [2 K] first entry of a link's row in the cut table: K links inside groups, K - 1 to the next
+    uint32_t *cut_at;            // [cols] the same for the link behind a stage that ends at device d
+    uint32_t *prow;              // [sets][n_tp][W]
+    uint16_t *reach;             // [2][sets][n_tp][W] reach of a stage under a cap
+    int64_t *mem;                // PP [W], PS [W] (H-1F1B form)
+    uint16_t *chain;             // [teams][cols]
+    unsigned long long *ok;      // [teams][2 K][NW]
+    uint16_t *col_lo, *col_hi;   // [2][cols]
+    uint32_t *col_min;           // [2][cols] least value of a column (min-max form)
+    int32_t *col_off;            // [2][cols] index of a column's first cell less its lowest cut
+    int32_t *tot, *base;         // [S_cap + 1] cells of a row, first cell of a row in hist
+    int32_t *cuts;               // [S_cap + 1]
+    int32_t *slot_first;         // [S_cap]
+    int32_t *warmup;             // [S_cap] counts of the plan (H-1F1B form)
+    uint16_t *slot_g;            // [S_cap]
+    uint8_t *slot_k;             // [S_cap]
+    uint32_t *scal;              // [8]
+    uint32_t *rows;              // [2][row_cap + pad]
+    uint16_t *counts;            // [2][row_cap + pad] (H-1F1B form)
+    uint16_t *map;               // [row_cap] column of a cell
+    int nthreads, wave;
+    int K, S, D, L, n_sets;
+    int least_cut;               // the cut behind the operator of least output (operators but the last)
+    bool rows_fit;               // the value rows of the last prepared cap fit in LDS
+
+    __device__ __forceinline__ Band(const TablesDev &t, const BandShape &s, unsigned char *lds, const uint16_t *lo,
+                                    const uint16_t *hi, const BandSlice &slice)
+        : tb(t), sh(s), lo_tab(lo), hi_tab(hi), sl(slice) {
+        offs = reinterpret_cast<int32_t *>(lds + sh.o_offs);
+        order = reinterpret_cast<uint16_t *>(lds + sh.o_order);
+        type = reinterpret_cast<uint16_t *>(lds + sh.o_type);
+        prow_at = reinterpret_cast<uint32_t *>(lds + sh.o_row_at);
+        index_at = prow_at + sh.K_cap;
+        link_at = index_at + sh.K_cap;
+        cut_at = reinterpret_cast<uint32_t *>(lds + sh.o_cut_at);
+        group_at = reinterpret_cast<uint16_t *>(lds + sh.o_group_at);
+        prow = reinterpret_cast<uint32_t *>(lds + sh.o_prow);
+        reach = reinterpret_cast<uint16_t *>(lds + sh.o_reach);
+        mem = reinterpret_cast<int64_t *>(lds + sh.o_mem);
+        chain = reinterpret_cast<uint16_t *>(lds + sh.o_chain);
+        ok = reinterpret_cast<unsigned long long *>(lds + sh.o_ok);
+        col_off = reinterpret_cast<int32_t *>(lds + sh.o_col);
+        col_min = reinterpret_cast<uint32_t *>(col_off + 2 * sh.cols);
+        col_lo = reinterpret_cast<uint16_t *>(col_min + 2 * sh.cols);
+        col_hi = col_lo + 2 * sh.cols;
+        scal = reinterpret_cast<uint32_t *>(lds + sh.o_small);
+        tot = reinterpret_cast<int32_t *>(scal + 8);
+        base = tot + (sh.S_cap + 1);
+        cuts = base + (sh.S_cap + 1);
+        slot_first = cuts + (sh.S_cap + 1);
+        warmup = slot_first + sh.S_cap;
+        slot_g = reinterpret_cast<uint16_t *>(warmup + sh.S_cap);
+        slot_k = reinterpret_cast<uint8_t *>(slot_g + sh.S_cap);
+        rows = reinterpret_cast<uint32_t *>(lds + sh.o_rows);
+        counts = reinterpret_cast<uint16_t *>(lds + sh.o_count);
+        map = reinterpret_cast<uint16_t *>(lds + sh.o_map);
+        nthreads = blockDim.x; wave = uniform(int(threadIdx.x) >> 6);
+        L = tb.L;
+        K = S = D = n_sets = 0;
+        rows_fit = false;
+        least_cut = 1;
+    }
+
+    // The thread's index, new to the compiler at every use: what a phase derives from it (LDS addresses,
+    // mostly) must not be hoisted out of the phase and kept in registers through all the others.
+    static __device__ __forceinline__ int thread_id() {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return t;
+    }
+
+    // All threads, once per kernel: the cheapest cut of the sequence on any link.
+    __device__ __forceinline__ void find_least_cut() {
+        const int tid = thread_id();
+        const int lane = tid & 63;
+        unsigned long long key = ~0ull;
+        for (int i = 1 + tid; i < L; i += nthreads) {
+            const unsigned long long a = (unsigned long long)tb.act_bytes[i - 1];
+            if (a < key) key = a;
+        }
+#pragma unroll
+        for (int x = 32; x >= 1; x >>= 1) {
+            const unsigned long long o = __shfl_xor(key, x, 64);
+            key = o < key ? o : key;
+        }
+        unsigned long long *part = ok;                     // free until the first ordering
+        if (lane == 0) part[wave & 1] = ~0ull;
+        __syncthreads();
+        if (lane == 0) atomicMin(&part[0], key);
+        __syncthreads();
+        key = part[0];
+        if (tid == 0) scal[0] = 1;
+        __syncthreads();
+        for (int i = 1 + tid; i < L; i += nthreads)
+            if ((unsigned long long)tb.act_bytes[i - 1] == key) scal[0] = uint32_t(i);      // any of them
+        __syncthreads();
+        least_cut = int(scal[0]);
+        __syncthreads();
+    }
+
+    __device__ __forceinline__ int in_flight(int s) const { return (S - s) < tb.M ? (S - s) : tb.M; }
+    // feasibility index of a stage with n micro-batches in flight: entry of degree q of group k at
+    // index_n(n) + index_at[k] + q * idx_pitch (the index and the cut table have fewer than 2^28 entries)
+    __device__ __forceinline__ uint32_t index_n(int n) const {
+        return uint32_t(n - 1) * uint32_t(tb.T) * uint32_t(tb.n_tp) * uint32_t(sh.idx_pitch);
+    }
+    // link behind a stage that ends at device d (1 <= d < D) as a mask index
+    __device__ __forceinline__ int link_of(int d) const {
+        const int k = group_at[d - 1];
+        return d == offs[k + 1] && k + 1 < K ? K + k : k;
+    }
+
+    // The ordering og[0 .. K): groups in range, distinct; offsets; time rows.  Returns 0, or 1 when the
+    // ordering is malformed (bad), 2 when no plan can exist, 3 when it does not fit this launch's LDS.
+    __device__ __forceinline__ int load(int S_, int K_, const int32_t *og, int S_max, int G_max) {
+        const int tid = thread_id();
+        S = S_; K = K_;
+        // (more groups than the problem has cannot be distinct)
+        int bad = (S < 1 || S > S_max || K < 1 || K > G_max || K > sh.K_cap) ? 1 : 0;
+        if (!bad)
+            for (int k = tid; k < K; k += nthreads) {
+                const int g = og[k];
+                if (g < 0 || g >= tb.G) { bad = 1; continue; }
+                for (int q = 0; q < k; ++q)
+                    if (og[q] == g) bad = 1;
+                order[k] = uint16_t(g);
+                type[k] = uint16_t(tb.group_type[g]);
+            }
+        if (__syncthreads_or(bad)) return 1;
+        if (tid == 0) {
+            int64_t o = 0;
+            offs[0] = 0;
+            for (int k = 0; k < K; ++k) { o += tb.group_ndev[order[k]]; offs[k + 1] = int32_t(o); }
+        }
+        // the set of time rows of a group: that of the first group with its type and own link
+        for (int k = tid; k < K; k += nthreads) {
+            const int g = order[k];
+            const int64_t link = tb.bw[int64_t(g) * tb.G + g];
+            int q = 0;
+            while (q < k && !(type[q] == type[k] && tb.bw[int64_t(order[q]) * tb.G + order[q]] == link)) ++q;
+            map[k] = uint16_t(q);
+            index_at[k] = uint32_t(type[k]) * uint32_t(tb.n_tp) * uint32_t(sh.idx_pitch);
+            link_at[k] = uint32_t(g * tb.G + g) * uint32_t(tb.pitch32);
+            if (k + 1 < K) link_at[K + k] = uint32_t(g * tb.G + order[k + 1]) * uint32_t(tb.pitch32);
+        }
+        __syncthreads();
+        D = offs[K];
+        if (S > L || S < K || S > D) return 2;
+        n_sets = 0;
+        for (int k = 0; k < K; ++k) n_sets += map[k] == k ? 1 : 0;
+        if (n_sets > sh.set_cap) return 3;
+        for (int k = 0, set = 0; k < K; ++k) {
+            if (map[k] != k) continue;
+            const uint32_t *from = tb.P32 + int64_t(order[k]) * tb.n_tp * tb.pitch32;
+            uint32_t *to = prow + set * tb.n_tp * sh.W;
+            for (int q = 0; q < tb.n_tp; ++q)
+                for (int i = tid; i <= L; i += nthreads) to[q * sh.W + i] = from[int64_t(q) * tb.pitch32 + i];
+            ++set;
+        }
+        for (int k = 0; k < K; ++k)
+            for (int d = offs[k] + tid; d < offs[k + 1]; d += nthreads) group_at[d] = uint16_t(k);
+        // sets are numbered in the order of their first groups
+        for (int k = tid; k < K; k += nthreads) {
+            uint32_t set = 0;
+            for (int q = 0; q < map[k]; ++q) set += map[q] == q ? 1u : 0u;
+            prow_at[k] = set * uint32_t(tb.n_tp) * uint32_t(sh.W);
+        }
+        __syncthreads();
+        for (int d = 1 + tid; d < D; d += nthreads) cut_at[d] = link_at[link_of(d)];
+        __syncthreads();
+        return 0;
+    }
+    __device__ __forceinline__ const uint32_t *time_row(int k) const { return prow + prow_at[k]; }   // degree q at q * W
+    __device__ __forceinline__ uint16_t *reach_row(int side, int k) const {
+        return reach + side * sh.set_cap * tb.n_tp * sh.W + prow_at[k];
+    }
+    __device__ __forceinline__ unsigned long long *masks(int team) const { return ok + size_t(team) * 2 * sh.K_cap * sh.NW; }
+
+    // All threads: cuts whose transfer time is at most t[w], one mask per link, for n values of t at once
+    // (the cut tables come from L2: four words are requested before the first is used).
+    __device__ __forceinline__ void cut_masks(int n, uint32_t ta, uint32_t tb_) {
+        const int lane = thread_id() & 63;
+        const int words = (2 * K - 1) * sh.NW, step = nthreads >> 6;
+        unsigned long long *ma = masks(0), *mb = masks(n - 1);
+        for (int x0 = wave; x0 < words; x0 += 4 * step) {
+            uint32_t cut[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int x = x0 + u * step, l = x / sh.NW, i = (x - l * sh.NW) * 64 + lane;
+                cut[u] = 0xFFFFFFFFu;
+                if (x < words && i >= 1 && i <= L) cut[u] = tb.CM[link_at[l] + uint32_t(i)];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int x = x0 + u * step;
+                const unsigned long long a = __ballot(cut[u] <= ta), b = __ballot(cut[u] <= tb_);
+                if (x < words && lane == 0) {
+                    ma[x] = a;
+                    if (n > 1) mb[x] = b;
+                }
+            }
+        }
+    }
+    // All threads: how far a stage gets under t on every (set, degree).  Upwards: entry j = the highest cut
+    // i with time(j, i) <= t; downwards: entry i = the lowest cut j with time(j, i) <= t.
+    template <bool kUp>
+    __device__ __forceinline__ void reach_table(uint32_t t, int side) {
+        const int tid = thread_id();
+        uint16_t *to = reach + side * sh.set_cap * tb.n_tp * sh.W;
+        const int n = n_sets * tb.n_tp * sh.W, top_step = 1 << (31 - __clz(L));
+        for (int x = tid; x < n; x += nthreads) {
+            const int r = x / sh.W, e = x - r * sh.W;
+            const uint64_t far = uint64_t(t) * uint32_t(tb.tp[r % tb.n_tp]);
+            const uint32_t *p = prow + r * sh.W;
+            const uint32_t pe = p[e];
+            int pos = e;
+            if (kUp) {
+                const uint32_t target = pe + far > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(pe + far);
+                for (int step = top_step; step > 0; step >>= 1) {
+                    const int nx = pos + step;
+                    pos = nx <= L && p[nx <= L ? nx : L] <= target ? nx : pos;
+                }
+            } else {
+                const uint32_t target = pe > far ? uint32_t(pe - far) : 0u;
+                for (int step = top_step; step > 0; step >>= 1) {
+                    const int nx = pos - step;
+                    pos = nx >= 0 && p[nx >= 0 ? nx : 0] >= target ? nx : pos;
+                }
+            }
+            to[x] = uint16_t(pos);
+        }
+    }
+    // highest cut <= i in a mask, -1 when there is none; lowest cut >= i, > L when there is none
+    __device__ __forceinline__ int mask_down(const unsigned long long *m, int i) const {
+        int w = i >> 6;
+        unsigned long long b = m[w] & (~0ull >> (63 - (i & 63)));
+        while (b == 0 && w > 0) b = m[--w];
+        return b == 0 ? -1 : w * 64 + 63 - __clzll((long long)b);
+    }
+    __device__ __forceinline__ int mask_up(const unsigned long long *m, int i) const {
+        int w = i >> 6;
+        unsigned long long b = m[w] & (~0ull << (i & 63));
+        while (b == 0 && w + 1 < sh.NW) b = m[++w];
+        return b == 0 ? L + 1 : w * 64 + __ffsll((long long)b) - 1;
+    }
+
+    // One wavefront: F of every (s, d) from the upward reach table `side`; true when (S, D) reaches L.  Fg
+    // null: the verdict only.
+    __device__ __forceinline__ bool forward_chain(int side, const unsigned long long *m, uint16_t *row, uint16_t *Fg) {
+        const int lane = thread_id() & 63;
+        for (int d = lane; d <= D; d += 64) {
+            const uint16_t v = d == 0 ? 0 : uint16_t(kNoCut);
+            row[d] = v;
+            if (Fg) Fg[d] = v;
+        }
+        wave_sync();
+        for (int s = 0; s < S; ++s) {
+            const bool last = s == S - 1;
+            const int n = in_flight(s), top = L - (S - 1 - s);
+            const int d_lo = last ? D : s + 1, d_hi = D - (S - 1 - s);
+            bool any = false;
+            for (int c = D >> 6; c >= 0; --c) {           // from the top: a column reads lower columns only
+                const int d2 = c * 64 + lane;
+                int best = -1;
+                if (d2 >= d_lo && d2 <= d_hi) {
+                    const int k = group_at[d2 - 1];
+                    const int from = offs[k] > s ? offs[k] : s;
+                    const uint16_t *far = reach_row(side, k);
+                    const uint16_t *fits = hi_tab + (index_n(n) + index_at[k]);
+                    for (int q0 = 0; q0 < tb.n_tp; q0 += 4) {
+                        // (no branches around the loads: the four degrees' are in flight together)
+                        uint32_t j[4];
+                        int a[4], b[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
+                            const int d = d2 - tb.tp[q];
+                            j[u] = row[d >= from ? d : 0];
+                            j[u] = d >= from ? j[u] : kNoCut;
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
+                            const int e = j[u] != kNoCut ? int(j[u]) : 0;
+                            a[u] = far[q * sh.W + e];
+                            b[u] = fits[q * sh.idx_pitch + e];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int i = a[u] < b[u] ? a[u] : b[u];
+                            best = j[u] != kNoCut && i > best ? i : best;
+                        }
+                    }
+                    best = best < top ? best : top;
+                    if (best >= 0 && !last) best = mask_down(m + link_of(d2) * sh.NW, best);
+                    if (best < s + 1) best = -1;
+                }
+                wave_sync();
+                if (d2 <= D) {
+                    const uint16_t v = best < 0 ? uint16_t(kNoCut) : uint16_t(best);
+                    row[d2] = v;
+                    if (Fg) Fg[size_t(s + 1) * sh.cols + d2] = v;
+                }
+                wave_sync();
+                any = any || __any(best >= 0);
+            }
+            if (!any) return false;
+        }
+        return uniform(row[D]) == L;
+    }
+
+    // One wavefront: B of every (s, d) from the downward reach table `side`; true when (0, 0) is reached.
+    __device__ __forceinline__ bool backward_chain(int side, const unsigned long long *m, uint16_t *row, uint16_t *Bg) {
+        const int lane = thread_id() & 63;
+        for (int d = lane; d <= D; d += 64) {
+            const uint16_t v = d == D ? uint16_t(L) : uint16_t(kNoCut);
+            row[d] = v;
+            Bg[size_t(S) * sh.cols + d] = v;
+        }
+        wave_sync();
+        for (int s = S - 1; s >= 0; --s) {
+            const int n = in_flight(s);
+            const int d_lo = s, d_hi = s == 0 ? 0 : D - (S - s);
+            bool any = false;
+            for (int c = 0; c <= (D >> 6); ++c) {         // from the bottom: a column reads higher columns only
+                const int d = c * 64 + lane;
+                int best = INT32_MAX;
+                if (d >= d_lo && d <= d_hi) {
+                    const int k = group_at[d], end = offs[k + 1];
+                    const uint16_t *far = reach_row(side, k);
+                    const uint16_t *fits = lo_tab + (index_n(n) + index_at[k]);
+                    for (int q0 = 0; q0 < tb.n_tp; q0 += 4) {
+                        uint32_t i[4];
+                        int a[4], b[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
+                            const int d1 = d + tb.tp[q];
+                            i[u] = row[d1 <= end ? d1 : 0];
+                            i[u] = d1 <= end ? i[u] : kNoCut;
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
+                            const int e = i[u] != kNoCut ? int(i[u]) : 0;
+                            a[u] = far[q * sh.W + e];
+                            b[u] = fits[q * sh.idx_pitch + e];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int j = a[u] > b[u] ? a[u] : b[u];
+                            best = i[u] != kNoCut && j < best ? j : best;
+                        }
+                    }
+                    best = best > s ? best : s;
+                    if (s > 0 && best <= L) best = mask_up(m + link_of(d) * sh.NW, best);
+                    if (best > L - (S - s) || (s == 0 && best != 0)) best = INT32_MAX;
+                }
+                wave_sync();
+                if (d <= D) {
+                    const uint16_t v = best == INT32_MAX ? uint16_t(kNoCut) : uint16_t(best);
+                    row[d] = v;
+                    Bg[size_t(s) * sh.cols + d] = v;
+                }
+                wave_sync();
+                any = any || __any(best != INT32_MAX);
+            }
+            if (!any) return false;
+        }
+        return uniform(row[0]) == 0;
+    }
+
+    // All threads: the ranges under t, cell numbering of every row.  False: no plan under t.
+    __device__ __forceinline__ bool prepare(uint32_t t) {
+        const int tid = thread_id();
+        const int lane = tid & 63;
+        __syncthreads();                                   // earlier use of rows, chains and ranges is over
+        cut_masks(1, t, t);
+        reach_table<true>(t, 0);
+        reach_table<false>(t, 1);
+        __syncthreads();
+        const bool two = sh.teams == 2;
+        if (wave == 0) {
+            bool good = forward_chain(0, masks(0), chain, sl.F);
+            if (!two && good) good = backward_chain(1, masks(0), chain, sl.B);
+            if (lane == 0) scal[0] = good ? 1u : 0u;
+        } else if (two && wave == 1) {
+            const bool good = backward_chain(1, masks(0), chain + sh.cols, sl.B);
+            if (lane == 0) scal[1] = good ? 1u : 0u;
+        }
+        __syncthreads();
+        if (scal[0] == 0 || (two && scal[1] == 0)) return false;
+        // cells of every row: columns one after the other, a wavefront per row
+        for (int s = wave; s <= S; s += nthreads >> 6) {
+            int total = 0;
+            for (int d0 = 0; d0 <= D; d0 += 64) {
+                const int d = d0 + lane;
+                uint32_t f = kNoCut, b = kNoCut;
+                if (d <= D) { f = sl.F[size_t(s) * sh.cols + d]; b = sl.B[size_t(s) * sh.cols + d]; }
+                const bool has = f != kNoCut && b != kNoCut && b <= f;
+                const int w = has ? int(f - b) + 1 : 0;
+                int inc = w;
+#pragma unroll
+                for (int x = 1; x < 64; x <<= 1) {
+                    const int o = __shfl_up(inc, x, 64);
+                    if (lane >= x) inc += o;
+                }
+                if (d <= D) {
+                    sl.off[size_t(s) * sh.cols + d] = total + inc - w - (has ? int(b) : 0);
+                    if (!has) { sl.F[size_t(s) * sh.cols + d] = 0; sl.B[size_t(s) * sh.cols + d] = 1; }
+                }
+                total += __shfl(inc, 63, 64);
+            }
+            if (lane == 0) tot[s] = total;
+        }
+        __syncthreads();
+        int most = 0, sum = 0, least = INT32_MAX;
+        for (int s = 0; s <= S; ++s) {
+            const int n = tot[s];
+            if (tid == 0) base[s] = sum;
+            sum += n;
+            most = n > most ? n : most;
+            least = n < least ? n : least;
+        }
+        rows_fit = most <= sh.row_cap;
+        __syncthreads();
+        return least > 0;
+    }
+
+    // Range and numbering of row s into column buffer b, and the column of every cell; a thread's first
+    // column is requested ahead (request_column) and waits in a register.
+    struct Column { int lo, hi, off; };
+    __device__ __forceinline__ Column request_column(int s) const {
+        const int tid = thread_id();
+        Column c{1, 0, 0};
+        if (tid <= D) {
+            const size_t at = size_t(s) * sh.cols + tid;
+            c.lo = sl.B[at]; c.hi = sl.F[at]; c.off = sl.off[at];
+        }
+        return c;
+    }
+    __device__ __forceinline__ void store_column(int d, const Column &c, int b, bool with_map) {
+        col_lo[b * sh.cols + d] = uint16_t(c.lo);
+        col_hi[b * sh.cols + d] = uint16_t(c.hi);
+        col_off[b * sh.cols + d] = c.off;
+        col_min[b * sh.cols + d] = 0xFFFFFFFFu;
+        if (with_map)
+            for (int i = c.lo; i <= c.hi; ++i) map[c.off + i] = uint16_t(d);
+    }
+    __device__ __forceinline__ void load_columns(int s, const Column &first, int b, bool with_map) {
+        const int tid = thread_id();
+        if (tid <= D) store_column(tid, first, b, with_map);
+        for (int d = tid + nthreads; d <= D; d += nthreads) {
+            const size_t at = size_t(s) * sh.cols + d;
+            store_column(d, Column{sl.B[at], sl.F[at], sl.off[at]}, b, with_map);
+        }
+    }
+    // column of cell x when there is no map: the last column that starts at or before x
+    __device__ __forceinline__ int find_column(int b, int x) const {
+        int lo = 0, hi = D;                                // first cells rise with d; empty columns share theirs
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            const int l = col_lo[b * sh.cols + mid], h = col_hi[b * sh.cols + mid];
+            const int first = col_off[b * sh.cols + mid] + (l <= h ? l : 0);
+            if (first <= x) lo = mid; else hi = mid - 1;
+        }
+        while (col_lo[b * sh.cols + lo] > col_hi[b * sh.cols + lo]) --lo;
+        return lo;
+    }
+
+    // One pass over all stages in the ranges of the last prepare.  kCapped = false: min-max, values above
+    // `t` count as unreachable.  kCapped = true: least sum of (t + 2c) over stage and transfer times of at
+    // most t.  Returns the value of (S, L, D), or kInf.
+    //
+    // Min-max cells scan windows of four cuts downwards and stop when the stage time alone exceeds the
+    // best value, or when nothing below the column's least value or the cell's transfer time is left to
+    // gain (where a slow link decides, most columns hold one value throughout).
+    // Least sums: D[j] + floor((P[i] + tp - 1 - P[j]) / tp) is floor((D[j] tp - P[j] + P[i] + tp - 1) / tp),
+    // and the minimum can be taken inside the floor, so a row kept in LDS is turned into D[j] tp - P[j] per
+    // degree once (key rows) and a cell is the minimum over a run of consecutive words: 2 instructions
+    // per cut instead of 11.
+    template <bool kCapped, bool kLds>
+    __device__ __forceinline__ int64_t value_pass_in(uint32_t t) {
+        const int tid = thread_id();
+        constexpr bool kKeys = kCapped && kLds;
+        constexpr int32_t kNoKey = INT32_MAX;
+        const uint32_t none = kCapped ? kInfSum : t + 1u;
+        const int pitch = sh.row_cap + kRowPad;
+        int32_t *keys = reinterpret_cast<int32_t *>(rows + pitch);         // [n_tp][pitch] (kKeys)
+        int cur = 0;
+        load_columns(0, request_column(0), 0, false);
+        Column ahead = request_column(1);
+        if (tid == 0) {                                    // row 0: no operators on no devices
+            rows[0] = 0;
+            sl.hist[0] = 0;
+            col_min[0] = 0;
+            if (kKeys)
+                for (int q = 0; q < tb.n_tp; ++q) keys[q * pitch] = 0;
+        }
+        for (int s = 0; s < S; ++s) {
+            const bool last = s == S - 1;
+            const int nxt = cur ^ 1;
+            load_columns(s + 1, ahead, nxt, kLds);
+            __syncthreads();                               // row s, its columns and those of row s + 1 are in place
+            if (!last) ahead = request_column(s + 2);
+            const uint32_t *prev = kLds ? rows + cur * pitch : sl.hist + base[s];
+            uint32_t *next = kKeys ? rows : rows + nxt * pitch;
+            uint32_t *out = sl.hist + base[s + 1];
+            const int total = tot[s + 1];
+            const uint32_t index_at_n = index_n(in_flight(s));
+            for (int x = tid; x < total; x += nthreads) {
+                const int d2 = kLds ? int(map[x]) : find_column(nxt, x);
+                const int i = x - col_off[nxt * sh.cols + d2];
+                const int k = group_at[d2 - 1];
+                const uint32_t cut = last ? 0u : tb.CM[cut_at[d2] + uint32_t(i)];
+                uint32_t best = none;
+                const uint32_t *p_k = time_row(k);
+                const int from = offs[k] > s ? offs[k] : s;
+                const uint16_t *fits = lo_tab + (index_at_n + index_at[k] + uint32_t(i)), *far = reach_row(1, k) + i;
+                // degrees from the largest down, four at a time: the first values found are then the best ones,
+                // and a degree whose column holds nothing below the best value is passed over
+                for (int q0 = (tb.n_tp - 1) & ~3; q0 >= 0; q0 -= 4) {
+                    int in_memory[4];                      // requested together, no branches in between
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) in_memory[u] = fits[(q0 + u < tb.n_tp ? q0 + u : q0) * sh.idx_pitch];
+#pragma unroll
+                    for (int u = 3; u >= 0; --u) {
+                        if (q0 + u >= tb.n_tp) continue;
+                        const int tp = tb.tp[q0 + u], d = d2 - tp, shift = tb.tp_shift[q0 + u];
+                        if (d < from || cut > t) continue;
+                        uint32_t floor_v = cut;
+                        if (!kCapped) {
+                            const uint32_t m = col_min[cur * sh.cols + d];
+                            floor_v = m > cut ? m : cut;
+                            if (floor_v >= best) continue;
+                        }
+                        // previous cuts: in the column's range, in memory, within t
+                        const int lo = col_lo[cur * sh.cols + d], hi = col_hi[cur * sh.cols + d];
+                        const int within = far[(q0 + u) * sh.W];
+                        int jl = in_memory[u] > within ? in_memory[u] : within;
+                        jl = jl > lo ? jl : lo;
+                        const int jh = (i - 1) < hi ? (i - 1) : hi;
+                        if (jl > jh) continue;
+                        const uint32_t *p = p_k + (q0 + u) * sh.W;
+                        const uint32_t xi = p[i] + uint32_t(tp) - 1u;
+                        const int off = col_off[cur * sh.cols + d];
+                        if (kKeys) {
+                            const int32_t *e = keys + (q0 + u) * pitch + off;
+                            int32_t m = kNoKey;
+                            int j = jl;
+                            for (; j + 7 <= jh; j += 8) {
+                                const int32_t e0 = e[j], e1 = e[j + 1], e2 = e[j + 2], e3 = e[j + 3];
+                                const int32_t e4 = e[j + 4], e5 = e[j + 5], e6 = e[j + 6], e7 = e[j + 7];
+                                m = least(least(least(e0, e1), m), least(least(e2, e3), e4));
+                                m = least(least(least(e5, e6), e7), m);
+                            }
+                            // what is left, in windows pushed up against jh or down against jl
+                            if (j <= jh) {
+                                if (jh - jl >= 7) {
+                                    j = jh - 7;
+                                    const int32_t e0 = e[j], e1 = e[j + 1], e2 = e[j + 2], e3 = e[j + 3];
+                                    const int32_t e4 = e[j + 4], e5 = e[j + 5], e6 = e[j + 6], e7 = e[j + 7];
+                                    m = least(least(least(e0, e1), m), least(least(e2, e3), e4));
+                                    m = least(least(least(e5, e6), e7), m);
+                                } else {
+                                    for (; j <= jh; ++j) m = least(m, e[j]);
+                                }
+                            }
+                            if (m != kNoKey) {
+                                const uint32_t v = (xi + uint32_t(m)) >> shift;
+                                best = least(best, v);
+                            }
+                        } else {
+                            const uint32_t *r = prev + off;
+                            // the first window may be cut short at its upper end, the last is pushed up
+                            // against jl (cuts seen twice do not matter to a minimum)
+                            int j = jh - 3 > jl ? jh - 3 : jl;
+                            uint32_t t0;
+                            {
+                                const uint32_t p0 = p[j], p1 = p[j + 1], p2 = p[j + 2], p3 = p[j + 3];
+                                const uint32_t r0 = r[j], r1 = r[j + 1], r2 = r[j + 2], r3 = r[j + 3];
+                                t0 = (xi - p0) >> shift;
+                                const uint32_t t1 = (xi - p1) >> shift, t2 = (xi - p2) >> shift, t3 = (xi - p3) >> shift;
+                                const uint32_t v0 = value<kCapped>(r0, t0, cut);
+                                const uint32_t v1 = j + 1 <= jh ? value<kCapped>(r1, t1, cut) : none;
+                                const uint32_t v2 = j + 2 <= jh ? value<kCapped>(r2, t2, cut) : none;
+                                const uint32_t v3 = j + 3 <= jh ? value<kCapped>(r3, t3, cut) : none;
+                                best = least(best, least(least(v0, v1), least(v2, v3)));
+                            }
+                            while (j > jl && (kCapped || (t0 <= best && best > floor_v))) {
+                                j = j - 4 > jl ? j - 4 : jl;
+                                const uint32_t p0 = p[j], p1 = p[j + 1], p2 = p[j + 2], p3 = p[j + 3];
+                                const uint32_t r0 = r[j], r1 = r[j + 1], r2 = r[j + 2], r3 = r[j + 3];
+                                t0 = (xi - p0) >> shift;
+                                const uint32_t t1 = (xi - p1) >> shift, t2 = (xi - p2) >> shift, t3 = (xi - p3) >> shift;
+                                const uint32_t v0 = value<kCapped>(r0, t0, cut), v1 = value<kCapped>(r1, t1, cut);
+                                const uint32_t v2 = value<kCapped>(r2, t2, cut), v3 = value<kCapped>(r3, t3, cut);
+                                best = least(best, least(least(v0, v1), least(v2, v3)));
+                            }
+                        }
+                    }
+                }
+                if (kCapped && best < kInfSum) best += 2u * cut;
+                if (kLds) next[x] = best;
+                // (lanes of a wavefront mostly share a column: the read in front spares the serialised atomics)
+                if (!kCapped && best < col_min[nxt * sh.cols + d2]) atomicMin(&col_min[nxt * sh.cols + d2], best);
+                out[x] = best;
+            }
+            __syncthreads();                               // row s + 1 is complete
+            if (kKeys && !last) {
+                // the row as stage s + 1 reads it: a stage that starts at device d runs on the group of d
+                for (int x = tid; x < total; x += nthreads) {
+                    const int d = map[x], i = x - col_off[nxt * sh.cols + d], k = group_at[d];
+                    const uint32_t v = rows[x], *p = time_row(k) + i;
+                    for (int q = 0; q < tb.n_tp; ++q)
+                        keys[q * pitch + x] = v < kInfSum ? int32_t(v * uint32_t(tb.tp[q])) - int32_t(p[q * sh.W]) : kNoKey;
+                }
+                __syncthreads();
+            }
+            cur = nxt;
+        }
+        const uint32_t v = kKeys ? rows[0] : kLds ? rows[cur * pitch] : sl.hist[base[S]];
+        return v >= none ? kInf : int64_t(v);
+    }
+    template <bool kCapped>
+    __device__ __forceinline__ uint32_t value(uint32_t before, uint32_t time, uint32_t cut) const {
+        if (kCapped) return before + time;
+        return fastdp::umax3(before, time, cut);
+    }
+    __device__ __forceinline__ int32_t least(int32_t a, int32_t b) const { return a < b ? a : b; }
+    __device__ __forceinline__ uint32_t least(uint32_t a, uint32_t b) const { return a < b ? a : b; }
+    template <bool kCapped>
+    __device__ __forceinline__ int64_t value_pass(uint32_t t) {
+        if (rows_fit) return value_pass_in<kCapped, true>(t);
+        return value_pass_in<kCapped, false>(t);
+    }
+
+    // All threads: the plan of the last value pass, value `v`, from the value rows: per stage the lowest
+    // previous cut, then the smallest degree, that attain the cell's value (lanes over degrees and cuts).
+    template <bool kCapped>
+    __device__ __forceinline__ void find_plan(uint32_t v, uint32_t cap) {
+        const int lane = thread_id() & 63;
+        if (wave == 0) {
+            const int per = tb.n_tp <= 1 ? 64 : tb.n_tp <= 2 ? 32 : tb.n_tp <= 4 ? 16 : 8;   // lanes per degree
+            const int q = lane / per, jj = lane - q * per;
+            const int tp = q < tb.n_tp ? tb.tp[q] : 0, shift = q < tb.n_tp ? tb.tp_shift[q] : 0;
+            int d2 = D, i = L;
+            if (lane == 0) cuts[S] = L;
+            for (int s = S - 1; s >= 0; --s) {
+                const int k = group_at[d2 - 1], n = in_flight(s), d = d2 - tp;
+                uint32_t want = v;
+                if (kCapped && s < S - 1) want = v - 2u * tb.CM[cut_at[d2] + uint32_t(i)];
+                const bool in = q < tb.n_tp && d >= offs[k] && d >= s;
+                int jl = 1, jh = 0, off = 0;
+                if (in) {
+                    const size_t at = size_t(s) * sh.cols + d;
+                    const int lo = sl.B[at], hi = sl.F[at], fits = lo_tab[index_n(n) + index_at[k] + uint32_t(q * sh.idx_pitch + i)];
+                    off = sl.off[at];
+                    jl = fits > lo ? fits : lo;
+                    jh = (i - 1) < hi ? (i - 1) : hi;
+                }
+                const uint32_t *p = time_row(k) + (in ? q : 0) * sh.W;
+                const uint32_t xi = p[i] + uint32_t(tp) - 1u;
+                uint32_t key = 0xFFFFFFFFu, val = 0;
+                for (int j = jl + jj; __any(in && j <= jh && key == 0xFFFFFFFFu); j += per) {
+                    if (in && j <= jh && key == 0xFFFFFFFFu) {
+                        const uint32_t time = (xi - p[j]) >> shift;
+                        if (time <= (kCapped ? cap : want)) {
+                            const uint32_t before = sl.hist[base[s] + off + j];
+                            const bool hit = kCapped ? before < kInfSum && before + time == want : before <= want;
+                            if (hit) { key = (uint32_t(j) << 3) | uint32_t(q); val = before; }
+                        }
+                    }
+                }
+                uint32_t low = key;
+#pragma unroll
+                for (int x = 32; x >= 1; x >>= 1) {
+                    const uint32_t o = __shfl_xor(low, x, 64);
+                    low = o < low ? o : low;
+                }
+                low = (uint32_t)uniform((int)low);
+                const unsigned long long who = __ballot(key == low);
+                v = __builtin_amdgcn_readlane(val, __ffsll((long long)who) - 1);
+                // a reached cell always has one; the clamps keep the indices inside the rows whatever happens
+                const int jn = int((low >> 3) & 0xFFFFu), qn = int(low & 7u);
+                i = jn < i ? jn : i - 1;
+                i = i > 0 ? i : 0;
+                d2 -= tb.tp[qn < tb.n_tp ? qn : 0];
+                d2 = d2 > 0 ? d2 : 0;
+                if (lane == 0) {
+                    cuts[s] = i;
+                    slot_g[s] = order[k];
+                    slot_k[s] = uint8_t(qn < tb.n_tp ? qn : 0);
+                    slot_first[s] = tb.group_base[order[k]] + (d2 - offs[k]);
+                }
+                if (s > 0 && d2 == 0) d2 = 1;
+            }
+        }
+        __syncthreads();
+    }
+
+    // The smallest bottleneck, its plan in cuts / slot_*; kInf when there is none.
+    __device__ __forceinline__ int64_t min_max() {
+        const int lane = thread_id() & 63;
+        // A first guess: every group takes work in proportion to its speed.  And a bound: every plan cuts
+        // somewhere on every link from a group to the next, no cheaper than at the operator of least output.
+        if (wave == 0) {
+            float share = 0.f;
+            uint32_t bound = 0;
+            for (int k = lane; k < K; k += 64) {
+                const float whole = float(tb.PF(type[k])[L]);
+                share += float(offs[k + 1] - offs[k]) / (whole > 1.f ? whole : 1.f);
+                if (k + 1 < K) {
+                    const uint32_t c = tb.CM[link_at[K + k] + uint32_t(least_cut)];
+                    bound = c > bound ? c : bound;
+                }
+            }
+#pragma unroll
+            for (int x = 32; x >= 1; x >>= 1) {
+                share += __shfl_xor(share, x, 64);
+                const uint32_t o = __shfl_xor(bound, x, 64);
+                bound = o > bound ? o : bound;
+            }
+            const float guess = 1.f / share;
+            if (lane == 0) { scal[5] = guess < 1.f ? 1u : guess > 1e9f ? 1000000000u : uint32_t(guess); scal[6] = bound; }
+        }
+        __syncthreads();
+        const int64_t bound = scal[6], g = int64_t(scal[5]) > bound ? int64_t(scal[5]) : bound;
+        int64_t bad = bound - 1, good = -1;                // largest t known to have no plan, smallest t whose chain succeeds
+        // until the two are within 1/12 of each other: below that the rows hardly get shorter than a workgroup
+        for (int round = 0; good < 0 || good - bad > good / 12 + 1; ++round) {
+            int64_t at[2];
+            for (int w = 0; w < 2; ++w) {
+                // the optimum lay at the guess on half of the orderings looked at, within a fifth above on most others
+                const int step = sh.teams == 2 ? round * 2 + w : round;
+                int64_t t;
+                if (good >= 0) t = bad + (good - bad) * (w + 1) / (sh.teams + 1);
+                else t = step == 0 ? g : step == 1 ? g + g * 7 / 32 + 1 : step == 2 ? g + g * 5 / 8 + 1 : step == 3 ? 5 * g / 2 + 1
+                         : step == 4 ? 8 * g + 1 : step == 5 ? 64 * g + 1 : int64_t(kTopCap);
+                at[w] = t < int64_t(kTopCap) ? t : int64_t(kTopCap);
+            }
+            __syncthreads();
+            cut_masks(sh.teams, uint32_t(at[0]), uint32_t(at[1]));
+            for (int w = 0; w < sh.teams; ++w) reach_table<true>(uint32_t(at[w]), w);
+            __syncthreads();
+            if (wave < sh.teams) {
+                const bool fine = forward_chain(wave, masks(wave), chain + wave * sh.cols, nullptr);
+                if (lane == 0) scal[wave] = fine ? 1u : 0u;
+            }
+            __syncthreads();
+            for (int w = sh.teams - 1; w >= 0; --w)
+                if (scal[w] != 0) good = at[w];
+            for (int w = 0; w < sh.teams; ++w)
+                if (scal[w] == 0 && at[w] > bad) bad = at[w];
+            if (good < 0 && bad >= int64_t(kTopCap)) return kInf;         // no plan under any cap
+            if (good == g) break;                                          // near enough
+        }
+        uint32_t t = uint32_t(good);
+        for (int tries = 0;; ++tries) {
+            if (prepare(t)) {
+                const int64_t v = value_pass<false>(t);
+                if (v != kInf) {
+                    find_plan<false>(uint32_t(v), t);
+                    return v;
+                }
+            }
+            if (t >= kTopCap) return kInf;
+            const int64_t up = int64_t(t) + (t >> (tries < 3 ? 3 - tries : 0)) + 1;
+            t = up < int64_t(kTopCap) ? uint32_t(up) : kTopCap;
+        }
+    }
+
+    // The recurrence with H-1F1B warm-up counts (eq. dp_ni) in the ranges of the last prepare, suffix
+    // direction: cell (s, d, i) = stages s .. S-1 hold the operators from i on, on the devices from d on.
+    // A row is stored ready for the stage in front of it: sum plus twice the transfer time of the cut
+    // at i (kInfSum beyond the cap) and the count that stage would have.  Ties: lowest end cut, then
+    // smallest degree.  The memory test runs only for a cut that would be taken.  Returns the value of
+    // (0, 0, 0) or kInf; back-pointers (cut | degree index << 13) go to the slice.
+    template <bool kLds>
+    __device__ __forceinline__ int64_t h1_pass_in(uint32_t cap) {
+        const int tid = thread_id();
+        const uint64_t e6 = uint64_t(cap) >> 6;
+        const uint32_t th1 = uint32_t(e6 >> 1), th2 = uint32_t((uint64_t(cap) + e6) >> 1);   // 2c - e > 0; > cap
+        const uint32_t m_cap = uint32_t(tb.M);
+        const int64_t *PP = mem, *PS = mem + sh.W;
+        uint16_t *back = reinterpret_cast<uint16_t *>(sl.hist);
+        auto row_h = [&](int b) -> uint32_t * { return kLds ? rows + b * (sh.row_cap + kRowPad) : sl.spare_h + b * sl.row; };
+        auto row_n = [&](int b) -> uint16_t * { return kLds ? counts + b * (sh.row_cap + kRowPad) : sl.spare_n + b * sl.row; };
+        int cur = 0;
+        load_columns(S, request_column(S), 0, false);
+        Column ahead = request_column(S - 1);
+        if (tid == 0) { row_h(0)[0] = 0; row_n(0)[0] = 1; }    // behind the last stage: it launches one
+        for (int s = S - 1; s >= 0; --s) {
+            const int n = in_flight(s);
+            const int nxt = cur ^ 1;
+            load_columns(s, ahead, nxt, kLds);
+            __syncthreads();
+            if (s > 0) ahead = request_column(s - 1);
+            const uint32_t *prev_h = row_h(cur);
+            const uint16_t *prev_n = row_n(cur);
+            uint32_t *next_h = row_h(nxt);
+            uint16_t *next_n = row_n(nxt);
+            const int total = tot[s], at = base[s];
+            for (int x = tid; x < total; x += nthreads) {
+                const int d = kLds ? int(map[x]) : find_column(nxt, x);
+                const int i = x - col_off[nxt * sh.cols + d];
+                const int k = group_at[d], end = offs[k + 1];
+                const int64_t mem_dev = tb.type_mem[type[k]];
+                const uint32_t cut = s > 0 ? tb.CM[cut_at[d] + uint32_t(i)] : 0u;
+                uint32_t best = kInfSum, best_n = 0;
+                int best_j = 0, best_q = 0;
+                for (int q = 0; q < tb.n_tp; ++q) {
+                    const int tp = tb.tp[q], d1 = d + tp;
+                    if (d1 > end) break;
+                    const int lo = col_lo[cur * sh.cols + d1], hi = col_hi[cur * sh.cols + d1];
+                    const int fits = hi_tab[index_n(n) + index_at[k] + uint32_t(q * sh.idx_pitch + i)];
+                    const int jl = (i + 1) > lo ? (i + 1) : lo, jh = fits < hi ? fits : hi;
+                    const uint32_t *p = time_row(k) + q * sh.W;
+                    const int off = col_off[cur * sh.cols + d1];
+                    const uint32_t xi = p[i] - uint32_t(tp) + 1u;
+                    const int shift = tb.tp_shift[q];
+                    const int64_t capm = int64_t(tp) * mem_dev;
+                    for (int j = jl; j <= jh; ++j) {
+                        const uint32_t time = (p[j] - xi) >> shift;
+                        if (time > cap) break;
+                        const uint32_t v = prev_h[off + j] + time;
+                        if (v < best || (v == best && j < best_j)) {
+                            const uint32_t cnt = prev_n[off + j];
+                            if ((PP[j] - PP[i]) + int64_t(cnt) * (PS[j] - PS[i]) <= capm) {
+                                best = v; best_j = j; best_q = q; best_n = cnt;
+                            }
+                        }
+                    }
+                }
+                back[at + x] = uint16_t(uint32_t(best_j) | (uint32_t(best_q) << 13));
+                if (s > 0) {
+                    const uint32_t h = best < kInfSum && cut <= cap ? best + 2u * cut : kInfSum;
+                    const uint32_t cnt = 1u + (cut > th1 ? 1u : 0u) + (cut > th2 ? 1u : 0u) + best_n;
+                    next_h[x] = h < kInfSum ? h : kInfSum;
+                    next_n[x] = uint16_t(cnt < m_cap ? cnt : m_cap);
+                } else {
+                    scal[4] = best;
+                }
+            }
+            __syncthreads();
+            cur = nxt;
+        }
+        const uint32_t v = scal[4];
+        return v >= kInfSum ? kInf : int64_t(v);
+    }
+    __device__ __forceinline__ int64_t h1_pass(uint32_t cap) {
+        if (rows_fit) return h1_pass_in<true>(cap);
+        return h1_pass_in<false>(cap);
+    }
+    // All threads: PP and PS into LDS, once per kernel
+    __device__ __forceinline__ void load_memory_sums() {
+        const int tid = thread_id();
+        const int64_t *PP = tb.PP(), *PS = tb.PS();
+        for (int j = tid; j <= L; j += nthreads) { mem[j] = PP[j]; mem[sh.W + j] = PS[j]; }
+        __syncthreads();
+    }
+    // All threads: the plan of the last H-1F1B pass, with its counts by eq. Ni.
+    __device__ __forceinline__ void find_h1_plan(uint32_t cap) {
+        const int lane = thread_id() & 63;
+        if (wave == 0) {
+            const uint16_t *back = reinterpret_cast<const uint16_t *>(sl.hist);
+            int d = 0, i = 0;
+            for (int s = 0; s < S; ++s) {
+                const int k = group_at[d];
+                const size_t at = size_t(s) * sh.cols + d;
+                const int lo = sl.B[at], hi = sl.F[at];
+                const int ic = i < lo ? lo : (i > hi ? hi : i);       // a finite sum only chains through cells
+                const uint32_t a = back[base[s] + sl.off[at] + ic];
+                const int q = int(a >> 13) & 7;
+                if (lane == 0) {
+                    cuts[s] = i;
+                    slot_g[s] = order[k];
+                    slot_k[s] = uint8_t(q < tb.n_tp ? q : 0);
+                    slot_first[s] = tb.group_base[order[k]] + (d - offs[k]);
+                }
+                i = int(a & 0x1FFFu);
+                d += tb.tp[q < tb.n_tp ? q : 0];
+                d = d < D ? d : (s + 1 < S ? D - 1 : D);
+            }
+            if (lane == 0) cuts[S] = L;
+            wave_sync();
+            const uint64_t e6 = uint64_t(cap) >> 6;
+            for (int s = lane; s < S; s += 64) {
+                uint32_t cut = 0;
+                if (s < S - 1) cut = tb.CM[(int64_t(slot_g[s]) * tb.G + slot_g[s + 1]) * tb.pitch32 + cuts[s + 1]];
+                warmup[s] = 1 + (2ull * cut > e6 ? 1 : 0) + (2ull * cut > uint64_t(cap) + e6 ? 1 : 0);
+            }
+            wave_sync();
+            if (lane == 0) {
+                int run = 0;
+                for (int s = S - 1; s >= 0; --s) {
+                    run += warmup[s];
+                    run = run < tb.M ? run : tb.M;
+                    warmup[s] = run;
+                }
+            }
+        }
+        __syncthreads();
+    }
+
+    // sums of S stage and twice S transfer times under the cap, times the largest degree, stay below 2^31
+    __device__ __forceinline__ bool sums_fit(int64_t cap) const {
+        return cap <= int64_t(kInfSum) / (3ll * S * tb.tp[tb.n_tp - 1]) - 1;
+    }
+};
+
+}  // namespace meshband
+}  // namespace harp

@@ -1,0 +1,73 @@
+"""The band-limited kernels of the submesh planner at the edges of their tiles: 64 columns, 64 cuts per
+mask word, four degrees per step, value rows beyond LDS, and the orderings they hand over."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2509_24859_amd import workloads as W
+
+from helpers import assert_plans_equal, oracle_plan_mesh_h1f1b_threaded, oracle_plan_mesh_threaded, simple_problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx(harp):
+    c = harp.Context(0)
+    yield c
+    c.close()
+
+
+def _problem(seed, L, ndev, tp, slow=False, scale=1, distinct_links=False):
+    rng = np.random.default_rng(seed)
+    G = len(ndev)
+    bw = rng.integers(20, 60, size=(G, G)) * (1 if not slow else 10)
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = np.arange(G) + 500 if distinct_links else 500
+    if slow and G > 1:
+        bw[0, 1] = bw[1, 0] = 1                 # one link decides the bottleneck: wide rows
+    p = simple_problem(np.zeros(L), M=6, T=2, G=G, ndev=ndev, tp=tp, gtype=[g % 2 for g in range(G)],
+                       fwd=rng.integers(1, 900, size=(2, L)) * scale, bwd=rng.integers(1, 900, size=(2, L)) * scale,
+                       act=rng.integers(100, 3000, size=L) * scale, params=rng.integers(0, 40, size=L),
+                       stash=rng.integers(0, 10, size=L), bw=bw)
+    p.type_mem_bytes[:] = 60 * L // max(1, len(ndev)) + 100
+    return p
+
+
+CASES = [  # L, devices per group, degrees, stage counts, slow link, scale of the times, distinct own links
+    (2, (1, 1), (1,), (2,), False, 1, False),
+    (63, (31, 32), (1, 2, 4, 8, 16), (5, 9), False, 1, False),
+    (64, (32, 32), (1, 2, 4, 8, 16, 32), (4, 7), True, 1, False),
+    (65, (33, 32), (1, 2, 4, 8, 16), (6, 8), True, 1, False),
+    (129, (64, 65), (1, 2, 4, 8, 16, 32, 64, 128), (4, 6), False, 1, False),
+    (30, (3, 2, 4), (1, 2, 4), (3, 5, 9), True, 1 << 14, False),       # sums beyond 2^31: handed over
+    (900, (1, 1, 1, 1), (1, 2, 4, 8, 16, 32, 64, 128), (4,), False, 1, True),   # time rows beyond LDS: handed over
+    (400, (32, 32), (1, 2, 4, 8, 16, 32), (8,), True, 1, False),       # value rows beyond LDS
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "L%d_D%d_q%d" % (c[0], sum(c[1]), len(c[2])))
+def test_band_kernels_at_their_edges(harp, ctx, case):
+    L, ndev, tp, stages, slow, scale, distinct = case
+    p = _problem(L, L, ndev, tp, slow, scale, distinct)
+    assert harp.Tables(ctx, p).fast32
+    G = len(ndev)
+    lists = [(S, order) for S in stages for order in (list(range(G)), list(range(G))[::-1])]
+    orders = W.orderings_from_lists(lists, S_max=max(stages))
+    ot = oracle.build_tables(p)
+    want = oracle_plan_mesh_threaded(ot, orders)
+    assert (want.status == oracle.OK).any()
+    fast, _ = harp.plan_mesh(ctx, p, orders, False, harp.PATH_FAST32)
+    assert_plans_equal(fast, want, "min-max")
+    assert (fast.stage_tp == want.stage_tp).all() and (fast.stage_group == want.stage_group).all()
+    # the exact form against the int64 kernel, which shares no search code with it
+    exact, _ = harp.plan_mesh(ctx, p, orders, True, harp.PATH_FAST32)
+    wide, _ = harp.plan_mesh(ctx, p, orders, True, harp.PATH_GENERIC)
+    assert_plans_equal(exact, wide, "exact")
+    assert (exact.stage_tp == wide.stage_tp).all() and (exact.n_passes == wide.n_passes).all()
+    # H-1F1B counts under caps at and above the bottleneck
+    caps = np.where(want.status == oracle.OK, want.bottleneck + np.arange(orders.C) * want.bottleneck // 7, -1)
+    hw = oracle_plan_mesh_h1f1b_threaded(ot, orders, caps)
+    hg, _ = harp.plan_mesh_h1f1b(ctx, p, orders, caps, harp.PATH_FAST32)
+    assert_plans_equal(hg, hw, "h1f1b")
+    assert (hg.warmup == hw.warmup).all() and (hg.stage_tp == hw.stage_tp).all()
