@@ -206,7 +206,7 @@ SweepLayout sweep_layout(const harp_ctx *ctx, const harp_tables *t, const harp_o
     s.W_climb = int(Wc);
     s.W = int(Wc);        // the rest of the sweep as well: more, shorter items even out orderings with many caps
     s.groups = int(resident < C * Wc ? resident : C * Wc);
-    s.bytes = 256 + size_t(s.groups) * s.per_group + size_t(C) * size_t(Wc + 1) * plan_mesh_sweep_slot_bytes(od->S_max) +
+    s.bytes = plan_mesh_ws_fixed(t->dev, od->S_max, int(C)) + size_t(s.groups) * s.per_group + size_t(C) * size_t(Wc + 1) * plan_mesh_sweep_slot_bytes(od->S_max) +
               ((size_t(C) * (sizeof(int64_t) + sizeof(int)) + 255) & ~size_t(255));
     return s;
 }
@@ -653,7 +653,7 @@ int harp_plan_mesh_h1f1b_sweep_batch(harp_ctx *ctx, harp_tables *t, const harp_o
     const PlansDev pl = { out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
     launch_plan_mesh_h1f1b_sweep(t->dev, o, nullptr, nullptr, max_caps, pl, stage_group, stage_tp, warmup, t_max_out, n_caps,
                                  use_fast_rows(ctx, t), workspace, lay.groups, lay.threads, lay.W_climb, lay.W, t->total_devices,
-                                 static_cast<hipStream_t>(hip_stream));
+                                 ctx->n_cu, static_cast<hipStream_t>(hip_stream));
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the submesh H-1F1B sweep kernel");
     return HARP_OK;
@@ -691,7 +691,7 @@ int harp_plan_h1f1b_sweep_batch(harp_ctx *ctx, harp_tables *t, const harp_candid
     const PlansDev pl = { out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
     launch_plan_mesh_h1f1b_sweep(t->dev, o, cd->cand_group, cd->cand_tp, max_caps, pl, nullptr, nullptr, warmup,
                                  t_max_out, n_caps, use_fast_rows(ctx, t), workspace, lay.groups, lay.threads, lay.W_climb, lay.W,
-                                 t->total_devices, static_cast<hipStream_t>(hip_stream));
+                                 t->total_devices, ctx->n_cu, static_cast<hipStream_t>(hip_stream));
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the search over the cap");
     return HARP_OK;

@@ -112,7 +112,7 @@ void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const i
                                   const int32_t *cand_tp, int max_caps, const PlansDev &out,
                                   int32_t *stage_group, int32_t *stage_tp, int32_t *warmup, int64_t *t_max_out,
                                   int32_t *n_caps, bool fast32, void *ws, int n_groups, int threads, int W_climb,
-                                  int W, int64_t total_devices, hipStream_t st);
+                                  int W, int64_t total_devices, int n_cu, hipStream_t st);
 size_t plan_mesh_sweep_slot_bytes(int S_max);
 size_t plan_mesh_ws_per_group(int L, int S_max, int64_t total_devices);
 size_t plan_mesh_ws_fixed(const TablesDev &tb, int S_max, int C);

@@ -23,7 +23,10 @@ namespace harp {
 
 using namespace meshdp;
 using meshband::Band;
+using meshband::BandArgs;
 using meshband::BandShape;
+using meshband::MeshWorkspace;
+using meshband::mesh_carve;
 
 namespace {
 
@@ -273,30 +276,6 @@ __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh_h1f1b(TablesDev tb, O
 
 // ------------------------------------------------------------------------------------ band form
 
-// What the band kernels share: the launch's LDS shape, the feasibility index, slices, and counters
-// [0] ticket, [1] orderings handed over, [2] ticket of the int64 kernel that takes those.
-struct BandArgs {
-    BandShape sh;
-    const uint16_t *lo_tab, *hi_tab;
-    unsigned char *slices;
-    size_t per_group;
-    int *counters;
-    int *redo;
-};
-
-// Outputs of an ordering whose plan is in the band's cuts / slot_*.
-__device__ __forceinline__ void write_slots(const TablesDev &tb, const PlansDev &out, const Band &b, int c, int S_max,
-                                            int32_t *sg, int32_t *stp) {
-    int32_t *sp = out.splits + int64_t(c) * (S_max + 1), *df = out.dev_first + int64_t(c) * S_max;
-    const int tid = Band::thread_id();
-    for (int s = tid; s <= S_max; s += b.nthreads) sp[s] = s <= b.S ? b.cuts[s] : -1;
-    for (int s = tid; s < S_max; s += b.nthreads) {
-        sg[s] = s < b.S ? int32_t(b.slot_g[s]) : -1;
-        stp[s] = s < b.S ? tb.tp[b.slot_k[s]] : -1;
-        df[s] = s < b.S ? b.slot_first[s] : -1;
-    }
-}
-
 // Bound by vector issue and by the latency of its serial parts (chains, plan recovery: one wavefront of a
 // workgroup).  Measured against the whole-table form on 32-bit rows it replaces: 4,096 orderings of 82
 // operators and 64 devices 3.57 -> 0.95 ms; exact form, 256 orderings of 160 operators and 128 devices,
@@ -314,16 +293,6 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
     const int S_max = od.S_max, tid = threadIdx.x;
     const int64_t m_cap = tb.M;
     b.find_least_cut();
-    auto score = [&](int64_t &bott, int64_t &total) {
-        if (b.wave == 0) {
-            int64_t x, y;
-            wave_score_partition(tb, b.S, b.slot_g, b.slot_k, b.cuts, tid & 63, x, y);
-            if ((tid & 63) == 0) { scored[0] = x; scored[1] = y; }
-        }
-        __syncthreads();
-        bott = scored[0];
-        total = scored[1];
-    };
     for (;;) {
         __syncthreads();
         if (tid == 0) item = atomicAdd(&ba.counters[0], 1);
@@ -341,43 +310,53 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE); continue; }
         auto hand_over = [&]() { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c; };
         if (verdict == 3) { hand_over(); continue; }
-        if (b.min_max() == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
-        int64_t t_S, best_T;
-        score(t_S, best_T);
-        if (kExact && b.S >= 2 && !b.sums_fit((best_T + m_cap - 1) / m_cap)) { hand_over(); continue; }
-        write_slots(tb, out, b, c, S_max, sg, stp);
-        int64_t best_b = t_S;
-        int passes = 0;
-        if (kExact) {
-            int64_t cap = t_S;
-            while (b.S >= 2) {
-                if (!b.prepare(uint32_t(cap))) break;             // cannot happen at or above t_S
-                const int64_t sum = b.template value_pass<true>(uint32_t(cap));
-                if (sum == kInf) break;
-                b.template find_plan<true>(uint32_t(sum), uint32_t(cap));
-                int64_t bn, T;
-                score(bn, T);
-                ++passes;
-                if (T < best_T || (T == best_T && bn <= best_b)) {   // equal totals: the lower cap; equal caps: the capped plan
-                    best_T = T;
-                    best_b = bn;
-                    write_slots(tb, out, b, c, S_max, sg, stp);
-                }
-                if (passes >= (1 << 20) || bn > cap) break;          // cannot happen: the cap falls with every pass
-                int64_t next_cap;
+        const int64_t opening = b.bracket();
+        if (opening < 0) { fail(HARP_CAND_INFEASIBLE); continue; }
+        int form = Band::kMinMax, tries = 0, passes = 0;
+        uint32_t cap = uint32_t(opening);
+        int64_t t_S = 0, best_T = kInf, best_b = kInf;
+        bool over = false;
+        for (;;) {
+            const int64_t v = b.template run<kExact ? Band::kMinMax | Band::kSum : Band::kMinMax>(form, cap);
+            if (v == kInf) {
+                if (form == Band::kSum || cap >= meshband::kTopCap) break;     // (a sum cannot fail at or above t_S)
+                cap = Band::raised(cap, tries++);
+                continue;
+            }
+            b.find_plan(form == Band::kSum, uint32_t(v), cap);
+            int64_t bn, T;
+            b.score(scored, bn, T);
+            if (form == Band::kMinMax) t_S = bn;
+            else ++passes;
+            if (T < best_T || (T == best_T && bn <= best_b)) {       // equal totals: the lower cap; equal caps: the capped plan
+                best_T = T;
+                best_b = bn;
+                b.write_slots(out, c, S_max, sg, stp);
+            }
+            if (!kExact || b.S < 2) break;
+            int64_t next_cap;
+            if (form == Band::kMinMax) {
+                over = !b.sums_fit((best_T + m_cap - 1) / m_cap);
+                if (over) break;
+                form = Band::kSum;
+                next_cap = t_S;
+            } else {
+                if (passes >= (1 << 20) || bn > int64_t(cap)) break;  // cannot happen: the cap falls with every pass
                 if (passes == 1) {
                     next_cap = (best_T + m_cap - 1) / m_cap;
                 } else {
                     next_cap = bn - 1;
                     if (m_cap > 1) {
-                        const int64_t bound = (best_T - sum) / (m_cap - 1);
+                        const int64_t bound = (best_T - v) / (m_cap - 1);
                         next_cap = next_cap < bound ? next_cap : bound;
                     }
                 }
                 if (next_cap <= t_S) break;
-                cap = next_cap;
             }
+            cap = uint32_t(next_cap);
         }
+        if (over) { hand_over(); continue; }
+        if (best_T == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
         if (tid == 0) {
             out.bottleneck[c] = best_b;
             out.iter_time[c] = best_T;
@@ -416,10 +395,10 @@ __global__ __launch_bounds__(1024) void k2_mesh_band_h1f1b(TablesDev tb, OrdDev 
             if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c;
             continue;
         }
-        const int64_t sum = b.prepare(uint32_t(cap)) ? b.h1_pass(uint32_t(cap)) : kInf;
+        const int64_t sum = b.run<Band::kH1>(Band::kH1, uint32_t(cap));
         if (sum == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
         b.find_h1_plan(uint32_t(cap));
-        write_slots(tb, out, b, c, S_max, sg, stp);
+        b.write_slots(out, c, S_max, sg, stp);
         for (int s = tid; s < S_max; s += b.nthreads) wu[s] = s < b.S ? b.warmup[s] : -1;
         if (b.wave == 0) {
             int64_t bott, iter;
@@ -437,33 +416,23 @@ __global__ void k2_mesh_clear(int *counters) {
     if (threadIdx.x < 8) counters[threadIdx.x] = 0;
 }
 
-// Workspace: counters | orderings handed over [C] | feasibility index | slices.
-struct MeshWorkspace {
-    int *counters, *redo;
-    uint16_t *index;
-    unsigned char *slices;
-    size_t before_slices;
-};
-MeshWorkspace mesh_carve(void *ws, int C, size_t index_bytes) {
+}  // namespace
+
+MeshWorkspace meshband::mesh_carve(const TablesDev &tb, int S_max, int C, void *ws) {
     auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
     unsigned char *p = static_cast<unsigned char *>(ws);
     MeshWorkspace w;
+    // no index: sequences too long for the band kernels, or an index too large
+    w.index_bytes = tb.L <= kFastRowsMaxL ? fastdp::lo_table_bytes(tb.L, S_max, tb.M, tb.T, tb.n_tp) : 0;
+    if (w.index_bytes > kFastIndexLimit) w.index_bytes = 0;
     size_t off = 0;
     w.counters = reinterpret_cast<int *>(p); off += 256;
     w.redo = reinterpret_cast<int *>(p + off); off += up(size_t(C) * sizeof(int));
-    w.index = reinterpret_cast<uint16_t *>(p + off); off += up(index_bytes);
+    w.index = reinterpret_cast<uint16_t *>(p + off); off += up(w.index_bytes);
     w.slices = p + off;
     w.before_slices = off;
     return w;
 }
-
-size_t mesh_index_bytes(const TablesDev &tb, int S_max) {
-    if (tb.L > kFastRowsMaxL) return 0;
-    const size_t n = fastdp::lo_table_bytes(tb.L, S_max, tb.M, tb.T, tb.n_tp);
-    return n <= kFastIndexLimit ? n : 0;
-}
-
-}  // namespace
 
 // LDS of a band workgroup: `budget` bytes, more when the time rows need it; false when they do not fit
 // the CU.
@@ -485,7 +454,8 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     sh.o_row_at = take(size_t(sh.K_cap) * 16);
     sh.o_cut_at = take(size_t(sh.cols) * 4);
     sh.o_group_at = take(size_t(sh.cols) * 2);
-    sh.o_mem = take(form == kFormH1 ? size_t(sh.W) * 16 : 0);
+    const bool sums = form == kFormSum || form == kFormSweep, h1 = form == kFormH1 || form == kFormSweep;
+    sh.o_mem = take(h1 ? size_t(sh.W) * 16 : 0);
     sh.o_chain = take(size_t(sh.teams) * sh.cols * 2);
     sh.o_ok = take(size_t(sh.teams) * 2 * sh.K_cap * sh.NW * 8);
     sh.o_col = take(size_t(sh.cols) * 24);
@@ -497,11 +467,12 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     const size_t least = size_t(tb.T < sh.K_cap ? tb.T : sh.K_cap);
     sets = sets < least ? least : sets;
     sh.set_cap = int(sets < size_t(sh.K_cap) ? sets : size_t(sh.K_cap));
+    sh.o_use = take(size_t(sh.set_cap) * 4);
     sh.o_prow = take(size_t(sh.set_cap) * per_set / 2 + 16);
     sh.o_reach = take(size_t(sh.set_cap) * per_set / 2);
     // bytes per cell: two value rows; or one and the key rows; or two rows of sums and counts; and the map
-    const size_t value_rows = form == kFormSum && tb.n_tp > 1 ? 1 + size_t(tb.n_tp) : 2;
-    const size_t per_cell = value_rows * 4 + (form == kFormH1 ? 4 : 0) + 2, lds_cu = size_t(160) << 10;
+    const size_t value_rows = sums && tb.n_tp > 1 ? 1 + size_t(tb.n_tp) : 2;
+    const size_t per_cell = value_rows * 4 + (h1 ? 4 : 0) + 2, lds_cu = size_t(160) << 10;
     size_t room = budget > off ? budget - off : 0;
     const size_t want = size_t(sh.K_cap) > 1024 ? size_t(sh.K_cap) : 1024;        // the map also numbers the sets
     if (room < want * per_cell + 128) room = want * per_cell + 128;
@@ -511,26 +482,22 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     cells = cells > all && all >= want ? all : cells;
     sh.row_cap = int(cells & ~size_t(7));
     const size_t row = size_t(sh.row_cap) + kRowPad;
-    sh.o_rows = take((value_rows > 2 ? value_rows : 2) * row * 4);
-    sh.o_count = take(form == kFormH1 ? 2 * row * 2 : 0);
+    sh.o_rows = take(value_rows * row * 4);
+    sh.o_count = take(h1 ? 2 * row * 2 : 0);
     sh.o_map = take(size_t(sh.row_cap) * 2);
     sh.total = uint32_t(off);
     return off <= lds_cu;
 }
 
-namespace {
-
 // Workgroups of the band kernels: a batch of at most one ordering per CU gets the whole CU's LDS and
 // 1,024 threads each; beyond that two workgroups of 512 threads share a CU (the key rows of the exact form
 // and the rows of the H-1F1B form want the room), or four of 256 in the min-max form.
-bool band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int &threads,
+bool meshband::band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int &threads,
                  BandShape &sh) {
     threads = od.C <= n_cu ? 1024 : (form != meshband::kFormMinMax || od.C <= 2 * n_cu) ? 512 : 256;
     const size_t budget = threads == 1024 ? (size_t(156) << 10) : threads == 512 ? (size_t(79) << 10) : (size_t(39) << 10);
-    return meshband::band_shape(tb, od.S_max, od.G_max, total_devices, threads, form, budget, sh);
+    return band_shape(tb, od.S_max, od.G_max, total_devices, threads, form, budget, sh);
 }
-
-}  // namespace
 
 // Threads of an int64 workgroup: a stage has up to L x devices target cells, so small tables get many
 // small workgroups (more orderings in flight), large ones few large workgroups (more lanes per ordering).
@@ -552,7 +519,7 @@ size_t plan_mesh_ws_per_group(int L, int S_max, int64_t total_devices) {
 }
 
 size_t plan_mesh_ws_fixed(const TablesDev &tb, int S_max, int C) {
-    return mesh_carve(nullptr, C, mesh_index_bytes(tb, S_max)).before_slices;
+    return mesh_carve(tb, S_max, C, nullptr).before_slices;
 }
 
 namespace {
@@ -562,16 +529,15 @@ namespace {
 template <typename BandFn, typename WideFn>
 void mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int form, void *ws, int n_groups, int threads,
                  int64_t total_devices, int n_cu, hipStream_t st, BandFn band, WideFn wide) {
-    const size_t index_bytes = mesh_index_bytes(tb, od.S_max);
-    const MeshWorkspace w = mesh_carve(ws, od.C, index_bytes);
+    const MeshWorkspace w = mesh_carve(tb, od.S_max, od.C, ws);
     const size_t per_group = plan_mesh_ws_per_group(tb.L, od.S_max, total_devices);
     hipLaunchKernelGGL(k2_mesh_clear, dim3(1), dim3(64), 0, st, w.counters);
     BandArgs ba;
     int band_threads = 0;
-    if (fast32 && index_bytes != 0 && band_launch(tb, od, total_devices, form, n_cu, band_threads, ba.sh)) {
+    if (fast32 && w.index_bytes != 0 && meshband::band_launch(tb, od, total_devices, form, n_cu, band_threads, ba.sh)) {
         launch_plan_index(tb, od.S_max, w.index, st);
         ba.lo_tab = w.index;
-        ba.hi_tab = w.index + index_bytes / 4;
+        ba.hi_tab = w.index + w.index_bytes / 4;
         ba.slices = w.slices;
         ba.per_group = per_group;
         ba.counters = w.counters;

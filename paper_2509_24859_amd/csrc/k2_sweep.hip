@@ -1,11 +1,16 @@
 // The search over the cap around the full recurrence (paper section 5.2.4 (2), (3)): the kernels of
 // harp_plan_mesh_h1f1b_sweep_batch (orderings) and harp_plan_h1f1b_sweep_batch (candidates with a fixed
 // slicing).  The passes themselves are in mesh_passes.h.
+#include "mesh_band.h"
 #include "mesh_passes.h"
 
 namespace harp {
 
 using namespace meshdp;
+using meshband::Band;
+using meshband::BandArgs;
+using meshband::MeshWorkspace;
+using meshband::mesh_carve;
 
 namespace {
 
@@ -182,12 +187,20 @@ __device__ __forceinline__ SweepSlot sweep_slot(unsigned char *slots, int S_max,
 // ordering each).  Ws is the number of walker slots per ordering in the workspace (the largest W of
 // the phases); slot Ws holds the opening.
 constexpr int kSweepLower = 0, kSweepClimb = 1, kSweepRest = 2;
+// Orderings the kernels of this search work on: all of the batch, or those the band kernel handed over.
+struct SweepItems {
+    const int *list;         // null: all
+    const int *n_list;
+};
+__device__ __forceinline__ int n_orderings(const SweepItems &it, int C) { return it.list ? *it.n_list : C; }
+__device__ __forceinline__ int ordering_of(const SweepItems &it, int n) { return it.list ? it.list[n] : n; }
+
 template <bool kFast, int kPhase, bool kForced>
 __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDev &od, const int32_t *cand_group,
                                                 const int32_t *cand_tp, int max_caps, int W, int Ws,
                                                 unsigned char *slots, int *first_idx, int64_t *lower,
                                                 unsigned char *ws, size_t per_group, int64_t n_dev, int *ticket,
-                                                size_t pos_bytes) {
+                                                size_t pos_bytes, const SweepItems &items) {
     constexpr bool kRest = kPhase == kSweepRest;
     // fast form: PP and PS (or Q), L + 1 entries each; then pos_bytes of cap positions
     extern __shared__ __align__(16) unsigned char mesh_lds[];
@@ -209,7 +222,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
     const int tid = threadIdx.x, nthreads = blockDim.x;
     const MeshSlice m = mesh_slice(ws, per_group, L, n_dev);
     const int64_t m_cap = tb.M;
-    const int n_items = od.C * W;
+    const int n_items = n_orderings(items, od.C) * W;
     const uint8_t *fq = kForced ? forced_q : nullptr;
     const int32_t *fo = kForced ? forced_off : nullptr;
 
@@ -219,7 +232,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
         __syncthreads();
         const int item = shared_int[0];
         if (item >= n_items) break;
-        const int c = item / W, j = item - c * W;
+        const int n = item / W, j = item - n * W, c = ordering_of(items, n);
         const SweepSlot opening = sweep_slot(slots, S_max, Ws, c, Ws);
         const SweepSlot mine = kPhase == kSweepLower ? opening : sweep_slot(slots, S_max, Ws, c, j);
         auto leave = [&](int state, int tried) {
@@ -398,9 +411,9 @@ __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh_h1f1b_sweep(TablesDev
                                                                        int Ws, unsigned char *slots, int *first_idx,
                                                                        int64_t *lower, unsigned char *ws,
                                                                        size_t per_group, int64_t n_dev, int *ticket,
-                                                                       size_t pos_bytes) {
+                                                                       size_t pos_bytes, SweepItems items) {
     mesh_sweep_body<kFast, kPhase, kForced>(tb, od, cand_group, cand_tp, max_caps, W, Ws, slots, first_idx, lower, ws,
-                                            per_group, n_dev, ticket, pos_bytes);
+                                            per_group, n_dev, ticket, pos_bytes, items);
 }
 
 // After the climb, one wavefront per ordering that the climb had to work on: the walker that found
@@ -408,10 +421,11 @@ __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh_h1f1b_sweep(TablesDev
 // the opening of the sweep; without one, the opening carries walker 0's verdict and count of caps
 // tried.
 __global__ __launch_bounds__(256) void k2_mesh_sweep_open(OrdDev od, int W, int Ws, unsigned char *slots,
-                                                          const int *first_idx) {
+                                                          const int *first_idx, SweepItems items) {
     const int lane = threadIdx.x & 63;
-    const int c = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (c >= od.C) return;
+    const int n = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (n >= n_orderings(items, od.C)) return;
+    const int c = ordering_of(items, n);
     const int S_max = od.S_max;
     const SweepSlot opening = sweep_slot(slots, S_max, Ws, c, Ws);
     if (opening.head->state != kSweepNone) return;        // malformed, or no plan even with the classic counts
@@ -432,19 +446,21 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_open(OrdDev od, int W, int 
     }
 }
 
-__global__ void k2_mesh_sweep_clear(int *ticket, int *first_idx, int C) {
+__global__ void k2_mesh_sweep_clear(int *counters, int *first_idx, int C) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c < 4) ticket[c] = 0;                    // one ticket per launch of the search
+    if (c < 8) counters[c] = 0;
     if (c < C) first_idx[c] = INT32_MAX;
 }
 
 // One wavefront per ordering: the best of its W + 1 kept plans goes to the outputs.
 __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev od, int W, int Ws, unsigned char *slots,
                                                           PlansDev out, int32_t *stage_group, int32_t *stage_tp,
-                                                          int32_t *warmup, int64_t *t_max_out, int32_t *n_caps) {
+                                                          int32_t *warmup, int64_t *t_max_out, int32_t *n_caps,
+                                                          SweepItems items) {
     const int lane = threadIdx.x & 63;
-    const int c = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (c >= od.C) return;
+    const int n = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (n >= n_orderings(items, od.C)) return;
+    const int c = ordering_of(items, n);
     const int S_max = od.S_max;
     int32_t *sp = out.splits + int64_t(c) * (S_max + 1), *df = out.dev_first + int64_t(c) * S_max;
     // a batch of candidates (fixed slicing) has no slicing to report
@@ -497,6 +513,198 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 }
 
 
+// The search on the ranges of mesh_band.h, one workgroup per ordering.  It tries few of the caps:
+//  * A plan with H-1F1B's counts under a cap t is a plan with the classic counts under t, so its sum is at
+//    least the classic least sum at t, which never grows with t.  With a plan of total T in hand and the
+//    classic sum c at a cap h, no cap t <= h can match T unless c + (B - 1) t <= T.  The upper end comes
+//    down from t_E with that bound until it holds still; the classic plan found there has its own
+//    bottleneck b, the classic sum is c for every cap in [b, h], and the candidate values there are tried
+//    from the lowest up, until the bound rules the rest out or the H-1F1B sum equals c (a higher cap in
+//    the interval then only costs more); the walk goes on below b.
+//  * When t_S itself has no plan, the lowest cap that can have one is searched for with the least-count
+//    form of the recurrence, whose verdict is exact and monotone in the cap, and the climb over the
+//    candidate values starts there.
+//  * How many values the sweep from t_S to t_E passes (n_caps, max_caps) is counted without trying them.
+// Measured on 48 orderings of 82 operators and 64 devices (about 1,000 values each between t_S and t_E, all
+// of them tried before, by up to 32 workgroups per ordering): 125-150 -> 1.0 ms per call, some 10 passes
+// per ordering, bound by the latency of one workgroup's passes one after the other.
+// The plan returned is the one the sweep over every value returns (least T, lower cap on equal T).  An
+// ordering whose climb fails at kMaxClimb values in a row (the recurrence keeps one continuation per state
+// and could miss plans that exist), that does not fit LDS or whose sums could pass 2^31 is handed over
+// to the kernels that try every value.
+constexpr int kMaxClimb = 64;
+
+__global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, int max_caps, PlansDev out,
+                                                      int32_t *stage_group, int32_t *stage_tp, int32_t *warmup,
+                                                      int64_t *t_max_out, int32_t *n_caps, BandArgs ba) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ int64_t scored[2];
+    __shared__ int item;
+    Band b(tb, ba.sh, lds_raw, ba.lo_tab, ba.hi_tab,
+           meshband::band_slice(ba.slices + size_t(blockIdx.x) * ba.per_group, ba.sh));
+    const int S_max = od.S_max, tid = threadIdx.x;
+    const int64_t m_less = int64_t(tb.M) - 1;
+    b.load_memory_sums();
+    b.find_least_cut();
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) item = atomicAdd(&ba.counters[0], 1);
+        __syncthreads();
+        const int c = item;
+        if (c >= od.C) break;
+        int32_t *sg = stage_group + int64_t(c) * S_max, *stp = stage_tp + int64_t(c) * S_max;
+        int32_t *wu = warmup + int64_t(c) * S_max;
+        auto fail = [&](int status, uint32_t tried) {
+            write_failed(out, c, S_max, status);
+            for (int s = tid; s < S_max; s += b.nthreads) { sg[s] = -1; stp[s] = -1; wu[s] = -1; }
+            if (tid == 0) {
+                t_max_out[c] = kInf;
+                if (n_caps) n_caps[c] = int32_t(tried);
+            }
+        };
+        auto hand_over = [&]() { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c; };
+        const int verdict = b.load(od.ord_S[c], od.ord_G[c], od.ord_group + int64_t(c) * od.G_max, S_max, od.G_max);
+        if (verdict == 1) { fail(HARP_CAND_INVALID, 0); continue; }
+        if (verdict == 2) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
+        if (verdict == 3) { hand_over(); continue; }
+        const int64_t opening = b.bracket();
+        if (opening < 0) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
+        const uint32_t more = uint32_t(max_caps) - 1u;          // values above t_S that may be tried
+        int64_t best_T = kInf, best_bott = kInf, classic = kInf, unused_T;
+        uint32_t t_S = 0, first = 0, best_cap = 0, values = 0, top = 0, lo = 0, hi = 0, unused = 0;
+        uint64_t step = 0;
+        uint32_t tried = 0;
+        bool run_out = false;
+        int bn = 0, climbed = 0, tries = 0;
+        auto keep = [&](uint32_t cap) {
+            b.find_h1_plan(cap);
+            b.score(scored, best_bott, unused_T);
+            b.write_slots(out, c, S_max, sg, stp);
+            const int t = Band::thread_id();
+            for (int s = t; s < S_max; s += b.nthreads) wu[s] = s < b.S ? b.warmup[s] : -1;
+        };
+        // where the search stands; every state waits for the result of one pass under `cap`
+        enum { kBottleneck, kAtBottleneck, kAtTop, kGallop, kBisect, kClimb, kUpper, kTry, kDone, kNoPlan, kOver };
+        int state = kBottleneck;
+        uint32_t cap = uint32_t(opening);
+        while (state < kDone) {
+            const int form = state == kBottleneck ? Band::kMinMax : state == kUpper ? Band::kSum
+                             : state == kAtTop || state == kGallop || state == kBisect ? Band::kAny : Band::kH1;
+            if (form != Band::kMinMax && !b.sums_fit(form == Band::kAny ? 0 : int64_t(cap))) { state = kOver; break; }
+            const int64_t v = b.run<Band::kMinMax | Band::kSum | Band::kH1 | Band::kAny>(form, cap);
+            const bool found = v != kInf;
+            bool opened = false, climb_on = false, try_on = false, upper_on = false;
+            if (state == kBottleneck) {
+                if (found) { t_S = uint32_t(v); cap = t_S; state = kAtBottleneck; }
+                else if (cap >= meshband::kTopCap) state = kNoPlan;
+                else cap = Band::raised(cap, tries++);
+            } else if (state == kAtBottleneck) {
+                if (found) {
+                    opened = true;
+                } else {
+                    top = b.largest_value();
+                    tried = 1;
+                    run_out = top > t_S && more > 0;
+                    if (!run_out) state = kNoPlan;
+                    else { cap = top; state = kAtTop; }
+                }
+            } else if (state == kAtTop) {
+                lo = t_S;
+                hi = top;
+                step = (t_S >> 4) + 1u;
+                if (!found) state = kNoPlan;
+                else if (lo + step < hi) { cap = lo + uint32_t(step); state = kGallop; }
+                else if (hi - lo > 1u + (hi >> 12)) { cap = lo + (hi - lo) / 2u; state = kBisect; }
+                else climb_on = true;
+            } else if (state == kGallop || state == kBisect) {
+                if (found) hi = cap; else lo = cap;
+                step *= 4;
+                if (state == kGallop && !found && lo + step < hi) cap = lo + uint32_t(step);
+                else if (hi - lo > 1u + (hi >> 12)) { cap = lo + (hi - lo) / 2u; state = kBisect; }
+                else climb_on = true;
+            } else if (state == kClimb) {
+                if (found) opened = true;
+                else { lo = cap; climb_on = true; }
+            } else if (state == kUpper) {
+                // no cap up to hi beats the best total unless the classic sum at hi leaves room for it
+                if (v > best_T) { state = kDone; break; }          // (without a plan included: cannot happen)
+                if (m_less > 0) {
+                    const int64_t lim = (best_T - v) / m_less;
+                    if (lim < int64_t(hi)) { hi = lim > 0 ? uint32_t(lim) : 0u; upper_on = true; }
+                }
+                if (!upper_on) {
+                    classic = v;
+                    b.find_plan(true, uint32_t(v), hi);
+                    int64_t bott;
+                    b.score(scored, bott, unused_T);
+                    bn = int(bott);
+                    cap = bott > int64_t(first) ? uint32_t(bott) - 1u : first;
+                    try_on = true;
+                }
+            } else {                                              // kTry
+                if (found) {
+                    const int64_t T = v + m_less * cap;
+                    if (T < best_T || (T == best_T && cap < best_cap)) {
+                        best_T = T;
+                        best_cap = cap;
+                        keep(cap);
+                    }
+                }
+                if (found && v == classic) { hi = bn > 0 ? uint32_t(bn) - 1u : 0u; upper_on = true; }
+                else try_on = true;
+            }
+            if (climb_on) {
+                cap = b.next_value(lo);
+                state = cap > top ? kNoPlan : ++climbed > kMaxClimb ? kOver : kClimb;
+            }
+            if (opened) {
+                first = best_cap = cap;
+                best_T = v + m_less * first;
+                keep(first);
+                const int64_t t_E = (best_T + m_less) / (m_less + 1);
+                if (!b.sums_fit(t_E)) { state = kOver; break; }
+                hi = uint32_t(t_E);
+                uint32_t last = t_S;
+                values = more == 0 ? 0u : b.count_values(t_S, hi, more, last);
+                if (values == more) {                              // max_caps cuts the sweep
+                    if (last < first) { state = kNoPlan; run_out = false; tried = 1u + more; break; }
+                    hi = last < hi ? last : hi;
+                }
+                upper_on = true;
+            }
+            if (try_on) {
+                // the next value of the interval in which the classic sum is `classic`
+                cap = b.next_value(cap);
+                const int64_t least_T = classic + m_less * cap;
+                if (cap > hi || least_T > best_T || (least_T == best_T && cap > best_cap)) {
+                    hi = bn > 0 ? uint32_t(bn) - 1u : 0u;
+                    upper_on = true;
+                } else {
+                    state = kTry;
+                }
+            }
+            if (upper_on) {
+                cap = hi;
+                state = hi > first ? kUpper : kDone;
+            }
+        }
+        if (state == kOver) { hand_over(); continue; }
+        if (state == kNoPlan) {
+            // caps tried: none without a bottleneck; all values, or as many as allowed
+            if (run_out) tried = 1u + b.count_values(t_S, top, more, unused);
+            fail(HARP_CAND_INFEASIBLE, tried);
+            continue;
+        }
+        if (tid == 0) {
+            out.bottleneck[c] = best_bott;
+            out.iter_time[c] = best_T;
+            out.status[c] = HARP_CAND_OK;
+            t_max_out[c] = int64_t(best_cap);
+            if (n_caps) n_caps[c] = int32_t(1u + values);
+        }
+    }
+}
+
 }  // namespace
 
 // cand_group / cand_tp not null: the batch holds candidates with a fixed slicing (od.ord_S = their
@@ -506,18 +714,35 @@ void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const i
                                   const int32_t *cand_tp, int max_caps, const PlansDev &out,
                                   int32_t *stage_group, int32_t *stage_tp, int32_t *warmup, int64_t *t_max_out,
                                   int32_t *n_caps, bool fast32, void *ws, int n_groups, int threads, int W_climb,
-                                  int W, int64_t total_devices, hipStream_t st) {
-    // layout: 256 bytes for the tickets | n_groups slices | (Ws + 1) kept plans per ordering | t_S per
+                                  int W, int64_t total_devices, int n_cu, hipStream_t st) {
+    // layout: what mesh_carve lays out, n_groups slices last | (Ws + 1) kept plans per ordering | t_S per
     // ordering | index of the first cap with a plan per ordering
-    int *ticket = static_cast<int *>(ws);
-    unsigned char *slices = static_cast<unsigned char *>(ws) + 256;
+    const MeshWorkspace w = mesh_carve(tb, od.S_max, od.C, ws);
     const size_t per_group = plan_mesh_ws_per_group(tb.L, od.S_max, total_devices);
     const int Ws = W_climb > W ? W_climb : W;
-    unsigned char *slots = slices + size_t(n_groups) * per_group;
+    unsigned char *slots = w.slices + size_t(n_groups) * per_group;
     int64_t *lower = reinterpret_cast<int64_t *>(slots + size_t(od.C) * size_t(Ws + 1) * sweep_slot_bytes(od.S_max));
     int *first_idx = reinterpret_cast<int *>(lower + od.C);
-    fast32 = fast32 && tb.L <= kMeshFastMaxL;
     const bool forced = cand_group != nullptr;
+    hipLaunchKernelGGL(k2_mesh_sweep_clear, dim3((od.C + 255) / 256), dim3(256), 0, st, w.counters, first_idx, od.C);
+    SweepItems items{nullptr, nullptr};
+    BandArgs ba;
+    int band_threads = 0;
+    if (fast32 && !forced && w.index_bytes != 0 &&
+        meshband::band_launch(tb, od, total_devices, meshband::kFormSweep, n_cu, band_threads, ba.sh)) {
+        launch_plan_index(tb, od.S_max, w.index, st);
+        ba.lo_tab = w.index;
+        ba.hi_tab = w.index + w.index_bytes / 4;
+        ba.slices = w.slices;
+        ba.per_group = per_group;
+        ba.counters = w.counters;
+        ba.redo = w.redo;
+        hipLaunchKernelGGL(k2_sweep_band, dim3(unsigned(od.C < n_groups ? od.C : n_groups)), dim3(band_threads),
+                           size_t(ba.sh.total), st, tb, od, max_caps, out, stage_group, stage_tp, warmup, t_max_out,
+                           n_caps, ba);
+        items = SweepItems{w.redo, w.counters + 1};
+    }
+    fast32 = fast32 && forced && tb.L <= kMeshFastMaxL;
     // cap positions: one uint16 per (row, start cut), kept in LDS when the largest item's rows fit
     // beside the static arrays in a workgroup's 64 KiB
     const size_t sums = fast32 ? 2 * size_t(tb.L + 1) * sizeof(int64_t) : 0;
@@ -526,26 +751,24 @@ void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const i
     if (sums + pos_bytes > (size_t(40) << 10)) pos_bytes = 0;
     const size_t lds = sums + pos_bytes;
     const dim3 block(threads);
-    auto grid_for = [&](long long items) { return dim3(unsigned(items < n_groups ? items : n_groups)); };
-    hipLaunchKernelGGL(k2_mesh_sweep_clear, dim3((od.C + 255) / 256), dim3(256), 0, st, ticket, first_idx, od.C);
+    auto grid_for = [&](long long n) { return dim3(unsigned(n < n_groups ? n : n_groups)); };
 #define HARP_SWEEP_PHASE(F, P, X, WALKERS, TICKET)                                                               \
     hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_mesh_h1f1b_sweep<F, P, X>), grid_for((long long)od.C * (WALKERS)), block,  \
-                       lds, st, tb, od, cand_group, cand_tp, max_caps, WALKERS, Ws, slots, first_idx, lower, slices, \
-                       per_group, total_devices, ticket + (TICKET), pos_bytes)
+                       lds, st, tb, od, cand_group, cand_tp, max_caps, WALKERS, Ws, slots, first_idx, lower,         \
+                       w.slices, per_group, total_devices, w.counters + (TICKET), pos_bytes, items)
 #define HARP_SWEEP_LAUNCH(F, X)                                                                                  \
-    HARP_SWEEP_PHASE(F, kSweepLower, X, 1, 0);                                                                    \
-    HARP_SWEEP_PHASE(F, kSweepClimb, X, W_climb, 1);                                                              \
+    HARP_SWEEP_PHASE(F, kSweepLower, X, 1, 2);                                                                    \
+    HARP_SWEEP_PHASE(F, kSweepClimb, X, W_climb, 3);                                                              \
     hipLaunchKernelGGL(k2_mesh_sweep_open, dim3((od.C + 3) / 4), dim3(256), 0, st, od, W_climb, Ws, slots,        \
-                       first_idx);                                                                                \
-    HARP_SWEEP_PHASE(F, kSweepRest, X, W, 2)
-    if (fast32 && forced) { HARP_SWEEP_LAUNCH(true, true); }
-    else if (fast32) { HARP_SWEEP_LAUNCH(true, false); }
+                       first_idx, items);                                                                         \
+    HARP_SWEEP_PHASE(F, kSweepRest, X, W, 4)
+    if (fast32) { HARP_SWEEP_LAUNCH(true, true); }
     else if (forced) { HARP_SWEEP_LAUNCH(false, true); }
     else { HARP_SWEEP_LAUNCH(false, false); }
 #undef HARP_SWEEP_LAUNCH
 #undef HARP_SWEEP_PHASE
     hipLaunchKernelGGL(k2_mesh_sweep_pick, dim3((od.C + 3) / 4), dim3(256), 0, st, tb, od, W, Ws, slots, out,
-                       stage_group, stage_tp, warmup, t_max_out, n_caps);
+                       stage_group, stage_tp, warmup, t_max_out, n_caps, items);
 }
 
 size_t plan_mesh_sweep_slot_bytes(int S_max) { return sweep_slot_bytes(S_max); }

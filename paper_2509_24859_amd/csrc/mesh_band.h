@@ -53,15 +53,39 @@ struct BandShape {
     int teams;                   // chains worked at once, by one wavefront each: 2, or 1 in a one-wavefront workgroup
     int S_cap;                   // min(S_max, L)
     int idx_pitch;               // feasibility index
-    uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_prow, o_reach, o_mem, o_chain, o_ok, o_col, o_small, o_rows,
+    uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_prow, o_reach, o_mem, o_chain, o_ok, o_col, o_small, o_rows,
         o_count, o_map, total;
 };
 
 constexpr int kMaxDevices = 2048;                // columns sit in LDS, 24 bytes each
 // forms of a launch: what the value rows hold
-constexpr int kFormMinMax = 0, kFormSum = 1, kFormH1 = 2;
+constexpr int kFormMinMax = 0, kFormSum = 1, kFormH1 = 2, kFormSweep = 3;
 bool band_shape(const TablesDev &tb, int S_max, int G_max, int64_t total_devices, int threads, int form, size_t budget,
                 BandShape &sh);
+
+// What the band kernels of a launch share: LDS shape, feasibility index, slices, and counters [0] ticket,
+// [1] orderings handed over to the int64 kernels, [2] .. tickets of those.
+struct BandArgs {
+    BandShape sh;
+    const uint16_t *lo_tab, *hi_tab;
+    unsigned char *slices;
+    size_t per_group;
+    int *counters;
+    int *redo;
+};
+
+// Workspace of a launch: counters | orderings handed over [C] | feasibility index | slices.
+struct MeshWorkspace {
+    int *counters, *redo;
+    uint16_t *index;
+    size_t index_bytes;
+    unsigned char *slices;
+    size_t before_slices;
+};
+MeshWorkspace mesh_carve(const TablesDev &tb, int S_max, int C, void *ws);
+// Threads and LDS of the band kernels for a batch; false when the batch is for the int64 kernels.
+bool band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int &threads,
+                 BandShape &sh);
 
 // Per workgroup, in the workspace slice: F, B [S_cap + 1][cols] uint16, first cell index less lowest
 // cut [S_cap + 1][cols] int32, value rows (uint32) or, H-1F1B, back-pointers (uint16).
@@ -102,6 +126,7 @@ struct Band {
     uint32_t *prow_at, *index_at;   // [K] first entry of a group's time rows (and reach rows), of its type's index rows
     uint32_t *link_at;           // [2 K] first entry of a link's row in the cut table: K links inside groups, K - 1 to the next
     uint32_t *cut_at;            // [cols] the same for the link behind a stage that ends at device d
+    uint32_t *use;               // [sets] largest group of a set: its degrees up to that size are candidate stages
     uint32_t *prow;              // [sets][n_tp][W]
     uint16_t *reach;             // [2][sets][n_tp][W] reach of a stage under a cap
     int64_t *mem;                // PP [W], PS [W] (H-1F1B form)
@@ -136,6 +161,7 @@ struct Band {
         link_at = index_at + sh.K_cap;
         cut_at = reinterpret_cast<uint32_t *>(lds + sh.o_cut_at);
         group_at = reinterpret_cast<uint16_t *>(lds + sh.o_group_at);
+        use = reinterpret_cast<uint32_t *>(lds + sh.o_use);
         prow = reinterpret_cast<uint32_t *>(lds + sh.o_prow);
         reach = reinterpret_cast<uint16_t *>(lds + sh.o_reach);
         mem = reinterpret_cast<int64_t *>(lds + sh.o_mem);
@@ -267,7 +293,10 @@ struct Band {
             for (int q = 0; q < map[k]; ++q) set += map[q] == q ? 1u : 0u;
             prow_at[k] = set * uint32_t(tb.n_tp) * uint32_t(sh.W);
         }
+        for (int x = tid; x < n_sets; x += nthreads) use[x] = 0;
         __syncthreads();
+        for (int k = tid; k < K; k += nthreads)
+            atomicMax(&use[prow_at[k] / uint32_t(tb.n_tp * sh.W)], uint32_t(offs[k + 1] - offs[k]));
         for (int d = 1 + tid; d < D; d += nthreads) cut_at[d] = link_at[link_of(d)];
         __syncthreads();
         return 0;
@@ -731,16 +760,9 @@ struct Band {
     }
     __device__ __forceinline__ int32_t least(int32_t a, int32_t b) const { return a < b ? a : b; }
     __device__ __forceinline__ uint32_t least(uint32_t a, uint32_t b) const { return a < b ? a : b; }
-    template <bool kCapped>
-    __device__ __forceinline__ int64_t value_pass(uint32_t t) {
-        if (rows_fit) return value_pass_in<kCapped, true>(t);
-        return value_pass_in<kCapped, false>(t);
-    }
-
     // All threads: the plan of the last value pass, value `v`, from the value rows: per stage the lowest
     // previous cut, then the smallest degree, that attain the cell's value (lanes over degrees and cuts).
-    template <bool kCapped>
-    __device__ __forceinline__ void find_plan(uint32_t v, uint32_t cap) {
+    __device__ __forceinline__ void find_plan(bool capped, uint32_t v, uint32_t cap) {
         const int lane = thread_id() & 63;
         if (wave == 0) {
             const int per = tb.n_tp <= 1 ? 64 : tb.n_tp <= 2 ? 32 : tb.n_tp <= 4 ? 16 : 8;   // lanes per degree
@@ -751,7 +773,7 @@ struct Band {
             for (int s = S - 1; s >= 0; --s) {
                 const int k = group_at[d2 - 1], n = in_flight(s), d = d2 - tp;
                 uint32_t want = v;
-                if (kCapped && s < S - 1) want = v - 2u * tb.CM[cut_at[d2] + uint32_t(i)];
+                if (capped && s < S - 1) want = v - 2u * tb.CM[cut_at[d2] + uint32_t(i)];
                 const bool in = q < tb.n_tp && d >= offs[k] && d >= s;
                 int jl = 1, jh = 0, off = 0;
                 if (in) {
@@ -767,9 +789,9 @@ struct Band {
                 for (int j = jl + jj; __any(in && j <= jh && key == 0xFFFFFFFFu); j += per) {
                     if (in && j <= jh && key == 0xFFFFFFFFu) {
                         const uint32_t time = (xi - p[j]) >> shift;
-                        if (time <= (kCapped ? cap : want)) {
+                        if (time <= (capped ? cap : want)) {
                             const uint32_t before = sl.hist[base[s] + off + j];
-                            const bool hit = kCapped ? before < kInfSum && before + time == want : before <= want;
+                            const bool hit = capped ? before < kInfSum && before + time == want : before <= want;
                             if (hit) { key = (uint32_t(j) << 3) | uint32_t(q); val = before; }
                         }
                     }
@@ -801,8 +823,8 @@ struct Band {
         __syncthreads();
     }
 
-    // The smallest bottleneck, its plan in cuts / slot_*; kInf when there is none.
-    __device__ __forceinline__ int64_t min_max() {
+    // All threads: the first cap to try the min-max pass under; -1 when no plan exists under any.
+    __device__ __forceinline__ int64_t bracket() {
         const int lane = thread_id() & 63;
         // A first guess: every group takes work in proportion to its speed.  And a bound: every plan cuts
         // somewhere on every link from a group to the next, no cheaper than at the operator of least output.
@@ -854,22 +876,15 @@ struct Band {
                 if (scal[w] != 0) good = at[w];
             for (int w = 0; w < sh.teams; ++w)
                 if (scal[w] == 0 && at[w] > bad) bad = at[w];
-            if (good < 0 && bad >= int64_t(kTopCap)) return kInf;         // no plan under any cap
+            if (good < 0 && bad >= int64_t(kTopCap)) return -1;           // no plan under any cap
             if (good == g) break;                                          // near enough
         }
-        uint32_t t = uint32_t(good);
-        for (int tries = 0;; ++tries) {
-            if (prepare(t)) {
-                const int64_t v = value_pass<false>(t);
-                if (v != kInf) {
-                    find_plan<false>(uint32_t(v), t);
-                    return v;
-                }
-            }
-            if (t >= kTopCap) return kInf;
-            const int64_t up = int64_t(t) + (t >> (tries < 3 ? 3 - tries : 0)) + 1;
-            t = up < int64_t(kTopCap) ? uint32_t(up) : kTopCap;
-        }
+        return good;
+    }
+    // the cap after one under which the min-max pass found no plan
+    static __device__ __forceinline__ uint32_t raised(uint32_t t, int tries) {
+        const int64_t up = int64_t(t) + (t >> (tries < 3 ? 3 - tries : 0)) + 1;
+        return up < int64_t(kTopCap) ? uint32_t(up) : kTopCap;
     }
 
     // The recurrence with H-1F1B warm-up counts (eq. dp_ni) in the ranges of the last prepare, suffix
@@ -878,22 +893,28 @@ struct Band {
     // at i (kInfSum beyond the cap) and the count that stage would have.  Ties: lowest end cut, then
     // smallest degree.  The memory test runs only for a cut that would be taken.  Returns the value of
     // (0, 0, 0) or kInf; back-pointers (cut | degree index << 13) go to the slice.
-    template <bool kLds>
+    //
+    // kCount: the least count of the first stage instead of the least sum (every row: the least count the
+    // stage in front could have).  A smaller count never hurts - it weakens every memory test in front of
+    // it - so this decides whether ANY plan exists under the cap, and it is monotone in the cap.
+    template <bool kCount, bool kLds>
     __device__ __forceinline__ int64_t h1_pass_in(uint32_t cap) {
+        constexpr uint32_t kNoCount = 0xFFFFu;
         const int tid = thread_id();
         const uint64_t e6 = uint64_t(cap) >> 6;
         const uint32_t th1 = uint32_t(e6 >> 1), th2 = uint32_t((uint64_t(cap) + e6) >> 1);   // 2c - e > 0; > cap
         const uint32_t m_cap = uint32_t(tb.M);
         const int64_t *PP = mem, *PS = mem + sh.W;
+        const int pitch = sh.row_cap + kRowPad;
         uint16_t *back = reinterpret_cast<uint16_t *>(sl.hist);
-        auto row_h = [&](int b) -> uint32_t * { return kLds ? rows + b * (sh.row_cap + kRowPad) : sl.spare_h + b * sl.row; };
-        auto row_n = [&](int b) -> uint16_t * { return kLds ? counts + b * (sh.row_cap + kRowPad) : sl.spare_n + b * sl.row; };
+        auto row_h = [&](int b) -> uint32_t * { return kLds ? rows + b * pitch : sl.spare_h + b * sl.row; };
+        auto row_n = [&](int b) -> uint16_t * { return kLds ? counts + b * pitch : sl.spare_n + b * sl.row; };
         int cur = 0;
         load_columns(S, request_column(S), 0, false);
         Column ahead = request_column(S - 1);
         if (tid == 0) { row_h(0)[0] = 0; row_n(0)[0] = 1; }    // behind the last stage: it launches one
         for (int s = S - 1; s >= 0; --s) {
-            const int n = in_flight(s);
+            const uint32_t index_at_n = index_n(in_flight(s));
             const int nxt = cur ^ 1;
             load_columns(s, ahead, nxt, kLds);
             __syncthreads();
@@ -909,39 +930,59 @@ struct Band {
                 const int k = group_at[d], end = offs[k + 1];
                 const int64_t mem_dev = tb.type_mem[type[k]];
                 const uint32_t cut = s > 0 ? tb.CM[cut_at[d] + uint32_t(i)] : 0u;
-                uint32_t best = kInfSum, best_n = 0;
+                const uint16_t *fits = hi_tab + (index_at_n + index_at[k] + uint32_t(i)), *far = reach_row(0, k) + i;
+                const uint32_t *p_k = time_row(k);
+                const int64_t ppi = PP[i], psi = PS[i];
+                uint32_t best = kInfSum, best_n = kCount ? kNoCount : 0u;
                 int best_j = 0, best_q = 0;
-                for (int q = 0; q < tb.n_tp; ++q) {
-                    const int tp = tb.tp[q], d1 = d + tp;
-                    if (d1 > end) break;
-                    const int lo = col_lo[cur * sh.cols + d1], hi = col_hi[cur * sh.cols + d1];
-                    const int fits = hi_tab[index_n(n) + index_at[k] + uint32_t(q * sh.idx_pitch + i)];
-                    const int jl = (i + 1) > lo ? (i + 1) : lo, jh = fits < hi ? fits : hi;
-                    const uint32_t *p = time_row(k) + q * sh.W;
-                    const int off = col_off[cur * sh.cols + d1];
-                    const uint32_t xi = p[i] - uint32_t(tp) + 1u;
-                    const int shift = tb.tp_shift[q];
-                    const int64_t capm = int64_t(tp) * mem_dev;
-                    for (int j = jl; j <= jh; ++j) {
-                        const uint32_t time = (p[j] - xi) >> shift;
-                        if (time > cap) break;
-                        const uint32_t v = prev_h[off + j] + time;
-                        if (v < best || (v == best && j < best_j)) {
-                            const uint32_t cnt = prev_n[off + j];
-                            if ((PP[j] - PP[i]) + int64_t(cnt) * (PS[j] - PS[i]) <= capm) {
-                                best = v; best_j = j; best_q = q; best_n = cnt;
+                for (int q0 = 0; q0 < tb.n_tp; q0 += 4) {
+                    int in_memory[4];                          // requested together, no branches in between
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) in_memory[u] = fits[(q0 + u < tb.n_tp ? q0 + u : q0) * sh.idx_pitch];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (q0 + u >= tb.n_tp) continue;
+                        const int q = q0 + u, tp = tb.tp[q], d1 = d + tp;
+                        if (d1 > end) continue;
+                        const int lo = col_lo[cur * sh.cols + d1], hi = col_hi[cur * sh.cols + d1];
+                        const int within = far[q * sh.W];
+                        const int jl = (i + 1) > lo ? (i + 1) : lo;
+                        int jh = in_memory[u] < within ? in_memory[u] : within;
+                        jh = jh < hi ? jh : hi;
+                        const uint32_t *p = p_k + q * sh.W;
+                        const int off = col_off[cur * sh.cols + d1];
+                        const uint32_t xi = p[i] - uint32_t(tp) + 1u;
+                        const int shift = tb.tp_shift[q];
+                        const int64_t capm = int64_t(tp) * mem_dev;
+                        for (int j = jl; j <= jh; ++j) {
+                            if (kCount) {
+                                const uint32_t cnt = prev_n[off + j];
+                                if (cnt < best_n && (PP[j] - ppi) + int64_t(cnt) * (PS[j] - psi) <= capm) best_n = cnt;
+                            } else {
+                                const uint32_t v = prev_h[off + j] + ((p[j] - xi) >> shift);
+                                if (v < best || (v == best && j < best_j)) {
+                                    const uint32_t cnt = prev_n[off + j];
+                                    if ((PP[j] - ppi) + int64_t(cnt) * (PS[j] - psi) <= capm) {
+                                        best = v; best_j = j; best_q = q; best_n = cnt;
+                                    }
+                                }
                             }
                         }
                     }
                 }
-                back[at + x] = uint16_t(uint32_t(best_j) | (uint32_t(best_q) << 13));
+                if (!kCount) back[at + x] = uint16_t(uint32_t(best_j) | (uint32_t(best_q) << 13));
                 if (s > 0) {
-                    const uint32_t h = best < kInfSum && cut <= cap ? best + 2u * cut : kInfSum;
                     const uint32_t cnt = 1u + (cut > th1 ? 1u : 0u) + (cut > th2 ? 1u : 0u) + best_n;
-                    next_h[x] = h < kInfSum ? h : kInfSum;
-                    next_n[x] = uint16_t(cnt < m_cap ? cnt : m_cap);
+                    const uint32_t cnt_m = cnt < m_cap ? cnt : m_cap;
+                    if (kCount) {
+                        next_n[x] = uint16_t(best_n != kNoCount && cut <= cap ? cnt_m : kNoCount);
+                    } else {
+                        const uint32_t h = best < kInfSum && cut <= cap ? best + 2u * cut : kInfSum;
+                        next_h[x] = h < kInfSum ? h : kInfSum;
+                        next_n[x] = uint16_t(cnt_m);
+                    }
                 } else {
-                    scal[4] = best;
+                    scal[4] = kCount ? (best_n != kNoCount ? 0u : kInfSum) : best;
                 }
             }
             __syncthreads();
@@ -950,9 +991,19 @@ struct Band {
         const uint32_t v = scal[4];
         return v >= kInfSum ? kInf : int64_t(v);
     }
-    __device__ __forceinline__ int64_t h1_pass(uint32_t cap) {
-        if (rows_fit) return h1_pass_in<true>(cap);
-        return h1_pass_in<false>(cap);
+    // One pass under the cap t in one of the four forms: the min-max value, the least sum, the least sum with
+    // H-1F1B's counts, or 0 when those admit a plan at all; kInf without one.  kForms: the forms a kernel
+    // uses, as a mask.  Called at one place of a kernel: every inlined copy of the passes costs registers
+    // everywhere else.
+    static constexpr int kMinMax = 1, kSum = 2, kH1 = 4, kAny = 8;
+    template <int kForms>
+    __device__ __forceinline__ int64_t run(int form, uint32_t t) {
+        if (!prepare(t)) return kInf;
+        if ((kForms & kMinMax) && form == kMinMax) return rows_fit ? value_pass_in<false, true>(t) : value_pass_in<false, false>(t);
+        if ((kForms & kSum) && form == kSum) return rows_fit ? value_pass_in<true, true>(t) : value_pass_in<true, false>(t);
+        if ((kForms & kH1) && form == kH1) return rows_fit ? h1_pass_in<false, true>(t) : h1_pass_in<false, false>(t);
+        if (kForms & kAny) return rows_fit ? h1_pass_in<true, true>(t) : h1_pass_in<true, false>(t);
+        return kInf;
     }
     // All threads: PP and PS into LDS, once per kernel
     __device__ __forceinline__ void load_memory_sums() {
@@ -1003,6 +1054,170 @@ struct Band {
             }
         }
         __syncthreads();
+    }
+
+    // Candidate caps of the ordering (section 5.2.4 (2)): every stage time of a listed group, a degree not
+    // above its size and an operator range; every transfer time of an inner cut inside a listed group
+    // or to the group after it.  All threads: visit(v) for every one in (a, b], repetitions included; a
+    // thread's `beyond` becomes the least value above b it has seen.
+    template <typename VisitFn>
+    __device__ __forceinline__ void visit_values(uint32_t a, uint32_t b, uint32_t &beyond, VisitFn visit) const {
+        const int tid = thread_id();
+        const int n = n_sets * tb.n_tp * L, top_step = 1 << (31 - __clz(L));
+        for (int x = tid; x < n; x += nthreads) {
+            const int r = x / L, j = x - r * L, set = r / tb.n_tp, q = r - set * tb.n_tp;
+            const uint32_t tp = uint32_t(tb.tp[q]);
+            if (tp > use[set]) continue;
+            const int shift = tb.tp_shift[q];
+            const uint32_t *p = prow + r * sh.W;
+            const uint32_t pj = p[j];
+            const uint64_t far = uint64_t(a) * tp + pj;        // time(j, i) <= a
+            const uint32_t target = far > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(far);
+            int i = j;
+            for (int step = top_step; step > 0; step >>= 1) {
+                const int nx = i + step;
+                i = nx <= L && p[nx <= L ? nx : L] <= target ? nx : i;
+            }
+            for (++i; i <= L; ++i) {
+                const uint32_t v = (p[i] - pj + tp - 1u) >> shift;
+                if (v > b) { beyond = v < beyond ? v : beyond; break; }
+                visit(v);
+            }
+        }
+        if (L < 2) return;
+        const int links = 2 * K - 1;
+        for (int x = tid; x < links * (L - 1); x += nthreads) {
+            const int l = x / (L - 1), i = 1 + x - l * (L - 1);
+            const uint32_t v = tb.CM[link_at[l] + uint32_t(i)];
+            if (v > b) beyond = v < beyond ? v : beyond;
+            else if (v > a) visit(v);
+        }
+    }
+    // All threads: a workgroup-wide minimum / sum through LDS
+    __device__ __forceinline__ uint32_t group_min(uint32_t v) {
+        const int tid = thread_id();
+#pragma unroll
+        for (int x = 32; x >= 1; x >>= 1) {
+            const uint32_t o = __shfl_xor(v, x, 64);
+            v = o < v ? o : v;
+        }
+        __syncthreads();
+        if (tid == 0) scal[7] = 0xFFFFFFFFu;
+        __syncthreads();
+        if ((tid & 63) == 0) atomicMin(&scal[7], v);
+        __syncthreads();
+        return scal[7];
+    }
+    // All threads: the smallest candidate cap above a; 0xFFFFFFFF when there is none.
+    __device__ __forceinline__ uint32_t next_value(uint32_t a) {
+        uint32_t beyond = 0xFFFFFFFFu;
+        visit_values(a, a, beyond, [](uint32_t) {});
+        return group_min(beyond);
+    }
+    // All threads: the largest candidate cap.
+    __device__ __forceinline__ uint32_t largest_value() {
+        const int tid = thread_id();
+        uint32_t most = 0;
+        for (int r = tid; r < n_sets * tb.n_tp; r += nthreads) {
+            const int set = r / tb.n_tp, q = r - set * tb.n_tp;
+            const uint32_t tp = uint32_t(tb.tp[q]);
+            const uint32_t v = (prow[r * sh.W + L] + tp - 1u) >> tb.tp_shift[q];
+            most = tp <= use[set] && v > most ? v : most;
+        }
+        const int links = L < 2 ? 0 : 2 * K - 1;
+        for (int x = tid; x < links * (L - 1); x += nthreads) {
+            const int l = x / (L - 1), i = 1 + x - l * (L - 1);
+            const uint32_t v = tb.CM[link_at[l] + uint32_t(i)];
+            most = v > most ? v : most;
+        }
+        return ~group_min(~most);
+    }
+    // All threads: how many distinct candidate caps lie in (a, b], counted up to `limit`; `last` becomes the
+    // limit-th of them when there are that many.  A bitmap over a window of values in LDS (the value rows,
+    // which no pass needs meanwhile), window after window, each starting at the next value there is.
+    __device__ __forceinline__ uint32_t count_values(uint32_t a, uint32_t b, uint32_t limit, uint32_t &last) {
+        const int tid = thread_id();
+        const uint32_t words = uint32_t(2 * (sh.row_cap + kRowPad)) & ~63u, span = words * 32u;
+        uint32_t *bits = rows;
+        uint32_t found = 0, from = a + 1u;
+        while (from <= b && found < limit) {
+            const uint32_t to = b - from < span ? b : from + (span - 1u);
+            __syncthreads();
+            for (uint32_t w = tid; w < words; w += nthreads) bits[w] = 0;
+            __syncthreads();
+            uint32_t beyond = 0xFFFFFFFFu;
+            visit_values(from - 1u, to, beyond, [&](uint32_t v) {
+                const uint32_t at = v - from;
+                atomicOr(&bits[at >> 5], 1u << (at & 31u));
+            });
+            const uint32_t next = group_min(beyond);       // (its barriers complete the bitmap)
+            uint32_t mine = 0;
+            for (uint32_t w = tid; w < words; w += nthreads) mine += __popc(bits[w]);
+#pragma unroll
+            for (int x = 32; x >= 1; x >>= 1) mine += __shfl_xor(mine, x, 64);
+            __syncthreads();
+            if (tid == 0) scal[7] = 0;
+            __syncthreads();
+            if ((tid & 63) == 0) atomicAdd(&scal[7], mine);
+            __syncthreads();
+            const uint32_t here = scal[7];
+            if (found + here >= limit) {
+                // the limit-th value: the words of the bitmap in order (rare, one wavefront)
+                __syncthreads();
+                if (tid < 64) {
+                    uint32_t left = limit - found;
+                    for (uint32_t w0 = 0; w0 < words; w0 += 64) {
+                        const uint32_t v = bits[w0 + tid];
+                        uint32_t inc = __popc(v);
+#pragma unroll
+                        for (int x = 1; x < 64; x <<= 1) {
+                            const uint32_t o = __shfl_up(inc, x, 64);
+                            if (tid >= x) inc += o;
+                        }
+                        const uint32_t all = __shfl(inc, 63, 64);
+                        if (left > all) { left -= all; continue; }
+                        const uint32_t before = inc - __popc(v);
+                        if (before < left && left <= inc) {
+                            uint32_t rest = v;
+                            for (uint32_t n = left - before; n > 1; --n) rest &= rest - 1u;
+                            scal[7] = from + (w0 + tid) * 32u + uint32_t(__ffs((int)rest) - 1);
+                        }
+                        break;
+                    }
+                }
+                __syncthreads();
+                last = scal[7];
+                return limit;
+            }
+            found += here;
+            if (next == 0xFFFFFFFFu || next > b) break;
+            from = next;
+        }
+        return found;
+    }
+
+    // All threads: the plan in cuts / slot_* to the outputs of ordering c.
+    __device__ __forceinline__ void write_slots(const PlansDev &out, int c, int S_max, int32_t *sg, int32_t *stp) const {
+        const int tid = thread_id();
+        int32_t *sp = out.splits + int64_t(c) * (S_max + 1), *df = out.dev_first + int64_t(c) * S_max;
+        for (int s = tid; s <= S_max; s += nthreads) sp[s] = s <= S ? cuts[s] : -1;
+        for (int s = tid; s < S_max; s += nthreads) {
+            sg[s] = s < S ? int32_t(slot_g[s]) : -1;
+            stp[s] = s < S ? tb.tp[slot_k[s]] : -1;
+            df[s] = s < S ? slot_first[s] : -1;
+        }
+    }
+    // All threads: bottleneck and iteration time of the plan in cuts / slot_* (scored: LDS, two entries).
+    __device__ __forceinline__ void score(int64_t *scored, int64_t &bott, int64_t &total) const {
+        const int lane = thread_id() & 63;
+        if (wave == 0) {
+            int64_t x, y;
+            wave_score_partition(tb, S, slot_g, slot_k, cuts, lane, x, y);
+            if (lane == 0) { scored[0] = x; scored[1] = y; }
+        }
+        __syncthreads();
+        bott = scored[0];
+        total = scored[1];
     }
 
     // sums of S stage and twice S transfer times under the cap, times the largest degree, stay below 2^31

@@ -71,3 +71,35 @@ def test_band_kernels_at_their_edges(harp, ctx, case):
     hg, _ = harp.plan_mesh_h1f1b(ctx, p, orders, caps, harp.PATH_FAST32)
     assert_plans_equal(hg, hw, "h1f1b")
     assert (hg.warmup == hw.warmup).all() and (hg.stage_tp == hw.stage_tp).all()
+
+
+@pytest.mark.parametrize("seed,L,ndev,tp,M", [(1, 33, (3, 4), (1, 2, 4), 9), (2, 64, (4, 4, 2), (1, 2), 5),
+                                              (3, 70, (2, 2, 2), (1, 2), 40), (4, 20, (8,), (1, 2, 4, 8), 12)],
+                         ids=lambda x: str(x).replace(" ", ""))
+def test_band_sweep_equals_the_exhaustive_one(harp, ctx, seed, L, ndev, tp, M):
+    """The bounded search over the cap against the kernels that try every cap (int64 path): plans that open
+    at the bottleneck, climbs to a larger cap (memory that only fits smaller counts), sweeps cut short."""
+    rng = np.random.default_rng(seed)
+    G = len(ndev)
+    climbs = 0
+    for tight in (10, 7, 5, 4):
+        bw = rng.integers(2, 40, size=(G, G))
+        bw = np.minimum(bw, bw.T)
+        bw[np.arange(G), np.arange(G)] = 60
+        p = simple_problem(np.zeros(L), M=M, T=2, G=G, ndev=ndev, tp=tp, gtype=[g % 2 for g in range(G)],
+                           fwd=rng.integers(1, 300, size=(2, L)), bwd=rng.integers(1, 300, size=(2, L)),
+                           act=rng.integers(100, 4000, size=L), params=rng.integers(0, 20, size=L),
+                           stash=rng.integers(1, 40, size=L), bw=bw)
+        p.type_mem_bytes[:] = tight * L * 10 // sum(ndev)
+        orders = W.make_orderings(p, seed, 5, G, min(L, sum(ndev)), 0, 12)
+        for max_caps in (1 << 20, 1, 2, 11):
+            fast, _ = harp.plan_mesh_h1f1b_sweep(ctx, p, orders, max_caps, harp.PATH_FAST32)
+            wide, _ = harp.plan_mesh_h1f1b_sweep(ctx, p, orders, max_caps, harp.PATH_GENERIC)
+            assert_plans_equal(fast, wide, "memory %d, at most %d caps" % (tight, max_caps))
+            for name in ("stage_group", "stage_tp", "warmup", "t_max", "n_caps"):
+                assert (getattr(fast, name) == getattr(wide, name)).all(), (tight, max_caps, name)
+        mm, _ = harp.plan_mesh(ctx, p, orders)
+        ok = mm.status == oracle.OK
+        at, _ = harp.plan_mesh_h1f1b(ctx, p, orders, np.where(ok, mm.bottleneck, -1))
+        climbs += int((ok & (at.status != oracle.OK)).sum())
+    assert climbs > 0
