@@ -12,10 +12,12 @@
 //
 // Two forms.  k2_mesh_band and k2_mesh_band_h1f1b run on the fused 32-bit rows, on the ranges of cuts
 // that some plan under the bottleneck (or cap) in question can have (mesh_band.h); k2_mesh and
-// k2_mesh_h1f1b fill the whole table in int64 (any degrees, any time width), one lane per target
-// cell (i, d'), rows and back-pointers in the workspace.  The int64 form serves tables without 32-bit
-// rows, more than 1,024 operators or 2,048 devices, and the orderings the band form hands over because
-// their sets of time rows do not fit its LDS or their sums could reach 2^31.
+// k2_mesh_h1f1b fill the whole table, one lane per target cell (i, d'), rows and back-pointers in the
+// workspace, with the passes of mesh_passes.h on the fused 32-bit rows (kFast) or on the int64 rows (any
+// degrees, any time width).  The int64 passes serve tables without 32-bit rows and more than 1,024
+// operators; the whole table on the 32-bit rows serves problems so small that finding the ranges costs more
+// than they save (whole_table), more than 2,048 devices, and the orderings the band form hands over
+// because their sets of time rows do not fit its LDS or their sums could reach 2^31.
 #include "mesh_band.h"
 #include "mesh_passes.h"
 
@@ -47,7 +49,7 @@ __device__ __forceinline__ int next_item(const MeshItems &it, int C) {
 // table is walked over the caps exactly as the exact search of the hot path walks them (first at
 // t_S, then down from ceil(T / B), skipping caps that the sums rule out; equal totals keep the lower
 // cap), which returns what the increasing sweep over every distinct stage cost returns.
-template <bool kExact>
+template <bool kExact, bool kFast>
 __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od, const PlansDev &out,
                                           int32_t *stage_group, int32_t *stage_tp, int32_t *n_passes,
                                           unsigned char *ws, size_t per_group, int64_t n_dev, const MeshItems &items) {
@@ -67,7 +69,7 @@ __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od,
 
     // all threads: thread 0 backtracks into cuts/slot_*, the first wave scores them
     auto backtrack_and_score = [&](int K, int S, int64_t &bott, int64_t &total) {
-        if (tid == 0) mesh_backtrack<false>(tb, m, offs, order, K, S, n_dev, cuts, slot_g, slot_k, slot_first);
+        if (tid == 0) mesh_backtrack<kFast>(tb, m, offs, order, K, S, n_dev, cuts, slot_g, slot_k, slot_first);
         __syncthreads();
         if (wave == 0) {
             int64_t b, t;
@@ -78,8 +80,12 @@ __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od,
         bott = scored[0];
         total = scored[1];
     };
+    extern __shared__ __align__(16) unsigned char mesh_lds[];      // kFast: a row of memory sums
+    int64_t *Q = reinterpret_cast<int64_t *>(mesh_lds);
     auto run_pass = [&](auto capped, int K, int S, int64_t cap) -> int64_t {
-        return mesh_pass<decltype(capped)::value>(tb, m, offs, order, group_at, K, S, n_dev, cap);
+        constexpr bool kCapped = decltype(capped)::value;
+        if constexpr (kFast) return mesh_pass_fast<kCapped>(tb, m, offs, order, group_at, Q, K, S, n_dev, cap);
+        else return mesh_pass<kCapped>(tb, m, offs, order, group_at, K, S, n_dev, cap);
     };
     auto keep = [&](int S) {
         for (int s = tid; s <= S; s += nthreads) kept_cuts[s] = cuts[s];
@@ -178,14 +184,15 @@ __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od,
     }
 }
 
-template <bool kExact>
+template <bool kExact, bool kFast>
 __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh(TablesDev tb, OrdDev od, PlansDev out,
                                                            int32_t *stage_group, int32_t *stage_tp,
                                                            int32_t *n_passes, unsigned char *ws,
                                                            size_t per_group, int64_t n_dev, MeshItems items) {
-    mesh_body<kExact>(tb, od, out, stage_group, stage_tp, n_passes, ws, per_group, n_dev, items);
+    mesh_body<kExact, kFast>(tb, od, out, stage_group, stage_tp, n_passes, ws, per_group, n_dev, items);
 }
 
+template <bool kFast>
 __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &od, const int64_t *t_max,
                                              const PlansDev &out, int32_t *stage_group, int32_t *stage_tp,
                                              int32_t *warmup, unsigned char *ws, size_t per_group, int64_t n_dev,
@@ -198,6 +205,8 @@ __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &
     __shared__ uint8_t slot_k[kMaxStages];
     __shared__ int32_t slot_first[kMaxStages];
     __shared__ int shared_int[2];
+    extern __shared__ __align__(16) unsigned char mesh_lds[];      // kFast: PP and PS, L + 1 entries each
+    int64_t *sums_lds = reinterpret_cast<int64_t *>(mesh_lds);
     const int L = tb.L, S_max = od.S_max;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthreads = blockDim.x;
     const MeshSlice m = mesh_slice(ws, per_group, L, n_dev);
@@ -241,9 +250,11 @@ __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &
             for (int k = 0; k < K; ++k)
                 for (int d = offs[k] + tid; d < offs[k + 1]; d += nthreads) group_at[d] = uint16_t(k);
         }
-        const int64_t sum = mesh_h1_pass(tb, m, offs, order, group_at, K, S, n_dev, cap);
+        int64_t sum;
+        if constexpr (kFast) sum = mesh_h1_pass_fast(tb, m, offs, order, group_at, sums_lds, K, S, n_dev, cap);
+        else sum = mesh_h1_pass(tb, m, offs, order, group_at, K, S, n_dev, cap);
         if (sum == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
-        if (tid == 0) mesh_h1_backtrack<false>(tb, m, offs, order, K, S, n_dev, cap, cuts, slot_g, slot_k, slot_first, count);
+        if (tid == 0) mesh_h1_backtrack<kFast>(tb, m, offs, order, K, S, n_dev, cap, cuts, slot_g, slot_k, slot_first, count);
         __syncthreads();
         int32_t *sp = out.splits + int64_t(c) * (S_max + 1);
         int32_t *df = out.dev_first + int64_t(c) * S_max;
@@ -266,12 +277,13 @@ __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &
     }
 }
 
+template <bool kFast>
 __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh_h1f1b(TablesDev tb, OrdDev od, const int64_t *t_max,
                                                                  PlansDev out, int32_t *stage_group,
                                                                  int32_t *stage_tp, int32_t *warmup,
                                                                  unsigned char *ws, size_t per_group,
                                                                  int64_t n_dev, MeshItems items) {
-    mesh_h1_body(tb, od, t_max, out, stage_group, stage_tp, warmup, ws, per_group, n_dev, items);
+    mesh_h1_body<kFast>(tb, od, t_max, out, stage_group, stage_tp, warmup, ws, per_group, n_dev, items);
 }
 
 // ------------------------------------------------------------------------------------ band form
@@ -499,7 +511,7 @@ bool meshband::band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_
     return band_shape(tb, od.S_max, od.G_max, total_devices, threads, form, budget, sh);
 }
 
-// Threads of an int64 workgroup: a stage has up to L x devices target cells, so small tables get many
+// Threads of a whole-table workgroup: a stage has up to L x devices target cells, so small tables get many
 // small workgroups (more orderings in flight), large ones few large workgroups (more lanes per ordering).
 int plan_mesh_threads(int L, int64_t total_devices, int C, int n_cu) {
     if (int64_t(L + 1) * (total_devices + 1) >= 16384) return kMeshMaxThreads;
@@ -524,17 +536,34 @@ size_t plan_mesh_ws_fixed(const TablesDev &tb, int S_max, int C) {
 
 namespace {
 
-// The band launch of a batch and, behind it, the int64 launch over what it handed over.  band(sh, ...)
-// and wide(items, ...) launch the two kernels.
-template <typename BandFn, typename WideFn>
+// Problems whose whole tables are worked faster than the ranges of their cuts are found.  A stage of the
+// whole table costs about (cuts) x (device offsets it can end at) x (degrees) x (cuts scanned), and the
+// offsets are at most devices - stages + 2 (every stage takes a device); the ranges cost a few serial steps
+// per stage whatever the size.  Measured over 70 random problems of both forms (whole table / ranges, us):
+// product 2,450: 76 / 367 (34 operators, 24 devices); 25,992: 72 / 157 (18, 30); 95,256: 277 / 272 (62, 12);
+// 154,880: 909 / 1144 (43, 40); 202,300: 208 / 115 (84, 14); 248,832: 383 / 291 (143, 8); 813,824: 2842 / 1397
+// (135, 16).  Below the line the ranges are ahead in 3 of 55 problems, by 1.4x at most; above it the whole
+// table in 4 of 15, by 1.6x at most.
+constexpr int64_t kWholeTable = 160000;
+bool whole_table(const TablesDev &tb, const OrdDev &od, int64_t total_devices) {
+    const int64_t stages = od.S_max < total_devices ? od.S_max : total_devices;
+    const int64_t cuts = tb.L + 1;
+    return cuts <= 1024 && cuts * cuts * (total_devices - stages + 2) * tb.n_tp <= kWholeTable;
+}
+
+// The band launch of a batch and, behind it, the whole-table launch over what it handed over.  band(sh, ...)
+// and whole(fast, items, ...) launch the two kernels.
+template <typename BandFn, typename WholeFn>
 void mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int form, void *ws, int n_groups, int threads,
-                 int64_t total_devices, int n_cu, hipStream_t st, BandFn band, WideFn wide) {
+                 int64_t total_devices, int n_cu, hipStream_t st, BandFn band, WholeFn whole) {
     const MeshWorkspace w = mesh_carve(tb, od.S_max, od.C, ws);
     const size_t per_group = plan_mesh_ws_per_group(tb.L, od.S_max, total_devices);
     hipLaunchKernelGGL(k2_mesh_clear, dim3(1), dim3(64), 0, st, w.counters);
     BandArgs ba;
     int band_threads = 0;
-    if (fast32 && w.index_bytes != 0 && meshband::band_launch(tb, od, total_devices, form, n_cu, band_threads, ba.sh)) {
+    const bool fast = fast32 && tb.L <= kMeshFastMaxL;       // (sums of memory in LDS)
+    if (fast32 && w.index_bytes != 0 && !whole_table(tb, od, total_devices) &&
+        meshband::band_launch(tb, od, total_devices, form, n_cu, band_threads, ba.sh)) {
         launch_plan_index(tb, od.S_max, w.index, st);
         ba.lo_tab = w.index;
         ba.hi_tab = w.index + w.index_bytes / 4;
@@ -543,10 +572,13 @@ void mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int form, v
         ba.counters = w.counters;
         ba.redo = w.redo;
         band(dim3(n_groups), dim3(band_threads), size_t(ba.sh.total), ba);
-        wide(dim3(n_groups < n_cu ? n_groups : n_cu), dim3(threads), MeshItems{w.counters + 2, w.redo, w.counters + 1},
-             w.slices, per_group);
+        whole(fast, dim3(n_groups < n_cu ? n_groups : n_cu), dim3(threads),
+              MeshItems{w.counters + 2, w.redo, w.counters + 1}, w.slices, per_group);
     } else {
-        wide(dim3(n_groups), dim3(threads), MeshItems{w.counters, nullptr, nullptr}, w.slices, per_group);
+        // as many workgroups as are resident
+        const long long resident = (long long)n_cu * (2048 / threads);
+        whole(fast, dim3(unsigned(n_groups < resident ? n_groups : resident)), dim3(threads),
+              MeshItems{w.counters, nullptr, nullptr}, w.slices, per_group);
     }
 }
 
@@ -564,13 +596,16 @@ void launch_plan_mesh(const TablesDev &tb, const OrdDev &od, const PlansDev &out
                         hipLaunchKernelGGL(k2_mesh_band<false>, grid, block, lds, st, tb, od, out, stage_group, stage_tp,
                                            n_passes, ba);
                 },
-                [&](dim3 grid, dim3 block, const MeshItems &items, unsigned char *slices, size_t per_group) {
-                    if (exact)
-                        hipLaunchKernelGGL(k2_mesh<true>, grid, block, 0, st, tb, od, out, stage_group, stage_tp,
-                                           n_passes, slices, per_group, total_devices, items);
-                    else
-                        hipLaunchKernelGGL(k2_mesh<false>, grid, block, 0, st, tb, od, out, stage_group, stage_tp,
-                                           n_passes, slices, per_group, total_devices, items);
+                [&](bool fast, dim3 grid, dim3 block, const MeshItems &items, unsigned char *slices, size_t per_group) {
+                    const size_t lds = fast ? size_t(tb.L + 1) * sizeof(int64_t) : 0;
+#define HARP_MESH_LAUNCH(E, F)                                                                                     \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_mesh<E, F>), grid, block, lds, st, tb, od, out, stage_group, stage_tp,   \
+                       n_passes, slices, per_group, total_devices, items)
+                    if (exact && fast) HARP_MESH_LAUNCH(true, true);
+                    else if (exact) HARP_MESH_LAUNCH(true, false);
+                    else if (fast) HARP_MESH_LAUNCH(false, true);
+                    else HARP_MESH_LAUNCH(false, false);
+#undef HARP_MESH_LAUNCH
                 });
 }
 
@@ -582,9 +617,14 @@ void launch_plan_mesh_h1f1b(const TablesDev &tb, const OrdDev &od, const int64_t
                     hipLaunchKernelGGL(k2_mesh_band_h1f1b, grid, block, lds, st, tb, od, t_max, out, stage_group,
                                        stage_tp, warmup, ba);
                 },
-                [&](dim3 grid, dim3 block, const MeshItems &items, unsigned char *slices, size_t per_group) {
-                    hipLaunchKernelGGL(k2_mesh_h1f1b, grid, block, 0, st, tb, od, t_max, out, stage_group, stage_tp,
-                                       warmup, slices, per_group, total_devices, items);
+                [&](bool fast, dim3 grid, dim3 block, const MeshItems &items, unsigned char *slices, size_t per_group) {
+                    const size_t lds = fast ? 2 * size_t(tb.L + 1) * sizeof(int64_t) : 0;
+                    if (fast)
+                        hipLaunchKernelGGL(k2_mesh_h1f1b<true>, grid, block, lds, st, tb, od, t_max, out, stage_group,
+                                           stage_tp, warmup, slices, per_group, total_devices, items);
+                    else
+                        hipLaunchKernelGGL(k2_mesh_h1f1b<false>, grid, block, lds, st, tb, od, t_max, out, stage_group,
+                                           stage_tp, warmup, slices, per_group, total_devices, items);
                 });
 }
 

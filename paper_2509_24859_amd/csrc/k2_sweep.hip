@@ -742,7 +742,7 @@ void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const i
                            n_caps, ba);
         items = SweepItems{w.redo, w.counters + 1};
     }
-    fast32 = fast32 && forced && tb.L <= kMeshFastMaxL;
+    fast32 = fast32 && tb.L <= kMeshFastMaxL;
     // cap positions: one uint16 per (row, start cut), kept in LDS when the largest item's rows fit
     // beside the static arrays in a workgroup's 64 KiB
     const size_t sums = fast32 ? 2 * size_t(tb.L + 1) * sizeof(int64_t) : 0;
@@ -762,7 +762,8 @@ void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const i
     hipLaunchKernelGGL(k2_mesh_sweep_open, dim3((od.C + 3) / 4), dim3(256), 0, st, od, W_climb, Ws, slots,        \
                        first_idx, items);                                                                         \
     HARP_SWEEP_PHASE(F, kSweepRest, X, W, 4)
-    if (fast32) { HARP_SWEEP_LAUNCH(true, true); }
+    if (fast32 && forced) { HARP_SWEEP_LAUNCH(true, true); }
+    else if (fast32) { HARP_SWEEP_LAUNCH(true, false); }
     else if (forced) { HARP_SWEEP_LAUNCH(false, true); }
     else { HARP_SWEEP_LAUNCH(false, false); }
 #undef HARP_SWEEP_LAUNCH

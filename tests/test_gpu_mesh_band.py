@@ -1,5 +1,6 @@
 """The band-limited kernels of the submesh planner at the edges of their tiles: 64 columns, 64 cuts per
-mask word, four degrees per step, value rows beyond LDS, and the orderings they hand over."""
+mask word, four degrees per step, value rows beyond LDS, the orderings they hand over, and the small
+problems that are worked as whole tables instead."""
 import numpy as np
 import pytest
 
@@ -40,7 +41,10 @@ CASES = [  # L, devices per group, degrees, stage counts, slow link, scale of th
     (64, (32, 32), (1, 2, 4, 8, 16, 32), (4, 7), True, 1, False),
     (65, (33, 32), (1, 2, 4, 8, 16), (6, 8), True, 1, False),
     (129, (64, 65), (1, 2, 4, 8, 16, 32, 64, 128), (4, 6), False, 1, False),
-    (30, (3, 2, 4), (1, 2, 4), (3, 5, 9), True, 1 << 14, False),       # sums beyond 2^31: handed over
+    (30, (3, 2, 4), (1, 2, 4), (3, 5, 9), True, 1 << 14, False),       # small: whole table, sums beyond 2^31
+    (20, (4, 4), (1, 2, 4), (3, 5), False, 1, False),                  # small: whole table
+    (59, (10, 12), (1,), (21, 22), False, 1, False),                   # one degree: whole table
+    (90, (10, 12, 9), (1, 2, 4), (9, 12), True, 1 << 13, False),        # sums beyond 2^31: handed over
     (900, (1, 1, 1, 1), (1, 2, 4, 8, 16, 32, 64, 128), (4,), False, 1, True),   # time rows beyond LDS: handed over
     (400, (32, 32), (1, 2, 4, 8, 16, 32), (8,), True, 1, False),       # value rows beyond LDS
 ]
