@@ -4,8 +4,8 @@
 // section 5.2.2 (eq. gpipe_cost_model), one wavefront per candidate, lanes over stages.
 // k3_score_fast is the same for tables with the 32-bit rows and at most 64 stages: the work is a
 // few gathers per candidate, so the kernel is a chain of memory round trips, and this form has
-// three of them where the general one has seven (everything whose address depends on nothing is
-// loaded first, for the next candidate while the current one is worked; the slot list is checked in
+// two of them, three for small batches, where the general one has seven (everything whose address
+// depends on nothing is loaded first, for the next candidate while the current one is worked; the slot list is checked in
 // registers; stage and transfer times come from the fused 32-bit rows, without divisions).
 // k4_argmin: final selection of section 5.2.3 (the min over evaluated candidates), lowest
 // candidate index on ties.  Both are O(C S) bytes of streaming work.
@@ -38,15 +38,57 @@ __global__ __launch_bounds__(64) void k3_score(TablesDev tb, CandDev cd, const i
     }
 }
 
-constexpr int kScoreWaves = 4;       // independent wavefronts per workgroup of k3_score_fast
+// Cross-lane steps on the DPP path of the vector unit, one instruction where a shuffle goes through LDS and
+// back (a score takes some forty of them, half of them in a chain).
+// Lanes a step has no source for read 0, so 0 has to be the neutral value.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp0(uint32_t v) {
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, kRows, 0xF, false));
+}
+constexpr int kRowShr = 0x110, kWaveShl1 = 0x130, kWaveShr1 = 0x138, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
 
-__global__ __launch_bounds__(kScoreWaves * 64) void k3_score_fast(TablesDev tb, CandDev cd, const int32_t *splits,
-                                                                  int64_t *bottleneck, int64_t *iter_time,
-                                                                  int32_t *status, uint32_t shift_packed) {
+// lane l: f over lanes 0 .. l; lane 63 holds the whole wavefront's
+template <typename F>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v, F f) {
+    v = f(v, dpp0<kRowShr + 1, 0xF>(v));
+    v = f(v, dpp0<kRowShr + 2, 0xF>(v));
+    v = f(v, dpp0<kRowShr + 4, 0xF>(v));
+    v = f(v, dpp0<kRowShr + 8, 0xF>(v));
+    v = f(v, dpp0<kRowBcast15, 0xA>(v));
+    v = f(v, dpp0<kRowBcast31, 0xC>(v));
+    return v;
+}
+template <typename F>
+__device__ __forceinline__ uint32_t wave_all(uint32_t v, F f) {
+    return uint32_t(__builtin_amdgcn_readlane(int(wave_scan(v, f)), 63));
+}
+__device__ __forceinline__ int64_t wave_up1(int64_t v) {
+    const uint32_t lo = dpp0<kWaveShr1, 0xF>(uint32_t(v)), hi = dpp0<kWaveShr1, 0xF>(uint32_t(uint64_t(v) >> 32));
+    return int64_t((uint64_t(hi) << 32) | lo);
+}
+
+constexpr int kScoreWaves = 4;        // independent wavefronts per workgroup of k3_score_fast
+constexpr int kStagedWaves = 16;      // the same when the workgroup keeps the memory sums in LDS
+constexpr size_t kStagedBytes = 64 << 10;    // LDS of such a workgroup at most: two are resident per CU
+
+// What bounds it: the issue of vector instructions and the lines a gather touches (one per cycle and CU; a
+// gather of a candidate's cuts touches as many lines as it has stages).  Of the six gathered operands of
+// a stage kStaged keeps the memory sums and the groups' limits in LDS, read once per workgroup.  Measured, with
+// shuffles, runs compared one by one and all operands gathered before: 262,144 candidates of up to 64
+// stages (512 operators, 32 groups) 209 -> 146 us, 1.4 TB/s of slots, cuts and results; 16,384 of them
+// 17.8 -> 11.4 us; 262,144 of up to 4 stages 99 -> 81 us.
+template <int kWaves, bool kStaged>
+__global__ __launch_bounds__(kWaves * 64) void k3_score_fast(TablesDev tb, CandDev cd, const int32_t *splits,
+                                                             int64_t *bottleneck, int64_t *iter_time,
+                                                             int32_t *status, uint32_t shift_packed) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63;
-    const int wave_id = blockIdx.x * kScoreWaves + (threadIdx.x >> 6), n_waves = gridDim.x * kScoreWaves;
+    const int wave_id = blockIdx.x * kWaves + (threadIdx.x >> 6), n_waves = gridDim.x * kWaves;
     const int S_max = cd.S_max, L = tb.L;
     const int64_t *PP = tb.PP(), *PS = tb.PS();
+    longlong2 *sums = reinterpret_cast<longlong2 *>(lds_raw);                 // [L + 1] running sums PP, PS
+    longlong2 *limit = sums + (L + 1);                                        // [G] bytes of one device, devices
+    auto plus = [](uint32_t a, uint32_t b) { return a + b; };
     // what a candidate's work starts from: its stage count and, lane s, slot s and the cuts s, s + 1
     struct First { int S, g, tp, j, i; };
     auto load_first = [&](int c) -> First {
@@ -63,6 +105,12 @@ __global__ __launch_bounds__(kScoreWaves * 64) void k3_score_fast(TablesDev tb, 
         return f;
     };
     First next = load_first(wave_id);
+    if (kStaged) {
+        for (int i = threadIdx.x; i <= L; i += kWaves * 64) sums[i] = longlong2{PP[i], PS[i]};
+        for (int g = threadIdx.x; g < tb.G; g += kWaves * 64)
+            limit[g] = longlong2{tb.type_mem[tb.group_type[g]], tb.group_ndev[g]};
+        __syncthreads();
+    }
     for (int c = wave_id; c < cd.C; c += n_waves) {
         const First f = next;
         next = load_first(c + n_waves);
@@ -76,54 +124,59 @@ __global__ __launch_bounds__(kScoreWaves * 64) void k3_score_fast(TablesDev tb, 
             if (tb.tp[q] == f.tp) k = q;
         // Second round trip: everything the checks and the score read, requested at once with indices
         // forced into range (a candidate that fails a check ignores what comes back).
-        const int g_next = __shfl_down(g, 1, 64);
+        const int g_next = int(dpp0<kWaveShl1, 0xF>(uint32_t(g))), g_prev = int(dpp0<kWaveShr1, 0xF>(uint32_t(g)));
         const bool slot_ok = g >= 0 && g < tb.G && k >= 0;
         const int gs = slot_ok ? g : 0, ks = slot_ok ? k : 0;
         const int gn = (g_next >= 0 && g_next < tb.G) ? g_next : 0;
         const int is = i < 0 ? 0 : (i > L ? L : i), js = j < 0 ? 0 : (j > L ? L : j);
-        const int ndev = tb.group_ndev[gs];
-        const int type = tb.group_type[gs];
         const uint32_t *p = tb.P32 + (int64_t(gs) * tb.n_tp + ks) * tb.pitch32;
         const uint32_t pi = p[is], pj = p[js];
         const uint32_t cut_here = tb.CM[(int64_t(gs) * tb.G + gn) * tb.pitch32 + is];
+        int64_t pp_i, ps_i, device_mem;
+        int ndev;
+        if (kStaged) {
+            const longlong2 at = sums[is], lim = limit[gs];
+            pp_i = at.x, ps_i = at.y, device_mem = lim.x, ndev = int(lim.y);
+        } else {
+            pp_i = PP[is], ps_i = PS[is], ndev = tb.group_ndev[gs];
+            device_mem = tb.type_mem[tb.group_type[gs]];
+        }
         // the running sums at a stage's lower cut are those at the upper cut of the stage before it
         // (cut 0, where they are 0, for the first): when the cuts are not a partition the candidate is
         // refused and the difference is not used
-        const int64_t pp_i = PP[is], ps_i = PS[is];
-        const int64_t pp_up = __shfl_up(pp_i, 1, 64), ps_up = __shfl_up(ps_i, 1, 64);
-        const int64_t dpp = pp_i - (lane > 0 ? pp_up : 0), dps = ps_i - (lane > 0 ? ps_up : 0);
+        const int64_t dpp = pp_i - wave_up1(pp_i), dps = ps_i - wave_up1(ps_i);
         if (S < 1 || S > S_max) {
             st = HARP_CAND_INVALID;
         } else if (__any(mine && !slot_ok)) {
             st = HARP_CAND_INVALID;
         } else {
             // runs of slots on one group: a group must not be entered twice, nor give more devices than it has
-            const int g_prev = __shfl_up(g, 1, 64);
             const bool start = mine && (lane == 0 || g_prev != g);
             const unsigned long long starts = __ballot(start);
             int bad = 0;
-            for (unsigned long long m = starts; m != 0; m &= m - 1) {
-                const int q = __ffsll((long long)m) - 1;
-                const int gq = __builtin_amdgcn_readlane(g, q);
-                if (start && q < lane && gq == g) bad = 1;
+            if (tb.G <= 64) {
+                // as many distinct groups as runs: two reductions instead of five instructions per run
+                auto either = [](uint32_t a, uint32_t b) { return a | b; };
+                const uint32_t bit = start ? 1u << (g & 31) : 0u;
+                int distinct = __popc(wave_all(g < 32 ? bit : 0u, either));
+                if (tb.G > 32) distinct += __popc(wave_all(g < 32 ? 0u : bit, either));
+                if (distinct != __popcll(starts)) bad = 1;
+            } else {
+                for (unsigned long long m = starts; m != 0; m &= m - 1) {
+                    const int q = __ffsll((long long)m) - 1;
+                    const int gq = __builtin_amdgcn_readlane(g, q);
+                    if (start && q < lane && gq == g) bad = 1;
+                }
             }
-            long long upto = mine ? f.tp : 0;              // devices of slots 0 .. lane
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const long long o = __shfl_up(upto, d, 64);
-                if (lane >= d) upto += o;
-            }
+            // devices of slots 0 .. lane: a degree is at most 2^16, 64 of them fit 32 bits
+            const uint32_t upto = wave_scan(mine ? uint32_t(f.tp) : 0u, plus);
             const unsigned long long later = lane < 63 ? starts >> (lane + 1) : 0ull;
             const int end = later != 0 ? lane + __ffsll((long long)later) - 1 : S - 1;    // last slot of this run
-            const long long upto_end = __shfl(upto, end, 64);
-            const long long before = __shfl_up(upto, 1, 64);
-            if (start && upto_end - (lane > 0 ? before : 0) > ndev) bad = 1;
-            if (__any(bad)) st = HARP_CAND_INVALID;
-        }
-        if (st == HARP_CAND_OK) {
+            const int used = __shfl(int(upto), end, 64) - int(dpp0<kWaveShr1, 0xF>(upto));
+            if (start && used > ndev) bad = 1;
             // the cuts rise strictly from 0 to L
-            int invalid = (lane == 0 && j != 0) || (lane == S - 1 && i != L) || (mine && i <= j);
-            if (__any(invalid)) st = HARP_CAND_INVALID;
+            if ((lane == 0 && j != 0) || (lane == S - 1 && i != L) || (mine && i <= j)) bad = 1;
+            if (__any(bad)) st = HARP_CAND_INVALID;
         }
         if (st == HARP_CAND_OK) {
             uint32_t time = 0, cu = 0;
@@ -132,22 +185,20 @@ __global__ __launch_bounds__(kScoreWaves * 64) void k3_score_fast(TablesDev tb, 
                 const int shift = int((shift_packed >> (4 * k)) & 15u);
                 if (lane < S - 1) cu = cut_here;
                 const int64_t n_inflight = (S - lane) < tb.M ? (S - lane) : tb.M;
-                if (dpp + n_inflight * dps > int64_t(f.tp) * tb.type_mem[type]) unfit = 1;
+                if (dpp + n_inflight * dps > int64_t(f.tp) * device_mem) unfit = 1;
                 time = (pi + (1u << shift) - 1u - pj) >> shift;
             }
             if (__any(unfit)) {
                 st = HARP_CAND_INFEASIBLE;
             } else {
-                uint32_t worst = time > cu ? time : cu;
-                int64_t single = int64_t(time) + 2 * int64_t(cu);
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) {
-                    const uint32_t ow = __shfl_xor(worst, d, 64);
-                    single += __shfl_xor(single, d, 64);
-                    worst = worst > ow ? worst : ow;
-                }
+                // time + 2 cu stays below 2^33: 64 of its lower 20 bits and of its upper 13 fit 32 bits each
+                const uint64_t single = uint64_t(time) + 2 * uint64_t(cu);
+                const uint32_t low = wave_all(uint32_t(single) & 0xFFFFFu, plus);
+                const uint32_t high = wave_all(uint32_t(single >> 20), plus);
+                const uint32_t worst = wave_all(time > cu ? time : cu,
+                                                [](uint32_t a, uint32_t b) { return a > b ? a : b; });
                 bott = int64_t(worst);
-                iter = single + int64_t(tb.M - 1) * int64_t(worst);
+                iter = (int64_t(high) << 20) + int64_t(low) + int64_t(tb.M - 1) * int64_t(worst);
             }
         }
         if (lane == 0) {
@@ -347,11 +398,22 @@ void launch_score(const TablesDev &tb, const CandDev &cd, const int32_t *splits,
     if (fast32 && cd.S_max <= 64) {
         uint32_t shift_packed = 0;
         for (int k = 0; k < tb.n_tp; ++k) shift_packed |= uint32_t(tb.tp_shift[k] & 15) << (4 * k);
-        int groups = n_cu * (32 / kScoreWaves);                  // as many wavefronts as the chip holds
+        // Reading the sums into LDS pays once every wavefront has two candidates: 16,384 candidates of up to
+        // 64 stages take 11.4 us with it, 16,383 without it 13.4 us.  Below that a workgroup would read more
+        // sums than its candidates use.
+        const size_t staged = (size_t(tb.L) + 1 + size_t(tb.G)) * sizeof(longlong2);
+        const int resident = n_cu * 32;                          // as many wavefronts as the chip holds
+        if (staged <= kStagedBytes && cd.C >= resident * 2) {
+            hipLaunchKernelGGL((k3_score_fast<kStagedWaves, true>), dim3(resident / kStagedWaves),
+                               dim3(kStagedWaves * 64), staged, st, tb, cd, splits, bottleneck, iter_time, status,
+                               shift_packed);
+            return;
+        }
+        int groups = resident / kScoreWaves;
         const int want = (cd.C + kScoreWaves - 1) / kScoreWaves;
         if (groups > want) groups = want;
-        hipLaunchKernelGGL(k3_score_fast, dim3(groups), dim3(kScoreWaves * 64), 0, st, tb, cd, splits, bottleneck,
-                           iter_time, status, shift_packed);
+        hipLaunchKernelGGL((k3_score_fast<kScoreWaves, false>), dim3(groups), dim3(kScoreWaves * 64), 0, st, tb, cd,
+                           splits, bottleneck, iter_time, status, shift_packed);
         return;
     }
     const int groups = cd.C < (1 << 20) ? cd.C : (1 << 20);

@@ -658,6 +658,52 @@ def test_score_checks_the_slot_lists_on_both_paths(harp, ctx):
             assert (b.cpu().numpy() == want[0]).all() and (t.cpu().numpy() == want[1]).all(), (S_max, path)
 
 
+@pytest.mark.parametrize("G,L,C", [(1, 4, 16384), (32, 90, 16384), (33, 90, 16391), (64, 4031, 16384), (65, 4031, 16384),
+                                   (65, 90, 16389), (64, 90, 16383)], ids=str)
+def test_score_of_large_batches(harp, ctx, G, L, C):
+    """The scorer's kernel for large batches at its edges: group sets of one and two words and beyond, sums
+    that just fit in LDS (L + 1 + G = 4,096) and do not, a last round that is nearly empty, the smallest
+    batch it takes on 256 CUs and one below; a quarter of the slot lists enter a group twice, use too many
+    devices or have cuts that do not rise."""
+    import torch
+    rng = np.random.default_rng(G * L)
+    S_max = 64
+    bw = rng.integers(2, 60, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    p = simple_problem(np.zeros(L), M=7, T=2, G=G, ndev=[4 + g % 3 for g in range(G)], tp=(1, 2, 4),
+                       fwd=rng.integers(1, 500, size=(2, L)), bwd=rng.integers(1, 900, size=(2, L)),
+                       act=rng.integers(0, 10**4, size=L), params=rng.integers(0, 1000, size=L),
+                       stash=rng.integers(0, 100, size=L), gtype=[g % 2 for g in range(G)],
+                       mem=[6000 * L // min(G, L), 4000 * L // min(G, L)], bw=bw)
+    lists, rows = [], []
+    for c in range(256):
+        S = int(rng.integers(1, min(S_max, L, 2 * G) + 1))
+        order = rng.permutation(G)
+        slots = [(int(order[s % G] if c % 8 == 1 else order[s // 2]), int(rng.choice([1, 2, 4 if c % 8 == 2 else 2])))
+                 for s in range(S)]
+        cut = np.sort(rng.choice(np.arange(1, L), size=S - 1, replace=False))
+        if c % 16 == 3 and S > 2:
+            cut[1] = cut[0]
+        lists.append(slots)
+        rows.append([0, *cut, L] + [-1] * (S_max - S))
+    at = rng.integers(0, 256, size=C)
+    few = cands_from_lists(lists, S_max=S_max)
+    want = oracle.score_1f1b(oracle.build_tables(p), few, np.array(rows, dtype=np.int32))
+    assert (want[2] == oracle.OK).any() and (want[2] != oracle.OK).any()
+    cands = W.Candidates(C, S_max, few.cand_S[at].copy(), few.cand_group.reshape(256, S_max)[at].copy(),
+                         few.cand_tp.reshape(256, S_max)[at].copy())
+    tables = harp.Tables(ctx, p)
+    assert tables.fast32
+    dc = harp.DeviceCandidates(ctx, cands)
+    sp = torch.from_numpy(np.array(rows, dtype=np.int32)[at].copy()).to(ctx.device)
+    b, t = (torch.full((C,), -7, dtype=torch.int64, device=ctx.device) for _ in range(2))
+    st = torch.full((C,), -7, dtype=torch.int32, device=ctx.device)
+    harp.harp_score_1f1b(ctx, tables, dc, sp, b, t, st)
+    torch.cuda.synchronize()
+    for got, name, expected in zip((b, t, st), ("bottleneck", "iter_time", "status"), want):
+        assert (got.cpu().numpy() == expected[at]).all(), name
+
+
 def test_argmin_parity(harp, ctx):
     import torch
     rng = np.random.default_rng(3)
