@@ -524,7 +524,8 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 //  * When t_S itself has no plan, the lowest cap that can have one is searched for with the least-count
 //    form of the recurrence, whose verdict is exact and monotone in the cap, and the climb over the
 //    candidate values starts there.
-//  * How many values the sweep from t_S to t_E passes (n_caps, max_caps) is counted without trying them.
+//  * How many values the sweep passes from t_S to t_E, or to the first cap with a plan where that is higher
+//    (n_caps, max_caps), is counted without trying them.
 // Measured on 48 orderings of 82 operators and 64 devices (about 1,000 values each between t_S and t_E, all
 // of them tried before, by up to 32 workgroups per ordering): 125-150 -> 1.0 ms per call, some 10 passes
 // per ordering, bound by the latency of one workgroup's passes one after the other.
@@ -664,8 +665,9 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                 const int64_t t_E = (best_T + m_less) / (m_less + 1);
                 if (!b.sums_fit(t_E)) { state = kOver; break; }
                 hi = uint32_t(t_E);
+                // the climb passed every value up to `first`, which is above t_E when it exceeds the plan's sum by M
                 uint32_t last = t_S;
-                values = more == 0 ? 0u : b.count_values(t_S, hi, more, last);
+                values = more == 0 ? 0u : b.count_values(t_S, hi > first ? hi : first, more, last);
                 if (values == more) {                              // max_caps cuts the sweep
                     if (last < first) { state = kNoPlan; run_out = false; tried = 1u + more; break; }
                     hi = last < hi ? last : hi;

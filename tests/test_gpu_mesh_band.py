@@ -7,7 +7,8 @@ import pytest
 import oracle
 from paper_2509_24859_amd import workloads as W
 
-from helpers import assert_plans_equal, oracle_plan_mesh_h1f1b_threaded, oracle_plan_mesh_threaded, simple_problem
+from helpers import (assert_plans_equal, oracle_plan_mesh_h1f1b_sweep_threaded, oracle_plan_mesh_h1f1b_threaded,
+                     oracle_plan_mesh_threaded, simple_problem)
 
 pytestmark = pytest.mark.gpu
 
@@ -107,3 +108,49 @@ def test_band_sweep_equals_the_exhaustive_one(harp, ctx, seed, L, ndev, tp, M):
         at, _ = harp.plan_mesh_h1f1b(ctx, p, orders, np.where(ok, mm.bottleneck, -1))
         climbs += int((ok & (at.status != oracle.OK)).sum())
     assert climbs > 0
+
+
+def _opening_beyond_the_end(seed):
+    """Problems whose memory only fits once a large cap has lowered the warm-up counts: such a cap can be
+    above t_E = ceil(T / M) of its own plan (it exceeds that plan's sum by M or more)."""
+    if seed < 0:
+        rng, L = np.random.default_rng(0), 24
+        p = simple_problem(np.zeros(L), M=4, G=1, ndev=(4,), tp=(1, 2), fwd=rng.integers(30, 60, size=(1, L)),
+                           bwd=np.zeros((1, L), dtype=np.int64), act=np.full(L, 5000), stash=[4] + [0] * (L - 1), mem=[5],
+                           bw=[[1000]], ar_count=0)
+        return p, W.orderings_from_lists([(2, [0])])
+    rng = np.random.default_rng(seed)
+    L, ndev = int(rng.integers(5, 14)), ((1, 1), (2, 1), (2, 2), (3,))[seed % 4]
+    G, M = len(ndev), int(rng.integers(2, 6))
+    bw = rng.integers(2, 5, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 60
+    p = simple_problem(np.zeros(L), M=M, T=2, G=G, ndev=ndev, tp=(1, 2) if max(ndev) > 1 else (1,),
+                       gtype=[g % 2 for g in range(G)], fwd=rng.integers(1, 6, size=(2, L)),
+                       bwd=rng.integers(1, 6, size=(2, L)), params=rng.integers(0, 4, size=L),
+                       act=np.where(rng.random(L) < 0.6, rng.integers(0, 7, size=L), rng.integers(300, 900, size=L)),
+                       stash=rng.integers(0, 10, size=L), bw=bw)
+    p.type_mem_bytes[:] = rng.integers(4, 10) * L // sum(ndev)
+    return p, W.make_orderings(p, seed, 5, 2, min(L, sum(ndev)), 0, 4)
+
+
+def test_band_sweep_opening_beyond_its_own_end(harp, ctx):
+    """Every cap up to the first one with a plan counts as tried, also those above the t_E which that plan
+    fixes, and max_caps cuts the climb to it: against the oracle."""
+    beyond = 0
+    for seed in range(-1, 40):
+        p, orders = _opening_beyond_the_end(seed)
+        ot = oracle.build_tables(p)
+        full = oracle_plan_mesh_h1f1b_sweep_threaded(ot, orders)
+        limits = {1, 1 << 20}
+        for n in full.n_caps[full.status == oracle.OK]:
+            limits.update(int(x) for x in range(max(1, n - 4), n + 2))
+        for max_caps in sorted(limits):
+            want = oracle_plan_mesh_h1f1b_sweep_threaded(ot, orders, max_caps)
+            got, _ = harp.plan_mesh_h1f1b_sweep(ctx, p, orders, max_caps, harp.PATH_FAST32)
+            assert_plans_equal(got, want, "seed %d, at most %d caps" % (seed, max_caps))
+            for name in ("stage_group", "stage_tp", "warmup", "t_max", "n_caps"):
+                assert (getattr(got, name) == getattr(want, name)).all(), (seed, max_caps, name)
+        # a sweep that opens above its own end has nothing left to try
+        beyond += int(((full.status == oracle.OK) & (full.t_max > -(-full.iter_time // p.M))).sum())
+    assert beyond >= 5
