@@ -484,11 +484,11 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     sh.o_reach = take(size_t(sh.set_cap) * per_set / 2);
     // bytes per cell: two value rows; or one and the key rows; or two rows of sums and counts; and the map
     const size_t value_rows = sums && tb.n_tp > 1 ? 1 + size_t(tb.n_tp) : 2;
-    const size_t per_cell = value_rows * 4 + (h1 ? 4 : 0) + 2, lds_cu = size_t(160) << 10;
+    const size_t per_cell = value_rows * 4 + (h1 ? 4 : 0) + 2;
     size_t room = budget > off ? budget - off : 0;
     const size_t want = size_t(sh.K_cap) > 1024 ? size_t(sh.K_cap) : 1024;        // the map also numbers the sets
     if (room < want * per_cell + 128) room = want * per_cell + 128;
-    if (off + room > lds_cu) return false;
+    if (off + room > kBandLds) return false;
     size_t cells = (room - 128) / per_cell;
     const size_t all = size_t(sh.cols) * sh.W;
     cells = cells > all && all >= want ? all : cells;
@@ -498,7 +498,7 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     sh.o_count = take(h1 ? 2 * row * 2 : 0);
     sh.o_map = take(size_t(sh.row_cap) * 2);
     sh.total = uint32_t(off);
-    return off <= lds_cu;
+    return off <= kBandLds;
 }
 
 // Workgroups of the band kernels: a batch of at most one ordering per CU gets the whole CU's LDS and

@@ -58,6 +58,9 @@ struct BandShape {
 };
 
 constexpr int kMaxDevices = 2048;                // columns sit in LDS, 24 bytes each
+// LDS of a CU, less what the band kernels hold statically (272 to 288 bytes: the ordering drawn, a score, and the
+// scratch of __syncthreads_or), which counts against the same limit
+constexpr size_t kBandLds = (size_t(160) << 10) - 1024;
 // forms of a launch: what the value rows hold
 constexpr int kFormMinMax = 0, kFormSum = 1, kFormH1 = 2, kFormSweep = 3;
 bool band_shape(const TablesDev &tb, int S_max, int G_max, int64_t total_devices, int threads, int form, size_t budget,

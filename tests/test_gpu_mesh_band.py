@@ -154,3 +154,34 @@ def test_band_sweep_opening_beyond_its_own_end(harp, ctx):
         # a sweep that opens above its own end has nothing left to try
         beyond += int(((full.status == oracle.OK) & (full.t_max > -(-full.iter_time // p.M))).sum())
     assert beyond >= 5
+
+
+# (form, L, types, groups, degrees, S_max, devices per group): LDS of the band kernels within 288 bytes of 160 KiB
+FULL_LDS = [("min-max", 882, 6, 3, 7, 50, 22), ("exact", 318, 7, 6, 8, 16, 3), ("exact", 528, 8, 8, 4, 32, 8),
+            ("h1f1b", 349, 7, 7, 7, 202, 1), ("sweep", 603, 5, 4, 6, 57, 1)]
+
+
+@pytest.mark.parametrize("form,L,T,G,n_tp,S_max,n", FULL_LDS, ids=lambda x: str(x))
+def test_shapes_that_would_fill_the_lds(harp, ctx, form, L, T, G, n_tp, S_max, n):
+    """Shapes whose dynamic LDS alone would fit a compute unit, and not together with what the band kernels
+    hold statically: they run on the whole-table kernels.  Against the int64 path."""
+    rng = np.random.default_rng(L)
+    bw = rng.integers(20, 60, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 500
+    p = simple_problem(np.zeros(L), M=6, T=T, G=G, ndev=(n,) * G, tp=[1 << k for k in range(n_tp)],
+                       gtype=[g % T for g in range(G)], fwd=rng.integers(1, 900, size=(T, L)),
+                       bwd=rng.integers(1, 900, size=(T, L)), act=rng.integers(100, 3000, size=L), bw=bw)
+    assert harp.Tables(ctx, p).fast32
+    S = G if n == 1 else min(G * n, S_max)
+    orders = W.orderings_from_lists([(S, list(range(G))), (S, list(range(G))[::-1])], S_max=S_max)
+    if form in ("min-max", "exact"):
+        got, want = (harp.plan_mesh(ctx, p, orders, form == "exact", path)[0] for path in (harp.PATH_FAST32, harp.PATH_GENERIC))
+    elif form == "h1f1b":
+        caps = harp.plan_mesh(ctx, p, orders)[0].bottleneck
+        got, want = (harp.plan_mesh_h1f1b(ctx, p, orders, caps, path)[0] for path in (harp.PATH_FAST32, harp.PATH_GENERIC))
+    else:
+        got, want = (harp.plan_mesh_h1f1b_sweep(ctx, p, orders, 9, path)[0] for path in (harp.PATH_FAST32, harp.PATH_GENERIC))
+    assert (want.status == oracle.OK).all()
+    assert_plans_equal(got, want, form)
+    assert (got.stage_tp == want.stage_tp).all() and (got.stage_group == want.stage_group).all()
