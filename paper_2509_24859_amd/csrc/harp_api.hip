@@ -575,10 +575,9 @@ int plan_mesh_common(harp_ctx *ctx, harp_tables *t, const harp_orderings *od, co
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     const OrdDev o = { od->C, od->G_max, od->S_max, od->ord_S, od->ord_G, od->ord_group };
     const PlansDev pl = { out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
-    launch_plan_mesh(t->dev, o, pl, stage_group, stage_tp, n_passes, exact, use_fast_rows(ctx, t), workspace, groups,
+    e = launch_plan_mesh(t->dev, o, pl, stage_group, stage_tp, n_passes, exact, use_fast_rows(ctx, t), workspace, groups,
                      threads, t->total_devices, ctx->n_cu,
                      static_cast<hipStream_t>(hip_stream));
-    e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the submesh planner kernel");
     return HARP_OK;
 }
@@ -619,9 +618,8 @@ int harp_plan_mesh_h1f1b_batch(harp_ctx *ctx, harp_tables *t, const harp_orderin
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     const OrdDev o = { od->C, od->G_max, od->S_max, od->ord_S, od->ord_G, od->ord_group };
     const PlansDev pl = { out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
-    launch_plan_mesh_h1f1b(t->dev, o, t_max, pl, stage_group, stage_tp, warmup, use_fast_rows(ctx, t), workspace, groups,
+    e = launch_plan_mesh_h1f1b(t->dev, o, t_max, pl, stage_group, stage_tp, warmup, use_fast_rows(ctx, t), workspace, groups,
                            threads, t->total_devices, ctx->n_cu, static_cast<hipStream_t>(hip_stream));
-    e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the submesh H-1F1B kernel");
     return HARP_OK;
 }
@@ -651,10 +649,9 @@ int harp_plan_mesh_h1f1b_sweep_batch(harp_ctx *ctx, harp_tables *t, const harp_o
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     const OrdDev o = { od->C, od->G_max, od->S_max, od->ord_S, od->ord_G, od->ord_group };
     const PlansDev pl = { out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
-    launch_plan_mesh_h1f1b_sweep(t->dev, o, nullptr, nullptr, max_caps, pl, stage_group, stage_tp, warmup, t_max_out, n_caps,
+    e = launch_plan_mesh_h1f1b_sweep(t->dev, o, nullptr, nullptr, max_caps, pl, stage_group, stage_tp, warmup, t_max_out, n_caps,
                                  use_fast_rows(ctx, t), workspace, lay.groups, lay.threads, lay.W_climb, lay.W, t->total_devices,
                                  ctx->n_cu, static_cast<hipStream_t>(hip_stream));
-    e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the submesh H-1F1B sweep kernel");
     return HARP_OK;
 }
@@ -689,10 +686,9 @@ int harp_plan_h1f1b_sweep_batch(harp_ctx *ctx, harp_tables *t, const harp_candid
     if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
     const OrdDev o = { cd->C, 1, cd->S_max, cd->cand_S, nullptr, nullptr };
     const PlansDev pl = { out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
-    launch_plan_mesh_h1f1b_sweep(t->dev, o, cd->cand_group, cd->cand_tp, max_caps, pl, nullptr, nullptr, warmup,
+    e = launch_plan_mesh_h1f1b_sweep(t->dev, o, cd->cand_group, cd->cand_tp, max_caps, pl, nullptr, nullptr, warmup,
                                  t_max_out, n_caps, use_fast_rows(ctx, t), workspace, lay.groups, lay.threads, lay.W_climb, lay.W,
                                  t->total_devices, ctx->n_cu, static_cast<hipStream_t>(hip_stream));
-    e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the search over the cap");
     return HARP_OK;
 }

@@ -552,9 +552,10 @@ bool whole_table(const TablesDev &tb, const OrdDev &od, int64_t total_devices) {
 }
 
 // The band launch of a batch and, behind it, the whole-table launch over what it handed over.  band(sh, ...)
-// and whole(fast, items, ...) launch the two kernels.
+// and whole(fast, items, ...) launch the two kernels.  The status of the first launch is read before the second
+// can replace it: without the first the second has nothing to take over.
 template <typename BandFn, typename WholeFn>
-void mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int form, void *ws, int n_groups, int threads,
+hipError_t mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int form, void *ws, int n_groups, int threads,
                  int64_t total_devices, int n_cu, hipStream_t st, BandFn band, WholeFn whole) {
     const MeshWorkspace w = mesh_carve(tb, od.S_max, od.C, ws);
     const size_t per_group = plan_mesh_ws_per_group(tb.L, od.S_max, total_devices);
@@ -572,6 +573,8 @@ void mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int form, v
         ba.counters = w.counters;
         ba.redo = w.redo;
         band(dim3(n_groups), dim3(band_threads), size_t(ba.sh.total), ba);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
         whole(fast, dim3(n_groups < n_cu ? n_groups : n_cu), dim3(threads),
               MeshItems{w.counters + 2, w.redo, w.counters + 1}, w.slices, per_group);
     } else {
@@ -580,14 +583,15 @@ void mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int form, v
         whole(fast, dim3(unsigned(n_groups < resident ? n_groups : resident)), dim3(threads),
               MeshItems{w.counters, nullptr, nullptr}, w.slices, per_group);
     }
+    return hipGetLastError();
 }
 
 }  // namespace
 
-void launch_plan_mesh(const TablesDev &tb, const OrdDev &od, const PlansDev &out, int32_t *stage_group,
+hipError_t launch_plan_mesh(const TablesDev &tb, const OrdDev &od, const PlansDev &out, int32_t *stage_group,
                       int32_t *stage_tp, int32_t *n_passes, bool exact, bool fast32, void *ws, int n_groups,
                       int threads, int64_t total_devices, int n_cu, hipStream_t st) {
-    mesh_launch(tb, od, fast32, exact ? meshband::kFormSum : meshband::kFormMinMax, ws, n_groups, threads, total_devices, n_cu, st,
+    return mesh_launch(tb, od, fast32, exact ? meshband::kFormSum : meshband::kFormMinMax, ws, n_groups, threads, total_devices, n_cu, st,
                 [&](dim3 grid, dim3 block, size_t lds, const BandArgs &ba) {
                     if (exact)
                         hipLaunchKernelGGL(k2_mesh_band<true>, grid, block, lds, st, tb, od, out, stage_group, stage_tp,
@@ -609,10 +613,10 @@ void launch_plan_mesh(const TablesDev &tb, const OrdDev &od, const PlansDev &out
                 });
 }
 
-void launch_plan_mesh_h1f1b(const TablesDev &tb, const OrdDev &od, const int64_t *t_max, const PlansDev &out,
+hipError_t launch_plan_mesh_h1f1b(const TablesDev &tb, const OrdDev &od, const int64_t *t_max, const PlansDev &out,
                             int32_t *stage_group, int32_t *stage_tp, int32_t *warmup, bool fast32, void *ws,
                             int n_groups, int threads, int64_t total_devices, int n_cu, hipStream_t st) {
-    mesh_launch(tb, od, fast32, meshband::kFormH1, ws, n_groups, threads, total_devices, n_cu, st,
+    return mesh_launch(tb, od, fast32, meshband::kFormH1, ws, n_groups, threads, total_devices, n_cu, st,
                 [&](dim3 grid, dim3 block, size_t lds, const BandArgs &ba) {
                     hipLaunchKernelGGL(k2_mesh_band_h1f1b, grid, block, lds, st, tb, od, t_max, out, stage_group,
                                        stage_tp, warmup, ba);

@@ -712,7 +712,7 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
 // cand_group / cand_tp not null: the batch holds candidates with a fixed slicing (od.ord_S = their
 // stage counts), and stage_group / stage_tp may be null.  W_climb and W walkers per ordering in the
 // climb and in the rest of the sweep.
-void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const int32_t *cand_group,
+hipError_t launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const int32_t *cand_group,
                                   const int32_t *cand_tp, int max_caps, const PlansDev &out,
                                   int32_t *stage_group, int32_t *stage_tp, int32_t *warmup, int64_t *t_max_out,
                                   int32_t *n_caps, bool fast32, void *ws, int n_groups, int threads, int W_climb,
@@ -742,6 +742,8 @@ void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const i
         hipLaunchKernelGGL(k2_sweep_band, dim3(unsigned(od.C < n_groups ? od.C : n_groups)), dim3(band_threads),
                            size_t(ba.sh.total), st, tb, od, max_caps, out, stage_group, stage_tp, warmup, t_max_out,
                            n_caps, ba);
+        const hipError_t e = hipGetLastError();            // before the launches over what it hands over replace it
+        if (e != hipSuccess) return e;
         items = SweepItems{w.redo, w.counters + 1};
     }
     fast32 = fast32 && tb.L <= kMeshFastMaxL;
@@ -772,6 +774,7 @@ void launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, const i
 #undef HARP_SWEEP_PHASE
     hipLaunchKernelGGL(k2_mesh_sweep_pick, dim3((od.C + 3) / 4), dim3(256), 0, st, tb, od, W, Ws, slots, out,
                        stage_group, stage_tp, warmup, t_max_out, n_caps, items);
+    return hipGetLastError();
 }
 
 size_t plan_mesh_sweep_slot_bytes(int S_max) { return sweep_slot_bytes(S_max); }
