@@ -38,6 +38,9 @@ struct MeshItems {
     const int *list;         // null: all
     const int *n_list;
 };
+// Workgroups beyond the orderings handed over leave without drawing from the ticket (2,048 of them drawing
+// one after the other take 29 us).
+__device__ __forceinline__ bool no_item(const MeshItems &it) { return it.list && int(blockIdx.x) >= *it.n_list; }
 __device__ __forceinline__ int next_item(const MeshItems &it, int C) {
     const int n = atomicAdd(it.ticket, 1);
     if (!it.list) return n < C ? n : -1;
@@ -66,6 +69,7 @@ __device__ __forceinline__ void mesh_body(const TablesDev &tb, const OrdDev &od,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthreads = blockDim.x;
     const MeshSlice m = mesh_slice(ws, per_group, L, n_dev);
     const int64_t m_cap = tb.M;
+    if (no_item(items)) return;
 
     // all threads: thread 0 backtracks into cuts/slot_*, the first wave scores them
     auto backtrack_and_score = [&](int K, int S, int64_t &bott, int64_t &total) {
@@ -211,6 +215,7 @@ __device__ __forceinline__ void mesh_h1_body(const TablesDev &tb, const OrdDev &
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nthreads = blockDim.x;
     const MeshSlice m = mesh_slice(ws, per_group, L, n_dev);
     const int64_t m_cap = tb.M;
+    if (no_item(items)) return;
 
     for (;;) {
         __syncthreads();
@@ -563,6 +568,11 @@ hipError_t mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int f
     BandArgs ba;
     int band_threads = 0;
     const bool fast = fast32 && tb.L <= kMeshFastMaxL;       // (sums of memory in LDS)
+    // whole-table workgroups: as many as are resident, also behind the band kernel, which can hand over the whole
+    // batch (4,096 orderings of 82 operators and 64 devices, H-1F1B, times too large for its sums: 16.6 ms on one
+    // workgroup per CU, 7.4 ms on eight)
+    const long long resident = (long long)n_cu * (2048 / threads);
+    const dim3 grid(unsigned(n_groups < resident ? n_groups : resident));
     if (fast32 && w.index_bytes != 0 && !whole_table(tb, od, total_devices) &&
         meshband::band_launch(tb, od, total_devices, form, n_cu, band_threads, ba.sh)) {
         launch_plan_index(tb, od.S_max, w.index, st);
@@ -575,13 +585,9 @@ hipError_t mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int f
         band(dim3(n_groups), dim3(band_threads), size_t(ba.sh.total), ba);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        whole(fast, dim3(n_groups < n_cu ? n_groups : n_cu), dim3(threads),
-              MeshItems{w.counters + 2, w.redo, w.counters + 1}, w.slices, per_group);
+        whole(fast, grid, dim3(threads), MeshItems{w.counters + 2, w.redo, w.counters + 1}, w.slices, per_group);
     } else {
-        // as many workgroups as are resident
-        const long long resident = (long long)n_cu * (2048 / threads);
-        whole(fast, dim3(unsigned(n_groups < resident ? n_groups : resident)), dim3(threads),
-              MeshItems{w.counters, nullptr, nullptr}, w.slices, per_group);
+        whole(fast, grid, dim3(threads), MeshItems{w.counters, nullptr, nullptr}, w.slices, per_group);
     }
     return hipGetLastError();
 }

@@ -185,3 +185,46 @@ def test_shapes_that_would_fill_the_lds(harp, ctx, form, L, T, G, n_tp, S_max, n
     assert (want.status == oracle.OK).all()
     assert_plans_equal(got, want, form)
     assert (got.stage_tp == want.stage_tp).all() and (got.stage_group == want.stage_group).all()
+
+
+def _repeated(orders, extra, C):
+    """A batch of C orderings: the given ones and the malformed `extra` ones over and over, in a fixed mix."""
+    at = np.random.default_rng(C).permutation(np.resize(np.arange(orders.C + len(extra)), C))
+    lists = [(int(orders.ord_S[c]), list(orders.ord_group[c, :orders.ord_G[c]])) for c in range(orders.C)] + extra
+    many = W.orderings_from_lists([lists[x] for x in at], S_max=orders.S_max, G_max=orders.G_max)
+    return at, W.orderings_from_lists(lists, S_max=orders.S_max, G_max=orders.G_max), many
+
+
+@pytest.mark.parametrize("scale", [1, 1 << 13], ids=["in_range", "handed_over"])
+@pytest.mark.parametrize("C", [300, 700, 2500])
+def test_band_kernels_on_large_batches(harp, ctx, C, scale):
+    """More orderings than compute units (512-thread workgroups), than twice as many (256 threads in the
+    min-max form), and than there are workgroups; in range, and with sums the band kernels hand over.  The
+    batch repeats a few orderings, malformed and infeasible ones among them, so the oracle works each once."""
+    ndev, tp = (40, 34, 2), (1, 2, 4, 8, 16)            # 77 columns
+    p = _problem(7, 75, ndev, tp, False, scale)
+    assert harp.Tables(ctx, p).fast32
+    orders = W.orderings_from_lists([(8, [0, 1, 2]), (7, [2, 1, 0]), (9, [1, 0]), (6, [0])], S_max=12, G_max=4)
+    extra = [(0, [0, 1]), (4, [0, 0]), (5, [0, 3]), (2, [0, 1, 2]), (12, [2])]
+    at, few, many = _repeated(orders, extra, C)
+    ot = oracle.build_tables(p)
+    want = oracle_plan_mesh_threaded(ot, few)
+    assert (want.status == oracle.OK).sum() >= 3 and (want.status != oracle.OK).sum() >= 5
+    # (every entry point in the order its rows are worked; rows are compared by the ordering they repeat)
+    names = ("status", "splits", "dev_first", "bottleneck", "iter_time", "stage_group", "stage_tp")
+
+    def same(got, want, extra_names=()):
+        for name in names + extra_names:
+            a, b = getattr(got, name), getattr(want, name)[at]
+            bad = np.nonzero((a != b).reshape(C, -1).any(axis=1))[0]
+            assert bad.size == 0, (name, bad.size, int(at[bad[0]]))
+
+    same(harp.plan_mesh(ctx, p, many, False, harp.PATH_FAST32)[0], want)
+    same(harp.plan_mesh(ctx, p, many, True, harp.PATH_FAST32)[0], harp.plan_mesh(ctx, p, few, True, harp.PATH_GENERIC)[0],
+         ("n_passes",))
+    caps = np.where(want.status == oracle.OK, want.bottleneck // 8 * 9, 0)
+    same(harp.plan_mesh_h1f1b(ctx, p, many, caps[at], harp.PATH_FAST32)[0], oracle_plan_mesh_h1f1b_threaded(ot, few, caps),
+         ("warmup",))
+    limit = 6                                            # caps: the int64 path tries every one
+    same(harp.plan_mesh_h1f1b_sweep(ctx, p, many, limit, harp.PATH_FAST32)[0],
+         harp.plan_mesh_h1f1b_sweep(ctx, p, few, limit, harp.PATH_GENERIC)[0], ("warmup", "t_max", "n_caps"))
