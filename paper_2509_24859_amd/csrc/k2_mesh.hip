@@ -327,13 +327,17 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE); continue; }
         auto hand_over = [&]() { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c; };
         if (verdict == 3) { hand_over(); continue; }
+        const uint64_t most = kExact ? b.most_sum() : 0;
+        const int64_t sum_cap = kExact ? b.largest_cap(most, false) : 0, key_cap = kExact ? b.largest_cap(most, true) : 0;
         const int64_t opening = b.bracket();
         if (opening < 0) { fail(HARP_CAND_INFEASIBLE); continue; }
+        if (kExact && b.S >= 2 && opening > sum_cap) { hand_over(); continue; }
         int form = Band::kMinMax, tries = 0, passes = 0;
         uint32_t cap = uint32_t(opening);
         int64_t t_S = 0, best_T = kInf, best_b = kInf;
         bool over = false;
         for (;;) {
+            b.keys_fit = int64_t(cap) <= key_cap;
             const int64_t v = b.template run<kExact ? Band::kMinMax | Band::kSum : Band::kMinMax>(form, cap);
             if (v == kInf) {
                 if (form == Band::kSum || cap >= meshband::kTopCap) break;     // (a sum cannot fail at or above t_S)
@@ -353,7 +357,7 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
             if (!kExact || b.S < 2) break;
             int64_t next_cap;
             if (form == Band::kMinMax) {
-                over = !b.sums_fit((best_T + m_cap - 1) / m_cap);
+                over = (best_T + m_cap - 1) / m_cap > sum_cap;
                 if (over) break;
                 form = Band::kSum;
                 next_cap = t_S;
@@ -370,7 +374,7 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
                 }
                 if (next_cap <= t_S) break;
             }
-            cap = uint32_t(next_cap);
+            cap = next_cap < int64_t(meshband::kTopCap) ? uint32_t(next_cap) : meshband::kTopCap;
         }
         if (over) { hand_over(); continue; }
         if (best_T == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
@@ -408,13 +412,15 @@ __global__ __launch_bounds__(1024) void k2_mesh_band_h1f1b(TablesDev tb, OrdDev 
         const int verdict = b.load(od.ord_S[c], od.ord_G[c], od.ord_group + int64_t(c) * od.G_max, S_max, od.G_max);
         if (verdict == 1 || cap_out_of_range(tb, cap)) { fail(HARP_CAND_INVALID); continue; }
         if (verdict == 2 || cap < 0) { fail(HARP_CAND_INFEASIBLE); continue; }
-        if (verdict == 3 || !b.sums_fit(cap)) {
+        // (caps up to the first bound need no look at the operators)
+        if (verdict == 3 || (cap > b.largest_cap(meshband::kInfSum, false) && cap > b.largest_cap(b.most_sum(), false))) {
             if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c;
             continue;
         }
-        const int64_t sum = b.run<Band::kH1>(Band::kH1, uint32_t(cap));
+        b.count_cap = cap;
+        const int64_t sum = b.run<Band::kH1>(Band::kH1, cap < int64_t(meshband::kTopCap) ? uint32_t(cap) : meshband::kTopCap);
         if (sum == kInf) { fail(HARP_CAND_INFEASIBLE); continue; }
-        b.find_h1_plan(uint32_t(cap));
+        b.find_h1_plan();
         b.write_slots(out, c, S_max, sg, stp);
         for (int s = tid; s < S_max; s += b.nthreads) wu[s] = s < b.S ? b.warmup[s] : -1;
         if (b.wave == 0) {
@@ -569,7 +575,7 @@ hipError_t mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int f
     int band_threads = 0;
     const bool fast = fast32 && tb.L <= kMeshFastMaxL;       // (sums of memory in LDS)
     // whole-table workgroups: as many as are resident, also behind the band kernel, which can hand over the whole
-    // batch (4,096 orderings of 82 operators and 64 devices, H-1F1B, times too large for its sums: 16.6 ms on one
+    // batch (4,096 orderings of 82 operators and 64 devices in the H-1F1B form, all handed over: 16.6 ms on one
     // workgroup per CU, 7.4 ms on eight)
     const long long resident = (long long)n_cu * (2048 / threads);
     const dim3 grid(unsigned(n_groups < resident ? n_groups : resident));

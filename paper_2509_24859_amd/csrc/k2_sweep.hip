@@ -568,8 +568,11 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
         if (verdict == 1) { fail(HARP_CAND_INVALID, 0); continue; }
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
         if (verdict == 3) { hand_over(); continue; }
+        const uint64_t most = b.most_sum();
+        const int64_t sum_cap = b.largest_cap(most, false), key_cap = b.largest_cap(most, true);
         const int64_t opening = b.bracket();
         if (opening < 0) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
+        if (opening > sum_cap) { hand_over(); continue; }
         const uint32_t more = uint32_t(max_caps) - 1u;          // values above t_S that may be tried
         int64_t best_T = kInf, best_bott = kInf, classic = kInf, unused_T;
         uint32_t t_S = 0, first = 0, best_cap = 0, values = 0, top = 0, lo = 0, hi = 0, unused = 0;
@@ -577,8 +580,8 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
         uint32_t tried = 0;
         bool run_out = false;
         int bn = 0, climbed = 0, tries = 0;
-        auto keep = [&](uint32_t cap) {
-            b.find_h1_plan(cap);
+        auto keep = [&]() {
+            b.find_h1_plan();
             b.score(scored, best_bott, unused_T);
             b.write_slots(out, c, S_max, sg, stp);
             const int t = Band::thread_id();
@@ -591,7 +594,9 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
         while (state < kDone) {
             const int form = state == kBottleneck ? Band::kMinMax : state == kUpper ? Band::kSum
                              : state == kAtTop || state == kGallop || state == kBisect ? Band::kAny : Band::kH1;
-            if (form != Band::kMinMax && !b.sums_fit(form == Band::kAny ? 0 : int64_t(cap))) { state = kOver; break; }
+            if ((form == Band::kSum || form == Band::kH1) && cap > sum_cap) { state = kOver; break; }
+            b.count_cap = cap;
+            b.keys_fit = cap <= key_cap;
             const int64_t v = b.run<Band::kMinMax | Band::kSum | Band::kH1 | Band::kAny>(form, cap);
             const bool found = v != kInf;
             bool opened = false, climb_on = false, try_on = false, upper_on = false;
@@ -648,7 +653,7 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                     if (T < best_T || (T == best_T && cap < best_cap)) {
                         best_T = T;
                         best_cap = cap;
-                        keep(cap);
+                        keep();
                     }
                 }
                 if (found && v == classic) { hi = bn > 0 ? uint32_t(bn) - 1u : 0u; upper_on = true; }
@@ -661,9 +666,8 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
             if (opened) {
                 first = best_cap = cap;
                 best_T = v + m_less * first;
-                keep(first);
+                keep();
                 const int64_t t_E = (best_T + m_less) / (m_less + 1);
-                if (!b.sums_fit(t_E)) { state = kOver; break; }
                 hi = uint32_t(t_E);
                 // the climb passed every value up to `first`, which is above t_E when it exceeds the plan's sum by M
                 uint32_t last = t_S;

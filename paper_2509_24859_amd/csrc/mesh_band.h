@@ -41,7 +41,7 @@ using fastdp::uniform;
 using fastdp::wave_sync;
 
 constexpr uint32_t kNoCut = 0xFFFFu;
-constexpr uint32_t kInfSum = 0x80000000u;        // least sums stay below this (sums_fit)
+constexpr uint32_t kInfSum = 0x80000000u;        // least sums stay below this (largest_cap)
 constexpr uint32_t kTopCap = 0x7FFFFFFFu;        // no time on these tables is larger
 constexpr int kRowPad = 4;                       // a window of four entries may overrun a row
 
@@ -152,6 +152,8 @@ struct Band {
     int K, S, D, L, n_sets;
     int least_cut;               // the cut behind the operator of least output (operators but the last)
     bool rows_fit;               // the value rows of the last prepared cap fit in LDS
+    bool keys_fit;               // and their key rows 32 bits, where the next pass is for the least sum
+    int64_t count_cap;           // the cap H-1F1B's counts are worked out with: the pass's own, or above any time
 
     __device__ __forceinline__ Band(const TablesDev &t, const BandShape &s, unsigned char *lds, const uint16_t *lo,
                                     const uint16_t *hi, const BandSlice &slice)
@@ -189,7 +191,9 @@ struct Band {
         L = tb.L;
         K = S = D = n_sets = 0;
         rows_fit = false;
+        keys_fit = true;
         least_cut = 1;
+        count_cap = 0;
     }
 
     // The thread's index, new to the compiler at every use: what a phase derives from it (LDS addresses,
@@ -747,7 +751,7 @@ struct Band {
                     const int d = map[x], i = x - col_off[nxt * sh.cols + d], k = group_at[d];
                     const uint32_t v = rows[x], *p = time_row(k) + i;
                     for (int q = 0; q < tb.n_tp; ++q)
-                        keys[q * pitch + x] = v < kInfSum ? int32_t(v * uint32_t(tb.tp[q])) - int32_t(p[q * sh.W]) : kNoKey;
+                        keys[q * pitch + x] = v < kInfSum ? int32_t(v * uint32_t(tb.tp[q]) - p[q * sh.W]) : kNoKey;
                 }
                 __syncthreads();
             }
@@ -904,8 +908,8 @@ struct Band {
     __device__ __forceinline__ int64_t h1_pass_in(uint32_t cap) {
         constexpr uint32_t kNoCount = 0xFFFFu;
         const int tid = thread_id();
-        const uint64_t e6 = uint64_t(cap) >> 6;
-        const uint32_t th1 = uint32_t(e6 >> 1), th2 = uint32_t((uint64_t(cap) + e6) >> 1);   // 2c - e > 0; > cap
+        const uint64_t e6 = uint64_t(count_cap) >> 6, x1 = e6 >> 1, x2 = (uint64_t(count_cap) + e6) >> 1;
+        const uint32_t th1 = uint32_t(x1 < kTopCap ? x1 : kTopCap), th2 = uint32_t(x2 < kTopCap ? x2 : kTopCap);   // 2c - e > 0; > cap
         const uint32_t m_cap = uint32_t(tb.M);
         const int64_t *PP = mem, *PS = mem + sh.W;
         const int pitch = sh.row_cap + kRowPad;
@@ -1003,7 +1007,7 @@ struct Band {
     __device__ __forceinline__ int64_t run(int form, uint32_t t) {
         if (!prepare(t)) return kInf;
         if ((kForms & kMinMax) && form == kMinMax) return rows_fit ? value_pass_in<false, true>(t) : value_pass_in<false, false>(t);
-        if ((kForms & kSum) && form == kSum) return rows_fit ? value_pass_in<true, true>(t) : value_pass_in<true, false>(t);
+        if ((kForms & kSum) && form == kSum) return rows_fit && keys_fit ? value_pass_in<true, true>(t) : value_pass_in<true, false>(t);
         if ((kForms & kH1) && form == kH1) return rows_fit ? h1_pass_in<false, true>(t) : h1_pass_in<false, false>(t);
         if (kForms & kAny) return rows_fit ? h1_pass_in<true, true>(t) : h1_pass_in<true, false>(t);
         return kInf;
@@ -1016,7 +1020,7 @@ struct Band {
         __syncthreads();
     }
     // All threads: the plan of the last H-1F1B pass, with its counts by eq. Ni.
-    __device__ __forceinline__ void find_h1_plan(uint32_t cap) {
+    __device__ __forceinline__ void find_h1_plan() {
         const int lane = thread_id() & 63;
         if (wave == 0) {
             const uint16_t *back = reinterpret_cast<const uint16_t *>(sl.hist);
@@ -1040,11 +1044,11 @@ struct Band {
             }
             if (lane == 0) cuts[S] = L;
             wave_sync();
-            const uint64_t e6 = uint64_t(cap) >> 6;
+            const uint64_t e6 = uint64_t(count_cap) >> 6;
             for (int s = lane; s < S; s += 64) {
                 uint32_t cut = 0;
                 if (s < S - 1) cut = tb.CM[(int64_t(slot_g[s]) * tb.G + slot_g[s + 1]) * tb.pitch32 + cuts[s + 1]];
-                warmup[s] = 1 + (2ull * cut > e6 ? 1 : 0) + (2ull * cut > uint64_t(cap) + e6 ? 1 : 0);
+                warmup[s] = 1 + (2ull * cut > e6 ? 1 : 0) + (2ull * cut > uint64_t(count_cap) + e6 ? 1 : 0);
             }
             wave_sync();
             if (lane == 0) {
@@ -1223,9 +1227,50 @@ struct Band {
         total = scored[1];
     }
 
-    // sums of S stage and twice S transfer times under the cap, times the largest degree, stay below 2^31
-    __device__ __forceinline__ bool sums_fit(int64_t cap) const {
-        return cap <= int64_t(kInfSum) / (3ll * S * tb.tp[tb.n_tp - 1]) - 1;
+    // All threads: what no plan of this ordering exceeds in sum, whatever its cap: every operator in the slowest
+    // way the ordering has for it (a stage's time, rounded up once, is at most the sum of its operators', each
+    // rounded up), every cut at the largest output over the slowest link.
+    __device__ __forceinline__ uint64_t most_sum() {
+        const int tid = thread_id();
+        uint64_t sum = 0;
+        for (int i = tid; i < L; i += nthreads) {
+            uint32_t worst = 0;
+            for (int r = 0; r < n_sets * tb.n_tp; ++r) {
+                const int set = r / tb.n_tp, q = r - set * tb.n_tp;
+                const uint32_t tp = uint32_t(tb.tp[q]), *p = prow + r * sh.W + i;
+                const uint32_t time = (p[1] - p[0] + tp - 1u) >> tb.tp_shift[q];
+                worst = tp <= use[set] && time > worst ? time : worst;
+            }
+            sum += worst;
+        }
+        uint32_t cut = 0;                                  // below 2^31 on these tables
+        for (int l = tid; l < 2 * K - 1; l += nthreads) {
+            const int g = order[l < K ? l : l - K], h = l < K ? g : order[l - K + 1];
+            const uint64_t link = uint64_t(tb.bw[int64_t(g) * tb.G + h]);
+            const uint32_t c = uint32_t((tb.header->max_act + link - 1u) / link);
+            cut = c > cut ? c : cut;
+        }
+        cut = ~group_min(~cut);
+#pragma unroll
+        for (int x = 32; x >= 1; x >>= 1) sum += __shfl_xor((unsigned long long)sum, x, 64);
+        if (tid == 0) ok[0] = 0;                           // (the masks are made anew for every pass)
+        __syncthreads();
+        if ((tid & 63) == 0) atomicAdd(&ok[0], (unsigned long long)sum);
+        __syncthreads();
+        return ok[0] + 2ull * uint64_t(S - 1) * cut;
+    }
+    // The largest cap under which sums stay below 2^31: S stage and twice S transfer times of at most the cap, or
+    // any cap when `most` (most_sum) does.  Key rows hold sums times a degree that a group has devices for; a pass
+    // whose sums fit but not those products works from the workspace's value rows, as one does whose rows leave LDS.
+    __device__ __forceinline__ int64_t largest_cap(uint64_t most, bool keys) const {
+        int degree = 1;
+        if (keys) {
+            uint32_t devices = 1;
+            for (int x = 0; x < n_sets; ++x) devices = use[x] > devices ? use[x] : devices;
+            for (int q = 1; q < tb.n_tp; ++q) degree = uint32_t(tb.tp[q]) <= devices ? tb.tp[q] : degree;
+        }
+        const int64_t limit = int64_t(kInfSum) / degree;
+        return most < uint64_t(limit) - 1u ? INT64_MAX : limit / (3ll * S) - 1;
     }
 };
 

@@ -45,7 +45,7 @@ CASES = [  # L, devices per group, degrees, stage counts, slow link, scale of th
     (30, (3, 2, 4), (1, 2, 4), (3, 5, 9), True, 1 << 14, False),       # small: whole table, sums beyond 2^31
     (20, (4, 4), (1, 2, 4), (3, 5), False, 1, False),                  # small: whole table
     (59, (10, 12), (1,), (21, 22), False, 1, False),                   # one degree: whole table
-    (90, (10, 12, 9), (1, 2, 4), (9, 12), True, 1 << 13, False),        # sums beyond 2^31: handed over
+    (90, (10, 12, 9), (1, 2, 4), (9, 12), True, 1 << 13, False),        # sums that leave 32 bits times a degree
     (900, (1, 1, 1, 1), (1, 2, 4, 8, 16, 32, 64, 128), (4,), False, 1, True),   # time rows beyond LDS: handed over
     (400, (32, 32), (1, 2, 4, 8, 16, 32), (8,), True, 1, False),       # value rows beyond LDS
 ]
@@ -195,22 +195,23 @@ def _repeated(orders, extra, C):
     return at, W.orderings_from_lists(lists, S_max=orders.S_max, G_max=orders.G_max), many
 
 
-@pytest.mark.parametrize("scale", [1, 1 << 13], ids=["in_range", "handed_over"])
+@pytest.mark.parametrize("scale,slow,stages", [(1, False, (8, 7, 9, 6)), (1 << 13, False, (8, 7, 9, 6)),
+                                               (1 << 14, True, (64, 60, 63, 26))], ids=["in_range", "no_keys", "handed_over"])
 @pytest.mark.parametrize("C", [300, 700, 2500])
-def test_band_kernels_on_large_batches(harp, ctx, C, scale):
+def test_band_kernels_on_large_batches(harp, ctx, C, scale, slow, stages):
     """More orderings than compute units (512-thread workgroups), than twice as many (256 threads in the
-    min-max form), and than there are workgroups; in range, and with sums the band kernels hand over.  The
-    batch repeats a few orderings, malformed and infeasible ones among them, so the oracle works each once."""
+    min-max form), and than there are workgroups; in range, with sums that leave 32 bits times a degree, and with
+    sums that leave 32 bits themselves (the band kernels hand those over).  The batch repeats a few orderings, malformed and infeasible ones among them, so the oracle works each once."""
     ndev, tp = (40, 34, 2), (1, 2, 4, 8, 16)            # 77 columns
-    p = _problem(7, 75, ndev, tp, False, scale)
+    p = _problem(7, 75, ndev, tp, slow, scale)
     assert harp.Tables(ctx, p).fast32
-    orders = W.orderings_from_lists([(8, [0, 1, 2]), (7, [2, 1, 0]), (9, [1, 0]), (6, [0])], S_max=12, G_max=4)
+    orders = W.orderings_from_lists(list(zip(stages, ([0, 1, 2], [2, 1, 0], [1, 0], [0]))), S_max=max(stages) + 3,
+                                    G_max=4)
     extra = [(0, [0, 1]), (4, [0, 0]), (5, [0, 3]), (2, [0, 1, 2]), (12, [2])]
     at, few, many = _repeated(orders, extra, C)
     ot = oracle.build_tables(p)
     want = oracle_plan_mesh_threaded(ot, few)
     assert (want.status == oracle.OK).sum() >= 3 and (want.status != oracle.OK).sum() >= 5
-    # (every entry point in the order its rows are worked; rows are compared by the ordering they repeat)
     names = ("status", "splits", "dev_first", "bottleneck", "iter_time", "stage_group", "stage_tp")
 
     def same(got, want, extra_names=()):
@@ -228,3 +229,25 @@ def test_band_kernels_on_large_batches(harp, ctx, C, scale):
     limit = 6                                            # caps: the int64 path tries every one
     same(harp.plan_mesh_h1f1b_sweep(ctx, p, many, limit, harp.PATH_FAST32)[0],
          harp.plan_mesh_h1f1b_sweep(ctx, p, few, limit, harp.PATH_GENERIC)[0], ("warmup", "t_max", "n_caps"))
+
+
+@pytest.mark.parametrize("slow,scale", [(True, 1 << 13), (False, 1), (False, 1 << 13)], ids=["slow_link", "small", "large"])
+def test_band_h1f1b_under_loose_caps(harp, ctx, slow, scale):
+    """Caps around and beyond 2^31, under which the sums are bounded by the operators instead: the counts
+    still follow the cap that was asked for (on the slow link up to 64 times twice 24e6 us, above 2^31)."""
+    p = _problem(3, 61, (5, 6), (1, 2, 4), slow, scale)
+    assert harp.Tables(ctx, p).fast32
+    orders = W.orderings_from_lists([(5, [0, 1]), (7, [1, 0]), (6, [0, 1]), (3, [1])], S_max=8)
+    ot = oracle.build_tables(p)
+    base = oracle_plan_mesh_threaded(ot, orders)
+    assert (base.status == oracle.OK).sum() >= 3
+    counts = set()
+    top = min((1 << 47) - 1, oracle.INF // (3 * p.L + p.M))
+    for cap in (0, (1 << 31) - 2, (1 << 31) - 1, 1 << 31, 3 * 10**9, (1 << 32) + 5, 1 << 40, top, top + 1):
+        caps = np.where(base.status == oracle.OK, base.bottleneck, 7) if cap == 0 else np.full(orders.C, cap)
+        want = oracle_plan_mesh_h1f1b_threaded(ot, orders, caps)
+        got, _ = harp.plan_mesh_h1f1b(ctx, p, orders, caps, harp.PATH_FAST32)
+        assert_plans_equal(got, want, "cap %d" % cap)
+        assert (got.warmup == want.warmup).all() and (got.stage_tp == want.stage_tp).all(), cap
+        counts.add(want.warmup.tobytes())
+    assert len(counts) >= 3
