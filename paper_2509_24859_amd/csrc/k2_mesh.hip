@@ -327,14 +327,11 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE); continue; }
         auto hand_over = [&]() { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c; };
         if (verdict == 3) { hand_over(); continue; }
-        const uint64_t most = kExact ? b.most_sum() : 0;
-        const int64_t sum_cap = kExact ? b.largest_cap(most, false) : 0, key_cap = kExact ? b.largest_cap(most, true) : 0;
         const int64_t opening = b.bracket();
         if (opening < 0) { fail(HARP_CAND_INFEASIBLE); continue; }
-        if (kExact && b.S >= 2 && opening > sum_cap) { hand_over(); continue; }
         int form = Band::kMinMax, tries = 0, passes = 0;
         uint32_t cap = uint32_t(opening);
-        int64_t t_S = 0, best_T = kInf, best_b = kInf;
+        int64_t t_S = 0, best_T = kInf, best_b = kInf, key_cap = 0;
         bool over = false;
         for (;;) {
             b.keys_fit = int64_t(cap) <= key_cap;
@@ -357,8 +354,15 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
             if (!kExact || b.S < 2) break;
             int64_t next_cap;
             if (form == Band::kMinMax) {
-                over = (best_T + m_cap - 1) / m_cap > sum_cap;
-                if (over) break;
+                // every cap of the walk is at most T / B rounded up; up to the first bound it needs no look at the operators
+                const int64_t t_E = (best_T + m_cap - 1) / m_cap;
+                key_cap = b.largest_cap(meshband::kInfSum, true);
+                if (t_E > key_cap) {
+                    const uint64_t most = b.most_sum();
+                    key_cap = b.largest_cap(most, true);
+                    over = t_E > b.largest_cap(most, false);
+                    if (over) break;
+                }
                 form = Band::kSum;
                 next_cap = t_S;
             } else {

@@ -568,11 +568,11 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
         if (verdict == 1) { fail(HARP_CAND_INVALID, 0); continue; }
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
         if (verdict == 3) { hand_over(); continue; }
-        const uint64_t most = b.most_sum();
-        const int64_t sum_cap = b.largest_cap(most, false), key_cap = b.largest_cap(most, true);
         const int64_t opening = b.bracket();
         if (opening < 0) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
-        if (opening > sum_cap) { hand_over(); continue; }
+        // caps up to these bounds need no look at the operators (looked: it has been taken)
+        int64_t sum_cap = b.largest_cap(meshband::kInfSum, false), key_cap = b.largest_cap(meshband::kInfSum, true);
+        bool looked = false;
         const uint32_t more = uint32_t(max_caps) - 1u;          // values above t_S that may be tried
         int64_t best_T = kInf, best_bott = kInf, classic = kInf, unused_T;
         uint32_t t_S = 0, first = 0, best_cap = 0, values = 0, top = 0, lo = 0, hi = 0, unused = 0;
@@ -594,7 +594,15 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
         while (state < kDone) {
             const int form = state == kBottleneck ? Band::kMinMax : state == kUpper ? Band::kSum
                              : state == kAtTop || state == kGallop || state == kBisect ? Band::kAny : Band::kH1;
-            if ((form == Band::kSum || form == Band::kH1) && cap > sum_cap) { state = kOver; break; }
+            if (form == Band::kSum || form == Band::kH1) {
+                if (cap > key_cap && !looked) {
+                    const uint64_t most = b.most_sum();
+                    sum_cap = b.largest_cap(most, false);
+                    key_cap = b.largest_cap(most, true);
+                    looked = true;
+                }
+                if (cap > sum_cap) { state = kOver; break; }
+            }
             b.count_cap = cap;
             b.keys_fit = cap <= key_cap;
             const int64_t v = b.run<Band::kMinMax | Band::kSum | Band::kH1 | Band::kAny>(form, cap);

@@ -200,8 +200,9 @@ def _repeated(orders, extra, C):
 @pytest.mark.parametrize("C", [300, 700, 2500])
 def test_band_kernels_on_large_batches(harp, ctx, C, scale, slow, stages):
     """More orderings than compute units (512-thread workgroups), than twice as many (256 threads in the
-    min-max form), and than there are workgroups; in range, with sums that leave 32 bits times a degree, and with
-    sums that leave 32 bits themselves (the band kernels hand those over).  The batch repeats a few orderings, malformed and infeasible ones among them, so the oracle works each once."""
+    min-max form), and than there are workgroups; in range, with sums that leave 32 bits times a degree, and
+    with sums that leave 32 bits themselves (the band kernels hand those over).  The batch repeats a few
+    orderings, malformed and infeasible ones among them, so the oracle works each once."""
     ndev, tp = (40, 34, 2), (1, 2, 4, 8, 16)            # 77 columns
     p = _problem(7, 75, ndev, tp, slow, scale)
     assert harp.Tables(ctx, p).fast32
@@ -251,3 +252,34 @@ def test_band_h1f1b_under_loose_caps(harp, ctx, slow, scale):
         assert (got.warmup == want.warmup).all() and (got.stage_tp == want.stage_tp).all(), cap
         counts.add(want.warmup.tobytes())
     assert len(counts) >= 3
+
+
+def test_band_orderings_without_a_plan(harp, ctx):
+    """Tight memory on one of two GPU types, as many stages as devices: the chains, which may leave a stage
+    without operators, reach the end on orderings that have no plan, and below the optimum of others."""
+    rng = np.random.default_rng(1)
+    L, G = 120, 4
+    bw = rng.integers(20, 60, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 500
+    p = simple_problem(np.zeros(L), M=20, T=2, G=G, ndev=(10,) * G, tp=[1 << k for k in range(8)],
+                       gtype=[g % 2 for g in range(G)], fwd=rng.integers(1, 900, size=(2, L)),
+                       bwd=rng.integers(1, 900, size=(2, L)), act=rng.integers(100, 3000, size=L),
+                       params=rng.integers(0, 40, size=L), stash=rng.integers(1, 20, size=L), bw=bw)
+    lists = [(S, [int(g) for g in rng.permutation(G)[:k]]) for S, k in ((40, 4),) * 8 + ((30, 3),) * 6 + ((20, 2),) * 4]
+    orders = W.orderings_from_lists(lists, S_max=40)
+    some = 0
+    for mem in ((900, 300), (1080, 360), (1200, 330)):
+        p.type_mem_bytes[:] = mem
+        want = oracle_plan_mesh_threaded(oracle.build_tables(p), orders)
+        some += int((want.status != oracle.OK).any() and (want.status == oracle.OK).any())
+        for exact in (False, True):
+            got, _ = harp.plan_mesh(ctx, p, orders, exact, harp.PATH_FAST32)
+            if exact:
+                want, _ = harp.plan_mesh(ctx, p, orders, True, harp.PATH_GENERIC)
+            assert_plans_equal(got, want, "memory %s, exact %d" % (mem, exact))
+            assert (got.stage_tp == want.stage_tp).all() and (got.stage_group == want.stage_group).all()
+        got, want = (harp.plan_mesh_h1f1b_sweep(ctx, p, orders, 5, path)[0] for path in (harp.PATH_FAST32, harp.PATH_GENERIC))
+        assert_plans_equal(got, want, "memory %s, sweep" % (mem,))
+        assert (got.n_caps == want.n_caps).all() and (got.t_max == want.t_max).all()
+    assert some >= 2
