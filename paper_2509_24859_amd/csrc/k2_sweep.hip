@@ -149,7 +149,7 @@ __device__ __forceinline__ int64_t mesh_next_cap_slots(const TablesDev &tb, int 
 struct SweepHead {
     int64_t T, cap;
     int32_t tried, state;    // state: kSweepNone, kSweepPlan, or kSweepFailed + a candidate status
-    int32_t pad[2];
+    int32_t rest[2];         // band form: the caps left to the walkers
 };
 constexpr int kSweepNone = 0, kSweepPlan = 1, kSweepFailed = 16;
 
@@ -191,9 +191,11 @@ constexpr int kSweepLower = 0, kSweepClimb = 1, kSweepRest = 2;
 struct SweepItems {
     const int *list;         // null: all
     const int *n_list;
+    const int *n_shared;     // orderings it left to its walkers, listed from the end (the pick looks at those too)
 };
+constexpr int kClimbOn = 1 << 30;        // flag on a listed ordering: the climb goes on where the band kernel left it
 __device__ __forceinline__ int n_orderings(const SweepItems &it, int C) { return it.list ? *it.n_list : C; }
-__device__ __forceinline__ int ordering_of(const SweepItems &it, int n) { return it.list ? it.list[n] : n; }
+__device__ __forceinline__ int ordering_of(const SweepItems &it, int n) { return it.list ? it.list[n] & (kClimbOn - 1) : n; }
 
 template <bool kFast, int kPhase, bool kForced>
 __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDev &od, const int32_t *cand_group,
@@ -223,6 +225,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
     const MeshSlice m = mesh_slice(ws, per_group, L, n_dev);
     const int64_t m_cap = tb.M;
     const int n_items = n_orderings(items, od.C) * W;
+    if (items.list && int(blockIdx.x) >= n_items) return;           // mostly none is handed over
     const uint8_t *fq = kForced ? forced_q : nullptr;
     const int32_t *fo = kForced ? forced_off : nullptr;
 
@@ -235,6 +238,8 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
         const int n = item / W, j = item - n * W, c = ordering_of(items, n);
         const SweepSlot opening = sweep_slot(slots, S_max, Ws, c, Ws);
         const SweepSlot mine = kPhase == kSweepLower ? opening : sweep_slot(slots, S_max, Ws, c, j);
+        // t_S and the caps up to where the climb goes on are done (head and lower are written)
+        if (kPhase == kSweepLower && items.list && (items.list[n] & kClimbOn)) continue;
         auto leave = [&](int state, int tried) {
             if (tid == 0) { mine.head->T = kInf; mine.head->cap = kInf; mine.head->tried = tried; mine.head->state = state; }
         };
@@ -354,13 +359,14 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
                 leave(kSweepNone, 1);
             }
         } else if constexpr (kPhase == kSweepClimb) {
-            // the climb from t_S (index 0, tried without a plan by the first launch) to the first cap
+            // the climb from t_S (tried without a plan by the first launch: index 0) to the first cap
             // with a plan, shared by the W walkers of the ordering: each walks every cap and tries
             // those whose index is congruent to its own; the lowest index found so far (first_idx, an
             // atomic minimum) tells the others where to stop.  Every index below the final minimum
             // has been tried by its walker and has no plan.
             cap = lower[c];
-            tried = 1;
+            const int passed = opening.head->tried;
+            tried = passed;
             int state = kSweepFailed + HARP_CAND_INFEASIBLE;
             for (int idx = 1;; ++idx) {
                 if (tried >= max_caps) break;
@@ -371,7 +377,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
                 if (tid == 0) shared_int[1] = atomicAdd(&first_idx[c], 0);
                 __syncthreads();
                 if (idx > shared_int[1]) { state = kSweepNone; break; }        // a lower cap already has a plan
-                tried = idx + 1;
+                tried = passed + idx;
                 if ((idx - 1) % W != j) continue;
                 const int64_t sum = h1_pass(cap);
                 if (sum == kInf) continue;
@@ -441,7 +447,7 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_open(OrdDev od, int W, int 
     if (lane == 0) {
         opening.head->T = from.head->T;
         opening.head->cap = from.head->cap;
-        opening.head->tried = f == INT32_MAX ? from.head->tried : f + 1;
+        opening.head->tried = f == INT32_MAX ? from.head->tried : opening.head->tried + f;
         opening.head->state = from.head->state;
     }
 }
@@ -459,8 +465,12 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
                                                           SweepItems items) {
     const int lane = threadIdx.x & 63;
     const int n = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (n >= n_orderings(items, od.C)) return;
-    const int c = ordering_of(items, n);
+    // behind those that were worked here: orderings whose rest went to the walkers of the band kernel, with a plan
+    // at the outputs already
+    const int own = n_orderings(items, od.C);
+    const bool shared = n >= own;
+    if (n >= own + (items.list ? *items.n_shared : 0)) return;
+    const int c = shared ? items.list[od.C - 1 - (n - own)] : ordering_of(items, n);
     const int S_max = od.S_max;
     int32_t *sp = out.splits + int64_t(c) * (S_max + 1), *df = out.dev_first + int64_t(c) * S_max;
     // a batch of candidates (fixed slicing) has no slicing to report
@@ -492,6 +502,7 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
             best = j; best_T = h->T; best_cap = h->cap;
         }
     }
+    if (shared && best == Ws) return;
     const SweepSlot b = sweep_slot(slots, S_max, Ws, c, best);
     const int S = od.ord_S[c];
     for (int s = lane; s <= S_max; s += 64) sp[s] = s <= S ? b.cuts[s] : -1;
@@ -508,7 +519,7 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
         out.iter_time[c] = best_T;
         out.status[c] = HARP_CAND_OK;
         t_max_out[c] = best_cap;
-        if (n_caps) n_caps[c] = sweep_slot(slots, S_max, Ws, c, 0).head->tried;
+        if (n_caps && !shared) n_caps[c] = sweep_slot(slots, S_max, Ws, c, 0).head->tried;
     }
 }
 
@@ -529,30 +540,53 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 // Measured on 48 orderings of 82 operators and 64 devices (about 1,000 values each between t_S and t_E, all
 // of them tried before, by up to 32 workgroups per ordering): 125-150 -> 1.0 ms per call, some 10 passes
 // per ordering, bound by the latency of one workgroup's passes one after the other.
+//  * The bounds are weak where tight memory keeps the H-1F1B sums above the classic ones and there are few
+//    micro-batches.  An ordering that has tried kMaxTries values without an end leaves the rest, a range of caps, to
+//    the second launch (kWalk): W workgroups take a part of the range each, start from the best plan so far and
+//    tell each other the least total they find.  Measured on orderings of 60 operators and 24 devices, 8
+//    micro-batches, tightest memory: 4 of them 92.3 -> 6.0 ms, 64 of them 92.1 -> 8.5 ms.
 // The plan returned is the one the sweep over every value returns (least T, lower cap on equal T).  An
-// ordering whose climb fails at kMaxClimb values in a row (the recurrence keeps one continuation per state
-// and could miss plans that exist), that does not fit LDS or whose sums could pass 2^31 is handed over
-// to the kernels that try every value.
-constexpr int kMaxClimb = 64;
+// ordering that does not fit LDS or whose sums could pass 2^31 is handed over to the kernels that try every
+// value; so is one whose climb fails at kMaxClimb values in a row (the recurrence keeps one continuation per
+// state and can miss plans that exist), from where it stands.
+constexpr int kMaxClimb = 8;
+constexpr int kMaxTries = 24;
 
+// The rest of an ordering's search: its slots as for the kernels above (the opening's head holds the best plan so
+// far and, in rest, the range of caps left: above the first, up to the second), the least total found per ordering
+// (or where its climb goes on), and the number of walkers per ordering; 1: the first launch goes on to the end by itself.
+struct SweepShare {
+    unsigned char *slots;
+    int Ws, W;
+    long long *least;
+};
+// counters of the band launch: orderings left to the walkers, and their ticket; their list grows from the end of redo
+constexpr int kShared = 5, kShareTicket = 6;
+
+template <bool kWalk>
 __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, int max_caps, PlansDev out,
                                                       int32_t *stage_group, int32_t *stage_tp, int32_t *warmup,
-                                                      int64_t *t_max_out, int32_t *n_caps, BandArgs ba) {
+                                                      int64_t *t_max_out, int32_t *n_caps, BandArgs ba, SweepShare sw) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ int64_t scored[2];
+    __shared__ long long least_found;
     __shared__ int item;
+    const int n_items = kWalk ? ba.counters[kShared] * sw.W : od.C;
+    if (kWalk && int(blockIdx.x) >= n_items) return;
     Band b(tb, ba.sh, lds_raw, ba.lo_tab, ba.hi_tab,
            meshband::band_slice(ba.slices + size_t(blockIdx.x) * ba.per_group, ba.sh));
     const int S_max = od.S_max, tid = threadIdx.x;
     const int64_t m_less = int64_t(tb.M) - 1;
     b.load_memory_sums();
-    b.find_least_cut();
+    if (!kWalk) b.find_least_cut();
     for (;;) {
         __syncthreads();
-        if (tid == 0) item = atomicAdd(&ba.counters[0], 1);
+        if (tid == 0) item = atomicAdd(&ba.counters[kWalk ? kShareTicket : 0], 1);
         __syncthreads();
-        const int c = item;
-        if (c >= od.C) break;
+        const int drawn = item;
+        if (drawn >= n_items) break;
+        const int c = kWalk ? ba.redo[od.C - 1 - drawn / sw.W] : drawn, walker = kWalk ? drawn % sw.W : sw.Ws;
+        const SweepSlot opening = sweep_slot(sw.slots, S_max, sw.Ws, c, sw.Ws), mine = sweep_slot(sw.slots, S_max, sw.Ws, c, walker);
         int32_t *sg = stage_group + int64_t(c) * S_max, *stp = stage_tp + int64_t(c) * S_max;
         int32_t *wu = warmup + int64_t(c) * S_max;
         auto fail = [&](int status, uint32_t tried) {
@@ -563,13 +597,13 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                 if (n_caps) n_caps[c] = int32_t(tried);
             }
         };
-        auto hand_over = [&]() { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c; };
+        auto hand_over = [&](int flag) { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c | flag; };
         const int verdict = b.load(od.ord_S[c], od.ord_G[c], od.ord_group + int64_t(c) * od.G_max, S_max, od.G_max);
         if (verdict == 1) { fail(HARP_CAND_INVALID, 0); continue; }
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
-        if (verdict == 3) { hand_over(); continue; }
-        const int64_t opening = b.bracket();
-        if (opening < 0) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
+        if (verdict == 3) { hand_over(0); continue; }
+        const int64_t start = kWalk ? 0 : b.bracket();
+        if (start < 0) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
         // caps up to these bounds need no look at the operators (looked: it has been taken)
         int64_t sum_cap = b.largest_cap(meshband::kInfSum, false), key_cap = b.largest_cap(meshband::kInfSum, true);
         bool looked = false;
@@ -579,19 +613,43 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
         uint64_t step = 0;
         uint32_t tried = 0;
         bool run_out = false;
-        int bn = 0, climbed = 0, tries = 0;
+        int bn = 0, climbed = 0, tries = 0, tested = 0;
+        bool kept = false, left = false;
         auto keep = [&]() {
             b.find_h1_plan();
+            const int t = Band::thread_id();
+            kept = true;
+            if (kWalk) {
+                for (int s = t; s <= b.S; s += b.nthreads) mine.cuts[s] = b.cuts[s];
+                for (int s = t; s < b.S; s += b.nthreads) {
+                    mine.g[s] = b.slot_g[s]; mine.k[s] = b.slot_k[s];
+                    mine.first[s] = b.slot_first[s]; mine.count[s] = b.warmup[s];
+                }
+                return;
+            }
             b.score(scored, best_bott, unused_T);
             b.write_slots(out, c, S_max, sg, stp);
-            const int t = Band::thread_id();
             for (int s = t; s < S_max; s += b.nthreads) wu[s] = s < b.S ? b.warmup[s] : -1;
         };
         // where the search stands; every state waits for the result of one pass under `cap`
-        enum { kBottleneck, kAtBottleneck, kAtTop, kGallop, kBisect, kClimb, kUpper, kTry, kDone, kNoPlan, kOver };
+        enum { kBottleneck, kAtBottleneck, kAtTop, kGallop, kBisect, kClimb, kUpper, kTry, kDone, kNoPlan, kOver, kClimbLeft };
         int state = kBottleneck;
-        uint32_t cap = uint32_t(opening);
+        uint32_t cap = uint32_t(start);
+        int64_t least_T = kInf;                                 // of any walker: what is above it cannot be the answer
+        if (kWalk) {
+            best_T = opening.head->T;
+            best_cap = uint32_t(opening.head->cap);
+            const uint32_t from = uint32_t(opening.head->rest[0]), range = uint32_t(opening.head->rest[1]) - from;
+            first = from + uint32_t(uint64_t(range) * uint32_t(walker) / uint32_t(sw.W));
+            cap = hi = from + uint32_t(uint64_t(range) * uint32_t(walker + 1) / uint32_t(sw.W));
+            state = b.next_value(first) <= hi ? kUpper : kDone;
+        }
         while (state < kDone) {
+            if (kWalk) {
+                if (tid == 0) least_found = atomicAdd(reinterpret_cast<unsigned long long *>(&sw.least[c]), 0ull);
+                __syncthreads();
+                least_T = least_found;
+            }
             const int form = state == kBottleneck ? Band::kMinMax : state == kUpper ? Band::kSum
                              : state == kAtTop || state == kGallop || state == kBisect ? Band::kAny : Band::kH1;
             if (form == Band::kSum || form == Band::kH1) {
@@ -605,14 +663,14 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
             }
             b.count_cap = cap;
             b.keys_fit = cap <= key_cap;
-            const int64_t v = b.run<Band::kMinMax | Band::kSum | Band::kH1 | Band::kAny>(form, cap);
+            const int64_t v = b.template run<kWalk ? Band::kSum | Band::kH1 : Band::kMinMax | Band::kSum | Band::kH1 | Band::kAny>(form, cap);
             const bool found = v != kInf;
             bool opened = false, climb_on = false, try_on = false, upper_on = false;
-            if (state == kBottleneck) {
+            if (!kWalk && state == kBottleneck) {
                 if (found) { t_S = uint32_t(v); cap = t_S; state = kAtBottleneck; }
                 else if (cap >= meshband::kTopCap) state = kNoPlan;
                 else cap = Band::raised(cap, tries++);
-            } else if (state == kAtBottleneck) {
+            } else if (!kWalk && state == kAtBottleneck) {
                 if (found) {
                     opened = true;
                 } else {
@@ -622,7 +680,7 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                     if (!run_out) state = kNoPlan;
                     else { cap = top; state = kAtTop; }
                 }
-            } else if (state == kAtTop) {
+            } else if (!kWalk && state == kAtTop) {
                 lo = t_S;
                 hi = top;
                 step = (t_S >> 4) + 1u;
@@ -630,20 +688,21 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                 else if (lo + step < hi) { cap = lo + uint32_t(step); state = kGallop; }
                 else if (hi - lo > 1u + (hi >> 12)) { cap = lo + (hi - lo) / 2u; state = kBisect; }
                 else climb_on = true;
-            } else if (state == kGallop || state == kBisect) {
+            } else if (!kWalk && (state == kGallop || state == kBisect)) {
                 if (found) hi = cap; else lo = cap;
                 step *= 4;
                 if (state == kGallop && !found && lo + step < hi) cap = lo + uint32_t(step);
                 else if (hi - lo > 1u + (hi >> 12)) { cap = lo + (hi - lo) / 2u; state = kBisect; }
                 else climb_on = true;
-            } else if (state == kClimb) {
+            } else if (!kWalk && state == kClimb) {
                 if (found) opened = true;
                 else { lo = cap; climb_on = true; }
             } else if (state == kUpper) {
                 // no cap up to hi beats the best total unless the classic sum at hi leaves room for it
-                if (v > best_T) { state = kDone; break; }          // (without a plan included: cannot happen)
+                const int64_t room = (least_T < best_T ? least_T : best_T) - v;
+                if (room < 0) { state = kDone; break; }            // (without a plan included: cannot happen)
                 if (m_less > 0) {
-                    const int64_t lim = (best_T - v) / m_less;
+                    const int64_t lim = room / m_less;
                     if (lim < int64_t(hi)) { hi = lim > 0 ? uint32_t(lim) : 0u; upper_on = true; }
                 }
                 if (!upper_on) {
@@ -662,16 +721,18 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                         best_T = T;
                         best_cap = cap;
                         keep();
+                        if (kWalk && tid == 0) atomicMin(&sw.least[c], (long long)T);
                     }
                 }
+                ++tested;
                 if (found && v == classic) { hi = bn > 0 ? uint32_t(bn) - 1u : 0u; upper_on = true; }
                 else try_on = true;
             }
             if (climb_on) {
                 cap = b.next_value(lo);
-                state = cap > top ? kNoPlan : ++climbed > kMaxClimb ? kOver : kClimb;
+                state = cap > top ? kNoPlan : climbed++ < kMaxClimb ? kClimb : kClimbLeft;
             }
-            if (opened) {
+            if (!kWalk && opened) {
                 first = best_cap = cap;
                 best_T = v + m_less * first;
                 keep();
@@ -689,8 +750,8 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
             if (try_on) {
                 // the next value of the interval in which the classic sum is `classic`
                 cap = b.next_value(cap);
-                const int64_t least_T = classic + m_less * cap;
-                if (cap > hi || least_T > best_T || (least_T == best_T && cap > best_cap)) {
+                const int64_t at_least = classic + m_less * cap;
+                if (cap > hi || at_least > best_T || at_least > least_T || (at_least == best_T && cap > best_cap)) {
                     hi = bn > 0 ? uint32_t(bn) - 1u : 0u;
                     upper_on = true;
                 } else {
@@ -701,8 +762,35 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                 cap = hi;
                 state = hi > first ? kUpper : kDone;
             }
+            if (!kWalk && sw.W > 1 && tested >= kMaxTries && (state == kTry || state == kUpper)) { left = true; state = kDone; }
         }
-        if (state == kOver) { hand_over(); continue; }
+        if (kWalk) {
+            if (tid == 0) {
+                mine.head->T = best_T;
+                mine.head->cap = int64_t(best_cap);
+                mine.head->state = kept ? kSweepPlan : kSweepNone;
+            }
+            continue;
+        }
+        if (state == kOver) { hand_over(0); continue; }
+        if (state == kClimbLeft) {
+            // no value up to lo has a plan: the climb goes on behind them, by several workgroups
+            const uint32_t passed = b.count_values(t_S, lo, more, unused);
+            if (passed < more) {
+                if (tid == 0) {
+                    opening.head->T = kInf;
+                    opening.head->cap = kInf;
+                    opening.head->tried = int32_t(1u + passed);
+                    opening.head->state = kSweepNone;
+                    sw.least[c] = (long long)lo;
+                }
+                hand_over(kClimbOn);
+                continue;
+            }
+            state = kNoPlan;
+            run_out = false;
+            tried = 1u + passed;
+        }
         if (state == kNoPlan) {
             // caps tried: none without a bottleneck; all values, or as many as allowed
             if (run_out) tried = 1u + b.count_values(t_S, top, more, unused);
@@ -715,6 +803,16 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
             out.status[c] = HARP_CAND_OK;
             t_max_out[c] = int64_t(best_cap);
             if (n_caps) n_caps[c] = int32_t(1u + values);
+            if (left) {
+                // the values tried in this interval are tried again: a walker's bounds start at the top of its part
+                opening.head->T = best_T;
+                opening.head->cap = int64_t(best_cap);
+                opening.head->state = kSweepPlan;
+                opening.head->rest[0] = int32_t(first);
+                opening.head->rest[1] = int32_t(hi);
+                sw.least[c] = (long long)best_T;
+                ba.redo[od.C - 1 - atomicAdd(&ba.counters[kShared], 1)] = c;
+            }
         }
     }
 }
@@ -739,7 +837,7 @@ hipError_t launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, c
     int *first_idx = reinterpret_cast<int *>(lower + od.C);
     const bool forced = cand_group != nullptr;
     hipLaunchKernelGGL(k2_mesh_sweep_clear, dim3((od.C + 255) / 256), dim3(256), 0, st, w.counters, first_idx, od.C);
-    SweepItems items{nullptr, nullptr};
+    SweepItems items{nullptr, nullptr, nullptr};
     BandArgs ba;
     int band_threads = 0;
     if (fast32 && !forced && w.index_bytes != 0 &&
@@ -751,12 +849,18 @@ hipError_t launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, c
         ba.per_group = per_group;
         ba.counters = w.counters;
         ba.redo = w.redo;
-        hipLaunchKernelGGL(k2_sweep_band, dim3(unsigned(od.C < n_groups ? od.C : n_groups)), dim3(band_threads),
+        const SweepShare sw{slots, Ws, W, reinterpret_cast<long long *>(lower)};
+        const long long walkers = (long long)od.C * W;
+        hipLaunchKernelGGL(k2_sweep_band<false>, dim3(unsigned(od.C < n_groups ? od.C : n_groups)), dim3(band_threads),
                            size_t(ba.sh.total), st, tb, od, max_caps, out, stage_group, stage_tp, warmup, t_max_out,
-                           n_caps, ba);
+                           n_caps, ba, sw);
         const hipError_t e = hipGetLastError();            // before the launches over what it hands over replace it
         if (e != hipSuccess) return e;
-        items = SweepItems{w.redo, w.counters + 1};
+        if (W > 1)
+            hipLaunchKernelGGL(k2_sweep_band<true>, dim3(unsigned(walkers < n_groups ? walkers : n_groups)),
+                               dim3(band_threads), size_t(ba.sh.total), st, tb, od, max_caps, out, stage_group, stage_tp,
+                               warmup, t_max_out, n_caps, ba, sw);
+        items = SweepItems{w.redo, w.counters + 1, w.counters + kShared};
     }
     fast32 = fast32 && tb.L <= kMeshFastMaxL;
     // cap positions: one uint16 per (row, start cut), kept in LDS when the largest item's rows fit

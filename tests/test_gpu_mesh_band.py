@@ -283,3 +283,52 @@ def test_band_orderings_without_a_plan(harp, ctx):
         assert_plans_equal(got, want, "memory %s, sweep" % (mem,))
         assert (got.n_caps == want.n_caps).all() and (got.t_max == want.t_max).all()
     assert some >= 2
+
+
+def _tight_sweep(seed):
+    """A random problem of a few groups with memory around what its plans need, orderings of it, a limit of caps."""
+    rng = np.random.default_rng(seed)
+    G = int(rng.integers(2, 6))
+    ndev = tuple(int(x) for x in rng.integers(1, 6, size=G))
+    L, M, T = int(rng.integers(max(8, G), 34)), int(rng.choice([2, 3, 5, 8, 20, 62])), int(rng.integers(1, 4))
+    bw = rng.integers(20, 900, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 4000
+    fwd = np.rint(np.exp(6 + 0.6 * rng.standard_normal((1, L)))).astype(np.int64)
+    act = rng.integers(8, 65, size=L) * int(rng.choice([100, 1000, 5000]))
+    p = simple_problem(np.zeros(L), M=M, T=T, G=G, ndev=ndev, tp=(1, 2, 4), gtype=[g % T for g in range(G)],
+                       fwd=np.concatenate([fwd * (t + 1) for t in range(T)]),
+                       bwd=np.concatenate([2 * fwd * (t + 1) for t in range(T)]), act=act, params=2000 * fwd[0],
+                       stash=4 * act, bw=bw)
+    need = p.param_bytes.sum() + min(M, sum(ndev) / 2) / 2 * p.stash_bytes.sum()
+    p.type_mem_bytes[:] = rng.uniform(0.6, 2.5) * rng.uniform(0.6, 1.4, size=T) * need / sum(ndev)
+    orders = W.make_orderings(p, seed, 5, G, max(G, min(L, sum(ndev))), 0, int(rng.integers(1, 6)))
+    return p, orders, int(rng.choice([1 << 20, 1 << 20, 5, 40, 300]))
+
+
+def test_band_sweep_left_to_several_workgroups(harp, ctx):
+    """Tight memory: orderings whose bounds rule little out leave the rest of their caps to several workgroups,
+    and those whose climb fails a few times leave it to the kernels that try every cap, from where it stands.
+    Against those kernels from the start (int64 path)."""
+    import torch
+    shared = climbing = 0
+    for seed in range(400):
+        p, orders, max_caps = _tight_sweep(seed)
+        tables = harp.Tables(ctx, p)
+        assert tables.fast32
+        do = harp.DeviceOrderings(ctx, orders)
+        C, S_max = orders.C, orders.S_max
+        out = harp.DevicePlans(ctx, C, S_max)
+        ints = [torch.full(n, -7, dtype=torch.int32, device=ctx.device) for n in ((C, S_max), (C, S_max), (C, S_max), (C,))]
+        group, tp, warmup, n_caps = ints
+        t_max = torch.full((C,), -7, dtype=torch.int64, device=ctx.device)
+        ws = harp.mesh_sweep_workspace(ctx, tables, do)
+        for _ in range(2):                               # the workspace of one call is lent to the next
+            harp.harp_plan_mesh_h1f1b_sweep_batch(ctx, tables, do, max_caps, out, group, tp, warmup, t_max, ws, n_caps)
+        want, _ = harp.plan_mesh_h1f1b_sweep(ctx, p, orders, max_caps, harp.PATH_GENERIC)
+        assert_plans_equal(out.to_host(), want, "seed %d" % seed)
+        for name, got in (("stage_group", group), ("stage_tp", tp), ("warmup", warmup), ("t_max", t_max), ("n_caps", n_caps)):
+            assert (got.cpu().numpy() == getattr(want, name)).all(), (seed, name)
+        counters = ws[:32].view(torch.int32).tolist()    # of the launch: orderings handed over [1], left to walkers [5]
+        climbing, shared = climbing + counters[1], shared + counters[5]
+    assert shared >= 3 and climbing >= 3
