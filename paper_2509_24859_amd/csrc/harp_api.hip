@@ -167,10 +167,10 @@ size_t plan_bytes_on_path(const harp_tables *t, const harp_candidates *cd, bool 
     return prepass + size_t(units) * plan_generic_ws_per_group(t->dev.L, cd->S_max) + 256;
 }
 
-// Workgroups of the submesh planner: as many of 256 threads as are resident, fewer when their slices
-// would pass 16 GiB.
-int n_mesh_groups(const harp_ctx *ctx, int C, size_t per_group) {
-    long long n = (long long)ctx->n_cu * 8;
+// Workgroups of the submesh planner that have a slice: as many of the whole-table form's as are resident, fewer
+// when their slices would pass 16 GiB.  The band form makes do with as many.
+int n_mesh_groups(const harp_ctx *ctx, int C, size_t per_group, int threads) {
+    long long n = (long long)ctx->n_cu * (2048 / threads);
     const long long fit = (long long)((size_t(16) << 30) / (per_group ? per_group : 1));
     if (n > fit) n = fit;
     if (n > C) n = C;
@@ -538,7 +538,8 @@ int harp_plan_h1f1b_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *
 size_t harp_plan_mesh_workspace_bytes(harp_ctx *ctx, harp_tables *t, const harp_orderings *od) {
     if (check_orderings(ctx, t, od) != HARP_OK) return 0;
     const size_t per_group = plan_mesh_ws_per_group(t->dev.L, od->S_max, t->total_devices);
-    return plan_mesh_ws_fixed(t->dev, od->S_max, od->C) + size_t(n_mesh_groups(ctx, od->C, per_group)) * per_group;
+    const int threads = plan_mesh_threads(t->dev.L, t->total_devices, od->C, ctx->n_cu);
+    return plan_mesh_ws_fixed(t->dev, od->S_max, od->C) + size_t(n_mesh_groups(ctx, od->C, per_group, threads)) * per_group;
 }
 
 size_t harp_plan_mesh_sweep_workspace_bytes(harp_ctx *ctx, harp_tables *t, const harp_orderings *od) {
@@ -565,7 +566,7 @@ int plan_mesh_common(harp_ctx *ctx, harp_tables *t, const harp_orderings *od, co
     if (!mesh_index_fits(t)) return fail(ctx, HARP_ERR_SHAPE, "(devices + 1) x (L + 1) must stay below 2^31 for the kernels with a device index");
     const size_t per_group = plan_mesh_ws_per_group(t->dev.L, od->S_max, t->total_devices);
     const int threads = plan_mesh_threads(t->dev.L, t->total_devices, od->C, ctx->n_cu);
-    const int groups = n_mesh_groups(ctx, od->C, per_group);
+    const int groups = n_mesh_groups(ctx, od->C, per_group, threads);
     const size_t need = plan_mesh_ws_fixed(t->dev, od->S_max, od->C) + size_t(groups) * per_group;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return fail(ctx, HARP_ERR_WORKSPACE, "workspace must be a 256-byte aligned device pointer");
@@ -608,7 +609,7 @@ int harp_plan_mesh_h1f1b_batch(harp_ctx *ctx, harp_tables *t, const harp_orderin
     if (!mesh_index_fits(t)) return fail(ctx, HARP_ERR_SHAPE, "(devices + 1) x (L + 1) must stay below 2^31 for the kernels with a device index");
     const size_t per_group = plan_mesh_ws_per_group(t->dev.L, od->S_max, t->total_devices);
     const int threads = plan_mesh_threads(t->dev.L, t->total_devices, od->C, ctx->n_cu);
-    const int groups = n_mesh_groups(ctx, od->C, per_group);
+    const int groups = n_mesh_groups(ctx, od->C, per_group, threads);
     const size_t need = plan_mesh_ws_fixed(t->dev, od->S_max, od->C) + size_t(groups) * per_group;
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return fail(ctx, HARP_ERR_WORKSPACE, "workspace must be a 256-byte aligned device pointer");

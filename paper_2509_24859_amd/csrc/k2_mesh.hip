@@ -518,10 +518,12 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
 
 // Workgroups of the band kernels: a batch of at most one ordering per CU gets the whole CU's LDS and
 // 1,024 threads each; beyond that two workgroups of 512 threads share a CU (the key rows of the exact form
-// and the rows of the H-1F1B form want the room), or four of 256 in the min-max form.
-bool meshband::band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int &threads,
-                 BandShape &sh) {
-    threads = od.C <= n_cu ? 1024 : (form != meshband::kFormMinMax || od.C <= 2 * n_cu) ? 512 : 256;
+// and the rows of the H-1F1B form want the room), or four of 256 in the min-max form where there are slices for
+// four: large tables have two per CU, and there, on 160 operators and 128 devices, 600 / 1,024 / 4,096 orderings
+// take 1.45 / 2.01 / 5.47 ms with two workgroups of 512, 2.24 / 2.37 / 5.40 ms with four of 256.
+bool meshband::band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int n_groups,
+                           int &threads, BandShape &sh) {
+    threads = od.C <= n_cu ? 1024 : (form != kFormMinMax || od.C <= 2 * n_cu || n_groups < 4 * n_cu) ? 512 : 256;
     const size_t budget = threads == 1024 ? (size_t(156) << 10) : threads == 512 ? (size_t(79) << 10) : (size_t(39) << 10);
     return band_shape(tb, od.S_max, od.G_max, total_devices, threads, form, budget, sh);
 }
@@ -584,7 +586,7 @@ hipError_t mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int f
     const long long resident = (long long)n_cu * (2048 / threads);
     const dim3 grid(unsigned(n_groups < resident ? n_groups : resident));
     if (fast32 && w.index_bytes != 0 && !whole_table(tb, od, total_devices) &&
-        meshband::band_launch(tb, od, total_devices, form, n_cu, band_threads, ba.sh)) {
+        meshband::band_launch(tb, od, total_devices, form, n_cu, n_groups, band_threads, ba.sh)) {
         launch_plan_index(tb, od.S_max, w.index, st);
         ba.lo_tab = w.index;
         ba.hi_tab = w.index + w.index_bytes / 4;
@@ -592,7 +594,8 @@ hipError_t mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int f
         ba.per_group = per_group;
         ba.counters = w.counters;
         ba.redo = w.redo;
-        band(dim3(n_groups), dim3(band_threads), size_t(ba.sh.total), ba);
+        const int band_resident = n_cu * (1024 / band_threads);
+        band(dim3(n_groups < band_resident ? n_groups : band_resident), dim3(band_threads), size_t(ba.sh.total), ba);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         whole(fast, grid, dim3(threads), MeshItems{w.counters + 2, w.redo, w.counters + 1}, w.slices, per_group);

@@ -841,7 +841,7 @@ hipError_t launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, c
     BandArgs ba;
     int band_threads = 0;
     if (fast32 && !forced && w.index_bytes != 0 &&
-        meshband::band_launch(tb, od, total_devices, meshband::kFormSweep, n_cu, band_threads, ba.sh)) {
+        meshband::band_launch(tb, od, total_devices, meshband::kFormSweep, n_cu, n_groups, band_threads, ba.sh)) {
         launch_plan_index(tb, od.S_max, w.index, st);
         ba.lo_tab = w.index;
         ba.hi_tab = w.index + w.index_bytes / 4;

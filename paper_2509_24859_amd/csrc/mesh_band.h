@@ -86,9 +86,10 @@ struct MeshWorkspace {
     size_t before_slices;
 };
 MeshWorkspace mesh_carve(const TablesDev &tb, int S_max, int C, void *ws);
-// Threads and LDS of the band kernels for a batch; false when the batch is for the int64 kernels.
-bool band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int &threads,
-                 BandShape &sh);
+// Threads and LDS of the band kernels for a batch, given how many workgroups have a slice; false when the batch
+// is for the whole-table kernels.
+bool band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int n_groups,
+                 int &threads, BandShape &sh);
 
 // Per workgroup, in the workspace slice: F, B [S_cap + 1][cols] uint16, first cell index less lowest
 // cut [S_cap + 1][cols] int32, value rows (uint32) or, H-1F1B, back-pointers (uint16).

@@ -332,3 +332,18 @@ def test_band_sweep_left_to_several_workgroups(harp, ctx):
         counters = ws[:32].view(torch.int32).tolist()    # of the launch: orderings handed over [1], left to walkers [5]
         climbing, shared = climbing + counters[1], shared + counters[5]
     assert shared >= 3 and climbing >= 3
+
+
+def test_mesh_workspace_has_a_slice_per_resident_workgroup(harp, ctx):
+    """160 operators, 128 devices, 32 stages: two whole-table workgroups of 1,024 threads are resident per
+    compute unit, and the band form needs no more slices than those have."""
+    import torch
+    L, D, S = 160, 128, 32
+    p = _problem(1, L, (D // 2, D // 2), (1, 2, 4, 8))
+    orders = W.orderings_from_lists([(S, [0, 1])] * 4096)
+    do = harp.DeviceOrderings(ctx, orders)
+    row = (L + 1) * (D + 1)
+    slice_bytes = 24 * row + 4 * S * row                     # two rows of values and counts, back-pointers
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    need = harp.mesh_workspace(ctx, harp.Tables(ctx, p), do).numel()
+    assert need <= 2 * n_cu * (slice_bytes + 256) + (1 << 22)     # lists and the feasibility index: below 4 MB
