@@ -398,12 +398,15 @@ void launch_score(const TablesDev &tb, const CandDev &cd, const int32_t *splits,
     if (fast32 && cd.S_max <= 64) {
         uint32_t shift_packed = 0;
         for (int k = 0; k < tb.n_tp; ++k) shift_packed |= uint32_t(tb.tp_shift[k] & 15) << (4 * k);
-        // Reading the sums into LDS pays once every wavefront has two candidates: 16,384 candidates of up to
-        // 64 stages take 11.4 us with it, 16,383 without it 13.4 us.  Below that a workgroup would read more
-        // sums than its candidates use.
+        // Reading the sums into LDS pays once every wavefront has two candidates and the gathers spared outweigh the
+        // reading.  The reading costs about 1.4 us per 64 KB, a thousand candidates of up to 8 stages gain about
+        // 0.033 us, longer ones in proportion (90 to 4,000 operators, 16,384 to 262,144 candidates).  Without / with
+        // it, us: 16,384 candidates of up to 64 stages 13.2 / 11.1 (512 operators), 24.0 / 19.5 (4,000); of up to 8
+        // stages 8.3 / 8.0 (512), 8.4 / 8.7 (2,000), 8.6 / 9.2 (4,000); 65,536 of those 25.5 / 25.2 (4,000).
         const size_t staged = (size_t(tb.L) + 1 + size_t(tb.G)) * sizeof(longlong2);
         const int resident = n_cu * 32;                          // as many wavefronts as the chip holds
-        if (staged <= kStagedBytes && cd.C >= resident * 2) {
+        const size_t stages = cd.S_max > 8 ? size_t(cd.S_max) : 8;
+        if (staged <= kStagedBytes && cd.C >= resident * 2 && 16 * staged <= 3 * size_t(cd.C) * stages) {
             hipLaunchKernelGGL((k3_score_fast<kStagedWaves, true>), dim3(resident / kStagedWaves),
                                dim3(kStagedWaves * 64), staged, st, tb, cd, splits, bottleneck, iter_time, status,
                                shift_packed);

@@ -660,14 +660,13 @@ def test_score_checks_the_slot_lists_on_both_paths(harp, ctx):
 
 @pytest.mark.parametrize("G,L,C", [(1, 4, 16384), (32, 90, 16384), (33, 90, 16391), (64, 4031, 16384), (65, 4031, 16384),
                                    (65, 90, 16389), (64, 90, 16383)], ids=str)
-def test_score_of_large_batches(harp, ctx, G, L, C):
+def test_score_of_large_batches(harp, ctx, G, L, C, S_max=64):
     """The scorer's kernel for large batches at its edges: group sets of one and two words and beyond, sums
     that just fit in LDS (L + 1 + G = 4,096) and do not, a last round that is nearly empty, the smallest
     batch it takes on 256 CUs and one below; a quarter of the slot lists enter a group twice, use too many
     devices or have cuts that do not rise."""
     import torch
     rng = np.random.default_rng(G * L)
-    S_max = 64
     bw = rng.integers(2, 60, size=(G, G))
     bw = np.minimum(bw, bw.T)
     p = simple_problem(np.zeros(L), M=7, T=2, G=G, ndev=[4 + g % 3 for g in range(G)], tp=(1, 2, 4),
@@ -702,6 +701,13 @@ def test_score_of_large_batches(harp, ctx, G, L, C):
     torch.cuda.synchronize()
     for got, name, expected in zip((b, t, st), ("bottleneck", "iter_time", "status"), want):
         assert (got.cpu().numpy() == expected[at]).all(), name
+
+
+@pytest.mark.parametrize("C", [21386, 21387], ids=str)
+def test_score_of_short_pipelines_in_long_sequences(harp, ctx, C):
+    """Up to 8 stages of 2,000 operators in 4 groups: the sums (16 bytes for every cut and group) go to LDS from
+    21,387 candidates on."""
+    test_score_of_large_batches(harp, ctx, 4, 2000, C, 8)
 
 
 def test_argmin_parity(harp, ctx):
