@@ -17,7 +17,8 @@
 // classic ones the ranges are worked out with).  For the min-max pass any t >= the optimum will do:
 // the smallest t at which F reaches (S, L, all devices) is found by a search over chains first.  A
 // chain can leave a stage without operators, so where some device's memory holds no operator alone the
-// pass may find no plan under that t; it is then repeated once without a cap on the times.  On orderings of 82 operators and 64 devices the ranges hold between
+// pass may find no plan under that t; it is then repeated under a higher one, and at last
+// without a cap on the times.  On orderings of 82 operators and 64 devices the ranges hold between
 // 0.1% and 25% of the (i, d) cells, the wide ones where a slow link decides the bottleneck.
 //
 // A chain is worked by one wavefront, lanes over the columns d, so several values of t are tried at
@@ -890,12 +891,13 @@ struct Band {
         return good;
     }
 
-    // The cap after one under which the min-max pass found no plan: an eighth above, where an optimum that the chains
-    // missed lies as a rule, then none: 1,024 orderings of 82 operators and 64 devices with a plan each take 478 us
-    // so, 567 us without the step; 1,024 of 120 operators and 60 stages on 64 devices, none with a plan, 747 and
-    // 618 us (2,660 us with steps that grow up to 2^31, some twenty passes).
+    // The cap after one under which the min-max pass found no plan: an eighth above, then a quarter, where an optimum
+    // that the chains missed lies as a rule, then none.  With no / one / both steps, us: 1,024 orderings of 82
+    // operators and 64 devices, each with a plan, 567 / 478 / 473; 160 operators and 128 devices 4,860 / 6,130 /
+    // 4,340; 120 operators, 60 stages on 64 devices, none with a plan, 618 / 746 / 870 (2,650 with steps that grow
+    // up to 2^31, some twenty passes).
     static __device__ __forceinline__ uint32_t raised(uint32_t t, int tries) {
-        return tries == 0 && t < kTopCap / 2 ? t + (t >> 3) + 1u : kTopCap;
+        return tries < 2 && t < kTopCap / 2 ? t + (t >> (3 - tries)) + 1u : kTopCap;
     }
 
     // The recurrence with H-1F1B warm-up counts (eq. dp_ni) in the ranges of the last prepare, suffix
