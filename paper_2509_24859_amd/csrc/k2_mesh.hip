@@ -18,6 +18,8 @@
 // operators; the whole table on the 32-bit rows serves problems so small that finding the ranges costs more
 // than they save (whole_table), more than 2,048 devices, and the orderings the band form hands over
 // because their sets of time rows do not fit its LDS or their sums could reach 2^31.
+#include <math.h>
+
 #include "mesh_band.h"
 #include "mesh_passes.h"
 
@@ -523,7 +525,8 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
 // take 1.45 / 2.01 / 5.47 ms with two workgroups of 512, 2.24 / 2.37 / 5.40 ms with four of 256.
 bool meshband::band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu, int n_groups,
                            int &threads, BandShape &sh) {
-    threads = od.C <= n_cu ? 1024 : (form != kFormMinMax || od.C <= 2 * n_cu || n_groups < 4 * n_cu) ? 512 : 256;
+    const int want = od.C < 4 * n_cu ? od.C : 4 * n_cu;
+    threads = od.C <= n_cu ? 1024 : (form != kFormMinMax || od.C <= 2 * n_cu || n_groups < want) ? 512 : 256;
     const size_t budget = threads == 1024 ? (size_t(156) << 10) : threads == 512 ? (size_t(79) << 10) : (size_t(39) << 10);
     return band_shape(tb, od.S_max, od.G_max, total_devices, threads, form, budget, sh);
 }
@@ -553,19 +556,24 @@ size_t plan_mesh_ws_fixed(const TablesDev &tb, int S_max, int C) {
 
 namespace {
 
-// Problems whose whole tables are worked faster than the ranges of their cuts are found.  A stage of the
-// whole table costs about (cuts) x (device offsets it can end at) x (degrees) x (cuts scanned), and the
-// offsets are at most devices - stages + 2 (every stage takes a device); the ranges cost a few serial steps
-// per stage whatever the size.  Measured over 70 random problems of both forms (whole table / ranges, us):
-// product 2,450: 76 / 367 (34 operators, 24 devices); 25,992: 72 / 157 (18, 30); 95,256: 277 / 272 (62, 12);
-// 154,880: 909 / 1144 (43, 40); 202,300: 208 / 115 (84, 14); 248,832: 383 / 291 (143, 8); 813,824: 2842 / 1397
-// (135, 16).  Below the line the ranges are ahead in 3 of 55 problems, by 1.4x at most; above it the whole
-// table in 4 of 15, by 1.6x at most.
-constexpr int64_t kWholeTable = 160000;
-bool whole_table(const TablesDev &tb, const OrdDev &od, int64_t total_devices) {
-    const int64_t stages = od.S_max < total_devices ? od.S_max : total_devices;
-    const int64_t cuts = tb.L + 1;
-    return cuts <= 1024 && cuts * cuts * (total_devices - stages + 2) * tb.n_tp <= kWholeTable;
+// Problems whose whole tables are worked faster than the ranges of their cuts are found.  A stage of the whole
+// table costs about (cuts) x (device offsets) x (degrees) x (cuts scanned).  With S stages it can end at most at
+// L - S + 1 cuts and devices - S + 1 offsets (every stage takes one of each); the H-1F1B form scans all L + 1.  The
+// ranges cost a few serial steps per stage whatever the size: a workgroup's lanes make the product cheap, and many
+// orderings share the lanes.  The orderings' own stage counts are not known here, so S is the largest.
+// Measured on 260 random problems of 10 to 160 operators, up to 80 devices and 4,096 orderings, product: whole
+// table / ranges, us.  Min-max: 1,680 (49 operators, 47 stages on 80 devices): 228 / 552; 106,090: 74 / 60; 145,800:
+// 190 / 157; 165,375: 55 / 91; 53,792 with 2,767 orderings: 1,468 / 910.  Exact: 44,944: 127 / 92; 61,952: 1,335 /
+// 1,668; 77,976: 608 / 531; 92,256: 5,600 / 3,406.  H-1F1B: 22,050: 69 / 86; 27,378: 290 / 246; 51,076: 48 / 66; 59,168: 238 / 202; 102,966: 151 / 79.
+// The form chosen takes 1.017 x the faster one's time on average and 1.9 x at most; the whole table always 1.15 x and
+// 6.8 x, the ranges always 1.7 x and 7.9 x.
+bool whole_table(const TablesDev &tb, const OrdDev &od, int64_t total_devices, int form, int n_cu) {
+    const int64_t most = total_devices < tb.L ? total_devices : tb.L, stages = od.S_max < most ? od.S_max : most;
+    const int64_t cuts = form == meshband::kFormH1 ? tb.L + 1 : tb.L - stages + 2;
+    if (cuts > 1024) return false;
+    const double per_cu = od.C > n_cu && form != meshband::kFormH1 ? sqrt(double(od.C) / n_cu) : 1.0;
+    const double limit = form == meshband::kFormH1 ? 20e3 : form == meshband::kFormSum ? 70e3 : 160e3;
+    return double(cuts * cuts * (total_devices - stages + 2) * tb.n_tp) * per_cu <= limit;
 }
 
 // The band launch of a batch and, behind it, the whole-table launch over what it handed over.  band(sh, ...)
@@ -585,7 +593,7 @@ hipError_t mesh_launch(const TablesDev &tb, const OrdDev &od, bool fast32, int f
     // workgroup per CU, 7.4 ms on eight)
     const long long resident = (long long)n_cu * (2048 / threads);
     const dim3 grid(unsigned(n_groups < resident ? n_groups : resident));
-    if (fast32 && w.index_bytes != 0 && !whole_table(tb, od, total_devices) &&
+    if (fast32 && w.index_bytes != 0 && !whole_table(tb, od, total_devices, form, n_cu) &&
         meshband::band_launch(tb, od, total_devices, form, n_cu, n_groups, band_threads, ba.sh)) {
         launch_plan_index(tb, od.S_max, w.index, st);
         ba.lo_tab = w.index;

@@ -195,16 +195,16 @@ def _repeated(orders, extra, C):
     return at, W.orderings_from_lists(lists, S_max=orders.S_max, G_max=orders.G_max), many
 
 
-@pytest.mark.parametrize("scale,slow,stages", [(1, False, (8, 7, 9, 6)), (1 << 13, False, (8, 7, 9, 6)),
-                                               (1 << 14, True, (64, 60, 63, 26))], ids=["in_range", "no_keys", "handed_over"])
+@pytest.mark.parametrize("L,scale,slow,stages", [(75, 1, False, (8, 7, 9, 6)), (75, 1 << 13, False, (8, 7, 9, 6)),
+                                                 (140, 1 << 13, True, (64, 60, 63, 26))], ids=["in_range", "no_keys", "handed_over"])
 @pytest.mark.parametrize("C", [300, 700, 2500])
-def test_band_kernels_on_large_batches(harp, ctx, C, scale, slow, stages):
+def test_band_kernels_on_large_batches(harp, ctx, C, L, scale, slow, stages):
     """More orderings than compute units (512-thread workgroups), than twice as many (256 threads in the
     min-max form), and than there are workgroups; in range, with sums that leave 32 bits times a degree, and
     with sums that leave 32 bits themselves (the band kernels hand those over).  The batch repeats a few
     orderings, malformed and infeasible ones among them, so the oracle works each once."""
     ndev, tp = (40, 34, 2), (1, 2, 4, 8, 16)            # 77 columns
-    p = _problem(7, 75, ndev, tp, slow, scale)
+    p = _problem(7, L, ndev, tp, slow, scale)
     assert harp.Tables(ctx, p).fast32
     orders = W.orderings_from_lists(list(zip(stages, ([0, 1, 2], [2, 1, 0], [1, 0], [0]))), S_max=max(stages) + 3,
                                     G_max=4)
@@ -258,7 +258,7 @@ def test_band_orderings_without_a_plan(harp, ctx):
     """Tight memory on one of two GPU types, as many stages as devices: the chains, which may leave a stage
     without operators, reach the end on orderings that have no plan, and below the optimum of others."""
     rng = np.random.default_rng(1)
-    L, G = 120, 4
+    L, G = 150, 4
     bw = rng.integers(20, 60, size=(G, G))
     bw = np.minimum(bw, bw.T)
     bw[np.arange(G), np.arange(G)] = 500
@@ -269,7 +269,7 @@ def test_band_orderings_without_a_plan(harp, ctx):
     lists = [(S, [int(g) for g in rng.permutation(G)[:k]]) for S, k in ((40, 4),) * 8 + ((30, 3),) * 6 + ((20, 2),) * 4]
     orders = W.orderings_from_lists(lists, S_max=40)
     some = 0
-    for mem in ((900, 300), (1080, 360), (1200, 330)):
+    for mem in ((1100, 370), (1350, 450), (1500, 400)):
         p.type_mem_bytes[:] = mem
         want = oracle_plan_mesh_threaded(oracle.build_tables(p), orders)
         some += int((want.status != oracle.OK).any() and (want.status == oracle.OK).any())
