@@ -465,14 +465,13 @@ MeshWorkspace meshband::mesh_carve(const TablesDev &tb, int S_max, int C, void *
 
 // LDS of a band workgroup: `budget` bytes, more when the time rows need it; false when they do not fit
 // the CU.
-bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t total_devices, int threads, int form,
-                          size_t budget, BandShape &sh) {
+bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t total_devices, int form, size_t budget,
+                          BandShape &sh) {
     if (total_devices > kMaxDevices) return false;
     sh.W = tb.L + 1;
     sh.NW = (sh.W + 63) / 64;
     sh.cols = int(total_devices) + 1;
     sh.K_cap = G_max < tb.G ? G_max : tb.G;
-    sh.teams = threads > 64 ? 2 : 1;
     sh.S_cap = S_max < tb.L ? S_max : tb.L;
     sh.idx_pitch = int(fastdp::lo_pitch(tb.L));
     size_t off = 0;
@@ -485,8 +484,8 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     sh.o_group_at = take(size_t(sh.cols) * 2);
     const bool sums = form == kFormSum || form == kFormSweep, h1 = form == kFormH1 || form == kFormSweep;
     sh.o_mem = take(h1 ? size_t(sh.W) * 16 : 0);
-    sh.o_chain = take(size_t(sh.teams) * sh.cols * 2);
-    sh.o_ok = take(size_t(sh.teams) * 2 * sh.K_cap * sh.NW * 8);
+    sh.o_chain = take(size_t(kTeams) * sh.cols * 2);
+    sh.o_ok = take(size_t(kTeams) * 2 * sh.K_cap * sh.NW * 8);
     sh.o_col = take(size_t(sh.cols) * 24);
     sh.o_small = take(32 + size_t(sh.S_cap + 1) * 12 + size_t(sh.S_cap) * 11);
     // time rows: of every group when they fit half the budget, else of as many sets as do, at least one per type
@@ -528,7 +527,7 @@ bool meshband::band_launch(const TablesDev &tb, const OrdDev &od, int64_t total_
     const int want = od.C < 4 * n_cu ? od.C : 4 * n_cu;
     threads = od.C <= n_cu ? 1024 : (form != kFormMinMax || od.C <= 2 * n_cu || n_groups < want) ? 512 : 256;
     const size_t budget = threads == 1024 ? (size_t(156) << 10) : threads == 512 ? (size_t(79) << 10) : (size_t(39) << 10);
-    return band_shape(tb, od.S_max, od.G_max, total_devices, threads, form, budget, sh);
+    return band_shape(tb, od.S_max, od.G_max, total_devices, form, budget, sh);
 }
 
 // Threads of a whole-table workgroup: a stage has up to L x devices target cells, so small tables get many

@@ -45,13 +45,13 @@ constexpr uint32_t kNoCut = 0xFFFFu;
 constexpr uint32_t kInfSum = 0x80000000u;        // least sums stay below this (largest_cap)
 constexpr uint32_t kTopCap = 0x7FFFFFFFu;        // no time on these tables is larger
 constexpr int kRowPad = 4;                       // a window of four entries may overrun a row
+constexpr int kTeams = 2;                        // chains worked at once, by one wavefront each
 
 // LDS layout of a launch (byte offsets into dynamic LDS) and its capacities.
 struct BandShape {
     int W, NW;                   // cuts (L + 1), 64-bit words of a mask of cuts
     int cols;                    // columns: devices + 1
     int K_cap, set_cap, row_cap; // groups of an ordering, sets of time rows, cells of a value row in LDS
-    int teams;                   // chains worked at once, by one wavefront each: 2, or 1 in a one-wavefront workgroup
     int S_cap;                   // min(S_max, L)
     int idx_pitch;               // feasibility index
     uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_prow, o_reach, o_mem, o_chain, o_ok, o_col, o_small, o_rows,
@@ -64,11 +64,11 @@ constexpr int kMaxDevices = 2048;                // columns sit in LDS, 24 bytes
 constexpr size_t kBandLds = (size_t(160) << 10) - 1024;
 // forms of a launch: what the value rows hold
 constexpr int kFormMinMax = 0, kFormSum = 1, kFormH1 = 2, kFormSweep = 3;
-bool band_shape(const TablesDev &tb, int S_max, int G_max, int64_t total_devices, int threads, int form, size_t budget,
+bool band_shape(const TablesDev &tb, int S_max, int G_max, int64_t total_devices, int form, size_t budget,
                 BandShape &sh);
 
 // What the band kernels of a launch share: LDS shape, feasibility index, slices, and counters [0] ticket,
-// [1] orderings handed over to the int64 kernels, [2] .. tickets of those.
+// [1] orderings handed over to the whole-table kernels, [2] .. tickets of those.
 struct BandArgs {
     BandShape sh;
     const uint16_t *lo_tab, *hi_tab;
@@ -135,8 +135,8 @@ struct Band {
     uint32_t *prow;              // [sets][n_tp][W]
     uint16_t *reach;             // [2][sets][n_tp][W] reach of a stage under a cap
     int64_t *mem;                // PP [W], PS [W] (H-1F1B form)
-    uint16_t *chain;             // [teams][cols]
-    unsigned long long *ok;      // [teams][2 K][NW]
+    uint16_t *chain;             // [kTeams][cols]
+    unsigned long long *ok;      // [kTeams][2 K][NW]
     uint16_t *col_lo, *col_hi;   // [2][cols]
     uint32_t *col_min;           // [2][cols] least value of a column (min-max form)
     int32_t *col_off;            // [2][cols] index of a column's first cell less its lowest cut
@@ -519,17 +519,15 @@ struct Band {
         reach_table<true>(t, 0);
         reach_table<false>(t, 1);
         __syncthreads();
-        const bool two = sh.teams == 2;
         if (wave == 0) {
-            bool good = forward_chain(0, masks(0), chain, sl.F);
-            if (!two && good) good = backward_chain(1, masks(0), chain, sl.B);
+            const bool good = forward_chain(0, masks(0), chain, sl.F);
             if (lane == 0) scal[0] = good ? 1u : 0u;
-        } else if (two && wave == 1) {
+        } else if (wave == 1) {
             const bool good = backward_chain(1, masks(0), chain + sh.cols, sl.B);
             if (lane == 0) scal[1] = good ? 1u : 0u;
         }
         __syncthreads();
-        if (scal[0] == 0 || (two && scal[1] == 0)) return false;
+        if (scal[0] == 0 || scal[1] == 0) return false;
         // cells of every row: columns one after the other, a wavefront per row
         for (int s = wave; s <= S; s += nthreads >> 6) {
             int total = 0;
@@ -862,28 +860,28 @@ struct Band {
         int64_t bad = bound - 1, good = -1;                // largest t known to have no plan, smallest t whose chain succeeds
         // until the two are within 1/12 of each other: below that the rows hardly get shorter than a workgroup
         for (int round = 0; good < 0 || good - bad > good / 12 + 1; ++round) {
-            int64_t at[2];
-            for (int w = 0; w < 2; ++w) {
+            int64_t at[kTeams];
+            for (int w = 0; w < kTeams; ++w) {
                 // the optimum lay at the guess on half of the orderings looked at, within a fifth above on most others
-                const int step = sh.teams == 2 ? round * 2 + w : round;
+                const int step = round * kTeams + w;
                 int64_t t;
-                if (good >= 0) t = bad + (good - bad) * (w + 1) / (sh.teams + 1);
+                if (good >= 0) t = bad + (good - bad) * (w + 1) / (kTeams + 1);
                 else t = step == 0 ? g : step == 1 ? g + g * 7 / 32 + 1 : step == 2 ? g + g * 5 / 8 + 1 : step == 3 ? 5 * g / 2 + 1
                          : step == 4 ? 8 * g + 1 : step == 5 ? 64 * g + 1 : int64_t(kTopCap);
                 at[w] = t < int64_t(kTopCap) ? t : int64_t(kTopCap);
             }
             __syncthreads();
-            cut_masks(sh.teams, uint32_t(at[0]), uint32_t(at[1]));
-            for (int w = 0; w < sh.teams; ++w) reach_table<true>(uint32_t(at[w]), w);
+            cut_masks(kTeams, uint32_t(at[0]), uint32_t(at[1]));
+            for (int w = 0; w < kTeams; ++w) reach_table<true>(uint32_t(at[w]), w);
             __syncthreads();
-            if (wave < sh.teams) {
+            if (wave < kTeams) {
                 const bool fine = forward_chain(wave, masks(wave), chain + wave * sh.cols, nullptr);
                 if (lane == 0) scal[wave] = fine ? 1u : 0u;
             }
             __syncthreads();
-            for (int w = sh.teams - 1; w >= 0; --w)
+            for (int w = kTeams - 1; w >= 0; --w)
                 if (scal[w] != 0) good = at[w];
-            for (int w = 0; w < sh.teams; ++w)
+            for (int w = 0; w < kTeams; ++w)
                 if (scal[w] == 0 && at[w] > bad) bad = at[w];
             if (good < 0 && bad >= int64_t(kTopCap)) return -1;           // no plan under any cap
             if (good == g) break;                                          // near enough
