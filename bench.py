@@ -326,7 +326,7 @@ def mesh_search(ctx, binding, torch, workloads, name, n_orders, reps, cpu_orders
     ok = got.status == 0
     S = orders.ord_S.astype(np.float64)
     dense = float((S * p.L * p.L / 2 * int(p.group_ndev.sum()) * len(p.tp_degrees)).sum())
-    res = {"kernel": "k2_mesh (one harp_plan_mesh_batch call)", "workload": "%s: L=%d, %d devices in %d groups, %d orderings, S<=%d"
+    res = {"kernel": "k2_mesh_band (one harp_plan_mesh_batch call)", "workload": "%s: L=%d, %d devices in %d groups, %d orderings, S<=%d"
            % (name, p.L, int(p.group_ndev.sum()), p.G, do.C, do.S_max), "ms_per_call": ms,
            "orderings_per_s": do.C / (ms * 1e-3), "dense_transitions_per_s": dense / (ms * 1e-3),
            "feasible_fraction": float(ok.mean()), "workspace_bytes": int(ws.numel())}
@@ -349,7 +349,8 @@ def mesh_search(ctx, binding, torch, workloads, name, n_orders, reps, cpu_orders
     res["exact_mean_capped_passes"] = float(npass.cpu().numpy()[ok].mean()) if ok.any() else None
     res["exact_mean_gain_over_min_max"] = (float((1.0 - got_e.iter_time[ok] / got.iter_time[ok]).mean())
                                            if ok.any() else None)
-    # the search around the full recurrence: every candidate cap from t_S to ceil(T / B), one pass each
+    # the search around the full recurrence over every candidate cap from t_S to ceil(T / B), most of them
+    # ruled out by bounds without a pass of their own (the oracle below tries every one)
     n_sweep = min(do.C, sweep_orders)
     if n_sweep:
         sub = orders.slice(0, n_sweep)
@@ -365,9 +366,9 @@ def mesh_search(ctx, binding, torch, workloads, name, n_orders, reps, cpu_orders
         got_s = out_s.to_host()
         oks = got_s.status == 0
         tried = nc.cpu().numpy()
-        res["sweep"] = {"kernel": "k2_mesh_h1f1b_sweep (one harp_plan_mesh_h1f1b_sweep_batch call)",
-                        "orderings": int(ds.C), "ms_per_call": ms_s, "mean_caps_tried": float(tried.mean()),
-                        "max_caps_tried": int(tried.max()), "passes_per_s": float(tried.sum()) / (ms_s * 1e-3),
+        res["sweep"] = {"kernel": "k2_sweep_band (one harp_plan_mesh_h1f1b_sweep_batch call)",
+                        "orderings": int(ds.C), "ms_per_call": ms_s, "mean_caps_covered": float(tried.mean()),
+                        "max_caps_covered": int(tried.max()), "caps_covered_per_s": float(tried.sum()) / (ms_s * 1e-3),
                         "feasible_fraction": float(oks.mean())}
         if cpu_orders:
             import oracle

@@ -295,10 +295,13 @@ __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh_h1f1b(TablesDev tb, O
 
 // ------------------------------------------------------------------------------------ band form
 
-// Bound by vector issue and by the latency of its serial parts (chains, plan recovery: one wavefront of a
-// workgroup).  Measured against the whole-table form on 32-bit rows it replaces: 4,096 orderings of 82
-// operators and 64 devices 3.57 -> 0.95 ms; exact form, 256 orderings of 160 operators and 128 devices,
-// 15-19 -> 3.4 ms (of an ordering's time there: finding t_S 4%, ranges of the caps 14%, value passes 68%).
+// Bound by latency: of the stages one after the other (a barrier or two each, short rows) and of the serial parts
+// (chains, plan recovery: one wavefront of a workgroup).  Vector issue is 34% of the rate in the min-max form and 21%
+// in the exact one, 3.3 wavefronts in flight per SIMD (4,096 orderings of 82 operators and 64 devices).  Measured
+// against the whole-table form on 32-bit rows it replaces: those orderings 3.57 -> 0.87-0.97 ms (of an ordering's
+// time 16% the search for the cap, 18% the ranges, 48% the value pass, 11% plan and score); exact form, 256
+// orderings of 160 operators and 128 devices, 15-19 -> 3.1-3.4 ms (3% the search for the cap, 4% and 10% the ranges
+// of the min-max pass and of the caps, 15% and 56% their value passes, 11% plans and scores).
 // The exact form walks the caps as k2_mesh does: first at t_S, then down from ceil(T / B).  A plan that
 // is not kept costs nothing but its score: the outputs are written whenever a better one is found.
 template <bool kExact>

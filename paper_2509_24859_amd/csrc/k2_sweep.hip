@@ -1,6 +1,7 @@
 // The search over the cap around the full recurrence (paper section 5.2.4 (2), (3)): the kernels of
 // harp_plan_mesh_h1f1b_sweep_batch (orderings) and harp_plan_h1f1b_sweep_batch (candidates with a fixed
-// slicing).  The passes themselves are in mesh_passes.h.
+// slicing).  k2_mesh_h1f1b_sweep tries every value of the cap with the passes of mesh_passes.h: candidates, and the
+// orderings that k2_sweep_band, on the ranges of mesh_band.h, does not take or hands over.
 #include "mesh_band.h"
 #include "mesh_passes.h"
 
@@ -538,8 +539,9 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 //  * How many values the sweep passes from t_S to t_E, or to the first cap with a plan where that is higher
 //    (n_caps, max_caps), is counted without trying them.
 // Measured on 48 orderings of 82 operators and 64 devices (about 1,000 values each between t_S and t_E, all
-// of them tried before, by up to 32 workgroups per ordering): 125-150 -> 1.0 ms per call, some 10 passes
-// per ordering, bound by the latency of one workgroup's passes one after the other.
+// of them tried before, by up to 32 workgroups per ordering): 125-150 -> 0.8-1.0 ms per call, some 10 passes
+// per ordering, bound by the latency of one workgroup's passes one after the other (vector issue 6% of the rate of
+// the 48 CUs at work).
 //  * The bounds are weak where tight memory keeps the H-1F1B sums above the classic ones and there are few
 //    micro-batches.  An ordering that has tried kMaxTries values without an end leaves the rest, a range of caps, to
 //    the second launch (kWalk): W workgroups take a part of the range each, start from the best plan so far and

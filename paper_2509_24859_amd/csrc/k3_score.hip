@@ -71,12 +71,14 @@ constexpr int kScoreWaves = 4;        // independent wavefronts per workgroup of
 constexpr int kStagedWaves = 16;      // the same when the workgroup keeps the memory sums in LDS
 constexpr size_t kStagedBytes = 64 << 10;    // LDS of such a workgroup at most: two are resident per CU
 
-// What bounds it: the issue of vector instructions and the lines a gather touches (one per cycle and CU; a
-// gather of a candidate's cuts touches as many lines as it has stages).  Of the six gathered operands of
-// a stage kStaged keeps the memory sums and the groups' limits in LDS, read once per workgroup.  Measured, with
-// shuffles, runs compared one by one and all operands gathered before: 262,144 candidates of up to 64
-// stages (512 operators, 32 groups) 209 -> 146 us, 1.4 TB/s of slots, cuts and results; 16,384 of them
-// 17.8 -> 11.4 us; 262,144 of up to 4 stages 99 -> 81 us.
+// What bounds it: nothing alone.  On 262,144 candidates of up to 64 stages vector issue takes 54% of the cycles, the
+// vector cache serves 0.54 lines per cycle and CU (a gather of a candidate's cuts touches as many lines as it has
+// stages) with requests waiting on it 56% of the time, at 5.2 wavefronts in flight per SIMD.  Of the six gathered
+// operands of a stage kStaged keeps the memory sums and the groups' limits in LDS, read once per workgroup.
+// Measured, with shuffles, runs compared one by one and all operands gathered before: 262,144 candidates of up to
+// 64 stages (512 operators, 32 groups) with the cuts of their plans, 29% without a plan, 209 -> 146 us; with cuts in
+// proportion to the stages' devices 266 -> 197 us; 16,384 of the former 17.8 -> 11.4 us; 262,144 of up to 4 stages
+// 99 -> 81 us.
 template <int kWaves, bool kStaged>
 __global__ __launch_bounds__(kWaves * 64) void k3_score_fast(TablesDev tb, CandDev cd, const int32_t *splits,
                                                              int64_t *bottleneck, int64_t *iter_time,
