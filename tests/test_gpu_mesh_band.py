@@ -195,15 +195,17 @@ def _repeated(orders, extra, C):
     return at, W.orderings_from_lists(lists, S_max=orders.S_max, G_max=orders.G_max), many
 
 
-@pytest.mark.parametrize("L,scale,slow,stages", [(75, 1, False, (8, 7, 9, 6)), (75, 1 << 13, False, (8, 7, 9, 6)),
-                                                 (140, 1 << 13, True, (64, 60, 63, 26))], ids=["in_range", "no_keys", "handed_over"])
+@pytest.mark.parametrize("L,ndev,scale,slow,stages", [
+    (75, (40, 34, 2), 1, False, (8, 7, 9, 6)), (75, (40, 34, 2), 1 << 13, False, (8, 7, 9, 6)),
+    (140, (40, 34, 2), 1 << 13, True, (64, 60, 63, 26)), (42, (160, 130, 2), 1, False, (22, 21, 19, 12))],
+    ids=["in_range", "no_keys", "handed_over", "wide"])
 @pytest.mark.parametrize("C", [300, 700, 2500])
-def test_band_kernels_on_large_batches(harp, ctx, C, L, scale, slow, stages):
+def test_band_kernels_on_large_batches(harp, ctx, C, L, ndev, scale, slow, stages):
     """More orderings than compute units (512-thread workgroups), than twice as many (256 threads in the
     min-max form), and than there are workgroups; in range, with sums that leave 32 bits times a degree, and
     with sums that leave 32 bits themselves (the band kernels hand those over).  The batch repeats a few
     orderings, malformed and infeasible ones among them, so the oracle works each once."""
-    ndev, tp = (40, 34, 2), (1, 2, 4, 8, 16)            # 77 columns
+    tp = (1, 2, 4, 8, 16)                               # 77 columns, or 293: more than a workgroup has threads
     p = _problem(7, L, ndev, tp, slow, scale)
     assert harp.Tables(ctx, p).fast32
     orders = W.orderings_from_lists(list(zip(stages, ([0, 1, 2], [2, 1, 0], [1, 0], [0]))), S_max=max(stages) + 3,
