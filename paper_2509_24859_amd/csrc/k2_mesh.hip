@@ -336,10 +336,11 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
         if (opening < 0) { fail(HARP_CAND_INFEASIBLE); continue; }
         int form = Band::kMinMax, tries = 0, passes = 0;
         uint32_t cap = uint32_t(opening);
-        int64_t t_S = 0, best_T = kInf, best_b = kInf, key_cap = 0;
+        int64_t t_S = 0, best_T = kInf, best_b = kInf;
+        bool keys_fit = true;
         bool over = false;
         for (;;) {
-            b.keys_fit = int64_t(cap) <= key_cap;
+            b.keys_fit = keys_fit;
             const int64_t v = b.template run<kExact ? Band::kMinMax | Band::kSum : Band::kMinMax>(form, cap);
             if (v == kInf) {
                 if (form == Band::kSum || cap >= meshband::kTopCap) break;     // (a sum cannot fail at or above t_S)
@@ -361,10 +362,9 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
             if (form == Band::kMinMax) {
                 // every cap of the walk is at most T / B rounded up; up to the first bound it needs no look at the operators
                 const int64_t t_E = (best_T + m_cap - 1) / m_cap;
-                key_cap = b.largest_cap(meshband::kInfSum, true);
-                if (t_E > key_cap) {
+                if (t_E > b.largest_cap(meshband::kInfSum, true)) {
                     const uint64_t most = b.most_sum();
-                    key_cap = b.largest_cap(most, true);
+                    keys_fit = t_E <= b.largest_cap(most, true);
                     over = t_E > b.largest_cap(most, false);
                     if (over) break;
                 }

@@ -226,7 +226,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
     const MeshSlice m = mesh_slice(ws, per_group, L, n_dev);
     const int64_t m_cap = tb.M;
     const int n_items = n_orderings(items, od.C) * W;
-    if (items.list && int(blockIdx.x) >= n_items) return;           // mostly none is handed over
+    if (!kForced && items.list && int(blockIdx.x) >= n_items) return;           // mostly none is handed over
     const uint8_t *fq = kForced ? forced_q : nullptr;
     const int32_t *fo = kForced ? forced_off : nullptr;
 
@@ -240,7 +240,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
         const SweepSlot opening = sweep_slot(slots, S_max, Ws, c, Ws);
         const SweepSlot mine = kPhase == kSweepLower ? opening : sweep_slot(slots, S_max, Ws, c, j);
         // t_S and the caps up to where the climb goes on are done (head and lower are written)
-        if (kPhase == kSweepLower && items.list && (items.list[n] & kClimbOn)) continue;
+        if (!kForced && kPhase == kSweepLower && items.list && (items.list[n] & kClimbOn)) continue;
         auto leave = [&](int state, int tried) {
             if (tid == 0) { mine.head->T = kInf; mine.head->cap = kInf; mine.head->tried = tried; mine.head->state = state; }
         };
@@ -366,7 +366,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
             // atomic minimum) tells the others where to stop.  Every index below the final minimum
             // has been tried by its walker and has no plan.
             cap = lower[c];
-            const int passed = opening.head->tried;
+            const int passed = kForced ? 1 : opening.head->tried;
             tried = passed;
             int state = kSweepFailed + HARP_CAND_INFEASIBLE;
             for (int idx = 1;; ++idx) {
