@@ -333,9 +333,9 @@ int harp_plan_mesh_h1f1b_sweep_batch(harp_ctx *ctx, harp_tables *tables, const h
  * transfer time of a cut 1 <= i <= L - 1 on the link between two consecutive slots.  Order of the
  * sweep, t_E, the answer, max_caps, t_max_out and n_caps as for harp_plan_mesh_h1f1b_sweep_batch;
  * out and warmup as for harp_plan_h1f1b_batch at the cap of the answer; statuses as for
- * harp_plan_batch, and HARP_CAND_INFEASIBLE when no tried cap has a plan.  It runs on the submesh
- * kernels with every stage's group and degree given (one device offset per stage), not on the hot
- * path's: meant for batches of moderate size.  Workspace: harp_plan_h1f1b_sweep_workspace_bytes,
+ * harp_plan_batch, and HARP_CAND_INFEASIBLE when no tried cap has a plan.  A workgroup searches for
+ * one candidate at a time: meant for batches of moderate size.  With 32-bit rows most values are ruled
+ * out by bounds; without them every one is tried.  Workspace: harp_plan_h1f1b_sweep_workspace_bytes,
  * 256-byte aligned, contents irrelevant. */
 size_t harp_plan_h1f1b_sweep_workspace_bytes(harp_ctx *ctx, harp_tables *tables, const harp_candidates *cands);
 int harp_plan_h1f1b_sweep_batch(harp_ctx *ctx, harp_tables *tables, const harp_candidates *cands,

@@ -1,9 +1,11 @@
 // The search over the cap around the full recurrence (paper section 5.2.4 (2), (3)): the kernels of
 // harp_plan_mesh_h1f1b_sweep_batch (orderings) and harp_plan_h1f1b_sweep_batch (candidates with a fixed
-// slicing).  k2_mesh_h1f1b_sweep tries every value of the cap with the passes of mesh_passes.h: candidates, and the
-// orderings that k2_sweep_band, on the ranges of mesh_band.h, does not take or hands over.
+// slicing).  On the 32-bit rows k2_sweep_band (orderings, ranges of mesh_band.h) and k2_sweep_slots (candidates,
+// passes of slot_passes.h) try few values of the cap; k2_mesh_h1f1b_sweep tries every one with the passes of
+// mesh_passes.h, for what those two do not take or hand over.
 #include "mesh_band.h"
 #include "mesh_passes.h"
+#include "slot_passes.h"
 
 namespace harp {
 
@@ -226,7 +228,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
     const MeshSlice m = mesh_slice(ws, per_group, L, n_dev);
     const int64_t m_cap = tb.M;
     const int n_items = n_orderings(items, od.C) * W;
-    if (!kForced && items.list && int(blockIdx.x) >= n_items) return;           // mostly none is handed over
+    if (items.list && int(blockIdx.x) >= n_items) return;           // mostly none is handed over
     const uint8_t *fq = kForced ? forced_q : nullptr;
     const int32_t *fo = kForced ? forced_off : nullptr;
 
@@ -240,7 +242,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
         const SweepSlot opening = sweep_slot(slots, S_max, Ws, c, Ws);
         const SweepSlot mine = kPhase == kSweepLower ? opening : sweep_slot(slots, S_max, Ws, c, j);
         // t_S and the caps up to where the climb goes on are done (head and lower are written)
-        if (!kForced && kPhase == kSweepLower && items.list && (items.list[n] & kClimbOn)) continue;
+        if (kPhase == kSweepLower && items.list && (items.list[n] & kClimbOn)) continue;
         auto leave = [&](int state, int tried) {
             if (tid == 0) { mine.head->T = kInf; mine.head->cap = kInf; mine.head->tried = tried; mine.head->state = state; }
         };
@@ -366,7 +368,7 @@ __device__ __forceinline__ void mesh_sweep_body(const TablesDev &tb, const OrdDe
             // atomic minimum) tells the others where to stop.  Every index below the final minimum
             // has been tried by its walker and has no plan.
             cap = lower[c];
-            const int passed = kForced ? 1 : opening.head->tried;
+            const int passed = opening.head->tried;
             tried = passed;
             int state = kSweepFailed + HARP_CAND_INFEASIBLE;
             for (int idx = 1;; ++idx) {
@@ -551,8 +553,11 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 // ordering that does not fit LDS or whose sums could pass 2^31 is handed over to the kernels that try every
 // value; so is one whose climb fails at kMaxClimb values in a row (the recurrence keeps one continuation per
 // state and can miss plans that exist), from where it stands.
-constexpr int kMaxClimb = 8;
-constexpr int kMaxTries = 24;
+// Candidates (k2_sweep_slots) are searched in the same way, on the passes of slot_passes.h.  Those also say up to
+// which cap they come out the same, so that the climb and the tries pass over the values below it: climbs
+// that took up to 20,000 passes take 1 to 3.  64 candidates of 82 operators, 8 to 16 stages on 8 groups of 8
+// devices (about 2,000 values each from t_S on, 29,000 at most): 146 ms, every value tried, -> 0.8-1.5 ms, some 30
+// passes for the longest searches, the least-count bisection two thirds of them.
 
 // The rest of an ordering's search: its slots as for the kernels above (the opening's head holds the best plan so
 // far and, in rest, the range of caps left: above the first, up to the second), the least total found per ordering
@@ -565,22 +570,18 @@ struct SweepShare {
 // counters of the band launch: orderings left to the walkers, and their ticket; their list grows from the end of redo
 constexpr int kShared = 5, kShareTicket = 6;
 
-template <bool kWalk>
-__global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, int max_caps, PlansDev out,
-                                                      int32_t *stage_group, int32_t *stage_tp, int32_t *warmup,
-                                                      int64_t *t_max_out, int32_t *n_caps, BandArgs ba, SweepShare sw) {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
+// E: the passes, Band (orderings) or Slots (candidates with a fixed slicing); all threads of a workgroup.
+template <bool kWalk, class E>
+__device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const OrdDev &od, int max_caps,
+                                             const PlansDev &out, int32_t *stage_group, int32_t *stage_tp,
+                                             int32_t *warmup, int64_t *t_max_out, int32_t *n_caps,
+                                             const BandArgs &ba, const SweepShare &sw, int n_items) {
     __shared__ int64_t scored[2];
     __shared__ long long least_found;
     __shared__ int item;
-    const int n_items = kWalk ? ba.counters[kShared] * sw.W : od.C;
-    if (kWalk && int(blockIdx.x) >= n_items) return;
-    Band b(tb, ba.sh, lds_raw, ba.lo_tab, ba.hi_tab,
-           meshband::band_slice(ba.slices + size_t(blockIdx.x) * ba.per_group, ba.sh));
     const int S_max = od.S_max, tid = threadIdx.x;
     const int64_t m_less = int64_t(tb.M) - 1;
-    b.load_memory_sums();
-    if (!kWalk) b.find_least_cut();
+    b.start(kWalk);
     for (;;) {
         __syncthreads();
         if (tid == 0) item = atomicAdd(&ba.counters[kWalk ? kShareTicket : 0], 1);
@@ -589,18 +590,21 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
         if (drawn >= n_items) break;
         const int c = kWalk ? ba.redo[od.C - 1 - drawn / sw.W] : drawn, walker = kWalk ? drawn % sw.W : sw.Ws;
         const SweepSlot opening = sweep_slot(sw.slots, S_max, sw.Ws, c, sw.Ws), mine = sweep_slot(sw.slots, S_max, sw.Ws, c, walker);
-        int32_t *sg = stage_group + int64_t(c) * S_max, *stp = stage_tp + int64_t(c) * S_max;
+        int32_t *sg = stage_group + int64_t(c) * S_max, *stp = stage_tp + int64_t(c) * S_max;     // null: no slicing to report
         int32_t *wu = warmup + int64_t(c) * S_max;
         auto fail = [&](int status, uint32_t tried) {
             write_failed(out, c, S_max, status);
-            for (int s = tid; s < S_max; s += b.nthreads) { sg[s] = -1; stp[s] = -1; wu[s] = -1; }
+            for (int s = tid; s < S_max; s += b.nthreads) {
+                wu[s] = -1;
+                if (E::kChoosesSlicing) { sg[s] = -1; stp[s] = -1; }
+            }
             if (tid == 0) {
                 t_max_out[c] = kInf;
                 if (n_caps) n_caps[c] = int32_t(tried);
             }
         };
         auto hand_over = [&](int flag) { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c | flag; };
-        const int verdict = b.load(od.ord_S[c], od.ord_G[c], od.ord_group + int64_t(c) * od.G_max, S_max, od.G_max);
+        const int verdict = b.load_item(od, c);
         if (verdict == 1) { fail(HARP_CAND_INVALID, 0); continue; }
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
         if (verdict == 3) { hand_over(0); continue; }
@@ -619,7 +623,7 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
         bool kept = false, left = false;
         auto keep = [&]() {
             b.find_h1_plan();
-            const int t = Band::thread_id();
+            const int t = E::thread_id();
             kept = true;
             if (kWalk) {
                 for (int s = t; s <= b.S; s += b.nthreads) mine.cuts[s] = b.cuts[s];
@@ -652,9 +656,9 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                 __syncthreads();
                 least_T = least_found;
             }
-            const int form = state == kBottleneck ? Band::kMinMax : state == kUpper ? Band::kSum
-                             : state == kAtTop || state == kGallop || state == kBisect ? Band::kAny : Band::kH1;
-            if (form == Band::kSum || form == Band::kH1) {
+            const int form = state == kBottleneck ? E::kMinMax : state == kUpper ? E::kSum
+                             : state == kAtTop || state == kGallop || state == kBisect ? E::kAny : E::kH1;
+            if (form == E::kSum || form == E::kH1) {
                 if (cap > key_cap && !looked) {
                     const uint64_t most = b.most_sum();
                     sum_cap = b.largest_cap(most, false);
@@ -665,13 +669,13 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
             }
             b.count_cap = cap;
             b.keys_fit = cap <= key_cap;
-            const int64_t v = b.template run<kWalk ? Band::kSum | Band::kH1 : Band::kMinMax | Band::kSum | Band::kH1 | Band::kAny>(form, cap);
+            const int64_t v = b.template run<kWalk ? E::kSum | E::kH1 : E::kMinMax | E::kSum | E::kH1 | E::kAny>(form, cap);
             const bool found = v != kInf;
             bool opened = false, climb_on = false, try_on = false, upper_on = false;
             if (!kWalk && state == kBottleneck) {
                 if (found) { t_S = uint32_t(v); cap = t_S; state = kAtBottleneck; }
                 else if (cap >= meshband::kTopCap) state = kNoPlan;
-                else cap = Band::raised(cap, tries++);
+                else cap = E::raised(cap, tries++);
             } else if (!kWalk && state == kAtBottleneck) {
                 if (found) {
                     opened = true;
@@ -679,11 +683,11 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                     top = b.largest_value();
                     tried = 1;
                     run_out = top > t_S && more > 0;
+                    lo = b.same_up_to(t_S);
                     if (!run_out) state = kNoPlan;
                     else { cap = top; state = kAtTop; }
                 }
             } else if (!kWalk && state == kAtTop) {
-                lo = t_S;
                 hi = top;
                 step = (t_S >> 4) + 1u;
                 if (!found) state = kNoPlan;
@@ -691,14 +695,14 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                 else if (hi - lo > 1u + (hi >> 12)) { cap = lo + (hi - lo) / 2u; state = kBisect; }
                 else climb_on = true;
             } else if (!kWalk && (state == kGallop || state == kBisect)) {
-                if (found) hi = cap; else lo = cap;
+                if (found) hi = cap; else lo = b.same_up_to(cap);
                 step *= 4;
                 if (state == kGallop && !found && lo + step < hi) cap = lo + uint32_t(step);
                 else if (hi - lo > 1u + (hi >> 12)) { cap = lo + (hi - lo) / 2u; state = kBisect; }
                 else climb_on = true;
             } else if (!kWalk && state == kClimb) {
                 if (found) opened = true;
-                else { lo = cap; climb_on = true; }
+                else { lo = b.same_up_to(cap); climb_on = true; }
             } else if (state == kUpper) {
                 // no cap up to hi beats the best total unless the classic sum at hi leaves room for it
                 const int64_t room = (least_T < best_T ? least_T : best_T) - v;
@@ -728,11 +732,11 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                 }
                 ++tested;
                 if (found && v == classic) { hi = bn > 0 ? uint32_t(bn) - 1u : 0u; upper_on = true; }
-                else try_on = true;
+                else { cap = b.same_up_to(cap); try_on = true; }
             }
             if (climb_on) {
                 cap = b.next_value(lo);
-                state = cap > top ? kNoPlan : climbed++ < kMaxClimb ? kClimb : kClimbLeft;
+                state = cap > top ? kNoPlan : climbed++ < E::kMaxClimb ? kClimb : kClimbLeft;
             }
             if (!kWalk && opened) {
                 first = best_cap = cap;
@@ -764,7 +768,7 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
                 cap = hi;
                 state = hi > first ? kUpper : kDone;
             }
-            if (!kWalk && sw.W > 1 && tested >= kMaxTries && (state == kTry || state == kUpper)) { left = true; state = kDone; }
+            if (!kWalk && sw.W > 1 && tested >= E::kMaxTries && (state == kTry || state == kUpper)) { left = true; state = kDone; }
         }
         if (kWalk) {
             if (tid == 0) {
@@ -819,6 +823,32 @@ __global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, i
     }
 }
 
+template <bool kWalk>
+__global__ __launch_bounds__(1024) void k2_sweep_band(TablesDev tb, OrdDev od, int max_caps, PlansDev out,
+                                                      int32_t *stage_group, int32_t *stage_tp, int32_t *warmup,
+                                                      int64_t *t_max_out, int32_t *n_caps, BandArgs ba, SweepShare sw) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const int n_items = kWalk ? ba.counters[kShared] * sw.W : od.C;
+    if (kWalk && int(blockIdx.x) >= n_items) return;
+    Band b(tb, ba.sh, lds_raw, ba.lo_tab, ba.hi_tab,
+           meshband::band_slice(ba.slices + size_t(blockIdx.x) * ba.per_group, ba.sh));
+    sweep_search<kWalk>(b, tb, od, max_caps, out, stage_group, stage_tp, warmup, t_max_out, n_caps, ba, sw, n_items);
+}
+
+template <bool kWalk, bool kResident>
+__global__ __launch_bounds__(slotdp::kThreads) void k2_sweep_slots(TablesDev tb, OrdDev od, const int32_t *cand_group,
+                                                                   const int32_t *cand_tp, int max_caps, PlansDev out,
+                                                                   int32_t *warmup, int64_t *t_max_out,
+                                                                   int32_t *n_caps, slotdp::SlotShape sh, BandArgs ba,
+                                                                   SweepShare sw) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ SlotInfo info;
+    const int n_items = kWalk ? ba.counters[kShared] * sw.W : od.C;
+    if (kWalk && int(blockIdx.x) >= n_items) return;
+    slotdp::Slots<kResident> b(tb, sh, lds_raw, info, cand_group, cand_tp, ba.slices + size_t(blockIdx.x) * ba.per_group);
+    sweep_search<kWalk>(b, tb, od, max_caps, out, nullptr, nullptr, warmup, t_max_out, n_caps, ba, sw, n_items);
+}
+
 }  // namespace
 
 // cand_group / cand_tp not null: the batch holds candidates with a fixed slicing (od.ord_S = their
@@ -840,30 +870,46 @@ hipError_t launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, c
     const bool forced = cand_group != nullptr;
     hipLaunchKernelGGL(k2_mesh_sweep_clear, dim3((od.C + 255) / 256), dim3(256), 0, st, w.counters, first_idx, od.C);
     SweepItems items{nullptr, nullptr, nullptr};
-    BandArgs ba;
+    BandArgs ba{};
+    ba.slices = w.slices;
+    ba.per_group = per_group;
+    ba.counters = w.counters;
+    ba.redo = w.redo;
+    const SweepShare sw{slots, Ws, W, reinterpret_cast<long long *>(lower)};
+    const long long walkers = (long long)od.C * W;
+    const dim3 band_grid(unsigned(od.C < n_groups ? od.C : n_groups)), walk_grid(unsigned(walkers < n_groups ? walkers : n_groups));
     int band_threads = 0;
-    if (fast32 && !forced && w.index_bytes != 0 &&
+    bool searched = false;
+    if (fast32 && forced) {
+        const slotdp::SlotShape sh = slotdp::slot_shape(tb.L, od.S_max);
+#define HARP_SWEEP_SLOTS(WALK, RESIDENT, GRID)                                                                   \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_sweep_slots<WALK, RESIDENT>), GRID, dim3(slotdp::kThreads),             \
+                       size_t(sh.total), st, tb, od, cand_group, cand_tp, max_caps, out, warmup, t_max_out, n_caps, sh, ba, sw)
+        if (sh.resident) HARP_SWEEP_SLOTS(false, true, band_grid);
+        else HARP_SWEEP_SLOTS(false, false, band_grid);
+        const hipError_t e = hipGetLastError();            // before the launches over what it hands over replace it
+        if (e != hipSuccess) return e;
+        if (W > 1 && sh.resident) HARP_SWEEP_SLOTS(true, true, walk_grid);
+        else if (W > 1) HARP_SWEEP_SLOTS(true, false, walk_grid);
+#undef HARP_SWEEP_SLOTS
+        searched = true;
+    } else if (fast32 && w.index_bytes != 0 &&
         meshband::band_launch(tb, od, total_devices, meshband::kFormSweep, n_cu, n_groups, band_threads, ba.sh)) {
         launch_plan_index(tb, od.S_max, w.index, st);
         ba.lo_tab = w.index;
         ba.hi_tab = w.index + w.index_bytes / 4;
-        ba.slices = w.slices;
-        ba.per_group = per_group;
-        ba.counters = w.counters;
-        ba.redo = w.redo;
-        const SweepShare sw{slots, Ws, W, reinterpret_cast<long long *>(lower)};
-        const long long walkers = (long long)od.C * W;
-        hipLaunchKernelGGL(k2_sweep_band<false>, dim3(unsigned(od.C < n_groups ? od.C : n_groups)), dim3(band_threads),
+        hipLaunchKernelGGL(k2_sweep_band<false>, band_grid, dim3(band_threads),
                            size_t(ba.sh.total), st, tb, od, max_caps, out, stage_group, stage_tp, warmup, t_max_out,
                            n_caps, ba, sw);
-        const hipError_t e = hipGetLastError();            // before the launches over what it hands over replace it
+        const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (W > 1)
-            hipLaunchKernelGGL(k2_sweep_band<true>, dim3(unsigned(walkers < n_groups ? walkers : n_groups)),
+            hipLaunchKernelGGL(k2_sweep_band<true>, walk_grid,
                                dim3(band_threads), size_t(ba.sh.total), st, tb, od, max_caps, out, stage_group, stage_tp,
                                warmup, t_max_out, n_caps, ba, sw);
-        items = SweepItems{w.redo, w.counters + 1, w.counters + kShared};
+        searched = true;
     }
+    if (searched) items = SweepItems{w.redo, w.counters + 1, w.counters + kShared};
     fast32 = fast32 && tb.L <= kMeshFastMaxL;
     // cap positions: one uint16 per (row, start cut), kept in LDS when the largest item's rows fit
     // beside the static arrays in a workgroup's 64 KiB

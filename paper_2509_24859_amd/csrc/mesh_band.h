@@ -121,6 +121,8 @@ inline size_t band_slice_bytes(int L, int S_max, int64_t total_devices) {
 }
 
 struct Band {
+    static constexpr bool kChoosesSlicing = true;
+    static constexpr int kMaxClimb = 8, kMaxTries = 24;      // see k2_sweep.hip
     const TablesDev &tb;
     const BandShape &sh;
     const uint16_t *lo_tab, *hi_tab;
@@ -1023,6 +1025,14 @@ struct Band {
         for (int j = tid; j <= L; j += nthreads) { mem[j] = PP[j]; mem[sh.W + j] = PS[j]; }
         __syncthreads();
     }
+    // All threads, once per kernel of the search over the cap (walk: no bracket in it), and its item c.
+    __device__ __forceinline__ void start(bool walk) {
+        load_memory_sums();
+        if (!walk) find_least_cut();
+    }
+    __device__ __forceinline__ int load_item(const OrdDev &od, int c) {
+        return load(od.ord_S[c], od.ord_G[c], od.ord_group + int64_t(c) * od.G_max, od.S_max, od.G_max);
+    }
     // All threads: the plan of the last H-1F1B pass, with its counts by eq. Ni.
     __device__ __forceinline__ void find_h1_plan() {
         const int lane = thread_id() & 63;
@@ -1119,6 +1129,8 @@ struct Band {
         __syncthreads();
         return scal[7];
     }
+    // The highest cap up to which the last pass, under the cap t, is known to come out the same.
+    __device__ __forceinline__ uint32_t same_up_to(uint32_t t) const { return t; }
     // All threads: the smallest candidate cap above a; 0xFFFFFFFF when there is none.
     __device__ __forceinline__ uint32_t next_value(uint32_t a) {
         uint32_t beyond = 0xFFFFFFFFu;

@@ -358,3 +358,54 @@ def test_h1f1b_sweep_of_candidates(harp, ctx):
         at, _ = harp.plan_h1f1b(ctx, w.problem, cands, np.where(ok, want.t_max, -1))
         for field in ("splits", "warmup", "iter_time"):
             assert (getattr(at, field)[ok] == getattr(got, field)[ok]).all(), (name, field)
+
+
+SWEEP_EDGES = [  # L, devices per group, stages per group, degrees, micro-batches, memory, scale of the times, of the outputs, max_caps
+    (2, (2, 1), (1, 1), (1, 2), 3, 1.2, 1, 1, 1 << 20),
+    (64, (8, 8), (3, 2), (1, 2, 4, 8), 7, 1.1, 1, 1, 1 << 20),
+    (65, (8, 8, 4), (4, 4, 2), (1, 2, 4), 2, 1.3, 1, 1, 1 << 20),
+    (130, (8, 6), (6, 4), (1, 2, 4), 1, 1.5, 1, 1, 60),
+    (83, (16, 16), (9, 7), (1, 2), 40, 1.2, 1, 30, 1 << 20),        # tight memory, slow links: climbs far above the bottleneck
+    (300, (24, 24), (24, 20), (1,), 9, 4.0, 1, 1, 12),                 # rows beyond LDS
+    (60, (8, 8), (5, 5), (1, 2), 5, 1.5, 1 << 13, 80, 40),             # sums that leave 32 bits: handed over
+]
+
+
+@pytest.mark.parametrize("case", SWEEP_EDGES, ids=lambda c: "L%d_S%d_M%d" % (c[0], sum(c[2]), c[4]))
+def test_sweep_of_candidates_at_its_edges(harp, ctx, case):
+    """The kernel that tries few values against the one that tries every value: 64 cuts a chain step, 64 cells a
+    round, rows in LDS and beyond, one micro-batch, deep climbs, sums beyond 2^31, the cut by max_caps."""
+    L, ndev, stages, degrees, M, memory, scale, outputs, max_caps = case
+    rng = np.random.default_rng(L)
+    G = len(ndev)
+    bw = rng.integers(20, 60, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 500
+    fwd = rng.integers(1, 900, size=(2, L)) * scale
+    p = simple_problem(np.zeros(L), M=M, T=2, G=G, ndev=ndev, tp=degrees, gtype=[g % 2 for g in range(G)], fwd=fwd,
+                       bwd=2 * fwd, act=rng.integers(100, 3000, size=L) * scale * outputs,
+                       params=rng.integers(1, 40, size=L), stash=rng.integers(1, 10, size=L), bw=bw)
+    in_flight = min(M, sum(stages)) / 2
+    p.type_mem_bytes[:] = int(memory * (p.param_bytes.sum() + in_flight * p.stash_bytes.sum()) / sum(ndev)) + 10
+    lists = []
+    for _ in range(6):
+        slots = []
+        for g in rng.permutation(G):
+            left = ndev[g]
+            for k in range(stages[g]):
+                room = left - (stages[g] - k - 1)
+                d = int(rng.choice([q for q in degrees if q <= room]))
+                slots.append((int(g), d))
+                left -= d
+        lists.append(slots)
+    lists.append(lists[0] + [lists[0][0]])                            # malformed where there are several groups
+    cands = cands_from_lists(lists)
+    assert harp.Tables(ctx, p).fast32
+    planned = 0
+    for limit in (max_caps, 3, 1):
+        got, want = (harp.plan_h1f1b_sweep(ctx, p, cands, limit, path)[0] for path in (harp.PATH_FAST32, harp.PATH_GENERIC))
+        assert_plans_equal(got, want, "max_caps %d" % limit)
+        for name in ("warmup", "t_max", "n_caps"):
+            assert (getattr(got, name) == getattr(want, name)).all(), (name, limit)
+        planned += int((want.status == 0).sum())
+    assert planned > 0
