@@ -67,6 +67,23 @@ static_assert(kFastCutTableLimit / 4 <= (size_t(1) << 27), "cut-table offsets mu
 __device__ __forceinline__ int band_lo(uint32_t w) { return int(w & 0xFFFFu); }
 __device__ __forceinline__ int band_hi(uint32_t w) { return int(w >> 16); }
 
+// How a stage time follows from a difference of its fused row.  `code`: log2 of the degree, or (kOdd: some
+// degree is no power of two) the degree's index.  The multiply takes four issue slots where the shift takes
+// one, so tables of powers of two keep the shift.
+template <bool kOdd>
+__device__ __forceinline__ TpDiv tp_div(const TablesDev &tb, uint32_t code) {
+    if (kOdd) return tb.tp_div[code];
+    return TpDiv{(1u << code) - 1u, 0u, int32_t(code)};
+}
+template <bool kOdd>
+__device__ __forceinline__ uint32_t tp_quot(uint32_t x, const TpDiv &d) {       // x: difference + d.add
+    return kOdd ? __umulhi(x, d.mul) >> d.shift : x >> d.shift;
+}
+template <bool kOdd>
+__device__ __forceinline__ uint32_t tp_code(const TablesDev &tb, int k) {
+    return uint32_t(kOdd ? k : tb.tp_shift[k]);
+}
+
 __device__ __forceinline__ int tp_index(const TablesDev &tb, int tp) {
     int k = -1;
     for (int q = 0; q < tb.n_tp; ++q)

@@ -32,7 +32,8 @@ struct harp_tables {
     int device;
     bool finalized;
     int verdict;
-    bool fast32;
+    bool fast32;          // 32-bit rows, degrees powers of two
+    bool odd32;           // 32-bit rows, other degrees among them
     long long total_devices;
     size_t bytes;
 };
@@ -54,6 +55,15 @@ int hip_fail(harp_ctx *ctx, hipError_t e, const char *what) {
 }
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+TpDiv tp_division(int degree) {
+    const uint64_t d = uint64_t(degree);
+    if (d == 1) return TpDiv{1u, 0xFFFFFFFFu, 0};
+    int l = 0;
+    while ((uint64_t(2) << l) <= d) ++l;
+    if ((d & (d - 1)) == 0) return TpDiv{uint32_t(d - 1), 0x80000000u, l - 1};
+    return TpDiv{uint32_t(d - 1), uint32_t(((uint64_t(1) << (32 + l)) + d - 1) / d), l};
+}
 
 struct Layout {
     size_t header, group_base, rows, chunk_sums, p32, cm, total;
@@ -86,10 +96,8 @@ Layout make_layout(const harp_problem *p) {
     y.group_base = off; off += align_up(size_t(p->G) * 4, 256);
     y.rows = off; off += align_up(n_rows * y.pitch * 8, 256);
     y.chunk_sums = off; off += align_up(n_rows * size_t(y.n_chunks) * 8, 256);
-    bool pow2 = true;
-    for (int k = 0; k < p->n_tp; ++k) pow2 = pow2 && (p->tp_degrees[k] & (p->tp_degrees[k] - 1)) == 0;
     const size_t cm_bytes = size_t(p->G) * p->G * y.pitch32 * 4;
-    y.fast = pow2 && p->L <= kFastMaxL && cm_bytes <= kFastCutTableLimit &&
+    y.fast = p->L <= kFastMaxL && cm_bytes <= kFastCutTableLimit &&
              size_t(p->G) * p->n_tp + size_t(p->G) * p->G <= 65535;
     y.p32 = off;
     if (y.fast) off += align_up(size_t(p->G) * p->n_tp * y.pitch32 * 4, 256);
@@ -107,7 +115,8 @@ int finalize_tables(harp_ctx *ctx, harp_tables *t) {
     e = hipStreamSynchronize(t->build_stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "waiting for the table build");
     t->finalized = true;
-    t->fast32 = ctx->pinned->fast32 != 0;
+    t->fast32 = ctx->pinned->fast32 == 1;
+    t->odd32 = ctx->pinned->fast32 == 2;
     t->total_devices = ctx->pinned->total_devices;
     if (ctx->pinned->bad_arg)
         t->verdict = fail(ctx, HARP_ERR_INVALID_ARG,
@@ -232,14 +241,16 @@ bool mesh_index_fits(const harp_tables *t) {
 
 // The 32-bit tables serve the min-max planner up to kFastMaxL operators; the kernels that keep
 // whole rows of several arrays in LDS (H-1F1B, the submesh planners) stop at kFastRowsMaxL.
-bool fast_allowed(const harp_tables *t, bool whole_rows) {
-    return t->fast32 && (!whole_rows || t->dev.L <= kFastRowsMaxL);
+// Asked for by name (HARP_PATH_FAST32) the 32-bit path is what it is for degrees that are powers of two; the
+// candidate planners take it for other degrees by themselves.
+bool fast_allowed(const harp_tables *t, bool whole_rows, bool odd = false) {
+    return (t->fast32 || (odd && t->odd32)) && (!whole_rows || t->dev.L <= kFastRowsMaxL);
 }
 bool use_fast_rows(const harp_ctx *ctx, const harp_tables *t) {
     return fast_allowed(t, true) && ctx->plan_path != HARP_PATH_GENERIC;
 }
 bool use_fast(const harp_ctx *ctx, const harp_tables *t, const harp_candidates *cd, bool whole_rows) {
-    return fast_allowed(t, whole_rows) && ctx->plan_path != HARP_PATH_GENERIC && fast_batch_ok(t, cd);
+    return fast_allowed(t, whole_rows, true) && ctx->plan_path != HARP_PATH_GENERIC && fast_batch_ok(t, cd);
 }
 
 }  // namespace
@@ -315,11 +326,12 @@ int harp_build_segment_costs(harp_ctx *ctx, const harp_problem *p, void *table_b
     unsigned char *base = static_cast<unsigned char *>(table_buf);
     TablesDev &d = t->dev;
     d.L = p->L; d.T = p->T; d.G = p->G; d.M = p->M; d.n_tp = p->n_tp; d.ar_count = p->ar_count;
-    for (int k = 0; k < kMaxTp; ++k) { d.tp[k] = 0; d.tp_shift[k] = -1; }
+    for (int k = 0; k < kMaxTp; ++k) { d.tp[k] = 0; d.tp_shift[k] = -1; d.tp_div[k] = TpDiv{0, 0, 0}; }
     for (int k = 0; k < p->n_tp; ++k) {
         const int v = p->tp_degrees[k];
         d.tp[k] = v;
         if ((v & (v - 1)) == 0) { int s = 0; while ((1 << s) < v) ++s; d.tp_shift[k] = s; }
+        d.tp_div[k] = tp_division(v);
     }
     d.pitch = y.pitch; d.pitch32 = y.pitch32;
     d.header = reinterpret_cast<BuildHeader *>(base + y.header);
@@ -342,7 +354,7 @@ int harp_build_segment_costs(harp_ctx *ctx, const harp_problem *p, void *table_b
     t->device = ctx->device;
     t->finalized = false;
     t->verdict = HARP_OK;
-    t->fast32 = false;
+    t->fast32 = t->odd32 = false;
     t->total_devices = 0;
     t->bytes = y.total;
 
@@ -433,6 +445,8 @@ int plan_prepare(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const
     pc.c = CandDev{ cd->C, cd->S_max, cd->cand_S, cd->cand_group, cd->cand_tp };
     pc.o = PlansDev{ out->splits, out->dev_first, out->bottleneck, out->iter_time, out->status };
     pc.fast = use_fast(ctx, t, cd, whole_rows);
+    // a batch of odd degrees that only the int64 path's smaller slices leave room for runs there
+    if (shrink && pc.fast && t->odd32 && plan_bytes_on_path(t, cd, true, kFastWaves) > limit_bytes) pc.fast = false;
     pc.banded = !pc.fast && fast_batch_ok(t, cd);
     pc.groups = n_plan_groups(ctx, cd->C, pc.fast, t->dev.L, cd->S_max);
     pc.slices = pc.fast ? n_fast_slices(ctx, cd->C, t->dev.L, cd->S_max) : pc.groups;
@@ -496,7 +510,7 @@ int harp_plan_batch_count_work(harp_ctx *ctx, harp_tables *t, const harp_candida
     const int rc = plan_prepare(ctx, t, cd, out, work == nullptr, false, workspace, workspace_bytes, false, hip_stream,
                                 pc);
     if (rc != HARP_OK) return rc;
-    if (!pc.fast)
+    if (!pc.fast || !t->fast32)
         return fail(ctx, HARP_ERR_UNIMPLEMENTED, "work is counted on the 32-bit path only");
     launch_clear_work(reinterpret_cast<unsigned long long *>(work), pc.st);
     if (cd->C == 0) return HARP_OK;

@@ -20,7 +20,7 @@ constexpr int64_t kTimeLimit = int64_t(1) << 47;
 struct BuildHeader {
     unsigned int bad_arg;        // nonzero: malformed values
     unsigned int overflow;       // nonzero: magnitudes out of range
-    unsigned int fast32;         // 1: 32-bit rows and cut table are valid
+    unsigned int fast32;         // not 0: 32-bit rows and cut table are valid; 1: and every degree is a power of two
     unsigned int pad;
     unsigned long long max_act;  // largest act_bytes entry
     long long worst_time;        // largest stage or transfer time any plan can see
@@ -28,11 +28,24 @@ struct BuildHeader {
     long long reserved[3];
 };
 
+// Division of a difference of a degree's fused 32-bit row, rounded up, for any degree d: the sum of the
+// difference and `add` is below 2^31, and
+//   d = 1:              add 1,     mul 2^32 - 1,            shift 0   (floor(x (1 - 2^-32)) = x - 1 for x >= 1)
+//   d = 2^l, l >= 1:    add d - 1, mul 2^31,                shift l - 1
+//   else, 2^l < d:      add d - 1, mul ceil(2^(32 + l) / d), shift l
+// give ceil = umulhi(x + add, mul) >> shift: mul d exceeds 2^(32 + l) by less than d < 2^(l + 1), which
+// times x < 2^31 stays below 2^(32 + l), one unit of the quotient's last place.
+struct TpDiv {
+    uint32_t add, mul;
+    int32_t shift;
+};
+
 // Everything a kernel needs to read the tables; passed by value.
 struct TablesDev {
     int32_t L, T, G, M, n_tp, ar_count;
     int32_t tp[kMaxTp];
     int32_t tp_shift[kMaxTp];    // log2(tp) when tp is a power of two, else -1
+    TpDiv tp_div[kMaxTp];
     int64_t pitch;               // elements between int64 rows
     int64_t pitch32;             // elements between uint32 rows
     BuildHeader *header;
@@ -50,6 +63,11 @@ struct TablesDev {
     __host__ __device__ const int64_t *PS() const { return rows + int64_t(T + 1) * pitch; }
     __host__ __device__ const int64_t *PR(int g, int k) const {
         return rows + (int64_t(T + 2) + int64_t(g) * n_tp + k) * pitch;
+    }
+    bool odd_degrees() const {   // some degree is no power of two
+        bool odd = false;
+        for (int k = 0; k < n_tp; ++k) odd = odd || tp_shift[k] < 0;
+        return odd;
     }
     __host__ __device__ int n_rows() const { return T + 2 + G * n_tp; }
 };

@@ -747,12 +747,12 @@ __global__ __launch_bounds__(256) void k1_finalize(TablesDev tb, BuildLimits lim
         h->bad_arg = bad_all;
         h->overflow = ovf_all;
         h->worst_time = worst;
-        h->fast32 = (!bad_all && !ovf_all && lim.want_fast && pow2 && worst32_s < lim32 && cut_worst < lim32) ? 1u : 0u;
+        h->fast32 = (!bad_all && !ovf_all && lim.want_fast && worst32_s < lim32 && cut_worst < lim32) ? (pow2 ? 1u : 2u) : 0u;
     }
 }
 
 // Launch 5: 32-bit rows of the fast path.  Row q < G*n_tp: PF[type g][i] + tp * PR[g][k][i]
-// (so that time(j, i) = (row[i] + tp - 1 - row[j]) >> log2 tp); then G*G rows of per-link cut times.
+// (so that time(j, i) = ceil((row[i] - row[j]) / tp)); then G*G rows of per-link cut times.
 __global__ __launch_bounds__(256) void k1_fast_rows(TablesDev tb) {
     if (tb.header->fast32 == 0) return;
     const int q = blockIdx.y;

@@ -43,6 +43,8 @@
 // widest stage does not fit the share is queued for k2_exact_rows, the workgroup-per-candidate form
 // with rows over the whole sequence (launched only when L makes such a candidate possible), and the
 // candidates that need 64-bit sums for k2_exact_wide.
+#include <type_traits>
+
 #include "fast_common.h"
 #include "harp_internal.h"
 #include "plan_common.h"
@@ -91,7 +93,7 @@ __host__ __device__ inline size_t exact_small_bytes(int S_max) {
 // per candidate (the launch has 64-thread workgroups), LDS rows that hold the cuts of one stage
 // (row s starts at B[s]); a candidate whose widest stage does not fit them is queued.  kMode 2: as
 // 0, on the candidates queued by 1.
-template <typename SumT, int kMode>
+template <typename SumT, int kMode, bool kOdd>
 __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &cd, const PlansDev &out,
                                            int32_t *n_passes, int *counts, const int32_t *live_list,
                                            uint32_t *dead_list, const uint32_t *bands, const uint16_t *lo_tab,
@@ -163,7 +165,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 sc[s].cap = int64_t(tb.tp[k]) * tb.type_mem[tb.group_type[g]];
                 sc[s].p_row = uint32_t((int64_t(g) * tb.n_tp + k) * tb.pitch32);
                 sc[s].cm_row_shift = uint32_t((int64_t(g) * tb.G + g_next) * tb.pitch32) |
-                                     (uint32_t(tb.tp_shift[k]) << 27);
+                                     (tp_code<kOdd>(tb, k) << 27);
                 const int n_inflight = int((S - s) < m_cap ? (S - s) : m_cap);
                 lo_off[s] = uint32_t((int64_t(n_inflight - 1) * tb.T * tb.n_tp + int64_t(tb.group_type[g]) * tb.n_tp + k) *
                                      lo_pitch);
@@ -257,8 +259,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                     continue;
                 }
                 const uint32_t rs = (uint32_t)uniform((int)sc[s].cm_row_shift);
-                const int shift = int(rs >> 27);
-                const uint32_t tp = 1u << shift;
+                const TpDiv div = tp_div<kOdd>(tb, rs >> 27);
                 const uint32_t b0 = (uint32_t)uniform((int)band[s]);
                 const int jl = band_lo(b0), jh = band_hi(b0);     // predecessors: row s
                 const int jl_f = kBandRows && fin_lo > jl ? fin_lo : jl;
@@ -303,7 +304,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 // whether the lane goes on.  Equal sums keep the lowest j.
                 auto cell = [&](int i, uint32_t cut, int lo_idx) -> int {
                     const int lo = lo_idx > jl_f ? lo_idx : jl_f;
-                    const uint32_t xi = prev[i].p + tp - 1;
+                    const uint32_t xi = prev[i].p + div.add;
                     SumT best = kInfSum;
                     int best_j = 0;
                     int j = (i - 1) < jh_f ? (i - 1) : jh_f;
@@ -314,7 +315,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                         uint32_t tj;
 #define HARP_STEP(E, K)                                                        \
     {                                                                          \
-        tj = (xi - (E).p) >> shift;                                            \
+        tj = tp_quot<kOdd>(xi - (E).p, div);                                   \
         const SumT v = (E).d + tj;                                             \
         const bool upd = (j - (K) >= lo) & (tj <= tcap) & (v <= best);         \
         best = upd ? v : best;                                                 \
@@ -371,11 +372,10 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             // the last stage has the single cell i = L: lanes over j, lexicographic reduction
             if (wave == 0) {
                 const int s = S - 1;
-                const int shift = int((uint32_t)uniform((int)sc[s].cm_row_shift) >> 27);
-                const uint32_t tp = 1u << shift;
+                const TpDiv div = tp_div<kOdd>(tb, (uint32_t)uniform((int)sc[s].cm_row_shift) >> 27);
                 const uint32_t b0 = (uint32_t)uniform((int)band[s]);
                 const Pair *prev = (cur ? buf1 : buf0) - (kBandRows ? band_lo(b0) : 0);
-                const uint32_t xi = prev[L].p + tp - 1;
+                const uint32_t xi = prev[L].p + div.add;
                 int hi = (L - 1) < band_hi(b0) ? (L - 1) : band_hi(b0);
                 const int lo_L = uniform((int)lo_tab[size_t((uint32_t)uniform((int)lo_off[s])) + L]);
                 int lo = lo_L > band_lo(b0) ? lo_L : band_lo(b0);
@@ -386,7 +386,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 unsigned long long best = kInfSum;
                 int best_j = INT32_MAX;
                 for (int j = lo + lane; j <= hi; j += 64) {
-                    const uint32_t tj = (xi - prev[j].p) >> shift;
+                    const uint32_t tj = tp_quot<kOdd>(xi - prev[j].p, div);
                     const unsigned long long v = (unsigned long long)prev[j].d + tj;
                     if (tj <= tcap && v < best) { best = v; best_j = j; }   // j rises within a lane
                 }
@@ -436,9 +436,9 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 for (int s = lane; s < S; s += 64) {
                     const int j = trial[s], i = trial[s + 1];
                     const uint32_t rs = sc[s].cm_row_shift;
-                    const int shift = int(rs >> 27);
+                    const TpDiv div = tp_div<kOdd>(tb, rs >> 27);
                     const uint32_t *p = tb.P32 + sc[s].p_row;
-                    const uint32_t t = (p[i] + (1u << shift) - 1u - p[j]) >> shift;
+                    const uint32_t t = tp_quot<kOdd>(p[i] + div.add - p[j], div);
                     const uint32_t cu = s < S - 1 ? tb.CM[(rs & kRowMask) + uint32_t(i)] : 0u;
                     const uint32_t m = t > cu ? t : cu;
                     w = w > m ? w : m;
@@ -506,11 +506,12 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
 }
 
 #define HARP_EXACT_KERNEL(NAME, BOUNDS, SUM, MODE)                                                                  \
+    template <bool kOdd>                                                                                           \
     __global__ BOUNDS void NAME(TablesDev tb, CandDev cd, PlansDev out, int32_t *n_passes, int *counts,            \
                                 const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands,             \
                                 const uint16_t *lo_tab, int lo_pitch, unsigned char *arg_base,                    \
                                 size_t arg_per_group, size_t arg_u8_off, int row_len, int lds_row_entries) {      \
-        exact_body<SUM, MODE>(tb, cd, out, n_passes, counts, live_list, dead_list, bands, lo_tab, lo_pitch,       \
+        exact_body<SUM, MODE, kOdd>(tb, cd, out, n_passes, counts, live_list, dead_list, bands, lo_tab, lo_pitch, \
                               arg_base, arg_per_group, arg_u8_off, row_len, lds_row_entries);                     \
     }
 HARP_EXACT_KERNEL(k2_exact, __launch_bounds__(64), uint32_t, 1)
@@ -542,16 +543,21 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
     const int lo_p = int(lo_pitch(tb.L));
     const size_t per_group = fast_arg_per_group(tb.L, cd.S_max);
     const size_t u8_off = fast_arg_u16_bytes(tb.L, cd.S_max);
-    hipLaunchKernelGGL(k2_exact, dim3(n_waves), dim3(64), small + size_t(entries) * 16, st, tb, cd, out, n_passes,
-                       w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg, per_group, u8_off,
-                       full_row, entries);
-    if (entries < full_row)
-        hipLaunchKernelGGL(k2_exact_rows, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 16, st,
-                           tb, cd, out, n_passes, w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p,
-                           w.arg, per_group, u8_off, full_row, full_row);
-    hipLaunchKernelGGL(k2_exact_wide, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 32, st, tb,
-                       cd, out, n_passes, w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg,
-                       per_group, u8_off, full_row, full_row);
+    auto launch = [&](auto odd_t) {
+        constexpr bool odd = decltype(odd_t)::value;
+        hipLaunchKernelGGL(k2_exact<odd>, dim3(n_waves), dim3(64), small + size_t(entries) * 16, st, tb, cd, out, n_passes,
+                           w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg, per_group, u8_off,
+                           full_row, entries);
+        if (entries < full_row)
+            hipLaunchKernelGGL(k2_exact_rows<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 16, st,
+                               tb, cd, out, n_passes, w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p,
+                               w.arg, per_group, u8_off, full_row, full_row);
+        hipLaunchKernelGGL(k2_exact_wide<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 32, st, tb,
+                           cd, out, n_passes, w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg,
+                           per_group, u8_off, full_row, full_row);
+    };
+    if (tb.odd_degrees()) launch(std::true_type());
+    else launch(std::false_type());
 }
 
 }  // namespace harp

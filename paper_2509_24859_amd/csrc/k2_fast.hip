@@ -32,10 +32,11 @@
 //    about the previous DP row (it is not monotone when transfer times dominate); in the worst
 //    case the scan covers the whole range.
 //
-// With tp a power of two and every time below 2^31 us (both checked by the table build), the
-// stage time is one subtraction and one shift on the fused 32-bit row
+// With every time below 2^31 us (checked by the table build), the stage time is one subtraction and one
+// shift on the fused 32-bit row
 //   P[j] = PF[type][j] + tp * PR[g][tp][j]:   time(s; j, i) = (P[i] + tp - 1 - P[j]) >> log2 tp,
-// because ceil(a / tp) + b = ceil((a + tp b) / tp) for integers.  Transfer times come from the
+// because ceil(a / tp) + b = ceil((a + tp b) / tp) for integers; where some degree is no power of two a
+// multiplication takes the place of the shift (TpDiv).  Transfer times come from the
 // per-link cut table built beside the rows.
 //
 // Mapping of k2_fast: one wavefront per live candidate at a time (persistent wavefronts draw from
@@ -294,7 +295,8 @@ __host__ __device__ inline size_t fast_row_bytes(int span) {
     return (size_t(span + kPad) * sizeof(Pair) + 15) & ~size_t(15);
 }
 
-template <bool kCount>
+// kCount: counts the transitions it evaluates.  kOdd: some degree is no power of two.
+template <bool kCount, bool kOdd>
 __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev cd, PlansDev out, int *counts,
                                                             const int32_t *live_list,
                                                             uint32_t *dead_list, FastArgs fa) {
@@ -326,7 +328,7 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
     struct Stage {
         const uint32_t *p_row, *cm_row;
         const uint16_t *lo;
-        int shift;
+        TpDiv div;
     };
     auto stage_of = [&](int s, int S) -> Stage {
         const uint32_t w = (uint32_t)uniform((int)slot[s]);
@@ -338,7 +340,7 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
         st.p_row = tb.P32 + (int64_t(g) * tb.n_tp + k) * tb.pitch32;
         st.cm_row = tb.CM + (int64_t(g) * tb.G + gn) * tb.pitch32;
         st.lo = fa.lo_tab + (int64_t(n - 1) * rows_per_n + t * tb.n_tp + k) * fa.lo_pitch;
-        st.shift = int((fa.shift_packed >> (4 * k)) & 15u);
+        st.div = tp_div<kOdd>(tb, kOdd ? uint32_t(k) : (fa.shift_packed >> (4 * k)) & 15u);
         return st;
     };
 
@@ -445,8 +447,7 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                 const int jl = band_lo(b0), jh = band_hi(b0);     // predecessors: row s
                 const int il = band_lo(b1), ih = band_hi(b1);     // cells: row s + 1
                 const int top_n = band_hi(b2);                    // stage s+1 reads its time row up to here
-                const int shift = cur.shift;
-                const uint32_t tp = 1u << shift;
+                const TpDiv div = cur.div;
                 const Stage nxt = stage_of(s + 1, S);
                 const bool nxt_is_last = s + 2 == S;
                 const uint32_t a_word = (uint32_t)uniform((int)aoff[s]);
@@ -488,17 +489,17 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                     if (i <= ih) {
                         const int hi = (i - 1) < jh ? (i - 1) : jh;
                         const int lo = lo_c > jl ? lo_c : jl;
-                        const uint32_t xi = rows[i].p + tp - 1;
+                        const uint32_t xi = rows[i].p + div.add;
                         const uint32_t cut = cut_c;
                         int bt = hi;
                         int j = hi;
                         while (j - 3 >= lo) {
                             const Pair *pe = rows + (j - 3);
                             const Pair e3 = pe[0], e2 = pe[1], e1 = pe[2], e0 = pe[3];
-                            const uint32_t t3 = (xi - e3.p) >> shift;
-                            const uint32_t v0 = umax3(e0.d, (xi - e0.p) >> shift, cut);
-                            const uint32_t v1 = umax3(e1.d, (xi - e1.p) >> shift, cut);
-                            const uint32_t v2 = umax3(e2.d, (xi - e2.p) >> shift, cut);
+                            const uint32_t t3 = tp_quot<kOdd>(xi - e3.p, div);
+                            const uint32_t v0 = umax3(e0.d, tp_quot<kOdd>(xi - e0.p, div), cut);
+                            const uint32_t v1 = umax3(e1.d, tp_quot<kOdd>(xi - e1.p, div), cut);
+                            const uint32_t v2 = umax3(e2.d, tp_quot<kOdd>(xi - e2.p, div), cut);
                             const uint32_t v3 = umax3(e3.d, t3, cut);
                             const uint32_t m = umin2(umin2(v0, v1), umin2(v2, v3));
                             const bool upd = m <= best;
@@ -511,9 +512,9 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                         {
                             const Pair *pe = rows + (j - 3);
                             const Pair e2 = pe[1], e1 = pe[2], e0 = pe[3];
-                            const uint32_t v0 = j >= lo ? umax3(e0.d, (xi - e0.p) >> shift, cut) : kInf32;
-                            const uint32_t v1 = j - 1 >= lo ? umax3(e1.d, (xi - e1.p) >> shift, cut) : kInf32;
-                            const uint32_t v2 = j - 2 >= lo ? umax3(e2.d, (xi - e2.p) >> shift, cut) : kInf32;
+                            const uint32_t v0 = j >= lo ? umax3(e0.d, tp_quot<kOdd>(xi - e0.p, div), cut) : kInf32;
+                            const uint32_t v1 = j - 1 >= lo ? umax3(e1.d, tp_quot<kOdd>(xi - e1.p, div), cut) : kInf32;
+                            const uint32_t v2 = j - 2 >= lo ? umax3(e2.d, tp_quot<kOdd>(xi - e2.p, div), cut) : kInf32;
                             const uint32_t m = umin2(umin2(v0, v1), v2);
                             const bool upd = (m <= best) & (j >= lo);
                             best = upd ? m : best;
@@ -524,9 +525,9 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                         {
                             const Pair *pw = rows + (bt - 3);
                             const Pair w3 = pw[0], w2 = pw[1], w1 = pw[2];
-                            const uint32_t u1 = umax3(w1.d, (xi - w1.p) >> shift, cut);
-                            const uint32_t u2 = umax3(w2.d, (xi - w2.p) >> shift, cut);
-                            const uint32_t u3 = umax3(w3.d, (xi - w3.p) >> shift, cut);
+                            const uint32_t u1 = umax3(w1.d, tp_quot<kOdd>(xi - w1.p, div), cut);
+                            const uint32_t u2 = umax3(w2.d, tp_quot<kOdd>(xi - w2.p, div), cut);
+                            const uint32_t u3 = umax3(w3.d, tp_quot<kOdd>(xi - w3.p, div), cut);
                             best_j = bt;
                             best_j = ((u1 == best) & (bt - 1 >= lo)) ? bt - 1 : best_j;
                             best_j = ((u2 == best) & (bt - 2 >= lo)) ? bt - 2 : best_j;
@@ -581,9 +582,9 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
             {
                 const int s = S - 1;
                 const uint32_t b0 = (uint32_t)uniform((int)band[s]);
-                const int shift = cur.shift;
+                const TpDiv div = cur.div;
                 const Pair *rows = rows0 - band_lo(b0);
-                const uint32_t xi = rows[L].p + (1u << shift) - 1;
+                const uint32_t xi = rows[L].p + div.add;
                 const int lo_L = uniform((int)cur.lo[L]);
                 const int lo = lo_L > band_lo(b0) ? lo_L : band_lo(b0);
                 const int hi = (L - 1) < band_hi(b0) ? (L - 1) : band_hi(b0);
@@ -591,7 +592,7 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                 int best_j = INT32_MAX;
                 for (int j = lo + lane; j <= hi; j += 64) {
                     const Pair e = rows[j];
-                    const uint32_t tj = (xi - e.p) >> shift;
+                    const uint32_t tj = tp_quot<kOdd>(xi - e.p, div);
                     const uint32_t v = e.d > tj ? e.d : tj;
                     if (v < best) { best = v; best_j = j; }   // j rises within a lane
                     if (kCount) ++n_trans;
@@ -640,10 +641,10 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
             for (int s = lane; s < S; s += 64) {
                 const uint32_t w = slot[s], wn = slot[s + 1 < S ? s + 1 : s];
                 const int g = int(w & 0xFFFu), k = int((w >> 12) & 7u), gn = int(wn & 0xFFFu);
-                const int shift = int((fa.shift_packed >> (4 * k)) & 15u);
+                const TpDiv div = tp_div<kOdd>(tb, kOdd ? uint32_t(k) : (fa.shift_packed >> (4 * k)) & 15u);
                 const uint32_t *p = tb.P32 + (int64_t(g) * tb.n_tp + k) * tb.pitch32;
                 const int j = cuts[s], i = cuts[s + 1];
-                const uint32_t t = (p[i] + (1u << shift) - 1u - p[j]) >> shift;
+                const uint32_t t = tp_quot<kOdd>(p[i] + div.add - p[j], div);
                 const uint32_t cu = s < S - 1 ? tb.CM[(int64_t(g) * tb.G + gn) * tb.pitch32 + i] : 0u;
                 const uint32_t m = t > cu ? t : cu;
                 worst = worst > m ? worst : m;
@@ -783,7 +784,8 @@ void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &ou
     fa.arg_u8_off = fast_arg_u16_bytes(tb.L, cd.S_max);
     fa.work = work;
     fa.lo_pitch = int(lo_pitch(tb.L));
-    fa.shift_packed = 0;
+    const bool odd = tb.odd_degrees();
+    fa.shift_packed = 0;          // (unused with odd degrees)
     for (int k = 0; k < tb.n_tp; ++k) fa.shift_packed |= uint32_t(tb.tp_shift[k] & 15) << (4 * k);
     for (int pass = 0; pass < (shape.second_pass ? 2 : 1); ++pass) {
         const int per_cu = pass ? shape.wide_waves_per_cu : shape.waves_per_cu;
@@ -796,11 +798,14 @@ void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &ou
         if (n_groups < 1) n_groups = 1;
         const size_t lds = size_t(kFastWaves) * fa.lds_per_wave;
         if (work)
-            hipLaunchKernelGGL(k2_fast<true>, dim3(n_groups), dim3(kFastWaves * 64), lds, st, tb, cd, out, w.counts,
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_fast<true, false>), dim3(n_groups), dim3(kFastWaves * 64), lds, st, tb, cd, out, w.counts,
                                w.live_list, w.dead_list, fa);
+        else if (odd)
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_fast<false, true>), dim3(n_groups), dim3(kFastWaves * 64), lds, st, tb, cd,
+                               out, w.counts, w.live_list, w.dead_list, fa);
         else
-            hipLaunchKernelGGL(k2_fast<false>, dim3(n_groups), dim3(kFastWaves * 64), lds, st, tb, cd, out, w.counts,
-                               w.live_list, w.dead_list, fa);
+            hipLaunchKernelGGL(HIP_KERNEL_NAME(k2_fast<false, false>), dim3(n_groups), dim3(kFastWaves * 64), lds, st, tb, cd,
+                               out, w.counts, w.live_list, w.dead_list, fa);
     }
 }
 

@@ -27,6 +27,8 @@
 // Sums are 32-bit while they stay below 2^31 - 1 - cap, so that a stored sum plus any admissible
 // stage time cannot reach infinity (2^31); a candidate for which some cell would exceed that is
 // queued and redone by the instantiation with 64-bit sums.
+#include <type_traits>
+
 #include "fast_common.h"
 #include "harp_internal.h"
 #include "plan_common.h"
@@ -76,7 +78,7 @@ __host__ __device__ inline size_t h1f1b_cut_bytes(size_t entry) { return sizeof(
 // per candidate (64-thread workgroups), LDS rows that hold the cuts one slot touches (a slot's cells
 // and continuations: B[slot] .. F[slot+1]), sized for the candidate's widest slot; a candidate that
 // does not fit is queued.  kMode 2: as 0, on the candidates queued by 1.
-template <typename SumT, int kMode>
+template <typename SumT, int kMode, bool kOdd>
 __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &cd, const int64_t *t_max,
                                            const PlansDev &out, int32_t *warmup, int *counts,
                                            const int32_t *live_list, uint32_t *dead_list,
@@ -157,7 +159,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                 sc[s].cap = int64_t(tb.tp[k]) * tb.type_mem[tb.group_type[g]];
                 sc[s].p_row = uint32_t((int64_t(g) * tb.n_tp + k) * tb.pitch32);
                 sc[s].cm_row_shift = uint32_t((int64_t(g) * tb.G + g_next) * tb.pitch32) |
-                                     (uint32_t(tb.tp_shift[k]) << 27);
+                                     (tp_code<kOdd>(tb, k) << 27);
                 int32_t first = tb.group_base[g];
                 for (int q = s - 1; q >= 0 && grp[q] == g; --q) first += tpv[q];
                 df[s] = first;
@@ -257,8 +259,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                 continue;
             }
             const uint32_t rsv = (uint32_t)uniform((int)sc[slot].cm_row_shift);
-            const int shift = int(rsv >> 27);
-            const uint32_t tp = 1u << shift;
+            const TpDiv div = tp_div<kOdd>(tb, rsv >> 27);
             const int64_t capm = uniform64(sc[slot].cap);
             const uint16_t *hi_row = hi_tab + (uint32_t)uniform((int)hi_off[slot]);
             // rows of this slot start at its lowest cell il, the row of continuations at jl, the rows
@@ -299,7 +300,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                         // the other rows hold there is never used
                         const Entry e = prev[j + u];
                         const MemPair mj = mem[j + u];
-                        tj = (pr_cur[j + u] + tp - 1 - xi) >> shift;
+                        tj = tp_quot<kOdd>(pr_cur[j + u] + div.add - xi, div);
                         const int64_t dpp = mj.pp - mi.pp, dps = mj.ps - mi.ps;
                         const bool fits = dpp + int64_t(e.nn) * dps <= capm;
                         const SumT v = e.h + tj;
@@ -377,9 +378,9 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             for (int s = lane; s < S; s += 64) {
                 const int j = trial[s], i = trial[s + 1];
                 const uint32_t rsl = sc[s].cm_row_shift;
-                const int shift = int(rsl >> 27);
+                const TpDiv div = tp_div<kOdd>(tb, rsl >> 27);
                 const uint32_t *p = tb.P32 + sc[s].p_row;
-                const uint32_t t = (p[i] + (1u << shift) - 1u - p[j]) >> shift;
+                const uint32_t t = tp_quot<kOdd>(p[i] + div.add - p[j], div);
                 const uint32_t cu = s < S - 1 ? tb.CM[(rsl & kRowMask) + uint32_t(i)] : 0u;
                 const uint32_t m = t > cu ? t : cu;
                 w = w > m ? w : m;
@@ -421,11 +422,12 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
 }
 
 #define HARP_H1F1B_KERNEL(NAME, BOUNDS, SUM, MODE)                                                                  \
+    template <bool kOdd>                                                                                           \
     __global__ BOUNDS void NAME(TablesDev tb, CandDev cd, const int64_t *t_max, PlansDev out, int32_t *warmup,     \
                                 int *counts, const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands, \
                                 const uint16_t *hi_tab, int idx_pitch, unsigned char *arg_base,                    \
                                 size_t arg_per_group, int row_len, int arg_pitch) {                                \
-        h1f1b_body<SUM, MODE>(tb, cd, t_max, out, warmup, counts, live_list, dead_list, bands, hi_tab, idx_pitch,  \
+        h1f1b_body<SUM, MODE, kOdd>(tb, cd, t_max, out, warmup, counts, live_list, dead_list, bands, hi_tab, idx_pitch, \
                               arg_base, arg_per_group, row_len, arg_pitch);                                        \
     }
 HARP_H1F1B_KERNEL(k2_h1f1b, __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5, 5))), uint32_t, 1)
@@ -470,16 +472,21 @@ void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_
     if (n_waves > n_slices) n_waves = n_slices;
     if (n_waves > cd.C) n_waves = cd.C;
     if (n_waves < 1) n_waves = 1;
-    hipLaunchKernelGGL(k2_h1f1b, dim3(n_waves), dim3(64), small + size_t(entries) * h1f1b_cut_bytes(8), st, tb, cd,
-                       t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab, idx_pitch, w.arg,
-                       per_group, entries, arg_pitch);
-    if (entries < row_len)
-        hipLaunchKernelGGL(k2_h1f1b_rows, dim3(n_groups), dim3(kFastThreads), h1f1b_lds_bytes(tb.L, cd.S_max, 8),
-                           st, tb, cd, t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab,
-                           idx_pitch, w.arg, per_group, row_len, arg_pitch);
-    hipLaunchKernelGGL(k2_h1f1b_wide, dim3(n_groups), dim3(kFastThreads), h1f1b_lds_bytes(tb.L, cd.S_max, 16), st,
-                       tb, cd, t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab, idx_pitch,
-                       w.arg, per_group, row_len, arg_pitch);
+    auto launch = [&](auto odd_t) {
+        constexpr bool odd = decltype(odd_t)::value;
+        hipLaunchKernelGGL(k2_h1f1b<odd>, dim3(n_waves), dim3(64), small + size_t(entries) * h1f1b_cut_bytes(8), st, tb, cd,
+                           t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab, idx_pitch, w.arg,
+                           per_group, entries, arg_pitch);
+        if (entries < row_len)
+            hipLaunchKernelGGL(k2_h1f1b_rows<odd>, dim3(n_groups), dim3(kFastThreads), h1f1b_lds_bytes(tb.L, cd.S_max, 8),
+                               st, tb, cd, t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab,
+                               idx_pitch, w.arg, per_group, row_len, arg_pitch);
+        hipLaunchKernelGGL(k2_h1f1b_wide<odd>, dim3(n_groups), dim3(kFastThreads), h1f1b_lds_bytes(tb.L, cd.S_max, 16), st,
+                           tb, cd, t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab, idx_pitch,
+                           w.arg, per_group, row_len, arg_pitch);
+    };
+    if (tb.odd_degrees()) launch(std::true_type());
+    else launch(std::false_type());
 }
 
 }  // namespace harp
