@@ -99,6 +99,50 @@ inline size_t fast_lds_bytes(int L, int S_max) {
     return (b + 15) & ~size_t(15);
 }
 
+// Which candidate a wavefront takes next, in the kernels that work one per wavefront.  One counter for all
+// would serialise them: an addition to a word that every XCD adds to takes 11.4 ns, whoever asks, so 16,384
+// draws cost 190 us where the candidates themselves take 60.  Hence the first candidate of a wavefront is
+// the one of its own number, and the others are dealt into 64 shares with a counter each, on a line of its
+// own, which only workgroups of one XCD draw from (consecutive workgroups go to the 8 XCDs in turn): 64
+// counters 14 ns apart each.  A wavefront whose share is used up reads all counters at once, a lane each,
+// and goes on with the next share that has candidates left.  Ends: a counter only rises, and every round
+// either returns a candidate or finds its share used up.
+constexpr int kShares = 64;
+constexpr int kShareInts = int(kTicketBytes / kShares / sizeof(int));
+constexpr int kTicketFast = 0, kTicketFastWide = 1, kTicketExact = 2, kTicketH1f1b = 3;   // word of a line
+struct Draw {
+    int *word;               // this kernel's word of the first share's line
+    int n_items, n_waves, home;
+    bool first;
+    __device__ __forceinline__ Draw(int *tickets, int which, int items, int waves)
+        : word(tickets + which), n_items(items), n_waves(waves), home(blockIdx.x & (kShares - 1)), first(true) {}
+    // All lanes of the wavefront: the next item, or -1.
+    __device__ __forceinline__ int next(int wave_id) {
+        if (first) {
+            first = false;
+            if (wave_id < n_items) return wave_id;
+        }
+        if (n_items <= n_waves) return -1;
+        for (;;) {
+            // (a lane number of its own: the compiler must not join this branch with another on lane 0 around it,
+            // or the other lanes reach the broadcast without lane 0's ticket)
+            int lane = threadIdx.x & 63;
+            asm volatile("" : "+v"(lane));
+            int t = 0;
+            if (lane == 0) t = atomicAdd(word + home * kShareInts, 1);
+            wave_sync();
+            const int n = n_waves + home + kShares * uniform(t);
+            if (n < n_items) return n;
+            const int seen = __hip_atomic_load(word + lane * kShareInts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long left = __ballot(n_waves + lane + kShares * seen < n_items);
+            if (left == 0) return -1;
+            const int from = (home + 1) & (kShares - 1);
+            const unsigned long long turned = from == 0 ? left : (left >> from) | (left << (64 - from));
+            home = uniform((from + __ffsll((long long)turned) - 1) & (kShares - 1));
+        }
+    }
+};
+
 // Back-pointer slice of one wavefront (k2_fast) or workgroup (the kernels built on it): a 16-bit
 // entry per DP cell, followed by the one-byte entries k2_fast uses for cells whose back-pointers
 // leave LDS (distance to the previous cut; the 16-bit entry holds the cut itself when the distance
@@ -125,10 +169,11 @@ inline size_t lo_table_bytes(int L, int S_max, int M, int T, int n_tp) {
     return 2 * size_t(lo_n_max(L, S_max, M)) * size_t(T) * size_t(n_tp) * lo_pitch(L) * sizeof(uint16_t);
 }
 
-// Workspace: counters | live list [C] | dead list [C] | bands [C][S_max+1] | feasibility index |
+// Workspace: counters | tickets | live list [C] | dead list [C] | bands [C][S_max+1] | feasibility index |
 // back-pointer slices (one per resident wavefront of k2_fast, one per workgroup of the other kernels).
 struct FastWorkspace {
     int *counts;
+    int *tickets;            // [kShares] lines
     int32_t *live_list;
     uint32_t *dead_list;
     uint32_t *bands;
@@ -151,6 +196,7 @@ inline FastWorkspace carve(void *ws, const FastShape &f, int n_slices) {
     FastWorkspace w;
     size_t off = 0;
     w.counts = reinterpret_cast<int *>(base + off); off += 256;
+    w.tickets = reinterpret_cast<int *>(base + off); off += kTicketBytes;
     w.live_list = reinterpret_cast<int32_t *>(base + off); off += up(size_t(f.C) * 4);
     w.dead_list = reinterpret_cast<uint32_t *>(base + off); off += up(size_t(f.C) * 4);
     w.bands = reinterpret_cast<uint32_t *>(base + off); off += up(size_t(f.C) * (f.S_max + 1) * 4);

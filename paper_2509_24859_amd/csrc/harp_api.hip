@@ -23,7 +23,7 @@ struct harp_ctx {
 // Planner workspace of harp_plan_batch_static.  In host code this name is only a handle for
 // hipGetSymbolAddress: harp_create asks for the device address once per context, with the
 // context's device current, and every later use goes through harp_ctx::scratch.
-static __device__ __align__(256) unsigned char scratch[HARP_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[HARP_STATIC_SCRATCH_BYTES + kTicketBytes];
 
 struct harp_tables {
     TablesDev dev;
@@ -499,7 +499,7 @@ int harp_plan_batch_static(harp_ctx *ctx, harp_tables *t, const harp_candidates 
                            void *hip_stream) {
     PlanCall pc;
     const int rc = plan_prepare(ctx, t, cd, out, false, false, ctx ? ctx->scratch : nullptr,
-                                size_t(HARP_STATIC_SCRATCH_BYTES), true, hip_stream, pc);
+                                size_t(HARP_STATIC_SCRATCH_BYTES) + kTicketBytes, true, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
     return plan_minmax(ctx, t, pc, ctx->scratch, nullptr);
 }

@@ -140,6 +140,7 @@ void launch_clear_work(unsigned long long *work, hipStream_t st);
 size_t plan_fast_index_bytes(const TablesDev &tb, int S_max);
 int plan_fast_groups(int L, int S_max, int n_cu);
 int plan_fast_waves(int L, int S_max, int n_cu);
+constexpr size_t kTicketBytes = 64 * 128; // tickets of the wavefront-per-candidate kernels (fast_common.h)
 constexpr int kFastWaves = 4;           // wavefronts per workgroup of k2_fast; they share nothing
 constexpr size_t kFastIndexLimit = size_t(256) << 20;   // feasibility index of the pre-pass
 constexpr int kIndexMaxL = 16383;       // its build keeps one 8-byte sum per cut in LDS (128 KB)

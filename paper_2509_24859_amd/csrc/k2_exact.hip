@@ -84,7 +84,7 @@ __host__ __device__ inline size_t exact_small_bytes(int S_max) {
 }
 
 // counts: [0] live candidates, [1] dead candidates, [2] candidates queued for 64-bit sums,
-// [3], [4] next item of the 32- and 64-bit kernels' work lists, [10] candidates queued for rows over
+// [4] next item of the 64-bit kernel's work list, [10] candidates queued for rows over
 // the whole sequence, [11] next item of that list.
 // Both queues sit in the unused tail of the dead list (live + dead = C entries in all): the 64-bit
 // one grows from its front, the other from its back.
@@ -95,8 +95,8 @@ __host__ __device__ inline size_t exact_small_bytes(int S_max) {
 // 0, on the candidates queued by 1.
 template <typename SumT, int kMode, bool kOdd>
 __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &cd, const PlansDev &out,
-                                           int32_t *n_passes, int *counts, const int32_t *live_list,
-                                           uint32_t *dead_list, const uint32_t *bands, const uint16_t *lo_tab,
+                                           int32_t *n_passes, int *counts, int *tickets,
+                                           const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands, const uint16_t *lo_tab,
                                            int lo_pitch, unsigned char *arg_base, size_t arg_per_group,
                                            size_t arg_u8_off, int row_len, int lds_row_entries) {
     using Pair = typename SumTraits<SumT>::Entry;
@@ -131,14 +131,21 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
     const int n_items = kWide ? counts[2] : kMode == 2 ? counts[10] : counts[0];
     const int64_t m_cap = tb.M;
 
-    // candidates differ widely in passes, so workgroups draw them from a shared counter
-    int *next_item = counts + (kWide ? 4 : kMode == 2 ? 11 : 3);
+    // candidates differ widely in passes, so workgroups draw them from shared counters
+    int *next_item = counts + (kWide ? 4 : 11);
+    Draw items(tickets, kTicketExact, n_items, int(gridDim.x));
     for (;;) {
         __syncthreads();   // the previous candidate's tail has finished with LDS
-        if (tid == 0) scal[0] = (uint64_t)atomicAdd(next_item, 1);
-        __syncthreads();
-        const int n = uniform((int)scal[0]);
-        if (n >= n_items) break;
+        int n;
+        if constexpr (kBandRows) {
+            n = items.next(int(blockIdx.x));
+            if (n < 0) break;
+        } else {
+            if (tid == 0) scal[0] = (uint64_t)atomicAdd(next_item, 1);
+            __syncthreads();
+            n = uniform((int)scal[0]);
+            if (n >= n_items) break;
+        }
         const int c = kWide ? int(dead_list[n_dead + n]) : kMode == 2 ? int(dead_list[cd.C - 1 - n]) : live_list[n];
         const int S = cd.cand_S[c];
         // the min-max planner has run on this batch: candidates it found no plan for stay as they are,
@@ -508,10 +515,10 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
 #define HARP_EXACT_KERNEL(NAME, BOUNDS, SUM, MODE)                                                                  \
     template <bool kOdd>                                                                                           \
     __global__ BOUNDS void NAME(TablesDev tb, CandDev cd, PlansDev out, int32_t *n_passes, int *counts,            \
-                                const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands,             \
+                                int *tickets, const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands,             \
                                 const uint16_t *lo_tab, int lo_pitch, unsigned char *arg_base,                    \
                                 size_t arg_per_group, size_t arg_u8_off, int row_len, int lds_row_entries) {      \
-        exact_body<SUM, MODE, kOdd>(tb, cd, out, n_passes, counts, live_list, dead_list, bands, lo_tab, lo_pitch, \
+        exact_body<SUM, MODE, kOdd>(tb, cd, out, n_passes, counts, tickets, live_list, dead_list, bands, lo_tab, lo_pitch, \
                               arg_base, arg_per_group, arg_u8_off, row_len, lds_row_entries);                     \
     }
 HARP_EXACT_KERNEL(k2_exact, __launch_bounds__(64), uint32_t, 1)
@@ -546,14 +553,14 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
     auto launch = [&](auto odd_t) {
         constexpr bool odd = decltype(odd_t)::value;
         hipLaunchKernelGGL(k2_exact<odd>, dim3(n_waves), dim3(64), small + size_t(entries) * 16, st, tb, cd, out, n_passes,
-                           w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg, per_group, u8_off,
+                           w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg, per_group, u8_off,
                            full_row, entries);
         if (entries < full_row)
             hipLaunchKernelGGL(k2_exact_rows<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 16, st,
-                               tb, cd, out, n_passes, w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p,
+                               tb, cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p,
                                w.arg, per_group, u8_off, full_row, full_row);
         hipLaunchKernelGGL(k2_exact_wide<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 32, st, tb,
-                           cd, out, n_passes, w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg,
+                           cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg,
                            per_group, u8_off, full_row, full_row);
     };
     if (tb.odd_degrees()) launch(std::true_type());

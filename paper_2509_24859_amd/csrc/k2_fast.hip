@@ -255,8 +255,9 @@ __global__ __launch_bounds__(256) void k2_band(TablesDev tb, CandDev cd, int *co
     }
 }
 
-__global__ void k2_clear_count(int *counts) {
-    if (threadIdx.x < 32) counts[threadIdx.x] = 0;
+// one workgroup: the counters and the tickets, which lie one after the other
+__global__ __launch_bounds__(256) void k2_clear_count(int *counts) {
+    for (int i = threadIdx.x; i < int((256 + kTicketBytes) / sizeof(int)); i += 256) counts[i] = 0;
 }
 
 __global__ void k2_clear_work(unsigned long long *work) {
@@ -273,6 +274,7 @@ constexpr uint32_t kArgInLds = 1u << 31;    // flag on that word: the stage's ba
 __device__ __forceinline__ uint32_t umin2(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
 struct FastArgs {
+    int *tickets;
     const uint32_t *bands;        // [C][S_max + 1]
     const uint16_t *lo_tab;       // feasibility index
     unsigned char *arg_base;      // back-pointer slices
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
     // first pass: the live list; second pass: the candidates the first one queued behind the dead list
     const int n_dead = counts[1];
     const int n_live = fa.wide_pass ? counts[8] : counts[0];
-    int *next_item = counts + (fa.wide_pass ? 9 : 5);
+    Draw items(fa.tickets, fa.wide_pass ? kTicketFastWide : kTicketFast, n_live, n_waves);
     const int m_cap = tb.M;
     const int rows_per_n = tb.T * tb.n_tp;
     unsigned long long n_trans = 0, n_cells = 0, n_trips = 0, n_cands = 0;
@@ -344,15 +346,11 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
         return st;
     };
 
-    // candidates differ in stages and band widths, so wavefronts draw them from a shared counter
+    // candidates differ in stages and band widths, so wavefronts draw them from shared counters
     for (;;) {
-        // Every lane takes part in the draw (only the first adds one).  A draw under `if (lane == 0)`
-        // would sit right behind the lane-0 stores that end the previous candidate; the compiler
-        // joins two such branches, and the other lanes then reach the broadcast below on their own,
-        // ahead of lane 0 and without a ticket.
         wave_sync();
-        const int n = uniform(atomicAdd(next_item, lane == 0 ? 1 : 0));
-        if (n >= n_live) break;
+        const int n = items.next(wave_id);
+        if (n < 0) break;
         const int c = uniform(fa.wide_pass ? int(dead_list[n_dead + n]) : live_list[n]);
         const int S = uniform(cd.cand_S[c]);
         wave_sync();              // the previous candidate's tail has finished with LDS
@@ -758,7 +756,7 @@ void launch_plan_index(const TablesDev &tb, int S_max, uint16_t *index, hipStrea
 // index.
 void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n_slices, hipStream_t st) {
     const FastWorkspace w = carve(ws, fast_shape(tb, cd), n_slices);
-    hipLaunchKernelGGL(k2_clear_count, dim3(1), dim3(64), 0, st, w.counts);
+    hipLaunchKernelGGL(k2_clear_count, dim3(1), dim3(256), 0, st, w.counts);
     const long long idx_rows = (long long)lo_n_max(tb.L, cd.S_max, tb.M) * tb.T * tb.n_tp;
     const int idx_pitch = int(lo_pitch(tb.L));
     launch_plan_index(tb, cd.S_max, w.lo_tab, st);
@@ -777,6 +775,7 @@ void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &ou
     launch_plan_prepass(tb, cd, ws, n_slices, st);
     const FastLaunch shape = fast_launch_shape(tb.L, cd.S_max);
     FastArgs fa;
+    fa.tickets = w.tickets;
     fa.bands = w.bands;
     fa.lo_tab = w.lo_tab;
     fa.arg_base = w.arg;

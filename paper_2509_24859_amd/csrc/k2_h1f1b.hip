@@ -69,8 +69,7 @@ __host__ __device__ inline size_t h1f1b_small_bytes(int S_max) {
 // of entries, one of times
 __host__ __device__ inline size_t h1f1b_cut_bytes(size_t entry) { return sizeof(MemPair) + 2 * entry + 4; }
 
-// counts: [0] live, [1] dead, [2] queued for 64-bit sums, [6] and [7] tickets of the 32- and 64-bit
-// kernels, [10] candidates queued for rows over the whole sequence, [11] next item of that list.
+// counts: [0] live, [1] dead, [2] queued for 64-bit sums, [7] ticket of the 64-bit kernel, [10] candidates queued for rows over the whole sequence, [11] next item of that list.
 // Both queues sit in the unused tail of the dead list, the 64-bit one from its front, the other from
 // its back.
 //
@@ -80,7 +79,7 @@ __host__ __device__ inline size_t h1f1b_cut_bytes(size_t entry) { return sizeof(
 // does not fit is queued.  kMode 2: as 0, on the candidates queued by 1.
 template <typename SumT, int kMode, bool kOdd>
 __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &cd, const int64_t *t_max,
-                                           const PlansDev &out, int32_t *warmup, int *counts,
+                                           const PlansDev &out, int32_t *warmup, int *counts, int *tickets,
                                            const int32_t *live_list, uint32_t *dead_list,
                                            const uint32_t *bands, const uint16_t *hi_tab, int idx_pitch,
                                            unsigned char *arg_base, size_t arg_per_group, int row_len,
@@ -119,7 +118,8 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
     uint16_t *arg = reinterpret_cast<uint16_t *>(arg_base + size_t(blockIdx.x) * arg_per_group);
     const int n_dead = counts[1];
     const int n_items = kWide ? counts[2] : kMode == 2 ? counts[10] : counts[0];
-    int *next_item = counts + (kWide ? 7 : kMode == 2 ? 11 : 6);
+    int *next_item = counts + (kWide ? 7 : 11);
+    Draw items(tickets, kTicketH1f1b, n_items, int(gridDim.x));
     const int64_t m_cap = tb.M;
     const int64_t *PP = tb.PP(), *PS = tb.PS();
 
@@ -132,10 +132,17 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
 
     for (;;) {
         __syncthreads();   // the previous candidate's tail has finished with LDS
-        if (tid == 0) { flags[0] = (uint32_t)atomicAdd(next_item, 1); flags[1] = 0; }
-        __syncthreads();
-        const int n = uniform((int)flags[0]);
-        if (n >= n_items) break;
+        int n;
+        if constexpr (kBandRows) {
+            n = items.next(int(blockIdx.x));
+            if (n < 0) break;
+            if (tid == 0) flags[1] = 0;
+        } else {
+            if (tid == 0) { flags[0] = (uint32_t)atomicAdd(next_item, 1); flags[1] = 0; }
+            __syncthreads();
+            n = uniform((int)flags[0]);
+            if (n >= n_items) break;
+        }
         const int c = kWide ? int(dead_list[n_dead + n]) : kMode == 2 ? int(dead_list[cd.C - 1 - n]) : live_list[n];
         const int S = cd.cand_S[c];
         const int64_t cap64 = t_max[c];
@@ -424,10 +431,11 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
 #define HARP_H1F1B_KERNEL(NAME, BOUNDS, SUM, MODE)                                                                  \
     template <bool kOdd>                                                                                           \
     __global__ BOUNDS void NAME(TablesDev tb, CandDev cd, const int64_t *t_max, PlansDev out, int32_t *warmup,     \
-                                int *counts, const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands, \
+                                int *counts, int *tickets, const int32_t *live_list, uint32_t *dead_list,          \
+                                const uint32_t *bands,                                                             \
                                 const uint16_t *hi_tab, int idx_pitch, unsigned char *arg_base,                    \
                                 size_t arg_per_group, int row_len, int arg_pitch) {                                \
-        h1f1b_body<SUM, MODE, kOdd>(tb, cd, t_max, out, warmup, counts, live_list, dead_list, bands, hi_tab, idx_pitch, \
+        h1f1b_body<SUM, MODE, kOdd>(tb, cd, t_max, out, warmup, counts, tickets, live_list, dead_list, bands, hi_tab, idx_pitch, \
                               arg_base, arg_per_group, row_len, arg_pitch);                                        \
     }
 HARP_H1F1B_KERNEL(k2_h1f1b, __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5, 5))), uint32_t, 1)
@@ -475,14 +483,14 @@ void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_
     auto launch = [&](auto odd_t) {
         constexpr bool odd = decltype(odd_t)::value;
         hipLaunchKernelGGL(k2_h1f1b<odd>, dim3(n_waves), dim3(64), small + size_t(entries) * h1f1b_cut_bytes(8), st, tb, cd,
-                           t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab, idx_pitch, w.arg,
+                           t_max, out, warmup, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, hi_tab, idx_pitch, w.arg,
                            per_group, entries, arg_pitch);
         if (entries < row_len)
             hipLaunchKernelGGL(k2_h1f1b_rows<odd>, dim3(n_groups), dim3(kFastThreads), h1f1b_lds_bytes(tb.L, cd.S_max, 8),
-                               st, tb, cd, t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab,
+                               st, tb, cd, t_max, out, warmup, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, hi_tab,
                                idx_pitch, w.arg, per_group, row_len, arg_pitch);
         hipLaunchKernelGGL(k2_h1f1b_wide<odd>, dim3(n_groups), dim3(kFastThreads), h1f1b_lds_bytes(tb.L, cd.S_max, 16), st,
-                           tb, cd, t_max, out, warmup, w.counts, w.live_list, w.dead_list, w.bands, hi_tab, idx_pitch,
+                           tb, cd, t_max, out, warmup, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, hi_tab, idx_pitch,
                            w.arg, per_group, row_len, arg_pitch);
     };
     if (tb.odd_degrees()) launch(std::true_type());
