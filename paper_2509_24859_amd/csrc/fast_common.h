@@ -109,6 +109,9 @@ inline size_t fast_lds_bytes(int L, int S_max) {
 // either returns a candidate or finds its share used up.
 constexpr int kShares = 64;
 constexpr int kShareInts = int(kTicketBytes / kShares / sizeof(int));
+constexpr int kWideBands = 12;          // counter: candidates listed with wide bands
+constexpr uint32_t kWideFlag = 1u << 30;    // on a live-list entry: the candidate is one of them, its bands are in `tight`
+__device__ __forceinline__ int listed(int32_t entry) { return int(uint32_t(entry) & (kWideFlag - 1u)); }
 constexpr int kTicketFast = 0, kTicketFastWide = 1, kTicketExact = 2, kTicketH1f1b = 3;   // word of a line
 struct Draw {
     int *word;               // this kernel's word of the first share's line
@@ -170,6 +173,7 @@ inline size_t lo_table_bytes(int L, int S_max, int M, int T, int n_tp) {
 }
 
 // Workspace: counters | tickets | live list [C] | dead list [C] | bands [C][S_max+1] | feasibility index |
+// list of wide candidates [C] | their bands under a cap [C][S_max+1] (both only where bands are narrowed) |
 // back-pointer slices (one per resident wavefront of k2_fast, one per workgroup of the other kernels).
 struct FastWorkspace {
     int *counts;
@@ -178,16 +182,19 @@ struct FastWorkspace {
     uint32_t *dead_list;
     uint32_t *bands;
     uint16_t *lo_tab;
+    int32_t *wide_list;      // [C] candidates with wide memory bands
+    uint32_t *tight;         // [C][S_max+1] their bands under a cap
     unsigned char *arg;
     size_t total;
 };
 
 struct FastShape {
     int L, S_max, C, M, T, n_tp;
+    bool narrow;             // bands under a cap where memory bands are wide (k2_narrow.hip, exact search)
 };
 
-inline FastShape fast_shape(const TablesDev &tb, const CandDev &cd) {
-    return FastShape{tb.L, cd.S_max, cd.C, tb.M, tb.T, tb.n_tp};
+inline FastShape fast_shape(const TablesDev &tb, const CandDev &cd, bool narrow) {
+    return FastShape{tb.L, cd.S_max, cd.C, tb.M, tb.T, tb.n_tp, narrow};
 }
 
 inline FastWorkspace carve(void *ws, const FastShape &f, int n_slices) {
@@ -201,6 +208,12 @@ inline FastWorkspace carve(void *ws, const FastShape &f, int n_slices) {
     w.dead_list = reinterpret_cast<uint32_t *>(base + off); off += up(size_t(f.C) * 4);
     w.bands = reinterpret_cast<uint32_t *>(base + off); off += up(size_t(f.C) * (f.S_max + 1) * 4);
     w.lo_tab = reinterpret_cast<uint16_t *>(base + off); off += up(lo_table_bytes(f.L, f.S_max, f.M, f.T, f.n_tp));
+    w.wide_list = nullptr;
+    w.tight = nullptr;
+    if (f.narrow) {
+        w.wide_list = reinterpret_cast<int32_t *>(base + off); off += up(size_t(f.C) * 4);
+        w.tight = reinterpret_cast<uint32_t *>(base + off); off += up(size_t(f.C) * (f.S_max + 1) * 4);
+    }
     w.arg = base + off; off += size_t(n_slices) * fast_arg_per_group(f.L, f.S_max);
     w.total = off;
     return w;

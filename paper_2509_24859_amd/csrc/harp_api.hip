@@ -170,9 +170,9 @@ bool fast_batch_ok(const harp_tables *t, const harp_candidates *cd) {
 }
 
 size_t plan_bytes_on_path(const harp_tables *t, const harp_candidates *cd, bool fast, int units) {
-    if (fast) return plan_fast_ws_bytes(t->dev, cd->S_max, cd->C, units) + 256;
+    if (fast) return plan_fast_ws_bytes(t->dev, cd->S_max, cd->C, units, false) + 256;
     // int64 path: the pre-pass area (lists, bands, index) when the index fits, then the workgroups' slices
-    const size_t prepass = fast_batch_ok(t, cd) ? plan_fast_ws_bytes(t->dev, cd->S_max, cd->C, 0) : 0;
+    const size_t prepass = fast_batch_ok(t, cd) ? plan_fast_ws_bytes(t->dev, cd->S_max, cd->C, 0, false) : 0;
     return prepass + size_t(units) * plan_generic_ws_per_group(t->dev.L, cd->S_max) + 256;
 }
 
@@ -406,10 +406,10 @@ size_t harp_plan_workspace_bytes(harp_ctx *ctx, const harp_tables *t, const harp
                                  ? plan_generic_ws_per_group(t->dev.L, cd->S_max)
                                  : plan_generic_h1f1b_ws_per_group(t->dev.L, cd->S_max);
     size_t gen = size_t(n_plan_groups(ctx, C, false, t->dev.L, cd->S_max)) * per_group;
-    if (fast_batch_ok(t, cd)) gen += plan_fast_ws_bytes(t->dev, cd->S_max, C, 0);
+    if (fast_batch_ok(t, cd)) gen += plan_fast_ws_bytes(t->dev, cd->S_max, C, 0, false);
     size_t fast = 0;
     if (t->lim.want_fast && fast_batch_ok(t, cd))
-        fast = plan_fast_ws_bytes(t->dev, cd->S_max, C, n_fast_slices(ctx, C, t->dev.L, cd->S_max));
+        fast = plan_fast_ws_bytes(t->dev, cd->S_max, C, n_fast_slices(ctx, C, t->dev.L, cd->S_max), t->dev.L >= kNarrowMinL);
     return (gen > fast ? gen : fast) + 256;
 }
 
@@ -475,8 +475,8 @@ int plan_prepare(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const
     return HARP_OK;
 }
 
-int plan_minmax(harp_ctx *ctx, harp_tables *t, const PlanCall &pc, void *ws, unsigned long long *work) {
-    if (pc.fast) launch_plan_fast(t->dev, pc.c, pc.o, ws, pc.slices, ctx->n_cu, work, pc.st);
+int plan_minmax(harp_ctx *ctx, harp_tables *t, const PlanCall &pc, void *ws, bool narrow, unsigned long long *work) {
+    if (pc.fast) launch_plan_fast(t->dev, pc.c, pc.o, ws, pc.slices, ctx->n_cu, narrow, work, pc.st);
     else launch_plan_generic(t->dev, pc.c, pc.o, ws, pc.groups, pc.banded, pc.st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the planner kernel");
@@ -492,7 +492,7 @@ int harp_plan_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, co
     PlanCall pc;
     const int rc = plan_prepare(ctx, t, cd, out, false, false, workspace, workspace_bytes, false, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
-    return plan_minmax(ctx, t, pc, workspace, nullptr);
+    return plan_minmax(ctx, t, pc, workspace, false, nullptr);
 }
 
 int harp_plan_batch_static(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const harp_plans *out,
@@ -501,7 +501,7 @@ int harp_plan_batch_static(harp_ctx *ctx, harp_tables *t, const harp_candidates 
     const int rc = plan_prepare(ctx, t, cd, out, false, false, ctx ? ctx->scratch : nullptr,
                                 size_t(HARP_STATIC_SCRATCH_BYTES) + kTicketBytes, true, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
-    return plan_minmax(ctx, t, pc, ctx->scratch, nullptr);
+    return plan_minmax(ctx, t, pc, ctx->scratch, false, nullptr);
 }
 
 int harp_plan_batch_count_work(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const harp_plans *out,
@@ -514,7 +514,7 @@ int harp_plan_batch_count_work(harp_ctx *ctx, harp_tables *t, const harp_candida
         return fail(ctx, HARP_ERR_UNIMPLEMENTED, "work is counted on the 32-bit path only");
     launch_clear_work(reinterpret_cast<unsigned long long *>(work), pc.st);
     if (cd->C == 0) return HARP_OK;
-    return plan_minmax(ctx, t, pc, workspace, reinterpret_cast<unsigned long long *>(work));
+    return plan_minmax(ctx, t, pc, workspace, false, reinterpret_cast<unsigned long long *>(work));
 }
 
 int harp_plan_exact_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const harp_plans *out,
@@ -524,9 +524,9 @@ int harp_plan_exact_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *
     int rc = plan_prepare(ctx, t, cd, out, false, false, workspace, workspace_bytes, false, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
     if (pc.fast) {
-        rc = plan_minmax(ctx, t, pc, workspace, nullptr);
+        rc = plan_minmax(ctx, t, pc, workspace, t->dev.L >= kNarrowMinL, nullptr);
         if (rc != HARP_OK) return rc;
-        launch_plan_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.slices, ctx->n_cu, pc.st);
+        launch_plan_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.slices, ctx->n_cu, t->dev.L >= kNarrowMinL, pc.st);
     } else {
         launch_plan_generic_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.banded, pc.st);
     }

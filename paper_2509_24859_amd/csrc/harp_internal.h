@@ -104,9 +104,14 @@ void launch_plan_generic_exact(const TablesDev &tb, const CandDev &cd, const Pla
                                void *ws, int n_groups, bool banded, hipStream_t st);
 size_t plan_generic_ws_per_group(int L, int S_max);
 void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &out, void *ws,
-                      int n_slices, int n_cu, unsigned long long *work, hipStream_t st);
+                      int n_slices, int n_cu, bool narrow, unsigned long long *work, hipStream_t st);
 void launch_plan_index(const TablesDev &tb, int S_max, uint16_t *index, hipStream_t st);
-void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n_groups, hipStream_t st);
+void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n_groups, bool narrow, hipStream_t st);
+// The exact search narrows bands (k2_narrow.hip) from this many operators on: a candidate is listed when its memory
+// bands are wider than kWideCells cuts a stage, one round of a wavefront's lanes, which shorter sequences rarely are.
+constexpr int kNarrowMinL = 128, kWideCells = 64;
+void launch_plan_narrow(const TablesDev &tb, const CandDev &cd, const PlansDev &out, void *ws, int n_slices, int n_cu,
+                        hipStream_t st);
 void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_max, const PlansDev &out,
                        int32_t *warmup, void *ws, int n_groups, int n_slices, int n_cu, hipStream_t st);
 void launch_plan_generic_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_max, const PlansDev &out,
@@ -135,7 +140,7 @@ size_t plan_mesh_sweep_slot_bytes(int S_max);
 size_t plan_mesh_ws_per_group(int L, int S_max, int64_t total_devices);
 size_t plan_mesh_ws_fixed(const TablesDev &tb, int S_max, int C);
 int plan_mesh_threads(int L, int64_t total_devices, int C, int n_cu);
-size_t plan_fast_ws_bytes(const TablesDev &tb, int S_max, int C, int n_slices);
+size_t plan_fast_ws_bytes(const TablesDev &tb, int S_max, int C, int n_slices, bool narrow);
 void launch_clear_work(unsigned long long *work, hipStream_t st);
 size_t plan_fast_index_bytes(const TablesDev &tb, int S_max);
 int plan_fast_groups(int L, int S_max, int n_cu);
@@ -145,7 +150,7 @@ constexpr int kFastWaves = 4;           // wavefronts per workgroup of k2_fast; 
 constexpr size_t kFastIndexLimit = size_t(256) << 20;   // feasibility index of the pre-pass
 constexpr int kIndexMaxL = 16383;       // its build keeps one 8-byte sum per cut in LDS (128 KB)
 void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &out, int32_t *n_passes,
-                       void *ws, int n_groups, int n_slices, int n_cu, hipStream_t st);
+                       void *ws, int n_groups, int n_slices, int n_cu, bool narrow, hipStream_t st);
 void launch_score(const TablesDev &tb, const CandDev &cd, const int32_t *splits,
                   int64_t *bottleneck, int64_t *iter_time, int32_t *status, bool fast32, int n_cu,
                   hipStream_t st);

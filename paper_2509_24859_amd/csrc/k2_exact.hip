@@ -96,7 +96,7 @@ __host__ __device__ inline size_t exact_small_bytes(int S_max) {
 template <typename SumT, int kMode, bool kOdd>
 __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &cd, const PlansDev &out,
                                            int32_t *n_passes, int *counts, int *tickets,
-                                           const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands, const uint16_t *lo_tab,
+                                           const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands, const uint32_t *tight, const uint16_t *lo_tab,
                                            int lo_pitch, unsigned char *arg_base, size_t arg_per_group,
                                            size_t arg_u8_off, int row_len, int lds_row_entries) {
     using Pair = typename SumTraits<SumT>::Entry;
@@ -146,7 +146,8 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             n = uniform((int)scal[0]);
             if (n >= n_items) break;
         }
-        const int c = kWide ? int(dead_list[n_dead + n]) : kMode == 2 ? int(dead_list[cd.C - 1 - n]) : live_list[n];
+        const int entry = kWide ? int(dead_list[n_dead + n]) : kMode == 2 ? int(dead_list[cd.C - 1 - n]) : live_list[n];
+        const int c = listed(entry);
         const int S = cd.cand_S[c];
         // the min-max planner has run on this batch: candidates it found no plan for stay as they are,
         // and a single stage has only one partition
@@ -158,7 +159,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
         const int64_t T_S = out.iter_time[c];
         const int64_t limit = T_S - (m_cap - 1) * t_S;      // the min-max plan's own sum
         if (!kWide && limit >= kNarrowLimit) {
-            if (tid == 0) dead_list[n_dead + atomicAdd(&counts[2], 1)] = uint32_t(c);
+            if (tid == 0) dead_list[n_dead + atomicAdd(&counts[2], 1)] = uint32_t(entry);
             continue;
         }
         {
@@ -177,7 +178,8 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 lo_off[s] = uint32_t((int64_t(n_inflight - 1) * tb.T * tb.n_tp + int64_t(tb.group_type[g]) * tb.n_tp + k) *
                                      lo_pitch);
             }
-            for (int s = tid; s <= S; s += nthreads) band[s] = bands[int64_t(c) * (S_max + 1) + s];
+            const uint32_t *bd = (c != entry ? tight : bands) + int64_t(c) * (S_max + 1);
+            for (int s = tid; s <= S; s += nthreads) band[s] = bd[s];
         }
         __syncthreads();
         if (kBandRows) {
@@ -194,7 +196,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             }
             const int row_entries = (uniform(span) + kPad + 1) & ~1;
             if (row_entries > lds_row_entries) {
-                if (tid == 0) dead_list[cd.C - 1 - atomicAdd(&counts[10], 1)] = uint32_t(c);
+                if (tid == 0) dead_list[cd.C - 1 - atomicAdd(&counts[10], 1)] = uint32_t(entry);
                 continue;
             }
             buf1 = buf0 + row_entries;
@@ -515,10 +517,10 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
 #define HARP_EXACT_KERNEL(NAME, BOUNDS, SUM, MODE)                                                                  \
     template <bool kOdd>                                                                                           \
     __global__ BOUNDS void NAME(TablesDev tb, CandDev cd, PlansDev out, int32_t *n_passes, int *counts,            \
-                                int *tickets, const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands,             \
+                                int *tickets, const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands, const uint32_t *tight, \
                                 const uint16_t *lo_tab, int lo_pitch, unsigned char *arg_base,                    \
                                 size_t arg_per_group, size_t arg_u8_off, int row_len, int lds_row_entries) {      \
-        exact_body<SUM, MODE, kOdd>(tb, cd, out, n_passes, counts, tickets, live_list, dead_list, bands, lo_tab, lo_pitch, \
+        exact_body<SUM, MODE, kOdd>(tb, cd, out, n_passes, counts, tickets, live_list, dead_list, bands, tight, lo_tab, lo_pitch, \
                               arg_base, arg_per_group, arg_u8_off, row_len, lds_row_entries);                     \
     }
 HARP_EXACT_KERNEL(k2_exact, __launch_bounds__(64), uint32_t, 1)
@@ -532,8 +534,9 @@ HARP_EXACT_KERNEL(k2_exact_wide, __launch_bounds__(kFastThreads), uint64_t, 0)
 // min-max results in `out` are its inputs.  n_groups: resident 256-thread workgroups; n_slices:
 // back-pointer slices in the workspace (the wavefront-per-candidate launch runs at most that many).
 void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &out, int32_t *n_passes,
-                       void *ws, int n_groups, int n_slices, int n_cu, hipStream_t st) {
-    const FastWorkspace w = carve(ws, fast_shape(tb, cd), n_groups);
+                       void *ws, int n_groups, int n_slices, int n_cu, bool narrow, hipStream_t st) {
+    const FastWorkspace w = carve(ws, fast_shape(tb, cd, narrow), n_groups);
+    if (narrow) launch_plan_narrow(tb, cd, out, ws, n_groups, n_cu, st);
     const int full_row = fast_row_len(tb.L);
     const size_t small = exact_small_bytes(cd.S_max);
     // Wavefronts per CU of the first launch (its registers allow five per SIMD; 16 to 24 per CU
@@ -553,14 +556,14 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
     auto launch = [&](auto odd_t) {
         constexpr bool odd = decltype(odd_t)::value;
         hipLaunchKernelGGL(k2_exact<odd>, dim3(n_waves), dim3(64), small + size_t(entries) * 16, st, tb, cd, out, n_passes,
-                           w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg, per_group, u8_off,
+                           w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.tight, w.lo_tab, lo_p, w.arg, per_group, u8_off,
                            full_row, entries);
         if (entries < full_row)
             hipLaunchKernelGGL(k2_exact_rows<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 16, st,
-                               tb, cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p,
+                               tb, cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.tight, w.lo_tab, lo_p,
                                w.arg, per_group, u8_off, full_row, full_row);
         hipLaunchKernelGGL(k2_exact_wide<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 32, st, tb,
-                           cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.lo_tab, lo_p, w.arg,
+                           cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.tight, w.lo_tab, lo_p, w.arg,
                            per_group, u8_off, full_row, full_row);
     };
     if (tb.odd_degrees()) launch(std::true_type());

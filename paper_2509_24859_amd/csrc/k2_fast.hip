@@ -123,7 +123,7 @@ constexpr uint16_t kBadSlot = 0xFFFFu;
 int band_threads(int S_max) { return S_max <= 64 ? 256 : (S_max <= 128 ? 128 : 64); }
 
 __global__ __launch_bounds__(256) void k2_band(TablesDev tb, CandDev cd, int *counts, int32_t *live_list,
-                                               uint32_t *dead_list, uint32_t *bands, int types_in_lds,
+                                               uint32_t *dead_list, uint32_t *bands, int32_t *wide_list, int types_in_lds,
                                                const uint16_t *lo_tab, const uint16_t *hi_tab, int idx_pitch) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int L = tb.L, S_max = cd.S_max, C = cd.C;
@@ -213,6 +213,7 @@ __global__ __launch_bounds__(256) void k2_band(TablesDev tb, CandDev cd, int *co
     }
     // backward chain: B[s] = smallest cut from which stage s can reach B[s+1]; B[s] takes the place of
     // the slot code of stage s, which is no longer needed
+    int cells = 0;
     if (status == HARP_CAND_OK && feasible) {
         int B = L;
         slots[S * pitch + cl] = (uint16_t)L;
@@ -224,6 +225,7 @@ __global__ __launch_bounds__(256) void k2_band(TablesDev tb, CandDev cd, int *co
             const int hi = ftile[s * pitch + cl];
             if (hi < B || (s == 0 && B != 0)) { feasible = false; break; }
             slots[s * pitch + cl] = (uint16_t)B;
+            cells += hi - B + 1;
         }
     }
     if (status == HARP_CAND_OK && !feasible) status = HARP_CAND_INFEASIBLE;
@@ -242,7 +244,16 @@ __global__ __launch_bounds__(256) void k2_band(TablesDev tb, CandDev cd, int *co
         base_live = __shfl(base_live, leader, 64);
         base_dead = __shfl(base_dead, leader, 64);
         const unsigned long long below = (1ull << lane) - 1ull;
-        if (alive) live_list[base_live + __popcll(live_m & below)] = c;
+        // wide bands, which the exact search narrows under a cap
+        const bool wide = wide_list != nullptr && alive && cells > kWideCells * S;
+        const unsigned long long wide_m = __ballot(wide);
+        if (wide_m != 0) {
+            int base_wide = 0;
+            if (lane == leader) base_wide = atomicAdd(&counts[kWideBands], __popcll(wide_m));
+            base_wide = __shfl(base_wide, leader, 64);
+            if (wide) wide_list[base_wide + __popcll(wide_m & below)] = c;
+        }
+        if (alive) live_list[base_live + __popcll(live_m & below)] = wide ? int32_t(uint32_t(c) | kWideFlag) : c;
         else if (mine) dead_list[base_dead + __popcll(dead_m & below)] = uint32_t(c) | (uint32_t(status) << kDeadStatusShift);
     }
     // the bands of the workgroup's candidates leave LDS as one contiguous run of rows (rows of
@@ -351,7 +362,7 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
         wave_sync();
         const int n = items.next(wave_id);
         if (n < 0) break;
-        const int c = uniform(fa.wide_pass ? int(dead_list[n_dead + n]) : live_list[n]);
+        const int c = uniform(fa.wide_pass ? int(dead_list[n_dead + n]) : listed(live_list[n]));
         const int S = uniform(cd.cand_S[c]);
         wave_sync();              // the previous candidate's tail has finished with LDS
         {
@@ -715,8 +726,8 @@ FastLaunch fast_launch_shape(int L, int S_max) {
 
 }  // namespace
 
-size_t plan_fast_ws_bytes(const TablesDev &tb, int S_max, int C, int n_slices) {
-    const FastShape f{tb.L, S_max, C, tb.M, tb.T, tb.n_tp};
+size_t plan_fast_ws_bytes(const TablesDev &tb, int S_max, int C, int n_slices, bool narrow) {
+    const FastShape f{tb.L, S_max, C, tb.M, tb.T, tb.n_tp, narrow};
     return carve(nullptr, f, n_slices).total;
 }
 
@@ -754,8 +765,8 @@ void launch_plan_index(const TablesDev &tb, int S_max, uint16_t *index, hipStrea
 // Pre-pass shared by every 32-bit planner entry point: clears the counters, checks the slot lists,
 // computes the reachability bands, compacts the live and dead lists, and writes the feasibility
 // index.
-void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n_slices, hipStream_t st) {
-    const FastWorkspace w = carve(ws, fast_shape(tb, cd), n_slices);
+void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n_slices, bool narrow, hipStream_t st) {
+    const FastWorkspace w = carve(ws, fast_shape(tb, cd, narrow), n_slices);
     hipLaunchKernelGGL(k2_clear_count, dim3(1), dim3(256), 0, st, w.counts);
     const long long idx_rows = (long long)lo_n_max(tb.L, cd.S_max, tb.M) * tb.T * tb.n_tp;
     const int idx_pitch = int(lo_pitch(tb.L));
@@ -764,15 +775,16 @@ void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n
     const int bt = band_threads(cd.S_max);
     const size_t band_lds = size_t(cd.S_max + 1) * (bt + 2) * 2 * 2 + (types_in_lds ? size_t(tb.G) * 8 : 0);
     hipLaunchKernelGGL(k2_band, dim3((cd.C + bt - 1) / bt), dim3(bt), band_lds, st, tb, cd, w.counts,
-                       w.live_list, w.dead_list, w.bands, types_in_lds, w.lo_tab,
+                       w.live_list, w.dead_list, w.bands, w.wide_list, types_in_lds, w.lo_tab,
                        w.lo_tab + idx_rows * idx_pitch, idx_pitch);
 }
 
-// n_slices: back-pointer slices in the workspace; k2_fast runs with at most that many wavefronts.
+// n_slices: back-pointer slices in the workspace; k2_fast runs with at most that many wavefronts.  narrow: the
+// exact search follows, list the candidates with wide bands.
 void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &out, void *ws,
-                      int n_slices, int n_cu, unsigned long long *work, hipStream_t st) {
-    const FastWorkspace w = carve(ws, fast_shape(tb, cd), n_slices);
-    launch_plan_prepass(tb, cd, ws, n_slices, st);
+                      int n_slices, int n_cu, bool narrow, unsigned long long *work, hipStream_t st) {
+    const FastWorkspace w = carve(ws, fast_shape(tb, cd, narrow), n_slices);
+    launch_plan_prepass(tb, cd, ws, n_slices, narrow, st);
     const FastLaunch shape = fast_launch_shape(tb.L, cd.S_max);
     FastArgs fa;
     fa.tickets = w.tickets;

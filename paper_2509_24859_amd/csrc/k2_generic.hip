@@ -899,8 +899,8 @@ size_t plan_generic_h1f1b_ws_per_group(int L, int S_max) {
 void launch_plan_generic_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_max, const PlansDev &out,
                                int32_t *warmup, void *ws, int n_groups, bool banded, hipStream_t st) {
     if (banded) {
-        const fastdp::FastWorkspace w = fastdp::carve(ws, fastdp::fast_shape(tb, cd), 0);
-        launch_plan_prepass(tb, cd, ws, 0, st);
+        const fastdp::FastWorkspace w = fastdp::carve(ws, fastdp::fast_shape(tb, cd, false), 0);
+        launch_plan_prepass(tb, cd, ws, 0, false, st);
         const long long idx_rows = (long long)fastdp::lo_n_max(tb.L, cd.S_max, tb.M) * tb.T * tb.n_tp;
         const int idx_pitch = int(fastdp::lo_pitch(tb.L));
         hipLaunchKernelGGL(k2_banded_h1f1b, dim3(n_groups), dim3(kBandedThreads), 0, st, tb, cd, t_max, out, warmup,
@@ -926,8 +926,8 @@ void launch_plan_generic(const TablesDev &tb, const CandDev &cd, const PlansDev 
                            static_cast<unsigned char *>(ws), plan_generic_ws_per_group(tb.L, cd.S_max));
         return;
     }
-    const fastdp::FastWorkspace w = fastdp::carve(ws, fastdp::fast_shape(tb, cd), 0);
-    launch_plan_prepass(tb, cd, ws, 0, st);
+    const fastdp::FastWorkspace w = fastdp::carve(ws, fastdp::fast_shape(tb, cd, false), 0);
+    launch_plan_prepass(tb, cd, ws, 0, false, st);
     hipLaunchKernelGGL(k2_banded, dim3(n_groups), dim3(kBandedThreads), banded_lds_bytes(tb.L), st, tb, cd, out,
                        w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab, int(fastdp::lo_pitch(tb.L)),
                        static_cast<unsigned char *>(ws) + w.total, plan_generic_ws_per_group(tb.L, cd.S_max));
@@ -936,8 +936,8 @@ void launch_plan_generic(const TablesDev &tb, const CandDev &cd, const PlansDev 
 void launch_plan_generic_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &out, int32_t *n_passes,
                                void *ws, int n_groups, bool banded, hipStream_t st) {
     if (banded) {
-        const fastdp::FastWorkspace w = fastdp::carve(ws, fastdp::fast_shape(tb, cd), 0);
-        launch_plan_prepass(tb, cd, ws, 0, st);
+        const fastdp::FastWorkspace w = fastdp::carve(ws, fastdp::fast_shape(tb, cd, false), 0);
+        launch_plan_prepass(tb, cd, ws, 0, false, st);
         hipLaunchKernelGGL(k2_banded_exact, dim3(n_groups), dim3(kBandedThreads), banded_lds_bytes(tb.L), st, tb, cd,
                            out, n_passes, w.counts, w.live_list, w.dead_list, w.bands, w.lo_tab,
                            int(fastdp::lo_pitch(tb.L)), static_cast<unsigned char *>(ws) + w.total,

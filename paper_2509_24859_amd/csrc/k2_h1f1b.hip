@@ -458,8 +458,8 @@ size_t h1f1b_lds_bytes(int L, int S_max, size_t entry) {
 // that many).
 void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_max, const PlansDev &out,
                        int32_t *warmup, void *ws, int n_groups, int n_slices, int n_cu, hipStream_t st) {
-    const FastWorkspace w = carve(ws, fast_shape(tb, cd), n_groups);
-    launch_plan_prepass(tb, cd, ws, n_groups, st);
+    const FastWorkspace w = carve(ws, fast_shape(tb, cd, false), n_groups);
+    launch_plan_prepass(tb, cd, ws, n_groups, false, st);
     const int row_len = h1f1b_row_len(tb.L);
     const int idx_pitch = int(lo_pitch(tb.L));
     const uint16_t *hi_tab = w.lo_tab + (long long)lo_n_max(tb.L, cd.S_max, tb.M) * tb.T * tb.n_tp * idx_pitch;

@@ -258,3 +258,36 @@ def test_exact_full_stress_batch_properties(harp, ctx):
     assert (ob == got.bottleneck[idx]).all() and (ot == got.iter_time[idx]).all() and (ost == 0).all()
     # the min-max plan is one of the partitions the sweep considers: strictly better somewhere
     assert (got.iter_time[ok] < minmax.iter_time[ok]).any()
+
+
+@pytest.mark.parametrize("L,degrees,link,memory", [
+    (127, (1, 2, 4), 400, 4.0),              # one operator short of narrowed bands
+    (128, (1, 2, 4), 400, 4.0),
+    (144, (1, 3), 400, 6.0),                 # rows of a whole number of sixteens and one: windows end with the row
+    (159, (1, 2, 4, 8), 4, 4.0),             # slow links decide: few cuts are allowed, chains step back
+    (201, (1, 2), 1, 2.5),
+    (330, (1, 2, 4), 40, 2.2),               # tighter memory
+])
+def test_exact_on_narrowed_bands(harp, ctx, L, degrees, link, memory):
+    """Wide memory bands are narrowed under the highest cap of the walk: same plans and passes as the int64
+    kernels on the memory bands, and as the oracle for some of them."""
+    rng = np.random.default_rng(L)
+    G, ndev = 4, (8, 6, 8, 3)
+    bw = rng.integers(link, 9 * link, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 9000
+    fwd = np.maximum(1, np.rint(np.exp(6 + 0.6 * rng.standard_normal((2, L))))).astype(np.int64)
+    p = simple_problem(np.zeros(L), M=24, T=2, G=G, ndev=ndev, tp=degrees, gtype=[g % 2 for g in range(G)], fwd=fwd,
+                       bwd=2 * fwd, act=rng.integers(8, 65, size=L) * 1000, params=2000 * fwd[0],
+                       stash=rng.integers(8, 65, size=L) * 4000, bw=bw)
+    p.type_mem_bytes[:] = int(memory * (p.param_bytes.sum() + 3 * p.stash_bytes.sum()) / sum(ndev))
+    cands = W.make_candidates(p, L, 78, 4, 11, 0, 200)
+    got, passes, _ = harp.plan_exact(ctx, p, cands)
+    want, want_passes, _ = harp.plan_exact(ctx, p, cands, harp.PATH_GENERIC)
+    assert_plans_equal(got, want, "narrowed")
+    assert (passes == want_passes).all() and (want.status == oracle.OK).any()
+    if L <= 144:                             # the oracle tries every cap
+        ok = np.nonzero(want.status == oracle.OK)[0][:2]
+        full = oracle_plan_exact_threaded(oracle.build_tables(p), cands.take(ok))
+        for field in ("splits", "bottleneck", "iter_time"):
+            assert (getattr(got, field)[ok] == getattr(full, field)).all(), field
