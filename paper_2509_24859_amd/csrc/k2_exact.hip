@@ -129,6 +129,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
     uint8_t *arg8 = reinterpret_cast<uint8_t *>(arg) + arg_u8_off;     // the slice's one-byte entries
     const int n_dead = counts[1];
     const int n_items = kWide ? counts[2] : kMode == 2 ? counts[10] : counts[0];
+    if (!kBandRows && int(blockIdx.x) >= n_items) return;      // mostly nothing is queued: no ticket to draw (25 us)
     const int64_t m_cap = tb.M;
 
     // candidates differ widely in passes, so workgroups draw them from shared counters

@@ -120,6 +120,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
     const int n_items = kWide ? counts[2] : kMode == 2 ? counts[10] : counts[0];
     int *next_item = counts + (kWide ? 7 : 11);
     Draw items(tickets, kTicketH1f1b, n_items, int(gridDim.x));
+    if (!kBandRows && int(blockIdx.x) >= n_items) return;      // mostly nothing is queued: no ticket to draw (25 us)
     const int64_t m_cap = tb.M;
     const int64_t *PP = tb.PP(), *PS = tb.PS();
 
