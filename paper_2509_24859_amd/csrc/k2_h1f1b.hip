@@ -44,14 +44,27 @@ constexpr int kTail = 4;     // spare entries behind a row: a group of four may 
 template <typename SumT> struct H1Traits;
 template <> struct H1Traits<uint32_t> {
     static constexpr uint32_t inf = 0x80000000u;
-    struct alignas(8) Entry { uint32_t h, nn; };
+    struct alignas(8) Entry { uint32_t h; float nn; };
 };
 template <> struct H1Traits<uint64_t> {
     static constexpr uint64_t inf = uint64_t(1) << 62;
-    struct alignas(16) Entry { uint64_t h; uint32_t nn; uint32_t unused; };
+    struct alignas(16) Entry { uint64_t h; float nn; uint32_t unused; };
 };
 
-struct alignas(16) MemPair { int64_t pp, ps; };
+// The memory test of a transition, eq. mem_cons, is a 64-bit sum with a 64 x 32 multiply, half of what a
+// transition costs in 64-bit integers.  It runs in float on running sums rounded to float (counts, at most
+// 3 S, are exact in float): the need comes out within a bound E of the true one, so a need of at most
+// cap - E fits and one above cap + E does not, and only a cell with a transition in between that would have been
+// taken is worked again in 64 bits, on the sums in global memory.  512 operators, 65,536 candidates, loose
+// memory: 18.1 -> 14.1 ms, 160 operators 1.60 -> 1.47 (with room for six wavefronts per SIMD: a cut takes 28
+// bytes of LDS instead of 36).  With u = 2^-24, P and Q the whole sums of
+// parameter and stash bytes and n the largest count: rounding two sums (sum_f), 6 u P and 6 u n Q; the
+// differences, u P and u n Q; the fused multiply-add, u (P + n Q); the cap, u cap.  E = 16 u (P + n Q) + 4 u cap.
+struct alignas(8) MemPair { float pp, ps; };
+// 0 <= v < 2^63 as a float, off by less than 3 u v: the halves (either is rounded to 24 bits) and their sum
+__device__ __forceinline__ float sum_f(int64_t v) {
+    return fmaf(float(uint32_t(uint64_t(v) >> 32)), 4294967296.f, float(uint32_t(v)));
+}
 
 // c <= cap, so the quotient of eq. dp_ni is 0, 1 or 2 and needs no division.
 __device__ __forceinline__ uint32_t h1f1b_delta(uint32_t c, int64_t cap) {
@@ -126,8 +139,8 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
 
     // the running sums of parameter and stash bytes are the same for every candidate
     if (!kBandRows) {
-        for (int j = tid; j <= L; j += nthreads) mem0[j] = MemPair{PP[j], PS[j]};
-        for (int j = L + 1 + tid; j < row_len; j += nthreads) mem0[j] = MemPair{0, 0};
+        for (int j = tid; j <= L; j += nthreads) mem0[j] = MemPair{sum_f(PP[j]), sum_f(PS[j])};
+        for (int j = L + 1 + tid; j < row_len; j += nthreads) mem0[j] = MemPair{0.f, 0.f};
         for (int j = L + 1 + tid; j < row_len; j += nthreads) { prow0[j] = 0; prow1[j] = 0; }
     }
 
@@ -178,6 +191,8 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             for (int s = S + tid; s < S_max; s += nthreads) df[s] = -1;
             for (int s = tid; s <= S; s += nthreads) band[s] = bands[int64_t(c) * (S_max + 1) + s];
         }
+        const int64_t most_n = m_cap < 3 * int64_t(S) ? m_cap : 3 * int64_t(S);
+        const float need_err = (float(PP[L]) + float(most_n) * float(PS[L])) * (16.f / 16777216.f);
         // stored sums stay this small, so that adding an admissible stage time cannot reach infinity
         const uint64_t limit = kWide ? uint64_t(kInfSum) - 1 : uint64_t(kInfSum) - 1 - tcap;
         __syncthreads();          // slot constants and bands are in LDS
@@ -205,7 +220,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
         {
             const int il0 = (S == 1) ? 0 : band_lo((uint32_t)uniform((int)band[S - 1]));
             Entry *row_S = rows0 - (kBandRows ? L : 0);
-            if (tid == 0) { row_S[L].h = 0; row_S[L].nn = 1; }
+            if (tid == 0) { row_S[L].h = 0; row_S[L].nn = 1.f; }
             if (tid >= 1 && tid <= kTail) row_S[L + tid].h = kInfSum;
             const uint32_t *p32 = tb.P32 + (uint32_t)uniform((int)sc[S - 1].p_row);
             uint32_t *pr = prow0 - (kBandRows ? il0 : 0);
@@ -213,7 +228,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             if (kBandRows) {
                 MemPair *mm = mem0 - il0;
                 for (int x = il0 + tid; x <= L + kTail - 1; x += nthreads)
-                    mm[x] = x <= L ? MemPair{PP[x], PS[x]} : MemPair{0, 0};
+                    mm[x] = x <= L ? MemPair{sum_f(PP[x]), sum_f(PS[x])} : MemPair{0.f, 0.f};
             }
         }
         lds_barrier();
@@ -269,6 +284,8 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             const uint32_t rsv = (uint32_t)uniform((int)sc[slot].cm_row_shift);
             const TpDiv div = tp_div<kOdd>(tb, rsv >> 27);
             const int64_t capm = uniform64(sc[slot].cap);
+            const float cap_f = float(capm), err = need_err + cap_f * (4.f / 16777216.f);
+            const float fits_up_to = cap_f - err, none_above = cap_f + err;
             const uint16_t *hi_row = hi_tab + (uint32_t)uniform((int)hi_off[slot]);
             // rows of this slot start at its lowest cell il, the row of continuations at jl, the rows
             // staged for the slot in front at nl
@@ -293,9 +310,11 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                 const MemPair mi = mem[i];
                 const uint32_t xi = pr_cur[i];
                 SumT best = kInfSum;
-                uint32_t best_n = 0;
+                float best_n = 0.f;
                 int best_j = 0;
-                int j = (i + 1) > jl_f ? (i + 1) : jl_f;
+                bool unsure = false;
+                const int first = (i + 1) > jl_f ? (i + 1) : jl_f;
+                int j = first;
                 // end cuts beyond the classic count's reach cannot fit with a larger count either
                 const int reach = hi_row[i];
                 const int end = reach < jh_f ? reach : jh_f;
@@ -309,16 +328,29 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                         const Entry e = prev[j + u];
                         const MemPair mj = mem[j + u];
                         tj = tp_quot<kOdd>(pr_cur[j + u] + div.add - xi, div);
-                        const int64_t dpp = mj.pp - mi.pp, dps = mj.ps - mi.ps;
-                        const bool fits = dpp + int64_t(e.nn) * dps <= capm;
+                        const float need = fmaf(e.nn, mj.ps - mi.ps, mj.pp - mi.pp);
                         const SumT v = e.h + tj;
-                        const bool upd = fits & (tj <= tcap) & (v < best) & ((j + u) <= end);
+                        const bool upd = (need <= none_above) & (tj <= tcap) & (v < best) & ((j + u) <= end);
+                        unsure = unsure | (upd & !(need <= fits_up_to));
                         best = upd ? v : best;
                         best_n = upd ? e.nn : best_n;
                         best_j = upd ? (j + u) : best_j;
                     }
                     more = ((j + 4) <= end) & (tj <= tcap);
                     j += 4;
+                }
+                if (unsure) {                        // rare: the cell again, in 64 bits
+                    best = kInfSum;
+                    best_n = 0.f;
+                    best_j = 0;
+                    for (j = first; j <= end; ++j) {
+                        const Entry e = prev[j];
+                        const uint32_t time = tp_quot<kOdd>(pr_cur[j] + div.add - xi, div);
+                        if (time > tcap) break;
+                        const SumT v = e.h + time;
+                        const int64_t dpp = PP[j] - PP[i], dps = PS[j] - PS[i];
+                        if (v < best && dpp + int64_t(e.nn) * dps <= capm) { best = v; best_n = e.nn; best_j = j; }
+                    }
                 }
                 arg[slot * arg_pitch + i] = (uint16_t)best_j;
                 if (stage_next) {
@@ -339,8 +371,8 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                             new_hi = hi_r > new_hi ? hi_r : new_hi;
                         }
                     }
-                    const uint32_t nn = h1f1b_delta(cf, cap64) + best_n;
-                    next[i].nn = nn < uint32_t(m_cap) ? nn : uint32_t(m_cap);
+                    const uint32_t nn = h1f1b_delta(cf, cap64) + uint32_t(best_n);
+                    next[i].nn = float(nn < uint32_t(m_cap) ? nn : uint32_t(m_cap));
                 } else {
                     scal[0] = uint64_t(best);
                 }
@@ -352,7 +384,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                 for (int x = xn + nthreads; x <= ih; x += nthreads) pr_next[x] = p32_n[x];
                 if (kBandRows) {
                     for (int x = xn; x <= ih + kTail - 1; x += nthreads)
-                        mem_next[x] = x <= L ? MemPair{PP[x], PS[x]} : MemPair{0, 0};
+                        mem_next[x] = x <= L ? MemPair{sum_f(PP[x]), sum_f(PS[x])} : MemPair{0.f, 0.f};
                 }
             }
             if (end_of_slot(slot, new_lo, new_hi)) break;
@@ -439,7 +471,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
         h1f1b_body<SUM, MODE, kOdd>(tb, cd, t_max, out, warmup, counts, tickets, live_list, dead_list, bands, hi_tab, idx_pitch, \
                               arg_base, arg_per_group, row_len, arg_pitch);                                        \
     }
-HARP_H1F1B_KERNEL(k2_h1f1b, __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5, 5))), uint32_t, 1)
+HARP_H1F1B_KERNEL(k2_h1f1b, __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 6))), uint32_t, 1)
 HARP_H1F1B_KERNEL(k2_h1f1b_rows, __launch_bounds__(kFastThreads) __attribute__((amdgpu_waves_per_eu(8, 8))), uint32_t, 2)
 HARP_H1F1B_KERNEL(k2_h1f1b_wide, __launch_bounds__(kFastThreads), uint64_t, 0)
 #undef HARP_H1F1B_KERNEL
@@ -467,10 +499,10 @@ void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_
     const size_t per_group = fast_arg_per_group(tb.L, cd.S_max);
     const int arg_pitch = fast_row_len(tb.L);
     // Wavefronts per CU of the first launch and the row entries their LDS share leaves: as many
-    // wavefronts as hold rows for the whole sequence, between 14 and 24 (measured on the 512-operator
-    // workload, where such rows would leave 7: 10 per CU 8.9 ms, 12 7.7, 14 7.6, 16 7.9, 20 10.4 - the
-    // smaller the share, the more candidates leave for the second launch; on the 160-operator one,
-    // where 22 fit: 16 per CU 2.2 ms, 20 2.0).
+    // wavefronts as hold rows for the whole sequence, between 14 and 24 (six per SIMD, what the registers
+    // allow; fewer hide less of the latency: 160 operators, five per SIMD 1.61 ms, six 1.47, seven 1.54 with
+    // spills).  The smaller the share, the more candidates leave for the second launch: 300 operators, 14 per
+    // CU 3.7 ms, 17 3.7, 20 4.9; 512 operators, tight memory 1.90, 1.88, 1.92, loose memory 14.1 for all.
     const size_t small = h1f1b_small_bytes(cd.S_max);
     int per_cu = int((size_t(160) << 10) / (small + size_t(row_len) * h1f1b_cut_bytes(8) + 128));
     per_cu = per_cu < 14 ? 14 : (per_cu > 24 ? 24 : per_cu);

@@ -409,3 +409,37 @@ def test_sweep_of_candidates_at_its_edges(harp, ctx, case):
             assert (getattr(got, name) == getattr(want, name)).all(), (name, limit)
         planned += int((want.status == 0).sum())
     assert planned > 0
+
+
+@pytest.mark.parametrize("scale", [1, 10**6, 10**12], ids=["bytes", "MB", "TB"])
+def test_memory_at_the_byte(harp, ctx, scale):
+    """Device memory of exactly what the tightest stage of a plan needs, and of a byte less and more: needs the
+    float test of the 32-bit kernel cannot tell from the limit."""
+    rng = np.random.default_rng(11)
+    L, G, M = 90, 3, 12
+    fwd = rng.integers(1, 900, size=(1, L))
+    p = simple_problem(np.zeros(L), M=M, G=G, ndev=(4, 4, 4), tp=(1,), fwd=fwd, bwd=2 * fwd, act=rng.integers(1, 300, size=L),
+                       params=rng.integers(1, 900, size=L) * scale + rng.integers(0, 9, size=L),
+                       stash=rng.integers(1, 300, size=L) * scale + rng.integers(0, 9, size=L), bw=[[90, 7, 5], [7, 90, 3], [5, 3, 90]])
+    cands = W.make_candidates(p, 5, 78, 5, 9, 0, 24)
+    p.type_mem_bytes[:] = 1 << 61
+    mm = oracle.plan_batch(oracle.build_tables(p), cands)
+    assert (mm.status == oracle.OK).all()
+    caps = mm.bottleneck + mm.bottleneck // 4
+    plan = oracle_plan_h1f1b_threaded(oracle.build_tables(p), cands, caps)
+    PP, PS = (np.concatenate([[0], np.cumsum(a)]) for a in (p.param_bytes, p.stash_bytes))
+    changed = 0
+    for c in range(0, cands.C, 3):
+        cut, n = plan.splits[c], plan.warmup[c]
+        S = int((cut >= 0).sum()) - 1
+        need = max(int(PP[cut[s + 1]] - PP[cut[s]] + int(n[s]) * (PS[cut[s + 1]] - PS[cut[s]])) for s in range(S))
+        plans = []
+        for mem in (need - 1, need, need + 1):
+            p.type_mem_bytes[:] = mem
+            want = oracle_plan_h1f1b_threaded(oracle.build_tables(p), cands, caps)
+            got, _ = harp.plan_h1f1b(ctx, p, cands, caps)
+            assert_plans_equal(got, want, "memory %d" % mem)
+            assert (got.warmup == want.warmup).all()
+            plans.append((want.status[c], want.splits[c].tolist()))
+        changed += plans[0] != plans[1]
+    assert changed > 0
