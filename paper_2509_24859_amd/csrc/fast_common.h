@@ -47,6 +47,17 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
+// A kernel argument in scalar registers of its own.  Arguments come in loads of up to sixteen registers, and where
+// scalars run out such a load is kept, and fetched back, as a whole: sixteen moves from a vector register's lanes for
+// one pointer (k2_fast: one stage in eight instructions).
+template <typename T>
+__device__ __forceinline__ T own_scalar(T v) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+    T own;
+    if constexpr (sizeof(T) == 8) asm("s_mov_b64 %0, %1" : "=s"(own) : "s"(v));
+    else asm("s_mov_b32 %0, %1" : "=s"(own) : "s"(v));
+    return own;
+}
 template <typename T>
 __device__ __forceinline__ const T *uniform_ptr(const T *p) {
     return reinterpret_cast<const T *>(uniform64(reinterpret_cast<int64_t>(p)));
@@ -78,6 +89,16 @@ __device__ __forceinline__ TpDiv tp_div(const TablesDev &tb, uint32_t code) {
 template <bool kOdd>
 __device__ __forceinline__ uint32_t tp_quot(uint32_t x, const TpDiv &d) {       // x: difference + d.add
     return kOdd ? __umulhi(x, d.mul) >> d.shift : x >> d.shift;
+}
+template <bool kOdd>
+__device__ __forceinline__ uint32_t tp_times(const TablesDev &tb, uint32_t x, uint32_t code) {   // x: below 2^32 / degree
+    return kOdd ? x * uint32_t(tb.tp[code]) : x << code;
+}
+// The largest difference of a fused row whose time is at most t.
+template <bool kOdd>
+__device__ __forceinline__ uint32_t cap_reach(const TablesDev &tb, uint32_t t, uint32_t code) {
+    const uint64_t far = kOdd ? uint64_t(t) * uint32_t(tb.tp[code]) : uint64_t(t) << code;
+    return far < 0xFFFFFFFFull ? uint32_t(far) : 0xFFFFFFFFu;
 }
 template <bool kOdd>
 __device__ __forceinline__ uint32_t tp_code(const TablesDev &tb, int k) {

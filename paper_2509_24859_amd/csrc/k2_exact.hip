@@ -35,7 +35,7 @@
 // a sum.  Candidates with U >= 2^31 (iterations of more than half an hour) are queued and redone
 // by the same kernel instantiated with 64-bit sums.
 //
-// Three launches.  k2_exact works a candidate per wavefront (64-thread workgroups, 20 per CU): a
+// Three launches.  k2_exact works a candidate per wavefront (64-thread workgroups, 24 per CU): a
 // DP row is 77 cuts wide on the 512-operator workload, so a 256-thread workgroup per candidate left
 // three wavefronts in four idle at every stage's barrier.  Its two LDS rows hold the cuts of one
 // stage only (row s starts at B[s], sized for the candidate's widest stage), and what is left of the
@@ -93,6 +93,23 @@ __host__ __device__ inline size_t exact_small_bytes(int S_max) {
 // per candidate (the launch has 64-thread workgroups), LDS rows that hold the cuts of one stage
 // (row s starts at B[s]); a candidate whose widest stage does not fit them is queued.  kMode 2: as
 // 0, on the candidates queued by 1.
+//
+// Key rows (wavefront per candidate).  D[j] + ceil((P[i] - P[j]) / tp) is floor((D[j] tp - P[j] + P[i] + tp - 1) / tp),
+// and the least of it over previous cuts can be taken inside the floor.  So a row entry holds the key
+// D[j] tp - P[j] of the stage that reads it instead of D[j]: a trip of four cuts is three minima, one quotient and
+// one update where each cut took a quotient, a sum and an update of its own, and the cap and memory limits are
+// looked at once per trip, at its lowest cut (both hold for all cuts above it).  Equal sums keep the lowest cut:
+// trips are taken downwards and a tie goes to the later one; inside the winning trip it is the lowest cut whose
+// key gives the best quotient.  Keys are 32 bits, so this is for candidates with U tp below kKeyLimit for every degree
+// tp (single passes of less than two minutes at degree 8): no finite key plus P[i] wraps, and kNoKey, an
+// infinite sum, never gives a quotient as low as U.  The others keep the sums.
+// 65,536 candidates of 160 operators, 16 to 32 stages, the whole call: 3.83 -> 3.68 ms with 5 wavefronts per SIMD, which
+// vector issue then no longer fills (69% of the rate; the wait for a trip's entries shows), 3.47 with 6, 3.50 with 7.
+constexpr int kExactWaves = 6;           // wavefronts per SIMD of k2_exact, registers held to that
+constexpr int64_t kKeyLimit = int64_t(1) << 30;
+constexpr int32_t kNoKey = INT32_MAX;
+__device__ __forceinline__ int32_t least(int32_t a, int32_t b) { return a < b ? a : b; }
+
 template <typename SumT, int kMode, bool kOdd>
 __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &cd, const PlansDev &out,
                                            int32_t *n_passes, int *counts, int *tickets,
@@ -131,6 +148,8 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
     const int n_items = kWide ? counts[2] : kMode == 2 ? counts[10] : counts[0];
     if (!kBandRows && int(blockIdx.x) >= n_items) return;      // mostly nothing is queued: no ticket to draw (25 us)
     const int64_t m_cap = tb.M;
+    const uint32_t *const P32 = own_scalar(tb.P32), *const CM = own_scalar(tb.CM);
+    const uint16_t *const lo_rows = own_scalar(lo_tab);
 
     // candidates differ widely in passes, so workgroups draw them from shared counters
     int *next_item = counts + (kWide ? 4 : 11);
@@ -163,6 +182,13 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             if (tid == 0) dead_list[n_dead + atomicAdd(&counts[2], 1)] = uint32_t(entry);
             continue;
         }
+        bool keyed = false;
+        if (kBandRows && !kWide) {
+            int tp_most = 1;
+            for (int q = 0; q < tb.n_tp; ++q) tp_most = tb.tp[q] > tp_most ? tb.tp[q] : tp_most;
+            keyed = uniform(limit * tp_most < kKeyLimit ? 1 : 0) != 0;
+        }
+        const uint32_t limit32 = uint32_t(limit);          // (keyed)
         {
             const int32_t *grp = cd.cand_group + int64_t(c) * S_max;
             const int32_t *tpv = cd.cand_tp + int64_t(c) * S_max;
@@ -237,16 +263,16 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             uint32_t cut_i = 0;
             int lo_i = 0;
             {
-                const uint32_t *p32 = tb.P32 + (uint32_t)uniform((int)sc[0].p_row);
-                const uint32_t *cm = tb.CM + ((uint32_t)uniform((int)sc[0].cm_row_shift) & kRowMask);
-                const uint16_t *lo0 = lo_tab + (uint32_t)uniform((int)lo_off[0]);
+                const uint32_t *p32 = P32 + (uint32_t)uniform((int)sc[0].p_row);
+                const uint32_t *cm = CM + ((uint32_t)uniform((int)sc[0].cm_row_shift) & kRowMask);
+                const uint16_t *lo0 = lo_rows + (uint32_t)uniform((int)lo_off[0]);
                 const uint32_t b1 = (uint32_t)uniform((int)band[1]);
                 Pair *rows = buf0;              // row 0 starts at cut 0 = B[0]
                 for (int j = tid; j <= band_hi(b1); j += nthreads) rows[j].p = p32[j];
                 if (band_lo(b1) + tid <= band_hi(b1)) { cut_i = cm[band_lo(b1) + tid]; lo_i = lo0[band_lo(b1) + tid]; }
                 // below cut 0: never a predecessor; the time read there must stay small
                 if (tid < 3) { rows[-1 - tid].d = kInfSum; rows[-1 - tid].p = 0xFFFFFFFFu; }
-                if (tid == 0) rows[0].d = 0;
+                if (tid == 0) rows[0].d = keyed ? SumT(0u - p32[0]) : SumT(0);
             }
             lds_barrier();
 
@@ -275,13 +301,16 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 const int jl_f = kBandRows && fin_lo > jl ? fin_lo : jl;
                 const int jh_f = kBandRows && fin_hi < jh ? fin_hi : jh;
                 int new_lo = INT32_MAX, new_hi = -1;               // cells of row s + 1 with a finite sum (wavefront form)
-                const uint32_t *cm_s = tb.CM + (rs & kRowMask);
-                const uint16_t *lo_s = lo_tab + (uint32_t)uniform((int)lo_off[s]);
-                const uint16_t *lo_n_row = lo_tab + (uint32_t)uniform((int)lo_off[s + 1]);
+                const uint32_t *cm_s = CM + (rs & kRowMask);
+                const uint16_t *lo_s = lo_rows + (uint32_t)uniform((int)lo_off[s]);
+                const uint16_t *lo_n_row = lo_rows + (uint32_t)uniform((int)lo_off[s + 1]);
                 const Pair *prev = (cur ? buf1 : buf0) - (kBandRows ? jl : 0);
                 Pair *next = (cur ? buf0 : buf1) - (kBandRows ? il : 0);
-                const uint32_t *p32_n = tb.P32 + (uint32_t)uniform((int)sc[s + 1].p_row);
-                const uint32_t *cm_n = tb.CM + ((uint32_t)uniform((int)sc[s + 1].cm_row_shift) & kRowMask);
+                const uint32_t *p32_n = P32 + (uint32_t)uniform((int)sc[s + 1].p_row);
+                const uint32_t rs_n = (uint32_t)uniform((int)sc[s + 1].cm_row_shift);
+                const uint32_t code_n = rs_n >> 27;
+                const uint32_t *cm_n = CM + (rs_n & kRowMask);
+                const uint32_t far = cap_reach<kOdd>(tb, tcap, rs >> 27);
                 const bool next_has_cut = s + 2 < S;
                 const uint32_t a_word = kBandRows ? (uint32_t)uniform((int)aoff[s]) : 0u;
                 const bool arg_in_lds = (a_word & kArgInLds) != 0;
@@ -355,18 +384,84 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                     }
                     return best >= kInfSum ? i - 1 : best_j;        // no previous cut: any value, a short one
                 };
+                // The same over key rows; writes the cell's entry as the next stage reads it.
+                auto cell_keys = [&](int i, uint32_t cut, int lo_idx, uint32_t p_next) -> int {
+                    const uint32_t pi = prev[i].p, xi = pi + div.add;
+                    const uint32_t target = pi > far ? pi - far : 0u;       // lowest cut under the cap: P[j] >= target
+                    int j = (i - 1) < jh_f ? (i - 1) : jh_f;
+                    j = j >= jl ? j : jl - 1;               // (jh_f is -1 where nothing is finite; reads start at j - 3)
+                    int lo = lo_idx > jl_f ? lo_idx : jl_f;
+                    lo = cut <= tcap ? lo : j + 1;
+                    uint32_t best = 0xFFFFFFFFu;
+                    int bt = j;
+                    int32_t k0, k1, k2;
+                    uint32_t p0, p1, p2;
+                    for (;;) {
+                        const Pair *pe = prev + (j - 3);
+                        const Pair e3 = pe[0], e2 = pe[1], e1 = pe[2], e0 = pe[3];
+                        k0 = int32_t(e0.d); k1 = int32_t(e1.d); k2 = int32_t(e2.d);
+                        p0 = e0.p; p1 = e1.p; p2 = e2.p;
+                        if (!((j - 3 >= lo) & (e3.p >= target))) break;
+                        const int32_t k = least(least(k0, k1), least(k2, int32_t(e3.d)));
+                        const uint32_t v = tp_quot<kOdd>(uint32_t(k) + xi, div);
+                        bt = v <= best ? j : bt;
+                        best = v <= best ? v : best;
+                        j -= 4;
+                    }
+                    // what is left of the range: at most three cuts, j downwards
+                    k0 = ((j >= lo) & (p0 >= target)) ? k0 : kNoKey;
+                    k1 = ((j - 1 >= lo) & (p1 >= target)) ? k1 : kNoKey;
+                    k2 = ((j - 2 >= lo) & (p2 >= target)) ? k2 : kNoKey;
+                    {
+                        const int32_t k = least(least(k0, k1), k2);
+                        const uint32_t v = tp_quot<kOdd>(uint32_t(k) + xi, div);
+                        const bool upd = (v <= best) & (k != kNoKey);
+                        bt = upd ? j : bt;
+                        best = upd ? v : best;
+                    }
+                    const uint64_t total = uint64_t(best) + 2ull * cut;
+                    const bool finite = total <= limit32;
+                    next[i] = Pair{finite ? SumT(tp_times<kOdd>(tb, uint32_t(total), code_n) - p_next) : SumT(kNoKey), p_next};
+                    const unsigned long long fm = __ballot(finite);
+                    if (fm == 0) return i - 1;
+                    {
+                        const int base = uniform(i - tid);
+                        const int lo_r = base + __ffsll((long long)fm) - 1, hi_r = base + 63 - __clzll((long long)fm);
+                        new_lo = lo_r < new_lo ? lo_r : new_lo;
+                        new_hi = hi_r > new_hi ? hi_r : new_hi;
+                    }
+                    // the lowest cut of the winning trip whose quotient is the best one
+                    const Pair *pw = prev + (bt - 3);
+                    const Pair w3 = pw[0], w2 = pw[1], w1 = pw[2];
+                    const int32_t most = int32_t(tp_times<kOdd>(tb, best, rs >> 27) - pi);      // quotient <= best
+                    int best_j = bt;
+                    best_j = ((int32_t(w1.d) <= most) & (bt - 1 >= lo) & (w1.p >= target)) ? bt - 1 : best_j;
+                    best_j = ((int32_t(w2.d) <= most) & (bt - 2 >= lo) & (w2.p >= target)) ? bt - 2 : best_j;
+                    best_j = ((int32_t(w3.d) <= most) & (bt - 3 >= lo) & (w3.p >= target)) ? bt - 3 : best_j;
+                    return finite ? best_j : i - 1;                 // no previous cut: any value, a short one
+                };
                 const int i0 = il + tid;
                 int first_j = 0;
-                if (i0 <= ih) first_j = cell(i0, cut_i, lo_i);
-                for (int i = i0 + nthreads; i <= ih; i += nthreads)
-                    put_arg(i, cell(i, cm_s[i], lo_s[i]));
+                if (kBandRows && !kWide && keyed) {
+                    // (the row and back-pointers of cells but the first are in place when the loop ends)
+                    if (i0 <= ih) first_j = cell_keys(i0, cut_i, lo_i, p_n);
+                    else if (jn <= top_n) next[jn].p = p_n;
+                    for (int i = i0 + nthreads; i <= ih; i += nthreads)
+                        put_arg(i, cell_keys(i, cm_s[i], lo_s[i], p32_n[i]));
+                    for (int j = jn + nthreads; j <= top_n; j += nthreads)
+                        if (j > ih) next[j].p = p32_n[j];
+                } else {
+                    if (i0 <= ih) first_j = cell(i0, cut_i, lo_i);
+                    for (int i = i0 + nthreads; i <= ih; i += nthreads)
+                        put_arg(i, cell(i, cm_s[i], lo_s[i]));
+                    if (jn <= top_n) next[jn].p = p_n;
+                    for (int j = jn + nthreads; j <= top_n; j += nthreads) next[j].p = p32_n[j];
+                }
                 if (tid < 3) {                                  // below the band of row s + 1
                     next[il - 1 - tid].d = kInfSum;
                     next[il - 1 - tid].p = 0xFFFFFFFFu;
                 }
 
-                if (jn <= top_n) next[jn].p = p_n;
-                for (int j = jn + nthreads; j <= top_n; j += nthreads) next[j].p = p32_n[j];
                 asm volatile("" : "+v"(cut_n));
                 cut_i = cut_n;
                 lo_i = lo_n;
@@ -385,9 +480,11 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 const TpDiv div = tp_div<kOdd>(tb, (uint32_t)uniform((int)sc[s].cm_row_shift) >> 27);
                 const uint32_t b0 = (uint32_t)uniform((int)band[s]);
                 const Pair *prev = (cur ? buf1 : buf0) - (kBandRows ? band_lo(b0) : 0);
-                const uint32_t xi = prev[L].p + div.add;
+                const uint32_t pi = prev[L].p, xi = pi + div.add;
+                const uint32_t far = cap_reach<kOdd>(tb, tcap, (uint32_t)uniform((int)sc[s].cm_row_shift) >> 27);
+                const uint32_t target = pi > far ? pi - far : 0u;
                 int hi = (L - 1) < band_hi(b0) ? (L - 1) : band_hi(b0);
-                const int lo_L = uniform((int)lo_tab[size_t((uint32_t)uniform((int)lo_off[s])) + L]);
+                const int lo_L = uniform((int)lo_rows[size_t((uint32_t)uniform((int)lo_off[s])) + L]);
                 int lo = lo_L > band_lo(b0) ? lo_L : band_lo(b0);
                 if (kBandRows && S > 1) {
                     hi = fin_hi < hi ? fin_hi : hi;
@@ -395,7 +492,13 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 }
                 unsigned long long best = kInfSum;
                 int best_j = INT32_MAX;
-                for (int j = lo + lane; j <= hi; j += 64) {
+                if (keyed) {
+                    for (int j = lo + lane; j <= hi; j += 64) {
+                        const Pair e = prev[j];
+                        const unsigned long long v = tp_quot<kOdd>(uint32_t(e.d) + xi, div);
+                        if ((e.p >= target) & (int32_t(e.d) != kNoKey) & (v < best)) { best = v; best_j = j; }
+                    }
+                } else for (int j = lo + lane; j <= hi; j += 64) {
                     const uint32_t tj = tp_quot<kOdd>(xi - prev[j].p, div);
                     const unsigned long long v = (unsigned long long)prev[j].d + tj;
                     if (tj <= tcap && v < best) { best = v; best_j = j; }   // j rises within a lane
@@ -447,9 +550,9 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                     const int j = trial[s], i = trial[s + 1];
                     const uint32_t rs = sc[s].cm_row_shift;
                     const TpDiv div = tp_div<kOdd>(tb, rs >> 27);
-                    const uint32_t *p = tb.P32 + sc[s].p_row;
+                    const uint32_t *p = P32 + sc[s].p_row;
                     const uint32_t t = tp_quot<kOdd>(p[i] + div.add - p[j], div);
-                    const uint32_t cu = s < S - 1 ? tb.CM[(rs & kRowMask) + uint32_t(i)] : 0u;
+                    const uint32_t cu = s < S - 1 ? CM[(rs & kRowMask) + uint32_t(i)] : 0u;
                     const uint32_t m = t > cu ? t : cu;
                     w = w > m ? w : m;
                 }
@@ -524,7 +627,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
         exact_body<SUM, MODE, kOdd>(tb, cd, out, n_passes, counts, tickets, live_list, dead_list, bands, tight, lo_tab, lo_pitch, \
                               arg_base, arg_per_group, arg_u8_off, row_len, lds_row_entries);                     \
     }
-HARP_EXACT_KERNEL(k2_exact, __launch_bounds__(64), uint32_t, 1)
+HARP_EXACT_KERNEL(k2_exact, __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kExactWaves, kExactWaves))), uint32_t, 1)
 HARP_EXACT_KERNEL(k2_exact_rows, __launch_bounds__(kFastThreads) __attribute__((amdgpu_waves_per_eu(8, 8))), uint32_t, 2)
 HARP_EXACT_KERNEL(k2_exact_wide, __launch_bounds__(kFastThreads), uint64_t, 0)
 #undef HARP_EXACT_KERNEL
@@ -540,10 +643,8 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
     if (narrow) launch_plan_narrow(tb, cd, out, ws, n_groups, n_cu, st);
     const int full_row = fast_row_len(tb.L);
     const size_t small = exact_small_bytes(cd.S_max);
-    // Wavefronts per CU of the first launch (its registers allow five per SIMD; 16 to 24 per CU
-    // measure the same, 28 and more are slower because more candidates leave for the second launch)
-    // and the row entries their LDS share leaves.
-    const int per_cu = 20;
+    // Wavefronts per CU of the first launch and the row entries their LDS share leaves.
+    const int per_cu = 4 * kExactWaves;
     size_t share = ((size_t(160) << 10) / per_cu - 128) & ~size_t(15);
     int entries = share > small + 2 * 8 * (kPad + 8) ? int((share - small) / 16) : kPad + 8;
     if (entries > full_row) entries = full_row;

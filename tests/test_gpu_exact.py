@@ -291,3 +291,36 @@ def test_exact_on_narrowed_bands(harp, ctx, L, degrees, link, memory):
         full = oracle_plan_exact_threaded(oracle.build_tables(p), cands.take(ok))
         for field in ("splits", "bottleneck", "iter_time"):
             assert (getattr(got, field)[ok] == getattr(full, field)).all(), field
+
+
+@pytest.mark.parametrize("L,degrees,time,spread,memory", [
+    (5, (1, 2, 4, 8), 40, 0, 50.0),          # equal operators: sums tie; windows shorter than a trip
+    (70, (1, 2, 4, 8), 40, 0, 50.0),         # rows of a wavefront and a few cells
+    (96, (1, 2, 8), 700000, 300000, 50.0),   # sums times 8 on both sides of 2^30: key rows and sums in one batch
+    (96, (1, 2, 8), 3000000, 9, 50.0),       # all above
+    (131, (1, 3, 6), 600000, 300000, 6.0),   # degrees that are no powers of two, both sides
+    (130, (1, 3), 50, 3, 3.0),               # memory ends the windows
+    (257, (1, 2, 4), 900, 800, 3.0),
+])
+def test_exact_key_rows(harp, ctx, L, degrees, time, spread, memory):
+    """Key rows (sum times degree less running time) return the plans and passes of the int64 kernels, whose
+    scan compares sums, also where many sums are equal."""
+    rng = np.random.default_rng(L + time)
+    G, ndev = 3, (8, 6, 9)
+    S_min, S_max = min(4, L - 1), min(9, L)
+    bw = rng.integers(20, 900, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 9000
+    fwd = time + rng.integers(0, spread + 1, size=(2, L))
+    p = simple_problem(np.zeros(L), M=24, T=2, G=G, ndev=ndev, tp=degrees, gtype=[g % 2 for g in range(G)], fwd=fwd,
+                       bwd=2 * fwd, act=rng.integers(1, 3, size=L) * 1000, params=np.full(L, 2000),
+                       stash=rng.integers(8, 65, size=L) * 4000, bw=bw)
+    p.type_mem_bytes[:] = int(memory * (p.param_bytes.sum() + 3 * p.stash_bytes.sum()) / sum(ndev))
+    cands = W.make_candidates(p, L, 78, S_min, S_max, 0, 160)
+    got, passes, _ = harp.plan_exact(ctx, p, cands)
+    want, want_passes, _ = harp.plan_exact(ctx, p, cands, harp.PATH_GENERIC)
+    assert_plans_equal(got, want, "key rows")
+    assert (passes == want_passes).all() and (want.status == oracle.OK).any()
+    if time == 700000:
+        sums = (want.iter_time - (p.M - 1) * want.bottleneck)[want.status == oracle.OK] * 8
+        assert (sums < 0.9 * 2 ** 30).any() and (sums > 1.1 * 2 ** 30).any()
