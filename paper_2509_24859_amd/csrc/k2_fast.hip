@@ -47,8 +47,8 @@
 // reads cuts below itself, so writing the new row over the old one never destroys a value that is
 // still needed, and the time row of the next stage replaces the current one once the stage is done
 // (its entries were requested from global memory before the stage's scans and wait in registers).
-// Previous cuts are scanned four per trip; a trip keeps the least of its four values and its own
-// position, and the lowest cut inside the winning trip is found once per cell afterwards.
+// Previous cuts are scanned in windows of four; a window keeps the least of its four values and its own
+// position, and the lowest cut inside the winning window is found once per cell afterwards.
 // The buffer is band-relative: the entry of cut j of stage s sits at offset j - B[s], and the buffer
 // is sized for the candidate's widest stage, not for L; a candidate whose widest stage does not fit
 // the wavefront's share of LDS is queued for a second pass with a share sized for L.
@@ -302,8 +302,8 @@ struct FastArgs {
 __host__ __device__ inline size_t fast_wave_small_bytes(int S_max) {
     return (size_t(S_max + 1) * 12 + size_t(S_max) * 4 + 15) & ~size_t(15);
 }
-// bytes of row entries for a stage that reads `span` cuts: kPad spare entries in front, so that the
-// group of four previous cuts ending at any cut of the stage can be read without clamping
+// bytes of row entries for a stage that reads `span` cuts: kPad spare entries behind them, so that the
+// window of four previous cuts that starts at any cut of the stage can be read without clamping
 __host__ __device__ inline size_t fast_row_bytes(int span) {
     return (size_t(span + kPad) * sizeof(Pair) + 15) & ~size_t(15);
 }
@@ -326,15 +326,20 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
     int32_t *cuts = reinterpret_cast<int32_t *>(aoff + (S_max + 1));                   // [S_max + 1]
     const int small_bytes = int(fast_wave_small_bytes(S_max));
     // row entries: entry of cut j of the stage whose lowest cut is `base` sits at rows0[j - base]
-    Pair *rows0 = reinterpret_cast<Pair *>(mine + small_bytes) + kPad;
+    Pair *rows0 = reinterpret_cast<Pair *>(mine + small_bytes);
     uint16_t *slice = reinterpret_cast<uint16_t *>(fa.arg_base + size_t(wave_id) * fa.arg_per_wave);
     uint8_t *slice8 = reinterpret_cast<uint8_t *>(slice) + fa.arg_u8_off;
     // first pass: the live list; second pass: the candidates the first one queued behind the dead list
     const int n_dead = counts[1];
     const int n_live = fa.wide_pass ? counts[8] : counts[0];
     Draw items(fa.tickets, fa.wide_pass ? kTicketFastWide : kTicketFast, n_live, n_waves);
-    const int m_cap = tb.M;
-    const int rows_per_n = tb.T * tb.n_tp;
+    const int m_cap = own_scalar(tb.M);
+    const int n_tp = own_scalar(tb.n_tp), G = own_scalar(tb.G);
+    const int rows_per_n = own_scalar(tb.T * tb.n_tp);
+    const uint32_t pitch32 = own_scalar(uint32_t(tb.pitch32)), lo_pitch = own_scalar(uint32_t(fa.lo_pitch));
+    const uint32_t shift_packed = own_scalar(fa.shift_packed);
+    const uint32_t *const p32 = own_scalar(tb.P32), *const cm = own_scalar(tb.CM);
+    const uint16_t *const lo_tab = own_scalar(fa.lo_tab);
     unsigned long long n_trans = 0, n_cells = 0, n_trips = 0, n_cands = 0;
 
     // scalars of one stage, from the packed slot word  g | k << 12 | type << 16
@@ -350,10 +355,11 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
         const int gn = int(wn & 0xFFFu);
         const int n = (S - s) < m_cap ? (S - s) : m_cap;
         Stage st;
-        st.p_row = tb.P32 + (int64_t(g) * tb.n_tp + k) * tb.pitch32;
-        st.cm_row = tb.CM + (int64_t(g) * tb.G + gn) * tb.pitch32;
-        st.lo = fa.lo_tab + (int64_t(n - 1) * rows_per_n + t * tb.n_tp + k) * fa.lo_pitch;
-        st.div = tp_div<kOdd>(tb, kOdd ? uint32_t(k) : (fa.shift_packed >> (4 * k)) & 15u);
+        // (fewer than 2^32 entries each: 65,535 rows of at most 4,112, and 256 MiB of index)
+        st.p_row = p32 + uint32_t(g * n_tp + k) * pitch32;
+        st.cm_row = cm + uint32_t(g * G + gn) * pitch32;
+        st.lo = lo_tab + uint32_t((n - 1) * rows_per_n + t * n_tp + k) * lo_pitch;
+        st.div = tp_div<kOdd>(tb, kOdd ? uint32_t(k) : (shift_packed >> (4 * k)) & 15u);
         return st;
     };
 
@@ -489,58 +495,67 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                         if (i2 <= top_n) { cut_n = nxt.cm_row[i2]; lo_n = nxt.lo[i2]; }
                     }
 
-                    // One DP cell: the previous cuts that fit are lo .. hi; four per trip, downwards.
-                    // A trip keeps the least of its four values; ties between trips go to the lower
+                    // One DP cell: the previous cuts that fit are lo .. hi, taken in windows of four, downwards.
+                    // The first window may reach beyond hi (those entries do not count), the last is pushed up
+                    // against lo: cuts seen twice do not matter to a minimum, so no ragged end is left over.
+                    // A window keeps the least of its four values; ties between windows go to the lower
                     // one.  Entries below a stop cannot match the best value (their stage time alone
-                    // exceeds it), so only the last entry of a trip decides whether the lane goes on.
+                    // exceeds it), so only the lowest entry of a window decides whether the lane goes on.
                     uint32_t best = kInf32;
                     int best_j = 0;
                     if (i <= ih) {
                         const int hi = (i - 1) < jh ? (i - 1) : jh;
                         const int lo = lo_c > jl ? lo_c : jl;
                         const uint32_t xi = rows[i].p + div.add;
-                        const uint32_t cut = cut_c;
-                        int bt = hi;
-                        int j = hi;
-                        while (j - 3 >= lo) {
-                            const Pair *pe = rows + (j - 3);
-                            const Pair e3 = pe[0], e2 = pe[1], e1 = pe[2], e0 = pe[3];
-                            const uint32_t t3 = tp_quot<kOdd>(xi - e3.p, div);
-                            const uint32_t v0 = umax3(e0.d, tp_quot<kOdd>(xi - e0.p, div), cut);
+                        const uint32_t cut = lo <= hi ? cut_c : kInf32;         // no previous cut fits
+                        int j = hi - 3 > lo ? hi - 3 : lo;
+                        j = j < hi ? j : hi;
+                        int bt = j;
+                        uint32_t t0;
+                        {
+                            const Pair *pe = rows + j;
+                            const Pair e0 = pe[0], e1 = pe[1], e2 = pe[2], e3 = pe[3];
+                            t0 = tp_quot<kOdd>(xi - e0.p, div);
+                            const uint32_t v0 = umax3(e0.d, t0, cut);
+                            uint32_t v1 = umax3(e1.d, tp_quot<kOdd>(xi - e1.p, div), cut);
+                            uint32_t v2 = umax3(e2.d, tp_quot<kOdd>(xi - e2.p, div), cut);
+                            uint32_t v3 = umax3(e3.d, tp_quot<kOdd>(xi - e3.p, div), cut);
+                            v1 = j + 1 <= hi ? v1 : kInf32;
+                            v2 = j + 2 <= hi ? v2 : kInf32;
+                            v3 = j + 3 <= hi ? v3 : kInf32;
+                            best = umin2(umin2(v0, v1), umin2(v2, v3));
+                            if (kCount) {
+                                n_trans += lo <= hi ? uint32_t(hi - j + 1) : 0u;
+                                n_trips += lo <= hi;
+                                ++n_cells;
+                            }
+                        }
+                        while ((j > lo) & (t0 <= best)) {
+                            if (kCount) { n_trans += uint32_t(j - lo < 4 ? j - lo : 4); ++n_trips; }
+                            j = j - 4 > lo ? j - 4 : lo;
+                            const Pair *pe = rows + j;
+                            const Pair e0 = pe[0], e1 = pe[1], e2 = pe[2], e3 = pe[3];
+                            t0 = tp_quot<kOdd>(xi - e0.p, div);
+                            const uint32_t v0 = umax3(e0.d, t0, cut);
                             const uint32_t v1 = umax3(e1.d, tp_quot<kOdd>(xi - e1.p, div), cut);
                             const uint32_t v2 = umax3(e2.d, tp_quot<kOdd>(xi - e2.p, div), cut);
-                            const uint32_t v3 = umax3(e3.d, t3, cut);
+                            const uint32_t v3 = umax3(e3.d, tp_quot<kOdd>(xi - e3.p, div), cut);
                             const uint32_t m = umin2(umin2(v0, v1), umin2(v2, v3));
                             const bool upd = m <= best;
                             best = upd ? m : best;
                             bt = upd ? j : bt;
-                            if (kCount) { n_trans += 4; ++n_trips; }
-                            j = t3 > best ? lo - 1 : j - 4;
                         }
-                        // what is left of the range: at most three cuts, j .. lo
+                        // the lowest cut of the winning window that attains the best value (one beyond hi never
+                        // is: an entry below it attains it too)
                         {
-                            const Pair *pe = rows + (j - 3);
-                            const Pair e2 = pe[1], e1 = pe[2], e0 = pe[3];
-                            const uint32_t v0 = j >= lo ? umax3(e0.d, tp_quot<kOdd>(xi - e0.p, div), cut) : kInf32;
-                            const uint32_t v1 = j - 1 >= lo ? umax3(e1.d, tp_quot<kOdd>(xi - e1.p, div), cut) : kInf32;
-                            const uint32_t v2 = j - 2 >= lo ? umax3(e2.d, tp_quot<kOdd>(xi - e2.p, div), cut) : kInf32;
-                            const uint32_t m = umin2(umin2(v0, v1), v2);
-                            const bool upd = (m <= best) & (j >= lo);
-                            best = upd ? m : best;
-                            bt = upd ? j : bt;
-                            if (kCount) { n_trans += j >= lo ? uint32_t(j - lo + 1) : 0u; n_trips += j >= lo; ++n_cells; }
-                        }
-                        // the lowest cut of the winning trip that attains the best value
-                        {
-                            const Pair *pw = rows + (bt - 3);
-                            const Pair w3 = pw[0], w2 = pw[1], w1 = pw[2];
+                            const Pair *pw = rows + bt;
+                            const Pair w0 = pw[0], w1 = pw[1], w2 = pw[2];
+                            const uint32_t u0 = umax3(w0.d, tp_quot<kOdd>(xi - w0.p, div), cut);
                             const uint32_t u1 = umax3(w1.d, tp_quot<kOdd>(xi - w1.p, div), cut);
                             const uint32_t u2 = umax3(w2.d, tp_quot<kOdd>(xi - w2.p, div), cut);
-                            const uint32_t u3 = umax3(w3.d, tp_quot<kOdd>(xi - w3.p, div), cut);
-                            best_j = bt;
-                            best_j = ((u1 == best) & (bt - 1 >= lo)) ? bt - 1 : best_j;
-                            best_j = ((u2 == best) & (bt - 2 >= lo)) ? bt - 2 : best_j;
-                            best_j = ((u3 == best) & (bt - 3 >= lo)) ? bt - 3 : best_j;
+                            best_j = u2 == best ? bt + 2 : bt + 3;
+                            best_j = u1 == best ? bt + 1 : best_j;
+                            best_j = u0 == best ? bt : best_j;
                             best_j = best == kInf32 ? i - 1 : best_j;      // no previous cut fits: any value
                         }
                     }
