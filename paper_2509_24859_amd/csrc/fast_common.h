@@ -40,6 +40,40 @@ __device__ __forceinline__ uint32_t umax3(uint32_t a, uint32_t b, uint32_t c) {
     return m > c ? m : c;
 }
 
+// Cross-lane steps on the DPP path of the vector unit, one instruction where a shuffle goes through LDS and
+// back (a score takes some forty of them, half of them in a chain; k2_fast some thirty per candidate).
+// Lanes a step has no source for read 0, so 0 has to be the neutral value.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t dpp0(uint32_t v) {
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, kRows, 0xF, false));
+}
+constexpr int kRowShr = 0x110, kWaveShl1 = 0x130, kWaveShr1 = 0x138, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
+
+// lane l: f over lanes 0 .. l; lane 63 holds the whole wavefront's
+template <typename F>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v, F f) {
+    v = f(v, dpp0<kRowShr + 1, 0xF>(v));
+    v = f(v, dpp0<kRowShr + 2, 0xF>(v));
+    v = f(v, dpp0<kRowShr + 4, 0xF>(v));
+    v = f(v, dpp0<kRowShr + 8, 0xF>(v));
+    v = f(v, dpp0<kRowBcast15, 0xA>(v));
+    v = f(v, dpp0<kRowBcast31, 0xC>(v));
+    return v;
+}
+template <typename F>
+__device__ __forceinline__ uint32_t wave_all(uint32_t v, F f) {
+    return uint32_t(__builtin_amdgcn_readlane(int(wave_scan(v, f)), 63));
+}
+__device__ __forceinline__ uint32_t sum2(uint32_t a, uint32_t b) { return a + b; }
+__device__ __forceinline__ uint32_t max2(uint32_t a, uint32_t b) { return a > b ? a : b; }
+// (the least value is the complement of the largest complement: 0 is neutral there)
+__device__ __forceinline__ uint32_t wave_least(uint32_t v) { return ~wave_all(~v, max2); }
+// sum of values from 0 to 2^40
+__device__ __forceinline__ int64_t wave_sum(int64_t v) {
+    const uint32_t lo = wave_all(uint32_t(v) & 0xFFFFFFu, sum2), hi = wave_all(uint32_t(v >> 24), sum2);
+    return (int64_t(hi) << 24) + lo;
+}
+
 // A value every lane of the wave holds, moved to a scalar register.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int64_t uniform64(int64_t v) {

@@ -216,12 +216,8 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 const int w = band_hi(band[s + 1]) - band_lo(band[s]) + 1;
                 span = w > span ? w : span;
             }
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) {
-                const int o = __shfl_xor(span, d, 64);
-                span = o > span ? o : span;
-            }
-            const int row_entries = (uniform(span) + kPad + 1) & ~1;
+            span = int(wave_all(uint32_t(span), max2));
+            const int row_entries = (span + kPad + 1) & ~1;
             if (row_entries > lds_row_entries) {
                 if (tid == 0) dead_list[cd.C - 1 - atomicAdd(&counts[10], 1)] = uint32_t(entry);
                 continue;
@@ -237,19 +233,14 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                 uint32_t b = 0, wdt = 0;
                 if (s <= S) b = band[s];
                 if (s >= 1 && s < S) wdt = uint32_t(band_hi(b) - band_lo(b) + 1);
-                uint32_t inc = wdt;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const uint32_t o = __shfl_up(inc, d, 64);
-                    if (lane >= d) inc += o;
-                }
+                const uint32_t inc = wave_scan(wdt, sum2);
                 if (s >= 1 && s <= S) {
                     const uint32_t begin = carry + inc - wdt;
                     uint32_t word = begin + kArgBias - uint32_t(band_lo(b));
                     if (s < S && begin + wdt <= arena_bytes) word |= kArgInLds;
                     aoff[s - 1] = word;
                 }
-                carry += __shfl(inc, 63, 64);
+                carry += uint32_t(__builtin_amdgcn_readlane(int(inc), 63));
             }
             __syncthreads();
         }
@@ -503,11 +494,17 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                     const unsigned long long v = (unsigned long long)prev[j].d + tj;
                     if (tj <= tcap && v < best) { best = v; best_j = j; }   // j rises within a lane
                 }
+                if constexpr (kWide) {
 #pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) {
-                    const unsigned long long ov = __shfl_xor(best, d, 64);
-                    const int oj = __shfl_xor(best_j, d, 64);
-                    if (ov < best || (ov == best && oj < best_j)) { best = ov; best_j = oj; }
+                    for (int d = 32; d >= 1; d >>= 1) {
+                        const unsigned long long ov = __shfl_xor(best, d, 64);
+                        const int oj = __shfl_xor(best_j, d, 64);
+                        if (ov < best || (ov == best && oj < best_j)) { best = ov; best_j = oj; }
+                    }
+                } else {                                       // sums taken are below kInfSum = 2^31
+                    const uint32_t mine = uint32_t(best);
+                    best = wave_least(mine);
+                    best_j = int(wave_least(mine == uint32_t(best) ? uint32_t(best_j) : 0xFFFFFFFFu));
                 }
                 if (lane == 0) {
                     if (kBandRows) trial[S - 1] = best_j;
@@ -556,11 +553,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                     const uint32_t m = t > cu ? t : cu;
                     w = w > m ? w : m;
                 }
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) {
-                    const uint32_t ow = __shfl_xor(w, d, 64);
-                    w = w > ow ? w : ow;
-                }
+                w = wave_all(w, max2);
                 if (lane == 0) scal[1] = w;
             }
             __syncthreads();

@@ -409,16 +409,11 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                 uint32_t b = 0, wdt = 0;
                 if (s <= S) { b = bd[s]; band[s] = b; }
                 if (s >= 1 && s < S) wdt = uint32_t(band_hi(b) - band_lo(b) + 1);
-                uint32_t inc = wdt;
-#pragma unroll
-                for (int d = 1; d < 64; d <<= 1) {
-                    const uint32_t o = __shfl_up(inc, d, 64);
-                    if (lane >= d) inc += o;
-                }
+                const uint32_t inc = wave_scan(wdt, sum2);
                 // aoff[s - 1] = where the back-pointer of cut 0 of row s would sit (stage s - 1 writes
                 // row s): the stage's offset less the row's lowest cut, biased to stay positive
                 if (s >= 1 && s <= S) aoff[s - 1] = carry + inc - wdt + kArgBias - uint32_t(band_lo(b));
-                carry += __shfl(inc, 63, 64);
+                carry += uint32_t(__builtin_amdgcn_readlane(int(inc), 63));
             }
         }
         wave_sync();
@@ -430,12 +425,7 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
             const int w = band_hi(band[s + 1]) - band_lo(band[s]) + 1;
             span = w > span ? w : span;
         }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            const int o = __shfl_xor(span, d, 64);
-            span = o > span ? o : span;
-        }
-        span = uniform(span);
+        span = int(wave_all(uint32_t(span), max2));
         const int row_bytes = int(fast_row_bytes(span));
         if (small_bytes + row_bytes > fa.lds_per_wave) {
             if (lane == 0) dead_list[n_dead + atomicAdd(&counts[8], 1)] = uint32_t(c);
@@ -637,14 +627,8 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                     if (kCount) ++n_trans;
                 }
                 if (kCount && lane == 0) { ++n_cells; ++n_cands; }
-#pragma unroll
-                for (int d = 32; d >= 1; d >>= 1) {
-                    const uint32_t ov = __shfl_xor(best, d, 64);
-                    const int oj = __shfl_xor(best_j, d, 64);
-                    if (ov < best || (ov == best && oj < best_j)) { best = ov; best_j = oj; }
-                }
-                final_v = (uint32_t)uniform((int)best);
-                last_j = uniform(best_j);
+                final_v = wave_least(best);
+                last_j = int(wave_least(best == final_v ? uint32_t(best_j) : 0xFFFFFFFFu));
             }
             if (final_v == kInf32) {          // the bands were bounds: the recurrence found no plan
                 write_failed_wave(out, c, S_max, HARP_CAND_INFEASIBLE, lane);
@@ -689,12 +673,8 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                 worst = worst > m ? worst : m;
                 single += int64_t(t) + 2 * int64_t(cu);
             }
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) {
-                const uint32_t ow = __shfl_xor(worst, d, 64);
-                single += __shfl_xor(single, d, 64);
-                worst = worst > ow ? worst : ow;
-            }
+            worst = wave_all(worst, max2);
+            single = wave_sum(single);
             if (lane == 0) {
                 out.bottleneck[c] = int64_t(worst);
                 out.iter_time[c] = single + int64_t(m_cap - 1) * int64_t(worst);

@@ -9,10 +9,13 @@
 // registers; stage and transfer times come from the fused 32-bit rows, without divisions).
 // k4_argmin: final selection of section 5.2.3 (the min over evaluated candidates), lowest
 // candidate index on ties.  Both are O(C S) bytes of streaming work.
+#include "fast_common.h"
 #include "harp_internal.h"
 #include "plan_common.h"
 
 namespace harp {
+
+using namespace fastdp;
 
 namespace {
 
@@ -38,30 +41,6 @@ __global__ __launch_bounds__(64) void k3_score(TablesDev tb, CandDev cd, const i
     }
 }
 
-// Cross-lane steps on the DPP path of the vector unit, one instruction where a shuffle goes through LDS and
-// back (a score takes some forty of them, half of them in a chain).
-// Lanes a step has no source for read 0, so 0 has to be the neutral value.
-template <int kCtrl, int kRows>
-__device__ __forceinline__ uint32_t dpp0(uint32_t v) {
-    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), kCtrl, kRows, 0xF, false));
-}
-constexpr int kRowShr = 0x110, kWaveShl1 = 0x130, kWaveShr1 = 0x138, kRowBcast15 = 0x142, kRowBcast31 = 0x143;
-
-// lane l: f over lanes 0 .. l; lane 63 holds the whole wavefront's
-template <typename F>
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v, F f) {
-    v = f(v, dpp0<kRowShr + 1, 0xF>(v));
-    v = f(v, dpp0<kRowShr + 2, 0xF>(v));
-    v = f(v, dpp0<kRowShr + 4, 0xF>(v));
-    v = f(v, dpp0<kRowShr + 8, 0xF>(v));
-    v = f(v, dpp0<kRowBcast15, 0xA>(v));
-    v = f(v, dpp0<kRowBcast31, 0xC>(v));
-    return v;
-}
-template <typename F>
-__device__ __forceinline__ uint32_t wave_all(uint32_t v, F f) {
-    return uint32_t(__builtin_amdgcn_readlane(int(wave_scan(v, f)), 63));
-}
 __device__ __forceinline__ int64_t wave_up1(int64_t v) {
     const uint32_t lo = dpp0<kWaveShr1, 0xF>(uint32_t(v)), hi = dpp0<kWaveShr1, 0xF>(uint32_t(uint64_t(v) >> 32));
     return int64_t((uint64_t(hi) << 32) | lo);
