@@ -65,6 +65,16 @@ template <> struct SumTraits<uint64_t> {
     struct alignas(16) Entry { uint64_t d; uint32_t p; uint32_t unused; };
 };
 
+// floor(a / b), a >= 0, 0 < b < 2^31: below 2^52 from a double, whose quotient is off by less than one, and a check;
+// the 64-bit division the compiler makes takes 130 instructions, twice in every pass.
+__device__ __forceinline__ int64_t quotient(int64_t a, int64_t b) {
+    if (a >= (int64_t(1) << 52)) return a / b;
+    int64_t q = int64_t(double(a) / double(b));
+    const int64_t rest = a - q * b;
+    q += rest < 0 ? -1 : (rest >= b ? 1 : 0);
+    return q;
+}
+
 constexpr int64_t kNarrowLimit = int64_t(1) << 31;   // sums below this run in 32 bits
 
 // One-byte back-pointers of the wavefront-per-candidate kernel, as in the min-max kernel: the distance
@@ -515,22 +525,32 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             __syncthreads();          // back-pointers of every wave are visible to thread 0
             const int64_t sum = uniform64((int64_t)scal[0]);
             if (sum >= int64_t(kInfSum)) break;   // no plan under this cap (cannot happen at or above t_S)
-            if (tid == 0) {
-                trial[S] = L;
-                if (kBandRows) {
-                    int b = trial[S - 1];
-                    for (int s = S - 2; s >= 0; --s) {
+            if constexpr (kBandRows) {
+                // as in the min-max kernel: the cut in a scalar, a lane per stage
+                int b = uniform(trial[S - 1]);
+                for (int s0 = (S - 2) & ~63; s0 >= 0; s0 -= 64) {
+                    const int hi = S - 2 - s0 < 63 ? S - 2 - s0 : 63;
+                    const int words = lane <= hi ? int(aoff[s0 + lane]) : 0, rows = lane <= hi ? int(band[s0 + lane + 1]) : 0;
+                    int found = 0;
+                    for (int s = hi; s >= 0; --s) {
                         // a finite sum only chains through cuts inside the rows; the clamp keeps the index
                         // inside the stage's back-pointers whatever the cut
-                        const uint32_t bw = band[s + 1];
+                        const uint32_t bw = uint32_t(__builtin_amdgcn_readlane(rows, s));
                         b = b < band_lo(bw) ? band_lo(bw) : (b > band_hi(bw) ? band_hi(bw) : b);
-                        const uint32_t word = aoff[s];
+                        const uint32_t word = uint32_t(__builtin_amdgcn_readlane(words, s));
                         const uint32_t at = (word & ~kArgInLds) - kArgBias + uint32_t(b);
-                        const int rel = (word & kArgInLds) ? arena[at] : arg8[at];
-                        b = rel == kArgEscape ? int(arg[at]) : b - 1 - rel;
-                        trial[s] = b;
+                        int rel;
+                        if (word & kArgInLds) rel = uniform(arena[at]);
+                        else rel = uniform(arg8[at]);
+                        b = rel == kArgEscape ? uniform(arg[at]) : b - 1 - rel;
+                        found = lane == s ? b : found;
                     }
-                } else {
+                    if (lane <= hi) trial[s0 + lane] = found;
+                }
+                if (tid == 0) trial[S] = L;
+            } else {
+                if (tid == 0) {
+                    trial[S] = L;
                     int b = L;
                     for (int s = S - 1; s >= 0; --s) {
                         b = arg[s * row_len + b];
@@ -570,7 +590,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             if (passes == 1) {
                 // every plan costs at least B times its bottleneck (the bottleneck is one of the
                 // terms of the sum), so nothing above t_E = ceil(T / B) can beat the total T in hand
-                next_cap = (best_T + m_cap - 1) / m_cap;
+                next_cap = quotient(best_T + m_cap - 1, m_cap);
                 if (next_cap > 0x7FFFFFFFll) next_cap = 0x7FFFFFFFll;   // no time on these tables is larger
             } else {
                 next_cap = b - 1;
@@ -579,7 +599,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             // the sum `sum` costs at least sum + (B - 1) b' with its own bottleneck b': it can match
             // the best total only if b' <= (best_T - sum) / (B - 1).  Caps above that are skipped.
             if (passes > 1 && m_cap > 1) {
-                const int64_t bound = (best_T - sum) / (m_cap - 1);
+                const int64_t bound = best_T >= sum ? quotient(best_T - sum, m_cap - 1) : -1;
                 next_cap = next_cap < bound ? next_cap : bound;
             }
             if (next_cap <= t_S) break;         // the plan at t_S is already in hand

@@ -634,19 +634,25 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
                 write_failed_wave(out, c, S_max, HARP_CAND_INFEASIBLE, lane);
                 continue;
             }
-            // backtrack along the back-pointers
-            if (lane == 0) {
+            // Backtrack along the back-pointers: the cut in a scalar, a lane per stage for the stages' words and the
+            // cuts found, which leaves one dependent read and five vector instructions a stage.
+            {
                 int b = last_j;
-                cuts[S] = L;
-                cuts[S - 1] = b;
-                for (int s = S - 2; s >= 0; --s) {
-                    const uint32_t a_word = aoff[s];
-                    const uint32_t at = (a_word & ~kArgInLds) - kArgBias + uint32_t(b);
-                    int rel;
-                    if (a_word & kArgInLds) rel = arena[at];
-                    else rel = slice8[at];
-                    b = rel == kArgEscape ? int(slice[at]) : b - 1 - rel;
-                    cuts[s] = b;
+                if (lane == 0) { cuts[S] = L; cuts[S - 1] = b; }
+                for (int s0 = (S - 2) & ~63; s0 >= 0; s0 -= 64) {
+                    const int hi = S - 2 - s0 < 63 ? S - 2 - s0 : 63;
+                    const int words = lane <= hi ? int(aoff[s0 + lane]) : 0;
+                    int found = 0;
+                    for (int s = hi; s >= 0; --s) {
+                        const uint32_t a_word = uint32_t(__builtin_amdgcn_readlane(words, s));
+                        const uint32_t at = (a_word & ~kArgInLds) - kArgBias + uint32_t(b);
+                        int rel;
+                        if (a_word & kArgInLds) rel = uniform(arena[at]);
+                        else rel = uniform(slice8[at]);
+                        b = rel == kArgEscape ? uniform(slice[at]) : b - 1 - rel;
+                        found = lane == s ? b : found;
+                    }
+                    if (lane <= hi) cuts[s0 + lane] = found;
                 }
             }
             wave_sync();

@@ -204,12 +204,8 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                 const int w = band_hi(band[s + 1]) - (s == 0 ? 0 : band_lo(band[s])) + 1;
                 span = w > span ? w : span;
             }
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) {
-                const int o = __shfl_xor(span, d, 64);
-                span = o > span ? o : span;
-            }
-            if (uniform(span) + kTail > row_len) {
+            span = int(wave_all(uint32_t(span), max2));
+            if (span + kTail > row_len) {
                 if (tid == 0) dead_list[cd.C - 1 - atomicAdd(&counts[10], 1)] = uint32_t(c);
                 continue;
             }
@@ -402,14 +398,20 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             for (int s = tid; s < S_max; s += nthreads) wu[s] = -1;
             continue;
         }
-        if (tid == 0) {
+        // the cuts, from the first slot on: the cut in a scalar, a lane per slot for the cuts found
+        if (wave == 0) {
             int b = 0;
-            for (int slot = 0; slot < S; ++slot) {
-                trial[slot] = b;
-                b = arg[slot * arg_pitch + b];
-                b = b <= L ? b : L;      // a finite sum only chains through cuts inside the row
+            for (int s0 = 0; s0 < S; s0 += 64) {
+                const int n = S - s0 < 64 ? S - s0 : 64;
+                int found = 0;
+                for (int s = 0; s < n; ++s) {
+                    found = lane == s ? b : found;
+                    b = uniform(arg[(s0 + s) * arg_pitch + b]);
+                    b = b <= L ? b : L;      // a finite sum only chains through cuts inside the row
+                }
+                if (lane < n) trial[s0 + lane] = found;
             }
-            trial[S] = b;
+            if (lane == 0) trial[S] = b;
         }
         __syncthreads();
         // one lane per stage: the plan's own bottleneck, and the counts by eq. Ni along the plan
@@ -426,11 +428,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                 w = w > m ? w : m;
                 deltas[s] = s < S - 1 ? h1f1b_delta(cu, cap64) : 1u;
             }
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) {
-                const uint32_t ow = __shfl_xor(w, d, 64);
-                w = w > ow ? w : ow;
-            }
+            w = wave_all(w, max2);
             if (lane == 0) {
                 out.bottleneck[c] = int64_t(w);
                 out.iter_time[c] = int64_t(sum) + (m_cap - 1) * cap64;
@@ -438,12 +436,14 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             }
         }
         __syncthreads();
-        if (tid == 0) {
-            uint32_t nrun = 0;
-            for (int s = S - 1; s >= 0; --s) {
-                nrun += deltas[s];
-                nrun = nrun < uint32_t(m_cap) ? nrun : uint32_t(m_cap);
-                wu[s] = int32_t(nrun);
+        // N of a stage = the growths from it to the last one, at most M: a running sum from the end
+        if (wave == 0) {
+            uint32_t behind = 0;
+            for (int s0 = (S - 1) & ~63; s0 >= 0; s0 -= 64) {
+                const int s = s0 + 63 - lane;
+                const uint32_t n = wave_scan(s < S ? uint32_t(deltas[s]) : 0u, sum2) + behind;
+                if (s < S) wu[s] = int32_t(n < uint32_t(m_cap) ? n : uint32_t(m_cap));
+                behind = uint32_t(__builtin_amdgcn_readlane(int(n), 63));
             }
         }
         for (int s = tid; s <= S_max; s += nthreads) sp[s] = s <= S ? trial[s] : -1;
