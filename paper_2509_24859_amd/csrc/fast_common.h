@@ -41,7 +41,8 @@ __device__ __forceinline__ uint32_t umax3(uint32_t a, uint32_t b, uint32_t c) {
 }
 
 // Cross-lane steps on the DPP path of the vector unit, one instruction where a shuffle goes through LDS and
-// back (a score takes some forty of them, half of them in a chain; k2_fast some thirty per candidate).
+// back (a score takes some forty of them, half of them in a chain; k2_fast some thirty per candidate: 262,144
+// candidates of 512 operators 4.69 -> 4.53 ms a step).
 // Lanes a step has no source for read 0, so 0 has to be the neutral value.
 template <int kCtrl, int kRows>
 __device__ __forceinline__ uint32_t dpp0(uint32_t v) {
