@@ -299,6 +299,13 @@ constexpr uint32_t kArgInLds = 1u << 31;    // flag on that word: the stage's ba
 
 __device__ __forceinline__ uint32_t umin2(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
+// Slot word of a stage: group (below 256: G * G rows of cut times are at most 65,535) | degree index << 8 |
+// log2 of the degree, or with odd degrees its index, << 11 (five bits: a degree is at most 2^16) | GPU type << 16.
+__device__ __forceinline__ int slot_group(uint32_t w) { return int(w & 0xFFu); }
+__device__ __forceinline__ int slot_degree(uint32_t w) { return int((w >> 8) & 7u); }
+__device__ __forceinline__ uint32_t slot_code(uint32_t w) { return (w >> 11) & 31u; }
+static_assert(kMaxTp <= 8, "three bits of degree index");
+
 struct FastArgs {
     int *tickets;
     const uint32_t *bands;        // [C][S_max + 1]
@@ -309,7 +316,6 @@ struct FastArgs {
     unsigned long long *work;     // [4] transitions, cells, trips, candidates (counting build only)
     int lo_pitch, lds_per_wave;
     int wide_pass;                // 1: the pass over the candidates the first pass found too wide for its LDS share
-    uint32_t shift_packed;        // log2 of degree k in bits 4k .. 4k+3
 };
 
 // per-wavefront LDS slice: band [S_max+1] | slot [S_max] | aoff [S_max+1] | cuts [S_max+1] | row entries
@@ -352,12 +358,11 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
     const int n_tp = own_scalar(tb.n_tp), G = own_scalar(tb.G);
     const int rows_per_n = own_scalar(tb.T * tb.n_tp);
     const uint32_t pitch32 = own_scalar(uint32_t(tb.pitch32)), lo_pitch = own_scalar(uint32_t(fa.lo_pitch));
-    const uint32_t shift_packed = own_scalar(fa.shift_packed);
     const uint32_t *const p32 = own_scalar(tb.P32), *const cm = own_scalar(tb.CM);
     const uint16_t *const lo_tab = own_scalar(fa.lo_tab);
     unsigned long long n_trans = 0, n_cells = 0, n_trips = 0, n_cands = 0;
 
-    // scalars of one stage, from the packed slot word  g | k << 12 | type << 16
+    // scalars of one stage, from its slot word
     struct Stage {
         const uint32_t *p_row, *cm_row;
         const uint16_t *lo;
@@ -366,15 +371,15 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
     auto stage_of = [&](int s, int S) -> Stage {
         const uint32_t w = (uint32_t)uniform((int)slot[s]);
         const uint32_t wn = (uint32_t)uniform((int)slot[s + 1 < S ? s + 1 : s]);
-        const int g = int(w & 0xFFFu), k = int((w >> 12) & 7u), t = int(w >> 16);
-        const int gn = int(wn & 0xFFFu);
+        const int g = slot_group(w), k = slot_degree(w), t = int(w >> 16);
+        const int gn = slot_group(wn);
         const int n = (S - s) < m_cap ? (S - s) : m_cap;
         Stage st;
         // (fewer than 2^32 entries each: 65,535 rows of at most 4,112, and 256 MiB of index)
         st.p_row = p32 + uint32_t(g * n_tp + k) * pitch32;
         st.cm_row = cm + uint32_t(g * G + gn) * pitch32;
         st.lo = lo_tab + uint32_t((n - 1) * rows_per_n + t * n_tp + k) * lo_pitch;
-        st.div = tp_div<kOdd>(tb, kOdd ? uint32_t(k) : (shift_packed >> (4 * k)) & 15u);
+        st.div = tp_div<kOdd>(tb, slot_code(w));
         return st;
     };
 
@@ -393,7 +398,8 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
             const uint32_t *bd = fa.bands + int64_t(c) * (S_max + 1);
             for (int s = lane; s < S; s += 64) {
                 const int g = grp[s], k = tp_index(tb, tpv[s]);
-                slot[s] = uint32_t(g) | (uint32_t(k) << 12) | (uint32_t(tb.group_type[g]) << 16);
+                const uint32_t code = kOdd ? uint32_t(k) : uint32_t(__builtin_ctz(uint32_t(tpv[s])));
+                slot[s] = uint32_t(g) | (uint32_t(k) << 8) | (code << 11) | (uint32_t(tb.group_type[g]) << 16);
                 // first device of the slot: its group's base plus the degrees of the group's
                 // earlier slots (they are adjacent; the pre-pass has checked that)
                 int32_t first = tb.group_base[g];
@@ -670,8 +676,8 @@ __global__ __launch_bounds__(kFastWaves * 64) void k2_fast(TablesDev tb, CandDev
             int64_t single = 0;
             for (int s = lane; s < S; s += 64) {
                 const uint32_t w = slot[s], wn = slot[s + 1 < S ? s + 1 : s];
-                const int g = int(w & 0xFFFu), k = int((w >> 12) & 7u), gn = int(wn & 0xFFFu);
-                const TpDiv div = tp_div<kOdd>(tb, kOdd ? uint32_t(k) : (fa.shift_packed >> (4 * k)) & 15u);
+                const int g = slot_group(w), k = slot_degree(w), gn = slot_group(wn);
+                const TpDiv div = tp_div<kOdd>(tb, slot_code(w));
                 const uint32_t *p = tb.P32 + (int64_t(g) * tb.n_tp + k) * tb.pitch32;
                 const int j = cuts[s], i = cuts[s + 1];
                 const uint32_t t = tp_quot<kOdd>(p[i] + div.add - p[j], div);
@@ -813,8 +819,6 @@ void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &ou
     fa.work = work;
     fa.lo_pitch = int(lo_pitch(tb.L));
     const bool odd = tb.odd_degrees();
-    fa.shift_packed = 0;          // (unused with odd degrees)
-    for (int k = 0; k < tb.n_tp; ++k) fa.shift_packed |= uint32_t(tb.tp_shift[k] & 15) << (4 * k);
     for (int pass = 0; pass < (shape.second_pass ? 2 : 1); ++pass) {
         const int per_cu = pass ? shape.wide_waves_per_cu : shape.waves_per_cu;
         fa.lds_per_wave = pass ? shape.wide_lds_per_wave : shape.lds_per_wave;

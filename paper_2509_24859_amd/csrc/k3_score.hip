@@ -61,7 +61,7 @@ constexpr size_t kStagedBytes = 64 << 10;    // LDS of such a workgroup at most:
 template <int kWaves, bool kStaged>
 __global__ __launch_bounds__(kWaves * 64) void k3_score_fast(TablesDev tb, CandDev cd, const int32_t *splits,
                                                              int64_t *bottleneck, int64_t *iter_time,
-                                                             int32_t *status, uint32_t shift_packed) {
+                                                             int32_t *status) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int lane = threadIdx.x & 63;
     const int wave_id = blockIdx.x * kWaves + (threadIdx.x >> 6), n_waves = gridDim.x * kWaves;
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kWaves * 64) void k3_score_fast(TablesDev tb, CandD
             uint32_t time = 0, cu = 0;
             int unfit = 0;
             if (mine) {
-                const int shift = int((shift_packed >> (4 * k)) & 15u);
+                const int shift = __builtin_ctz(uint32_t(f.tp));         // degrees are powers of two here
                 if (lane < S - 1) cu = cut_here;
                 const int64_t n_inflight = (S - lane) < tb.M ? (S - lane) : tb.M;
                 if (dpp + n_inflight * dps > int64_t(f.tp) * device_mem) unfit = 1;
@@ -377,8 +377,6 @@ void launch_score(const TablesDev &tb, const CandDev &cd, const int32_t *splits,
                   hipStream_t st) {
     if (cd.C == 0) return;
     if (fast32 && cd.S_max <= 64) {
-        uint32_t shift_packed = 0;
-        for (int k = 0; k < tb.n_tp; ++k) shift_packed |= uint32_t(tb.tp_shift[k] & 15) << (4 * k);
         // Reading the sums into LDS pays once every wavefront has two candidates and the gathers spared outweigh the
         // reading.  The reading costs about 1.4 us per 64 KB, a thousand candidates of up to 8 stages gain about
         // 0.033 us, longer ones in proportion (90 to 4,000 operators, 16,384 to 262,144 candidates).  Without / with
@@ -389,15 +387,14 @@ void launch_score(const TablesDev &tb, const CandDev &cd, const int32_t *splits,
         const size_t stages = cd.S_max > 8 ? size_t(cd.S_max) : 8;
         if (staged <= kStagedBytes && cd.C >= resident * 2 && 16 * staged <= 3 * size_t(cd.C) * stages) {
             hipLaunchKernelGGL((k3_score_fast<kStagedWaves, true>), dim3(resident / kStagedWaves),
-                               dim3(kStagedWaves * 64), staged, st, tb, cd, splits, bottleneck, iter_time, status,
-                               shift_packed);
+                               dim3(kStagedWaves * 64), staged, st, tb, cd, splits, bottleneck, iter_time, status);
             return;
         }
         int groups = resident / kScoreWaves;
         const int want = (cd.C + kScoreWaves - 1) / kScoreWaves;
         if (groups > want) groups = want;
         hipLaunchKernelGGL((k3_score_fast<kScoreWaves, false>), dim3(groups), dim3(kScoreWaves * 64), 0, st, tb, cd,
-                           splits, bottleneck, iter_time, status, shift_packed);
+                           splits, bottleneck, iter_time, status);
         return;
     }
     const int groups = cd.C < (1 << 20) ? cd.C : (1 << 20);

@@ -78,6 +78,39 @@ def test_largest_stage_count(harp, ctx):
     assert e.value.code == harp.ERR_SHAPE
 
 
+@pytest.mark.parametrize("degrees", [(1, 65536), (1, 32768, 65536), (1, 2, 4, 8, 16, 128, 32768, 65536)],
+                         ids=lambda d: "%d_degrees" % len(d))
+def test_largest_degree(harp, ctx, degrees):
+    """Degree 65,536 = 2^16, the largest the problem header takes, on every kernel that divides by it: the 32-bit
+    planners, the counting form of the min-max kernel and both forms of the scorer."""
+    import torch
+    rng = np.random.default_rng(len(degrees))
+    L, G, most = 40, 2, degrees[-1]
+    p = simple_problem(np.zeros(L), M=7, T=2, G=G, ndev=(2 * most, 2 * most), tp=degrees, gtype=[0, 1],
+                       fwd=rng.integers(1, 1 << 24, size=(2, L)), bwd=rng.integers(1, 1 << 24, size=(2, L)),
+                       act=rng.integers(1, 90, size=L), params=rng.integers(1, 40, size=L), stash=rng.integers(1, 9, size=L),
+                       mem=[700, 900], bw=[[900, 5], [5, 900]])
+    lists = [[(0, most)], [(1, most), (1, most)], [(0, most), (0, most), (1, most)], [(0, most), (1, 1), (1, most)],
+             [(1, degrees[-2]), (0, most)], [(0, most), (0, degrees[-2]), (1, most), (1, most)], [(0, most)] * 3]
+    cands = cands_from_lists(lists)
+    want, fast32 = _all_entry_points(harp, ctx, p, cands, "degree 65,536")
+    assert fast32 and (want.status == oracle.OK).sum() == 6
+    tables, dc, out = harp.Tables(ctx, p), harp.DeviceCandidates(ctx, cands), harp.DevicePlans(ctx, cands.C, cands.S_max)
+    ws = harp.plan_workspace(ctx, tables, dc)
+    work = torch.zeros(8, dtype=torch.int64, device=ctx.device)
+    harp.harp_plan_batch_count_work(ctx, tables, dc, out, ws, work)
+    torch.cuda.synchronize()
+    assert_plans_equal(out.to_host(), want, "counting")
+    for C in (cands.C, 40000):                                     # the scorer's two forms: sums read, or kept in LDS
+        many = cands.take(np.arange(C) % cands.C)
+        splits = torch.from_numpy(np.ascontiguousarray(want.splits[np.arange(C) % cands.C])).to(ctx.device)
+        res = [torch.empty(C, dtype=t, device=ctx.device) for t in (torch.int64, torch.int64, torch.int32)]
+        harp.harp_score_1f1b(ctx, tables, harp.DeviceCandidates(ctx, many), splits, *res)
+        ok = want.status[np.arange(C) % cands.C] == oracle.OK
+        for name, r in zip(("bottleneck", "iter_time"), res):
+            assert (r.cpu().numpy()[ok] == getattr(want, name)[np.arange(C) % cands.C][ok]).all(), (C, name)
+
+
 def test_every_operator_its_own_stage(harp, ctx):
     """S = L: the only partition has one operator per stage; S = L + 1 has none."""
     rng = np.random.default_rng(42)
