@@ -411,6 +411,30 @@ def test_sweep_of_candidates_at_its_edges(harp, ctx, case):
     assert planned > 0
 
 
+@pytest.mark.parametrize("n", [5, 330], ids=["few", "many"])
+def test_sweep_without_a_plan_under_any_cap(harp, ctx, n):
+    """The recurrence keeps one continuation per cell.  Here it keeps the cheaper last cut, whose transfer raises the
+    counts beyond the first stage's memory at every cap, while the dearer one would fit: the pass at the bottleneck
+    already tells that no cap has a plan, the least-count pass at the largest value does not.  Every value above the
+    bottleneck counts as tried, none below it: the first stage's n operators of 90 us give values just below."""
+    t_S, piece, sigma = 1 << 27, 1000, 1000
+    L = n + 4
+    fwd = np.ones((3, L), dtype=np.int64)
+    fwd[0, 0], fwd[0, 1:n + 1] = t_S - 90 * n, 90
+    fwd[1, n + 1], fwd[1, n + 2] = 1000, (1 << 26) + (1 << 22)
+    params = np.full(L, piece)
+    params[[0, n + 1, n + 2]] = 0, 10 * piece, piece // 4
+    stash, act = np.zeros(L, dtype=np.int64), np.ones(L, dtype=np.int64)
+    stash[0], act[n + 1] = sigma, 1 << 25                              # (2 x cut exceeds cap / 64 for every cap below 2^32)
+    p = simple_problem(np.zeros(L), M=8, T=3, G=3, ndev=(1, 1, 1), gtype=[0, 1, 2], fwd=fwd, bwd=np.zeros_like(fwd), act=act,
+                       params=params, stash=stash, bw=np.ones((3, 3)),
+                       mem=[n * piece + 3 * sigma + sigma // 2, 10 * piece + piece // 2, 5 * piece])
+    cands = cands_from_lists([[(0, 1), (1, 1), (2, 1)]])
+    assert oracle.plan_batch(oracle.build_tables(p), cands).bottleneck[0] == t_S
+    got, want = _check_sweep(harp, ctx, p, cands, "no plan")
+    assert want.status[0] == oracle.INFEASIBLE and want.n_caps[0] == 4
+
+
 @pytest.mark.parametrize("scale", [1, 10**6, 10**12], ids=["bytes", "MB", "TB"])
 def test_memory_at_the_byte(harp, ctx, scale):
     """Device memory of exactly what the tightest stage of a plan needs, and of a byte less and more: needs the
