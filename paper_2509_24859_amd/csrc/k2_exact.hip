@@ -656,8 +656,15 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
     if (narrow) launch_plan_narrow(tb, cd, out, ws, n_groups, n_cu, st);
     const int full_row = fast_row_len(tb.L);
     const size_t small = exact_small_bytes(cd.S_max);
-    // Wavefronts per CU of the first launch and the row entries their LDS share leaves.
-    const int per_cu = 4 * kExactWaves;
+    // Wavefronts per CU of the first launch and the row entries their LDS share leaves: 24 (six per SIMD, what the
+    // registers allow), or as many as hold rows over the whole sequence where that is 18 or more, so that no candidate
+    // is left for the second launch.  A few left over make the call as long as the longest of either launch after one
+    // another: 400 operators, 4,096 candidates of up to 32 stages 4.9 ms with 24 per CU (539 left), 3.5 with 20; 32,768
+    // of up to 8 stages 8.5 and 6.3 with 22.  With fewer than 18 the latency of a stage shows, and the second launch's 256
+    // threads are the better place for long rows: 512 operators, 16 stages, 4,096 candidates 16 ms with 24 per CU (4,081
+    // left), 22 with 16; 64 of up to 128 stages 5.7 and 12.
+    int per_cu = int((size_t(160) << 10) / (small + size_t(full_row) * 16 + 128));
+    if (per_cu < 18 || per_cu > 4 * kExactWaves) per_cu = 4 * kExactWaves;
     size_t share = ((size_t(160) << 10) / per_cu - 128) & ~size_t(15);
     int entries = share > small + 2 * 8 * (kPad + 8) ? int((share - small) / 16) : kPad + 8;
     if (entries > full_row) entries = full_row;

@@ -324,3 +324,36 @@ def test_exact_key_rows(harp, ctx, L, degrees, time, spread, memory):
     if time == 700000:
         sums = (want.iter_time - (p.M - 1) * want.bottleneck)[want.status == oracle.OK] * 8
         assert (sums < 0.9 * 2 ** 30).any() and (sums > 1.1 * 2 ** 30).any()
+
+
+@pytest.mark.parametrize("L,S_max,memory,left", [
+    (400, 8, 9.0, 0),                         # 22 wavefronts per CU hold whole rows
+    (400, 30, 9.0, 0),                        # 20
+    (512, 8, 9.0, 0),                         # 18
+    (512, 20, 9.0, 1),                        # 17: 24 with smaller shares, the widest candidates are left
+    (512, 200, 9.0, 1),                       # shares of a few cuts: nearly all are
+])
+def test_exact_share_of_a_wavefront(harp, ctx, L, S_max, memory, left):
+    """Where the shares of 18 wavefronts or more hold rows over the whole sequence no candidate is queued for the
+    second launch; otherwise some are.  Plans and passes are the int64 kernels' either way."""
+    import torch
+    rng = np.random.default_rng(L + S_max)
+    G = 4
+    bw = rng.integers(400, 3600, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 9000
+    fwd = np.maximum(1, np.rint(np.exp(6 + 0.6 * rng.standard_normal((2, L))))).astype(np.int64)
+    p = simple_problem(np.zeros(L), M=24, T=2, G=G, ndev=(50, 50, 50, 50), tp=(1, 2, 4), gtype=[0, 1, 0, 1], fwd=fwd,
+                       bwd=2 * fwd, act=rng.integers(8, 65, size=L) * 1000, params=2000 * fwd[0],
+                       stash=rng.integers(8, 65, size=L) * 4000, bw=bw)
+    p.type_mem_bytes[:] = int(memory * (p.param_bytes.sum() + min(24, S_max) / 2 * p.stash_bytes.sum()) / (2 * S_max))
+    cands = W.make_candidates(p, L, 78, max(4, S_max // 2), S_max, 0, 64)
+    want, want_passes, _ = harp.plan_exact(ctx, p, cands, harp.PATH_GENERIC)
+    tables, dc, out = harp.Tables(ctx, p), harp.DeviceCandidates(ctx, cands), harp.DevicePlans(ctx, 64, S_max)
+    ws, passes = harp.plan_workspace(ctx, tables, dc), torch.zeros(64, dtype=torch.int32, device=ctx.device)
+    harp.harp_plan_exact_batch(ctx, tables, dc, out, ws, passes)
+    queued = int(ws[:64].view(torch.int32)[10])
+    assert_plans_equal(out.to_host(), want, "S_max %d" % S_max)
+    ok = want.status == oracle.OK
+    assert (passes.cpu().numpy() == want_passes).all() and ok.sum() > 20
+    assert (queued > 0) == bool(left), queued
