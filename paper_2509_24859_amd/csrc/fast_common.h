@@ -179,6 +179,9 @@ constexpr int kWideBands = 12;          // counter: candidates listed with wide 
 constexpr uint32_t kWideFlag = 1u << 30;    // on a live-list entry: the candidate is one of them, its bands are in `tight`
 __device__ __forceinline__ int listed(int32_t entry) { return int(uint32_t(entry) & (kWideFlag - 1u)); }
 constexpr int kTicketFast = 0, kTicketFastWide = 1, kTicketExact = 2, kTicketH1f1b = 3;   // word of a line
+constexpr int kLongRows = 4;            // another: candidates whose narrowed bands are too wide for a wavefront's share
+// Bands of listed candidates are narrowed (k2_narrow) where at least a quarter of the live ones are listed.
+__device__ __forceinline__ bool bands_narrowed(const int *counts) { return 4 * int64_t(counts[kWideBands]) >= counts[0]; }
 struct Draw {
     int *word;               // this kernel's word of the first share's line
     int n_items, n_waves, home;

@@ -409,7 +409,8 @@ size_t harp_plan_workspace_bytes(harp_ctx *ctx, const harp_tables *t, const harp
     if (fast_batch_ok(t, cd)) gen += plan_fast_ws_bytes(t->dev, cd->S_max, C, 0, false);
     size_t fast = 0;
     if (t->lim.want_fast && fast_batch_ok(t, cd))
-        fast = plan_fast_ws_bytes(t->dev, cd->S_max, C, n_fast_slices(ctx, C, t->dev.L, cd->S_max), t->dev.L >= kNarrowMinL);
+        fast = plan_fast_ws_bytes(t->dev, cd->S_max, C, n_fast_slices(ctx, C, t->dev.L, cd->S_max),
+                                  exact_narrows(t->dev.L, cd->S_max, C, ctx->n_cu));
     return (gen > fast ? gen : fast) + 256;
 }
 
@@ -524,9 +525,10 @@ int harp_plan_exact_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *
     int rc = plan_prepare(ctx, t, cd, out, false, false, workspace, workspace_bytes, false, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
     if (pc.fast) {
-        rc = plan_minmax(ctx, t, pc, workspace, t->dev.L >= kNarrowMinL, nullptr);
+        const bool narrow = exact_narrows(t->dev.L, cd->S_max, cd->C, ctx->n_cu);
+        rc = plan_minmax(ctx, t, pc, workspace, narrow, nullptr);
         if (rc != HARP_OK) return rc;
-        launch_plan_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.slices, ctx->n_cu, t->dev.L >= kNarrowMinL, pc.st);
+        launch_plan_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.slices, ctx->n_cu, narrow, pc.st);
     } else {
         launch_plan_generic_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.banded, pc.st);
     }

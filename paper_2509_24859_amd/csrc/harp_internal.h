@@ -107,11 +107,12 @@ void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &ou
                       int n_slices, int n_cu, bool narrow, unsigned long long *work, hipStream_t st);
 void launch_plan_index(const TablesDev &tb, int S_max, uint16_t *index, hipStream_t st);
 void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n_groups, bool narrow, hipStream_t st);
-// The exact search narrows bands (k2_narrow.hip) from this many operators on: a candidate is listed when its memory
-// bands are wider than kWideCells cuts a stage, one round of a wavefront's lanes, which shorter sequences rarely are.
-constexpr int kNarrowMinL = 128, kWideCells = 64;
+// Whether the exact search narrows bands (k2_narrow.hip); a candidate is listed for it when its memory bands are wider
+// than kWideCells cuts a stage, one round of a wavefront's lanes.
+bool exact_narrows(int L, int S_max, int C, int n_cu);
+constexpr int kWideCells = 64;
 void launch_plan_narrow(const TablesDev &tb, const CandDev &cd, const PlansDev &out, void *ws, int n_slices, int n_cu,
-                        hipStream_t st);
+                        int row_entries, hipStream_t st);
 void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_max, const PlansDev &out,
                        int32_t *warmup, void *ws, int n_groups, int n_slices, int n_cu, hipStream_t st);
 void launch_plan_generic_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_max, const PlansDev &out,

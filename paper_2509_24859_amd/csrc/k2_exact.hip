@@ -125,7 +125,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
                                            int32_t *n_passes, int *counts, int *tickets,
                                            const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands, const uint32_t *tight, const uint16_t *lo_tab,
                                            int lo_pitch, unsigned char *arg_base, size_t arg_per_group,
-                                           size_t arg_u8_off, int row_len, int lds_row_entries) {
+                                           size_t arg_u8_off, int row_len, int lds_row_entries, int eighths) {
     using Pair = typename SumTraits<SumT>::Entry;
     constexpr SumT kInfSum = SumTraits<SumT>::inf;
     constexpr bool kWide = sizeof(SumT) == 8;
@@ -155,7 +155,14 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
     uint16_t *arg = reinterpret_cast<uint16_t *>(arg_base + size_t(blockIdx.x) * arg_per_group);
     uint8_t *arg8 = reinterpret_cast<uint8_t *>(arg) + arg_u8_off;     // the slice's one-byte entries
     const int n_dead = counts[1];
-    const int n_items = kWide ? counts[2] : kMode == 2 ? counts[10] : counts[0];
+    // whether the workgroup-per-candidate form takes the whole batch (see the launch)
+    bool all_to_rows = false;
+    if (!kWide && eighths > 0) {
+        const uint32_t long_rows = wave_all(uint32_t(tickets[lane * kShareInts + kLongRows]), sum2);
+        all_to_rows = long_rows > 0 && 8ull * long_rows >= uint64_t(eighths) * uint32_t(counts[0]);
+    }
+    if (tight && !bands_narrowed(counts)) tight = bands;
+    const int n_items = kWide ? counts[2] : (kMode == 2) == all_to_rows ? counts[0] : kMode == 2 ? counts[10] : 0;
     if (!kBandRows && int(blockIdx.x) >= n_items) return;      // mostly nothing is queued: no ticket to draw (25 us)
     const int64_t m_cap = tb.M;
     const uint32_t *const P32 = own_scalar(tb.P32), *const CM = own_scalar(tb.CM);
@@ -176,7 +183,7 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
             n = uniform((int)scal[0]);
             if (n >= n_items) break;
         }
-        const int entry = kWide ? int(dead_list[n_dead + n]) : kMode == 2 ? int(dead_list[cd.C - 1 - n]) : live_list[n];
+        const int entry = kWide ? int(dead_list[n_dead + n]) : kMode == 2 && !all_to_rows ? int(dead_list[cd.C - 1 - n]) : live_list[n];
         const int c = listed(entry);
         const int S = cd.cand_S[c];
         // the min-max planner has run on this batch: candidates it found no plan for stay as they are,
@@ -636,9 +643,10 @@ __device__ __forceinline__ void exact_body(const TablesDev &tb, const CandDev &c
     __global__ BOUNDS void NAME(TablesDev tb, CandDev cd, PlansDev out, int32_t *n_passes, int *counts,            \
                                 int *tickets, const int32_t *live_list, uint32_t *dead_list, const uint32_t *bands, const uint32_t *tight, \
                                 const uint16_t *lo_tab, int lo_pitch, unsigned char *arg_base,                    \
-                                size_t arg_per_group, size_t arg_u8_off, int row_len, int lds_row_entries) {      \
+                                size_t arg_per_group, size_t arg_u8_off, int row_len, int lds_row_entries,        \
+                                int eighths) {                                                                     \
         exact_body<SUM, MODE, kOdd>(tb, cd, out, n_passes, counts, tickets, live_list, dead_list, bands, tight, lo_tab, lo_pitch, \
-                              arg_base, arg_per_group, arg_u8_off, row_len, lds_row_entries);                     \
+                              arg_base, arg_per_group, arg_u8_off, row_len, lds_row_entries, eighths);            \
     }
 HARP_EXACT_KERNEL(k2_exact, __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kExactWaves, kExactWaves))), uint32_t, 1)
 HARP_EXACT_KERNEL(k2_exact_rows, __launch_bounds__(kFastThreads) __attribute__((amdgpu_waves_per_eu(8, 8))), uint32_t, 2)
@@ -653,7 +661,6 @@ HARP_EXACT_KERNEL(k2_exact_wide, __launch_bounds__(kFastThreads), uint64_t, 0)
 void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &out, int32_t *n_passes,
                        void *ws, int n_groups, int n_slices, int n_cu, bool narrow, hipStream_t st) {
     const FastWorkspace w = carve(ws, fast_shape(tb, cd, narrow), n_groups);
-    if (narrow) launch_plan_narrow(tb, cd, out, ws, n_groups, n_cu, st);
     const int full_row = fast_row_len(tb.L);
     const size_t small = exact_small_bytes(cd.S_max);
     // Wavefronts per CU of the first launch and the row entries their LDS share leaves: 24 (six per SIMD, what the
@@ -672,6 +679,15 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
     if (n_waves > n_slices) n_waves = n_slices;
     if (n_waves > cd.C) n_waves = cd.C;
     if (n_waves < 1) n_waves = 1;
+    // The second launch takes the whole batch where narrowed bands leave it three quarters of the candidates, or where
+    // the batch is one round of its workgroups and an eighth have a stage that spans more than 128 cuts, two rounds of
+    // a wavefront's lanes: such a call is as long as its longest candidates, on 256 threads half as long as on 64.
+    // 128 candidates of 240 operators, up to 32 stages 1.74 / 1.17 ms without / with it, of 512 operators 4.1 / 2.0; 1,024
+    // of 640 operators, up to 32 stages 9.5 / 3.6.
+    const bool one_round = cd.C <= n_groups;
+    const int long_row = one_round && entries > 128 ? 128 : entries;
+    const int eighths = !narrow ? 0 : one_round ? 1 : entries < full_row ? 6 : 0;
+    if (narrow) launch_plan_narrow(tb, cd, out, ws, n_groups, n_cu, long_row, st);
     const int lo_p = int(lo_pitch(tb.L));
     const size_t per_group = fast_arg_per_group(tb.L, cd.S_max);
     const size_t u8_off = fast_arg_u16_bytes(tb.L, cd.S_max);
@@ -679,14 +695,14 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
         constexpr bool odd = decltype(odd_t)::value;
         hipLaunchKernelGGL(k2_exact<odd>, dim3(n_waves), dim3(64), small + size_t(entries) * 16, st, tb, cd, out, n_passes,
                            w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.tight, w.lo_tab, lo_p, w.arg, per_group, u8_off,
-                           full_row, entries);
-        if (entries < full_row)
+                           full_row, entries, eighths);
+        if (entries < full_row || eighths > 0)
             hipLaunchKernelGGL(k2_exact_rows<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 16, st,
                                tb, cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.tight, w.lo_tab, lo_p,
-                               w.arg, per_group, u8_off, full_row, full_row);
+                               w.arg, per_group, u8_off, full_row, full_row, eighths);
         hipLaunchKernelGGL(k2_exact_wide<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 32, st, tb,
                            cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.tight, w.lo_tab, lo_p, w.arg,
-                           per_group, u8_off, full_row, full_row);
+                           per_group, u8_off, full_row, full_row, eighths);
     };
     if (tb.odd_degrees()) launch(std::true_type());
     else launch(std::false_type());

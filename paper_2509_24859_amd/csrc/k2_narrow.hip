@@ -172,8 +172,8 @@ struct Chains {
         }
         return at == 0;
     }
-    // Rising ranges to `row`; false, and nothing written, when one is empty.
-    __device__ __forceinline__ bool ranges(uint32_t *row) const {
+    // Rising ranges to `row`, and the cuts of the widest stage; false, and nothing written, when a range is empty.
+    __device__ __forceinline__ bool ranges(uint32_t *row, int &span) const {
         int f = L + 1;
         for (int s = S; s >= 0; --s) {
             const int own = F[s * kCands + q];
@@ -191,8 +191,15 @@ struct Chains {
         }
         if (empty) return false;
         wave_sync();
-        for (int s = r; s <= S; s += 4)
-            row[s] = uint32_t(B[s * kCands + q]) | (uint32_t(F[s * kCands + q]) << 16);
+        for (int s = r; s <= S; s += 4) {
+            const int lo = B[s * kCands + q], hi = F[s * kCands + q];
+            row[s] = uint32_t(lo) | (uint32_t(hi) << 16);
+            if (s < S) {
+                const int w = F[(s + 1) * kCands + q] - lo + 1;
+                span = w > span ? w : span;
+            }
+        }
+        span = quad_max(span);
         return true;
     }
 };
@@ -202,7 +209,7 @@ size_t narrow_lds_bytes(int S_max) {
 }
 
 __global__ __launch_bounds__(64) void k2_narrow(TablesDev tb, CandDev cd, PlansDev out, const int *counts,
-                                                const int32_t *wide_list, const uint32_t *bands, uint32_t *tight,
+                                                int *tickets, int row_entries, const int32_t *wide_list, const uint32_t *bands, uint32_t *tight,
                                                 const uint16_t *lo_tab, const uint16_t *hi_tab, int idx_pitch) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int S_max = cd.S_max, L = tb.L;
@@ -210,6 +217,8 @@ __global__ __launch_bounds__(64) void k2_narrow(TablesDev tb, CandDev cd, PlansD
     uint32_t *tp = ix_row + S_max * kCands;
     uint16_t *F = reinterpret_cast<uint16_t *>(tp + 8), *B = F + (S_max + 1) * kCands;
     const int n_items = counts[kWideBands];
+    if (!bands_narrowed(counts)) return;
+    int too_wide = 0;
     const int lane = threadIdx.x, q = lane >> 2, r = lane & 3;
     if (lane < 8) tp[lane] = lane < tb.n_tp ? uint32_t(tb.tp[lane]) : 1u;
     for (int base = blockIdx.x * kCands; base < n_items; base += gridDim.x * kCands) {
@@ -234,18 +243,33 @@ __global__ __launch_bounds__(64) void k2_narrow(TablesDev tb, CandDev cd, PlansD
         bool through = ch.forward(cap);
         through = through && ch.backward(cap);
         wave_sync();                 // both chains are in LDS
-        if (through && ch.ranges(row)) continue;
+        int span = 0;
+        if (through && ch.ranges(row, span)) {
+            if (r == 0 && span + kPad > row_entries) ++too_wide;
+            continue;
+        }
         // (cannot happen: the min-max plan is a plan under t_E)
         const uint32_t *wide = bands + int64_t(c) * (S_max + 1);
         for (int s = r; s <= ch.S; s += 4) row[s] = wide[s];
     }
+    too_wide = int(wave_all(uint32_t(too_wide), sum2));
+    if (too_wide != 0 && lane == 0) atomicAdd(tickets + (blockIdx.x & (kShares - 1)) * kShareInts + kLongRows, too_wide);
 }
 
 }  // namespace
 
-// Behind launch_plan_fast, on its workspace and results.
+// Narrowing costs a chain of some 3 to 5 us a stage whatever the batch, and gains where a stage has cuts to lose.
+// Exact search without / with it: 128 operators, up to 16 stages, 4,096 candidates 0.42 / 0.46 ms; 160 operators, up to
+// 32 stages, 32,768 candidates 2.71 / 2.52; 300 operators, up to 128 stages, 4,096 candidates 2.4 / 3.0: five operators
+// a stage divide the last two.  A batch that the chip works in one round has the whole chain to bear: 512 candidates
+// of 160 operators and up to 32 stages 0.49 / 0.57.
+bool exact_narrows(int L, int S_max, int C, int n_cu) {
+    return L >= 144 && L >= (C > 8 * n_cu ? 5 : 6) * S_max;
+}
+
+// Behind launch_plan_fast, on its workspace and results.  row_entries: candidates with a stage that spans more are counted.
 void launch_plan_narrow(const TablesDev &tb, const CandDev &cd, const PlansDev &out, void *ws, int n_slices, int n_cu,
-                        hipStream_t st) {
+                        int row_entries, hipStream_t st) {
     const FastWorkspace w = carve(ws, fast_shape(tb, cd, true), n_slices);
     const size_t lds = narrow_lds_bytes(cd.S_max);
     int per_cu = int((size_t(160) << 10) / (lds + 128));
@@ -254,8 +278,8 @@ void launch_plan_narrow(const TablesDev &tb, const CandDev &cd, const PlansDev &
     if (grid > (long long)per_cu * n_cu) grid = (long long)per_cu * n_cu;
     const long long idx_rows = (long long)lo_n_max(tb.L, cd.S_max, tb.M) * tb.T * tb.n_tp;
     const int idx_pitch = int(lo_pitch(tb.L));
-    hipLaunchKernelGGL(k2_narrow, dim3(unsigned(grid)), dim3(64), lds, st, tb, cd, out, w.counts, w.wide_list, w.bands,
-                       w.tight, w.lo_tab, w.lo_tab + idx_rows * idx_pitch, idx_pitch);
+    hipLaunchKernelGGL(k2_narrow, dim3(unsigned(grid)), dim3(64), lds, st, tb, cd, out, w.counts, w.tickets, row_entries,
+                       w.wide_list, w.bands, w.tight, w.lo_tab, w.lo_tab + idx_rows * idx_pitch, idx_pitch);
 }
 
 }  // namespace harp
