@@ -182,7 +182,8 @@ typedef struct {
  * measurements.  HARP_ERR_INVALID_ARG on an unknown value. */
 int harp_set_plan_path(harp_ctx *ctx, int path);
 
-/* Bytes of DEVICE workspace harp_plan_batch needs for this batch (0 on malformed arguments). */
+/* Bytes of DEVICE workspace that harp_plan_batch, harp_plan_exact_batch and harp_plan_h1f1b_batch need for this
+ * batch, the most of the three (0 on malformed arguments). */
 size_t harp_plan_workspace_bytes(harp_ctx *ctx, const harp_tables *tables,
                                  const harp_candidates *cands);
 

@@ -396,10 +396,13 @@ int harp_set_plan_path(harp_ctx *ctx, int path) {
     return HARP_OK;
 }
 
-size_t harp_plan_workspace_bytes(harp_ctx *ctx, const harp_tables *t, const harp_candidates *cd) {
-    if (!ctx || !t || !cd || cd->C < 0 || cd->S_max < 1 || cd->S_max > kMaxStages) return 0;
-    if (t->dev.L > HARP_MAX_L_PLAN) return 0;
-    // sized for whichever path may run, so that the answer does not depend on the build verdict
+}  // extern "C"
+
+namespace {
+
+// Workspace of the candidate planners: sized for whichever path may run, so that it does not depend on the build
+// verdict.  narrow: with the area of the exact search's narrowed bands.
+size_t plan_workspace(const harp_ctx *ctx, const harp_tables *t, const harp_candidates *cd, bool narrow) {
     const int C = cd->C;
     const size_t per_group = plan_generic_ws_per_group(t->dev.L, cd->S_max) >
                                      plan_generic_h1f1b_ws_per_group(t->dev.L, cd->S_max)
@@ -409,12 +412,17 @@ size_t harp_plan_workspace_bytes(harp_ctx *ctx, const harp_tables *t, const harp
     if (fast_batch_ok(t, cd)) gen += plan_fast_ws_bytes(t->dev, cd->S_max, C, 0, false);
     size_t fast = 0;
     if (t->lim.want_fast && fast_batch_ok(t, cd))
-        fast = plan_fast_ws_bytes(t->dev, cd->S_max, C, n_fast_slices(ctx, C, t->dev.L, cd->S_max),
-                                  exact_narrows(t->dev.L, cd->S_max, C, ctx->n_cu));
+        fast = plan_fast_ws_bytes(t->dev, cd->S_max, C, n_fast_slices(ctx, C, t->dev.L, cd->S_max), narrow);
     return (gen > fast ? gen : fast) + 256;
 }
 
-}  // extern "C"
+}  // namespace
+
+extern "C" size_t harp_plan_workspace_bytes(harp_ctx *ctx, const harp_tables *t, const harp_candidates *cd) {
+    if (!ctx || !t || !cd || cd->C < 0 || cd->S_max < 1 || cd->S_max > kMaxStages) return 0;
+    if (t->dev.L > HARP_MAX_L_PLAN) return 0;
+    return plan_workspace(ctx, t, cd, exact_narrows(t->dev.L, cd->S_max, cd->C, ctx->n_cu));
+}
 
 namespace {
 
@@ -424,6 +432,7 @@ struct PlanCall {
     CandDev c;
     PlansDev o;
     bool fast;
+    bool narrow;     // exact search: bands are narrowed
     bool banded;     // int64 path: the min-max planner runs behind the pre-pass (the index fits)
     int groups;      // workgroups of the one-candidate-per-workgroup kernels
     int slices;      // back-pointer slices of the 32-bit path (>= groups, a multiple of kFastWaves)
@@ -431,10 +440,11 @@ struct PlanCall {
 };
 
 // limit_bytes: the memory at hand.  With shrink the unit count is cut down to what fits (the
-// static-scratch entry point); without, the full resident count must fit.
+// static-scratch entry point); without, the full resident count must fit.  exact: the exact search, whose
+// narrowed bands must fit as well.
 int plan_prepare(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const harp_plans *out,
                  bool extra_null, bool whole_rows, const void *workspace, size_t limit_bytes, bool shrink,
-                 void *hip_stream, PlanCall &pc) {
+                 bool exact, void *hip_stream, PlanCall &pc) {
     int rc = check_batch(ctx, t, cd);
     if (rc != HARP_OK) return rc;
     if (!out || extra_null ||
@@ -448,6 +458,7 @@ int plan_prepare(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const
     pc.fast = use_fast(ctx, t, cd, whole_rows);
     // a batch of odd degrees that only the int64 path's smaller slices leave room for runs there
     if (shrink && pc.fast && t->odd32 && plan_bytes_on_path(t, cd, true, kFastWaves) > limit_bytes) pc.fast = false;
+    pc.narrow = exact && pc.fast && exact_narrows(t->dev.L, cd->S_max, cd->C, ctx->n_cu);
     pc.banded = !pc.fast && fast_batch_ok(t, cd);
     pc.groups = n_plan_groups(ctx, cd->C, pc.fast, t->dev.L, cd->S_max);
     pc.slices = pc.fast ? n_fast_slices(ctx, cd->C, t->dev.L, cd->S_max) : pc.groups;
@@ -456,7 +467,7 @@ int plan_prepare(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
         return fail(ctx, HARP_ERR_WORKSPACE, "workspace must be a 256-byte aligned device pointer");
     if (!shrink) {
-        const size_t need = harp_plan_workspace_bytes(ctx, t, cd);
+        const size_t need = plan_workspace(ctx, t, cd, pc.narrow);
         if (limit_bytes < need)
             return fail(ctx, HARP_ERR_WORKSPACE, "workspace holds %zu bytes, %zu needed", limit_bytes, need);
     } else {
@@ -476,8 +487,8 @@ int plan_prepare(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const
     return HARP_OK;
 }
 
-int plan_minmax(harp_ctx *ctx, harp_tables *t, const PlanCall &pc, void *ws, bool narrow, unsigned long long *work) {
-    if (pc.fast) launch_plan_fast(t->dev, pc.c, pc.o, ws, pc.slices, ctx->n_cu, narrow, work, pc.st);
+int plan_minmax(harp_ctx *ctx, harp_tables *t, const PlanCall &pc, void *ws, unsigned long long *work) {
+    if (pc.fast) launch_plan_fast(t->dev, pc.c, pc.o, ws, pc.slices, ctx->n_cu, pc.narrow, work, pc.st);
     else launch_plan_generic(t->dev, pc.c, pc.o, ws, pc.groups, pc.banded, pc.st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the planner kernel");
@@ -491,44 +502,43 @@ extern "C" {
 int harp_plan_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const harp_plans *out,
                     void *workspace, size_t workspace_bytes, void *hip_stream) {
     PlanCall pc;
-    const int rc = plan_prepare(ctx, t, cd, out, false, false, workspace, workspace_bytes, false, hip_stream, pc);
+    const int rc = plan_prepare(ctx, t, cd, out, false, false, workspace, workspace_bytes, false, false, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
-    return plan_minmax(ctx, t, pc, workspace, false, nullptr);
+    return plan_minmax(ctx, t, pc, workspace, nullptr);
 }
 
 int harp_plan_batch_static(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const harp_plans *out,
                            void *hip_stream) {
     PlanCall pc;
     const int rc = plan_prepare(ctx, t, cd, out, false, false, ctx ? ctx->scratch : nullptr,
-                                size_t(HARP_STATIC_SCRATCH_BYTES) + kTicketBytes, true, hip_stream, pc);
+                                size_t(HARP_STATIC_SCRATCH_BYTES) + kTicketBytes, true, false, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
-    return plan_minmax(ctx, t, pc, ctx->scratch, false, nullptr);
+    return plan_minmax(ctx, t, pc, ctx->scratch, nullptr);
 }
 
 int harp_plan_batch_count_work(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const harp_plans *out,
                                void *workspace, size_t workspace_bytes, uint64_t *work, void *hip_stream) {
     PlanCall pc;
-    const int rc = plan_prepare(ctx, t, cd, out, work == nullptr, false, workspace, workspace_bytes, false, hip_stream,
+    const int rc = plan_prepare(ctx, t, cd, out, work == nullptr, false, workspace, workspace_bytes, false, false, hip_stream,
                                 pc);
     if (rc != HARP_OK) return rc;
     if (!pc.fast || !t->fast32)
         return fail(ctx, HARP_ERR_UNIMPLEMENTED, "work is counted on the 32-bit path only");
     launch_clear_work(reinterpret_cast<unsigned long long *>(work), pc.st);
     if (cd->C == 0) return HARP_OK;
-    return plan_minmax(ctx, t, pc, workspace, false, reinterpret_cast<unsigned long long *>(work));
+    return plan_minmax(ctx, t, pc, workspace, reinterpret_cast<unsigned long long *>(work));
 }
 
 int harp_plan_exact_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const harp_plans *out,
                           int32_t *n_passes, void *workspace, size_t workspace_bytes, void *hip_stream) {
     PlanCall pc;
     // (the exact search's two rows of 8- or 16-byte entries fit LDS for every L of the 32-bit tables)
-    int rc = plan_prepare(ctx, t, cd, out, false, false, workspace, workspace_bytes, false, hip_stream, pc);
+    int rc = plan_prepare(ctx, t, cd, out, false, false, workspace, workspace_bytes, false, true, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
     if (pc.fast) {
-        const bool narrow = exact_narrows(t->dev.L, cd->S_max, cd->C, ctx->n_cu);
-        rc = plan_minmax(ctx, t, pc, workspace, narrow, nullptr);
+        rc = plan_minmax(ctx, t, pc, workspace, nullptr);
         if (rc != HARP_OK) return rc;
-        launch_plan_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.slices, ctx->n_cu, narrow, pc.st);
+        launch_plan_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.slices, ctx->n_cu, pc.narrow, pc.st);
     } else {
         launch_plan_generic_exact(t->dev, pc.c, pc.o, n_passes, workspace, pc.groups, pc.banded, pc.st);
     }
@@ -542,7 +552,7 @@ int harp_plan_h1f1b_batch(harp_ctx *ctx, harp_tables *t, const harp_candidates *
                           void *hip_stream) {
     PlanCall pc;
     const int rc = plan_prepare(ctx, t, cd, out, cd && cd->C > 0 && (!warmup || !t_max), true, workspace,
-                                workspace_bytes, false, hip_stream, pc);
+                                workspace_bytes, false, false, hip_stream, pc);
     if (rc != HARP_OK || cd->C == 0) return rc;
     if (pc.fast) launch_plan_h1f1b(t->dev, pc.c, t_max, pc.o, warmup, workspace, pc.groups, pc.slices, ctx->n_cu, pc.st);
     else launch_plan_generic_h1f1b(t->dev, pc.c, t_max, pc.o, warmup, workspace, pc.groups, pc.banded, pc.st);

@@ -201,6 +201,30 @@ def test_sequences_beyond_the_feasibility_index(harp, ctx):
         assert_plans_equal(got, want, "L = %d without the index" % L)
 
 
+def test_workspace_without_narrowed_bands(harp, ctx):
+    """The exact search keeps a second set of bands for long sequences.  harp_plan_workspace_bytes counts it; planners
+    that do not use it take a workspace without it, and it is the exact search that refuses one."""
+    import torch
+    rng = np.random.default_rng(50)
+    L, C, S_max = 160, 40000, 8
+    p = simple_problem(rng.integers(1, 100, size=L), M=7, G=2, ndev=(8, 8), tp=(1, 2), act=rng.integers(0, 2000, size=L),
+                       bw=[[100, 7], [7, 90]])
+    cands = W.make_candidates(p, 3, 78, 2, S_max, 0, 64).take(np.arange(C) % 64)
+    tables, dc, out = harp.Tables(ctx, p), harp.DeviceCandidates(ctx, cands), harp.DevicePlans(ctx, C, S_max)
+    full = harp.plan_workspace(ctx, tables, dc)
+    less = full[:full.numel() - 4 * C * (S_max + 2)]                   # a list and a row of bands per candidate
+    caps, warm = torch.full((C,), 10 ** 6, device=ctx.device), torch.zeros((C, S_max), dtype=torch.int32, device=ctx.device)
+    harp.harp_plan_batch(ctx, tables, dc, out, less)
+    want = out.to_host()
+    harp.harp_plan_batch(ctx, tables, dc, out, full)
+    assert_plans_equal(out.to_host(), want, "min-max")
+    harp.harp_plan_h1f1b_batch(ctx, tables, dc, caps, out, warm, less)
+    with pytest.raises(harp.HarpError) as e:
+        harp.harp_plan_exact_batch(ctx, tables, dc, out, less)
+    assert e.value.code == harp.ERR_WORKSPACE
+    harp.harp_plan_exact_batch(ctx, tables, dc, out, full)
+
+
 def test_argument_errors_of_the_newer_entry_points(harp, ctx):
     """Every planner entry point refuses a short or misaligned workspace, null arrays and shapes
     beyond its limits with an error code, and launches nothing."""
