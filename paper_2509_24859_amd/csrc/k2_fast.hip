@@ -120,11 +120,14 @@ __global__ __launch_bounds__(256) void k2_index(TablesDev tb, uint16_t *lo_tab, 
 constexpr int kBandTypeTable = 2048;    // GPU type and size of every group kept in LDS when G is at most this
 constexpr uint16_t kBadSlot = 0xFFFFu;
 
-// Candidates per workgroup: what leaves room for two workgroups' tiles on a CU, and of that no more than gives every
-// CU a workgroup (16,384 candidates of 82 operators on 64 workgroups of 256 left three CUs in four idle).
+// Threads (and candidates) per workgroup: what leaves room for two workgroups' tiles on a CU, and of that no more than
+// gives 256 CUs a workgroup each: a batch of one workgroup keeps them all for the reading of its slots and group types.
+// us with 64 / 256 threads: 16,384 candidates of up to 64 stages 92.8 / 99.3, of up to 16 26.4 / 25.6; 64 candidates of
+// up to 64 stages 95.3 / 77.2, of up to 8 14.3 / 11.9.
+constexpr int kBandSpread = 256;
 int band_threads(int S_max, int C) {
     int threads = S_max <= 64 ? 256 : (S_max <= 128 ? 128 : 64);
-    while (threads > 64 && C < 256 * threads) threads /= 2;
+    while (threads > 64 && C > 64 && C < kBandSpread * threads) threads /= 2;
     return threads;
 }
 
