@@ -39,6 +39,7 @@ using namespace fastdp;
 
 namespace {
 
+constexpr size_t kLdsGranule = 1280;     // LDS is allocated in units of this many bytes
 constexpr int kTail = 4;     // spare entries behind a row: a group of four may overrun the band
 
 template <typename SumT> struct H1Traits;
@@ -73,9 +74,9 @@ __device__ __forceinline__ uint32_t h1f1b_delta(uint32_t c, int64_t cap) {
 }
 
 // LDS in front of the rows: per-slot constants, two scalars, band and trial cuts, two flags, the
-// wavefronts' ranges of finite sums, index-row offsets, the plan's deltas, slot lists
+// wavefronts' ranges of finite sums, index-row offsets, the plan's deltas
 __host__ __device__ inline size_t h1f1b_small_bytes(int S_max) {
-    const size_t b = size_t(S_max) * sizeof(StageConst) + 16 + size_t(S_max + 1) * 8 + 8 + 64 + size_t(S_max) * 11;
+    const size_t b = size_t(S_max) * sizeof(StageConst) + 16 + size_t(S_max + 1) * 8 + 8 + 64 + size_t(S_max) * 8;
     return (b + 15) & ~size_t(15);
 }
 // bytes per cut of the rows in LDS when every row is sized for one slot: one row of memory sums, two
@@ -116,15 +117,12 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
     int32_t *fin_w = reinterpret_cast<int32_t *>(flags + 2);                           // [2][4][2]: per slot parity and wavefront, lowest and highest cell with a finite sum
     uint32_t *hi_off = reinterpret_cast<uint32_t *>(fin_w + 16);                       // [S_max]
     uint32_t *deltas = hi_off + S_max;                                                 // [S_max]
-    uint16_t *slot_g = reinterpret_cast<uint16_t *>(deltas + S_max);                   // [S_max]
-    uint8_t *slot_k = reinterpret_cast<uint8_t *>(slot_g + S_max);                     // [S_max]
     // Rows of row_len entries.  Whole-sequence form: one row of memory sums, two of entries, two of
     // times; entry x of a row is cut x.  Slot-sized form: a row's entry 0 is the lowest cut of the
     // slot it serves, and the memory sums and times of the slot in front take the place of this
     // slot's once its cells are done (one wavefront: its LDS operations execute in order).
     MemPair *mem0 = reinterpret_cast<MemPair *>(lds_raw + h1f1b_small_bytes(S_max));
-    MemPair *mem1 = mem0;
-    Entry *rows0 = reinterpret_cast<Entry *>(mem1 + row_len);
+    Entry *rows0 = reinterpret_cast<Entry *>(mem0 + row_len);
     Entry *rows1 = rows0 + row_len;
     uint32_t *prow0 = reinterpret_cast<uint32_t *>(rows1 + row_len);
     uint32_t *prow1 = kBandRows ? prow0 : prow0 + row_len;
@@ -175,8 +173,6 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             for (int s = tid; s < S; s += nthreads) {
                 const int g = grp[s], k = tp_index(tb, tpv[s]);
                 const int g_next = s + 1 < S ? grp[s + 1] : g;
-                slot_g[s] = (uint16_t)g;
-                slot_k[s] = (uint8_t)k;
                 sc[s].cap = int64_t(tb.tp[k]) * tb.type_mem[tb.group_type[g]];
                 sc[s].p_row = uint32_t((int64_t(g) * tb.n_tp + k) * tb.pitch32);
                 sc[s].cm_row_shift = uint32_t((int64_t(g) * tb.G + g_next) * tb.pitch32) |
@@ -287,8 +283,8 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             // staged for the slot in front at nl
             const uint32_t *pr_cur = (pcur ? prow1 : prow0) - (kBandRows ? il : 0);
             uint32_t *pr_next = (pcur ? prow0 : prow1) - (kBandRows ? nl : 0);
-            const MemPair *mem = (pcur ? mem1 : mem0) - (kBandRows ? il : 0);
-            MemPair *mem_next = (pcur ? mem0 : mem1) - (kBandRows ? nl : 0);
+            const MemPair *mem = mem0 - (kBandRows ? il : 0);
+            MemPair *mem_next = mem0 - (kBandRows ? nl : 0);
             const Entry *prev = (cur ? rows1 : rows0) - (kBandRows ? jl : 0);
             Entry *next = (cur ? rows0 : rows1) - (kBandRows ? il : 0);
             // the cut in front of this slot's stage (between slot - 1 and slot)
@@ -499,14 +495,15 @@ void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_
     const size_t per_group = fast_arg_per_group(tb.L, cd.S_max);
     const int arg_pitch = fast_row_len(tb.L);
     // Wavefronts per CU of the first launch and the row entries their LDS share leaves: as many
-    // wavefronts as hold rows for the whole sequence, between 14 and 24 (six per SIMD, what the registers
-    // allow; fewer hide less of the latency: 160 operators, five per SIMD 1.61 ms, six 1.47, seven 1.54 with
-    // spills).  The smaller the share, the more candidates leave for the second launch: 300 operators, 14 per
+    // wavefronts as hold rows for the whole sequence, between 14 and 24 (six per SIMD, held to 80 registers with 2 of
+    // them spilled; fewer hide less of the latency: 160 operators, five per SIMD 1.61 ms, six 1.47, seven 1.54 with
+    // more spills).  Shares are whole units of allocation: 28 bytes beyond nine of them leave room for 12 wavefronts
+    // instead of 14 (512 operators, tight memory 2.01 ms for 1.87).  The smaller the share, the more candidates leave for the second launch: 300 operators, 14 per
     // CU 3.7 ms, 17 3.7, 20 4.9; 512 operators, tight memory 1.90, 1.88, 1.92, loose memory 14.1 for all.
     const size_t small = h1f1b_small_bytes(cd.S_max);
     int per_cu = int((size_t(160) << 10) / (small + size_t(row_len) * h1f1b_cut_bytes(8) + 128));
     per_cu = per_cu < 14 ? 14 : (per_cu > 24 ? 24 : per_cu);
-    const size_t share = ((size_t(160) << 10) / per_cu - 128) & ~size_t(15);
+    const size_t share = (size_t(160) << 10) / per_cu / kLdsGranule * kLdsGranule;
     int entries = share > small + h1f1b_cut_bytes(8) * 16 ? int((share - small) / h1f1b_cut_bytes(8)) & ~1 : 16;
     if (entries > row_len) entries = row_len;
     int n_waves = per_cu * n_cu;
