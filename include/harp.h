@@ -143,7 +143,10 @@ int harp_tables_finalize(harp_ctx *ctx, harp_tables *tables);
  * its feasibility index (two tables of min(S_max, M, L) * T * n_tp rows of L + 1 16-bit entries)
  * stays within 256 MiB as well.  The min-max planner and the exact search use it for every such L;
  * the H-1F1B planner and the submesh planners, whose 32-bit kernels keep whole rows of several
- * arrays in LDS, use it up to L = 1024 and run on the int64 path beyond. */
+ * arrays in LDS, use it up to L = 1024 and run on the int64 path beyond.  Tables with other degrees
+ * have the 32-bit rows and cut times as well (and their share of harp_tables_bytes and of the build):
+ * harp_plan_batch, harp_plan_exact_batch and harp_plan_h1f1b_batch take them there by themselves, everything
+ * else runs in int64, and this stays 0. */
 int harp_tables_fast32(const harp_tables *tables);
 
 /* DEVICE pointers into the table buffer, for inspection: running sums indexed [row][i],

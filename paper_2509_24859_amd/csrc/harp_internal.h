@@ -33,8 +33,9 @@ struct BuildHeader {
 //   d = 1:              add 1,     mul 2^32 - 1,            shift 0   (floor(x (1 - 2^-32)) = x - 1 for x >= 1)
 //   d = 2^l, l >= 1:    add d - 1, mul 2^31,                shift l - 1
 //   else, 2^l < d:      add d - 1, mul ceil(2^(32 + l) / d), shift l
-// give ceil = umulhi(x + add, mul) >> shift: mul d exceeds 2^(32 + l) by less than d < 2^(l + 1), which
-// times x < 2^31 stays below 2^(32 + l), one unit of the quotient's last place.
+// give ceil = umulhi(x + add, mul) >> shift: mul d exceeds 2^(32 + l) by e <= d - 1 <= 2^(l + 1) - 2, and e x stays below
+// 2^(32 + l), one unit of the quotient's last place, for every x below 2^31 (1 + 2^-l).  The key rows of the exact search
+// need the margin: their quotients go up to x = 2^31 + d - 2, and with l <= 15 there are 2^31 2^-l >= 2^16 > d to spare.
 struct TpDiv {
     uint32_t add, mul;
     int32_t shift;

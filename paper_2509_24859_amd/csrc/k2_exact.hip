@@ -35,7 +35,7 @@
 // a sum.  Candidates with U >= 2^31 (iterations of more than half an hour) are queued and redone
 // by the same kernel instantiated with 64-bit sums.
 //
-// Three launches.  k2_exact works a candidate per wavefront (64-thread workgroups, 24 per CU): a
+// Three launches.  k2_exact works a candidate per wavefront (64-thread workgroups, 18 to 24 per CU): a
 // DP row is 77 cuts wide on the 512-operator workload, so a 256-thread workgroup per candidate left
 // three wavefronts in four idle at every stage's barrier.  Its two LDS rows hold the cuts of one
 // stage only (row s starts at B[s], sized for the candidate's widest stage), and what is left of the
@@ -115,7 +115,7 @@ __host__ __device__ inline size_t exact_small_bytes(int S_max) {
 // infinite sum, never gives a quotient as low as U.  The others keep the sums.
 // 65,536 candidates of 160 operators, 16 to 32 stages, the whole call: 3.83 -> 3.68 ms with 5 wavefronts per SIMD, which
 // vector issue then no longer fills (69% of the rate; the wait for a trip's entries shows), 3.47 with 6, 3.50 with 7.
-constexpr int kExactWaves = 6;           // wavefronts per SIMD of k2_exact, registers held to that
+constexpr int kExactWaves = 6;           // wavefronts per SIMD of k2_exact: registers held to 80, 4 of them spilled to scratch
 constexpr int64_t kKeyLimit = int64_t(1) << 30;
 constexpr int32_t kNoKey = INT32_MAX;
 __device__ __forceinline__ int32_t least(int32_t a, int32_t b) { return a < b ? a : b; }

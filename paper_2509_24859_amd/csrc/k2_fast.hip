@@ -40,7 +40,7 @@
 // per-link cut table built beside the rows.
 //
 // Mapping of k2_fast: one wavefront per live candidate at a time (persistent wavefronts draw from
-// the list k2_band compacted through a shared counter; the wavefronts of a workgroup share nothing
+// the list k2_band compacted, 64 counters deal it out; the wavefronts of a workgroup share nothing
 // and never meet at a barrier), one lane per DP cell of the current stage's band, 64 cells per
 // chunk.  The DP row and the stage's fused time row sit interleaved in LDS, one 8-byte entry per
 // cut, in a single buffer: chunks are taken from the top of the band downwards and a cell only

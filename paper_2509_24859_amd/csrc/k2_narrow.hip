@@ -21,7 +21,8 @@
 // and of the cut row), so that a step is one round trip to L2 for a window of 16 cuts.  A chain of S dependent
 // steps is bound by their latency; fewer lanes per candidate put more candidates in flight.
 // 65,536 candidates of 160 operators, 16 to 32 stages: 78 cuts a row -> about 50; this launch takes 0.13 ms and
-// takes k2_exact from 3.11 to 2.62 ms.  Not used for the min-max planner, where the cap has to be searched for
+// takes k2_exact from 3.11 to 2.62 ms; 131,072 of 512 operators, up to 64 stages, tight memory: the call 8.6 -> 7.6 ms.
+// Not used for the min-max planner, where the cap has to be searched for
 // (1.5 to 4 chains a candidate, as many as the slowest of 16 needs: 0.29 to 2.2 ms for 0.13 to 0.27 ms less in
 // k2_fast), nor for H-1F1B under a given cap (0.13 ms for 0.10).
 #include "fast_common.h"

@@ -25,7 +25,8 @@ namespace slotdp {
 using fastdp::uniform;
 using fastdp::wave_sync;
 
-// 64 candidates of 82 operators and 8 to 16 stages, ms: 256 threads 1.20, 512 0.94, 1,024 0.97.
+// 64 candidates of 82 operators and 8 to 16 stages, ms: 256 threads 1.20, 512 0.94, 1,024 0.97; 4 of those 0.63, 0.60,
+// 0.63; 16 of 12 operators 0.087, 0.092, 0.103; 16 of 300 operators and up to 32 stages 12.6, 8.2, 6.3; 8 of 512 8.4, 6.4, 6.0.
 constexpr int kThreads = 512;
 constexpr int kTeams = kThreads / 64;            // chains worked at once, by one wavefront each
 constexpr int kPart = 8;                         // lanes per cell
@@ -65,7 +66,9 @@ inline SlotShape slot_shape(int L, int S_max) {
 template <bool kResident>
 struct Slots {
     static constexpr bool kChoosesSlicing = false;
-    static constexpr int kMaxClimb = 256, kMaxTries = 24;    // see k2_sweep.hip
+    // see k2_sweep.hip; a climb passes over the values that change nothing and takes 1 to 3 passes, so kMaxClimb is a
+    // bound for constructed inputs, where each of many operators of a few microseconds changes something
+    static constexpr int kMaxClimb = 256, kMaxTries = 24;
     struct alignas(16) Stage { uint32_t row_at, cut_at; int32_t tp, shift; };
     const TablesDev &tb;
     const SlotShape &sh;
