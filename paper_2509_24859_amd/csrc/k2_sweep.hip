@@ -690,11 +690,11 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
             } else if (!kWalk && state == kAtTop) {
                 hi = top;
                 step = (t_S >> 4) + 1u;
-                // (lo >= hi: the pass at t_S has no plan up to the largest value; the recurrence can miss what the
-                // least-count pass says exists)
-                if (!found || lo >= hi) state = kNoPlan;
+                // (lo may lie above hi: the pass at t_S may hold for every value there is, and the recurrence can miss
+                // what the least-count pass says exists)
+                if (!found) state = kNoPlan;
                 else if (lo + step < hi) { cap = lo + uint32_t(step); state = kGallop; }
-                else if (hi - lo > 1u + (hi >> 12)) { cap = lo + (hi - lo) / 2u; state = kBisect; }
+                else if (lo + (1ull + (hi >> 12)) < hi) { cap = lo + (hi - lo) / 2u; state = kBisect; }
                 else climb_on = true;
             } else if (!kWalk && (state == kGallop || state == kBisect)) {
                 if (found) hi = cap; else lo = b.same_up_to(cap);
