@@ -366,3 +366,28 @@ def test_exact_share_of_a_wavefront(harp, ctx, L, S_max, memory, left):
         assert (passes.cpu().numpy() == want_passes[which]).all(), C
         if C == 2200: assert (queued + long_rows > 0) == bool(left), (queued, long_rows)
         elif L == 400: assert long_rows > 0 and queued == 0
+
+
+@pytest.mark.parametrize("n_wide", [2, 30], ids=["few", "many"])
+def test_exact_with_few_wide_candidates(harp, ctx, n_wide):
+    """A batch narrows the bands of its wide candidates only where they are a quarter of the live ones; listed or not,
+    narrowed or not, they get the plans and passes of the int64 kernels."""
+    import torch
+    rng = np.random.default_rng(5)
+    L, S_max, C = 156, 25, 40
+    fwd = rng.integers(200, 900, size=(1, L))
+    p = simple_problem(np.zeros(L), M=40, G=2, ndev=(40, 40), tp=(1, 8), fwd=fwd, bwd=2 * fwd, act=rng.integers(8, 65, size=L) * 100,
+                       params=np.full(L, 1000), stash=np.full(L, 20), bw=[[9000, 90], [90, 9000]])
+    p.type_mem_bytes[:] = int(1.25 * (L * 1000 + 12 * L * 20) / 25)
+    tight = [[(g, 1)] * 13 + [(1 - g, 1)] * 12 for g in (0, 1)]       # little room beyond what the stages need
+    loose = [[(g, 8)] * 2 + [(1 - g, 8)] * (2 + g) for g in (0, 1)]    # eight times the memory a stage
+    cands = cands_from_lists([loose[c % 2] if c % 20 < n_wide // 2 else tight[c % 2] for c in range(C)], S_max=S_max)
+    want, want_passes, _ = harp.plan_exact(ctx, p, cands, harp.PATH_GENERIC)
+    assert (want.status == oracle.OK).all()
+    tables, dc, out = harp.Tables(ctx, p), harp.DeviceCandidates(ctx, cands), harp.DevicePlans(ctx, C, S_max)
+    ws, passes = harp.plan_workspace(ctx, tables, dc), torch.full((C,), -7, dtype=torch.int32, device=ctx.device)
+    harp.harp_plan_exact_batch(ctx, tables, dc, out, ws, passes)
+    live, wide = int(ws[:64].view(torch.int32)[0]), int(ws[:64].view(torch.int32)[12])
+    assert live == C and 0 < wide and (4 * wide >= live) == (n_wide == 30), (live, wide)
+    assert_plans_equal(out.to_host(), want, "%d wide" % wide)
+    assert (passes.cpu().numpy() == want_passes).all()
