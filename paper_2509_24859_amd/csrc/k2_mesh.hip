@@ -332,10 +332,9 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE); continue; }
         auto hand_over = [&]() { if (tid == 0) ba.redo[atomicAdd(&ba.counters[1], 1)] = c; };
         if (verdict == 3) { hand_over(); continue; }
-        const int64_t opening = b.bracket();
-        if (opening < 0) { fail(HARP_CAND_INFEASIBLE); continue; }
         int form = Band::kMinMax, tries = 0, passes = 0;
-        uint32_t cap = uint32_t(opening);
+        uint32_t cap = b.guess();
+        bool guessed = true;
         int64_t t_S = 0, best_T = kInf, best_b = kInf;
         bool keys_fit = true;
         bool over = false;
@@ -344,7 +343,14 @@ __global__ __launch_bounds__(1024) void k2_mesh_band(TablesDev tb, OrdDev od, Pl
             const int64_t v = b.template run<kExact ? Band::kMinMax | Band::kSum : Band::kMinMax>(form, cap);
             if (v == kInf) {
                 if (form == Band::kSum || cap >= meshband::kTopCap) break;     // (a sum cannot fail at or above t_S)
-                cap = Band::raised(cap, tries++);
+                if (guessed && !b.reached) {
+                    const int64_t next = b.bracket(cap);
+                    if (next < 0) break;
+                    cap = uint32_t(next);
+                } else {
+                    cap = Band::raised(cap, tries++);
+                }
+                guessed = false;
                 continue;
             }
             b.find_plan(form == Band::kSum, uint32_t(v), cap);
@@ -487,7 +493,7 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     sh.o_group_at = take(size_t(sh.cols) * 2);
     const bool sums = form == kFormSum || form == kFormSweep, h1 = form == kFormH1 || form == kFormSweep;
     sh.o_mem = take(h1 ? size_t(sh.W) * 16 : 0);
-    sh.o_chain = take(size_t(kTeams) * sh.cols * 2);
+    sh.o_chain = take(size_t(kTeams) * 2 * (sh.cols + 1) * 2);
     sh.o_ok = take(size_t(kTeams) * 2 * sh.K_cap * sh.NW * 8);
     sh.o_col = take(size_t(sh.cols) * 24);
     sh.o_small = take(32 + size_t(sh.S_cap + 1) * 12 + size_t(sh.S_cap) * 11);
@@ -499,25 +505,17 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     sets = sets < least ? least : sets;
     sh.set_cap = int(sets < size_t(sh.K_cap) ? sets : size_t(sh.K_cap));
     sh.o_use = take(size_t(sh.set_cap) * 4);
-    sh.o_prow = take(size_t(sh.set_cap) * per_set / 2 + 16);
-    sh.o_reach = take(size_t(sh.set_cap) * per_set / 2);
+    sh.o_prow = take(16 + size_t(sh.set_cap) * per_set);
     // bytes per cell: two value rows; or one and the key rows; or two rows of sums and counts; and the map
-    const size_t value_rows = sums && tb.n_tp > 1 ? 1 + size_t(tb.n_tp) : 2;
-    const size_t per_cell = value_rows * 4 + (h1 ? 4 : 0) + 2;
-    size_t room = budget > off ? budget - off : 0;
-    const size_t want = size_t(sh.K_cap) > 1024 ? size_t(sh.K_cap) : 1024;        // the map also numbers the sets
-    if (room < want * per_cell + 128) room = want * per_cell + 128;
-    if (off + room > kBandLds) return false;
-    size_t cells = (room - 128) / per_cell;
-    const size_t all = size_t(sh.cols) * sh.W;
-    cells = cells > all && all >= want ? all : cells;
-    sh.row_cap = int(cells & ~size_t(7));
-    const size_t row = size_t(sh.row_cap) + kRowPad;
-    sh.o_rows = take(value_rows * row * 4);
-    sh.o_count = take(h1 ? 2 * row * 2 : 0);
-    sh.o_map = take(size_t(sh.row_cap) * 2);
-    sh.total = uint32_t(off);
-    return off <= kBandLds;
+    sh.value_rows = sums && tb.n_tp > 1 ? 1 + tb.n_tp : 2;
+    sh.cell_bytes = sh.value_rows * 4 + (h1 ? 4 : 0) + 2;
+    // the rest of the budget holds rows (place_rows), at least 1,024 cells of them and the numbering of an ordering's sets
+    const size_t want = 1024 * size_t(sh.cell_bytes) + 256, numbering = size_t(sh.K_cap) * 2;
+    const size_t room = want > numbering ? want : numbering;
+    sh.o_set_of = uint32_t(off);
+    sh.total = uint32_t(off + room > budget ? off + room : budget & ~size_t(15));
+    sh.w_inv = uint32_t(0xFFFFFFFFu / uint32_t(sh.W) + 1u);
+    return sh.total <= kBandLds;
 }
 
 // Workgroups of the band kernels: a batch of at most one ordering per CU gets the whole CU's LDS and

@@ -608,8 +608,9 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
         if (verdict == 1) { fail(HARP_CAND_INVALID, 0); continue; }
         if (verdict == 2) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
         if (verdict == 3) { hand_over(0); continue; }
-        const int64_t start = kWalk ? 0 : b.bracket();
+        const int64_t start = kWalk ? 0 : b.guess();
         if (start < 0) { fail(HARP_CAND_INFEASIBLE, 0); continue; }
+        bool guessed = E::kGuesses;
         // caps up to these bounds need no look at the operators (looked: it has been taken)
         int64_t sum_cap = b.largest_cap(meshband::kInfSum, false), key_cap = b.largest_cap(meshband::kInfSum, true);
         bool looked = false;
@@ -675,7 +676,13 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
             if (!kWalk && state == kBottleneck) {
                 if (found) { t_S = uint32_t(v); cap = t_S; state = kAtBottleneck; }
                 else if (cap >= meshband::kTopCap) state = kNoPlan;
+                else if (guessed && !b.reached) {
+                    const int64_t next = b.bracket(cap);
+                    if (next < 0) state = kNoPlan;
+                    else cap = uint32_t(next);
+                }
                 else cap = E::raised(cap, tries++);
+                guessed = false;
             } else if (!kWalk && state == kAtBottleneck) {
                 if (found) {
                     opened = true;

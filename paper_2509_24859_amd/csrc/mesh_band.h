@@ -45,17 +45,19 @@ constexpr uint32_t kNoCut = 0xFFFFu;
 constexpr uint32_t kInfSum = 0x80000000u;        // least sums stay below this (largest_cap)
 constexpr uint32_t kTopCap = 0x7FFFFFFFu;        // no time on these tables is larger
 constexpr int kRowPad = 4;                       // a window of four entries may overrun a row
-constexpr int kTeams = 2;                        // chains worked at once, by one wavefront each
+constexpr int kTeams = 2;                        // chains worked at once
 
 // LDS layout of a launch (byte offsets into dynamic LDS) and its capacities.
 struct BandShape {
     int W, NW;                   // cuts (L + 1), 64-bit words of a mask of cuts
     int cols;                    // columns: devices + 1
-    int K_cap, set_cap, row_cap; // groups of an ordering, sets of time rows, cells of a value row in LDS
+    int K_cap, set_cap;          // groups of an ordering, sets of time rows
+    int value_rows, cell_bytes;  // rows of 32-bit words a pass keeps in LDS, bytes per cell with counts and map
     int S_cap;                   // min(S_max, L)
     int idx_pitch;               // feasibility index
-    uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_prow, o_reach, o_mem, o_chain, o_ok, o_col, o_small, o_rows,
-        o_count, o_map, total;
+    uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_mem, o_chain, o_ok, o_col, o_small, o_prow,
+        o_set_of, total;
+    uint32_t w_inv;              // x / W is the high half of x * w_inv for x below 2^32 / W
 };
 
 constexpr int kMaxDevices = 2048;                // columns sit in LDS, 24 bytes each
@@ -121,7 +123,7 @@ inline size_t band_slice_bytes(int L, int S_max, int64_t total_devices) {
 }
 
 struct Band {
-    static constexpr bool kChoosesSlicing = true;
+    static constexpr bool kChoosesSlicing = true, kGuesses = true;
     static constexpr int kMaxClimb = 8, kMaxTries = 24;      // see k2_sweep.hip
     const TablesDev &tb;
     const BandShape &sh;
@@ -137,11 +139,10 @@ struct Band {
     uint32_t *prow;              // [sets][n_tp][W]
     uint16_t *reach;             // [2][sets][n_tp][W] reach of a stage under a cap
     int64_t *mem;                // PP [W], PS [W] (H-1F1B form)
-    uint16_t *chain;             // [kTeams][cols]
+    uint16_t *chain;             // [kTeams][2][cols + 1]
     unsigned long long *ok;      // [kTeams][2 K][NW]
-    uint16_t *col_lo, *col_hi;   // [2][cols]
+    uint2 *col;                  // [2][cols] lowest and highest cut of a column | index of its first cell less its lowest cut
     uint32_t *col_min;           // [2][cols] least value of a column (min-max form)
-    int32_t *col_off;            // [2][cols] index of a column's first cell less its lowest cut
     int32_t *tot, *base;         // [S_cap + 1] cells of a row, first cell of a row in hist
     int32_t *cuts;               // [S_cap + 1]
     int32_t *slot_first;         // [S_cap]
@@ -149,14 +150,19 @@ struct Band {
     uint16_t *slot_g;            // [S_cap]
     uint8_t *slot_k;             // [S_cap]
     uint32_t *scal;              // [8]
-    uint32_t *rows;              // [2][row_cap + pad]
-    uint16_t *counts;            // [2][row_cap + pad] (H-1F1B form)
-    uint16_t *map;               // [row_cap] column of a cell
+    uint16_t *set_of;            // [K] first group with the same time rows, while an ordering is loaded: in the room of the rows
+    uint32_t *rows;              // rows of a pass, [n][pitch], behind the sets the ordering has
+    uint16_t *counts;            // [2][pitch] (H-1F1B form)
+    uint16_t *map;               // [pitch] column of a cell
+    uint32_t room;               // bytes for rows, counts and map
+    int pitch;                   // cells of a row that fit, and a window
+    bool reached;                // the last prepared cap: its chains get from end to end
+    int most_cells;              // of a row of the last prepared cap
+    int map_shift;               // load_columns
     int nthreads, wave;
     int K, S, D, L, n_sets;
     int least_cut;               // the cut behind the operator of least output (operators but the last)
-    bool rows_fit;               // the value rows of the last prepared cap fit in LDS
-    bool keys_fit;               // and their key rows 32 bits, where the next pass is for the least sum
+    bool keys_fit;               // sums times a degree fit 32 bits under the cap of the next pass for the least sum
     int64_t count_cap;           // the cap H-1F1B's counts are worked out with: the pass's own, or above any time
 
     __device__ __forceinline__ Band(const TablesDev &t, const BandShape &s, unsigned char *lds, const uint16_t *lo,
@@ -172,14 +178,12 @@ struct Band {
         group_at = reinterpret_cast<uint16_t *>(lds + sh.o_group_at);
         use = reinterpret_cast<uint32_t *>(lds + sh.o_use);
         prow = reinterpret_cast<uint32_t *>(lds + sh.o_prow);
-        reach = reinterpret_cast<uint16_t *>(lds + sh.o_reach);
+        set_of = reinterpret_cast<uint16_t *>(lds + sh.o_set_of);
         mem = reinterpret_cast<int64_t *>(lds + sh.o_mem);
         chain = reinterpret_cast<uint16_t *>(lds + sh.o_chain);
         ok = reinterpret_cast<unsigned long long *>(lds + sh.o_ok);
-        col_off = reinterpret_cast<int32_t *>(lds + sh.o_col);
-        col_min = reinterpret_cast<uint32_t *>(col_off + 2 * sh.cols);
-        col_lo = reinterpret_cast<uint16_t *>(col_min + 2 * sh.cols);
-        col_hi = col_lo + 2 * sh.cols;
+        col = reinterpret_cast<uint2 *>(lds + sh.o_col);
+        col_min = reinterpret_cast<uint32_t *>(col + 2 * sh.cols);
         scal = reinterpret_cast<uint32_t *>(lds + sh.o_small);
         tot = reinterpret_cast<int32_t *>(scal + 8);
         base = tot + (sh.S_cap + 1);
@@ -188,16 +192,28 @@ struct Band {
         warmup = slot_first + sh.S_cap;
         slot_g = reinterpret_cast<uint16_t *>(warmup + sh.S_cap);
         slot_k = reinterpret_cast<uint8_t *>(slot_g + sh.S_cap);
-        rows = reinterpret_cast<uint32_t *>(lds + sh.o_rows);
-        counts = reinterpret_cast<uint16_t *>(lds + sh.o_count);
-        map = reinterpret_cast<uint16_t *>(lds + sh.o_map);
+        find_room(0);
         nthreads = blockDim.x; wave = uniform(int(threadIdx.x) >> 6);
         L = tb.L;
         K = S = D = n_sets = 0;
-        rows_fit = false;
+        pitch = most_cells = map_shift = 0;
+        reached = false;
         keys_fit = true;
         least_cut = 1;
         count_cap = 0;
+    }
+
+    // What the sets of an ordering leave of the LDS holds the rows of its passes: a fixed share for the most sets an
+    // ordering may have, cut for the widest form of a row, left values of 160 operators and 128 devices room for 2,900
+    // cells where 12,000 fit (256 orderings, exact form: two of three least-sum passes worked from the workspace).
+    static constexpr int kValueBytes = 10, kCountBytes = 14;       // of a cell: two rows of values (and of counts), and the map
+    __device__ __forceinline__ int keys_bytes() const { return 4 * (1 + tb.n_tp) + 2; }
+    __device__ __forceinline__ void find_room(int sets) {
+        const uint32_t per_table = uint32_t(sets) * uint32_t(tb.n_tp) * uint32_t(sh.W);      // entries
+        reach = reinterpret_cast<uint16_t *>(prow + per_table + 4);                          // (a window may overrun the last row)
+        const uint32_t from = (sh.o_prow + 16u + per_table * 8u + 15u) & ~15u;
+        rows = prow + (from - sh.o_prow) / 4u;
+        room = sh.total - from - 256u;                     // (256: what windows may overrun)
     }
 
     // The thread's index, new to the compiler at every use: what a phase derives from it (LDS addresses,
@@ -277,7 +293,7 @@ struct Band {
             const int64_t link = tb.bw[int64_t(g) * tb.G + g];
             int q = 0;
             while (q < k && !(type[q] == type[k] && tb.bw[int64_t(order[q]) * tb.G + order[q]] == link)) ++q;
-            map[k] = uint16_t(q);
+            set_of[k] = uint16_t(q);
             index_at[k] = uint32_t(type[k]) * uint32_t(tb.n_tp) * uint32_t(sh.idx_pitch);
             link_at[k] = uint32_t(g * tb.G + g) * uint32_t(tb.pitch32);
             if (k + 1 < K) link_at[K + k] = uint32_t(g * tb.G + order[k + 1]) * uint32_t(tb.pitch32);
@@ -286,10 +302,14 @@ struct Band {
         D = offs[K];
         if (S > L || S < K || S > D) return 2;
         n_sets = 0;
-        for (int k = 0; k < K; ++k) n_sets += map[k] == k ? 1 : 0;
+        for (int k = 0; k < K; ++k) n_sets += set_of[k] == k ? 1 : 0;
+        n_sets = uniform(n_sets);
         if (n_sets > sh.set_cap) return 3;
+        find_room(n_sets);
+        map_shift = 0;
+        while (map_shift < 3 && (D << (map_shift + 1)) <= nthreads) ++map_shift;
         for (int k = 0, set = 0; k < K; ++k) {
-            if (map[k] != k) continue;
+            if (set_of[k] != k) continue;
             const uint32_t *from = tb.P32 + int64_t(order[k]) * tb.n_tp * tb.pitch32;
             uint32_t *to = prow + set * tb.n_tp * sh.W;
             for (int q = 0; q < tb.n_tp; ++q)
@@ -301,7 +321,7 @@ struct Band {
         // sets are numbered in the order of their first groups
         for (int k = tid; k < K; k += nthreads) {
             uint32_t set = 0;
-            for (int q = 0; q < map[k]; ++q) set += map[q] == q ? 1u : 0u;
+            for (int q = 0; q < set_of[k]; ++q) set += set_of[q] == q ? 1u : 0u;
             prow_at[k] = set * uint32_t(tb.n_tp) * uint32_t(sh.W);
         }
         for (int x = tid; x < n_sets; x += nthreads) use[x] = 0;
@@ -314,7 +334,7 @@ struct Band {
     }
     __device__ __forceinline__ const uint32_t *time_row(int k) const { return prow + prow_at[k]; }   // degree q at q * W
     __device__ __forceinline__ uint16_t *reach_row(int side, int k) const {
-        return reach + side * sh.set_cap * tb.n_tp * sh.W + prow_at[k];
+        return reach + side * n_sets * tb.n_tp * sh.W + prow_at[k];
     }
     __device__ __forceinline__ unsigned long long *masks(int team) const { return ok + size_t(team) * 2 * sh.K_cap * sh.NW; }
 
@@ -343,33 +363,41 @@ struct Band {
             }
         }
     }
-    // All threads: how far a stage gets under t on every (set, degree).  Upwards: entry j = the highest cut
-    // i with time(j, i) <= t; downwards: entry i = the lowest cut j with time(j, i) <= t.
+    // All threads: how far a stage gets under t on every (set, degree), into table `side`.  Upwards: entry j = the
+    // highest cut i with time(j, i) <= t; downwards: entry i = the lowest cut j with time(j, i) <= t.  A binary search
+    // is a chain of LDS reads; a thread has four of them under way (4,096 orderings of 82 operators and 64 devices: of
+    // an ordering's 157 us the tables took 30 with one after the other).
     template <bool kUp>
     __device__ __forceinline__ void reach_table(uint32_t t, int side) {
         const int tid = thread_id();
-        uint16_t *to = reach + side * sh.set_cap * tb.n_tp * sh.W;
+        uint16_t *to = reach + side * n_sets * tb.n_tp * sh.W;
         const int n = n_sets * tb.n_tp * sh.W, top_step = 1 << (31 - __clz(L));
-        for (int x = tid; x < n; x += nthreads) {
-            const int r = x / sh.W, e = x - r * sh.W;
-            const uint64_t far = uint64_t(t) * uint32_t(tb.tp[r % tb.n_tp]);
-            const uint32_t *p = prow + r * sh.W;
-            const uint32_t pe = p[e];
-            int pos = e;
-            if (kUp) {
-                const uint32_t target = pe + far > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(pe + far);
-                for (int step = top_step; step > 0; step >>= 1) {
-                    const int nx = pos + step;
-                    pos = nx <= L && p[nx <= L ? nx : L] <= target ? nx : pos;
-                }
-            } else {
-                const uint32_t target = pe > far ? uint32_t(pe - far) : 0u;
-                for (int step = top_step; step > 0; step >>= 1) {
-                    const int nx = pos - step;
-                    pos = nx >= 0 && p[nx >= 0 ? nx : 0] >= target ? nx : pos;
+        for (int x0 = tid; x0 < n; x0 += 4 * nthreads) {
+            const uint32_t *p[4];
+            uint32_t target[4];
+            int pos[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int x = x0 + u * nthreads < n ? x0 + u * nthreads : x0;
+                const int r = int(__umulhi(uint32_t(x), sh.w_inv)), e = x - r * sh.W;
+                const uint64_t far = uint64_t(t) * uint32_t(tb.tp[r % tb.n_tp]);
+                p[u] = prow + r * sh.W;
+                const uint32_t pe = p[u][e];
+                if (kUp) target[u] = pe + far > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(pe + far);
+                else target[u] = pe > far ? uint32_t(pe - far) : 0u;
+                pos[u] = e;
+            }
+            for (int step = top_step; step > 0; step >>= 1) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int nx = kUp ? pos[u] + step : pos[u] - step;
+                    if (kUp) pos[u] = nx <= L && p[u][nx <= L ? nx : L] <= target[u] ? nx : pos[u];
+                    else pos[u] = nx >= 0 && p[u][nx >= 0 ? nx : 0] >= target[u] ? nx : pos[u];
                 }
             }
-            to[x] = uint16_t(pos);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (x0 + u * nthreads < n) to[x0 + u * nthreads] = uint16_t(pos[u]);
         }
     }
     // highest cut <= i in a mask, -1 when there is none; lowest cut >= i, > L when there is none
@@ -386,130 +414,120 @@ struct Band {
         return b == 0 ? L + 1 : w * 64 + __ffsll((long long)b) - 1;
     }
 
-    // One wavefront: F of every (s, d) from the upward reach table `side`; true when (S, D) reaches L.  Fg
-    // null: the verdict only.
-    __device__ __forceinline__ bool forward_chain(int side, const unsigned long long *m, uint16_t *row, uint16_t *Fg) {
-        const int lane = thread_id() & 63;
-        for (int d = lane; d <= D; d += 64) {
-            const uint16_t v = d == 0 ? 0 : uint16_t(kNoCut);
-            row[d] = v;
-            if (Fg) Fg[d] = v;
-        }
-        wave_sync();
-        for (int s = 0; s < S; ++s) {
-            const bool last = s == S - 1;
-            const int n = in_flight(s), top = L - (S - 1 - s);
-            const int d_lo = last ? D : s + 1, d_hi = D - (S - 1 - s);
-            bool any = false;
-            for (int c = D >> 6; c >= 0; --c) {           // from the top: a column reads lower columns only
-                const int d2 = c * 64 + lane;
-                int best = -1;
-                if (d2 >= d_lo && d2 <= d_hi) {
-                    const int k = group_at[d2 - 1];
-                    const int from = offs[k] > s ? offs[k] : s;
-                    const uint16_t *far = reach_row(side, k);
-                    const uint16_t *fits = hi_tab + (index_n(n) + index_at[k]);
-                    for (int q0 = 0; q0 < tb.n_tp; q0 += 4) {
-                        // (no branches around the loads: the four degrees' are in flight together)
-                        uint32_t j[4];
-                        int a[4], b[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
-                            const int d = d2 - tb.tp[q];
-                            j[u] = row[d >= from ? d : 0];
-                            j[u] = d >= from ? j[u] : kNoCut;
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
-                            const int e = j[u] != kNoCut ? int(j[u]) : 0;
-                            a[u] = far[q * sh.W + e];
-                            b[u] = fits[q * sh.idx_pitch + e];
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int i = a[u] < b[u] ? a[u] : b[u];
-                            best = j[u] != kNoCut && i > best ? i : best;
-                        }
-                    }
-                    best = best < top ? best : top;
-                    if (best >= 0 && !last) best = mask_down(m + link_of(d2) * sh.NW, best);
-                    if (best < s + 1) best = -1;
-                }
-                wave_sync();
-                if (d2 <= D) {
-                    const uint16_t v = best < 0 ? uint16_t(kNoCut) : uint16_t(best);
-                    row[d2] = v;
-                    if (Fg) Fg[size_t(s + 1) * sh.cols + d2] = v;
-                }
-                wave_sync();
-                any = any || __any(best >= 0);
-            }
-            if (!any) return false;
-        }
-        return uniform(row[D]) == L;
+    // A chain step, a lane per column: F of the columns d after stage s (forwards, from the upward reach table),
+    // or B of those in front of it (backwards).  What a column's lane needs of its group does not change from stage to
+    // stage (chain_lane).
+    struct ChainLane { int d, edge; uint32_t index, far, link; };
+    template <bool kBack>
+    __device__ __forceinline__ ChainLane chain_lane(int c) const {
+        ChainLane l;
+        l.d = c * 64 + (thread_id() & 63) + (kBack ? 0 : 1);       // forwards columns 1 .. D, backwards 0 .. D - 1
+        const int stage_on = kBack ? (l.d < D ? l.d : D - 1) : (l.d <= D ? l.d : D) - 1, k = group_at[stage_on];
+        l.edge = offs[kBack ? k + 1 : k];
+        l.index = index_at[k];
+        l.far = prow_at[k];
+        const int cut_on = kBack ? stage_on : stage_on + 1;
+        l.link = uint32_t(cut_on > 0 ? link_of(cut_on) : 0) * uint32_t(sh.NW);
+        return l;
     }
-
-    // One wavefront: B of every (s, d) from the downward reach table `side`; true when (0, 0) is reached.
-    __device__ __forceinline__ bool backward_chain(int side, const unsigned long long *m, uint16_t *row, uint16_t *Bg) {
-        const int lane = thread_id() & 63;
-        for (int d = lane; d <= D; d += 64) {
-            const uint16_t v = d == D ? uint16_t(L) : uint16_t(kNoCut);
-            row[d] = v;
-            Bg[size_t(S) * sh.cols + d] = v;
-        }
-        wave_sync();
-        for (int s = S - 1; s >= 0; --s) {
-            const int n = in_flight(s);
-            const int d_lo = s, d_hi = s == 0 ? 0 : D - (S - s);
-            bool any = false;
-            for (int c = 0; c <= (D >> 6); ++c) {         // from the bottom: a column reads higher columns only
-                const int d = c * 64 + lane;
-                int best = INT32_MAX;
-                if (d >= d_lo && d <= d_hi) {
-                    const int k = group_at[d], end = offs[k + 1];
-                    const uint16_t *far = reach_row(side, k);
-                    const uint16_t *fits = lo_tab + (index_n(n) + index_at[k]);
-                    for (int q0 = 0; q0 < tb.n_tp; q0 += 4) {
-                        uint32_t i[4];
-                        int a[4], b[4];
+    template <bool kBack>
+    __device__ __forceinline__ void chain_step(const ChainLane &l, int c, int s, int side, const unsigned long long *m,
+                                               const uint16_t *from, uint16_t *to, uint16_t *G) const {
+        const uint16_t *far = reach + side * n_sets * tb.n_tp * sh.W;
+        const uint16_t *fits = (kBack ? lo_tab : hi_tab) + index_n(in_flight(s));
+        int best = kBack ? INT32_MAX : -1;
+        for (int q0 = 0; q0 < tb.n_tp; q0 += 4) {
+            // (no branches around the loads: the four degrees' are in flight together)
+            uint32_t v[4];
+            int a[4], b[4];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
-                            const int d1 = d + tb.tp[q];
-                            i[u] = row[d1 <= end ? d1 : 0];
-                            i[u] = d1 <= end ? i[u] : kNoCut;
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
-                            const int e = i[u] != kNoCut ? int(i[u]) : 0;
-                            a[u] = far[q * sh.W + e];
-                            b[u] = fits[q * sh.idx_pitch + e];
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int j = a[u] > b[u] ? a[u] : b[u];
-                            best = i[u] != kNoCut && j < best ? j : best;
-                        }
-                    }
-                    best = best > s ? best : s;
-                    if (s > 0 && best <= L) best = mask_up(m + link_of(d) * sh.NW, best);
-                    if (best > L - (S - s) || (s == 0 && best != 0)) best = INT32_MAX;
-                }
-                wave_sync();
-                if (d <= D) {
-                    const uint16_t v = best == INT32_MAX ? uint16_t(kNoCut) : uint16_t(best);
-                    row[d] = v;
-                    Bg[size_t(s) * sh.cols + d] = v;
-                }
-                wave_sync();
-                any = any || __any(best != INT32_MAX);
+            for (int u = 0; u < 4; ++u) {
+                const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
+                const int d = kBack ? l.d + tb.tp[q] : l.d - tb.tp[q];
+                v[u] = from[(kBack ? d <= l.edge : d >= l.edge) ? d : sh.cols];      // [cols]: no cut
             }
-            if (!any) return false;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
+                const uint32_t e = v[u] != kNoCut ? v[u] : 0u;
+                a[u] = far[l.far + uint32_t(q * sh.W) + e];
+                b[u] = fits[l.index + uint32_t(q * sh.idx_pitch) + e];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (kBack) {
+                    const int j = a[u] > b[u] ? a[u] : b[u];
+                    best = v[u] != kNoCut && j < best ? j : best;
+                } else {
+                    const int i = a[u] < b[u] ? a[u] : b[u];
+                    best = v[u] != kNoCut && i > best ? i : best;
+                }
+            }
         }
-        return uniform(row[0]) == 0;
+        if (kBack) {
+            const int d_hi = s == 0 ? 0 : D - (S - s);
+            best = best > s ? best : s;
+            if (s > 0 && best <= L) best = mask_up(m + l.link, best);
+            if (best > L - (S - s) || (s == 0 && best != 0) || l.d > d_hi) best = -1;
+        } else {
+            const int top = L - (S - 1 - s), d_hi = D - (S - 1 - s);
+            const bool last = s == S - 1;
+            best = best < top ? best : top;
+            if (best >= 0 && !last) best = mask_down(m + l.link, best);
+            if (best < s + 1 || l.d > d_hi || (last && l.d != D)) best = -1;
+        }
+        const int row = kBack ? s : s + 1, outside = kBack ? D : 0;        // the column that only the first row has
+        const uint16_t v = best < 0 ? uint16_t(kNoCut) : uint16_t(best);
+        if (kBack ? l.d < D : l.d <= D) {
+            to[l.d] = v;
+            if (G) G[size_t(row) * sh.cols + l.d] = v;
+        }
+        if (c == 0 && (threadIdx.x & 63) == 0) {
+            to[outside] = uint16_t(kNoCut);
+            if (G) G[size_t(row) * sh.cols + outside] = uint16_t(kNoCut);
+        }
+    }
+    // All threads: two chains at once, the one of team 0 forwards, that of team 1 forwards or (kBack) backwards, a
+    // wavefront for every 64 columns where there are as many, and a barrier per stage.  F0, B1 null: the verdicts only.
+    // Verdict: (S, D) reaches L, or (0, 0) is reached.  (4,096 orderings of 82 operators and 64 devices: a chain on one
+    // wavefront, group and row addresses worked out in every stage, took 14 us, of which the stages are about 12.)
+    template <bool kBack>
+    __device__ __forceinline__ void run_chains(uint16_t *F0, uint16_t *B1, bool &good0, bool &good1) {
+        const int chunks = (D + 63) >> 6, half = nthreads >> 7, waves = chunks < half ? chunks : half;
+        const int team = wave < waves ? 0 : wave < 2 * waves ? 1 : 2, first = team == 1 ? wave - waves : wave;
+        const int pitch16 = sh.cols + 1;
+        uint16_t *buf = chain + (team == 1 ? 2 : 0) * pitch16;
+        for (int x = thread_id(); x < 4 * pitch16; x += nthreads) {
+            const int b = x / pitch16, d = x - b * pitch16;
+            uint16_t v = uint16_t(kNoCut);
+            if (kBack && b == 2) v = d == D ? uint16_t(L) : v;
+            else if (b == 0 || b == 2) v = d == 0 ? uint16_t(0) : v;
+            chain[x] = v;
+            if (b == 0 && F0 && d <= D) F0[d] = v;
+            if (kBack && b == 2 && d <= D) B1[size_t(S) * sh.cols + d] = v;
+        }
+        __syncthreads();
+        const bool back = kBack && team == 1;
+        const unsigned long long *m = masks(kBack ? 0 : team == 1 ? 1 : 0);
+        ChainLane l = back ? chain_lane<true>(first) : chain_lane<false>(first);
+        for (int n = 0; n < S; ++n) {
+            const uint16_t *from = buf + (n & 1) * pitch16;
+            uint16_t *to = buf + ((n & 1) ^ 1) * pitch16;
+            if (team < 2)
+                for (int c = first; c < chunks; c += waves) {
+                    if (back) {
+                        if (chunks > waves) l = chain_lane<true>(c);
+                        chain_step<true>(l, c, S - 1 - n, 1, m, from, to, B1);
+                    } else {
+                        if (chunks > waves) l = chain_lane<false>(c);
+                        chain_step<false>(l, c, n, team, m, from, to, team == 0 ? F0 : nullptr);
+                    }
+                }
+            __syncthreads();
+        }
+        const int at = (S & 1) * pitch16;
+        good0 = uniform(chain[at + D]) == L;
+        good1 = kBack ? uniform(chain[2 * pitch16 + at]) == 0 : uniform(chain[2 * pitch16 + at + D]) == L;
     }
 
     // All threads: the ranges under t, cell numbering of every row.  False: no plan under t.
@@ -520,36 +538,28 @@ struct Band {
         cut_masks(1, t, t);
         reach_table<true>(t, 0);
         reach_table<false>(t, 1);
-        __syncthreads();
-        if (wave == 0) {
-            const bool good = forward_chain(0, masks(0), chain, sl.F);
-            if (lane == 0) scal[0] = good ? 1u : 0u;
-        } else if (wave == 1) {
-            const bool good = backward_chain(1, masks(0), chain + sh.cols, sl.B);
-            if (lane == 0) scal[1] = good ? 1u : 0u;
-        }
-        __syncthreads();
-        if (scal[0] == 0 || scal[1] == 0) return false;
-        // cells of every row: columns one after the other, a wavefront per row
+        bool good0, good1;
+        run_chains<true>(sl.F, sl.B, good0, good1);        // (its first barrier stands behind the tables)
+        reached = good0 && good1;
+        if (!reached) return false;
+        // cells of every row: columns one after the other (column 0 has one in row 0), a wavefront per row
         for (int s = wave; s <= S; s += nthreads >> 6) {
-            int total = 0;
-            for (int d0 = 0; d0 <= D; d0 += 64) {
-                const int d = d0 + lane;
+            int total = s == 0 ? 1 : 0;
+            const size_t row = size_t(s) * sh.cols;
+            if (lane == 0) {
+                sl.off[row] = 0;
+                if (s > 0) { sl.F[row] = 0; sl.B[row] = 1; }
+            }
+            for (int d = 1 + lane; d - lane <= D; d += 64) {
                 uint32_t f = kNoCut, b = kNoCut;
-                if (d <= D) { f = sl.F[size_t(s) * sh.cols + d]; b = sl.B[size_t(s) * sh.cols + d]; }
+                if (d <= D) { f = sl.F[row + d]; b = sl.B[row + d]; }
                 const bool has = f != kNoCut && b != kNoCut && b <= f;
-                const int w = has ? int(f - b) + 1 : 0;
-                int inc = w;
-#pragma unroll
-                for (int x = 1; x < 64; x <<= 1) {
-                    const int o = __shfl_up(inc, x, 64);
-                    if (lane >= x) inc += o;
-                }
+                const int w = has ? int(f - b) + 1 : 0, inc = int(fastdp::wave_scan(uint32_t(w), fastdp::sum2));
                 if (d <= D) {
-                    sl.off[size_t(s) * sh.cols + d] = total + inc - w - (has ? int(b) : 0);
-                    if (!has) { sl.F[size_t(s) * sh.cols + d] = 0; sl.B[size_t(s) * sh.cols + d] = 1; }
+                    sl.off[row + d] = total + inc - w - (has ? int(b) : 0);
+                    if (!has) { sl.F[row + d] = 0; sl.B[row + d] = 1; }
                 }
-                total += __shfl(inc, 63, 64);
+                total += __builtin_amdgcn_readlane(inc, 63);
             }
             if (lane == 0) tot[s] = total;
         }
@@ -562,71 +572,228 @@ struct Band {
             most = n > most ? n : most;
             least = n < least ? n : least;
         }
-        rows_fit = most <= sh.row_cap;
+        most_cells = most;
         __syncthreads();
         return least > 0;
     }
 
     // Range and numbering of row s into column buffer b, and the column of every cell; a thread's first
-    // column is requested ahead (request_column) and waits in a register.
+    // column is requested ahead (request_column) and waits in a register.  2^map_shift threads share a column: they
+    // write its part of the map together.  Column 0 has a cell in row 0 only.
     struct Column { int lo, hi, off; };
     __device__ __forceinline__ Column request_column(int s) const {
-        const int tid = thread_id();
+        const int d = 1 + (thread_id() >> map_shift);
         Column c{1, 0, 0};
-        if (tid <= D) {
-            const size_t at = size_t(s) * sh.cols + tid;
+        if (d <= D) {
+            const size_t at = size_t(s) * sh.cols + d;
             c.lo = sl.B[at]; c.hi = sl.F[at]; c.off = sl.off[at];
         }
         return c;
     }
     __device__ __forceinline__ void store_column(int d, const Column &c, int b, bool with_map) {
-        col_lo[b * sh.cols + d] = uint16_t(c.lo);
-        col_hi[b * sh.cols + d] = uint16_t(c.hi);
-        col_off[b * sh.cols + d] = c.off;
-        col_min[b * sh.cols + d] = 0xFFFFFFFFu;
+        const int part = thread_id() & ((1 << map_shift) - 1);
+        if (part == 0) {
+            col[b * sh.cols + d] = uint2{uint32_t(c.lo) | (uint32_t(c.hi) << 16), uint32_t(c.off)};
+            col_min[b * sh.cols + d] = 0xFFFFFFFFu;
+        }
         if (with_map)
-            for (int i = c.lo; i <= c.hi; ++i) map[c.off + i] = uint16_t(d);
+            for (int i = c.lo + part; i <= c.hi; i += 1 << map_shift) map[c.off + i] = uint16_t(d);
     }
     __device__ __forceinline__ void load_columns(int s, const Column &first, int b, bool with_map) {
         const int tid = thread_id();
-        if (tid <= D) store_column(tid, first, b, with_map);
-        for (int d = tid + nthreads; d <= D; d += nthreads) {
+        const int d0 = 1 + (tid >> map_shift);
+        if (d0 <= D) store_column(d0, first, b, with_map);
+        for (int d = d0 + (nthreads >> map_shift); d <= D; d += nthreads >> map_shift) {
             const size_t at = size_t(s) * sh.cols + d;
             store_column(d, Column{sl.B[at], sl.F[at], sl.off[at]}, b, with_map);
         }
+        if (tid == 0) {
+            col[b * sh.cols] = uint2{s == 0 ? 0u : 1u, 0u};
+            col_min[b * sh.cols] = 0xFFFFFFFFu;
+            if (s == 0 && with_map) map[0] = 0;
+        }
     }
+    __device__ __forceinline__ static int col_lo(const uint2 &c) { return int(c.x & 0xFFFFu); }
+    __device__ __forceinline__ static int col_hi(const uint2 &c) { return int(c.x >> 16); }
     // column of cell x when there is no map: the last column that starts at or before x
     __device__ __forceinline__ int find_column(int b, int x) const {
+        const uint2 *cols = col + b * sh.cols;
         int lo = 0, hi = D;                                // first cells rise with d; empty columns share theirs
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            const int l = col_lo[b * sh.cols + mid], h = col_hi[b * sh.cols + mid];
-            const int first = col_off[b * sh.cols + mid] + (l <= h ? l : 0);
+            const uint2 c = cols[mid];
+            const int first = int(c.y) + (col_lo(c) <= col_hi(c) ? col_lo(c) : 0);
             if (first <= x) lo = mid; else hi = mid - 1;
         }
-        while (col_lo[b * sh.cols + lo] > col_hi[b * sh.cols + lo]) --lo;
+        while (col_lo(cols[lo]) > col_hi(cols[lo])) --lo;
         return lo;
     }
 
-    // One pass over all stages in the ranges of the last prepare.  kCapped = false: min-max, values above
-    // `t` count as unreachable.  kCapped = true: least sum of (t + 2c) over stage and transfer times of at
-    // most t.  Returns the value of (S, L, D), or kInf.
+    // Rows of a pass in what the sets of an ordering leave of the LDS: n rows of values, two of counts (H-1F1B), the map.
+    __device__ __forceinline__ int cells_that_fit(int bytes_per_cell) const { return int(room / uint32_t(bytes_per_cell)) & ~7; }
+    __device__ __forceinline__ void place_rows(int n, int n_counts, int bytes_per_cell) {
+        pitch = cells_that_fit(bytes_per_cell) + kRowPad;
+        counts = reinterpret_cast<uint16_t *>(rows + n * pitch);
+        map = counts + n_counts * pitch;
+    }
+
+    // One pass over all stages in the ranges of the last prepare.  Min-max: values above `t` count as
+    // unreachable.  Otherwise: least sum of (t + 2c) over stage and transfer times of at most t.  Returns the value of
+    // (S, L, D), or kInf.
     //
     // Min-max cells scan windows of four cuts downwards and stop when the stage time alone exceeds the
     // best value, or when nothing below the column's least value or the cell's transfer time is left to
     // gain (where a slow link decides, most columns hold one value throughout).
     // Least sums: D[j] + floor((P[i] + tp - 1 - P[j]) / tp) is floor((D[j] tp - P[j] + P[i] + tp - 1) / tp),
-    // and the minimum can be taken inside the floor, so a row kept in LDS is turned into D[j] tp - P[j] per
-    // degree once (key rows) and a cell is the minimum over a run of consecutive words: 2 instructions
-    // per cut instead of 11.
-    template <bool kCapped, bool kLds>
+    // and the minimum can be taken inside the floor.  A row that fits LDS n_tp times over is turned into D[j] tp - P[j] per
+    // degree once (key rows), and a cell is the minimum over a run of consecutive words; where only the values fit, the
+    // product and the difference are formed on the way (two rows to read and two instructions more per cut); from the
+    // workspace, and where the products do not fit 32 bits, a cut takes its whole time.
+    enum { kPassMinMax, kPassSum, kPassKeys };
+    struct StageCtx {
+        int s, cur, nxt, total;
+        bool last;
+        const uint32_t *prev;
+        uint32_t *next, *out;
+        const int32_t *keys;
+        const uint32_t *cut_tab;
+        const uint16_t *fits_tab;
+        uint32_t t, none;
+    };
+    template <int kPass, bool kLds>
+    __device__ __forceinline__ void degree_best(const StageCtx &c, int q, int tp, int shift, int d2, int i, uint32_t cut, int from,
+                                                int in_memory, int within, const uint32_t *p_k, uint32_t &best) const {
+        const int d = d2 - tp;
+        if (d < from) return;
+        uint32_t floor_v = cut;
+        if (kPass == kPassMinMax) {
+            const uint32_t m = col_min[c.cur * sh.cols + d];
+            floor_v = m > cut ? m : cut;
+            if (floor_v >= best) return;
+        }
+        // previous cuts: in the column's range, in memory, within t
+        const uint2 w = col[c.cur * sh.cols + d];
+        int jl = in_memory > within ? in_memory : within;
+        jl = jl > col_lo(w) ? jl : col_lo(w);
+        const int jh = (i - 1) < col_hi(w) ? (i - 1) : col_hi(w);
+        if (jl > jh) return;
+        const uint32_t *p = p_k + q * sh.W;
+        const uint32_t xi = p[i] + uint32_t(tp) - 1u;
+        const int off = int(w.y);
+        if (kPass == kPassKeys || (kPass == kPassSum && kLds)) {
+            constexpr int32_t kNoKey = INT32_MAX;
+            const int32_t *e = c.keys + q * pitch + off;
+            const uint32_t *r = c.prev + off;
+            auto key = [&](int j) -> int32_t { return kPass == kPassKeys ? e[j] : int32_t((r[j] << shift) - p[j]); };
+            // the first window may reach beyond jh (what it reads there does not count), the others are pushed down
+            // against it: cuts seen twice do not matter to a minimum
+            int j = jl;
+            const int32_t e0 = key(j);
+            int32_t e1 = key(j + 1), e2 = key(j + 2), e3 = key(j + 3);
+            e1 = j + 1 <= jh ? e1 : kNoKey;
+            e2 = j + 2 <= jh ? e2 : kNoKey;
+            e3 = j + 3 <= jh ? e3 : kNoKey;
+            int32_t m = least(least(e0, e1), least(e2, e3));
+            while (j + 3 < jh) {
+                j = j + 4 < jh - 3 ? j + 4 : jh - 3;
+                const int32_t f0 = key(j), f1 = key(j + 1), f2 = key(j + 2), f3 = key(j + 3);
+                m = least(least(least(f0, f1), m), least(f2, f3));
+            }
+            if (kPass == kPassSum || m != kNoKey) best = least(best, (xi + uint32_t(m)) >> shift);
+        } else {
+            constexpr bool kCapped = kPass == kPassSum;
+            const uint32_t *r = c.prev + off;
+            // the first window may be cut short at its upper end, the last is pushed up
+            // against jl (cuts seen twice do not matter to a minimum)
+            int j = jh - 3 > jl ? jh - 3 : jl;
+            uint32_t t0;
+            {
+                const uint32_t p0 = p[j], p1 = p[j + 1], p2 = p[j + 2], p3 = p[j + 3];
+                const uint32_t r0 = r[j], r1 = r[j + 1], r2 = r[j + 2], r3 = r[j + 3];
+                t0 = (xi - p0) >> shift;
+                const uint32_t t1 = (xi - p1) >> shift, t2 = (xi - p2) >> shift, t3 = (xi - p3) >> shift;
+                const uint32_t v0 = value<kCapped>(r0, t0, cut);
+                const uint32_t v1 = j + 1 <= jh ? value<kCapped>(r1, t1, cut) : c.none;
+                const uint32_t v2 = j + 2 <= jh ? value<kCapped>(r2, t2, cut) : c.none;
+                const uint32_t v3 = j + 3 <= jh ? value<kCapped>(r3, t3, cut) : c.none;
+                best = least(best, least(least(v0, v1), least(v2, v3)));
+            }
+            while (j > jl && (kCapped || (t0 <= best && best > floor_v))) {
+                j = j - 4 > jl ? j - 4 : jl;
+                const uint32_t p0 = p[j], p1 = p[j + 1], p2 = p[j + 2], p3 = p[j + 3];
+                const uint32_t r0 = r[j], r1 = r[j + 1], r2 = r[j + 2], r3 = r[j + 3];
+                t0 = (xi - p0) >> shift;
+                const uint32_t t1 = (xi - p1) >> shift, t2 = (xi - p2) >> shift, t3 = (xi - p3) >> shift;
+                const uint32_t v0 = value<kCapped>(r0, t0, cut), v1 = value<kCapped>(r1, t1, cut);
+                const uint32_t v2 = value<kCapped>(r2, t2, cut), v3 = value<kCapped>(r3, t3, cut);
+                best = least(best, least(least(v0, v1), least(v2, v3)));
+            }
+        }
+    }
+    // The cells of a row.  kSplit: four lanes share a cell, a degree each (at most four degrees, my_*: the lane's own):
+    // a row of few cells is bound by the chain of one cell's degrees.
+    template <int kPass, bool kLds, bool kSplit>
+    __device__ __forceinline__ void row_cells(const StageCtx &c, int my_q, int my_tp, int my_shift) {
+        const int tid = thread_id();
+        const int part = kSplit ? tid & 3 : 0, step = kSplit ? nthreads >> 2 : nthreads;
+        for (int x = kSplit ? tid >> 2 : tid; x < c.total; x += step) {
+            const int d2 = kLds ? int(map[x]) : find_column(c.nxt, x);
+            const int i = x - int(col[c.nxt * sh.cols + d2].y);
+            const int k = group_at[d2 - 1];
+            const uint32_t cut = c.last ? 0u : c.cut_tab[cut_at[d2] + uint32_t(i)];
+            uint32_t best = c.none;
+            const uint32_t *p_k = time_row(k);
+            const int from = offs[k] > c.s ? offs[k] : c.s;
+            const uint16_t *fits = c.fits_tab + (index_at[k] + uint32_t(i)), *far = reach_row(1, k) + i;
+            if (kSplit) {
+                int in_memory = fits[my_q * sh.idx_pitch];
+                const int within = far[my_q * sh.W];
+                if (cut <= c.t && my_tp != 0)
+                    degree_best<kPass, kLds>(c, my_q, my_tp, my_shift, d2, i, cut, from, in_memory, within, p_k, best);
+                best = least(best, uint32_t(__builtin_amdgcn_update_dpp(int(best), int(best), 0xB1, 0xF, 0xF, false)));   // lanes 1 and 2 apart
+                best = least(best, uint32_t(__builtin_amdgcn_update_dpp(int(best), int(best), 0x4E, 0xF, 0xF, false)));
+                if (part != 0) continue;
+            } else {
+                // degrees from the largest down, four at a time: the first values found are then the best ones,
+                // and a degree whose column holds nothing below the best value is passed over
+                for (int q0 = (tb.n_tp - 1) & ~3; q0 >= 0; q0 -= 4) {
+                    int in_memory[4], within[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int q = q0 + u < tb.n_tp ? q0 + u : q0;
+                        in_memory[u] = fits[q * sh.idx_pitch];
+                        within[u] = far[q * sh.W];
+                    }
+                    // (requested together: a load that the compiler moves into a branch is waited for there)
+                    asm volatile("" : "+v"(in_memory[0]), "+v"(in_memory[1]), "+v"(in_memory[2]), "+v"(in_memory[3]));
+                    if (cut > c.t) break;
+#pragma unroll
+                    for (int u = 3; u >= 0; --u)
+                        if (q0 + u < tb.n_tp)
+                            degree_best<kPass, kLds>(c, q0 + u, tb.tp[q0 + u], tb.tp_shift[q0 + u], d2, i, cut, from, in_memory[u],
+                                                     within[u], p_k, best);
+                }
+            }
+            if (kPass != kPassMinMax) best = best < c.none ? best + 2u * cut : c.none;
+            if (kLds) c.next[x] = best;
+            // (lanes of a wavefront mostly share a column: the read in front spares the serialised atomics)
+            if (kPass == kPassMinMax && best < col_min[c.nxt * sh.cols + d2]) atomicMin(&col_min[c.nxt * sh.cols + d2], best);
+            c.out[x] = best;
+        }
+    }
+    template <int kPass, bool kLds>
     __device__ __forceinline__ int64_t value_pass_in(uint32_t t) {
         const int tid = thread_id();
-        constexpr bool kKeys = kCapped && kLds;
+        constexpr bool kKeys = kPass == kPassKeys;
         constexpr int32_t kNoKey = INT32_MAX;
-        const uint32_t none = kCapped ? kInfSum : t + 1u;
-        const int pitch = sh.row_cap + kRowPad;
+        // sums are below 2^31, and where keys are formed below 2^31 / degree, less one (largest_cap)
+        const uint32_t none = kPass == kPassMinMax ? t + 1u : kPass == kPassSum && kLds ? key_limit() - 1u : kInfSum;
+        if (kLds) place_rows(kKeys ? 1 + tb.n_tp : 2, 0, kKeys ? keys_bytes() : kValueBytes);
         int32_t *keys = reinterpret_cast<int32_t *>(rows + pitch);         // [n_tp][pitch] (kKeys)
+        int my_q = 0, my_tp = 0, my_shift = 0;                             // (no degree: no stage)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if ((tid & 3) == q && q < tb.n_tp) { my_q = q; my_tp = tb.tp[q]; my_shift = tb.tp_shift[q]; }
         int cur = 0;
         load_columns(0, request_column(0), 0, false);
         Column ahead = request_column(1);
@@ -638,119 +805,27 @@ struct Band {
                 for (int q = 0; q < tb.n_tp; ++q) keys[q * pitch] = 0;
         }
         for (int s = 0; s < S; ++s) {
-            const bool last = s == S - 1;
             const int nxt = cur ^ 1;
             load_columns(s + 1, ahead, nxt, kLds);
             __syncthreads();                               // row s, its columns and those of row s + 1 are in place
-            if (!last) ahead = request_column(s + 2);
-            const uint32_t *prev = kLds ? rows + cur * pitch : sl.hist + base[s];
-            uint32_t *next = kKeys ? rows : rows + nxt * pitch;
-            uint32_t *out = sl.hist + base[s + 1];
-            const int total = tot[s + 1];
-            const uint32_t index_at_n = index_n(in_flight(s));
-            for (int x = tid; x < total; x += nthreads) {
-                const int d2 = kLds ? int(map[x]) : find_column(nxt, x);
-                const int i = x - col_off[nxt * sh.cols + d2];
-                const int k = group_at[d2 - 1];
-                const uint32_t cut = last ? 0u : tb.CM[cut_at[d2] + uint32_t(i)];
-                uint32_t best = none;
-                const uint32_t *p_k = time_row(k);
-                const int from = offs[k] > s ? offs[k] : s;
-                const uint16_t *fits = lo_tab + (index_at_n + index_at[k] + uint32_t(i)), *far = reach_row(1, k) + i;
-                // degrees from the largest down, four at a time: the first values found are then the best ones,
-                // and a degree whose column holds nothing below the best value is passed over
-                for (int q0 = (tb.n_tp - 1) & ~3; q0 >= 0; q0 -= 4) {
-                    int in_memory[4];                      // requested together, no branches in between
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) in_memory[u] = fits[(q0 + u < tb.n_tp ? q0 + u : q0) * sh.idx_pitch];
-#pragma unroll
-                    for (int u = 3; u >= 0; --u) {
-                        if (q0 + u >= tb.n_tp) continue;
-                        const int tp = tb.tp[q0 + u], d = d2 - tp, shift = tb.tp_shift[q0 + u];
-                        if (d < from || cut > t) continue;
-                        uint32_t floor_v = cut;
-                        if (!kCapped) {
-                            const uint32_t m = col_min[cur * sh.cols + d];
-                            floor_v = m > cut ? m : cut;
-                            if (floor_v >= best) continue;
-                        }
-                        // previous cuts: in the column's range, in memory, within t
-                        const int lo = col_lo[cur * sh.cols + d], hi = col_hi[cur * sh.cols + d];
-                        const int within = far[(q0 + u) * sh.W];
-                        int jl = in_memory[u] > within ? in_memory[u] : within;
-                        jl = jl > lo ? jl : lo;
-                        const int jh = (i - 1) < hi ? (i - 1) : hi;
-                        if (jl > jh) continue;
-                        const uint32_t *p = p_k + (q0 + u) * sh.W;
-                        const uint32_t xi = p[i] + uint32_t(tp) - 1u;
-                        const int off = col_off[cur * sh.cols + d];
-                        if (kKeys) {
-                            const int32_t *e = keys + (q0 + u) * pitch + off;
-                            int32_t m = kNoKey;
-                            int j = jl;
-                            for (; j + 7 <= jh; j += 8) {
-                                const int32_t e0 = e[j], e1 = e[j + 1], e2 = e[j + 2], e3 = e[j + 3];
-                                const int32_t e4 = e[j + 4], e5 = e[j + 5], e6 = e[j + 6], e7 = e[j + 7];
-                                m = least(least(least(e0, e1), m), least(least(e2, e3), e4));
-                                m = least(least(least(e5, e6), e7), m);
-                            }
-                            // what is left, in windows pushed up against jh or down against jl
-                            if (j <= jh) {
-                                if (jh - jl >= 7) {
-                                    j = jh - 7;
-                                    const int32_t e0 = e[j], e1 = e[j + 1], e2 = e[j + 2], e3 = e[j + 3];
-                                    const int32_t e4 = e[j + 4], e5 = e[j + 5], e6 = e[j + 6], e7 = e[j + 7];
-                                    m = least(least(least(e0, e1), m), least(least(e2, e3), e4));
-                                    m = least(least(least(e5, e6), e7), m);
-                                } else {
-                                    for (; j <= jh; ++j) m = least(m, e[j]);
-                                }
-                            }
-                            if (m != kNoKey) {
-                                const uint32_t v = (xi + uint32_t(m)) >> shift;
-                                best = least(best, v);
-                            }
-                        } else {
-                            const uint32_t *r = prev + off;
-                            // the first window may be cut short at its upper end, the last is pushed up
-                            // against jl (cuts seen twice do not matter to a minimum)
-                            int j = jh - 3 > jl ? jh - 3 : jl;
-                            uint32_t t0;
-                            {
-                                const uint32_t p0 = p[j], p1 = p[j + 1], p2 = p[j + 2], p3 = p[j + 3];
-                                const uint32_t r0 = r[j], r1 = r[j + 1], r2 = r[j + 2], r3 = r[j + 3];
-                                t0 = (xi - p0) >> shift;
-                                const uint32_t t1 = (xi - p1) >> shift, t2 = (xi - p2) >> shift, t3 = (xi - p3) >> shift;
-                                const uint32_t v0 = value<kCapped>(r0, t0, cut);
-                                const uint32_t v1 = j + 1 <= jh ? value<kCapped>(r1, t1, cut) : none;
-                                const uint32_t v2 = j + 2 <= jh ? value<kCapped>(r2, t2, cut) : none;
-                                const uint32_t v3 = j + 3 <= jh ? value<kCapped>(r3, t3, cut) : none;
-                                best = least(best, least(least(v0, v1), least(v2, v3)));
-                            }
-                            while (j > jl && (kCapped || (t0 <= best && best > floor_v))) {
-                                j = j - 4 > jl ? j - 4 : jl;
-                                const uint32_t p0 = p[j], p1 = p[j + 1], p2 = p[j + 2], p3 = p[j + 3];
-                                const uint32_t r0 = r[j], r1 = r[j + 1], r2 = r[j + 2], r3 = r[j + 3];
-                                t0 = (xi - p0) >> shift;
-                                const uint32_t t1 = (xi - p1) >> shift, t2 = (xi - p2) >> shift, t3 = (xi - p3) >> shift;
-                                const uint32_t v0 = value<kCapped>(r0, t0, cut), v1 = value<kCapped>(r1, t1, cut);
-                                const uint32_t v2 = value<kCapped>(r2, t2, cut), v3 = value<kCapped>(r3, t3, cut);
-                                best = least(best, least(least(v0, v1), least(v2, v3)));
-                            }
-                        }
-                    }
-                }
-                if (kCapped && best < kInfSum) best += 2u * cut;
-                if (kLds) next[x] = best;
-                // (lanes of a wavefront mostly share a column: the read in front spares the serialised atomics)
-                if (!kCapped && best < col_min[nxt * sh.cols + d2]) atomicMin(&col_min[nxt * sh.cols + d2], best);
-                out[x] = best;
-            }
+            if (s + 1 < S) ahead = request_column(s + 2);
+            StageCtx c;
+            c.s = s; c.cur = cur; c.nxt = nxt; c.t = t; c.none = none;
+            c.last = s == S - 1;
+            c.total = tot[s + 1];
+            c.prev = kLds ? rows + cur * pitch : sl.hist + base[s];
+            c.next = kKeys ? rows : rows + nxt * pitch;
+            c.out = sl.hist + base[s + 1];
+            c.keys = keys;
+            c.cut_tab = tb.CM;
+            c.fits_tab = lo_tab + index_n(in_flight(s));
+            if (kLds && tb.n_tp > 1 && tb.n_tp <= 4 && 2 * c.total <= nthreads) row_cells<kPass, kLds, true>(c, my_q, my_tp, my_shift);
+            else row_cells<kPass, kLds, false>(c, my_q, my_tp, my_shift);
             __syncthreads();                               // row s + 1 is complete
-            if (kKeys && !last) {
+            if (kKeys && !c.last) {
                 // the row as stage s + 1 reads it: a stage that starts at device d runs on the group of d
-                for (int x = tid; x < total; x += nthreads) {
-                    const int d = map[x], i = x - col_off[nxt * sh.cols + d], k = group_at[d];
+                for (int x = tid; x < c.total; x += nthreads) {
+                    const int d = map[x], i = x - int(col[nxt * sh.cols + d].y), k = group_at[d];
                     const uint32_t v = rows[x], *p = time_row(k) + i;
                     for (int q = 0; q < tb.n_tp; ++q)
                         keys[q * pitch + x] = v < kInfSum ? int32_t(v * uint32_t(tb.tp[q]) - p[q * sh.W]) : kNoKey;
@@ -832,11 +907,13 @@ struct Band {
         __syncthreads();
     }
 
-    // All threads: the first cap to try the min-max pass under; -1 when no plan exists under any.
-    __device__ __forceinline__ int64_t bracket() {
+    // All threads: the first cap to try the min-max pass under.  Every group takes work in proportion to its speed; and
+    // every plan cuts somewhere on every link from a group to the next, no cheaper than at the operator of least output.
+    // The optimum lies there on half of the orderings looked at: the ranges under this cap are worked out at once, and
+    // only where they do not meet is a higher one looked for (82 operators and 64 devices: two reach tables and one
+    // round of chains where a search in front of the ranges takes four and two).
+    __device__ __forceinline__ uint32_t guess() {
         const int lane = thread_id() & 63;
-        // A first guess: every group takes work in proportion to its speed.  And a bound: every plan cuts
-        // somewhere on every link from a group to the next, no cheaper than at the operator of least output.
         if (wave == 0) {
             float share = 0.f;
             uint32_t bound = 0;
@@ -858,35 +935,34 @@ struct Band {
             if (lane == 0) { scal[5] = guess < 1.f ? 1u : guess > 1e9f ? 1000000000u : uint32_t(guess); scal[6] = bound; }
         }
         __syncthreads();
-        const int64_t bound = scal[6], g = int64_t(scal[5]) > bound ? int64_t(scal[5]) : bound;
-        int64_t bad = bound - 1, good = -1;                // largest t known to have no plan, smallest t whose chain succeeds
+        const uint32_t g = scal[5] > scal[6] ? scal[5] : scal[6];
+        return g < kTopCap ? g : kTopCap;
+    }
+    // All threads: the next cap to try when the ranges under the first, g, did not meet; -1 when no plan exists under any.
+    __device__ __forceinline__ int64_t bracket(int64_t g) {
+        int64_t bad = g, good = -1;                        // largest t known to have no plan, smallest t whose chain succeeds
         // until the two are within 1/12 of each other: below that the rows hardly get shorter than a workgroup
         for (int round = 0; good < 0 || good - bad > good / 12 + 1; ++round) {
             int64_t at[kTeams];
             for (int w = 0; w < kTeams; ++w) {
-                // the optimum lay at the guess on half of the orderings looked at, within a fifth above on most others
-                const int step = round * kTeams + w;
+                // where the optimum did not lie at the guess it lay within a fifth above on most
+                const int step = round * kTeams + w + 1;
                 int64_t t;
                 if (good >= 0) t = bad + (good - bad) * (w + 1) / (kTeams + 1);
-                else t = step == 0 ? g : step == 1 ? g + g * 7 / 32 + 1 : step == 2 ? g + g * 5 / 8 + 1 : step == 3 ? 5 * g / 2 + 1
+                else t = step == 1 ? g + g * 7 / 32 + 1 : step == 2 ? g + g * 5 / 8 + 1 : step == 3 ? 5 * g / 2 + 1
                          : step == 4 ? 8 * g + 1 : step == 5 ? 64 * g + 1 : int64_t(kTopCap);
                 at[w] = t < int64_t(kTopCap) ? t : int64_t(kTopCap);
             }
             __syncthreads();
             cut_masks(kTeams, uint32_t(at[0]), uint32_t(at[1]));
             for (int w = 0; w < kTeams; ++w) reach_table<true>(uint32_t(at[w]), w);
-            __syncthreads();
-            if (wave < kTeams) {
-                const bool fine = forward_chain(wave, masks(wave), chain + wave * sh.cols, nullptr);
-                if (lane == 0) scal[wave] = fine ? 1u : 0u;
-            }
-            __syncthreads();
+            bool fine[kTeams];
+            run_chains<false>(nullptr, nullptr, fine[0], fine[1]);
             for (int w = kTeams - 1; w >= 0; --w)
-                if (scal[w] != 0) good = at[w];
+                if (fine[w]) good = at[w];
             for (int w = 0; w < kTeams; ++w)
-                if (scal[w] == 0 && at[w] > bad) bad = at[w];
+                if (!fine[w] && at[w] > bad) bad = at[w];
             if (good < 0 && bad >= int64_t(kTopCap)) return -1;           // no plan under any cap
-            if (good == g) break;                                          // near enough
         }
         return good;
     }
@@ -918,7 +994,7 @@ struct Band {
         const uint32_t th1 = uint32_t(x1 < kTopCap ? x1 : kTopCap), th2 = uint32_t(x2 < kTopCap ? x2 : kTopCap);   // 2c - e > 0; > cap
         const uint32_t m_cap = uint32_t(tb.M);
         const int64_t *PP = mem, *PS = mem + sh.W;
-        const int pitch = sh.row_cap + kRowPad;
+        if (kLds) place_rows(2, 2, kCountBytes);
         uint16_t *back = reinterpret_cast<uint16_t *>(sl.hist);
         auto row_h = [&](int b) -> uint32_t * { return kLds ? rows + b * pitch : sl.spare_h + b * sl.row; };
         auto row_n = [&](int b) -> uint16_t * { return kLds ? counts + b * pitch : sl.spare_n + b * sl.row; };
@@ -939,7 +1015,7 @@ struct Band {
             const int total = tot[s], at = base[s];
             for (int x = tid; x < total; x += nthreads) {
                 const int d = kLds ? int(map[x]) : find_column(nxt, x);
-                const int i = x - col_off[nxt * sh.cols + d];
+                const int i = x - int(col[nxt * sh.cols + d].y);
                 const int k = group_at[d], end = offs[k + 1];
                 const int64_t mem_dev = tb.type_mem[type[k]];
                 const uint32_t cut = s > 0 ? tb.CM[cut_at[d] + uint32_t(i)] : 0u;
@@ -957,13 +1033,14 @@ struct Band {
                         if (q0 + u >= tb.n_tp) continue;
                         const int q = q0 + u, tp = tb.tp[q], d1 = d + tp;
                         if (d1 > end) continue;
-                        const int lo = col_lo[cur * sh.cols + d1], hi = col_hi[cur * sh.cols + d1];
+                        const uint2 w = col[cur * sh.cols + d1];
+                        const int lo = col_lo(w), hi = col_hi(w);
                         const int within = far[q * sh.W];
                         const int jl = (i + 1) > lo ? (i + 1) : lo;
                         int jh = in_memory[u] < within ? in_memory[u] : within;
                         jh = jh < hi ? jh : hi;
                         const uint32_t *p = p_k + q * sh.W;
-                        const int off = col_off[cur * sh.cols + d1];
+                        const int off = int(w.y);
                         const uint32_t xi = p[i] - uint32_t(tp) + 1u;
                         const int shift = tb.tp_shift[q];
                         const int64_t capm = int64_t(tp) * mem_dev;
@@ -1012,8 +1089,14 @@ struct Band {
     template <int kForms>
     __device__ __forceinline__ int64_t run(int form, uint32_t t) {
         if (!prepare(t)) return kInf;
-        if ((kForms & kMinMax) && form == kMinMax) return rows_fit ? value_pass_in<false, true>(t) : value_pass_in<false, false>(t);
-        if ((kForms & kSum) && form == kSum) return rows_fit && keys_fit ? value_pass_in<true, true>(t) : value_pass_in<true, false>(t);
+        if ((kForms & (kMinMax | kSum)) && (form == kMinMax || form == kSum)) {
+            const bool values_fit = most_cells <= cells_that_fit(kValueBytes);
+            if ((kForms & kMinMax) && form == kMinMax)
+                return values_fit ? value_pass_in<kPassMinMax, true>(t) : value_pass_in<kPassMinMax, false>(t);
+            if (keys_fit && most_cells <= cells_that_fit(keys_bytes())) return value_pass_in<kPassKeys, true>(t);
+            return keys_fit && values_fit ? value_pass_in<kPassSum, true>(t) : value_pass_in<kPassSum, false>(t);
+        }
+        const bool rows_fit = most_cells <= cells_that_fit(kCountBytes);
         if ((kForms & kH1) && form == kH1) return rows_fit ? h1_pass_in<false, true>(t) : h1_pass_in<false, false>(t);
         if (kForms & kAny) return rows_fit ? h1_pass_in<true, true>(t) : h1_pass_in<true, false>(t);
         return kInf;
@@ -1160,7 +1243,7 @@ struct Band {
     // which no pass needs meanwhile), window after window, each starting at the next value there is.
     __device__ __forceinline__ uint32_t count_values(uint32_t a, uint32_t b, uint32_t limit, uint32_t &last) {
         const int tid = thread_id();
-        const uint32_t words = uint32_t(2 * (sh.row_cap + kRowPad)) & ~63u, span = words * 32u;
+        const uint32_t words = (room / 4u) & ~63u, span = words * 32u;
         uint32_t *bits = rows;
         uint32_t found = 0, from = a + 1u;
         while (from <= b && found < limit) {
@@ -1275,17 +1358,19 @@ struct Band {
         __syncthreads();
         return ok[0] + 2ull * uint64_t(S - 1) * cut;
     }
+    // 2^31 over the largest degree that a group has devices for.
+    __device__ __forceinline__ uint32_t key_limit() const {
+        uint32_t devices = 1;
+        int degree = 1;
+        for (int x = 0; x < n_sets; ++x) devices = use[x] > devices ? use[x] : devices;
+        for (int q = 1; q < tb.n_tp; ++q) degree = uint32_t(tb.tp[q]) <= devices ? tb.tp[q] : degree;
+        return uint32_t(uniform(int(kInfSum / uint32_t(degree))));
+    }
     // The largest cap under which sums stay below 2^31: S stage and twice S transfer times of at most the cap, or
     // any cap when `most` (most_sum) does.  Key rows hold sums times a degree that a group has devices for; a pass
     // whose sums fit but not those products works from the workspace's value rows, as one does whose rows leave LDS.
     __device__ __forceinline__ int64_t largest_cap(uint64_t most, bool keys) const {
-        int degree = 1;
-        if (keys) {
-            uint32_t devices = 1;
-            for (int x = 0; x < n_sets; ++x) devices = use[x] > devices ? use[x] : devices;
-            for (int q = 1; q < tb.n_tp; ++q) degree = uint32_t(tb.tp[q]) <= devices ? tb.tp[q] : degree;
-        }
-        const int64_t limit = int64_t(kInfSum) / degree;
+        const int64_t limit = keys ? int64_t(key_limit()) : int64_t(kInfSum);
         return most < uint64_t(limit) - 1u ? INT64_MAX : limit / (3ll * S) - 1;
     }
 };

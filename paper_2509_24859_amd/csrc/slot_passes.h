@@ -65,7 +65,7 @@ inline SlotShape slot_shape(int L, int S_max) {
 
 template <bool kResident>
 struct Slots {
-    static constexpr bool kChoosesSlicing = false;
+    static constexpr bool kChoosesSlicing = false, kGuesses = false;
     // see k2_sweep.hip; a climb passes over the values that change nothing and takes 1 to 3 passes, so kMaxClimb is a
     // bound for constructed inputs, where each of many operators of a few microseconds changes something
     static constexpr int kMaxClimb = 256, kMaxTries = 24;
@@ -91,6 +91,8 @@ struct Slots {
     int nthreads, wave;
     int S, L, n_rows, n_links;
     bool keys_fit;
+    static constexpr bool reached = true;        // (guess() has looked)
+    __device__ __forceinline__ int64_t bracket(int64_t) const { return -1; }
     int64_t count_cap;                           // as in mesh_band.h
 
     __device__ __forceinline__ Slots(const TablesDev &t, const SlotShape &s, unsigned char *lds, SlotInfo &si,
@@ -498,7 +500,7 @@ struct Slots {
     // All threads: the first cap to try the min-max pass under; -1 when no plan exists under any.  As in
     // mesh_band.h, with kTeams caps at once: the speeds of the stages give a first guess, the cheapest cut on
     // every link a bound from below.
-    __device__ __forceinline__ int64_t bracket() {
+    __device__ __forceinline__ int64_t guess() {
         const int tid = threadIdx.x, lane = tid & 63;
         if (tid == 0) scal[6] = 0;
         __syncthreads();
