@@ -38,6 +38,7 @@
 namespace harp {
 namespace meshband {
 
+using fastdp::lds_barrier;
 using fastdp::uniform;
 using fastdp::wave_sync;
 
@@ -45,6 +46,7 @@ constexpr uint32_t kNoCut = 0xFFFFu;
 constexpr uint32_t kInfSum = 0x80000000u;        // least sums stay below this (largest_cap)
 constexpr uint32_t kTopCap = 0x7FFFFFFFu;        // no time on these tables is larger
 constexpr int kRowPad = 4;                       // a window of four entries may overrun a row
+constexpr int kReachRun = 8;
 constexpr int kTeams = 2;                        // chains worked at once
 
 // LDS layout of a launch (byte offsets into dynamic LDS) and its capacities.
@@ -57,7 +59,8 @@ struct BandShape {
     int idx_pitch;               // feasibility index
     uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_mem, o_chain, o_ok, o_col, o_small, o_prow,
         o_set_of, total;
-    uint32_t w_inv;              // x / W is the high half of x * w_inv for x below 2^32 / W
+    int runs;                    // of kReachRun entries in a row of time sums or reaches
+    uint32_t runs_inv;           // x / runs is the high half of x * runs_inv for x below 2^32 / runs (runs above 1)
 };
 
 constexpr int kMaxDevices = 2048;                // columns sit in LDS, 24 bytes each
@@ -156,6 +159,13 @@ struct Band {
     uint16_t *map;               // [pitch] column of a cell
     uint32_t room;               // bytes for rows, counts and map
     int pitch;                   // cells of a row that fit, and a window
+    bool ranges_in_lds;          // the last prepared cap: F, B and off sit in LDS, not in the slice
+    bool whole;                  // the last pass: all its rows are in LDS, none in the slice
+    uint32_t *rows_all, *ring;   // rows of the whole pass; rows it keeps the last ones of
+    uint32_t pass_room;          // what the ranges leave of the room
+    uint32_t *pass_at;
+    bool chains_in_lds;
+    int all_cells;               // of all rows of the last prepared cap
     bool reached;                // the last prepared cap: its chains get from end to end
     int most_cells;              // of a row of the last prepared cap
     int map_shift;               // load_columns
@@ -199,6 +209,8 @@ struct Band {
         pitch = most_cells = map_shift = 0;
         reached = false;
         keys_fit = true;
+        ranges_in_lds = chains_in_lds = whole = false;
+        all_cells = 0;
         least_cut = 1;
         count_cap = 0;
     }
@@ -253,6 +265,8 @@ struct Band {
         __syncthreads();
     }
 
+    __device__ __forceinline__ int shift_of(int q) const { return tb.tp_shift[q]; }
+    __device__ __forceinline__ int tp_of(int q) const { return tb.tp[q]; }
     __device__ __forceinline__ int in_flight(int s) const { return (S - s) < tb.M ? (S - s) : tb.M; }
     // feasibility index of a stage with n micro-batches in flight: entry of degree q of group k at
     // index_n(n) + index_at[k] + q * idx_pitch (the index and the cut table have fewer than 2^28 entries)
@@ -269,7 +283,7 @@ struct Band {
     // ordering is malformed (bad), 2 when no plan can exist, 3 when it does not fit this launch's LDS.
     __device__ __forceinline__ int load(int S_, int K_, const int32_t *og, int S_max, int G_max) {
         const int tid = thread_id();
-        S = S_; K = K_;
+        S = uniform(S_); K = uniform(K_);
         // (more groups than the problem has cannot be distinct)
         int bad = (S < 1 || S > S_max || K < 1 || K > G_max || K > sh.K_cap) ? 1 : 0;
         if (!bad)
@@ -299,7 +313,7 @@ struct Band {
             if (k + 1 < K) link_at[K + k] = uint32_t(g * tb.G + order[k + 1]) * uint32_t(tb.pitch32);
         }
         __syncthreads();
-        D = offs[K];
+        D = uniform(offs[K]);
         if (S > L || S < K || S > D) return 2;
         n_sets = 0;
         for (int k = 0; k < K; ++k) n_sets += set_of[k] == k ? 1 : 0;
@@ -328,7 +342,7 @@ struct Band {
         __syncthreads();
         for (int k = tid; k < K; k += nthreads)
             atomicMax(&use[prow_at[k] / uint32_t(tb.n_tp * sh.W)], uint32_t(offs[k + 1] - offs[k]));
-        for (int d = 1 + tid; d < D; d += nthreads) cut_at[d] = link_at[link_of(d)];
+        for (int d = tid; d <= D; d += nthreads) cut_at[d] = link_at[d == 0 ? 0 : d == D ? K - 1 : link_of(d)];
         __syncthreads();
         return 0;
     }
@@ -364,40 +378,37 @@ struct Band {
         }
     }
     // All threads: how far a stage gets under t on every (set, degree), into table `side`.  Upwards: entry j = the
-    // highest cut i with time(j, i) <= t; downwards: entry i = the lowest cut j with time(j, i) <= t.  A binary search
-    // is a chain of LDS reads; a thread has four of them under way (4,096 orderings of 82 operators and 64 devices: of
-    // an ordering's 157 us the tables took 30 with one after the other).
+    // highest cut i with time(j, i) <= t; downwards: entry i = the lowest cut j with time(j, i) <= t.  Neither falls from
+    // one entry to the next, so a thread finds the first of a run of kReachRun entries by bisection and goes on from there:
+    // a cut or so per entry, where a bisection each takes seven or eight steps (4,096 orderings of 82 operators and 64
+    // devices: of an ordering's 145 us the tables took 31, now @@).
     template <bool kUp>
     __device__ __forceinline__ void reach_table(uint32_t t, int side) {
-        const int tid = thread_id();
         uint16_t *to = reach + side * n_sets * tb.n_tp * sh.W;
-        const int n = n_sets * tb.n_tp * sh.W, top_step = 1 << (31 - __clz(L));
-        for (int x0 = tid; x0 < n; x0 += 4 * nthreads) {
-            const uint32_t *p[4];
-            uint32_t target[4];
-            int pos[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int x = x0 + u * nthreads < n ? x0 + u * nthreads : x0;
-                const int r = int(__umulhi(uint32_t(x), sh.w_inv)), e = x - r * sh.W;
-                const uint64_t far = uint64_t(t) * uint32_t(tb.tp[r % tb.n_tp]);
-                p[u] = prow + r * sh.W;
-                const uint32_t pe = p[u][e];
-                if (kUp) target[u] = pe + far > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(pe + far);
-                else target[u] = pe > far ? uint32_t(pe - far) : 0u;
-                pos[u] = e;
-            }
-            for (int step = top_step; step > 0; step >>= 1) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int nx = kUp ? pos[u] + step : pos[u] - step;
-                    if (kUp) pos[u] = nx <= L && p[u][nx <= L ? nx : L] <= target[u] ? nx : pos[u];
-                    else pos[u] = nx >= 0 && p[u][nx >= 0 ? nx : 0] >= target[u] ? nx : pos[u];
+        const int top_step = 1 << (31 - __clz(L));
+        for (int x = thread_id(); x < n_sets * tb.n_tp * sh.runs; x += nthreads) {
+            const int r = sh.runs == 1 ? x : int(__umulhi(uint32_t(x), sh.runs_inv)), e0 = (x - r * sh.runs) * kReachRun, end = e0 + kReachRun < sh.W ? e0 + kReachRun : sh.W;
+            const uint64_t far = uint64_t(t) * uint32_t(tb.tp[r % tb.n_tp]);
+            const uint32_t reach_of = far > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(far);
+            const uint32_t *p = prow + r * sh.W;
+            uint16_t *out = to + r * sh.W;
+            int pos = e0;
+            for (int e = e0; e < end; ++e) {
+                const uint32_t pe = p[e];
+                const uint32_t target = kUp ? (pe > 0xFFFFFFFFu - reach_of ? 0xFFFFFFFFu : pe + reach_of) : (pe > reach_of ? pe - reach_of : 0u);
+                if (e == e0) {
+                    for (int step = top_step; step > 0; step >>= 1) {
+                        const int nx = kUp ? pos + step : pos - step;
+                        if (kUp) pos = nx <= L && p[nx <= L ? nx : L] <= target ? nx : pos;
+                        else pos = nx >= 0 && p[nx >= 0 ? nx : 0] >= target ? nx : pos;
+                    }
+                } else if (kUp) {
+                    while (pos < L && p[pos + 1] <= target) ++pos;
+                } else {
+                    while (p[pos] < target) ++pos;                     // (p[e] is no less)
                 }
+                out[e] = uint16_t(pos);
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (x0 + u * nthreads < n) to[x0 + u * nthreads] = uint16_t(pos[u]);
         }
     }
     // highest cut <= i in a mask, -1 when there is none; lowest cut >= i, > L when there is none
@@ -432,7 +443,7 @@ struct Band {
     }
     template <bool kBack>
     __device__ __forceinline__ void chain_step(const ChainLane &l, int c, int s, int side, const unsigned long long *m,
-                                               const uint16_t *from, uint16_t *to, uint16_t *G) const {
+                                               const uint16_t *from, uint16_t *to, bool keep) const {
         const uint16_t *far = reach + side * n_sets * tb.n_tp * sh.W;
         const uint16_t *fits = (kBack ? lo_tab : hi_tab) + index_n(in_flight(s));
         int best = kBack ? INT32_MAX : -1;
@@ -443,7 +454,7 @@ struct Band {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int q = q0 + u < tb.n_tp ? q0 + u : tb.n_tp - 1;
-                const int d = kBack ? l.d + tb.tp[q] : l.d - tb.tp[q];
+                const int d = kBack ? l.d + tp_of(q) : l.d - tp_of(q);
                 v[u] = from[(kBack ? d <= l.edge : d >= l.edge) ? d : sh.cols];      // [cols]: no cut
             }
 #pragma unroll
@@ -476,23 +487,32 @@ struct Band {
             if (best >= 0 && !last) best = mask_down(m + l.link, best);
             if (best < s + 1 || l.d > d_hi || (last && l.d != D)) best = -1;
         }
-        const int row = kBack ? s : s + 1, outside = kBack ? D : 0;        // the column that only the first row has
+        const int outside = kBack ? D : 0;                         // the column that only the first row has
+        const uint32_t row = uint32_t(kBack ? s : s + 1) * uint32_t(sh.cols);
         const uint16_t v = best < 0 ? uint16_t(kNoCut) : uint16_t(best);
         if (kBack ? l.d < D : l.d <= D) {
             to[l.d] = v;
-            if (G) G[size_t(row) * sh.cols + l.d] = v;
+            if (keep) put_range<kBack>(row + l.d, v);
         }
         if (c == 0 && (threadIdx.x & 63) == 0) {
             to[outside] = uint16_t(kNoCut);
-            if (G) G[size_t(row) * sh.cols + outside] = uint16_t(kNoCut);
+            if (keep) put_range<kBack>(row + outside, uint16_t(kNoCut));
         }
     }
-    // All threads: two chains at once, the one of team 0 forwards, that of team 1 forwards or (kBack) backwards, a
-    // wavefront for every 64 columns where there are as many, and a barrier per stage.  F0, B1 null: the verdicts only.
-    // Verdict: (S, D) reaches L, or (0, 0) is reached.  (4,096 orderings of 82 operators and 64 devices: a chain on one
-    // wavefront, group and row addresses worked out in every stage, took 14 us, of which the stages are about 12.)
     template <bool kBack>
-    __device__ __forceinline__ void run_chains(uint16_t *F0, uint16_t *B1, bool &good0, bool &good1) {
+    __device__ __forceinline__ void put_range(uint32_t at, uint16_t v) const {
+        if (chains_in_lds) reinterpret_cast<uint16_t *>(rows)[at + (kBack ? n_ranges() : 0u)] = v;
+        else if (kBack) sl.B[at] = v;
+        else sl.F[at] = v;
+    }
+    // Ranges in LDS, in front of the rows: F, B, off, of n_ranges entries each.  (Kept as pointers beside those of the slice
+    // they would be chosen between by name, and the whole object stays in memory.)
+    __device__ __forceinline__ uint32_t n_ranges() const { return uint32_t(S + 1) * uint32_t(sh.cols); }
+    // All threads: two chains at once, the one of team 0 forwards, that of team 1 forwards or (kBack) backwards, a
+    // wavefront for every 64 columns where there are as many, and a barrier per stage that waits for LDS only.  Backwards: F and
+    // B are kept, in the room of the rows where they fit, else in the slice.  Verdict: (S, D) reaches L, or (0, 0) is reached.
+    template <bool kBack>
+    __device__ __forceinline__ void run_chains(bool &good0, bool &good1) {
         const int chunks = (D + 63) >> 6, half = nthreads >> 7, waves = chunks < half ? chunks : half;
         const int team = wave < waves ? 0 : wave < 2 * waves ? 1 : 2, first = team == 1 ? wave - waves : wave;
         const int pitch16 = sh.cols + 1;
@@ -503,8 +523,8 @@ struct Band {
             if (kBack && b == 2) v = d == D ? uint16_t(L) : v;
             else if (b == 0 || b == 2) v = d == 0 ? uint16_t(0) : v;
             chain[x] = v;
-            if (b == 0 && F0 && d <= D) F0[d] = v;
-            if (kBack && b == 2 && d <= D) B1[size_t(S) * sh.cols + d] = v;
+            if (kBack && b == 0 && d <= D) put_range<false>(uint32_t(d), v);
+            if (kBack && b == 2 && d <= D) put_range<true>(uint32_t(S * sh.cols + d), v);
         }
         __syncthreads();
         const bool back = kBack && team == 1;
@@ -517,14 +537,15 @@ struct Band {
                 for (int c = first; c < chunks; c += waves) {
                     if (back) {
                         if (chunks > waves) l = chain_lane<true>(c);
-                        chain_step<true>(l, c, S - 1 - n, 1, m, from, to, B1);
+                        chain_step<true>(l, c, S - 1 - n, 1, m, from, to, true);
                     } else {
                         if (chunks > waves) l = chain_lane<false>(c);
-                        chain_step<false>(l, c, n, team, m, from, to, team == 0 ? F0 : nullptr);
+                        chain_step<false>(l, c, n, team, m, from, to, kBack);
                     }
                 }
-            __syncthreads();
+            lds_barrier();
         }
+        if (kBack && !chains_in_lds) __syncthreads();
         const int at = (S & 1) * pitch16;
         good0 = uniform(chain[at + D]) == L;
         good1 = kBack ? uniform(chain[2 * pitch16 + at]) == 0 : uniform(chain[2 * pitch16 + at + D]) == L;
@@ -539,29 +560,14 @@ struct Band {
         reach_table<true>(t, 0);
         reach_table<false>(t, 1);
         bool good0, good1;
-        run_chains<true>(sl.F, sl.B, good0, good1);        // (its first barrier stands behind the tables)
+        chains_in_lds = n_ranges() * 4u <= room;
+        run_chains<true>(good0, good1);                    // (its first barrier stands behind the tables)
         reached = good0 && good1;
         if (!reached) return false;
         // cells of every row: columns one after the other (column 0 has one in row 0), a wavefront per row
         for (int s = wave; s <= S; s += nthreads >> 6) {
-            int total = s == 0 ? 1 : 0;
-            const size_t row = size_t(s) * sh.cols;
-            if (lane == 0) {
-                sl.off[row] = 0;
-                if (s > 0) { sl.F[row] = 0; sl.B[row] = 1; }
-            }
-            for (int d = 1 + lane; d - lane <= D; d += 64) {
-                uint32_t f = kNoCut, b = kNoCut;
-                if (d <= D) { f = sl.F[row + d]; b = sl.B[row + d]; }
-                const bool has = f != kNoCut && b != kNoCut && b <= f;
-                const int w = has ? int(f - b) + 1 : 0, inc = int(fastdp::wave_scan(uint32_t(w), fastdp::sum2));
-                if (d <= D) {
-                    sl.off[row + d] = total + inc - w - (has ? int(b) : 0);
-                    if (!has) { sl.F[row + d] = 0; sl.B[row + d] = 1; }
-                }
-                total += __builtin_amdgcn_readlane(inc, 63);
-            }
-            if (lane == 0) tot[s] = total;
+            const int n = number_row(s, false);
+            if (lane == 0) tot[s] = n;
         }
         __syncthreads();
         int most = 0, sum = 0, least = INT32_MAX;
@@ -572,22 +578,65 @@ struct Band {
             most = n > most ? n : most;
             least = n < least ? n : least;
         }
+        all_cells = uniform(sum);
+        most = uniform(most);
+        // F, B and the numbering stay in LDS where the rows of the whole pass fit beside them (with room for any form), else
+        // they go to the slice: rows that leave LDS for them cost more
+        const uint32_t bytes = (n_ranges() * 8u + 15u) & ~15u;
+        ranges_in_lds = chains_in_lds && bytes + uint32_t(all_cells) * 4u + uint32_t(most) * 16u + 256u <= room;
+        pass_at = rows + (ranges_in_lds ? bytes / 4u : 0u);
+        pass_room = room - (ranges_in_lds ? bytes : 0u);
+        for (int s = wave; s <= S; s += nthreads >> 6) number_row(s, true);
         most_cells = most;
         __syncthreads();
         return least > 0;
     }
 
+    // One wavefront: the cells of row s; their numbering goes to LDS or to the slice (keep).
+    __device__ __forceinline__ int number_row(int s, bool keep) const {
+        const int lane = thread_id() & 63;
+        int total = s == 0 ? 1 : 0;
+        const uint32_t row = uint32_t(s) * uint32_t(sh.cols);
+        for (int d = 1 + lane; d - lane <= D; d += 64) {
+            uint32_t f = kNoCut, b = kNoCut;
+            if (d <= D) {
+                if (chains_in_lds) { const uint16_t *f_lds = reinterpret_cast<const uint16_t *>(rows) + row + d; f = f_lds[0]; b = f_lds[n_ranges()]; }
+                else { f = sl.F[row + d]; b = sl.B[row + d]; }
+            }
+            const bool has = f != kNoCut && b != kNoCut && b <= f;
+            const int w = has ? int(f - b) + 1 : 0, inc = int(fastdp::wave_scan(uint32_t(w), fastdp::sum2));
+            if (keep && d <= D) put_column(row + d, has ? b : 1u, has ? f : 0u, total + inc - w - (has ? int(b) : 0));
+            total += __builtin_amdgcn_readlane(inc, 63);
+        }
+        if (keep && lane == 0) put_column(row, s > 0 ? 1u : 0u, 0u, 0);
+        return total;
+    }
+    __device__ __forceinline__ void put_column(uint32_t at, uint32_t lo, uint32_t hi, int off) const {
+        if (ranges_in_lds) {
+            uint16_t *f = reinterpret_cast<uint16_t *>(rows) + at;
+            f[0] = uint16_t(hi);
+            f[n_ranges()] = uint16_t(lo);
+            reinterpret_cast<int32_t *>(rows)[n_ranges() + at] = off;
+        } else { sl.F[at] = uint16_t(hi); sl.B[at] = uint16_t(lo); sl.off[at] = off; }
+    }
+    struct Column { int lo, hi, off; };
+    __device__ __forceinline__ Column column(uint32_t at) const {
+        Column c;
+        if (ranges_in_lds) {
+            const uint16_t *f = reinterpret_cast<const uint16_t *>(rows) + at;
+            c.hi = f[0];
+            c.lo = f[n_ranges()];
+            c.off = reinterpret_cast<const int32_t *>(rows)[n_ranges() + at];
+        } else { c.lo = sl.B[at]; c.hi = sl.F[at]; c.off = sl.off[at]; }
+        return c;
+    }
     // Range and numbering of row s into column buffer b, and the column of every cell; a thread's first
     // column is requested ahead (request_column) and waits in a register.  2^map_shift threads share a column: they
     // write its part of the map together.  Column 0 has a cell in row 0 only.
-    struct Column { int lo, hi, off; };
     __device__ __forceinline__ Column request_column(int s) const {
         const int d = 1 + (thread_id() >> map_shift);
         Column c{1, 0, 0};
-        if (d <= D) {
-            const size_t at = size_t(s) * sh.cols + d;
-            c.lo = sl.B[at]; c.hi = sl.F[at]; c.off = sl.off[at];
-        }
+        if (d <= D) c = column(uint32_t(s * sh.cols + d));
         return c;
     }
     __device__ __forceinline__ void store_column(int d, const Column &c, int b, bool with_map) {
@@ -603,10 +652,8 @@ struct Band {
         const int tid = thread_id();
         const int d0 = 1 + (tid >> map_shift);
         if (d0 <= D) store_column(d0, first, b, with_map);
-        for (int d = d0 + (nthreads >> map_shift); d <= D; d += nthreads >> map_shift) {
-            const size_t at = size_t(s) * sh.cols + d;
-            store_column(d, Column{sl.B[at], sl.F[at], sl.off[at]}, b, with_map);
-        }
+        for (int d = d0 + (nthreads >> map_shift); d <= D; d += nthreads >> map_shift)
+            store_column(d, column(uint32_t(s * sh.cols + d)), b, with_map);
         if (tid == 0) {
             col[b * sh.cols] = uint2{s == 0 ? 0u : 1u, 0u};
             col_min[b * sh.cols] = 0xFFFFFFFFu;
@@ -629,11 +676,19 @@ struct Band {
         return lo;
     }
 
-    // Rows of a pass in what the sets of an ordering leave of the LDS: n rows of values, two of counts (H-1F1B), the map.
-    __device__ __forceinline__ int cells_that_fit(int bytes_per_cell) const { return int(room / uint32_t(bytes_per_cell)) & ~7; }
-    __device__ __forceinline__ void place_rows(int n, int n_counts, int bytes_per_cell) {
-        pitch = cells_that_fit(bytes_per_cell) + kRowPad;
-        counts = reinterpret_cast<uint16_t *>(rows + n * pitch);
+    // Rows of a pass in what the sets and the ranges of an ordering leave of the LDS: n rows of values of which a pass
+    // keeps the last ones, two of counts (H-1F1B), the map.
+    __device__ __forceinline__ int cells_that_fit(int bytes_per_cell) const { return int(pass_room / uint32_t(bytes_per_cell)) & ~7; }
+    // All rows one after the other where they fit (whole; cell_bytes: of what a cell leaves behind, ring_bytes: of the
+    // rest): nothing of the pass is stored to the slice then, and the plan is found from LDS.  Else the last rows, cut for
+    // as many cells as fit.
+    __device__ __forceinline__ void place_rows(int n, int n_counts, int cell_bytes, int ring_bytes, int bytes_per_cell) {
+        const uint32_t most = (uint32_t(most_cells) + 7u) & ~7u, all = (uint32_t(all_cells) * uint32_t(cell_bytes) + 31u) & ~15u;
+        whole = all + most * uint32_t(ring_bytes) <= pass_room;
+        rows_all = pass_at;
+        ring = whole ? pass_at + all / 4u : pass_at;
+        pitch = (whole ? int(most) : cells_that_fit(bytes_per_cell)) + kRowPad;
+        counts = reinterpret_cast<uint16_t *>(ring + n * pitch);
         map = counts + n_counts * pitch;
     }
 
@@ -661,9 +716,9 @@ struct Band {
         uint32_t t, none;
     };
     template <int kPass, bool kLds>
-    __device__ __forceinline__ void degree_best(const StageCtx &c, int q, int tp, int shift, int d2, int i, uint32_t cut, int from,
+    __device__ __forceinline__ void degree_best(const StageCtx &c, int q, int shift, int d2, int i, uint32_t cut, int from,
                                                 int in_memory, int within, const uint32_t *p_k, uint32_t &best) const {
-        const int d = d2 - tp;
+        const int tp = 1 << shift, d = d2 - tp;
         if (d < from) return;
         uint32_t floor_v = cut;
         if (kPass == kPassMinMax) {
@@ -733,23 +788,24 @@ struct Band {
     // The cells of a row.  kSplit: four lanes share a cell, a degree each (at most four degrees, my_*: the lane's own):
     // a row of few cells is bound by the chain of one cell's degrees.
     template <int kPass, bool kLds, bool kSplit>
-    __device__ __forceinline__ void row_cells(const StageCtx &c, int my_q, int my_tp, int my_shift) {
+    __device__ __forceinline__ void row_cells(const StageCtx &c, int my_q, int my_shift) {
         const int tid = thread_id();
         const int part = kSplit ? tid & 3 : 0, step = kSplit ? nthreads >> 2 : nthreads;
-        for (int x = kSplit ? tid >> 2 : tid; x < c.total; x += step) {
+        int x = kSplit ? tid >> 2 : tid;
+        for (; x < c.total; x += step) {
             const int d2 = kLds ? int(map[x]) : find_column(c.nxt, x);
             const int i = x - int(col[c.nxt * sh.cols + d2].y);
             const int k = group_at[d2 - 1];
-            const uint32_t cut = c.last ? 0u : c.cut_tab[cut_at[d2] + uint32_t(i)];
+            uint32_t cut = c.cut_tab[cut_at[d2] + uint32_t(i)];        // (read behind the last stage too: no branch to wait in)
             uint32_t best = c.none;
             const uint32_t *p_k = time_row(k);
             const int from = offs[k] > c.s ? offs[k] : c.s;
             const uint16_t *fits = c.fits_tab + (index_at[k] + uint32_t(i)), *far = reach_row(1, k) + i;
             if (kSplit) {
-                int in_memory = fits[my_q * sh.idx_pitch];
-                const int within = far[my_q * sh.W];
-                if (cut <= c.t && my_tp != 0)
-                    degree_best<kPass, kLds>(c, my_q, my_tp, my_shift, d2, i, cut, from, in_memory, within, p_k, best);
+                const int in_memory = fits[my_q * sh.idx_pitch], within = far[my_q * sh.W];
+                cut = c.last ? 0u : cut;
+                if (cut <= c.t && my_shift >= 0)
+                    degree_best<kPass, kLds>(c, my_q, my_shift, d2, i, cut, from, in_memory, within, p_k, best);
                 best = least(best, uint32_t(__builtin_amdgcn_update_dpp(int(best), int(best), 0xB1, 0xF, 0xF, false)));   // lanes 1 and 2 apart
                 best = least(best, uint32_t(__builtin_amdgcn_update_dpp(int(best), int(best), 0x4E, 0xF, 0xF, false)));
                 if (part != 0) continue;
@@ -766,19 +822,19 @@ struct Band {
                     }
                     // (requested together: a load that the compiler moves into a branch is waited for there)
                     asm volatile("" : "+v"(in_memory[0]), "+v"(in_memory[1]), "+v"(in_memory[2]), "+v"(in_memory[3]));
+                    cut = c.last ? 0u : cut;
                     if (cut > c.t) break;
 #pragma unroll
                     for (int u = 3; u >= 0; --u)
                         if (q0 + u < tb.n_tp)
-                            degree_best<kPass, kLds>(c, q0 + u, tb.tp[q0 + u], tb.tp_shift[q0 + u], d2, i, cut, from, in_memory[u],
-                                                     within[u], p_k, best);
+                            degree_best<kPass, kLds>(c, q0 + u, shift_of(q0 + u), d2, i, cut, from, in_memory[u], within[u], p_k, best);
                 }
             }
             if (kPass != kPassMinMax) best = best < c.none ? best + 2u * cut : c.none;
             if (kLds) c.next[x] = best;
             // (lanes of a wavefront mostly share a column: the read in front spares the serialised atomics)
             if (kPass == kPassMinMax && best < col_min[c.nxt * sh.cols + d2]) atomicMin(&col_min[c.nxt * sh.cols + d2], best);
-            c.out[x] = best;
+            if (!kLds || c.out) c.out[x] = best;
         }
     }
     template <int kPass, bool kLds>
@@ -788,18 +844,24 @@ struct Band {
         constexpr int32_t kNoKey = INT32_MAX;
         // sums are below 2^31, and where keys are formed below 2^31 / degree, less one (largest_cap)
         const uint32_t none = kPass == kPassMinMax ? t + 1u : kPass == kPassSum && kLds ? key_limit() - 1u : kInfSum;
-        if (kLds) place_rows(kKeys ? 1 + tb.n_tp : 2, 0, kKeys ? keys_bytes() : kValueBytes);
-        int32_t *keys = reinterpret_cast<int32_t *>(rows + pitch);         // [n_tp][pitch] (kKeys)
-        int my_q = 0, my_tp = 0, my_shift = 0;                             // (no degree: no stage)
+        // kept for the plan: the rows of values; for the next stage: key rows, the map
+        if (kLds) place_rows(kKeys ? tb.n_tp : 0, 0, 4, kKeys ? 4 * tb.n_tp + 2 : 2, kKeys ? keys_bytes() : kValueBytes);
+        else whole = false;
+        // (not whole: the one row of values, or the two, behind the key rows)
+        int32_t *keys = reinterpret_cast<int32_t *>(ring);                 // [n_tp][pitch] (kKeys)
+        uint32_t *values = ring + (kKeys ? tb.n_tp * pitch : 0);
+        if (kLds && !whole) map = reinterpret_cast<uint16_t *>(values + (kKeys ? 1 : 2) * pitch);
+        int my_q = 0, my_shift = -1;                                       // (no degree: no stage)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if ((tid & 3) == q && q < tb.n_tp) { my_q = q; my_tp = tb.tp[q]; my_shift = tb.tp_shift[q]; }
+            if ((tid & 3) == q && q < tb.n_tp) { my_q = q; my_shift = shift_of(q); }
         int cur = 0;
         load_columns(0, request_column(0), 0, false);
         Column ahead = request_column(1);
         if (tid == 0) {                                    // row 0: no operators on no devices
-            rows[0] = 0;
-            sl.hist[0] = 0;
+            if (!kLds) sl.hist[0] = 0;
+            else if (whole) rows_all[0] = 0;
+            else values[0] = sl.hist[0] = 0;
             col_min[0] = 0;
             if (kKeys)
                 for (int q = 0; q < tb.n_tp; ++q) keys[q * pitch] = 0;
@@ -807,35 +869,43 @@ struct Band {
         for (int s = 0; s < S; ++s) {
             const int nxt = cur ^ 1;
             load_columns(s + 1, ahead, nxt, kLds);
-            __syncthreads();                               // row s, its columns and those of row s + 1 are in place
+            pass_barrier<kLds>();                          // row s, its columns and those of row s + 1 are in place
             if (s + 1 < S) ahead = request_column(s + 2);
             StageCtx c;
             c.s = s; c.cur = cur; c.nxt = nxt; c.t = t; c.none = none;
             c.last = s == S - 1;
-            c.total = tot[s + 1];
-            c.prev = kLds ? rows + cur * pitch : sl.hist + base[s];
-            c.next = kKeys ? rows : rows + nxt * pitch;
-            c.out = sl.hist + base[s + 1];
+            c.total = uniform(tot[s + 1]);
+            const int at = uniform(base[s]), at_next = uniform(base[s + 1]);
+            c.prev = kLds ? (whole ? rows_all + at : values + cur * pitch) : sl.hist + at;
+            c.next = whole ? rows_all + at_next : kKeys ? values : values + nxt * pitch;
+            c.out = whole ? nullptr : sl.hist + at_next;
             c.keys = keys;
             c.cut_tab = tb.CM;
             c.fits_tab = lo_tab + index_n(in_flight(s));
-            if (kLds && tb.n_tp > 1 && tb.n_tp <= 4 && 2 * c.total <= nthreads) row_cells<kPass, kLds, true>(c, my_q, my_tp, my_shift);
-            else row_cells<kPass, kLds, false>(c, my_q, my_tp, my_shift);
-            __syncthreads();                               // row s + 1 is complete
+            if (kLds && tb.n_tp > 1 && tb.n_tp <= 4 && 2 * c.total <= nthreads) row_cells<kPass, kLds, true>(c, my_q, my_shift);
+            else row_cells<kPass, kLds, false>(c, my_q, my_shift);
+            pass_barrier<kLds>();                          // row s + 1 is complete
             if (kKeys && !c.last) {
                 // the row as stage s + 1 reads it: a stage that starts at device d runs on the group of d
                 for (int x = tid; x < c.total; x += nthreads) {
                     const int d = map[x], i = x - int(col[nxt * sh.cols + d].y), k = group_at[d];
-                    const uint32_t v = rows[x], *p = time_row(k) + i;
+                    const uint32_t v = c.next[x], *p = time_row(k) + i;
                     for (int q = 0; q < tb.n_tp; ++q)
-                        keys[q * pitch + x] = v < kInfSum ? int32_t(v * uint32_t(tb.tp[q]) - p[q * sh.W]) : kNoKey;
+                        keys[q * pitch + x] = v < kInfSum ? int32_t((v << shift_of(q)) - p[q * sh.W]) : kNoKey;
                 }
-                __syncthreads();
+                lds_barrier();
             }
             cur = nxt;
         }
-        const uint32_t v = kKeys ? rows[0] : kLds ? rows[cur * pitch] : sl.hist[base[S]];
+        if (kLds && !whole) __syncthreads();               // (the slice's rows, for the plan)
+        const int end = uniform(base[S]);
+        const uint32_t v = !kLds ? sl.hist[end] : whole ? rows_all[end] : values[kKeys ? 0 : cur * pitch];
         return v >= none ? kInf : int64_t(v);
+    }
+    template <bool kLds>
+    __device__ __forceinline__ void pass_barrier() const {
+        if (kLds) lds_barrier();
+        else __syncthreads();
     }
     template <bool kCapped>
     __device__ __forceinline__ uint32_t value(uint32_t before, uint32_t time, uint32_t cut) const {
@@ -851,7 +921,7 @@ struct Band {
         if (wave == 0) {
             const int per = tb.n_tp <= 1 ? 64 : tb.n_tp <= 2 ? 32 : tb.n_tp <= 4 ? 16 : 8;   // lanes per degree
             const int q = lane / per, jj = lane - q * per;
-            const int tp = q < tb.n_tp ? tb.tp[q] : 0, shift = q < tb.n_tp ? tb.tp_shift[q] : 0;
+            const int tp = q < tb.n_tp ? tp_of(q) : 0, shift = q < tb.n_tp ? shift_of(q) : 0;
             int d2 = D, i = L;
             if (lane == 0) cuts[S] = L;
             for (int s = S - 1; s >= 0; --s) {
@@ -861,11 +931,11 @@ struct Band {
                 const bool in = q < tb.n_tp && d >= offs[k] && d >= s;
                 int jl = 1, jh = 0, off = 0;
                 if (in) {
-                    const size_t at = size_t(s) * sh.cols + d;
-                    const int lo = sl.B[at], hi = sl.F[at], fits = lo_tab[index_n(n) + index_at[k] + uint32_t(q * sh.idx_pitch + i)];
-                    off = sl.off[at];
-                    jl = fits > lo ? fits : lo;
-                    jh = (i - 1) < hi ? (i - 1) : hi;
+                    const int fits = lo_tab[index_n(n) + index_at[k] + uint32_t(q * sh.idx_pitch + i)];
+                    const Column w = column(uint32_t(s * sh.cols + d));
+                    off = w.off;
+                    jl = fits > w.lo ? fits : w.lo;
+                    jh = (i - 1) < w.hi ? (i - 1) : w.hi;
                 }
                 const uint32_t *p = time_row(k) + (in ? q : 0) * sh.W;
                 const uint32_t xi = p[i] + uint32_t(tp) - 1u;
@@ -874,26 +944,22 @@ struct Band {
                     if (in && j <= jh && key == 0xFFFFFFFFu) {
                         const uint32_t time = (xi - p[j]) >> shift;
                         if (time <= (capped ? cap : want)) {
-                            const uint32_t before = sl.hist[base[s] + off + j];
+                            const int at = base[s] + off + j;
+                            uint32_t before;
+                            if (whole) before = rows_all[at]; else before = sl.hist[at];
                             const bool hit = capped ? before < kInfSum && before + time == want : before <= want;
                             if (hit) { key = (uint32_t(j) << 3) | uint32_t(q); val = before; }
                         }
                     }
                 }
-                uint32_t low = key;
-#pragma unroll
-                for (int x = 32; x >= 1; x >>= 1) {
-                    const uint32_t o = __shfl_xor(low, x, 64);
-                    low = o < low ? o : low;
-                }
-                low = (uint32_t)uniform((int)low);
+                const uint32_t low = fastdp::wave_least(key);
                 const unsigned long long who = __ballot(key == low);
                 v = __builtin_amdgcn_readlane(val, __ffsll((long long)who) - 1);
                 // a reached cell always has one; the clamps keep the indices inside the rows whatever happens
                 const int jn = int((low >> 3) & 0xFFFFu), qn = int(low & 7u);
                 i = jn < i ? jn : i - 1;
                 i = i > 0 ? i : 0;
-                d2 -= tb.tp[qn < tb.n_tp ? qn : 0];
+                d2 -= tp_of(qn < tb.n_tp ? qn : 0);
                 d2 = d2 > 0 ? d2 : 0;
                 if (lane == 0) {
                     cuts[s] = i;
@@ -957,7 +1023,7 @@ struct Band {
             cut_masks(kTeams, uint32_t(at[0]), uint32_t(at[1]));
             for (int w = 0; w < kTeams; ++w) reach_table<true>(uint32_t(at[w]), w);
             bool fine[kTeams];
-            run_chains<false>(nullptr, nullptr, fine[0], fine[1]);
+            run_chains<false>(fine[0], fine[1]);
             for (int w = kTeams - 1; w >= 0; --w)
                 if (fine[w]) good = at[w];
             for (int w = 0; w < kTeams; ++w)
@@ -994,9 +1060,10 @@ struct Band {
         const uint32_t th1 = uint32_t(x1 < kTopCap ? x1 : kTopCap), th2 = uint32_t(x2 < kTopCap ? x2 : kTopCap);   // 2c - e > 0; > cap
         const uint32_t m_cap = uint32_t(tb.M);
         const int64_t *PP = mem, *PS = mem + sh.W;
-        if (kLds) place_rows(2, 2, kCountBytes);
-        uint16_t *back = reinterpret_cast<uint16_t *>(sl.hist);
-        auto row_h = [&](int b) -> uint32_t * { return kLds ? rows + b * pitch : sl.spare_h + b * sl.row; };
+        if (kLds) place_rows(2, 2, 2, kCountBytes, kCountBytes);
+        else whole = false;
+        uint16_t *back = reinterpret_cast<uint16_t *>(sl.hist), *back_lds = reinterpret_cast<uint16_t *>(rows_all);
+        auto row_h = [&](int b) -> uint32_t * { return kLds ? ring + b * pitch : sl.spare_h + b * sl.row; };
         auto row_n = [&](int b) -> uint16_t * { return kLds ? counts + b * pitch : sl.spare_n + b * sl.row; };
         int cur = 0;
         load_columns(S, request_column(S), 0, false);
@@ -1006,7 +1073,7 @@ struct Band {
             const uint32_t index_at_n = index_n(in_flight(s));
             const int nxt = cur ^ 1;
             load_columns(s, ahead, nxt, kLds);
-            __syncthreads();
+            pass_barrier<kLds>();
             if (s > 0) ahead = request_column(s - 1);
             const uint32_t *prev_h = row_h(cur);
             const uint16_t *prev_n = row_n(cur);
@@ -1018,10 +1085,11 @@ struct Band {
                 const int i = x - int(col[nxt * sh.cols + d].y);
                 const int k = group_at[d], end = offs[k + 1];
                 const int64_t mem_dev = tb.type_mem[type[k]];
-                const uint32_t cut = s > 0 ? tb.CM[cut_at[d] + uint32_t(i)] : 0u;
+                uint32_t cut = tb.CM[cut_at[d] + uint32_t(i)];             // (read in front of the first stage too: no branch to wait in)
                 const uint16_t *fits = hi_tab + (index_at_n + index_at[k] + uint32_t(i)), *far = reach_row(0, k) + i;
                 const uint32_t *p_k = time_row(k);
                 const int64_t ppi = PP[i], psi = PS[i];
+                cut = s > 0 ? cut : 0u;
                 uint32_t best = kInfSum, best_n = kCount ? kNoCount : 0u;
                 int best_j = 0, best_q = 0;
                 for (int q0 = 0; q0 < tb.n_tp; q0 += 4) {
@@ -1031,7 +1099,7 @@ struct Band {
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         if (q0 + u >= tb.n_tp) continue;
-                        const int q = q0 + u, tp = tb.tp[q], d1 = d + tp;
+                        const int q = q0 + u, shift = shift_of(q), tp = 1 << shift, d1 = d + tp;
                         if (d1 > end) continue;
                         const uint2 w = col[cur * sh.cols + d1];
                         const int lo = col_lo(w), hi = col_hi(w);
@@ -1042,7 +1110,6 @@ struct Band {
                         const uint32_t *p = p_k + q * sh.W;
                         const int off = int(w.y);
                         const uint32_t xi = p[i] - uint32_t(tp) + 1u;
-                        const int shift = tb.tp_shift[q];
                         const int64_t capm = int64_t(tp) * mem_dev;
                         for (int j = jl; j <= jh; ++j) {
                             if (kCount) {
@@ -1060,7 +1127,10 @@ struct Band {
                         }
                     }
                 }
-                if (!kCount) back[at + x] = uint16_t(uint32_t(best_j) | (uint32_t(best_q) << 13));
+                if (!kCount) {
+                    const uint16_t to = uint16_t(uint32_t(best_j) | (uint32_t(best_q) << 13));
+                    if (whole) back_lds[at + x] = to; else back[at + x] = to;
+                }
                 if (s > 0) {
                     const uint32_t cnt = 1u + (cut > th1 ? 1u : 0u) + (cut > th2 ? 1u : 0u) + best_n;
                     const uint32_t cnt_m = cnt < m_cap ? cnt : m_cap;
@@ -1075,9 +1145,10 @@ struct Band {
                     scal[4] = kCount ? (best_n != kNoCount ? 0u : kInfSum) : best;
                 }
             }
-            __syncthreads();
+            pass_barrier<kLds>();
             cur = nxt;
         }
+        if (kLds && !kCount && !whole) __syncthreads();    // (the slice's back-pointers, for the plan)
         const uint32_t v = scal[4];
         return v >= kInfSum ? kInf : int64_t(v);
     }
@@ -1120,14 +1191,15 @@ struct Band {
     __device__ __forceinline__ void find_h1_plan() {
         const int lane = thread_id() & 63;
         if (wave == 0) {
-            const uint16_t *back = reinterpret_cast<const uint16_t *>(sl.hist);
+            const uint16_t *back = reinterpret_cast<const uint16_t *>(sl.hist), *back_lds = reinterpret_cast<const uint16_t *>(rows_all);
             int d = 0, i = 0;
             for (int s = 0; s < S; ++s) {
                 const int k = group_at[d];
-                const size_t at = size_t(s) * sh.cols + d;
-                const int lo = sl.B[at], hi = sl.F[at];
-                const int ic = i < lo ? lo : (i > hi ? hi : i);       // a finite sum only chains through cells
-                const uint32_t a = back[base[s] + sl.off[at] + ic];
+                const Column w = column(uint32_t(s * sh.cols + d));
+                const int ic = i < w.lo ? w.lo : (i > w.hi ? w.hi : i);       // a finite sum only chains through cells
+                const int at = base[s] + w.off + ic;
+                uint32_t a;
+                if (whole) a = back_lds[at]; else a = back[at];
                 const int q = int(a >> 13) & 7;
                 if (lane == 0) {
                     cuts[s] = i;
