@@ -115,6 +115,7 @@ __host__ __device__ inline size_t exact_small_bytes(int S_max) {
 // infinite sum, never gives a quotient as low as U.  The others keep the sums.
 // 65,536 candidates of 160 operators, 16 to 32 stages, the whole call: 3.83 -> 3.68 ms with 5 wavefronts per SIMD, which
 // vector issue then no longer fills (69% of the rate; the wait for a trip's entries shows), 3.47 with 6, 3.50 with 7.
+constexpr size_t kLdsUnit = 1280;        // LDS is allocated in units of this many bytes
 constexpr int kExactWaves = 6;           // wavefronts per SIMD of k2_exact: registers held to 80, 4 of them spilled to scratch
 constexpr int64_t kKeyLimit = int64_t(1) << 30;
 constexpr int32_t kNoKey = INT32_MAX;
@@ -670,11 +671,15 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
     // of up to 8 stages 8.5 and 6.3 with 22.  With fewer than 18 the latency of a stage shows, and the second launch's 256
     // threads are the better place for long rows: 512 operators, 16 stages, 4,096 candidates 16 ms with 24 per CU (4,081
     // left), 22 with 16; 64 of up to 128 stages 5.7 and 12.
-    int per_cu = int((size_t(160) << 10) / (small + size_t(full_row) * 16 + 128));
+    // Shares are whole units of LDS allocation, or fewer wavefronts are resident than meant (21 of 24 with an even split).
+    // What rows over the whole sequence leave of a share holds back-pointers (512 operators, the whole batch 8.46 -> 8.24 ms;
+    // 160 operators, 65,536 candidates 3.36 -> 3.33, 64 of them 0.655 -> 0.637).
+    const size_t units = (size_t(160) << 10) / kLdsUnit;
+    int per_cu = int(units / ((small + size_t(full_row) * 16 + kLdsUnit - 1) / kLdsUnit));
     if (per_cu < 18 || per_cu > 4 * kExactWaves) per_cu = 4 * kExactWaves;
-    size_t share = ((size_t(160) << 10) / per_cu - 128) & ~size_t(15);
-    int entries = share > small + 2 * 8 * (kPad + 8) ? int((share - small) / 16) : kPad + 8;
-    if (entries > full_row) entries = full_row;
+    const size_t share = units / per_cu * kLdsUnit;
+    const int held = share > small + 2 * 8 * (kPad + 8) ? int((share - small) / 16) : kPad + 8;
+    const int entries = held < full_row ? held : full_row;
     int n_waves = per_cu * n_cu;
     if (n_waves > n_slices) n_waves = n_slices;
     if (n_waves > cd.C) n_waves = cd.C;
@@ -693,9 +698,9 @@ void launch_plan_exact(const TablesDev &tb, const CandDev &cd, const PlansDev &o
     const size_t u8_off = fast_arg_u16_bytes(tb.L, cd.S_max);
     auto launch = [&](auto odd_t) {
         constexpr bool odd = decltype(odd_t)::value;
-        hipLaunchKernelGGL(k2_exact<odd>, dim3(n_waves), dim3(64), small + size_t(entries) * 16, st, tb, cd, out, n_passes,
+        hipLaunchKernelGGL(k2_exact<odd>, dim3(n_waves), dim3(64), small + size_t(held) * 16, st, tb, cd, out, n_passes,
                            w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.tight, w.lo_tab, lo_p, w.arg, per_group, u8_off,
-                           full_row, entries, eighths);
+                           full_row, held, eighths);
         if (entries < full_row || eighths > 0)
             hipLaunchKernelGGL(k2_exact_rows<odd>, dim3(n_groups), dim3(kFastThreads), small + size_t(full_row) * 16, st,
                                tb, cd, out, n_passes, w.counts, w.tickets, w.live_list, w.dead_list, w.bands, w.tight, w.lo_tab, lo_p,
