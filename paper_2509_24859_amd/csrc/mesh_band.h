@@ -434,7 +434,9 @@ struct Band {
         ChainLane l;
         l.d = c * 64 + (thread_id() & 63) + (kBack ? 0 : 1);       // forwards columns 1 .. D, backwards 0 .. D - 1
         const int stage_on = kBack ? (l.d < D ? l.d : D - 1) : (l.d <= D ? l.d : D) - 1, k = group_at[stage_on];
-        l.edge = offs[kBack ? k + 1 : k];
+        // (a lane behind column D has no column to come from: its offsets would lie behind the row, and what it read there
+        // would be taken for a cut of the index in memory)
+        l.edge = kBack ? offs[k + 1] : l.d <= D ? offs[k] : INT32_MAX;
         l.index = index_at[k];
         l.far = prow_at[k];
         const int cut_on = kBack ? stage_on : stage_on + 1;
