@@ -541,14 +541,13 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 //  * How many values the sweep passes from t_S to t_E, or to the first cap with a plan where that is higher
 //    (n_caps, max_caps), is counted without trying them.
 // Measured on 48 orderings of 82 operators and 64 devices (about 1,000 values each between t_S and t_E, all
-// of them tried before, by up to 32 workgroups per ordering): 125-150 -> 0.8-1.0 ms per call, some 10 passes
+// of them tried before, by up to 32 workgroups per ordering): 125-150 -> 0.6-0.8 ms per call, some 10 passes
 // per ordering, bound by the latency of one workgroup's passes one after the other (vector issue 6% of the rate of
 // the 48 CUs at work).
 //  * The bounds are weak where tight memory keeps the H-1F1B sums above the classic ones and there are few
-//    micro-batches.  An ordering that has tried kMaxTries values without an end leaves the rest, a range of caps, to
+//    micro-batches.  An ordering that has run a few passes without an end leaves the rest, a range of caps, to
 //    the second launch (kWalk): W workgroups take a part of the range each, start from the best plan so far and
-//    tell each other the least total they find.  Measured on orderings of 60 operators and 24 devices, 8
-//    micro-batches, tightest memory: 4 of them 92.3 -> 6.0 ms, 64 of them 92.1 -> 8.5 ms.
+//    tell each other the least total they find.  How many passes: see the launch.
 // The plan returned is the one the sweep over every value returns (least T, lower cap on equal T).  An
 // ordering that does not fit LDS or whose sums could pass 2^31 is handed over to the kernels that try every
 // value; so is one whose climb fails at kMaxClimb values in a row (the recurrence keeps one continuation per
@@ -556,8 +555,8 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 // Candidates (k2_sweep_slots) are searched in the same way, on the passes of slot_passes.h.  Those also say up to
 // which cap they come out the same, so that the climb and the tries pass over the values below it: climbs
 // that took up to 20,000 passes take 1 to 3.  64 candidates of 82 operators, 8 to 16 stages on 8 groups of 8
-// devices (about 2,000 values each from t_S on, 29,000 at most): 146 ms, every value tried, -> 0.8-1.5 ms, some 30
-// passes for the longest searches, the least-count bisection two thirds of them.
+// devices (about 2,000 values each from t_S on, 29,000 at most): 146 ms, every value tried, -> 0.8-1.5 ms, of late 1.2
+// where that was 1.4 (the least-count passes on a wavefront each, the rest left to the second launch sooner).
 
 // The rest of an ordering's search: its slots as for the kernels above (the opening's head holds the best plan so
 // far and, in rest, the range of caps left: above the first, up to the second), the least total found per ordering
@@ -565,6 +564,7 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 struct SweepShare {
     unsigned char *slots;
     int Ws, W;
+    int tries;               // values the first launch tries before it leaves the rest of an ordering to the second
     long long *least;
 };
 // counters of the band launch: orderings left to the walkers, and their ticket; their list grows from the end of redo
@@ -658,7 +658,7 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
                 least_T = least_found;
             }
             const int form = state == kBottleneck ? E::kMinMax : state == kUpper ? E::kSum
-                             : state == kAtTop || state == kGallop || state == kBisect ? E::kAny : E::kH1;
+                             : !E::kSpreads && (state == kAtTop || state == kGallop || state == kBisect) ? E::kAny : E::kH1;
             if (form == E::kSum || form == E::kH1) {
                 if (cap > key_cap && !looked) {
                     const uint64_t most = b.most_sum();
@@ -691,10 +691,17 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
                     tried = 1;
                     run_out = top > t_S && more > 0;
                     lo = b.same_up_to(t_S);
-                    if (!run_out) state = kNoPlan;
-                    else { cap = top; state = kAtTop; }
+                    if (!run_out) {
+                        state = kNoPlan;
+                    } else if constexpr (E::kSpreads) {
+                        climb_on = b.least_cap(top, lo, hi);
+                        if (!climb_on) state = kNoPlan;
+                    } else {
+                        cap = top;
+                        state = kAtTop;
+                    }
                 }
-            } else if (!kWalk && state == kAtTop) {
+            } else if (!kWalk && !E::kSpreads && state == kAtTop) {
                 hi = top;
                 step = (t_S >> 4) + 1u;
                 // (lo may lie above hi: the pass at t_S may hold for every value there is, and the recurrence can miss
@@ -703,7 +710,7 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
                 else if (lo + step < hi) { cap = lo + uint32_t(step); state = kGallop; }
                 else if (lo + (1ull + (hi >> 12)) < hi) { cap = lo + (hi - lo) / 2u; state = kBisect; }
                 else climb_on = true;
-            } else if (!kWalk && (state == kGallop || state == kBisect)) {
+            } else if (!kWalk && !E::kSpreads && (state == kGallop || state == kBisect)) {
                 if (found) hi = cap; else lo = b.same_up_to(cap);
                 step *= 4;
                 if (state == kGallop && !found && lo + step < hi) cap = lo + uint32_t(step);
@@ -713,6 +720,7 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
                 if (found) opened = true;
                 else { lo = b.same_up_to(cap); climb_on = true; }
             } else if (state == kUpper) {
+                ++tested;
                 // no cap up to hi beats the best total unless the classic sum at hi leaves room for it
                 const int64_t room = (least_T < best_T ? least_T : best_T) - v;
                 if (room < 0) { state = kDone; break; }            // (without a plan included: cannot happen)
@@ -730,6 +738,7 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
                     try_on = true;
                 }
             } else {                                              // kTry
+                ++tested;
                 if (found) {
                     const int64_t T = v + m_less * cap;
                     if (T < best_T || (T == best_T && cap < best_cap)) {
@@ -739,7 +748,6 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
                         if (kWalk && tid == 0) atomicMin(&sw.least[c], (long long)T);
                     }
                 }
-                ++tested;
                 if (found && v == classic) { hi = bn > 0 ? uint32_t(bn) - 1u : 0u; upper_on = true; }
                 else { cap = b.same_up_to(cap); try_on = true; }
             }
@@ -777,7 +785,7 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
                 cap = hi;
                 state = hi > first ? kUpper : kDone;
             }
-            if (!kWalk && sw.W > 1 && tested >= E::kMaxTries && (state == kTry || state == kUpper)) { left = true; state = kDone; }
+            if (!kWalk && sw.W > 1 && tested >= sw.tries && (state == kTry || state == kUpper)) { left = true; state = kDone; }
         }
         if (kWalk) {
             if (tid == 0) {
@@ -884,7 +892,13 @@ hipError_t launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, c
     ba.per_group = per_group;
     ba.counters = w.counters;
     ba.redo = w.redo;
-    const SweepShare sw{slots, Ws, W, reinterpret_cast<long long *>(lower)};
+    // Least-sum passes and values tried after which the first launch leaves the rest to the second, 24 values before.  Orderings
+    // (a pass of 40 us and more), us with 24 values / 3 / 5 / 8: 48 of 82 operators 907 / 766 / 807 / 920; 16 of 60 operators,
+    // 8 micro-batches 2,830 / 810 / 896 / 1,116; 300 of 60 operators 1,504 / 908 / 861 / 984.  Candidates (a pass of 20 us),
+    // 2 values / 3 / 5 / 8: 16 of 300 operators 1,330 / 742 / 825 / 1,017; 16 of 12 operators 126 / 149 / 127 / 127; where the batch
+    // fills the chip the second launch repeats work for nothing: 300 of 82 operators 1,363 (8 values) / 1,611 / 1,538 / 1,459.
+    const int tries = !forced ? 4 : od.C <= n_cu ? 5 : 20;
+    const SweepShare sw{slots, Ws, W, tries, reinterpret_cast<long long *>(lower)};
     const long long walkers = (long long)od.C * W;
     const dim3 band_grid(unsigned(od.C < n_groups ? od.C : n_groups)), walk_grid(unsigned(walkers < n_groups ? walkers : n_groups));
     int band_threads = 0;

@@ -126,8 +126,8 @@ inline size_t band_slice_bytes(int L, int S_max, int64_t total_devices) {
 }
 
 struct Band {
-    static constexpr bool kChoosesSlicing = true, kGuesses = true;
-    static constexpr int kMaxClimb = 8, kMaxTries = 24;      // see k2_sweep.hip
+    static constexpr bool kChoosesSlicing = true, kGuesses = true, kSpreads = false;
+    static constexpr int kMaxClimb = 8;       // see k2_sweep.hip
     const TablesDev &tb;
     const BandShape &sh;
     const uint16_t *lo_tab, *hi_tab;
@@ -381,7 +381,7 @@ struct Band {
     // highest cut i with time(j, i) <= t; downwards: entry i = the lowest cut j with time(j, i) <= t.  Neither falls from
     // one entry to the next, so a thread finds the first of a run of kReachRun entries by bisection and goes on from there:
     // a cut or so per entry, where a bisection each takes seven or eight steps (4,096 orderings of 82 operators and 64
-    // devices: of an ordering's 145 us the tables took 31, now @@).
+    // devices: of an ordering's 145 us the tables took 31, now 19).
     template <bool kUp>
     __device__ __forceinline__ void reach_table(uint32_t t, int side) {
         uint16_t *to = reach + side * n_sets * tb.n_tp * sh.W;

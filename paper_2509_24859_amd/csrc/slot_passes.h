@@ -65,10 +65,10 @@ inline SlotShape slot_shape(int L, int S_max) {
 
 template <bool kResident>
 struct Slots {
-    static constexpr bool kChoosesSlicing = false, kGuesses = false;
+    static constexpr bool kChoosesSlicing = false, kGuesses = false, kSpreads = true;
     // see k2_sweep.hip; a climb passes over the values that change nothing and takes 1 to 3 passes, so kMaxClimb is a
     // bound for constructed inputs, where each of many operators of a few microseconds changes something
-    static constexpr int kMaxClimb = 256, kMaxTries = 24;
+    static constexpr int kMaxClimb = 256;
     struct alignas(16) Stage { uint32_t row_at, cut_at; int32_t tp, shift; };
     const TablesDev &tb;
     const SlotShape &sh;
@@ -331,13 +331,12 @@ struct Slots {
 
     // The recurrence in the ranges of the last prepare under the cap t, in one of the forms below.  A cell's
     // best is one key, value << 32 | end cut << 16 | count of the stage: the least value, the lowest end cut
-    // among equal ones.  kAny: the least count a first stage can have (a smaller count weakens every memory
-    // test in front of it, so this decides whether any plan exists under the cap).
-    static constexpr int kMinMax = 1, kSum = 2, kH1 = 4, kAny = 8;
+    // among equal ones.
+    static constexpr int kMinMax = 1, kSum = 2, kH1 = 4, kAny = 0;       // (whether any plan exists: least_cap)
     template <int kForm>
     __device__ __forceinline__ int64_t pass(uint32_t t) {
         constexpr unsigned long long kNone = ~0ull;
-        constexpr bool kCounts = kForm == kH1 || kForm == kAny;
+        constexpr bool kCounts = kForm == kH1;
         const int tid = threadIdx.x, part = tid & (kPart - 1);
         const uint64_t e6 = uint64_t(count_cap) >> 6, x1 = e6 >> 1, x2 = (uint64_t(count_cap) + e6) >> 1;
         const uint32_t th1 = uint32_t(x1 < kTopCap ? x1 : kTopCap), th2 = uint32_t(x2 < kTopCap ? x2 : kTopCap);   // 2c - e > 0; > cap
@@ -374,14 +373,13 @@ struct Slots {
                         if (kCounts && (PP[j] - ppi) + int64_t(classic) * (PS[j] - psi) <= room) ev = time < ev ? time : ev;
                         break;
                     }
-                    const uint32_t before = kForm == kAny ? 0u : prev_h[j];
+                    const uint32_t before = prev_h[j];
                     const uint32_t cnt = kCounts ? uint32_t(prev_n[j]) : classic;
                     const int64_t need = (PP[j] - ppi) + int64_t(cnt) * (PS[j] - psi);
                     uint32_t v;
-                    if (kForm == kAny) v = cnt;
-                    else if (kForm == kMinMax) v = before > time ? before : time;
+                    if (kForm == kMinMax) v = before > time ? before : time;
                     else v = before + time;
-                    const bool out = kForm == kAny ? cnt == 0xFFFFu : before >= kInfSum;
+                    const bool out = before >= kInfSum;
                     const unsigned long long key = ((unsigned long long)v << 32) | (uint32_t(j) << 16) | (kCounts ? cnt : 0u);
                     if (!out && need <= room && key < best) best = key;
                 }
@@ -391,17 +389,14 @@ struct Slots {
                 if (part != 0) continue;
                 const bool has = best != kNone;
                 const uint32_t v = uint32_t(best >> 32), cnt0 = uint32_t(best) & 0xFFFFu;
-                if (kForm != kMinMax && kForm != kAny) back[i] = uint16_t(uint32_t(best) >> 16);
+                if (kForm != kMinMax) back[i] = uint16_t(uint32_t(best) >> 16);
                 if (s > 0) {
                     const bool in = has && cut <= t;   // constraint (ii)
-                    if (kForm != kAny) {
-                        const uint32_t w = kForm == kMinMax ? (v > cut ? v : cut) : v + 2u * cut;
-                        next_h[i] = in && w < kInfSum ? w : kInfSum;
-                    }
+                    const uint32_t w = kForm == kMinMax ? (v > cut ? v : cut) : v + 2u * cut;
+                    next_h[i] = in && w < kInfSum ? w : kInfSum;
                     if (kCounts) {
                         const uint32_t cnt = 1u + (cut > th1 ? 1u : 0u) + (cut > th2 ? 1u : 0u) + cnt0;   // eq. dp_ni
-                        const uint32_t capped = cnt < m_cap ? cnt : m_cap;
-                        next_n[i] = uint16_t(kForm == kAny && !in ? 0xFFFFu : capped);
+                        next_n[i] = uint16_t(cnt < m_cap ? cnt : m_cap);
                     }
                     if (kCounts && has) {
                         // the cap that admits the cut, or at which its delta falls: 2c - e <= 0 from 128 c on,
@@ -414,7 +409,7 @@ struct Slots {
                         ev = at < ev ? uint32_t(at) : ev;
                     }
                 } else {
-                    scal[4] = has ? (kForm == kAny ? 0u : v) : kInfSum;
+                    scal[4] = has ? v : kInfSum;
                 }
             }
             cur ^= 1;
@@ -424,14 +419,124 @@ struct Slots {
         const uint32_t v = scal[4];
         return v >= kInfSum ? kInf : int64_t(v);
     }
+    // The least-count pass under the cap t on one wavefront, ranges included, in `mine` (team_words words of LDS): whether any
+    // plan exists under t (a smaller count weakens every memory test in front of it).  ev: as for the passes of the workgroup.
+    __device__ __forceinline__ uint32_t team_words() const { return (uint32_t(2 * sh.W) + uint32_t(2 * (sh.S_cap + 1)) + 3u) / 2u + 1u; }
+    __device__ __forceinline__ bool any_plan(uint32_t t, uint32_t *mine, uint32_t &ev) const {
+        const int lane = threadIdx.x & 63, part = lane & (kPart - 1);
+        uint16_t *rows = reinterpret_cast<uint16_t *>(mine + 1), *Fs = rows + 2 * sh.W, *Bs = Fs + (sh.S_cap + 1);
+        ev = 0xFFFFFFFFu;
+        if (!forward_chain(t, Fs, ev) || !backward_chain(t, Bs, ev)) return false;
+        wave_sync();
+        const uint64_t e6 = uint64_t(t) >> 6, x1 = e6 >> 1, x2 = (uint64_t(t) + e6) >> 1;
+        const uint32_t th1 = uint32_t(x1 < kTopCap ? x1 : kTopCap), th2 = uint32_t(x2 < kTopCap ? x2 : kTopCap);
+        const uint32_t m_cap = uint32_t(tb.M);
+        const int64_t *PP = mem, *PS = mem + sh.W;
+        bool found = false;
+        int cur = 0;
+        if (lane == 0) rows[L] = 1;
+        for (int s = S - 1; s >= 0; --s) {
+            wave_sync();
+            const int jl = uniform(Bs[s + 1]), jh = uniform(Fs[s + 1]), il = uniform(Bs[s]), ih = uniform(Fs[s]);
+            if (jl > jh || il > ih) return false;
+            const uint16_t *prev = rows + cur * sh.W;
+            uint16_t *next = rows + (cur ^ 1) * sh.W;
+            const uint32_t *p = time_row(s), *cut_s = cut_row(s > 0 ? s - 1 : 0);
+            const uint32_t tp = uint32_t(stage[s].tp), classic = uint32_t(in_flight(s));
+            const int shift = stage[s].shift;
+            const int64_t room = capm[s];
+            for (int i0 = il; i0 <= ih; i0 += 64 / kPart) {
+                const int i = i0 + lane / kPart;
+                if (i > ih) continue;                  // (all lanes of a cell together)
+                const uint32_t cut = s > 0 ? cut_s[i] : 0u;
+                const uint32_t xi = p[i] - tp + 1u;
+                const int64_t ppi = PP[i], psi = PS[i];
+                uint32_t best = 0xFFFFu;
+                for (int j = (i + 1 > jl ? i + 1 : jl) + part; j <= jh; j += kPart) {
+                    const uint32_t time = (p[j] - xi) >> shift;
+                    const int64_t held = PP[j] - ppi, stash = PS[j] - psi;
+                    if (time > t) {
+                        if (held + int64_t(classic) * stash <= room) ev = time < ev ? time : ev;
+                        break;
+                    }
+                    const uint32_t cnt = prev[j];      // (0xFFFF: no plan from there)
+                    if (cnt < best && held + int64_t(cnt) * stash <= room) best = cnt;
+                }
+                best = least32<0xB1>(best);            // lanes 1, 2 and 4 apart
+                best = least32<0x4E>(best);
+                best = least32<0x141>(best);
+                if (part != 0) continue;
+                const bool has = best != 0xFFFFu;
+                if (s == 0) { found = has; continue; }
+                const uint32_t cnt = 1u + (cut > th1 ? 1u : 0u) + (cut > th2 ? 1u : 0u) + best, capped = cnt < m_cap ? cnt : m_cap;
+                next[i] = uint16_t(has && cut <= t ? capped : 0xFFFFu);
+                if (has) {
+                    uint64_t at = ~0ull;
+                    if (cut > t) at = cut;
+                    else if (cut > th2) at = 128ull * cut / 65u;
+                    else if (cut > th1) at = 128ull * cut;
+                    at = at > t ? at : t + 1u;
+                    ev = at < ev ? uint32_t(at) : ev;
+                }
+            }
+            cur ^= 1;
+        }
+        return __any(found);
+    }
+    template <int kCtrl>
+    static __device__ __forceinline__ uint32_t least32(uint32_t v) {
+        const uint32_t o = uint32_t(__builtin_amdgcn_update_dpp(int(v), int(v), kCtrl, 0xF, 0xF, false));
+        return o < v ? o : v;
+    }
+    // All threads: whether any cap up to `top` has a plan; if so the lowest that can have one lies above lo and not above hi,
+    // which come within 1/4,096 of each other.  lo: no plan up to there.  Every wavefront tries a cap of its own, at
+    // distances that grow by four first, evenly spread then: a pass is as long as its stages are one after the other, whoever
+    // works it.  One cap after the other on the whole workgroup took up to twenty passes: 64 candidates of 40 operators
+    // 884 -> 793 us, 64 of 82 with tight memory 588 -> 471, 16 of 12 operators 188 -> 127.
+    __device__ __forceinline__ bool least_cap(uint32_t top, uint32_t &lo, uint32_t &hi) {
+        // (six at least: sequences of up to 1,024 operators and 256 stages come here)
+        const int fit = int(kBitWords / team_words()), lane = threadIdx.x & 63, n = fit < kTeams ? fit : kTeams;
+        uint32_t *mine = bits + uint32_t(wave < n ? wave : 0) * team_words();
+        const uint64_t step = (lo >> 4) + 1u;
+        hi = 0;                                        // (none known)
+        for (bool first = true; first || (lo < hi && hi - lo > 1u + (hi >> 12)); first = false) {
+            auto cap_of = [&](int w) -> uint32_t {
+                if (first) {
+                    const uint64_t t = lo + (step << (2 * w));
+                    return w == n - 1 || t > top ? top : uint32_t(t);
+                }
+                return lo + uint32_t(uint64_t(hi - lo) * uint32_t(w + 1) / uint32_t(n + 1));
+            };
+            __syncthreads();
+            if (wave < n) {
+                uint32_t ev;
+                const bool found = any_plan(cap_of(wave), mine, ev);
+                ev = fastdp::wave_least(ev);
+                if (lane == 0) { scal[wave] = found ? 1u : 0u; mine[0] = ev; }
+            }
+            __syncthreads();
+            // the verdict never changes back as the cap grows
+            int w = 0;
+            while (w < n && scal[w] == 0) ++w;
+            if (first && w == n) return false;
+            uint32_t low = lo;
+            if (w > 0) {
+                const uint32_t t = cap_of(w - 1), e = bits[uint32_t(w - 1) * team_words()];
+                low = e > t ? e - 1u : t;
+            }
+            if (w < n) hi = cap_of(w);
+            lo = low > lo ? low : lo;
+        }
+        return true;
+    }
+
     // One pass under the cap t; kInf without a plan.  kForms: the forms a kernel uses, as a mask.
     template <int kForms>
     __device__ __forceinline__ int64_t run(int form, uint32_t t) {
         if (!prepare(t)) return kInf;
         if ((kForms & kMinMax) && form == kMinMax) return pass<kMinMax>(t);
         if ((kForms & kSum) && form == kSum) return pass<kSum>(t);
-        if ((kForms & kH1) && form == kH1) return pass<kH1>(t);
-        if (kForms & kAny) return pass<kAny>(t);
+        if (kForms & kH1) return pass<kH1>(t);
         return kInf;
     }
 

@@ -411,6 +411,20 @@ def test_sweep_of_candidates_at_its_edges(harp, ctx, case):
     assert planned > 0
 
 
+SWEEP_CLIMBS = [  # as above: tight memory and slow links, the bottleneck has no plan
+    (9, (4, 4), (3, 2), (1, 2), 16, 1.2, 1, 30, 1 << 20),
+    (83, (16, 16), (9, 7), (1, 2), 40, 1.25, 1, 60, 1 << 20),
+    (700, (16, 16), (6, 5), (1, 2, 4), 30, 1.2, 1, 30, 40),             # rows beyond LDS
+    (1024, (8, 8), (3, 3), (1, 2, 4), 24, 1.2, 1, 30, 40),              # fewer wavefronts with a cap of their own
+]
+
+
+@pytest.mark.parametrize("case", SWEEP_CLIMBS, ids=lambda c: "L%d_S%d_M%d" % (c[0], sum(c[2]), c[4]))
+def test_sweep_of_candidates_finds_the_first_cap_with_a_plan(harp, ctx, case):
+    """A cap per wavefront, over the lengths of the sequence: the search starts at the first value that has a plan."""
+    test_sweep_of_candidates_at_its_edges(harp, ctx, case)
+
+
 @pytest.mark.parametrize("n", [5, 330], ids=["few", "many"])
 def test_sweep_without_a_plan_under_any_cap(harp, ctx, n):
     """The recurrence keeps one continuation per cell.  Here it keeps the cheaper last cut, whose transfer raises the

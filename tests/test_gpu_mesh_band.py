@@ -78,6 +78,36 @@ def test_band_kernels_at_their_edges(harp, ctx, case):
     assert (hg.warmup == hw.warmup).all() and (hg.stage_tp == hw.stage_tp).all()
 
 
+ROW_FORMS = [  # L, devices per group, degrees, stages, slow link
+    (40, (8, 9), (1, 2), 11, False),                      # every row in LDS for good, two lanes of four with a degree
+    (96, (24, 24), (1, 2, 4, 8), 9, False),
+    (160, (64, 64), (1, 2, 4, 8), 20, True),              # rows that fit as values and not as key rows
+    (160, (64, 64), (1, 2, 4, 8, 16), 18, True),          # five degrees: a lane takes all of a cell's
+    (250, (64, 64), (1, 2, 4), 36, True),                 # rows of the workspace
+]
+
+
+@pytest.mark.parametrize("case", ROW_FORMS, ids=lambda c: "L%d_D%d_q%d" % (c[0], sum(c[1]), len(c[2])))
+@pytest.mark.parametrize("copies", [1, 300], ids=["few", "many"])
+def test_band_rows_in_every_form(harp, ctx, case, copies):
+    """Rows of a pass all in LDS, the last two there as values or as key rows, or none of them; a whole compute unit's
+    LDS for an ordering and half of it."""
+    L, ndev, tp, S, slow = case
+    p = _problem(L + S, L, ndev, tp, slow)
+    orders = W.orderings_from_lists([(s, order) for s in (S, S - 2) for order in ([0, 1], [1, 0])] * copies, S_max=S)
+    want = oracle_plan_mesh_threaded(oracle.build_tables(p), W.orderings_from_lists(
+        [(s, order) for s in (S, S - 2) for order in ([0, 1], [1, 0])], S_max=S))
+    assert (want.status == oracle.OK).any()
+    got, _ = harp.plan_mesh(ctx, p, orders, False, harp.PATH_FAST32)
+    for field in ("splits", "dev_first", "bottleneck", "iter_time", "status", "stage_group", "stage_tp"):
+        assert (getattr(got, field).reshape(copies, 4, -1) == getattr(want, field).reshape(1, 4, -1)).all(), field
+    exact, _ = harp.plan_mesh(ctx, p, orders, True, harp.PATH_FAST32)
+    wide, _ = harp.plan_mesh(ctx, p, W.orderings_from_lists(
+        [(s, order) for s in (S, S - 2) for order in ([0, 1], [1, 0])], S_max=S), True, harp.PATH_GENERIC)
+    for field in ("splits", "dev_first", "bottleneck", "iter_time", "status", "stage_group", "stage_tp", "n_passes"):
+        assert (getattr(exact, field).reshape(copies, 4, -1) == getattr(wide, field).reshape(1, 4, -1)).all(), field
+
+
 @pytest.mark.parametrize("seed,L,ndev,tp,M", [(1, 33, (3, 4), (1, 2, 4), 9), (2, 64, (4, 4, 2), (1, 2), 5),
                                               (3, 70, (2, 2, 2), (1, 2), 40), (4, 20, (8,), (1, 2, 4, 8), 12)],
                          ids=lambda x: str(x).replace(" ", ""))
