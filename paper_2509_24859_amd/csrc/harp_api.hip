@@ -35,6 +35,7 @@ struct harp_tables {
     bool fast32;          // 32-bit rows, degrees powers of two
     bool odd32;           // 32-bit rows, other degrees among them
     long long total_devices;
+    long long worst_time; // the largest stage or transfer time of any plan
     size_t bytes;
 };
 
@@ -120,6 +121,7 @@ int finalize_tables(harp_ctx *ctx, harp_tables *t) {
     t->fast32 = ctx->pinned->fast32 == 1;
     t->odd32 = ctx->pinned->fast32 == 2;
     t->total_devices = ctx->pinned->total_devices;
+    t->worst_time = ctx->pinned->worst_time;
     if (ctx->pinned->bad_arg)
         t->verdict = fail(ctx, HARP_ERR_INVALID_ARG,
                           "problem arrays hold a negative value, a bandwidth below 1, a group type out of range or an empty group");
@@ -490,7 +492,7 @@ int plan_prepare(harp_ctx *ctx, harp_tables *t, const harp_candidates *cd, const
 }
 
 int plan_minmax(harp_ctx *ctx, harp_tables *t, const PlanCall &pc, void *ws, unsigned long long *work) {
-    if (pc.fast) launch_plan_fast(t->dev, pc.c, pc.o, ws, pc.slices, ctx->n_cu, pc.narrow, work, pc.st);
+    if (pc.fast) launch_plan_fast(t->dev, pc.c, pc.o, ws, pc.slices, ctx->n_cu, pc.narrow, t->worst_time, work, pc.st);
     else launch_plan_generic(t->dev, pc.c, pc.o, ws, pc.groups, pc.banded, pc.st);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(ctx, e, "launching the planner kernel");

@@ -105,7 +105,7 @@ void launch_plan_generic_exact(const TablesDev &tb, const CandDev &cd, const Pla
                                void *ws, int n_groups, bool banded, hipStream_t st);
 size_t plan_generic_ws_per_group(int L, int S_max);
 void launch_plan_fast(const TablesDev &tb, const CandDev &cd, const PlansDev &out, void *ws,
-                      int n_slices, int n_cu, bool narrow, unsigned long long *work, hipStream_t st);
+                      int n_slices, int n_cu, bool narrow, int64_t worst_time, unsigned long long *work, hipStream_t st);
 void launch_plan_index(const TablesDev &tb, int S_max, uint16_t *index, hipStream_t st);
 void launch_plan_prepass(const TablesDev &tb, const CandDev &cd, void *ws, int n_groups, bool narrow, hipStream_t st);
 // Whether the exact search narrows bands (k2_narrow.hip); a candidate is listed for it when its memory bands are wider

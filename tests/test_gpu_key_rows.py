@@ -1,0 +1,58 @@
+"""The min-max planner on both sides of the line between key rows and value rows: the largest time of any plan
+against 2^31 over the largest degree, with degrees of both kinds, rows of one chunk and of several."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2509_24859_amd import workloads as W
+
+from helpers import assert_plans_equal, simple_problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx(harp):
+    c = harp.Context(0)
+    yield c
+    c.close()
+
+
+def _worst_time(p):
+    """The whole sequence on the slowest group, or the largest output over the slowest link."""
+    t = oracle.build_tables(p)
+    n_tp = len(p.tp_degrees)
+    stage = max(int(t.PF[p.group_type[g]][p.L]) + int(t.PR[g][k][p.L]) for g in range(p.G) for k in range(n_tp))
+    return max(stage, -(-int(p.act_bytes.max()) // int(p.bw.min())))
+
+
+@pytest.mark.parametrize("beyond", [-(1 << 20), -1, 0, 5])
+@pytest.mark.parametrize("L,degrees,ndev", [(9, (1,), (4, 3)), (70, (1, 2, 4, 8), (8, 9, 8)), (70, (1, 2, 3, 6), (8, 9, 8)),
+                                            (300, (1, 5, 7), (9, 8)), (300, (1, 2, 4), (9, 8))],
+                         ids=lambda x: str(x).replace(" ", ""))
+def test_times_around_the_limit_of_key_rows(harp, ctx, L, degrees, ndev, beyond):
+    rng = np.random.default_rng(L + len(degrees))
+    G = len(ndev)
+    bw = rng.integers(20, 60, size=(G, G))
+    bw = np.minimum(bw, bw.T)
+    bw[np.arange(G), np.arange(G)] = 700
+    fwd = rng.integers(1, 2000, size=(1, L))
+    p = simple_problem(np.zeros(L), M=9, T=1, G=G, ndev=ndev, tp=degrees, gtype=[0] * G, fwd=fwd,
+                       bwd=rng.integers(1, 2000, size=(1, L)), act=rng.integers(10, 30000, size=L),
+                       params=rng.integers(0, 40, size=L), stash=rng.integers(0, 10, size=L), bw=bw)
+    p.type_mem_bytes[:] = 90 * L // sum(ndev) + 100
+    limit = (2 ** 31 - 1) // max(degrees)
+    # most of the time in three operators: stages that hold none of them compare small keys with large ones
+    rest = limit + beyond - _worst_time(p)
+    for i, part in ((0, rest // 2), (L // 2, rest // 3), (L - 1, rest - rest // 2 - rest // 3)):
+        p.fwd_us[0, i] += part
+    assert _worst_time(p) == limit + beyond
+    cands = W.make_candidates(p, L, 5, G, min(L, G * 4), 0, 96)
+    ot = oracle.build_tables(p)
+    want = oracle.plan_batch(ot, cands)
+    assert (want.status == oracle.OK).sum() >= 8
+    got, _ = harp.plan(ctx, p, cands)
+    assert_plans_equal(got, want, "plans")
+    exact, _, _ = harp.plan_exact(ctx, p, cands)                     # (works on those results)
+    ok = want.status == oracle.OK
+    assert (exact.status == want.status).all() and (exact.iter_time[ok] <= want.iter_time[ok]).all()
