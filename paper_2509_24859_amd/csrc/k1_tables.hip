@@ -610,12 +610,12 @@ __global__ __launch_bounds__(kScanThreads) void k1_long_scan(TablesDev tb, Build
     report(tb.header, bad, ovf, act_seen, lane == 0 && blockIdx.y == 0);
 }
 
-// Launch 4 (one workgroup): checks of the small arrays, device numbering of the groups, the
+// Launch 4, one workgroup of it: checks of the small arrays, device numbering of the groups, the
 // magnitude verdict, and whether the 32-bit fast path may be used.  The kernel is a chain of
 // dependent memory round trips and little else, so everything whose address depends on nothing -
 // each thread's first element of every array, the all-reduce totals, what thread 0 needs at the end -
 // is loaded before the first wait; only the work totals (their row is the group's type) come second.
-__global__ __launch_bounds__(256) void k1_finalize(TablesDev tb, BuildLimits lim) {
+__device__ __forceinline__ void finalize(const TablesDev &tb, const BuildLimits &lim) {
     __shared__ unsigned int bad_s, ovf_s;
     __shared__ unsigned long long min_bw_s;
     __shared__ long long worst_s, worst32_s;
@@ -751,23 +751,49 @@ __global__ __launch_bounds__(256) void k1_finalize(TablesDev tb, BuildLimits lim
     }
 }
 
-// Launch 5: 32-bit rows of the fast path.  Row q < G*n_tp: PF[type g][i] + tp * PR[g][k][i]
-// (so that time(j, i) = ceil((row[i] - row[j]) / tp)); then G*G rows of per-link cut times.
-__global__ __launch_bounds__(256) void k1_fast_rows(TablesDev tb) {
-    if (tb.header->fast32 == 0) return;
-    const int q = blockIdx.y;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > tb.L) return;
+__global__ __launch_bounds__(256) void k1_finalize(TablesDev tb, BuildLimits lim) { finalize(tb, lim); }
+
+// The other workgroups of launch 4: 32-bit rows of the fast path.  Row q < G*n_tp: PF[type g][i] + tp * PR[g][k][i]
+// (so that time(j, i) = ceil((row[i] - row[j]) / tp)); then G*G rows of per-link cut times.  They need the sums and no
+// verdict - rows that turn out not to fit 32 bits are not read - so they do not wait for it: a launch and its gap less,
+// and the verdict's chain of round trips is hidden behind the rows (build and verdict, us: 12
+// operators 31.4 -> 29.4, 82 37.1 -> 34.5, 1,000 on 32 groups 43.6 -> 38.9).  A malformed problem's
+// rows are left out.  A thread takes four entries 256 apart (4,000 operators, 100 groups: 160,000 workgroups with one, 167 ->
+// 111 us).
+constexpr int kRowEntries = 4;
+template <bool kVerdict>
+__global__ __launch_bounds__(256) void k1_fast_rows(TablesDev tb, BuildLimits lim) {
+    int q = blockIdx.y;
+    if (kVerdict) {
+        if (q == 0) {
+            if (blockIdx.x == 0) finalize(tb, lim);
+            return;
+        }
+        --q;
+    }
+    const int i0 = blockIdx.x * blockDim.x * kRowEntries + threadIdx.x;
     const int n_time_rows = tb.G * tb.n_tp;
     if (q < n_time_rows) {
-        int g = q / tb.n_tp, k = q - g * tb.n_tp;
-        int64_t v = tb.PF(tb.group_type[g])[i] + int64_t(tb.tp[k]) * tb.PR(g, k)[i];
-        tb.P32[int64_t(q) * tb.pitch32 + i] = (uint32_t)v;
+        const int g = q / tb.n_tp, k = q - g * tb.n_tp, t = tb.group_type[g];
+        if (t < 0 || t >= tb.T) return;
+        const int64_t *pf = tb.PF(t), *pr = tb.PR(g, k);
+        uint32_t *to = tb.P32 + int64_t(q) * tb.pitch32;
+#pragma unroll
+        for (int u = 0; u < kRowEntries; ++u) {
+            const int i = i0 + u * 256;
+            if (i <= tb.L) to[i] = uint32_t(uint64_t(pf[i]) + uint64_t(tb.tp[k]) * uint64_t(pr[i]));
+        }
     } else {
-        int e = q - n_time_rows;
+        const int e = q - n_time_rows;
         const int64_t link = tb.bw[e];
-        int64_t v = (i == 0) ? 0 : ceil_div_inv(tb.act_bytes[i - 1], link, 1.0 / (double)link);
-        tb.CM[int64_t(e) * tb.pitch32 + i] = (uint32_t)v;
+        if (link < 1) return;
+        const double inv = 1.0 / (double)link;
+        uint32_t *to = tb.CM + int64_t(e) * tb.pitch32;
+#pragma unroll
+        for (int u = 0; u < kRowEntries; ++u) {
+            const int i = i0 + u * 256;
+            if (i <= tb.L) to[i] = i == 0 ? 0u : (uint32_t)ceil_div_inv(tb.act_bytes[i - 1], link, inv);
+        }
     }
 }
 
@@ -805,11 +831,11 @@ void launch_build(const TablesDev &tb, const BuildLimits &lim, hipStream_t st) {
         hipLaunchKernelGGL(k1_scan_chunk_sums, dim3(n_rows), dim3(kScanThreads), 0, st, tb, n_chunks);
     }
     hipLaunchKernelGGL(k1_scan_rows, dim3(n_rows, n_chunks), dim3(kScanThreads), 0, st, tb, lim, n_chunks);
-    hipLaunchKernelGGL(k1_finalize, dim3(1), dim3(256), 0, st, tb, lim);
-    if (lim.want_fast) {
-        const int q = tb.G * tb.n_tp + tb.G * tb.G;
-        hipLaunchKernelGGL(k1_fast_rows, dim3((tb.L + 256) / 256, q), dim3(256), 0, st, tb);
-    }
+    const int q = lim.want_fast ? tb.G * tb.n_tp + tb.G * tb.G : 0, per = 256 * kRowEntries;
+    const bool together = q > 0 && q < 65535;          // (workgroups in a launch's second dimension)
+    if (!together) hipLaunchKernelGGL(k1_finalize, dim3(1), dim3(256), 0, st, tb, lim);
+    if (together) hipLaunchKernelGGL(k1_fast_rows<true>, dim3((tb.L + per) / per, q + 1), dim3(256), 0, st, tb, lim);
+    else if (q > 0) hipLaunchKernelGGL(k1_fast_rows<false>, dim3((tb.L + per) / per, q), dim3(256), 0, st, tb, lim);
 }
 
 }  // namespace harp

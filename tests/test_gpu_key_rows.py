@@ -1,4 +1,4 @@
-"""The min-max planner on both sides of the line between key rows and value rows: the largest time of any plan
+"""The 32-bit rows that the build writes, and the min-max planner on both sides of the line between key rows and value rows: the largest time of any plan
 against 2^31 over the largest degree, with degrees of both kinds, rows of one chunk and of several."""
 import numpy as np
 import pytest
@@ -56,3 +56,18 @@ def test_times_around_the_limit_of_key_rows(harp, ctx, L, degrees, ndev, beyond)
     exact, _, _ = harp.plan_exact(ctx, p, cands)                     # (works on those results)
     ok = want.status == oracle.OK
     assert (exact.status == want.status).all() and (exact.iter_time[ok] <= want.iter_time[ok]).all()
+
+
+@pytest.mark.parametrize("L", [255, 256, 1023, 1024, 1025])
+def test_rows_at_the_edges_of_a_thread(harp, ctx, L):
+    """Four entries of a row per thread, 256 apart: stages that end at and around them."""
+    rng = np.random.default_rng(L)
+    p = simple_problem(np.zeros(L), M=4, T=2, G=2, ndev=(4, 3), tp=(1, 2, 4), gtype=[0, 1], fwd=rng.integers(1, 90, size=(2, L)),
+                       bwd=rng.integers(1, 90, size=(2, L)), act=rng.integers(10, 3000, size=L),
+                       params=np.ones(L, dtype=np.int64), stash=np.ones(L, dtype=np.int64), bw=np.full((2, 2), 40))
+    p.type_mem_bytes[:] = 6 * L
+    cands = W.make_candidates(p, L, 3, 2, 5, 0, 12)
+    want = oracle.plan_batch(oracle.build_tables(p), cands)
+    assert (want.status == oracle.OK).any() and harp.Tables(ctx, p).fast32
+    got, _ = harp.plan(ctx, p, cands, harp.PATH_FAST32)
+    assert_plans_equal(got, want, "L %d" % L)
