@@ -55,12 +55,19 @@ template <> struct H1Traits<uint64_t> {
 // The memory test of a transition, eq. mem_cons, is a 64-bit sum with a 64 x 32 multiply, half of what a
 // transition costs in 64-bit integers.  It runs in float on running sums rounded to float (counts, at most
 // 3 S, are exact in float): the need comes out within a bound E of the true one, so a need of at most
-// cap - E fits and one above cap + E does not, and only a cell with a transition in between that would have been
-// taken is worked again in 64 bits, on the sums in global memory.  512 operators, 65,536 candidates, loose
-// memory: 18.1 -> 14.1 ms, 160 operators 1.60 -> 1.47 (with room for six wavefronts per SIMD: a cut takes 28
-// bytes of LDS instead of 36).  With u = 2^-24, P and Q the whole sums of
-// parameter and stash bytes and n the largest count: rounding two sums (sum_f), 6 u P and 6 u n Q; the
-// differences, u P and u n Q; the fused multiply-add, u (P + n Q); the cap, u cap.  E = 16 u (P + n Q) + 4 u cap.
+// cap - E fits and one above cap + E does not.  A transition is taken up to cap + E, and where the need of the one a cell
+// ends with is above cap - E the cell is worked again in 64 bits, on the sums in global memory (any other transition is
+// either refused for certain or no better, whether it fits or not).  512 operators, 65,536 candidates, loose
+// memory: 18.1 -> 14.1 ms, 160 operators 1.60 -> 1.47.
+// What end cut j puts into the need, P[j] + n Q[j] with n the count of its entry, is worked out once when the entry is
+// made and sits in a row of its own; cut i adds P[i] to the limits and n Q[i] in one fused operation: 9 vector
+// instructions a transition for 14 (us a call: 160 operators, 65,536 candidates 1,452 -> 1,249; 512 operators, 65,536, loose
+// memory 15,107 -> 13,374, tight 1,995 -> 1,736; 307 operators, degrees 1 2 3 6, 1,531 -> 1,241; the scans are bound by the
+// issue of vector instructions).  Measured and left: the least of four first and its place found after the scan (1,279
+// for 1,250), the reach requested a slot ahead (1,260 for 1,250).  With u = 2^-24, P
+// and Q the whole sums of parameter and stash bytes and n the largest count: rounding two sums each (sum_f), 6 u P and
+// 6 u n Q; the two fused operations, 2 u (P + n Q); the limits with P[i], u P; the cap, 3 u cap.
+// E = 16 u (P + n Q) + 4 u cap.
 struct alignas(8) MemPair { float pp, ps; };
 // 0 <= v < 2^63 as a float, off by less than 3 u v: the halves (either is rounded to 24 bits) and their sum
 __device__ __forceinline__ float sum_f(int64_t v) {
@@ -79,9 +86,8 @@ __host__ __device__ inline size_t h1f1b_small_bytes(int S_max) {
     const size_t b = size_t(S_max) * sizeof(StageConst) + 16 + size_t(S_max + 1) * 8 + 8 + 64 + size_t(S_max) * 8;
     return (b + 15) & ~size_t(15);
 }
-// bytes per cut of the rows in LDS when every row is sized for one slot: one row of memory sums, two
-// of entries, one of times
-__host__ __device__ inline size_t h1f1b_cut_bytes(size_t entry) { return sizeof(MemPair) + 2 * entry + 4; }
+// bytes per cut of the rows in LDS when every row is sized for one slot: two rows of entries, two of needs, one of times
+__host__ __device__ inline size_t h1f1b_cut_bytes(size_t entry) { return 2 * entry + 2 * sizeof(float) + 4; }
 
 // counts: [0] live, [1] dead, [2] queued for 64-bit sums, [7] ticket of the 64-bit kernel, [10] candidates queued for rows over the whole sequence, [11] next item of that list.
 // Both queues sit in the unused tail of the dead list, the 64-bit one from its front, the other from
@@ -117,14 +123,14 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
     int32_t *fin_w = reinterpret_cast<int32_t *>(flags + 2);                           // [2][4][2]: per slot parity and wavefront, lowest and highest cell with a finite sum
     uint32_t *hi_off = reinterpret_cast<uint32_t *>(fin_w + 16);                       // [S_max]
     uint32_t *deltas = hi_off + S_max;                                                 // [S_max]
-    // Rows of row_len entries.  Whole-sequence form: one row of memory sums, two of entries, two of
-    // times; entry x of a row is cut x.  Slot-sized form: a row's entry 0 is the lowest cut of the
-    // slot it serves, and the memory sums and times of the slot in front take the place of this
+    // Rows of row_len entries.  Whole-sequence form: two rows of entries, two of needs, two of times;
+    // entry x of a row is cut x.  Slot-sized form: a row's entry 0 is the lowest cut of the
+    // slot it serves, and the times of the slot in front take the place of this
     // slot's once its cells are done (one wavefront: its LDS operations execute in order).
-    MemPair *mem0 = reinterpret_cast<MemPair *>(lds_raw + h1f1b_small_bytes(S_max));
-    Entry *rows0 = reinterpret_cast<Entry *>(mem0 + row_len);
+    Entry *rows0 = reinterpret_cast<Entry *>(lds_raw + h1f1b_small_bytes(S_max));
     Entry *rows1 = rows0 + row_len;
-    uint32_t *prow0 = reinterpret_cast<uint32_t *>(rows1 + row_len);
+    float *needs0 = reinterpret_cast<float *>(rows1 + row_len), *needs1 = needs0 + row_len;
+    uint32_t *prow0 = reinterpret_cast<uint32_t *>(needs1 + row_len);
     uint32_t *prow1 = kBandRows ? prow0 : prow0 + row_len;
     uint16_t *arg = reinterpret_cast<uint16_t *>(arg_base + size_t(blockIdx.x) * arg_per_group);
     const int n_dead = counts[1];
@@ -135,12 +141,9 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
     const int64_t m_cap = tb.M;
     const int64_t *PP = tb.PP(), *PS = tb.PS();
 
-    // the running sums of parameter and stash bytes are the same for every candidate
-    if (!kBandRows) {
-        for (int j = tid; j <= L; j += nthreads) mem0[j] = MemPair{sum_f(PP[j]), sum_f(PS[j])};
-        for (int j = L + 1 + tid; j < row_len; j += nthreads) mem0[j] = MemPair{0.f, 0.f};
+    auto sums_at = [&](int x) { return MemPair{sum_f(PP[x]), sum_f(PS[x])}; };
+    if (!kBandRows)
         for (int j = L + 1 + tid; j < row_len; j += nthreads) { prow0[j] = 0; prow1[j] = 0; }
-    }
 
     for (;;) {
         __syncthreads();   // the previous candidate's tail has finished with LDS
@@ -209,19 +212,21 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
         // prologue: behind the last stage no operators are left and nothing is launched yet (the last
         // stage itself adds delta(0) = 1); the fused time row of the last slot over its cells and its
         // single continuation
+        MemPair sums_n{0.f, 0.f};            // memory sums at this lane's first cell of the slot to come
         {
             const int il0 = (S == 1) ? 0 : band_lo((uint32_t)uniform((int)band[S - 1]));
             Entry *row_S = rows0 - (kBandRows ? L : 0);
-            if (tid == 0) { row_S[L].h = 0; row_S[L].nn = 1.f; }
+            if (tid == 0) {
+                const MemPair all = sums_at(L);
+                row_S[L].h = 0;
+                row_S[L].nn = 1.f;
+                (needs0 - (kBandRows ? L : 0))[L] = all.pp + all.ps;
+            }
             if (tid >= 1 && tid <= kTail) row_S[L + tid].h = kInfSum;
             const uint32_t *p32 = tb.P32 + (uint32_t)uniform((int)sc[S - 1].p_row);
             uint32_t *pr = prow0 - (kBandRows ? il0 : 0);
             for (int x = il0 + tid; x <= L; x += nthreads) pr[x] = p32[x];
-            if (kBandRows) {
-                MemPair *mm = mem0 - il0;
-                for (int x = il0 + tid; x <= L + kTail - 1; x += nthreads)
-                    mm[x] = x <= L ? MemPair{sum_f(PP[x]), sum_f(PS[x])} : MemPair{0.f, 0.f};
-            }
+            if (il0 + tid <= L) sums_n = sums_at(il0 + tid);
         }
         lds_barrier();
         int cur = 0, pcur = 0;
@@ -283,28 +288,28 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
             // staged for the slot in front at nl
             const uint32_t *pr_cur = (pcur ? prow1 : prow0) - (kBandRows ? il : 0);
             uint32_t *pr_next = (pcur ? prow0 : prow1) - (kBandRows ? nl : 0);
-            const MemPair *mem = mem0 - (kBandRows ? il : 0);
-            MemPair *mem_next = mem0 - (kBandRows ? nl : 0);
             const Entry *prev = (cur ? rows1 : rows0) - (kBandRows ? jl : 0);
             Entry *next = (cur ? rows0 : rows1) - (kBandRows ? il : 0);
+            const float *needs = (cur ? needs1 : needs0) - (kBandRows ? jl : 0);
+            float *needs_next = (cur ? needs0 : needs1) - (kBandRows ? il : 0);
             // the cut in front of this slot's stage (between slot - 1 and slot)
             const uint32_t *cm_front = stage_next ? tb.CM + ((uint32_t)uniform((int)sc[slot - 1].cm_row_shift) & kRowMask)
                                                   : nullptr;
             const uint32_t *p32_n = stage_next ? tb.P32 + (uint32_t)uniform((int)sc[slot - 1].p_row) : nullptr;
-            // requests for the slot in front: entry xn of its time row, and this lane's own cut time
+            // requests for the slot in front: entry xn of its time row and the memory sums there, and this lane's own cut time
             const int xn = nl + tid;
             uint32_t p_n = 0, cf_first = 0;
-            if (stage_next && xn <= ih) p_n = p32_n[xn];
+            int64_t pp_n = 0, ps_n = 0;
+            if (stage_next && xn <= ih) { p_n = p32_n[xn]; pp_n = PP[xn]; ps_n = PS[xn]; }
             if (stage_next && il + tid <= ih) cf_first = cm_front[il + tid];
 
             bool first_trip = true;
             for (int i = il + tid; i <= ih; i += nthreads) {
-                const MemPair mi = mem[i];
-                const uint32_t xi = pr_cur[i];
+                const MemPair mi = first_trip ? sums_n : sums_at(i);
+                const float fits = fits_up_to + mi.pp, none = none_above + mi.pp;
+                const uint32_t xi = pr_cur[i], add = div.add - xi;
                 SumT best = kInfSum;
-                float best_n = 0.f;
-                int best_j = 0;
-                bool unsure = false;
+                int best_j = jl;
                 const int first = (i + 1) > jl_f ? (i + 1) : jl_f;
                 int j = first;
                 // end cuts beyond the classic count's reach cannot fit with a larger count either
@@ -315,33 +320,29 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                     uint32_t tj = 0;
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        // entries behind the band (up to kTail behind L) hold an infinite sum; what
-                        // the other rows hold there is never used
-                        const Entry e = prev[j + u];
-                        const MemPair mj = mem[j + u];
-                        tj = tp_quot<kOdd>(pr_cur[j + u] + div.add - xi, div);
-                        const float need = fmaf(e.nn, mj.ps - mi.ps, mj.pp - mi.pp);
-                        const SumT v = e.h + tj;
-                        const bool upd = (need <= none_above) & (tj <= tcap) & (v < best) & ((j + u) <= end);
-                        unsure = unsure | (upd & !(need <= fits_up_to));
+                        // end cuts behind jh_f (up to kTail behind L) hold an infinite sum, whatever the other
+                        // rows hold there; those behind `reach` need more memory than there is with any count
+                        const float need = fmaf(-prev[j + u].nn, mi.ps, needs[j + u]);
+                        tj = tp_quot<kOdd>(pr_cur[j + u] + add, div);
+                        const SumT v = prev[j + u].h + tj;
+                        const bool upd = (need <= none) & (tj <= tcap) & (v < best);
                         best = upd ? v : best;
-                        best_n = upd ? e.nn : best_n;
                         best_j = upd ? (j + u) : best_j;
                     }
                     more = ((j + 4) <= end) & (tj <= tcap);
                     j += 4;
                 }
-                if (unsure) {                        // rare: the cell again, in 64 bits
+                if (best < kInfSum && !(fmaf(-prev[best_j].nn, mi.ps, needs[best_j]) <= fits)) {
+                    // rare: the cell again, in 64 bits
                     best = kInfSum;
-                    best_n = 0.f;
-                    best_j = 0;
+                    best_j = jl;
                     for (j = first; j <= end; ++j) {
                         const Entry e = prev[j];
-                        const uint32_t time = tp_quot<kOdd>(pr_cur[j] + div.add - xi, div);
+                        const uint32_t time = tp_quot<kOdd>(pr_cur[j] + add, div);
                         if (time > tcap) break;
                         const SumT v = e.h + time;
                         const int64_t dpp = PP[j] - PP[i], dps = PS[j] - PS[i];
-                        if (v < best && dpp + int64_t(e.nn) * dps <= capm) { best = v; best_n = e.nn; best_j = j; }
+                        if (v < best && dpp + int64_t(e.nn) * dps <= capm) { best = v; best_j = j; }
                     }
                 }
                 arg[slot * arg_pitch + i] = (uint16_t)best_j;
@@ -363,8 +364,10 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                             new_hi = hi_r > new_hi ? hi_r : new_hi;
                         }
                     }
-                    const uint32_t nn = h1f1b_delta(cf, cap64) + uint32_t(best_n);
-                    next[i].nn = float(nn < uint32_t(m_cap) ? nn : uint32_t(m_cap));
+                    const uint32_t nn = h1f1b_delta(cf, cap64) + uint32_t(prev[best_j].nn);
+                    const float n_f = float(nn < uint32_t(m_cap) ? nn : uint32_t(m_cap));
+                    next[i].nn = n_f;
+                    needs_next[i] = fmaf(n_f, mi.ps, mi.pp);
                 } else {
                     scal[0] = uint64_t(best);
                 }
@@ -374,10 +377,7 @@ __device__ __forceinline__ void h1f1b_body(const TablesDev &tb, const CandDev &c
                 if (tid < kTail) next[ih + 1 + tid].h = kInfSum;     // behind the band
                 if (xn <= ih) pr_next[xn] = p_n;
                 for (int x = xn + nthreads; x <= ih; x += nthreads) pr_next[x] = p32_n[x];
-                if (kBandRows) {
-                    for (int x = xn; x <= ih + kTail - 1; x += nthreads)
-                        mem_next[x] = x <= L ? MemPair{sum_f(PP[x]), sum_f(PS[x])} : MemPair{0.f, 0.f};
-                }
+                sums_n = MemPair{sum_f(pp_n), sum_f(ps_n)};
             }
             if (end_of_slot(slot, new_lo, new_hi)) break;
             cur ^= 1;
@@ -474,9 +474,9 @@ HARP_H1F1B_KERNEL(k2_h1f1b_wide, __launch_bounds__(kFastThreads), uint64_t, 0)
 
 int h1f1b_row_len(int L) { return (L + 1 + kTail + 7) / 8 * 8; }
 
-// whole-sequence rows: one of memory sums, two of entries, two of times
+// whole-sequence rows: two of entries, two of needs, two of times
 size_t h1f1b_lds_bytes(int L, int S_max, size_t entry) {
-    return h1f1b_small_bytes(S_max) + size_t(h1f1b_row_len(L)) * (sizeof(MemPair) + 2 * entry + 8);
+    return h1f1b_small_bytes(S_max) + size_t(h1f1b_row_len(L)) * (2 * entry + 2 * sizeof(float) + 8);
 }
 
 }  // namespace
@@ -495,7 +495,7 @@ void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_
     const size_t per_group = fast_arg_per_group(tb.L, cd.S_max);
     const int arg_pitch = fast_row_len(tb.L);
     // Wavefronts per CU of the first launch and the row entries their LDS share leaves: as many
-    // wavefronts as hold rows for the whole sequence, between 14 and 24 (six per SIMD, held to 80 registers with 2 of
+    // wavefronts as hold rows for the whole sequence, between 14 and 24 (six per SIMD, held to 80 registers with 5 of
     // them spilled; fewer hide less of the latency: 160 operators, five per SIMD 1.61 ms, six 1.47, seven 1.54 with
     // more spills).  Shares are whole units of allocation: 28 bytes beyond nine of them leave room for 12 wavefronts
     // instead of 14 (512 operators, tight memory 2.01 ms for 1.87).  The smaller the share, the more candidates leave for the second launch: 300 operators, 14 per
