@@ -295,13 +295,13 @@ __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh_h1f1b(TablesDev tb, O
 
 // ------------------------------------------------------------------------------------ band form
 
-// Bound by latency: of the stages one after the other (a barrier or two each, short rows) and of the serial parts
-// (chains, plan recovery: one wavefront of a workgroup).  Vector issue is 34% of the rate in the min-max form and 21%
-// in the exact one, 3.3 wavefronts in flight per SIMD (4,096 orderings of 82 operators and 64 devices).  Measured
-// against the whole-table form on 32-bit rows it replaces: those orderings 3.57 -> 0.87-0.97 ms (of an ordering's
-// time 16% the search for the cap, 18% the ranges, 48% the value pass, 11% plan and score); exact form, 256
-// orderings of 160 operators and 128 devices, 15-19 -> 3.1-3.4 ms (3% the search for the cap, 4% and 10% the ranges
-// of the min-max pass and of the caps, 15% and 56% their value passes, 11% plans and scores).
+// Bound by latency where rows are short - stages one after the other, a barrier or two each, serial parts on a wavefront
+// or two (chains, plan recovery) - and by vector issue where they are long, which few orderings have and all wait for.
+// Measured against the whole-table form on 32-bit rows it replaces: 4,096 orderings of 82 operators and 64 devices 3.57 ->
+// 0.67-0.75 ms (of an ordering's 132 us 36% the value pass, 23% the chains, 15% the reach tables, 13% plan and score); exact
+// form, 256 orderings of 160 operators and 128 devices, 15-19 -> 2.2-2.4 ms (of an ordering's 1.1 ms 53% the least-sum
+// passes, 17% the min-max pass, 11% the chains, 13% plans and scores; the longest takes twice that).  Tried in vain: five
+// workgroups of 256 threads on a CU (680 -> 705 us), a cell requested while the one before it is worked (exact form 10% slower).
 // The exact form walks the caps as k2_mesh does: first at t_S, then down from ceil(T / B).  A plan that
 // is not kept costs nothing but its score: the outputs are written whenever a better one is found.
 template <bool kExact>
