@@ -610,7 +610,7 @@ __global__ __launch_bounds__(kScanThreads) void k1_long_scan(TablesDev tb, Build
     report(tb.header, bad, ovf, act_seen, lane == 0 && blockIdx.y == 0);
 }
 
-// Launch 4, one workgroup of it: checks of the small arrays, device numbering of the groups, the
+// Launch 4, one workgroup: checks of the small arrays, device numbering of the groups, the
 // magnitude verdict, and whether the 32-bit fast path may be used.  The kernel is a chain of
 // dependent memory round trips and little else, so everything whose address depends on nothing -
 // each thread's first element of every array, the all-reduce totals, what thread 0 needs at the end -
@@ -753,25 +753,17 @@ __device__ __forceinline__ void finalize(const TablesDev &tb, const BuildLimits 
 
 __global__ __launch_bounds__(256) void k1_finalize(TablesDev tb, BuildLimits lim) { finalize(tb, lim); }
 
-// The other workgroups of launch 4: 32-bit rows of the fast path.  Row q < G*n_tp: PF[type g][i] + tp * PR[g][k][i]
-// (so that time(j, i) = ceil((row[i] - row[j]) / tp)); then G*G rows of per-link cut times.  They need the sums and no
-// verdict - rows that turn out not to fit 32 bits are not read - so they do not wait for it: a launch and its gap less,
-// and the verdict's chain of round trips is hidden behind the rows (build and verdict, us: 12
-// operators 31.4 -> 29.4, 82 37.1 -> 34.5, 1,000 on 32 groups 43.6 -> 38.9).  A malformed problem's
-// rows are left out.  A thread takes four entries 256 apart (4,000 operators, 100 groups: 160,000 workgroups with one, 167 ->
-// 111 us).
+// Launch 4 of a problem short enough for 32-bit rows: the verdict, and beside it those rows.  Row q < G*n_tp: PF[type g][i] +
+// tp * PR[g][k][i] (so that time(j, i) = ceil((row[i] - row[j]) / tp)); then G*G rows of per-link cut times.  They need
+// the sums and no verdict, so they do not wait for it: a launch and its gap less, and the verdict's chain of round trips is
+// hidden behind the rows (build and verdict, us: 12 operators 31.4 -> 29.4, 82 37.1 -> 34.5, 1,000 on 32 groups 43.6
+// -> 38.9).  A thread takes four entries 256 apart (4,000 operators, 100 groups: 160,000 workgroups with one, 167 -> 111 us).
+// Rows that turn out not to fit 32 bits are written with what is left of them and not read; a malformed problem's are left out.
 constexpr int kRowEntries = 4;
-template <bool kVerdict>
-__global__ __launch_bounds__(256) void k1_fast_rows(TablesDev tb, BuildLimits lim) {
-    int q = blockIdx.y;
-    if (kVerdict) {
-        if (q == 0) {
-            if (blockIdx.x == 0) finalize(tb, lim);
-            return;
-        }
-        --q;
-    }
-    const int i0 = blockIdx.x * blockDim.x * kRowEntries + threadIdx.x;
+__global__ __launch_bounds__(256) void k1_fast_rows(TablesDev tb, BuildLimits lim, int per_row) {
+    if (blockIdx.x == 0) { finalize(tb, lim); return; }
+    const int q = int((blockIdx.x - 1) / uint32_t(per_row));
+    const int i0 = int(blockIdx.x - 1 - uint32_t(q * per_row)) * 256 * kRowEntries + threadIdx.x;
     const int n_time_rows = tb.G * tb.n_tp;
     if (q < n_time_rows) {
         const int g = q / tb.n_tp, k = q - g * tb.n_tp, t = tb.group_type[g];
@@ -831,11 +823,12 @@ void launch_build(const TablesDev &tb, const BuildLimits &lim, hipStream_t st) {
         hipLaunchKernelGGL(k1_scan_chunk_sums, dim3(n_rows), dim3(kScanThreads), 0, st, tb, n_chunks);
     }
     hipLaunchKernelGGL(k1_scan_rows, dim3(n_rows, n_chunks), dim3(kScanThreads), 0, st, tb, lim, n_chunks);
-    const int q = lim.want_fast ? tb.G * tb.n_tp + tb.G * tb.G : 0, per = 256 * kRowEntries;
-    const bool together = q > 0 && q < 65535;          // (workgroups in a launch's second dimension)
-    if (!together) hipLaunchKernelGGL(k1_finalize, dim3(1), dim3(256), 0, st, tb, lim);
-    if (together) hipLaunchKernelGGL(k1_fast_rows<true>, dim3((tb.L + per) / per, q + 1), dim3(256), 0, st, tb, lim);
-    else if (q > 0) hipLaunchKernelGGL(k1_fast_rows<false>, dim3((tb.L + per) / per, q), dim3(256), 0, st, tb, lim);
+    if (!lim.want_fast) {
+        hipLaunchKernelGGL(k1_finalize, dim3(1), dim3(256), 0, st, tb, lim);
+        return;
+    }
+    const int rows32 = tb.G * tb.n_tp + tb.G * tb.G, per_row = (tb.L + 256 * kRowEntries) / (256 * kRowEntries);
+    hipLaunchKernelGGL(k1_fast_rows, dim3(1 + rows32 * per_row), dim3(256), 0, st, tb, lim, per_row);
 }
 
 }  // namespace harp

@@ -6,7 +6,7 @@ import pytest
 import oracle
 from paper_2509_24859_amd import workloads as W
 
-from helpers import assert_plans_equal, simple_problem
+from helpers import assert_plans_equal, cands_from_lists, simple_problem
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +71,18 @@ def test_rows_at_the_edges_of_a_thread(harp, ctx, L):
     assert (want.status == oracle.OK).any() and harp.Tables(ctx, p).fast32
     got, _ = harp.plan(ctx, p, cands, harp.PATH_FAST32)
     assert_plans_equal(got, want, "L %d" % L)
+
+
+def test_as_many_rows_as_there_can_be(harp, ctx):
+    """255 groups with two degrees: 65,535 rows of the 32-bit tables."""
+    G, L = 255, 300
+    rng = np.random.default_rng(5)
+    p = simple_problem(np.zeros(L), M=4, T=3, G=G, ndev=[2] * G, tp=(1, 2), gtype=[g % 3 for g in range(G)],
+                       fwd=rng.integers(1, 90, size=(3, L)), bwd=rng.integers(1, 90, size=(3, L)), act=rng.integers(10, 3000, size=L),
+                       params=np.ones(L, dtype=np.int64), stash=np.ones(L, dtype=np.int64), bw=rng.integers(20, 60, size=(G, G)))
+    cands = cands_from_lists([[(int(g), int(t)) for g, t in zip(rng.permutation(G)[:9], rng.integers(1, 3, 9))] for _ in range(24)]
+                             + [[(254, 2), (253, 1), (0, 2)], [(0, 1), (254, 1)]])
+    want = oracle.plan_batch(oracle.build_tables(p), cands)
+    assert (want.status == oracle.OK).all() and harp.Tables(ctx, p).fast32
+    got, _ = harp.plan(ctx, p, cands, harp.PATH_FAST32)
+    assert_plans_equal(got, want, "255 groups")
