@@ -21,7 +21,7 @@ struct BuildHeader {
     unsigned int bad_arg;        // nonzero: malformed values
     unsigned int overflow;       // nonzero: magnitudes out of range
     unsigned int fast32;         // not 0: 32-bit rows and cut table are valid; 1: and every degree is a power of two
-    unsigned int pad;
+    unsigned int beyond32;       // nonzero: the scan has seen a sum that alone is too large for 32-bit rows
     unsigned long long max_act;  // largest act_bytes entry
     long long worst_time;        // largest stage or transfer time any plan can see
     long long total_devices;     // sum of group_ndev

@@ -190,6 +190,22 @@ __global__ __launch_bounds__(kScanThreads) void k1_scan_chunk_sums(TablesDev tb,
     report(tb.header, 0, over, 0, false);
 }
 
+// All lanes of the wavefront that has the last entry of row r: whether it rules out 32-bit rows alone (k1_fast_rows) - the work
+// of a type that some group has, or a degree times its all-reduce time.
+__device__ __forceinline__ void note_total(const TablesDev &tb, int r, unsigned long long total) {
+    const int lane = threadIdx.x & 63;
+    if (r == tb.T || r == tb.T + 1) return;                             // bytes
+    bool used = r >= tb.T;
+    unsigned long long part = total;
+    if (used) {
+        const unsigned long long tp = (unsigned long long)tb.tp[(r - (tb.T + 2)) % tb.n_tp];
+        part = total < (1ull << 40) ? tp * total + tp - 1 : ~0ull;
+    }
+    if (part < (1ull << 31)) return;
+    for (int g = lane; g < tb.G; g += 64) used = used || tb.group_type[g] == r;
+    if (__any(used) && lane == 0) atomicOr(&tb.header->beyond32, 1u);
+}
+
 // Launch 3: scan each chunk, add the chunk's offset, write the table row (entry i = l + 1).
 __global__ __launch_bounds__(kScanThreads) void k1_scan_rows(TablesDev tb, BuildLimits lim, int n_chunks) {
     const int r = blockIdx.x, chunk = blockIdx.y;   // rows fastest: a chunk of act_bytes is reused across rows while in L2
@@ -218,6 +234,10 @@ __global__ __launch_bounds__(kScanThreads) void k1_scan_rows(TablesDev tb, Build
     for (int q = 0; q < kScanItems; ++q) {
         run = add_checked(run, v[q], ovf);
         if (base + q < tb.L) out[base + q + 1] = run;
+    }
+    if (lim.want_fast) {
+        const unsigned long long who = __ballot(base < tb.L && base + kScanItems >= tb.L);
+        if (who != 0) note_total(tb, r, (unsigned long long)__shfl(run, __ffsll((long long)who) - 1, 64));
     }
     unsigned long long wave_act = act_seen;
     if (src.track_act) {
@@ -758,16 +778,22 @@ __global__ __launch_bounds__(256) void k1_finalize(TablesDev tb, BuildLimits lim
 // the sums and no verdict, so they do not wait for it: a launch and its gap less, and the verdict's chain of round trips is
 // hidden behind the rows (build and verdict, us: 12 operators 31.4 -> 29.4, 82 37.1 -> 34.5, 1,000 on 32 groups 43.6
 // -> 38.9).  A thread takes four entries 256 apart (4,000 operators, 100 groups: 160,000 workgroups with one, 167 -> 111 us).
-// Rows that turn out not to fit 32 bits are written with what is left of them and not read; a malformed problem's are left out.
+//
+// A problem that will have no such rows is left without, as far as a workgroup can tell from what is there before the launch:
+// it is malformed, a sum alone is too large (4,000 operators, 100 groups: 111 -> 67 us), or the row's own transfers are.  Where only
+// two sums together reach 2^31, or another link's transfers, rows that nothing reads are written (111); a look at
+// every pair of sums in every workgroup that may need one takes longer (163).
 constexpr int kRowEntries = 4;
 __global__ __launch_bounds__(256) void k1_fast_rows(TablesDev tb, BuildLimits lim, int per_row) {
     if (blockIdx.x == 0) { finalize(tb, lim); return; }
     const int q = int((blockIdx.x - 1) / uint32_t(per_row));
     const int i0 = int(blockIdx.x - 1 - uint32_t(q * per_row)) * 256 * kRowEntries + threadIdx.x;
     const int n_time_rows = tb.G * tb.n_tp;
+    const BuildHeader *h = tb.header;
+    const bool none = (h->bad_arg | h->overflow | h->beyond32) != 0;      // (the verdict may join the first two meanwhile)
     if (q < n_time_rows) {
         const int g = q / tb.n_tp, k = q - g * tb.n_tp, t = tb.group_type[g];
-        if (t < 0 || t >= tb.T) return;
+        if (none | (t < 0) | (t >= tb.T)) return;
         const int64_t *pf = tb.PF(t), *pr = tb.PR(g, k);
         uint32_t *to = tb.P32 + int64_t(q) * tb.pitch32;
 #pragma unroll
@@ -778,7 +804,8 @@ __global__ __launch_bounds__(256) void k1_fast_rows(TablesDev tb, BuildLimits li
     } else {
         const int e = q - n_time_rows;
         const int64_t link = tb.bw[e];
-        if (link < 1) return;
+        const unsigned long long most = h->max_act;
+        if (none | (link < 1) || (link <= INT32_MAX && most > (unsigned long long)link * INT32_MAX)) return;
         const double inv = 1.0 / (double)link;
         uint32_t *to = tb.CM + int64_t(e) * tb.pitch32;
 #pragma unroll
@@ -791,7 +818,7 @@ __global__ __launch_bounds__(256) void k1_fast_rows(TablesDev tb, BuildLimits li
 
 __global__ void k1_clear_header(BuildHeader *h) {
     if (threadIdx.x == 0) {
-        h->bad_arg = 0; h->overflow = 0; h->fast32 = 0; h->pad = 0;
+        h->bad_arg = 0; h->overflow = 0; h->fast32 = 0; h->beyond32 = 0;
         h->max_act = 0; h->worst_time = 0; h->total_devices = 0;
         for (int q = 0; q < 3; ++q) h->reserved[q] = 0;
     }

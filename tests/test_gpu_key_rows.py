@@ -73,6 +73,73 @@ def test_rows_at_the_edges_of_a_thread(harp, ctx, L):
     assert_plans_equal(got, want, "L %d" % L)
 
 
+def _totals_problem(L, work, all_reduce, idle_type=0):
+    """Two groups of one type; `work`: its compute time, `all_reduce`: the degree-2 total; `idle_type`: of a type no group has."""
+    rng = np.random.default_rng(L)
+    fwd = rng.integers(1, 90, size=(2, L))
+    act = np.full(L, 40 * (all_reduce // (4 * L)))                        # 4 act / bw per operator at degree 2
+    act[L - 1] += 40 * (all_reduce // 4 - all_reduce // (4 * L) * L)
+    fwd[0, L // 2] += work - fwd[0].sum()
+    fwd[1, 0] += idle_type
+    return simple_problem(np.zeros(L), M=4, T=2, G=2, ndev=(4, 3), tp=(1, 2), gtype=[0, 0], fwd=fwd, bwd=np.zeros_like(fwd),
+                          act=act, params=np.ones(L, dtype=np.int64), stash=np.ones(L, dtype=np.int64),
+                          bw=np.full((2, 2), 40))
+
+
+TOTALS = {  # compute time, all-reduce time at degree 2, an idle type's time, 32-bit rows
+    "work": (2 ** 31, 4000, 0, False),
+    "all-reduce": (9000000, 2 ** 30, 0, False),
+    "sum_at_the_limit": (2 ** 30, 2 ** 29, 0, False),                      # and the rounding of the division: 2^31 + 1
+    "sum_below": (2 ** 30 - 2, 2 ** 29, 0, True),                          # 2^31 - 1
+    "idle_type": (9000000, 4000, 2 ** 31, True),
+}
+
+
+@pytest.mark.parametrize("L", [70, 1024, 1025, 4000])
+@pytest.mark.parametrize("why", list(TOTALS) + ["malformed"])
+def test_rows_are_written_where_they_are_read(harp, ctx, why, L):
+    """Sums on both sides of 2^31, in one part or in their sum: the 32-bit rows are left alone where one part alone says
+    that no kernel reads them."""
+    work, all_reduce, idle, fast = TOTALS.get(why, (9000000, 4000, 0, False))
+    p = _totals_problem(L, work, all_reduce, idle)
+    if why == "malformed":
+        p.stash_bytes[L - 1] = -1
+    tables = harp.Tables(ctx, p, finalize=False)
+    rows = p.G * p.n_tp + p.G * p.G
+    area = tables.buf[-rows * ((L + 1 + 15) // 16 * 64):]                  # (the rows are the last of the buffer)
+    area.fill_(0x5A)
+    tables.rebuild()
+    if why == "malformed":
+        with pytest.raises(harp.HarpError):
+            tables.finalize()
+    else:
+        tables.finalize()
+        assert tables.fast32 == fast
+    if why != "sum_at_the_limit":
+        assert bool((area == 0x5A).all()) == (not fast)
+    if fast:
+        cands = W.make_candidates(p, L, 3, 2, 5, 0, 12)
+        want = oracle.plan_batch(oracle.build_tables(p), cands)
+        assert (want.status == oracle.OK).any()
+        got, _ = harp.plan(ctx, p, cands, harp.PATH_FAST32)
+        assert_plans_equal(got, want, why)
+
+
+def test_a_row_of_transfers_too_long_for_it_is_not_written(harp, ctx):
+    L = 1025
+    p = _totals_problem(L, 9000000, 4000)
+    p.act_bytes[5] = 2 ** 31
+    p.bw[0, 1] = p.bw[1, 0] = 1                                            # 2^31 us; the groups' own links, 2^31 / 40
+    tables = harp.Tables(ctx, p, finalize=False)
+    pitch = (L + 1 + 15) // 16 * 64
+    cuts = tables.buf[-4 * pitch:].view(4, pitch)
+    cuts.fill_(0x5A)
+    tables.rebuild()
+    tables.finalize()
+    assert not tables.fast32
+    assert [bool((row == 0x5A).all()) for row in cuts] == [False, True, True, False]
+
+
 def test_as_many_rows_as_there_can_be(harp, ctx):
     """255 groups with two degrees: 65,535 rows of the 32-bit tables."""
     G, L = 255, 300
