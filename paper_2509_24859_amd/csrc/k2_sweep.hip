@@ -564,7 +564,7 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 struct SweepShare {
     unsigned char *slots;
     int Ws, W;
-    int tries;               // values the first launch tries before it leaves the rest of an ordering to the second
+    int passes;              // least-sum passes and values tried before the first launch leaves the rest of a search to the second
     long long *least;
 };
 // counters of the band launch: orderings left to the walkers, and their ticket; their list grows from the end of redo
@@ -785,7 +785,7 @@ __device__ __forceinline__ void sweep_search(E &b, const TablesDev &tb, const Or
                 cap = hi;
                 state = hi > first ? kUpper : kDone;
             }
-            if (!kWalk && sw.W > 1 && tested >= sw.tries && (state == kTry || state == kUpper)) { left = true; state = kDone; }
+            if (!kWalk && sw.W > 1 && tested >= sw.passes && (state == kTry || state == kUpper)) { left = true; state = kDone; }
         }
         if (kWalk) {
             if (tid == 0) {
@@ -892,13 +892,19 @@ hipError_t launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, c
     ba.per_group = per_group;
     ba.counters = w.counters;
     ba.redo = w.redo;
-    // Least-sum passes and values tried after which the first launch leaves the rest to the second, 24 values before.  Orderings
-    // (a pass of 40 us and more), us with 24 values / 3 / 5 / 8: 48 of 82 operators 907 / 766 / 807 / 920; 16 of 60 operators,
-    // 8 micro-batches 2,830 / 810 / 896 / 1,116; 300 of 60 operators 1,504 / 908 / 861 / 984.  Candidates (a pass of 20 us),
-    // 2 values / 3 / 5 / 8: 16 of 300 operators 1,330 / 742 / 825 / 1,017; 16 of 12 operators 126 / 149 / 127 / 127; where the batch
-    // fills the chip the second launch repeats work for nothing: 300 of 82 operators 1,363 (8 values) / 1,611 / 1,538 / 1,459.
-    const int tries = !forced ? 4 : od.C <= n_cu ? 5 : 20;
-    const SweepShare sw{slots, Ws, W, tries, reinterpret_cast<long long *>(lower)};
+    // Passes (least sums and values tried) after which the first launch leaves the rest of a search to the second.  Where orderings or
+    // candidates outnumber half of the compute units, the second launch takes the place of work in the first and
+    // repeats some of it.  Orderings, us with 4 / 6 / 8 / 24 passes (means over three to five batches): 48 of 82 operators 912 / 956
+    // / 973 / 1,161, 128 of them 1,109 / 1,051 / 1,057 / 1,164; 16 of 60 operators, 8 micro-batches 415 / 475 / 486 / 618; 16 of
+    // 20 operators 333 / 381 / 408 / 393; but 16 of 30 operators 418 / 402 / 414 / 399, and up to 14 operators a pass is too short
+    // for it to pay: 16 of 12 237 / 215 / 215 / 216.  More of them: 160 of 82 1,120 / 1,150 / 1,107 / 1,057, 300 of them 1,429 /
+    // 1,489 / 1,434 / 1,286; 220 of 24 operators 1,033 / 818 / 736 / 650; 300 of 40 842 / 859 / 915 / 975.  Candidates, 5 / 8 / 12 / 20
+    // passes: 16 of 82 operators 647 / 689 / 725 / 853, 16 of 300 11,841 / 12,443 / 13,191 / 14,866, 64 of 60 with tight memory 416
+    // / 436 / 452 / 518 (3 passes: 607, 11,439, 397, but 16 of 12 operators 93 for 83); 256 of 82 1,311 / 1,199 / 1,132 / 1,150, 512 of
+    // them 1,523 / 1,418 / 1,330 / 1,400, 400 of 60 with tight memory 530 / 549 / 608 / 711.
+    const bool many = od.C > n_cu / 2;
+    const int passes = forced ? (many ? 12 : 5) : many ? 24 : tb.L < 16 ? 8 : 4;
+    const SweepShare sw{slots, Ws, W, passes, reinterpret_cast<long long *>(lower)};
     const long long walkers = (long long)od.C * W;
     const dim3 band_grid(unsigned(od.C < n_groups ? od.C : n_groups)), walk_grid(unsigned(walkers < n_groups ? walkers : n_groups));
     int band_threads = 0;
