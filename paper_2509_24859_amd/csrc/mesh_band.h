@@ -1314,13 +1314,14 @@ struct Band {
     }
     // All threads: how many distinct candidate caps lie in (a, b], counted up to `limit`; `last` becomes the
     // limit-th of them when there are that many.  A bitmap over a window of values in LDS (the value rows,
-    // which no pass needs meanwhile), window after window, each starting at the next value there is.
+    // which no pass needs meanwhile) no longer than the values left, window after window, each starting at the next value there is.
     __device__ __forceinline__ uint32_t count_values(uint32_t a, uint32_t b, uint32_t limit, uint32_t &last) {
         const int tid = thread_id();
-        const uint32_t words = (room / 4u) & ~63u, span = words * 32u;
+        const uint32_t most = (room / 4u) & ~63u;
         uint32_t *bits = rows;
         uint32_t found = 0, from = a + 1u;
         while (from <= b && found < limit) {
+            const uint32_t left = ((b - from) / 2048u + 1u) * 64u, words = left < most ? left : most, span = words * 32u;
             const uint32_t to = b - from < span ? b : from + (span - 1u);
             __syncthreads();
             for (uint32_t w = tid; w < words; w += nthreads) bits[w] = 0;
@@ -1345,7 +1346,7 @@ struct Band {
                 // the limit-th value: the words of the bitmap in order (rare, one wavefront)
                 __syncthreads();
                 if (tid < 64) {
-                    uint32_t left = limit - found;
+                    uint32_t rank = limit - found;
                     for (uint32_t w0 = 0; w0 < words; w0 += 64) {
                         const uint32_t v = bits[w0 + tid];
                         uint32_t inc = __popc(v);
@@ -1355,11 +1356,11 @@ struct Band {
                             if (tid >= x) inc += o;
                         }
                         const uint32_t all = __shfl(inc, 63, 64);
-                        if (left > all) { left -= all; continue; }
+                        if (rank > all) { rank -= all; continue; }
                         const uint32_t before = inc - __popc(v);
-                        if (before < left && left <= inc) {
+                        if (before < rank && rank <= inc) {
                             uint32_t rest = v;
-                            for (uint32_t n = left - before; n > 1; --n) rest &= rest - 1u;
+                            for (uint32_t n = rank - before; n > 1; --n) rest &= rest - 1u;
                             scal[7] = from + (w0 + tid) * 32u + uint32_t(__ffs((int)rest) - 1);
                         }
                         break;
