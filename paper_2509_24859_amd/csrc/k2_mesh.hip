@@ -514,8 +514,6 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     const size_t room = want > numbering ? want : numbering;
     sh.o_set_of = uint32_t(off);
     sh.total = uint32_t(off + room > budget ? off + room : budget & ~size_t(15));
-    sh.runs = (sh.W + kReachRun - 1) / kReachRun;
-    sh.runs_inv = uint32_t(0xFFFFFFFFu / uint32_t(sh.runs) + 1u);
     return sh.total <= kBandLds;
 }
 

@@ -46,7 +46,7 @@ constexpr uint32_t kNoCut = 0xFFFFu;
 constexpr uint32_t kInfSum = 0x80000000u;        // least sums stay below this (largest_cap)
 constexpr uint32_t kTopCap = 0x7FFFFFFFu;        // no time on these tables is larger
 constexpr int kRowPad = 4;                       // a window of four entries may overrun a row
-constexpr int kReachRun = 8;
+constexpr int kReachRun = 8;                     // entries of a reach table that a thread works at most
 constexpr int kTeams = 2;                        // chains worked at once
 
 // LDS layout of a launch (byte offsets into dynamic LDS) and its capacities.
@@ -59,8 +59,6 @@ struct BandShape {
     int idx_pitch;               // feasibility index
     uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_mem, o_chain, o_ok, o_col, o_small, o_prow,
         o_set_of, total;
-    int runs;                    // of kReachRun entries in a row of time sums or reaches
-    uint32_t runs_inv;           // x / runs is the high half of x * runs_inv for x below 2^32 / runs (runs above 1)
 };
 
 constexpr int kMaxDevices = 2048;                // columns sit in LDS, 24 bytes each
@@ -172,6 +170,8 @@ struct Band {
     int nthreads, wave;
     int K, S, D, L, n_sets;
     int least_cut;               // the cut behind the operator of least output (operators but the last)
+    int run_len, runs;           // entries of a reach table that a thread works, such runs in a row of it
+    uint32_t runs_inv;           // x / runs is the high half of x * runs_inv for x below 2^32 / runs (runs above 1)
     bool keys_fit;               // sums times a degree fit 32 bits under the cap of the next pass for the least sum
     int64_t count_cap;           // the cap H-1F1B's counts are worked out with: the pass's own, or above any time
 
@@ -208,6 +208,8 @@ struct Band {
         K = S = D = n_sets = 0;
         pitch = most_cells = map_shift = 0;
         reached = false;
+        run_len = runs = 1;
+        runs_inv = 0;
         keys_fit = true;
         ranges_in_lds = chains_in_lds = whole = false;
         all_cells = 0;
@@ -320,6 +322,10 @@ struct Band {
         n_sets = uniform(n_sets);
         if (n_sets > sh.set_cap) return 3;
         find_room(n_sets);
+        run_len = (n_sets * tb.n_tp * sh.W + nthreads - 1) / nthreads;
+        run_len = uniform(run_len < kReachRun ? run_len : kReachRun);
+        runs = (sh.W + run_len - 1) / run_len;
+        runs_inv = uint32_t(uniform(int(0xFFFFFFFFu / uint32_t(runs) + 1u)));
         map_shift = 0;
         while (map_shift < 3 && (D << (map_shift + 1)) <= nthreads) ++map_shift;
         for (int k = 0, set = 0; k < K; ++k) {
@@ -379,15 +385,17 @@ struct Band {
     }
     // All threads: how far a stage gets under t on every (set, degree), into table `side`.  Upwards: entry j = the
     // highest cut i with time(j, i) <= t; downwards: entry i = the lowest cut j with time(j, i) <= t.  Neither falls from
-    // one entry to the next, so a thread finds the first of a run of kReachRun entries by bisection and goes on from there:
+    // one entry to the next, so a thread finds the first of a run of entries by bisection and goes on from there:
     // a cut or so per entry, where a bisection each takes seven or eight steps (4,096 orderings of 82 operators and 64
-    // devices: of an ordering's 145 us the tables took 31, now 19).
+    // devices: of an ordering's 145 us the tables took 31, now 19).  Runs are as long as the workgroup's threads leave entries
+    // to each, up to kReachRun: a run is a chain of LDS reads, and with runs of eight for 104 entries (12 operators) the
+    // tables of a cap took 5 us, 1.5 with one entry a thread.
     template <bool kUp>
     __device__ __forceinline__ void reach_table(uint32_t t, int side) {
         uint16_t *to = reach + side * n_sets * tb.n_tp * sh.W;
         const int top_step = 1 << (31 - __clz(L));
-        for (int x = thread_id(); x < n_sets * tb.n_tp * sh.runs; x += nthreads) {
-            const int r = sh.runs == 1 ? x : int(__umulhi(uint32_t(x), sh.runs_inv)), e0 = (x - r * sh.runs) * kReachRun, end = e0 + kReachRun < sh.W ? e0 + kReachRun : sh.W;
+        for (int x = thread_id(); x < n_sets * tb.n_tp * runs; x += nthreads) {
+            const int r = runs == 1 ? x : int(__umulhi(uint32_t(x), runs_inv)), e0 = (x - r * runs) * run_len, end = e0 + run_len < sh.W ? e0 + run_len : sh.W;
             const uint64_t far = uint64_t(t) * uint32_t(tb.tp[r % tb.n_tp]);
             const uint32_t reach_of = far > 0xFFFFFFFFull ? 0xFFFFFFFFu : uint32_t(far);
             const uint32_t *p = prow + r * sh.W;

@@ -108,6 +108,20 @@ def test_band_rows_in_every_form(harp, ctx, case, copies):
         assert (getattr(exact, field).reshape(copies, 4, -1) == getattr(wide, field).reshape(1, 4, -1)).all(), field
 
 
+RUN_LENGTHS = [  # as above: entries of a reach table that a thread works, between one and eight, and a row's last run cut short
+    (255, (5, 4), (1, 2, 4), 4, False),
+    (511, (8, 8), (1, 2, 4, 8), 5, True),
+    (1000, (8, 9), (1, 2, 4, 8), 4, False),
+]
+
+
+@pytest.mark.parametrize("case", RUN_LENGTHS, ids=lambda c: "L%d_q%d" % (c[0], len(c[2])))
+@pytest.mark.parametrize("copies", [1, 80, 300])
+def test_reach_tables_by_runs(harp, ctx, case, copies):
+    """Workgroups of every size over tables of one to several entries a thread."""
+    test_band_rows_in_every_form(harp, ctx, case, copies)
+
+
 @pytest.mark.parametrize("seed,L,ndev,tp,M", [(1, 33, (3, 4), (1, 2, 4), 9), (2, 64, (4, 4, 2), (1, 2), 5),
                                               (3, 70, (2, 2, 2), (1, 2), 40), (4, 20, (8,), (1, 2, 4, 8), 12)],
                          ids=lambda x: str(x).replace(" ", ""))
