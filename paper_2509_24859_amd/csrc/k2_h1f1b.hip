@@ -494,18 +494,23 @@ void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_
     const uint16_t *hi_tab = w.lo_tab + (long long)lo_n_max(tb.L, cd.S_max, tb.M) * tb.T * tb.n_tp * idx_pitch;
     const size_t per_group = fast_arg_per_group(tb.L, cd.S_max);
     const int arg_pitch = fast_row_len(tb.L);
-    // Wavefronts per CU of the first launch and the row entries their LDS share leaves: as many
-    // wavefronts as hold rows for the whole sequence, between 14 and 24 (six per SIMD, held to 80 registers with 5 of
+    // Wavefronts per CU of the first launch and the row entries their LDS share leaves.  LDS is allocated in units, so a share
+    // is as many units as hold rows for the sequence, up to one cut in forty that hardly any slot needs, and there are as
+    // many wavefronts as such shares fit, between 14 and 24 (six per SIMD, held to 80 registers with 5 of
     // them spilled; fewer hide less of the latency: 160 operators, five per SIMD 1.61 ms, six 1.47, seven 1.54 with
-    // more spills).  Shares are whole units of allocation: 28 bytes beyond nine of them leave room for 12 wavefronts
-    // instead of 14 (512 operators, tight memory 2.01 ms for 1.87).  The smaller the share, the more candidates leave for the second launch: 300 operators, 14 per
-    // CU 3.7 ms, 17 3.7, 20 4.9; 512 operators, tight memory 1.90, 1.88, 1.92, loose memory 14.1 for all.
-    const size_t small = h1f1b_small_bytes(cd.S_max);
-    int per_cu = int((size_t(160) << 10) / (small + size_t(row_len) * h1f1b_cut_bytes(8) + 128));
-    per_cu = per_cu < 14 ? 14 : (per_cu > 24 ? 24 : per_cu);
-    const size_t share = (size_t(160) << 10) / per_cu / kLdsGranule * kLdsGranule;
-    int entries = share > small + h1f1b_cut_bytes(8) * 16 ? int((share - small) / h1f1b_cut_bytes(8)) & ~1 : 16;
-    if (entries > row_len) entries = row_len;
+    // more spills).  The smaller the share, the more candidates leave for the second launch: 300 operators, 14 per
+    // CU 3.7 ms, 17 3.7, 20 4.9; 512 operators, tight memory 1.90, 1.88, 1.92, loose memory 14.1 for all.  Counted in bytes, a number of
+    // wavefronts left part of a unit to each and rows that just do not fit: 20,000 candidates of up to 32 stages, us by
+    // bytes / by units: 200 operators 759 / 669, 230 792 / 781, 245 897 / 848, 280 921 / 901, 330 1,145 / 1,107.
+    const size_t small = h1f1b_small_bytes(cd.S_max), units = (size_t(160) << 10) / kLdsGranule;
+    auto held = [&](size_t n) -> int {
+        const size_t share = n * kLdsGranule;
+        return share > small + h1f1b_cut_bytes(8) * 16 ? int((share - small) / h1f1b_cut_bytes(8)) & ~1 : 16;
+    };
+    size_t n_units = units / 24;
+    while (n_units < units / 14 && held(n_units) < (tb.L + 1) - (tb.L + 1) / 40) ++n_units;
+    const int per_cu = units / n_units < 24 ? int(units / n_units) : 24;
+    const int entries = held(n_units) < row_len ? held(n_units) : row_len;
     int n_waves = per_cu * n_cu;
     if (n_waves > n_slices) n_waves = n_slices;
     if (n_waves > cd.C) n_waves = cd.C;

@@ -176,6 +176,23 @@ def test_h1f1b_wide_bands_ties_and_degenerate(harp, ctx):
     assert got.status.shape == (0,)
 
 
+@pytest.mark.parametrize("L", [186, 190, 191, 192, 232, 237, 238, 280, 285, 325, 331, 377, 378])
+def test_h1f1b_rows_about_as_long_as_a_share(harp, ctx, L):
+    """Loose memory, so slots span most of the sequence: shares of LDS that hold all of a row, all but a few cuts of it
+    (those slots go to the second launch), and the next larger one."""
+    rng = np.random.default_rng(L)
+    G, T = 2, 2
+    fwd = rng.integers(1, 3000, size=(T, L))
+    p = simple_problem(np.zeros(L), M=12, T=T, G=G, ndev=[16] * G, tp=(1, 2), fwd=fwd, bwd=fwd,
+                       params=rng.integers(1, 10**6, size=L), stash=rng.integers(0, 10**4, size=L),
+                       act=rng.integers(0, 10**6, size=L), gtype=[0, 1], mem=[1 << 50, 1 << 50],
+                       bw=np.array([[4000, 30], [30, 3000]]))
+    cands = W.make_candidates(p, 0, 281, G, 4, 0, 12)
+    caps, _ = _caps_from_min_max(p, cands, 9, 8)
+    got, want, _ = _check(harp, ctx, p, cands, caps, "L %d" % L)
+    assert (want.status == oracle.OK).any()
+
+
 def test_h1f1b_counts_decide_feasibility(harp, ctx):
     # three one-operator stages, stash 10 each, slow link then fast link: counts 5, 2, 1
     for mem, st in ((50, oracle.OK), (49, oracle.INFEASIBLE)):
