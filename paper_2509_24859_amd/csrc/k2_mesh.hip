@@ -506,11 +506,10 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     sh.set_cap = int(sets < size_t(sh.K_cap) ? sets : size_t(sh.K_cap));
     sh.o_use = take(size_t(sh.set_cap) * 4);
     sh.o_prow = take(16 + size_t(sh.set_cap) * per_set);
-    // bytes per cell: two value rows; or one and the key rows; or two rows of sums and counts; and the map
-    sh.value_rows = sums && tb.n_tp > 1 ? 1 + tb.n_tp : 2;
-    sh.cell_bytes = sh.value_rows * 4 + (h1 ? 4 : 0) + 2;
-    // the rest of the budget holds rows (place_rows), at least 1,024 cells of them and the numbering of an ordering's sets
-    const size_t want = 1024 * size_t(sh.cell_bytes) + 256, numbering = size_t(sh.K_cap) * 2;
+    // the rest of the budget holds rows (Band::place_rows), at least 1,024 cells in the widest form of a pass - two rows of
+    // values, or one and the key rows, counts, the map - and the numbering of an ordering's sets
+    const size_t value_rows = sums && tb.n_tp > 1 ? size_t(1 + tb.n_tp) : 2, cell = value_rows * 4 + (h1 ? 4 : 0) + 2;
+    const size_t want = 1024 * cell + 256, numbering = size_t(sh.K_cap) * 2;
     const size_t room = want > numbering ? want : numbering;
     sh.o_set_of = uint32_t(off);
     sh.total = uint32_t(off + room > budget ? off + room : budget & ~size_t(15));

@@ -54,7 +54,6 @@ struct BandShape {
     int W, NW;                   // cuts (L + 1), 64-bit words of a mask of cuts
     int cols;                    // columns: devices + 1
     int K_cap, set_cap;          // groups of an ordering, sets of time rows
-    int value_rows, cell_bytes;  // rows of 32-bit words a pass keeps in LDS, bytes per cell with counts and map
     int S_cap;                   // min(S_max, L)
     int idx_pitch;               // feasibility index
     uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_mem, o_chain, o_ok, o_col, o_small, o_prow,
