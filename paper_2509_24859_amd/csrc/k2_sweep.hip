@@ -541,7 +541,7 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 //  * How many values the sweep passes from t_S to t_E, or to the first cap with a plan where that is higher
 //    (n_caps, max_caps), is counted without trying them.
 // Measured on 48 orderings of 82 operators and 64 devices (about 1,000 values each between t_S and t_E, all
-// of them tried before, by up to 32 workgroups per ordering): 125-150 -> 0.6-0.8 ms per call, some 10 passes
+// of them tried before, by up to 32 workgroups per ordering): 125-150 -> 0.7-1.1 ms per call over ten draws, some 10 passes
 // per ordering, bound by the latency of one workgroup's passes one after the other (vector issue 6% of the rate of
 // the 48 CUs at work).
 //  * The bounds are weak where tight memory keeps the H-1F1B sums above the classic ones and there are few
@@ -554,9 +554,9 @@ __global__ __launch_bounds__(256) void k2_mesh_sweep_pick(TablesDev tb, OrdDev o
 // state and can miss plans that exist), from where it stands.
 // Candidates (k2_sweep_slots) are searched in the same way, on the passes of slot_passes.h.  Those also say up to
 // which cap they come out the same, so that the climb and the tries pass over the values below it: climbs
-// that took up to 20,000 passes take 1 to 3.  64 candidates of 82 operators, 8 to 16 stages on 8 groups of 8
-// devices (about 2,000 values each from t_S on, 29,000 at most): 146 ms, every value tried, -> 0.8-1.5 ms, of late 1.2
-// where that was 1.4 (the least-count passes on a wavefront each, the rest left to the second launch sooner).
+// that took up to 20,000 passes take 1 to 3 as a rule.  64 candidates of 82 operators, 8 to 16 stages on 8 groups of 8
+// devices (about 2,000 values each from t_S on, 29,000 at most): 146 ms, every value tried, -> 0.8-1.0 ms on seven of nine
+// draws, 1.7 where one candidate climbs over 32 values, 46 where one fails at kMaxClimb and is handed over.
 
 // The rest of an ordering's search: its slots as for the kernels above (the opening's head holds the best plan so
 // far and, in rest, the range of caps left: above the first, up to the second), the least total found per ordering
