@@ -493,9 +493,11 @@ bool meshband::band_shape(const TablesDev &tb, int S_max, int G_max, int64_t tot
     sh.o_group_at = take(size_t(sh.cols) * 2);
     const bool sums = form == kFormSum || form == kFormSweep, h1 = form == kFormH1 || form == kFormSweep;
     sh.o_mem = take(h1 ? size_t(sh.W) * 16 : 0);
-    sh.o_chain = take(size_t(kTeams) * 2 * (sh.cols + 1) * 2);
     sh.o_ok = take(size_t(kTeams) * 2 * sh.K_cap * sh.NW * 8);
-    sh.o_col = take(size_t(sh.cols) * 24);
+    // (the chains of a cap are over before its first pass loads columns; with LDS of their own, large problems at the edge of what
+    // fits went to the whole-table form: 32 orderings of 170 operators, 16 groups of 32 devices, a type each 55 -> 1.3 ms)
+    const size_t chains = size_t(kTeams) * 2 * (sh.cols + 1) * 2, columns = size_t(sh.cols) * 24;
+    sh.o_col = take(chains > columns ? chains : columns);
     sh.o_small = take(32 + size_t(sh.S_cap + 1) * 12 + size_t(sh.S_cap) * 11);
     // time rows: of every group when they fit half the budget, else of as many sets as do, at least one per type
     // (a set: its time rows and its two reach tables)

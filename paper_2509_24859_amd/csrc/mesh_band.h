@@ -56,7 +56,7 @@ struct BandShape {
     int K_cap, set_cap;          // groups of an ordering, sets of time rows
     int S_cap;                   // min(S_max, L)
     int idx_pitch;               // feasibility index
-    uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_mem, o_chain, o_ok, o_col, o_small, o_prow,
+    uint32_t o_offs, o_order, o_type, o_row_at, o_group_at, o_cut_at, o_use, o_mem, o_ok, o_col, o_small, o_prow,
         o_set_of, total;
 };
 
@@ -139,7 +139,7 @@ struct Band {
     uint32_t *prow;              // [sets][n_tp][W]
     uint16_t *reach;             // [2][sets][n_tp][W] reach of a stage under a cap
     int64_t *mem;                // PP [W], PS [W] (H-1F1B form)
-    uint16_t *chain;             // [kTeams][2][cols + 1]
+    uint16_t *chain;             // [kTeams][2][cols + 1], where the columns of the passes go
     unsigned long long *ok;      // [kTeams][2 K][NW]
     uint2 *col;                  // [2][cols] lowest and highest cut of a column | index of its first cell less its lowest cut
     uint32_t *col_min;           // [2][cols] least value of a column (min-max form)
@@ -189,7 +189,7 @@ struct Band {
         prow = reinterpret_cast<uint32_t *>(lds + sh.o_prow);
         set_of = reinterpret_cast<uint16_t *>(lds + sh.o_set_of);
         mem = reinterpret_cast<int64_t *>(lds + sh.o_mem);
-        chain = reinterpret_cast<uint16_t *>(lds + sh.o_chain);
+        chain = reinterpret_cast<uint16_t *>(lds + sh.o_col);
         ok = reinterpret_cast<unsigned long long *>(lds + sh.o_ok);
         col = reinterpret_cast<uint2 *>(lds + sh.o_col);
         col_min = reinterpret_cast<uint32_t *>(col + 2 * sh.cols);

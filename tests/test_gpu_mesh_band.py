@@ -108,6 +108,32 @@ def test_band_rows_in_every_form(harp, ctx, case, copies):
         assert (getattr(exact, field).reshape(copies, 4, -1) == getattr(wide, field).reshape(1, 4, -1)).all(), field
 
 
+@pytest.mark.parametrize("L", [134, 136, 137, 142, 144, 145, 160, 162, 163, 169, 171, 172])
+def test_layouts_that_just_fit(harp, ctx, L):
+    """512 devices in 16 groups of a type each, six degrees: LDS layouts from some room to spare to none at all, in each of the
+    band kernels' forms (up to 136 the search over the cap, to 144 the exact form, to 162 H-1F1B's, to 171 min-max), against the int64
+    kernels."""
+    G, S_max = 16, 24
+    rng = np.random.default_rng(L)
+    p = simple_problem(np.zeros(L), M=6, T=G, G=G, ndev=[32] * G, tp=(1, 2, 4, 8, 16, 32), gtype=list(range(G)),
+                       fwd=rng.integers(1, 30, size=(G, L)), bwd=rng.integers(1, 30, size=(G, L)), act=rng.integers(10, 300, size=L),
+                       params=rng.integers(0, 40, size=L), stash=rng.integers(0, 10, size=L), bw=rng.integers(20, 60, size=(G, G)),
+                       mem=[200 * L] * G)
+    orders = W.orderings_from_lists([(S, order) for S in (17, S_max) for order in (list(range(G)), list(range(G))[::-1])], S_max=S_max)
+    assert harp.Tables(ctx, p).fast32
+    fields = ("splits", "dev_first", "bottleneck", "iter_time", "status", "stage_group", "stage_tp")
+    want, _ = harp.plan_mesh(ctx, p, orders, False, harp.PATH_GENERIC)
+    assert (want.status == oracle.OK).any()
+    caps = np.where(want.status == oracle.OK, want.bottleneck + np.arange(orders.C) * want.bottleneck // 7, -1)
+    for run, more in ((lambda path: harp.plan_mesh(ctx, p, orders, False, path)[0], ()),
+                      (lambda path: harp.plan_mesh(ctx, p, orders, True, path)[0], ("n_passes",)),
+                      (lambda path: harp.plan_mesh_h1f1b(ctx, p, orders, caps, path)[0], ("warmup",)),
+                      (lambda path: harp.plan_mesh_h1f1b_sweep(ctx, p, orders, path=path)[0], ("warmup", "t_max", "n_caps"))):
+        fast, wide = run(harp.PATH_FAST32), run(harp.PATH_GENERIC)
+        for field in fields + more:
+            assert (getattr(fast, field) == getattr(wide, field)).all(), field
+
+
 RUN_LENGTHS = [  # as above: entries of a reach table that a thread works, between one and eight, and a row's last run cut short
     (255, (5, 4), (1, 2, 4), 4, False),
     (511, (8, 8), (1, 2, 4, 8), 5, True),
