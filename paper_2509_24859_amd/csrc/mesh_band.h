@@ -14,19 +14,20 @@
 // outside the range are on no plan under t.  Leaving them out changes no cell on such a plan: its
 // value, and the lowest previous cut that attains it, come from cells on plans under t as well.
 // For the capped (least-sum) and H-1F1B passes t is the cap (H-1F1B's counts are never below the
-// classic ones the ranges are worked out with).  For the min-max pass any t >= the optimum will do:
-// the smallest t at which F reaches (S, L, all devices) is found by a search over chains first.  A
+// classic ones the ranges are worked out with).  For the min-max pass any t >= the optimum will do: a
+// guess from the groups' speeds (guess), and where F does not reach (S, L, all devices) under it, a t little
+// above the smallest at which it does, found by a search over chains (bracket).  A
 // chain can leave a stage without operators, so where some device's memory holds no operator alone the
 // pass may find no plan under that t; it is then repeated under a higher one, and at last
 // without a cap on the times.  On orderings of 82 operators and 64 devices the ranges hold between
 // 0.1% and 25% of the (i, d) cells, the wide ones where a slow link decides the bottleneck.
 //
-// A chain is worked by one wavefront, lanes over the columns d, so several values of t are tried at
-// once by the wavefronts of a workgroup.  A pass keeps two value rows in LDS (cells of a row packed
-// one column after the other), writes every row to the workgroup's slice of the workspace, and keeps
-// no back-pointers: the plan is found from the value rows, per stage one step for all degrees and
-// cuts at once.  That leaves a minimum per transition (a subtraction, a shift, a three-way maximum)
-// where back-pointers cost a 64-bit key.  Rows of the fused stage times sit in LDS, one set per
+// Two chains are worked at once, F and B of one t or F of two, a lane per column d and a wavefront per 64 of
+// them.  A pass keeps its value rows in LDS (cells of a row packed one column after the other), all of
+// them where they fit, else the last two with every row written to the workgroup's slice of the workspace,
+// and where not even two fit it works from the slice.  Only the H-1F1B pass keeps back-pointers: the plans of the
+// others are found from the value rows, per stage one step for all degrees and cuts at once.  That leaves a minimum
+// per transition (a subtraction, a shift, a three-way maximum) where back-pointers cost a 64-bit key.  Rows of the fused stage times sit in LDS, one set per
 // distinct (GPU type, own link) of the ordering; memory limits come from the feasibility index
 // (k2_index), one 16-bit load per cell and degree.
 #pragma once
@@ -164,6 +165,7 @@ struct Band {
     bool chains_in_lds;
     int all_cells;               // of all rows of the last prepared cap
     bool reached;                // the last prepared cap: its chains get from end to end
+    bool unlikely;               // no plan is expected under the first cap: the next pass is taken for one that found none
     int most_cells;              // of a row of the last prepared cap
     int map_shift;               // load_columns
     int nthreads, wave;
@@ -206,7 +208,7 @@ struct Band {
         L = tb.L;
         K = S = D = n_sets = 0;
         pitch = most_cells = map_shift = 0;
-        reached = false;
+        reached = unlikely = false;
         run_len = runs = 1;
         runs_inv = 0;
         keys_fit = true;
@@ -984,9 +986,14 @@ struct Band {
 
     // All threads: the first cap to try the min-max pass under.  Every group takes work in proportion to its speed; and
     // every plan cuts somewhere on every link from a group to the next, no cheaper than at the operator of least output.
-    // The optimum lies there on half of the orderings looked at: the ranges under this cap are worked out at once, and
+    // Where a link decides, the optimum mostly lies there: the ranges under this cap are worked out at once, and
     // only where they do not meet is a higher one looked for (82 operators and 64 devices: two reach tables and one
-    // round of chains where a search in front of the ranges takes four and two).
+    // round of chains where a search in front of the ranges takes four and two).  Where the speeds decide, no plan spreads the
+    // work that evenly, and with hardly more operators than stages the dear cuts cannot be avoided: there the search
+    // comes first, and a round of chains that fails is spared.  us with it tried at once / with the search first:
+    // 4,096 orderings of 82 operators 725 / 714; the search over the cap, one degree, 18 of 29 operators and 25 stages 615 / 593, 5 of
+    // 43 and 36 stages 774 / 742, 16 of 29 and 4 stages 142 / 137; but 10 of 19 operators and up to 11 stages 196 / 221, so the
+    // line lies above three stages to four operators.
     __device__ __forceinline__ uint32_t guess() {
         const int lane = thread_id() & 63;
         if (wave == 0) {
@@ -1011,6 +1018,7 @@ struct Band {
         }
         __syncthreads();
         const uint32_t g = scal[5] > scal[6] ? scal[5] : scal[6];
+        unlikely = (scal[5] > scal[6] || 4 * S > 3 * L) && g < kTopCap;
         return g < kTopCap ? g : kTopCap;
     }
     // All threads: the next cap to try when the ranges under the first, g, did not meet; -1 when no plan exists under any.
@@ -1168,6 +1176,7 @@ struct Band {
     static constexpr int kMinMax = 1, kSum = 2, kH1 = 4, kAny = 8;
     template <int kForms>
     __device__ __forceinline__ int64_t run(int form, uint32_t t) {
+        if (unlikely) { unlikely = reached = false; return kInf; }
         if (!prepare(t)) return kInf;
         if ((kForms & (kMinMax | kSum)) && (form == kMinMax || form == kSum)) {
             const bool values_fit = most_cells <= cells_that_fit(kValueBytes);

@@ -134,6 +134,46 @@ def test_layouts_that_just_fit(harp, ctx, L):
             assert (getattr(fast, field) == getattr(wide, field)).all(), field
 
 
+FIRST_CAPS = [  # L, devices per group, degrees, stages, slow link: which of them decides, and stages to operators about 3 to 4
+    (30, (14, 14), (1,), 28, False),
+    (30, (14, 14), (1,), 28, True),
+    (32, (14, 14), (1, 2), 24, True),
+    (32, (14, 14), (1, 2), 25, True),
+    (90, (8, 9), (1, 2, 4), 9, False),
+    (90, (8, 9), (1, 2, 4), 9, True),
+]
+
+
+@pytest.mark.parametrize("case", FIRST_CAPS, ids=lambda c: "L%d_S%d_%s" % (c[0], c[3], "link" if c[4] else "speeds"))
+def test_first_caps(harp, ctx, case):
+    """Orderings whose first cap is tried at once and ones that search first, against the int64 kernels."""
+    L, ndev, tp, S, slow = case
+    p = _problem(3 * L + S, L, ndev, tp, slow)
+    orders = W.orderings_from_lists([(s, order) for s in (S, S - 1) for order in ([0, 1], [1, 0])] * 80, S_max=S)
+    for run, more in ((lambda path: harp.plan_mesh(ctx, p, orders, False, path)[0], ()),
+                      (lambda path: harp.plan_mesh(ctx, p, orders, True, path)[0], ("n_passes",)),
+                      (lambda path: harp.plan_mesh_h1f1b_sweep(ctx, p, orders.slice(0, 4), path=path)[0], ("warmup", "t_max", "n_caps"))):
+        fast, wide = run(harp.PATH_FAST32), run(harp.PATH_GENERIC)
+        assert (wide.status == oracle.OK).any()
+        for field in ("splits", "dev_first", "bottleneck", "iter_time", "status", "stage_group", "stage_tp") + more:
+            assert (getattr(fast, field) == getattr(wide, field)).all(), field
+
+
+def test_a_first_cap_above_which_there_is_none(harp, ctx):
+    """The cheapest cut of the only link takes 2^31 - 1 us: the first cap is the largest there is."""
+    L = 90
+    p = _problem(7, L, (8, 9), (1, 2, 4))
+    p.act_bytes[:] = 2 ** 31 - 1
+    p.bw[0, 1] = p.bw[1, 0] = 1
+    p.bw[0, 0] = p.bw[1, 1] = 2 ** 31
+    assert harp.Tables(ctx, p).fast32
+    orders = W.orderings_from_lists([(s, order) for s in (5, 9) for order in ([0, 1], [1, 0])], S_max=9)
+    want = oracle_plan_mesh_threaded(oracle.build_tables(p), orders)
+    assert (want.status == oracle.OK).all() and (want.bottleneck == 2 ** 31 - 1).all()
+    got, _ = harp.plan_mesh(ctx, p, orders, False, harp.PATH_FAST32)
+    assert_plans_equal(got, want, "min-max")
+
+
 RUN_LENGTHS = [  # as above: entries of a reach table that a thread works, between one and eight, and a row's last run cut short
     (255, (5, 4), (1, 2, 4), 4, False),
     (511, (8, 8), (1, 2, 4, 8), 5, True),
