@@ -989,11 +989,9 @@ struct Band {
     // Where a link decides, the optimum mostly lies there: the ranges under this cap are worked out at once, and
     // only where they do not meet is a higher one looked for (82 operators and 64 devices: two reach tables and one
     // round of chains where a search in front of the ranges takes four and two).  Where the speeds decide, no plan spreads the
-    // work that evenly, and with hardly more operators than stages the dear cuts cannot be avoided: there the search
-    // comes first, and a round of chains that fails is spared.  us with it tried at once / with the search first:
-    // 4,096 orderings of 82 operators 725 / 714; the search over the cap, one degree, 18 of 29 operators and 25 stages 615 / 593, 5 of
-    // 43 and 36 stages 774 / 742, 16 of 29 and 4 stages 142 / 137; but 10 of 19 operators and up to 11 stages 196 / 221, so the
-    // line lies above three stages to four operators.
+    // work that evenly: there the search comes first, and a round of chains that fails is spared (us with it tried at once /
+    // with the search first: 4,096 orderings of 82 operators 725 / 714; search over the cap, 16 of 29 operators and 4 stages 142 /
+    // 137).
     __device__ __forceinline__ uint32_t guess() {
         const int lane = thread_id() & 63;
         if (wave == 0) {
@@ -1018,7 +1016,7 @@ struct Band {
         }
         __syncthreads();
         const uint32_t g = scal[5] > scal[6] ? scal[5] : scal[6];
-        unlikely = (scal[5] > scal[6] || 4 * S > 3 * L) && g < kTopCap;
+        unlikely = scal[5] > scal[6] && g < kTopCap;
         return g < kTopCap ? g : kTopCap;
     }
     // All threads: the next cap to try when the ranges under the first, g, did not meet; -1 when no plan exists under any.

@@ -134,7 +134,7 @@ def test_layouts_that_just_fit(harp, ctx, L):
             assert (getattr(fast, field) == getattr(wide, field)).all(), field
 
 
-FIRST_CAPS = [  # L, devices per group, degrees, stages, slow link: which of them decides, and stages to operators about 3 to 4
+FIRST_CAPS = [  # L, devices per group, degrees, stages, slow link: which of them decides, few and many stages
     (30, (14, 14), (1,), 28, False),
     (30, (14, 14), (1,), 28, True),
     (32, (14, 14), (1, 2), 24, True),
