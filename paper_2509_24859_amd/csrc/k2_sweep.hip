@@ -892,18 +892,19 @@ hipError_t launch_plan_mesh_h1f1b_sweep(const TablesDev &tb, const OrdDev &od, c
     ba.per_group = per_group;
     ba.counters = w.counters;
     ba.redo = w.redo;
-    // Passes (least sums and values tried) after which the first launch leaves the rest of a search to the second.  Where orderings or
-    // candidates outnumber half of the compute units, the second launch takes the place of work in the first and
-    // repeats some of it.  Orderings, us with 4 / 6 / 8 / 24 passes (means over three to five batches): 48 of 82 operators 912 / 956
-    // / 973 / 1,161, 128 of them 1,109 / 1,051 / 1,057 / 1,164; 16 of 60 operators, 8 micro-batches 415 / 475 / 486 / 618; 16 of
-    // 20 operators 333 / 381 / 408 / 393; but 16 of 30 operators 418 / 402 / 414 / 399, and up to 14 operators a pass is too short
-    // for it to pay: 16 of 12 237 / 215 / 215 / 216.  More of them: 160 of 82 1,120 / 1,150 / 1,107 / 1,057, 300 of them 1,429 /
-    // 1,489 / 1,434 / 1,286; 220 of 24 operators 1,033 / 818 / 736 / 650; 300 of 40 842 / 859 / 915 / 975.  Candidates, 5 / 8 / 12 / 20
-    // passes: 16 of 82 operators 647 / 689 / 725 / 853, 16 of 300 11,841 / 12,443 / 13,191 / 14,866, 64 of 60 with tight memory 416
-    // / 436 / 452 / 518 (3 passes: 607, 11,439, 397, but 16 of 12 operators 93 for 83); 256 of 82 1,311 / 1,199 / 1,132 / 1,150, 512 of
-    // them 1,523 / 1,418 / 1,330 / 1,400, 400 of 60 with tight memory 530 / 549 / 608 / 711.
-    const bool many = od.C > n_cu / 2;
-    const int passes = forced ? (many ? 12 : 5) : many ? 24 : tb.L < 16 ? 8 : 4;
+    // Passes (least sums and values tried) after which the first launch leaves the rest of a search to the second.  A pass is 20 to 80 us
+    // on one CU, the second launch some 100 us whatever is left, so a search that is not over after a few passes is better
+    // left; where there are more of them than half of the compute units, it takes the place of work in the first and repeats
+    // some of it.  Orderings, mean time by the passes, that of 4 being 1: up to 128 of 82 operators 6 passes 1.04, 8 1.11, 12 1.22
+    // (28 batches), of 12 to 82 operators 6 1.02, 8 1.04, 24 1.13 (90 batches); 130 to 400 of 82 operators 6 0.96, 8 1.05, 12 1.27, 24 1.98
+    // (18 batches: 256 of them 1,264 / 1,144 / 1,260 / 1,531 / 2,483 us), of 15 to 81 operators 0.98, 0.99, 1.00, 1.07 (36 batches); but
+    // a pass is as long as its stages, and 300 of 43 operators and 39 stages take 1,717 us with 4, 1,907 with 6.  Up to 14
+    // operators a pass is too short for a second launch to pay early: 16 of 12 operators 237 us with 4, 215 with 8.  Candidates:
+    // 5 / 8 / 12 / 20 passes, 16 of 82 operators 647 / 689 / 725 / 853 us, 16 of 300 11,841 / 12,443 / 13,191 / 14,866, 64 of 60 with
+    // tight memory 416 / 436 / 452 / 518 (3 passes: 607, 11,439, 397, but 16 of 12 operators 93 for 83).  More than compute units: 400 of
+    // 28 operators 452 with 8, 418 with 20, 400 of 15 operators 155 and 132, 600 of 82 4,927 with 5, 4,706 with 20; over 36 batches of
+    // 130 to 600 the means of all four lie within 2%.
+    const int passes = forced ? (od.C > n_cu ? 20 : 5) : tb.L < 16 ? 8 : od.C > n_cu / 2 && od.S_max <= 24 ? 6 : 4;
     const SweepShare sw{slots, Ws, W, passes, reinterpret_cast<long long *>(lower)};
     const long long walkers = (long long)od.C * W;
     const dim3 band_grid(unsigned(od.C < n_groups ? od.C : n_groups)), walk_grid(unsigned(walkers < n_groups ? walkers : n_groups));
