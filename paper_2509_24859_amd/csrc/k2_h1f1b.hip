@@ -495,20 +495,23 @@ void launch_plan_h1f1b(const TablesDev &tb, const CandDev &cd, const int64_t *t_
     const size_t per_group = fast_arg_per_group(tb.L, cd.S_max);
     const int arg_pitch = fast_row_len(tb.L);
     // Wavefronts per CU of the first launch and the row entries their LDS share leaves.  LDS is allocated in units, so a share
-    // is as many units as hold rows for the sequence, up to one cut in forty that hardly any slot needs, and there are as
-    // many wavefronts as such shares fit, between 14 and 24 (six per SIMD, held to 80 registers with 5 of
-    // them spilled; fewer hide less of the latency: 160 operators, five per SIMD 1.61 ms, six 1.47, seven 1.54 with
+    // is as many units as hold the widest slot of a candidate with a stage on every group (S stages: L - S + 2 cuts), or rows for
+    // the sequence up to one cut in forty that hardly any slot needs, and there are as many wavefronts as such shares fit, between
+    // 14 and 24 (six per SIMD, held to 80 registers with 5 of them spilled; fewer hide less of the latency: 160 operators, five per SIMD 1.61 ms, six 1.47, seven 1.54 with
     // more spills).  The smaller the share, the more candidates leave for the second launch: 300 operators, 14 per
     // CU 3.7 ms, 17 3.7, 20 4.9; 512 operators, tight memory 1.90, 1.88, 1.92, loose memory 14.1 for all.  Counted in bytes, a number of
     // wavefronts left part of a unit to each and rows that just do not fit: 20,000 candidates of up to 32 stages, us by
-    // bytes / by units: 200 operators 759 / 669, 230 792 / 781, 245 897 / 848, 280 921 / 901, 330 1,145 / 1,107.
+    // bytes / by units: 200 operators 759 / 669, 230 792 / 781, 245 897 / 848, 280 921 / 901, 330 1,145 / 1,107.  Rows
+    // for the whole sequence where candidates have a stage on each of many groups take more than their slots need: 278 operators on 32
+    // groups, 12,000 candidates 727 -> 694 with shares for the widest slot, 209 on 30, 42,385 candidates 1,767 -> 1,641.
     const size_t small = h1f1b_small_bytes(cd.S_max), units = (size_t(160) << 10) / kLdsGranule;
     auto held = [&](size_t n) -> int {
         const size_t share = n * kLdsGranule;
         return share > small + h1f1b_cut_bytes(8) * 16 ? int((share - small) / h1f1b_cut_bytes(8)) & ~1 : 16;
     };
     size_t n_units = units / 24;
-    while (n_units < units / 14 && held(n_units) < (tb.L + 1) - (tb.L + 1) / 40) ++n_units;
+    const int stages = tb.G < cd.S_max ? tb.G : cd.S_max, widest = tb.L - stages + 2 + kTail, nearly = (tb.L + 1) - (tb.L + 1) / 40;
+    while (n_units < units / 14 && held(n_units) < (widest < nearly ? widest : nearly)) ++n_units;
     const int per_cu = units / n_units < 24 ? int(units / n_units) : 24;
     const int entries = held(n_units) < row_len ? held(n_units) : row_len;
     int n_waves = per_cu * n_cu;

@@ -193,6 +193,22 @@ def test_h1f1b_rows_about_as_long_as_a_share(harp, ctx, L):
     assert (want.status == oracle.OK).any()
 
 
+@pytest.mark.parametrize("L", [191, 192, 208, 209, 246, 247, 278, 279, 331, 332])
+def test_h1f1b_rows_about_as_long_as_the_widest_slot(harp, ctx, L):
+    """A stage or two on each of 16 groups: shares of LDS that just hold the widest slot of a candidate, or a cut less."""
+    rng = np.random.default_rng(L)
+    G, T = 16, 2
+    fwd = rng.integers(1, 3000, size=(T, L))
+    p = simple_problem(np.zeros(L), M=12, T=T, G=G, ndev=[4] * G, tp=(1, 2), fwd=fwd, bwd=fwd,
+                       params=rng.integers(1, 10**6, size=L), stash=rng.integers(0, 10**4, size=L),
+                       act=rng.integers(0, 10**6, size=L), gtype=[g % 2 for g in range(G)], mem=[1 << 50, 1 << 50],
+                       bw=np.full((G, G), 3000))
+    cands = W.make_candidates(p, 0, 281, G, 20, 0, 12)
+    caps, _ = _caps_from_min_max(p, cands, 9, 8)
+    got, want, _ = _check(harp, ctx, p, cands, caps, "L %d" % L)
+    assert (want.status == oracle.OK).any()
+
+
 def test_h1f1b_counts_decide_feasibility(harp, ctx):
     # three one-operator stages, stash 10 each, slow link then fast link: counts 5, 2, 1
     for mem, st in ((50, oracle.OK), (49, oracle.INFEASIBLE)):
