@@ -298,7 +298,7 @@ __global__ __launch_bounds__(kMeshMaxThreads) void k2_mesh_h1f1b(TablesDev tb, O
 // Bound by latency where rows are short - stages one after the other, a barrier or two each, serial parts on a wavefront
 // or two (chains, plan recovery) - and by vector issue where they are long, which few orderings have and all wait for.
 // Measured against the whole-table form on 32-bit rows it replaces: 4,096 orderings of 82 operators and 64 devices 3.57 ->
-// 0.67-0.80 ms (of an ordering's 128 us 44% the value pass, 24% the chains, 13% the reach tables, 13% plan and score); exact
+// 0.58-0.80 ms (of an ordering's 128 us 44% the value pass, 24% the chains, 13% the reach tables, 13% plan and score); exact
 // form, 256 orderings of 160 operators and 128 devices, 15-19 -> 2.2-3.1 ms (of an ordering's 1.1 ms 54% the least-sum
 // passes, 16% the min-max pass, 10% the chains, 15% plans and scores; the longest takes twice that).  Tried in vain: five
 // workgroups of 256 threads on a CU (680 -> 705 us), a cell requested while the one before it is worked (exact form 10% slower).
